@@ -124,10 +124,10 @@ int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M,
 
 /* Pins the GEMM kernel variant that quota_w4a4_gemm and the layer calls use
  * from now on (process-wide; for tests and tuning): -1 = chosen per launch
- * (default); 0..4 = the workgroup-tiled kernels 64x256, 64x128, 32x128,
- * 32x128 deep prefetch, 64x128 lean.  Launches a variant cannot take (at
- * most 16 rows, the int32 output, the 256-column tile with the fused QKV
- * epilogue) ignore the pin.  QUOTA_ERR_INVALID_ARG for other values. */
+ * (default); 0..4 = the workgroup tiles (rows x columns) 64x256, 64x128,
+ * 32x128, 32x64, 128x256.  Launches a variant cannot take (at most 16 rows,
+ * the int32 output, tiles that would straddle q | k | v or cut a head with the
+ * fused QKV epilogue) ignore the pin.  QUOTA_ERR_INVALID_ARG for other values. */
 int quota_set_gemm_variant(int variant);
 
 /* ---- RoPE + 4-bit KV quantization (quantized KV cache) ------------------ */
@@ -487,7 +487,7 @@ int quota_decode_layer(const quota_layer *L, const void *x_f16,
  * because each shape is a separate kernel (and a separate profiler row). */
 enum {
     QUOTA_K_QUANTIZE_ACT = 0, QUOTA_K_RMSNORM_QUANTIZE_ACT, QUOTA_K_SILU_MUL_QUANTIZE_ACT,
-    QUOTA_K_GEMM_64X256, QUOTA_K_GEMM_64X128, QUOTA_K_GEMM_32X128, QUOTA_K_GEMM_32X128_DEEP, QUOTA_K_GEMM_64X128_LEAN,
+    QUOTA_K_GEMM_64X256, QUOTA_K_GEMM_64X128, QUOTA_K_GEMM_32X128, QUOTA_K_GEMM_32X64, QUOTA_K_GEMM_128X256,
     QUOTA_K_GEMM_OTHER, QUOTA_K_ROPE_KV_QUANT,
     QUOTA_K_KV_QUANT_APPEND, QUOTA_K_ATTENTION_FWD, QUOTA_K_ATTENTION_COLMASS,
     QUOTA_K_SCORE_TOKENS, QUOTA_K_TOPK_PRUNE, QUOTA_K_COMPACT_ROWS, QUOTA_K_QUANTIZE_WEIGHTS,

@@ -1,25 +1,22 @@
-// W4A4 GEMM for gfx950: int4 codes are unpacked to int8 and contracted with
-// v_mfma_i32_32x32x32_i8; the per-group weight scales are applied in fp32
-// inside the K loop (one convert + one fma per output element and group).
+// W4A4 GEMM for gfx950 on the fp8 matrix cores: y = (int4 activations) x (int4 weights)^T with an
+// fp32 scale per 128-channel weight group.
 //
-// Unpack trick: a nibble placed in the HIGH half of a byte is the int8 value
-// 16*code (two's complement carries the sign), so "(w << 4) & 0xF0F0F0F0" and
-// "w & 0xF0F0F0F0" turn one packed dword into two dwords of int8 without any
-// sign-extension arithmetic.  Both operands are shifted, every group
-// accumulator is therefore exactly 256x the true integer dot product; the
-// factor 2^-8 is folded into the token scale (exact in fp32).
+// Small integers are exact in fp8 (e4m3), and the fp32 accumulator of v_mfma_f32_16x16x128_f8f6f4 is
+// exact for sums below 2^24 units, so one such instruction returns the exact integer dot product of a
+// whole 128-deep group -- already as a float.  That halves the scale chain against an int8 contraction
+// (one fma per element and group instead of a convert and an fma) and that chain is what bounds the
+// kernel: every element needs y = fma(acc_g, s_g, y) group after group.
 //
-// Data flow per 128-deep group:
-//   activations: global (packed) -> registers -> unpack -> LDS (int8, shared by
-//                the 4 waves) -> MFMA A fragments
-//   weights:     global (packed) -> registers -> unpack -> MFMA B fragments.
-//                The 4 waves of a workgroup own disjoint column ranges, so a
-//                weight is needed by exactly one wave and never touches LDS.
-// The order of k inside a group does not matter for an integer dot product,
-// so both operands just use the same assignment of elements to MFMA k-slots:
-// a 16-byte packed chunk c (32 codes) yields "even" (low nibbles) and "odd"
-// (high nibbles) int8 vectors; lane half h of k-step ks takes the even (ks
-// even) or odd (ks odd) vector of chunk 2*h + ks/2.
+// Weights: a nibble c + 8 in 0..15 placed in the low half of a byte IS the e4m3 number (c + 8) / 512
+// (the subnormals and the first binade of e4m3 are one linear range), so the unpack stays at 3 vector
+// instructions per 8 codes: lo = (w & 0x0f..) ^ 0x08.., hi = (w >> 4 & 0x0f..) ^ 0x08...
+// Activations are signed e4m3 numbers a / 512.  The weights' offset of 8 comes back out through the
+// accumulator's start value: acc = corr + sum (a / 512) (c + 8) / 512 with corr = -8 / 2^18 * sum of the
+// group's activation codes, one number per (row, group).  The 2^18 goes into the token scale (exact).
+//
+// Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes [M][128 G], every 8
+// codes stored as evens then odds (the order the weight unpack produces), plus corr [ceil(G / 4)][M][4].  The public
+// entry point takes packed int4 rows and converts them while staging (PACKED).
 #include "common.h"
 #include "internal.h"
 #include "ropequant.h"
@@ -27,300 +24,324 @@
 
 namespace {
 
-constexpr int AROW = 9;     // LDS row stride in 16-byte units: 8 data + 1 pad (conflict-free b128)
+// Lane l of a wave owns row (A) or column (B) l % 16 and the 32 channels number l / 16 of the group for
+// both operands, so the order of channels inside a group cancels; it receives column l % 16, rows
+// 4 (l / 16) .. + 3 of the 16 x 16 result.
 
-// Workgroup tile (32*TM) x (128*TN); wave w owns columns [w*32*TN, (w+1)*32*TN).
-// CH > 0: the LDS stage holds CH groups of activations, so the workgroup meets at a
-// barrier once per CH groups instead of once per group (DEPTH must be a multiple of CH).
-template <int TM, int TN, int DEPTH, int CH, bool PIPE, bool ACC_OUT, bool QKV, int WPE>
-__global__ __launch_bounds__(256, WPE) void w4a4_gemm_kernel(
-    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
-    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
+// 16 (4) bytes per lane from global memory to LDS, lane l at lds + 16 l (4 l), without passing registers.
+// In assembly because the compiler, which cannot tell the LDS buffers apart, would make every LDS read
+// wait for the copies just started; the kernel waits for them itself (drain) before the barrier that
+// hands the buffer over.
+__device__ __forceinline__ void copy16_to_lds(const void *base, unsigned off, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void copy4_to_lds(const void *addr, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(addr) : "memory");
+}
+// All of this wave's loads and copies have arrived.  In assembly, because the compiler drops a wait that
+// it thinks has nothing to wait for; the builtin as well, so that it knows its own loads have arrived.
+__device__ __forceinline__ void drain()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+}
+
+// Workgroup tile (16 RT) x (16 CT NW): NW waves side by side, each with all rows and its own 16 CT
+// columns, so a weight is read and unpacked by exactly one wave and never touches LDS, while activations,
+// corr and group scales are staged in LDS.
+// The K loop runs in stages of CH groups: during a stage everything of the next one is set off -- weights into
+// registers, the rest into the other LDS buffer -- and a stage ends with one wait for all of it and one
+// barrier; nothing in between waits for memory.
+//   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
+//   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
+//   one-group stages of the 128-row tile and the 32-row tiles have no time to spare and lose by it).
+//   PIPE: weights of group g+1 are unpacked between the MFMAs of group g (twice the fragment registers).
+// LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that the 8 lanes of one LDS
+// cycle (8 rows, same piece) cover all banks.
+template <int RT, int CT, int NW, int CH, int SP, bool PIPE, bool PACKED, bool ACC_OUT, bool QKV, int OCC>
+__global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
+    const uint8_t *__restrict__ qa, const float *__restrict__ corr, const float *__restrict__ sa, int M, int K,
+    int G, const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
     const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n,
     int vec_store, quota_qkv_epilogue qe)
 {
-    constexpr int BM = 32 * TM, WN = 32 * TN, BN = 4 * WN;
-    constexpr int LA = (BM * 4 + 255) / 256;         // 16-byte activation loads per thread per group
-    constexpr int CROW = WN + 8;                     // halves per staged output row (16-byte pad)
-    constexpr int ASTAGE = BM * AROW + 2;            // uint4 per group of activations in LDS (+ spare slot)
-    constexpr bool CHUNK = CH > 0;
-    constexpr int CHN = CHUNK ? CH : 1;
-    static_assert(DEPTH % CHN == 0, "DEPTH must be a multiple of CH");
-    constexpr int TROW = BN + 8;                     // halves per row of the workgroup-wide QKV tile
-    constexpr int LDS_A = 2 * CHN * ASTAGE, LDS_C = (QKV ? 32 * TROW : 4 * 32 * CROW) / 8;     // in uint4
-    __shared__ uint4 lds_raw[LDS_A > LDS_C ? LDS_A : LDS_C];
+    constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
+    constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : BM * 8 / NT;    // 16-byte pieces per thread and group
+    constexpr int KD = (BM + BN / 2 + NT - 1) / NT;                      // corr / scale dwords per thread and group
+    static_assert(RT % 2 == 0 && (PACKED || BM * 8 % NT == 0), "whole rows per copy, fragment double buffer");
+    // one group in LDS: activations, then dwords: BM of corr, BN / 2 of scales, up to whole waves.  PACKED
+    // computes corr and keeps it behind that (+ a spare piece for threads without one)
+    constexpr int AST = BM * 8, KST = KD * NT / 4, CST = PACKED ? AST + KST : AST;          // in uint4
+    constexpr int GST = AST + KST + (PACKED ? BM / 4 + 3 : 0);
+    constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
+    constexpr int LDS_A = 2 * CH * GST, LDS_Q = QKV ? 32 * TROW / 8 : 32 * FROW / 4;
+    __shared__ uint4 lds_raw[LDS_A > LDS_Q ? LDS_A : LDS_Q];
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds_raw;
 
-    const int tile = xcd_remap(blockIdx.x, tiles_m * tiles_n);
-    const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hl = lane >> 5;
-    const int Kb = K >> 1;   // bytes per packed activation row
+    int tile_m, tile_n;
+    tile_of(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tile_m, tile_n);
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // Global loads are unconditional with clamped addresses (no branches in the
-    // main loop): rows past M or N repeat the last row and are never stored; a
-    // chunk past the end of a ragged K repeats the last chunk and meets the
-    // zero padding of the packed weights.  Addresses are a wave-uniform base
-    // that advances with the group plus a loop-invariant 32-bit lane offset.
-    unsigned oa[LA];                // byte offset of this thread's activation chunk in group 0
-    int ca[LA], la[LA];
-    bool a_on[LA];
+    // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
+    // ones and are never stored; groups past G repeat the last one and meet a zero scale.
+    const int Kb = PACKED ? K >> 1 : G * 128;            // bytes per activation row
+    unsigned oa[LA];                                     // byte offset of this thread's piece of group 0
+    int la[LA], pa[LA], lk[LA];                          // PACKED: LDS slots of the piece and of corr
+    // (threads without one write a spare slot: a branch would let the compiler sink the scale chain behind it)
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
-        int i = tid + 256 * j, row = i >> 2, c = i & 3;
-        a_on[j] = row < BM;
-        row = min(row, BM - 1);
-        ca[j] = c * 16;
-        oa[j] = (unsigned)(min(m0 + row, M - 1) - m0) * (unsigned)Kb;
-        la[j] = a_on[j] ? row * AROW + 2 * c : BM * AROW;   // spare slot after the tile
+        const int i = tid + NT * j;
+        const int row = PACKED ? i >> 2 : i >> 3, p = PACKED ? i & 3 : (i & 7) ^ (row & 7);
+        oa[j] = (unsigned)(min(m0 + min(row, BM - 1), M - 1) - m0) * (unsigned)Kb;
+        if (!PACKED) oa[j] += 16 * p;
+        pa[j] = 16 * p;
+        la[j] = row < BM ? row * 8 + ((2 * p) ^ (row & 7)) : (CST + BM / 4 + 1) & ~1;
+        lk[j] = row < BM && p == 0 ? row : BM;
     }
     const uint8_t *abase = qa + (size_t)m0 * Kb;
-    unsigned ow[TN], os[TN];        // uint4 / f16 index of this lane's weight chunk / scale in group 0
-    int ncol[TN];
+    const int nw = min(n0 + wave * WN, N - WN);          // this wave's first column (N is a multiple of 64)
+    const bool n_ok = n0 + wave * WN < N;
+    const unsigned wl = (unsigned)(c16 * 4 + q);         // this lane's uint4 of a 16-column block
+
+    const float *kaddr[KD];                              // this thread's corr / scale dwords of group 0
+    bool k_scale[KD];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        ncol[j] = n0 + wave * WN + 32 * j + l32;
-        int n = min(ncol[j], N - 1);
-        ow[j] = (unsigned)n * 4 + 2 * hl;
-        os[j] = (unsigned)n;
+    for (int k = 0; k < KD; ++k) {
+        const int d = tid + NT * k;
+        k_scale[k] = d >= BM;
+        kaddr[k] = k_scale[k] || PACKED
+                       ? reinterpret_cast<const float *>(sw) + min((n0 >> 1) + max(d - BM, 0), (N >> 1) - 1)
+                       : corr + 4 * (size_t)min(m0 + d, M - 1);
     }
 
-    uint4 ra[CHUNK ? CHN : DEPTH][LA], rw[DEPTH][TN][2];
-    f16 rs[DEPTH][TN];
-    auto load_w = [&](int stage, int g) {
-        g = min(g, G - 1);
-        const uint4 *wg = wp + (size_t)g * N * 4;        // uniform
-        const f16 *sg = sw + (size_t)g * N;              // uniform
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            rw[stage][j][0] = wg[ow[j]];
-            rw[stage][j][1] = wg[ow[j] + 1];
-            rs[stage][j] = sg[os[j]];
+    constexpr int WS = CH > 1 || PIPE ? 2 : 1;           // register sets of packed weights
+    uint4 rw[WS][CH][CT];
+    i32x4 ra[CH][LA];                                    // PACKED staging (struct uint4 here would live in scratch memory)
+    // What a stage needs, load by load: for each of its groups CT weight pieces, LA activation pieces, KD
+    // dwords of corr and scales.
+    constexpr int LG = CT + LA + KD, LOADS = CH * LG;
+    auto load = [&](int k, int set, int half, int g0) {
+        const int c = k / LG, r = k % LG, g = min(g0 + c, G - 1);
+        const unsigned dst = lds0 + (unsigned)(half * CH + c) * (GST * 16);
+        if (r < CT) {
+            const uint4 *wg = wp + ((size_t)g * N + nw) * 4;             // uniform
+            rw[set][c][r] = wg[wl + 64 * r];
+        } else if (r < CT + LA) {
+            const int j = r - CT;
+            if constexpr (PACKED) {
+                const unsigned kb = (unsigned)min(g * 64 + pa[j], Kb - 16);
+                ra[c][j] = *reinterpret_cast<const i32x4 *>(abase + (oa[j] + kb));
+            } else {
+                copy16_to_lds(abase + (size_t)g * 128, oa[j], dst + (unsigned)(wave + NW * j) * 1024);
+            }
+        } else {
+            const int j = r - CT - LA;
+            const size_t koff = ((size_t)(g >> 2) * M) * 16 + (g & 3) * 4, soff = (size_t)g * N * 2;
+            copy4_to_lds(reinterpret_cast<const char *>(kaddr[j]) + (k_scale[j] || PACKED ? soff : koff),
+                         dst + AST * 16 + (unsigned)(wave + NW * j) * 256);
         }
     };
-    auto load_a = [&](int stage, int g) {
-        g = min(g, G - 1);
+    auto store_packed = [&](int half) {                  // convert and store what load_rest brought
+        if constexpr (PACKED) {
 #pragma unroll
-        for (int j = 0; j < LA; ++j) {
-            int kb = min(g * 64 + ca[j], Kb - 16);
-            ra[stage][j] = *reinterpret_cast<const uint4 *>(abase + oa[j] + (unsigned)kb);
-        }
-    };
-    auto store_a = [&](int stage, uint4 *dst) {
+            for (int c = 0; c < CH; ++c) {
+                uint4 *dst = lds_raw + (half * CH + c) * GST;
+                float *dk = reinterpret_cast<float *>(dst + CST);
 #pragma unroll
-        for (int j = 0; j < LA; ++j) {
-            uint4 lo, hi;
-            unpack16(ra[stage][j], lo, hi);
-            dst[la[j]] = lo;            // threads without a row write the spare slot
-            dst[la[j] + 1] = hi;
+                for (int j = 0; j < LA; ++j) {
+                    uint4 e0, e1;
+                    int sum;
+                    codes_to_e4m3(make_uint4(ra[c][j][0], ra[c][j][1], ra[c][j][2], ra[c][j][3]), e0, e1, sum);
+                    sum += __builtin_amdgcn_update_dpp(0, sum, 0xB1, 0xf, 0xf, false);     // the 4 pieces of a row
+                    sum += __builtin_amdgcn_update_dpp(0, sum, 0x4E, 0xf, 0xf, false);     // sit in 4 lanes
+                    dst[la[j]] = e0;
+                    dst[la[j] ^ 1] = e1;
+                    dk[lk[j]] = (float)sum * F8_CORR;
+                }
+            }
         }
     };
 
-    constexpr int T = TM * TN;
-    float yacc[TM][TN][16];
-    int tot[ACC_OUT ? TM : 1][ACC_OUT ? TN : 1][16];
+    float yacc[RT][CT][4];
+    int tot[ACC_OUT ? RT : 1][ACC_OUT ? CT : 1][4];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < CT; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < 4; ++r) {
                 yacc[i][j][r] = 0.0f;
                 if (ACC_OUT) tot[i][j][r] = 0;
             }
-    const int fra = l32 * AROW + 4 * hl;       // this lane's A fragment (row l32 of a 32-row block)
+    // dword i (8 codes) of a packed piece
+    auto unpack_w = [&](const uint4 &w4, int i, i32x8 &fb) {
+        const uint32_t w = i == 0 ? w4.x : i == 1 ? w4.y : i == 2 ? w4.z : w4.w;
+        fb[2 * i] = (int)((w & 0x0F0F0F0Fu) ^ 0x08080808u);
+        fb[2 * i + 1] = (int)(((w >> 4) & 0x0F0F0F0Fu) ^ 0x08080808u);
+    };
+    // this lane's activation fragment of row block i with the start values of its four results, and the
+    // scale of its column in block j, of the group at `gp`
+    const int fr = c16 * 8, fx = c16 & 7;
+    auto read_a = [&](const uint4 *gp, int i, i32x8 &fa, f32x4 &k4) {
+        const uint4 a0 = gp[i * 128 + fr + ((2 * q) ^ fx)], a1 = gp[i * 128 + fr + ((2 * q + 1) ^ fx)];
+        fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
+        k4 = *reinterpret_cast<const f32x4 *>(gp + CST + 4 * i + q);
+    };
+    auto read_scale = [&](const uint4 *gp, int g, int j) {
+        const f16 s = reinterpret_cast<const f16 *>(gp + AST + BM / 4)[wave * WN + 16 * j + c16];
+        return g < G ? (float)s : 0.0f;
+    };
+    // The group scale of a result is applied LAG results later, so that the matrix core's latency is
+    // covered; the last ones of a group are finished during the next.
+    constexpr int LAG = 2;
+    static_assert(T % LAG == 0, "the carried results keep their order");
+    f32x4 pend[LAG];
+    float pscale[LAG];
+    bool plive = false;
+#pragma unroll
+    for (int i = 0; i < LAG; ++i) { pend[i] = f32x4{0, 0, 0, 0}; pscale[i] = 0.0f; }
+    auto scale_in = [&](int t, const f32x4 &a, float s, bool live) {
+        const int i = t / CT, j = t % CT;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            yacc[i][j][r] = __builtin_fmaf(a[r], s, yacc[i][j][r]);
+            if (ACC_OUT) tot[i][j][r] += live ? (int)(a[r] * F8_UNIT) : 0;
+        }
+    };
 
 #pragma unroll
-    for (int s = 0; s < DEPTH; ++s) load_w(s, s);
-    if (CHUNK) {
-#pragma unroll
-        for (int s = 0; s < CHN; ++s) load_a(s, s);
-#pragma unroll
-        for (int s = 0; s < CHN; ++s) store_a(s, lds_raw + s * ASTAGE);
-    } else {
-#pragma unroll
-        for (int s = 0; s < DEPTH; ++s) load_a(s, s);
-        store_a(0, lds_raw);
-    }
+    for (int k = 0; k < LOADS; ++k) load(k, 0, 0, 0);
+    drain();
+    store_packed(0);
     __syncthreads();
-    int cb = 0;                     // CHUNK: which half of the LDS buffer holds the current groups
 
-    // Software pipeline over the 32x32 sub-tiles, carried across groups: while the
-    // matrix core runs the 4 MFMAs of a sub-tile, the vector ALU applies the group
-    // scale (one convert + one fma per element) to the previous sub-tile -- for the
-    // first sub-tile of a group that is the last sub-tile of the group before.
-    i32x16 pend = i32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};   // sub-tile awaiting its scale
-    float sw_prev = 0.0f;           // scale that goes with the pending sub-tile
-    bool live_prev = false;
-    auto scale_in = [&](int t, const i32x16 &a, float scale, bool live) {
-        const int i = t / TN, j = t % TN;
+    i32x8 fb[PIPE ? 2 : 1][CT];
+    if (PIPE)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            yacc[i][j][r] = __builtin_fmaf((float)a[r], scale, yacc[i][j][r]);
-            if (ACC_OUT) tot[i][j][r] += live ? a[r] : 0;
-        }
-    };
-
-    auto unpack_w = [&](int stage, int g, i32x4 (&fb)[TN][4], float (&swn)[TN]) {
+        for (int j = 0; j < CT; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            swn[j] = (g < G && ncol[j] < N) ? (float)rs[stage][j] : 0.0f;
-            uint4 lo, hi;
-            unpack16(rw[stage][j][0], lo, hi);
-            fb[j][0] = as_i32x4(lo);
-            fb[j][1] = as_i32x4(hi);
-            unpack16(rw[stage][j][1], lo, hi);
-            fb[j][2] = as_i32x4(lo);
-            fb[j][3] = as_i32x4(hi);
-        }
-    };
-    auto read_a = [&](const uint4 *abuf, i32x4 (&fa)[TM][4]) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) fa[i][ks] = as_i32x4(abuf[fra + 32 * i * AROW + ks]);
-    };
-    // MFMAs of group g with the scale of the previous sub-tile interleaved
-    auto mfma_group = [&](const i32x4 (&fa)[TM][4], const i32x4 (&fb)[TN][4], const float (&swn)[TN], int g) {
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int i = t / TN, j = t % TN;
-            i32x16 a = i32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                a = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i][ks], fb[j][ks], a, 0, 0, 0);
-            if (t == 0) scale_in(T - 1, pend, sw_prev, live_prev);
-            else scale_in(t - 1, pend, swn[(t - 1) % TN], g < G);
-            pend = a;
-        }
-        sw_prev = swn[(T - 1) % TN];
-        live_prev = g < G;
-    };
-
-    const int Gpad = (G + DEPTH - 1) / DEPTH * DEPTH;
-    if constexpr (PIPE) {
-        // Group-level software pipeline for the narrow tiles, where little else hides
-        // latency: while the MFMAs of group g run, the weights of group g+1 are unpacked and
-        // its activation fragments are already on their way from LDS.  Scheduling barriers
-        // pin the phases of an iteration; without them the fragment reads sink next to their
-        // first use and every MFMA waits on LDS.
-        static_assert(CHUNK && DEPTH % 2 == 0, "PIPE needs chunked staging and an even DEPTH");
-        i32x4 fbp[2][TN][4], fap[2][TM][4];
-        float swp[2][TN];
-        unpack_w(0, 0, fbp[0], swp[0]);
-        read_a(lds_raw, fap[0]);
+            for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[0][j]);
+    constexpr int SU = PIPE && CH % 2 ? 2 : WS;          // stages per loop body (parities are compile-time)
+    const int stages = (G + CH - 1) / CH;
+    i32x8 fa[2];
+    f32x4 k4[2];
 #pragma unroll 1
-        for (int g0 = 0; g0 < Gpad; g0 += DEPTH) {
+    for (int st0 = 0; st0 < stages; st0 += SU) {
 #pragma unroll
-            for (int s = 0; s < DEPTH; ++s) {
-                const int g = g0 + s, cur = s & 1, nxt = cur ^ 1, s1 = (s + 1) % DEPTH;
-                const bool chunk_end = s % CHN == CHN - 1;
-                if (s % CHN == 0) {             // activations of the next CH groups -> registers
+        for (int su = 0; su < SU; ++su) {
+            const int g0 = (st0 + su) * CH, half = SU == 2 ? su : st0 & 1, set = su % WS;
+            const uint4 *gp = lds_raw + half * CH * GST;
+            read_a(gp, 0, fa[0], k4[0]);
+            if (!PIPE && CH == 1) {
 #pragma unroll
-                    for (int c = 0; c < CHN; ++c) load_a(c, g + CHN + c);
+                for (int j = 0; j < CT; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[0][j]);
+            }
+#pragma unroll
+            for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1, g0 + CH);
+#pragma unroll
+            for (int c = 0; c < CH; ++c, gp += GST) {
+                const int g = g0 + c, cur = PIPE ? (su * CH + c) & 1 : 0;
+                float sc[CT];
+#pragma unroll
+                for (int j = 0; j < CT; ++j) sc[j] = read_scale(gp, g, j);
+                if (!PIPE && CH > 1) {
+#pragma unroll
+                    for (int j = 0; j < CT; ++j)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) unpack_w(rw[set][c][j], i, fb[0][j]);
                 }
-                load_w(s, g + DEPTH);           // stage s was unpacked during the previous group
-                if (!chunk_end) read_a(lds_raw + (cb * CHN + s % CHN + 1) * ASTAGE, fap[nxt]);
-                __builtin_amdgcn_sched_barrier(0);
-                mfma_group(fap[cur], fbp[cur], swp[cur], g);
-                unpack_w(s1, g + 1, fbp[nxt], swp[nxt]);
+                // The issue order is pinned result by result (left alone the scheduler puts the scale chain
+                // of a result right behind its own MFMA and waits out the matrix core's latency, and reads
+                // every row block's fragments up front, which does not fit the registers): one MFMA, the
+                // chain of the result LAG places back, a share of the next group's unpacking (PIPE).  The
+                // next row block's fragments are read at the start of a row block.
 #pragma unroll
-                for (int q = 0; q < 4 * T; ++q) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, (ACC_OUT ? 12 : 8) + 6 / TM, 0);
+                for (int i = 0; i < RT; ++i) {
+                    if (i + 1 < RT) read_a(gp, i + 1, fa[(i + 1) & 1], k4[(i + 1) & 1]);
+                    else if (c + 1 < CH) read_a(gp + GST, 0, fa[0], k4[0]);
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        const int t = i * CT + j;
+                        const f32x4 a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 1], fb[cur][j], k4[i & 1], 0, 0, 0, 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (t < LAG) scale_in(T - LAG + t, pend[t], pscale[t], plive);
+                        else scale_in(t - LAG, pend[t % LAG], sc[(t - LAG) % CT], g < G);
+                        pend[t % LAG] = a;
+#pragma unroll
+                        for (int k = 0; k < (SP ? LOADS : 0); ++k)
+                            if (k * (CH * T * SP / 8) / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1, g0 + CH);
+                        if (PIPE && c + 1 < CH) {
+#pragma unroll
+                            for (int u = t * 4 * CT / T; u < (t + 1) * 4 * CT / T; ++u)
+                                unpack_w(rw[set][c + 1][u / 4], u % 4, fb[cur ^ 1][u / 4]);
+                        }
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if (chunk_end) {                // next CH groups of activations -> the other half
 #pragma unroll
-                    for (int c = 0; c < CHN; ++c) store_a(c, lds_raw + ((cb ^ 1) * CHN + c) * ASTAGE);
-                    __syncthreads();
-                    cb ^= 1;
-                    read_a(lds_raw + cb * CHN * ASTAGE, fap[nxt]);
-                }
+                for (int i = 0; i < LAG; ++i) pscale[i] = sc[(T - LAG + i) % CT];
+                plive = g < G;
             }
-        }
-    } else {
-#pragma unroll 1
-    for (int g0 = 0; g0 < Gpad; g0 += DEPTH) {
+            drain();
+            store_packed(half ^ 1);
+            __syncthreads();
+            if (PIPE)
 #pragma unroll
-        for (int s = 0; s < DEPTH; ++s) {
-            const int g = g0 + s;
-            if (CHUNK && s % CHN == 0) {        // activations of the next CH groups -> registers
+                for (int j = 0; j < CT; ++j)
 #pragma unroll
-                for (int c = 0; c < CHN; ++c) load_a(c, g + CHN + c);
-            }
-            const uint4 *abuf = lds_raw + (CHUNK ? (cb * CHN + s % CHN) : (g & 1)) * ASTAGE;
-            // activation fragments of group g from LDS, weights of group g from registers
-            i32x4 fa[TM][4], fb[TN][4];
-            float swn[TN];
-            read_a(abuf, fa);
-            unpack_w(s, g, fb, swn);
-            // the stage that held group g is free again: prefetch group g + DEPTH into it
-            // (its activation registers were stored to LDS one iteration ago)
-            load_w(s, g + DEPTH);
-            if (!CHUNK) load_a(s, g + DEPTH);
-            mfma_group(fa, fb, swn, g);
-            // issue order hint: 1 MFMA : 8 VALU
-#pragma unroll
-            for (int q = 0; q < 4 * T; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, ACC_OUT ? 12 : 8, 0);
-            }
-            if (!CHUNK) {           // activations of group g+1 -> the other LDS buffer
-                store_a((s + 1) % DEPTH, lds_raw + ((g & 1) ^ 1) * ASTAGE);
-                __syncthreads();
-            }
-            if (CHUNK && s % CHN == CHN - 1) {  // activations of the next CH groups -> the other half
-#pragma unroll
-                for (int c = 0; c < CHN; ++c) store_a(c, lds_raw + ((cb ^ 1) * CHN + c) * ASTAGE);
-                __syncthreads();
-                cb ^= 1;
-            }
+                    for (int i = 0; i < 4; ++i) unpack_w(rw[(set + 1) % WS][0][j], i, fb[((su + 1) * CH) & 1][j]);
         }
     }
-    }
-    scale_in(T - 1, pend, sw_prev, live_prev);
+#pragma unroll
+    for (int i = 0; i < LAG; ++i) scale_in(T - LAG + i, pend[i], pscale[i], plive);
 
-    // epilogue: token scale (with the 2^-8 of the shifted operands), residual, fp16.
-    // With an aligned output the fp16 tile goes through LDS (the activation buffers
-    // are free after the last barrier) so that every lane stores 16 contiguous bytes.
+    // epilogue: token scale (with the 2^18 of the operands' e4m3 units), residual, fp16
     if constexpr (QKV) {
-        // Fused epilogue of the QKV projection: the fp16 tile (whole heads: the tile width
-        // divides the model width and is a multiple of the head size) is staged in LDS by all
-        // four waves; then every thread takes (row, 8-channel chunk) items and applies RoPE at
-        // the token's position id (q and k tiles) and the 4-bit K/V group quantizer (k and v
-        // tiles) exactly as the stand-alone kernel does.  q | k | v are column ranges
-        // [0,d) [d,d+dkv) [d+dkv,d+2dkv), so a tile lies in one of them.
-        f16 *tile = reinterpret_cast<f16 *>(lds_raw);
+        // Fused epilogue of the QKV projection: 32 rows of the fp16 tile (whole heads: the tile width divides
+        // the model width and is a multiple of the head size) at a time are staged in LDS by all waves; then
+        // every thread takes (row, 8-channel chunk) items and applies RoPE at the token's position id (q
+        // and k tiles) and the 4-bit K/V group quantizer (k and v tiles) exactly as the stand-alone kernel
+        // does.  q | k | v are column ranges [0,d) [d,d+dkv) [d+dkv,d+2dkv), so a tile lies in one of them.
+        f16 *stage = reinterpret_cast<f16 *>(lds_raw);
         const int d = qe.d, dkv = qe.dkv;
         const int region = n0 < d ? 0 : (n0 < d + dkv ? 1 : 2);          // tile-uniform
         const int c0 = n0 - (region == 0 ? 0 : (region == 1 ? d : d + dkv));
         const int CPH = qe.dh >> 3, HALF = CPH >> 1, cpr = dkv >> 3, gpr = dkv >> 6;
         const int row_step = qe.row_step ? min(max(*qe.row_step, 0), qe.max_steps - 1) : 0;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            if (i) __syncthreads();                   // the previous row block has been read
+        for (int ib = 0; ib < RT / 2; ++ib) {
+            if (ib) __syncthreads();                  // the previous 32 rows have been read
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = 8 * (r >> 2) + 4 * hl + (r & 3);
-                const int m = m0 + 32 * i + row;
-                const float sam = sa[m < M ? m : M - 1] * 0.00390625f;
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    tile[row * TROW + wave * WN + 32 * j + l32] = to_f16(yacc[i][j][r] * sam);
-            }
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * h + 4 * q + r, m = m0 + 32 * ib + row;
+                    const float sam = sa[m < M ? m : M - 1] * F8_UNIT;
+                    f16 *p = stage + row * TROW + wave * WN + c16;
+#pragma unroll
+                    for (int j = 0; j < CT; ++j) p[16 * j] = to_f16(yacc[2 * ib + h][j][r] * sam);
+                }
             __syncthreads();
 #pragma unroll
-            for (int q = 0; q < 32 * (BN / 8) / 256; ++q) {
-                const int idx = q * 256 + tid, row = idx / (BN / 8), c = idx % (BN / 8);
-                const int m = m0 + 32 * i + row;
+            for (int k = 0; k < 32 * (BN / 8) / NT; ++k) {
+                const int idx = k * NT + tid, row = idx / (BN / 8), c = idx % (BN / 8);
+                const int m = m0 + 32 * ib + row;
                 const bool m_ok = m < M;
                 const int mm = m_ok ? m : M - 1;
                 Pack16 x, xp, out;
-                x.u = *reinterpret_cast<const uint4 *>(tile + row * TROW + 8 * c);
+                x.u = *reinterpret_cast<const uint4 *>(stage + row * TROW + 8 * c);
                 if (y && m_ok) *reinterpret_cast<uint4 *>(y + (size_t)m * ldy + n0 + 8 * c) = x.u;
                 const int col = c0 + 8 * c;           // first channel of the chunk inside q, k or v
                 if (region < 2) {
                     const int cc = c % CPH;
-                    xp.u = *reinterpret_cast<const uint4 *>(tile + row * TROW + 8 * (c ^ HALF));
+                    xp.u = *reinterpret_cast<const uint4 *>(stage + row * TROW + 8 * (c ^ HALF));
                     const int pr = min(max(qe.pos[mm], 0), qe.n_pos - 1);
                     const float *cp = qe.cosT + (size_t)pr * (qe.dh >> 1) + 8 * (cc % HALF);
                     const float *sp = qe.sinT + (size_t)pr * (qe.dh >> 1) + 8 * (cc % HALF);
@@ -340,8 +361,8 @@ __global__ __launch_bounds__(256, WPE) void w4a4_gemm_kernel(
 #pragma unroll
                     for (int e = 0; e < 8; ++e) f[e] = (float)out.h[e];
                     Pack16 hat;
-                    f16 sc;
-                    const uint32_t word = kv_quant8(f, &sc, &hat);     // all 8 lanes of a group take part
+                    f16 sc8;
+                    const uint32_t word = kv_quant8(f, &sc8, &hat);    // all 8 lanes of a group take part
                     if (m_ok) {
                         f16 *xh = region == 1 ? qe.khat : qe.vhat;
                         uint32_t *codes = region == 1 ? qe.k_codes : qe.v_codes;
@@ -349,44 +370,59 @@ __global__ __launch_bounds__(256, WPE) void w4a4_gemm_kernel(
                         *reinterpret_cast<uint4 *>(xh + (size_t)m * dkv + col) = hat.u;
                         const size_t orow = (size_t)m * qe.code_row_stride + qe.code_row_offset + row_step;
                         codes[orow * cpr + (col >> 3)] = word;
-                        if ((c & 7) == 0) scales[orow * gpr + (col >> 6)] = sc;
+                        if ((c & 7) == 0) scales[orow * gpr + (col >> 6)] = sc8;
                     }
                 }
             }
         }
         return;
     }
-    f16 *cw = reinterpret_cast<f16 *>(lds_raw) + wave * 32 * CROW;
+    // 32 rows at a time through LDS as fp32, so that a thread finishes 8 neighbouring columns of a row: one
+    // 16-byte residual load, one 16-byte store
+    float *stage = reinterpret_cast<float *>(lds_raw);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int ib = 0; ib < RT / 2; ++ib) {
+        if (ib) __syncthreads();                      // the previous 32 rows have been read
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = 8 * (r >> 2) + 4 * hl + (r & 3);
-            const int m = m0 + 32 * i + row;
-            const bool m_ok = m < M;
-            const float sam = sa[m_ok ? m : M - 1] * 0.00390625f;
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = ncol[j];
-                const bool ok = m_ok && n < N;
-                float v = yacc[i][j][r] * sam;
-                if (res && ok) v = v + (float)res[(size_t)m * ldr + n];
-                const f16 h = to_f16(v);
-                if (vec_store) cw[row * CROW + 32 * j + l32] = h;
-                else if (y && ok) y[(size_t)m * ldy + n] = h;
-                if (ACC_OUT && ok) acc_out[(size_t)m * N + n] = tot[i][j][r] >> 8;
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * h + 4 * q + r, m = m0 + 32 * ib + row;
+                const float sam = sa[m < M ? m : M - 1] * F8_UNIT;
+                float *p = stage + row * FROW + wave * WN + c16;
+#pragma unroll
+                for (int j = 0; j < CT; ++j) {
+                    p[16 * j] = yacc[2 * ib + h][j][r] * sam;
+                    if (ACC_OUT && m < M && n_ok) acc_out[(size_t)m * N + nw + 16 * j + c16] = tot[2 * ib + h][j][r];
+                }
             }
-        }
-        if (vec_store) {
-            __syncthreads();                      // staged tile visible (also fences the type-punned LDS accesses)
+        __syncthreads();
 #pragma unroll
-            for (int q = 0; q < 32 * (WN / 8) / 64; ++q) {
-                const int idx = q * 64 + lane, row = idx / (WN / 8), ch = idx % (WN / 8);
-                const int m = m0 + 32 * i + row, n = n0 + wave * WN + 8 * ch;
-                const uint4 v = *reinterpret_cast<const uint4 *>(cw + row * CROW + 8 * ch);
-                if (m < M && n < N) *reinterpret_cast<uint4 *>(y + (size_t)m * ldy + n) = v;
+        for (int k = 0; k < 32 * (BN / 8) / NT; ++k) {
+            const int idx = k * NT + tid, row = idx / (BN / 8), n = n0 + 8 * (idx % (BN / 8));
+            const int m = m0 + 32 * ib + row;
+            const float4 *p = reinterpret_cast<const float4 *>(stage + row * FROW + 8 * (idx % (BN / 8)));
+            const float4 lo = p[0], hi = p[1];
+            float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            if (!y || m >= M || n >= N) continue;
+            Pack16 o;
+            if (res) {
+                const f16 *rp = res + (size_t)m * ldr + n;
+                Pack16 rv;
+                if (vec_store & 2) rv.u = *reinterpret_cast<const uint4 *>(rp);
+                else
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) rv.h[e] = rp[e];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv.h[e];
             }
-            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o.h[e] = to_f16(v[e]);
+            f16 *yp = y + (size_t)m * ldy + n;
+            if (vec_store & 1) *reinterpret_cast<uint4 *>(yp) = o.u;
+            else
+#pragma unroll
+                for (int e = 0; e < 8; ++e) yp[e] = o.h[e];
         }
     }
 }
@@ -506,39 +542,88 @@ int launch_gemv16(const uint8_t *qa, const float *sa, int M, const quota_weights
     return QUOTA_OK;
 }
 
-template <int TM, int TN, int DEPTH, int CH, bool PIPE, bool ACC_OUT, bool QKV = false, int WPE = 1>
-int launch(int kernel_id, const uint8_t *qa, const float *sa, int M, const quota_weights *W, f16 *y,
-           int ldy, const f16 *res, int ldr, int32_t *acc, hipStream_t st,
-           const quota_qkv_epilogue *qe = nullptr)
+// Tile instantiations; the number is what quota_set_gemm_variant pins.
+//                                            RT CT NW CH SP PIPE          OCC
+#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, false, P, A, QK, 2>  // 64 x 256
+#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, false, P, A, QK, 2>  // 64 x 128
+#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, false, P, A, QK, 2>  // 32 x 128
+#define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, false, P, A, QK, 2>  // 32 x 64
+#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 0, false, P, A, QK, 2>  // 128 x 256
+
+struct TileShape { int bm, bn, nt, kernel_id; };
+const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128, QUOTA_K_GEMM_64X128},
+                             {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
+                             {128, 256, 256, QUOTA_K_GEMM_128X256}};
+
+typedef void (*f8_kernel)(const uint8_t *, const float *, const float *, int, int, int, const uint4 *, const f16 *,
+                          int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
+
+template <bool P, bool QK>
+f8_kernel tile_kernel(int v)
 {
-    constexpr int BM = 32 * TM, BN = 128 * TN;
-    int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    int tiles_m = (M + BM - 1) / BM, tiles_n = (W->N + BN - 1) / BN;
+    switch (v) {
+    case 0: return F8_TILE_0(P, false, QK);
+    case 1: return F8_TILE_1(P, false, QK);
+    case 2: return F8_TILE_2(P, false, QK);
+    case 3: return F8_TILE_3(P, false, QK);
+    default: return F8_TILE_4(P, false, QK);
+    }
+}
+
+int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const float *corr, const float *sa, int M,
+              const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int32_t *acc, hipStream_t st,
+              const quota_qkv_epilogue *qe = nullptr)
+{
+    const TileShape &t = kTiles[v];
+    const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
+    const int tiles_m = (M + t.bm - 1) / t.bm, tiles_n = (W->N + t.bn - 1) / t.bn;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(kernel_id, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md +
-                       (QKV ? Md * (Nd / 3) * (7 + 1.0 / 16) + 4 * Md : 2.0 * Md * Nd * (res ? 2 : 1)), st);
+                       (qe ? Md * (Nd / 3) * (7 + 1.0 / 16) + 4 * Md : 2.0 * Md * Nd * (res ? 2 : 1)), st);
     static const quota_qkv_epilogue no_qe = {};
-    w4a4_gemm_kernel<TM, TN, DEPTH, CH, PIPE, ACC_OUT, QKV, WPE><<<dim3(tiles_m * tiles_n), dim3(256), 0, st>>>(
-        qa, sa, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr,
-        acc, tiles_m, tiles_n, (y && ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0) ? 1 : 0,
-        qe ? *qe : no_qe);
+    auto aligned = [](const void *p, int ld) { return ld % 8 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+    const int vec = (y && aligned(y, ldy) ? 1 : 0) | (res && aligned(res, ldr) ? 2 : 0);
+    kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>(qa, corr, sa, M, W->K, G, (const uint4 *)W->packed,
+                                                           (const f16 *)W->scales, W->N, y, ldy, res, ldr, acc, tiles_m,
+                                                           tiles_n, vec, qe ? *qe : no_qe);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
 
-}  // namespace
+int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
 
-// Tile choice by a small cost model fitted to measured kernel times on this GPU (us).
-// W workgroups run R at a time per CU on 256 CUs; a launch that fits (W <= 256 R) costs
-// c0 + G * u[workgroups per CU - 1], a larger one c0 + G * u[R-1] * (f0 + f1 * W / (256 R)).
-// Wide tiles reuse each unpacked weight for 64 rows but need full rounds; the 32-row tiles
-// spread small problems over more waves; the deep variant prefetches weights 8 groups
-// ahead for launches of at most one workgroup per CU; the lean 64x128 variant (no group
-// pipeline, registers capped so that three workgroups fit on a CU) takes the launches that
-// would need a second round of the pipelined one.  `allow_wide` = false leaves the
-// 256-column tile out.
-static int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
+// Tile choice by a cost model fitted to measured kernel times on this GPU (us).  With x workgroups per CU a
+// group of the K loop takes u[ceil(x) - 1] for x <= 4 and slope * x beyond; c0 is the prologue and epilogue.
+// Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
+// tiles spread small problems over more waves.  Columns of a tile lie in [min_bn, max_bn] (the QKV
+// epilogue needs whole heads that stay inside q, k or v).
+int choose_tile(int M, int N, int K, int min_bn, int max_bn)
+{
+    struct Cost { float c0, u[4], slope; };
+    static const Cost cost[5] = {
+        {3.0f, {0.80f, 1.12f, 1.65f, 2.15f}, 0.56f},
+        {3.0f, {0.58f, 0.95f, 1.03f, 1.08f}, 0.30f},
+        {2.5f, {0.31f, 0.48f, 0.76f, 0.96f}, 0.235f},
+        {2.0f, {0.25f, 0.345f, 0.46f, 0.66f}, 0.165f},
+        {5.0f, {1.20f, 1.90f, 2.90f, 3.90f}, 0.97f},
+    };
+    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn; };
+    if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
+    const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
+    int best = -1;
+    float best_t = 0.0f;
+    for (int v = 0; v < 5; ++v) {
+        if (!fits(v)) continue;
+        const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn);
+        const float x = (float)wgs / 256.0f;
+        const float t = cost[v].c0 + G * (x <= 4.0f ? cost[v].u[(wgs + 255) / 256 - 1] : cost[v].slope * x);
+        if (best < 0 || t < best_t) { best = v; best_t = t; }
+    }
+    return best;
+}
+
+}  // namespace
 
 extern "C" int quota_set_gemm_variant(int variant)
 {
@@ -547,31 +632,16 @@ extern "C" int quota_set_gemm_variant(int variant)
     return QUOTA_OK;
 }
 
-static int choose_tile(int M, int N, int K, bool allow_wide)
+// GEMM on activations in the internal A8 format (M > 16 rows of a layer).
+int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *corr, const float *sa, int M, const quota_weights *W,
+                                void *y_f16, int ldy, const void *residual_opt, int ldr, hipStream_t st)
 {
-    struct Tile { int bm, bn, R; float c0, u[3], f0, f1; };
-    static const Tile tiles[5] = {
-        {64, 256, 2, 13.0f, {0.69f, 1.34f, 0.0f}, 0.0f, 1.22f},     // <2,2,3,0>
-        {64, 128, 2, 6.0f, {0.39f, 0.69f, 0.0f}, 0.0f, 1.27f},      // <2,1,4,2> pipelined
-        {32, 128, 3, 0.5f, {0.39f, 0.61f, 0.82f}, 0.35f, 0.92f},    // <1,1,4,2> pipelined
-        {32, 128, 2, 4.0f, {0.27f, 0.46f, 0.0f}, 0.0f, 1.45f},      // <1,1,8,4> pipelined, deep prefetch
-        {64, 128, 3, 6.0f, {0.53f, 0.75f, 1.06f}, 0.0f, 1.3f},      // <2,1,3,0>, three workgroups per CU
-    };
-    if (g_gemm_variant >= (allow_wide ? 0 : 1) && g_gemm_variant < 5) return g_gemm_variant;
-    const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    int best = -1;
-    float best_t = 0.0f;
-    for (int i = allow_wide ? 0 : 1; i < 5; ++i) {
-        const Tile &t = tiles[i];
-        const long wgs = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        const float x = (float)wgs / (256.0f * t.R);
-        // a launch that spills into a second round pays for most of that round (measured: >= 1.6x)
-        const float over = t.f0 + t.f1 * x;
-        const float est = x <= 1.0f ? t.c0 + G * t.u[(wgs + 255) / 256 - 1]
-                                    : t.c0 + G * t.u[t.R - 1] * (i == 1 && over < 1.6f ? 1.6f : over);
-        if (best < 0 || est < best_t) { best = i; best_t = est; }
-    }
-    return best;
+    if (!qa8 || !corr || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
+    if (W->N % 64 != 0 || W->K % 32 != 0) return QUOTA_ERR_SHAPE;
+    if (M <= 0) return QUOTA_OK;
+    const int v = choose_tile(M, W->N, W->K, 0, 256);
+    return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, corr, sa, M, W, (f16 *)y_f16, ldy,
+                     (const f16 *)residual_opt, ldr, nullptr, st);
 }
 
 extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const quota_weights *W,
@@ -589,23 +659,19 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     f16 *y = (f16 *)y_f16;
     const f16 *res = (const f16 *)residual_opt;
     if (acc_i32_opt)
-        return launch<2, 1, 2, 0, false, true>(QUOTA_K_GEMM_OTHER, qa, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
+        return launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, nullptr, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
     if (M <= 16)            // the decode step: stream the weights once, groups spread over 8 waves
         return W->N <= 8192 ? launch_gemv16<1, 2>(qa, sa, M, W, y, ldy, res, ldr, st)
                             : launch_gemv16<2, 2>(qa, sa, M, W, y, ldy, res, ldr, st);
-    switch (choose_tile(M, W->N, W->K, true)) {
-    case 0: return launch<2, 2, 3, 0, false, false>(QUOTA_K_GEMM_64X256, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
-    case 1: return launch<2, 1, 4, 2, true, false>(QUOTA_K_GEMM_64X128, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
-    case 2: return launch<1, 1, 4, 2, true, false>(QUOTA_K_GEMM_32X128, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
-    case 3: return launch<1, 1, 8, 4, true, false>(QUOTA_K_GEMM_32X128_DEEP, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
-    default: return launch<2, 1, 3, 0, false, false, false, 3>(QUOTA_K_GEMM_64X128_LEAN, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
-    }
+    const int v = choose_tile(M, W->N, W->K, 0, 256);
+    return launch_f8(tile_kernel<true, false>(v), v, kTiles[v].kernel_id, qa, nullptr, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
 // QKV projection with the RoPE + 4-bit K/V quantizer fused into the epilogue (see the kernel).
+// corr: null for packed int4 activations (few rows: the 32-row tile), else qa is in the A8 format.
 // y_opt, when not null, also receives the plain fp16 q | k | v.  Returns QUOTA_ERR_SHAPE when the
 // shape does not fit the fused form (the caller then runs the two kernels separately).
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, const float *corr, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st)
 {
     if (!qa || !sa || !W || !W->packed || !W->scales || !qe || !qe->pos || !qe->cosT || !qe->sinT ||
@@ -617,12 +683,7 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, const float *sa, int M, cons
         W->N != d + 2 * dkv || W->K % 32 != 0)
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
-    f16 *y = (f16 *)y_opt;
-    // (the 256-column tile is left out: with this epilogue it runs at its register limit)
-    switch (choose_tile(M, W->N, W->K, false)) {
-    case 1: return launch<2, 1, 4, 2, true, false, true>(QUOTA_K_GEMM_64X128, qa, sa, M, W, y, W->N, nullptr, 0, nullptr, st, qe);
-    case 2: return launch<1, 1, 4, 2, true, false, true>(QUOTA_K_GEMM_32X128, qa, sa, M, W, y, W->N, nullptr, 0, nullptr, st, qe);
-    case 3: return launch<1, 1, 8, 4, true, false, true>(QUOTA_K_GEMM_32X128_DEEP, qa, sa, M, W, y, W->N, nullptr, 0, nullptr, st, qe);
-    default: return launch<2, 1, 3, 0, false, false, true, 3>(QUOTA_K_GEMM_64X128_LEAN, qa, sa, M, W, y, W->N, nullptr, 0, nullptr, st, qe);
-    }
+    const int v = corr ? choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128) : 2;
+    f8_kernel kernel = corr ? tile_kernel<false, true>(v) : F8_TILE_2(true, false, true);
+    return launch_f8(kernel, v, kTiles[v].kernel_id, qa, corr, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0, nullptr, st, qe);
 }

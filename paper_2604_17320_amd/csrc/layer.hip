@@ -24,8 +24,8 @@ struct Carver {
 };
 
 struct LayerWs {
-    uint8_t *qa;        // packed int4 activations of the current GEMM input
-    float *sa;
+    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format (packed for at most 16 rows)
+    float *corr, *sa;
     f16 *qkv, *q_rot, *khat, *vhat, *o;
     uint8_t *skc, *svc; // staged 4-bit K/V of all rows
     f16 *sks, *svs;
@@ -42,7 +42,8 @@ LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
     LayerWs w;
     size_t M = (size_t)B * N, d = (size_t)H * dh, dkv = (size_t)Hkv * dh;
     size_t kmax = d > (size_t)F ? d : (size_t)F;
-    w.qa = c.take<uint8_t>(M * kmax / 2);
+    w.qa = c.take<uint8_t>(M * quota_a8_row_bytes((int)kmax));
+    w.corr = c.take<float>(M * quota_a8_corr_floats((int)kmax));
     w.sa = c.take<float>(M);
     w.qkv = c.take<f16>(M * (d + 2 * dkv));
     w.q_rot = c.take<f16>(M * d);
@@ -87,11 +88,34 @@ int dump(void *dst, const void *src, size_t bytes, hipStream_t st)
 
 }  // namespace
 
+// At most this many rows take the weight-streaming GEMM, which reads packed int4 activations; more rows
+// use the A8 format end to end.
+#define ROWS_PACKED 16
+
 #define TRY(expr)                         \
     do {                                  \
         int rc_ = (expr);                 \
         if (rc_ != QUOTA_OK) return rc_;  \
     } while (0)
+
+// The four GEMM inputs of a layer: quantize M rows in the format the M-row GEMM reads, then multiply.
+static int rmsnorm_quantize(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps, float *sumsq,
+                            float *ressq, hipStream_t st)
+{
+    if (M <= ROWS_PACKED)
+        return quota_rmsnorm_quantize_act(x, M, d, d, gamma, eps, w.qa, w.sa, sumsq, ressq, nullptr, st);
+    return quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.corr, w.sa, sumsq, ressq, st);
+}
+static int silu_mul_quantize(const LayerWs &w, int M, int F, void *z, const void *z_inject, hipStream_t st)
+{
+    if (M <= ROWS_PACKED) return quota_silu_mul_quantize_act(w.gu, M, F, w.qa, w.sa, z, z_inject, st);
+    return quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.corr, w.sa, z, z_inject, st);
+}
+static int gemm(const LayerWs &w, int M, const quota_weights *W, void *y, int ldy, const void *res, int ldr, hipStream_t st)
+{
+    if (M <= ROWS_PACKED) return quota_w4a4_gemm(w.qa, w.sa, M, W, y, ldy, res, ldr, nullptr, st);
+    return quota_internal_w4a4_gemm_a8(w.qa, w.corr, w.sa, M, W, y, ldy, res, ldr, st);
+}
 
 // QKV projection of the quantized rows in w.qa, RoPE at `pos`, 4-bit K/V of every row: one
 // kernel (the GEMM with the fused epilogue) when the shape allows it, else the GEMM followed by
@@ -115,10 +139,10 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
         qe.code_row_stride = append_to->capacity; qe.code_row_offset = append_to->len;
         qe.row_step = append_to->step_dev; qe.max_steps = append_to->max_steps;
     }
-    int rc = quota_internal_w4a4_gemm_qkv(w.qa, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
+    int rc = quota_internal_w4a4_gemm_qkv(w.qa, M <= ROWS_PACKED ? nullptr : w.corr, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
     if (rc != QUOTA_ERR_SHAPE) return rc;
     if (append_to && append_to->step_dev) return QUOTA_ERR_SHAPE;      // the device-side step needs the fused form
-    TRY(quota_w4a4_gemm(w.qa, w.sa, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, nullptr, st));
+    TRY(gemm(w, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, st));
     TRY(quota_internal_rope_kv_quant(w.qkv, M, L->H, Hkv, L->dh, pos, L->cosT, L->sinT, L->n_pos, w.q_rot,
                                      w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st));
     return append_to ? quota_internal_kv_append_rows(dkv, w.skc, w.sks, w.svc, w.svs, append_to, st) : QUOTA_OK;
@@ -179,8 +203,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
     // attention half on every token that entered the layer (the two vector cues of Eq. 6 are side
     // outputs of the first quantizer, taken only where they are used)
-    TRY(quota_rmsnorm_quantize_act(s->x, M, d, d, L->gamma1, L->eps, w.qa, w.sa, score ? w.sumsq : nullptr,
-                                   score ? w.ressq : nullptr, nullptr, st));
+    TRY(rmsnorm_quantize(w, s->x, M, d, L->gamma1, L->eps, score ? w.sumsq : nullptr, score ? w.ressq : nullptr, st));
     TRY(qkv_rope_kv_quant(L, w, M, s->pos, t->qkv != nullptr, st));
     TRY(dump(t->qkv, w.qkv, (size_t)M * (d + 2 * dkv) * 2, st));
     TRY(dump(t->q_rot, w.q_rot, (size_t)M * d * 2, st));
@@ -227,6 +250,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     ca.d = d; ca.dkv = dkv; ca.keep_idx = score ? w.keep_idx : nullptr; ca.x = s->x; ca.o = o_used; ca.pos = s->pos;
     ca.skc = w.skc; ca.sks = w.sks; ca.svc = w.svc; ca.svs = w.svs;
     ca.x_out = w.x_keep; ca.o_out = nullptr; ca.oq_out = w.qa; ca.os_out = w.sa;
+    ca.ocorr_out = Mk <= ROWS_PACKED ? nullptr : w.corr;
     ca.pos_out = s->pos_out; ca.rows_out = w.rows;
     ca.cache = cache;
     TRY(quota_internal_compact(&ca, st));
@@ -234,14 +258,13 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
     // token-wise rest of the block on the kept rows only
     if (Mk > 0) {
-        TRY(quota_w4a4_gemm(w.qa, w.sa, Mk, &L->o, w.x1, d, w.x_keep, d, nullptr, st));
+        TRY(gemm(w, Mk, &L->o, w.x1, d, w.x_keep, d, st));
         TRY(dump(t->x1, w.x1, (size_t)Mk * d * 2, st));
-        TRY(quota_rmsnorm_quantize_act(w.x1, Mk, d, d, L->gamma2, L->eps, w.qa, w.sa, nullptr,
-                                       nullptr, nullptr, st));
-        TRY(quota_w4a4_gemm(w.qa, w.sa, Mk, &L->gu, w.gu, 2 * F, nullptr, 0, nullptr, st));
+        TRY(rmsnorm_quantize(w, w.x1, Mk, d, L->gamma2, L->eps, nullptr, nullptr, st));
+        TRY(gemm(w, Mk, &L->gu, w.gu, 2 * F, nullptr, 0, st));
         TRY(dump(t->gu, w.gu, (size_t)Mk * 2 * F * 2, st));
-        TRY(quota_silu_mul_quantize_act(w.gu, Mk, F, w.qa, w.sa, t->z, t->inject_z, st));
-        TRY(quota_w4a4_gemm(w.qa, w.sa, Mk, &L->down, s->x_out, d, w.x1, d, nullptr, st));
+        TRY(silu_mul_quantize(w, Mk, F, t->z, t->inject_z, st));
+        TRY(gemm(w, Mk, &L->down, s->x_out, d, w.x1, d, st));
     }
     // the descriptors move only now that every step has been enqueued
     cache->len += n_keep;
@@ -274,8 +297,7 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
     static const quota_taps no_taps = {};
     const quota_taps *t = taps ? taps : &no_taps;
 
-    TRY(quota_rmsnorm_quantize_act(x_f16, B, d, d, L->gamma1, L->eps, w.qa, w.sa, nullptr, nullptr,
-                                   nullptr, st));
+    TRY(rmsnorm_quantize(w, x_f16, B, d, L->gamma1, L->eps, nullptr, nullptr, st));
     // the new token's K/V join the cache first (written by the QKV epilogue itself, or by the
     // append kernel on the unfused path); attention then reads all of it in 4-bit form
     TRY(qkv_rope_kv_quant(L, w, B, pos, t->qkv != nullptr, st, cache));
@@ -287,15 +309,15 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
     TRY(dump(t->o, w.o, (size_t)B * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
 
-    TRY(quota_quantize_act(o_used, B, d, d, w.qa, w.sa, nullptr, nullptr, st));
-    TRY(quota_w4a4_gemm(w.qa, w.sa, B, &L->o, w.x1, d, x_f16, d, nullptr, st));
+    if (B <= ROWS_PACKED) TRY(quota_quantize_act(o_used, B, d, d, w.qa, w.sa, nullptr, nullptr, st));
+    else TRY(quota_internal_quantize_a8(o_used, B, d, w.qa, w.corr, w.sa, st));
+    TRY(gemm(w, B, &L->o, w.x1, d, x_f16, d, st));
     TRY(dump(t->x1, w.x1, (size_t)B * d * 2, st));
-    TRY(quota_rmsnorm_quantize_act(w.x1, B, d, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr,
-                                   nullptr, st));
-    TRY(quota_w4a4_gemm(w.qa, w.sa, B, &L->gu, w.gu, 2 * F, nullptr, 0, nullptr, st));
+    TRY(rmsnorm_quantize(w, w.x1, B, d, L->gamma2, L->eps, nullptr, nullptr, st));
+    TRY(gemm(w, B, &L->gu, w.gu, 2 * F, nullptr, 0, st));
     TRY(dump(t->gu, w.gu, (size_t)B * 2 * F * 2, st));
-    TRY(quota_silu_mul_quantize_act(w.gu, B, F, w.qa, w.sa, t->z, t->inject_z, st));
-    TRY(quota_w4a4_gemm(w.qa, w.sa, B, &L->down, x_out_f16, d, w.x1, d, nullptr, st));
+    TRY(silu_mul_quantize(w, B, F, t->z, t->inject_z, st));
+    TRY(gemm(w, B, &L->down, x_out_f16, d, w.x1, d, st));
     if (!stepped) cache->len += 1;      // only now that every step has been enqueued
     return QUOTA_OK;
 }

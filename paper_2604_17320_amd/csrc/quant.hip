@@ -81,10 +81,10 @@ __device__ __forceinline__ void group_reduce(float &mx, double &s0, double &s1, 
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
     (void)sm
 
-template <bool WANT_METRICS, int GROUP, int NCH>
+template <bool WANT_METRICS, int GROUP, int NCH, typename OUT>
 __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     const f16 *__restrict__ x, int M, int d, long ldx, int rows_per_seq, long seq_stride,
-    uint32_t *__restrict__ q, float *__restrict__ scale, float *__restrict__ sumsq,
+    OUT q, float *__restrict__ scale, float *__restrict__ sumsq,
     float *__restrict__ ressq)
 {
     ROW_PROLOGUE();
@@ -111,8 +111,7 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     double zero = 0.0;
     group_reduce<GROUP>(a, ss, zero, sm);
     float s;
-    double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a,
-                                                              q ? q + (size_t)row * nchunk : nullptr, s);
+    double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
     if (WANT_METRICS) { float dummy = 0.0f; group_reduce<GROUP>(dummy, rs, zero, sm); }
     if (lane == 0) {
         if (scale) scale[row] = s;
@@ -123,10 +122,10 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     }
 }
 
-template <bool WANT_METRICS, int GROUP, int NCH>
+template <bool WANT_METRICS, int GROUP, int NCH, typename OUT>
 __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
     const f16 *__restrict__ x, int M, int d, long ldx, const float *__restrict__ gamma, float eps,
-    uint32_t *__restrict__ q, float *__restrict__ scale, float *__restrict__ sumsq,
+    OUT q, float *__restrict__ scale, float *__restrict__ sumsq,
     float *__restrict__ ressq, f16 *__restrict__ h_out)
 {
     ROW_PROLOGUE();
@@ -205,7 +204,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
     }
     group_reduce<GROUP>(a, rs, zero, sm);
     float s;
-    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, q + (size_t)row * nchunk, s);
+    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
     if (lane == 0) {
         scale[row] = s;
         if (WANT_METRICS) {
@@ -217,9 +216,9 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
 
 // EARLY: every load before the first use (short launches, latency counts); otherwise chunk by
 // chunk (long launches: fewer live registers, more waves per SIMD to hide the latency instead).
-template <int GROUP, int NCH, bool EARLY>
+template <int GROUP, int NCH, bool EARLY, typename OUT>
 __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
-    const f16 *__restrict__ gu, int M, int F, uint32_t *__restrict__ q, float *__restrict__ scale,
+    const f16 *__restrict__ gu, int M, int F, OUT q, float *__restrict__ scale,
     f16 *__restrict__ z_out, const f16 *__restrict__ z_inject)
 {
     ROW_PROLOGUE();
@@ -263,7 +262,7 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
     double z0 = 0.0, z1 = 0.0;
     group_reduce<GROUP>(a, z0, z1, sm);
     float s;
-    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, q + (size_t)row * nchunk, s);
+    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
     if (lane == 0) scale[row] = s;
 }
 
@@ -331,11 +330,11 @@ extern "C" int quota_quantize_act(const void *x_f16, int M, int d, int ldx, uint
     const bool metrics = sumsq_opt || ressq_opt, small = d <= 4096 && M >= ROW_WAVE_MIN_ROWS;
     const dim3 grid(small ? (M + 3) / 4 : M), blk(ROW_THREADS);
     const f16 *x = (const f16 *)x_f16;
-    uint32_t *q = (uint32_t *)q_packed;
+    const RowOutPacked q{(uint32_t *)q_packed};
     const bool few = (d >> 3) <= 2 * (small ? 64 : 256);      // two chunks per thread are enough
     const bool many = d > 16384;                              // sixteen chunks per thread
 #define QUOTA_LAUNCH_Q(MET, GRP, NCH) \
-    quantize_act_kernel<MET, GRP, NCH><<<grid, blk, 0, st>>>(x, M, d, ldx, M, 0, q, scale, sumsq_opt, ressq_opt)
+    quantize_act_kernel<MET, GRP, NCH, RowOutPacked><<<grid, blk, 0, st>>>(x, M, d, ldx, M, 0, q, scale, sumsq_opt, ressq_opt)
     if (metrics) {
         if (small) { if (few) QUOTA_LAUNCH_Q(true, 64, 2); else QUOTA_LAUNCH_Q(true, 64, 8); }
         else if (many) QUOTA_LAUNCH_Q(true, 256, 16);
@@ -350,28 +349,20 @@ extern "C" int quota_quantize_act(const void *x_f16, int M, int d, int ldx, uint
     return QUOTA_OK;
 }
 
-extern "C" int quota_rmsnorm_quantize_act(const void *x_f16, int M, int d, int ldx,
-                                          const float *gamma, float eps, uint8_t *q_packed,
-                                          float *scale, float *sumsq_opt, float *ressq_opt,
-                                          void *h_opt, void *stream)
+template <typename OUT>
+static int rmsnorm_quantize(const void *x_f16, int M, int d, int ldx, const float *gamma, float eps, OUT q,
+                            float *scale, float *sumsq_opt, float *ressq_opt, void *h_opt, hipStream_t st)
 {
-    int rc = check_rows(x_f16, M, d, ldx, q_packed, scale);
-    if (rc != QUOTA_OK) return rc;
-    if (!gamma) return QUOTA_ERR_NULL;
-    if (!(eps >= 0.0f)) return QUOTA_ERR_INVALID_ARG;
-    if (M == 0) return QUOTA_OK;
-    hipStream_t st = (hipStream_t)stream;
     ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
     const bool metrics = sumsq_opt || ressq_opt, small = d <= 4096 && M >= ROW_WAVE_MIN_ROWS;
     const dim3 grid(small ? (M + 3) / 4 : M), blk(ROW_THREADS);
     const f16 *x = (const f16 *)x_f16;
-    uint32_t *q = (uint32_t *)q_packed;
     f16 *h = (f16 *)h_opt;
     const bool few = (d >> 3) <= 2 * (small ? 64 : 256);      // two chunks per thread are enough
     const bool many = d > 16384;                              // sixteen chunks per thread
-#define QUOTA_LAUNCH_R(MET, GRP, NCH)                                                                  \
-    rmsnorm_quantize_act_kernel<MET, GRP, NCH><<<grid, blk, 0, st>>>(x, M, d, ldx, gamma, eps, q, scale, \
-                                                                     sumsq_opt, ressq_opt, h)
+#define QUOTA_LAUNCH_R(MET, GRP, NCH)                                                                       \
+    rmsnorm_quantize_act_kernel<MET, GRP, NCH, OUT><<<grid, blk, 0, st>>>(x, M, d, ldx, gamma, eps, q, scale, \
+                                                                          sumsq_opt, ressq_opt, h)
     if (metrics) {
         if (small) { if (few) QUOTA_LAUNCH_R(true, 64, 2); else QUOTA_LAUNCH_R(true, 64, 8); }
         else if (many) QUOTA_LAUNCH_R(true, 256, 16);
@@ -386,21 +377,42 @@ extern "C" int quota_rmsnorm_quantize_act(const void *x_f16, int M, int d, int l
     return QUOTA_OK;
 }
 
-extern "C" int quota_silu_mul_quantize_act(const void *gu_f16, int M, int F, uint8_t *q_packed,
-                                           float *scale, void *z_opt, const void *z_inject_opt,
-                                           void *stream)
+extern "C" int quota_rmsnorm_quantize_act(const void *x_f16, int M, int d, int ldx,
+                                          const float *gamma, float eps, uint8_t *q_packed,
+                                          float *scale, float *sumsq_opt, float *ressq_opt,
+                                          void *h_opt, void *stream)
 {
-    int rc = check_rows(gu_f16, M, F, F, q_packed, scale);
+    int rc = check_rows(x_f16, M, d, ldx, q_packed, scale);
+    if (rc != QUOTA_OK) return rc;
+    if (!gamma) return QUOTA_ERR_NULL;
+    if (!(eps >= 0.0f)) return QUOTA_ERR_INVALID_ARG;
+    if (M == 0) return QUOTA_OK;
+    return rmsnorm_quantize(x_f16, M, d, ldx, gamma, eps, RowOutPacked{(uint32_t *)q_packed}, scale, sumsq_opt,
+                            ressq_opt, h_opt, (hipStream_t)stream);
+}
+
+int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa8,
+                                       float *corr, float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st)
+{
+    int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    ProfScope prof(QUOTA_K_SILU_MUL_QUANTIZE_ACT, 0, 4.5 * M * F + 4.0 * M, (hipStream_t)stream);
+    return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, RowOutA8{(uint2 *)qa8, corr, M}, scale, sumsq_opt, ressq_opt,
+                            nullptr, st);
+}
+
+template <typename OUT>
+static int silu_mul_quantize(const void *gu_f16, int M, int F, OUT q, float *scale, void *z_opt,
+                             const void *z_inject_opt, hipStream_t st)
+{
+    ProfScope prof(QUOTA_K_SILU_MUL_QUANTIZE_ACT, 0, 4.5 * M * F + 4.0 * M, st);
     const bool small = F <= 4096 && M >= ROW_WAVE_MIN_ROWS;
     const dim3 grid(small ? (M + 3) / 4 : M), blk(ROW_THREADS);
     const bool few = (F >> 3) <= 2 * (small ? 64 : 256);
     const bool many = F > 16384;          // sixteen chunks per thread, loaded chunk by chunk
-#define QUOTA_LAUNCH_S(GRP, NCH, EARLY)                                                               \
-    silu_mul_quantize_act_kernel<GRP, NCH, EARLY><<<grid, blk, 0, (hipStream_t)stream>>>(             \
-        (const f16 *)gu_f16, M, F, (uint32_t *)q_packed, scale, (f16 *)z_opt, (const f16 *)z_inject_opt)
+#define QUOTA_LAUNCH_S(GRP, NCH, EARLY)                                              \
+    silu_mul_quantize_act_kernel<GRP, NCH, EARLY, OUT><<<grid, blk, 0, st>>>(        \
+        (const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt)
     if (many) QUOTA_LAUNCH_S(256, 16, false);
     else if (M >= ROW_WAVE_MIN_ROWS) {
         if (small) { if (few) QUOTA_LAUNCH_S(64, 2, false); else QUOTA_LAUNCH_S(64, 8, false); }
@@ -410,6 +422,42 @@ extern "C" int quota_silu_mul_quantize_act(const void *gu_f16, int M, int F, uin
         else { if (few) QUOTA_LAUNCH_S(256, 2, true); else QUOTA_LAUNCH_S(256, 8, true); }
     }
 #undef QUOTA_LAUNCH_S
+    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    return QUOTA_OK;
+}
+
+extern "C" int quota_silu_mul_quantize_act(const void *gu_f16, int M, int F, uint8_t *q_packed,
+                                           float *scale, void *z_opt, const void *z_inject_opt,
+                                           void *stream)
+{
+    int rc = check_rows(gu_f16, M, F, F, q_packed, scale);
+    if (rc != QUOTA_OK) return rc;
+    if (M == 0) return QUOTA_OK;
+    return silu_mul_quantize(gu_f16, M, F, RowOutPacked{(uint32_t *)q_packed}, scale, z_opt, z_inject_opt,
+                             (hipStream_t)stream);
+}
+
+int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *corr, float *scale,
+                                        void *z_opt, const void *z_inject_opt, hipStream_t st)
+{
+    int rc = check_rows(gu_f16, M, F, F, qa8, scale);
+    if (rc != QUOTA_OK) return rc;
+    if (M == 0) return QUOTA_OK;
+    return silu_mul_quantize(gu_f16, M, F, RowOutA8{(uint2 *)qa8, corr, M}, scale, z_opt, z_inject_opt, st);
+}
+
+// Per-token quantizer of a dense fp16 [M][d] into the A8 format.
+int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *corr, float *scale, hipStream_t st)
+{
+    int rc = check_rows(x_f16, M, d, d, qa8, scale);
+    if (rc != QUOTA_OK) return rc;
+    if (M == 0) return QUOTA_OK;
+    ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
+    const bool many = d > 16384, few = (d >> 3) <= 512;
+    auto kernel = many ? quantize_act_kernel<false, 256, 16, RowOutA8>
+                       : few ? quantize_act_kernel<false, 256, 2, RowOutA8> : quantize_act_kernel<false, 256, 8, RowOutA8>;
+    kernel<<<dim3(M), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, RowOutA8{(uint2 *)qa8, corr, M}, scale,
+                                                  nullptr, nullptr);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -429,8 +477,8 @@ int quota_internal_vector_metrics(const void *v_f16, int B, int Nv, int d, int l
     const dim3 grid(small ? (B * Nv + 3) / 4 : B * Nv), blk(ROW_THREADS);
     const bool few = (d >> 3) <= 2 * (small ? 64 : 256);
 #define QUOTA_LAUNCH_V(GRP, NCH)                                                                           \
-    quantize_act_kernel<true, GRP, NCH><<<grid, blk, 0, st>>>((const f16 *)v_f16, B * Nv, d, ldv, Nv, stride_b, \
-                                                              nullptr, nullptr, sumsq, ressq)
+    quantize_act_kernel<true, GRP, NCH, RowOutPacked><<<grid, blk, 0, st>>>(                               \
+        (const f16 *)v_f16, B * Nv, d, ldv, Nv, stride_b, RowOutPacked{nullptr}, nullptr, sumsq, ressq)
     if (small) { if (few) QUOTA_LAUNCH_V(64, 2); else QUOTA_LAUNCH_V(64, 8); }
     else if (d > 16384) QUOTA_LAUNCH_V(256, 16);
     else { if (few) QUOTA_LAUNCH_V(256, 2); else QUOTA_LAUNCH_V(256, 8); }
