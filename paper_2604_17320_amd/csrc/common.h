@@ -114,10 +114,8 @@ __device__ __forceinline__ uint32_t code_bits(float t)
     t = fminf(fmaxf(t, -8.0f), 7.0f);          // NaN -> -8, as in code_from
     return __float_as_uint(t + ROW_MAGIC);
 }
-// Units of the fp8 GEMM operands: code / 512 is an e4m3 number for every int4 code, a group's accumulator
-// therefore counts in 2^-18, and corr = F8_CORR * (sum of a group's activation codes) takes the
-// weights' offset of 8 out again (see gemm.hip).
+// Units of the fp8 GEMM operands: code / 512 is an e4m3 number for every int4 code, so a group's
+// accumulator counts in 2^-18 (see gemm.hip).
 #define F8_UNIT 262144.0f
-#define F8_CORR (-8.0f / 262144.0f)
 __device__ __forceinline__ float code_float(uint32_t bits) { return __uint_as_float(bits) - ROW_MAGIC; }
 

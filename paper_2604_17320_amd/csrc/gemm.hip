@@ -11,12 +11,14 @@
 // (the subnormals and the first binade of e4m3 are one linear range), so the unpack stays at 3 vector
 // instructions per 8 codes: lo = (w & 0x0f..) ^ 0x08.., hi = (w >> 4 & 0x0f..) ^ 0x08...
 // Activations are signed e4m3 numbers a / 512.  The weights' offset of 8 comes back out through the
-// accumulator's start value: acc = corr + sum (a / 512) (c + 8) / 512 with corr = -8 / 2^18 * sum of the
-// group's activation codes, one number per (row, group).  The 2^18 goes into the token scale (exact).
+// accumulator's start value, -8 / 2^18 * sum of the group's activation codes: one more MFMA per 16 rows and
+// group, against a constant -8 / 512, whose result already lies where the C operand wants it.  The 2^18
+// of the operands' units goes into the token scale (exact).
 //
-// Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes [M][128 G], every 8
-// codes stored as evens then odds (the order the weight unpack produces), plus corr [ceil(G / 4)][M][4].  The public
-// entry point takes packed int4 rows and converts them while staging (PACKED).
+// Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes, row stride 128 (G | 1) (an
+// odd number of 128-byte lines: with a power of two the rows a tile reads together share one L2 channel), every 8
+// codes stored as evens then odds (the order the weight unpack produces).  The public entry point takes
+// packed int4 rows and converts them while staging (PACKED).
 #include "common.h"
 #include "internal.h"
 #include "ropequant.h"
@@ -36,9 +38,9 @@ __device__ __forceinline__ void copy16_to_lds(const void *base, unsigned off, un
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
 }
-__device__ __forceinline__ void copy4_to_lds(const void *addr, unsigned lds)
+__device__ __forceinline__ void copy4_to_lds(const void *base, unsigned off, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(addr) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
 }
 // All of this wave's loads and copies have arrived.  In assembly, because the compiler drops a wait that
 // it thinks has nothing to wait for; the builtin as well, so that it knows its own loads have arrived.
@@ -49,34 +51,33 @@ __device__ __forceinline__ void drain()
 }
 
 // Workgroup tile (16 RT) x (16 CT NW): NW waves side by side, each with all rows and its own 16 CT
-// columns, so a weight is read and unpacked by exactly one wave and never touches LDS, while activations,
-// corr and group scales are staged in LDS.
+// columns, so a weight is read and unpacked by exactly one wave and never touches LDS, while activations
+// and group scales are staged in LDS.
 // The K loop runs in stages of CH groups: during a stage everything of the next one is set off -- weights into
 // registers, the rest into the other LDS buffer -- and a stage ends with one wait for all of it and one
 // barrier; nothing in between waits for memory.
 //   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
 //   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
-//   one-group stages of the 128-row tile and the 32-row tiles have no time to spare and lose by it).
+//   32-row tiles have no time to spare and lose by it).
 //   PIPE: weights of group g+1 are unpacked between the MFMAs of group g (twice the fragment registers).
 // LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that the 8 lanes of one LDS
 // cycle (8 rows, same piece) cover all banks.
 template <int RT, int CT, int NW, int CH, int SP, bool PIPE, bool PACKED, bool ACC_OUT, bool QKV, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
-    const uint8_t *__restrict__ qa, const float *__restrict__ corr, const float *__restrict__ sa, int M, int K,
-    int G, const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
+    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
+    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
     const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n,
     int vec_store, quota_qkv_epilogue qe)
 {
     constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
     constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : BM * 8 / NT;    // 16-byte pieces per thread and group
-    constexpr int KD = (BM + BN / 2 + NT - 1) / NT;                      // corr / scale dwords per thread and group
+    constexpr int KD = (CH * BN / 2 + NT - 1) / NT;                      // scale dwords per thread and stage
     static_assert(RT % 2 == 0 && (PACKED || BM * 8 % NT == 0), "whole rows per copy, fragment double buffer");
-    // one group in LDS: activations, then dwords: BM of corr, BN / 2 of scales, up to whole waves.  PACKED
-    // computes corr and keeps it behind that (+ a spare piece for threads without one)
-    constexpr int AST = BM * 8, KST = KD * NT / 4, CST = PACKED ? AST + KST : AST;          // in uint4
-    constexpr int GST = AST + KST + (PACKED ? BM / 4 + 3 : 0);
+    // one stage in LDS (in uint4): CH groups of activations (+ a spare piece for PACKED threads without one),
+    // then the group scales, up to whole waves
+    constexpr int AST = BM * 8 + (PACKED ? 2 : 0), GST = CH * AST, STG = GST + KD * NT / 4;
     constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
-    constexpr int LDS_A = 2 * CH * GST, LDS_Q = QKV ? 32 * TROW / 8 : 32 * FROW / 4;
+    constexpr int LDS_A = 2 * STG, LDS_Q = QKV ? 32 * TROW / 8 : 32 * FROW / 4;
     __shared__ uint4 lds_raw[LDS_A > LDS_Q ? LDS_A : LDS_Q];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds_raw;
 
@@ -88,9 +89,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
     // ones and are never stored; groups past G repeat the last one and meet a zero scale.
-    const int Kb = PACKED ? K >> 1 : G * 128;            // bytes per activation row
+    const int Kb = PACKED ? K >> 1 : 128 * (G | 1);      // bytes per activation row
     unsigned oa[LA];                                     // byte offset of this thread's piece of group 0
-    int la[LA], pa[LA], lk[LA];                          // PACKED: LDS slots of the piece and of corr
+    int la[LA], pa[LA];                                  // PACKED: LDS slot of the piece
     // (threads without one write a spare slot: a branch would let the compiler sink the scale chain behind it)
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
@@ -99,68 +100,68 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         oa[j] = (unsigned)(min(m0 + min(row, BM - 1), M - 1) - m0) * (unsigned)Kb;
         if (!PACKED) oa[j] += 16 * p;
         pa[j] = 16 * p;
-        la[j] = row < BM ? row * 8 + ((2 * p) ^ (row & 7)) : (CST + BM / 4 + 1) & ~1;
-        lk[j] = row < BM && p == 0 ? row : BM;
+        la[j] = row < BM ? row * 8 + ((2 * p) ^ (row & 7)) : BM * 8;
     }
-    const uint8_t *abase = qa + (size_t)m0 * Kb;
     const int nw = min(n0 + wave * WN, N - WN);          // this wave's first column (N is a multiple of 64)
     const bool n_ok = n0 + wave * WN < N;
     const unsigned wl = (unsigned)(c16 * 4 + q);         // this lane's uint4 of a 16-column block
-
-    const float *kaddr[KD];                              // this thread's corr / scale dwords of group 0
-    bool k_scale[KD];
+    // scale dword tid + NT k of a stage: two neighbouring columns of one of its groups
+    unsigned os[KD];
+    int gs[KD];
 #pragma unroll
     for (int k = 0; k < KD; ++k) {
-        const int d = tid + NT * k;
-        k_scale[k] = d >= BM;
-        kaddr[k] = k_scale[k] || PACKED
-                       ? reinterpret_cast<const float *>(sw) + min((n0 >> 1) + max(d - BM, 0), (N >> 1) - 1)
-                       : corr + 4 * (size_t)min(m0 + d, M - 1);
+        const int d = min(tid + NT * k, CH * BN / 2 - 1);
+        gs[k] = d / (BN / 2);
+        os[k] = 4u * (unsigned)min((n0 >> 1) + d % (BN / 2), (N >> 1) - 1);
     }
 
     constexpr int WS = CH > 1 || PIPE ? 2 : 1;           // register sets of packed weights
     uint4 rw[WS][CH][CT];
     i32x4 ra[CH][LA];                                    // PACKED staging (struct uint4 here would live in scratch memory)
-    // What a stage needs, load by load: for each of its groups CT weight pieces, LA activation pieces, KD
-    // dwords of corr and scales.
-    constexpr int LG = CT + LA + KD, LOADS = CH * LG;
-    auto load = [&](int k, int set, int half, int g0) {
-        const int c = k / LG, r = k % LG, g = min(g0 + c, G - 1);
-        const unsigned dst = lds0 + (unsigned)(half * CH + c) * (GST * 16);
-        if (r < CT) {
-            const uint4 *wg = wp + ((size_t)g * N + nw) * 4;             // uniform
-            rw[set][c][r] = wg[wl + 64 * r];
-        } else if (r < CT + LA) {
-            const int j = r - CT;
-            if constexpr (PACKED) {
-                const unsigned kb = (unsigned)min(g * 64 + pa[j], Kb - 16);
-                ra[c][j] = *reinterpret_cast<const i32x4 *>(abase + (oa[j] + kb));
+    // What a stage needs, load by load: for each of its groups CT weight pieces and LA activation pieces, then
+    // KD dwords of scales.  The pointers (uniform, of the next group to load) stop at the last group:
+    // groups past it are loaded but never used.
+    constexpr int LG = CT + LA, LOADS = CH * LG + KD;
+    const uint4 *wnext = wp + (size_t)nw * 4;
+    const uint8_t *anext = qa + (size_t)m0 * Kb;
+    int gnext = 0, gstage = 0;                            // next group to load, first group of the stage being loaded
+    auto load = [&](int k, int set, int half) {
+        const unsigned dst = lds0 + (unsigned)half * (STG * 16);
+        if (k < CH * LG) {
+            const int c = k / LG, r = k % LG;
+            if (r < CT) {
+                rw[set][c][r] = wnext[wl + 64 * r];
             } else {
-                copy16_to_lds(abase + (size_t)g * 128, oa[j], dst + (unsigned)(wave + NW * j) * 1024);
+                const int j = r - CT;
+                if constexpr (PACKED) {
+                    const unsigned kb = (unsigned)min(gnext * 64 + pa[j], Kb - 16);
+                    ra[c][j] = *reinterpret_cast<const i32x4 *>(qa + (size_t)m0 * Kb + (oa[j] + kb));
+                } else {
+                    copy16_to_lds(anext, oa[j], dst + (unsigned)(c * AST * 16 + (wave + NW * j) * 1024));
+                }
+            }
+            if (r == LG - 1) {
+                const bool more = gnext + 1 < G;
+                wnext += more ? (size_t)N * 4 : 0;
+                anext += more ? 128 : 0;
+                gnext += more;
             }
         } else {
-            const int j = r - CT - LA;
-            const size_t koff = ((size_t)(g >> 2) * M) * 16 + (g & 3) * 4, soff = (size_t)g * N * 2;
-            copy4_to_lds(reinterpret_cast<const char *>(kaddr[j]) + (k_scale[j] || PACKED ? soff : koff),
-                         dst + AST * 16 + (unsigned)(wave + NW * j) * 256);
+            const int j = k - CH * LG;
+            copy4_to_lds(sw, os[j] + (unsigned)min(gstage + gs[j], G - 1) * (unsigned)(2 * N), dst + (unsigned)(GST * 16 + (wave + NW * j) * 256));
         }
     };
-    auto store_packed = [&](int half) {                  // convert and store what load_rest brought
+    auto store_packed = [&](int half) {                  // convert and store what the loads brought
         if constexpr (PACKED) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                uint4 *dst = lds_raw + (half * CH + c) * GST;
-                float *dk = reinterpret_cast<float *>(dst + CST);
+                uint4 *dst = lds_raw + half * STG + c * AST;
 #pragma unroll
                 for (int j = 0; j < LA; ++j) {
                     uint4 e0, e1;
-                    int sum;
-                    codes_to_e4m3(make_uint4(ra[c][j][0], ra[c][j][1], ra[c][j][2], ra[c][j][3]), e0, e1, sum);
-                    sum += __builtin_amdgcn_update_dpp(0, sum, 0xB1, 0xf, 0xf, false);     // the 4 pieces of a row
-                    sum += __builtin_amdgcn_update_dpp(0, sum, 0x4E, 0xf, 0xf, false);     // sit in 4 lanes
+                    codes_to_e4m3(make_uint4(ra[c][j][0], ra[c][j][1], ra[c][j][2], ra[c][j][3]), e0, e1);
                     dst[la[j]] = e0;
                     dst[la[j] ^ 1] = e1;
-                    dk[lk[j]] = (float)sum * F8_CORR;
                 }
             }
         }
@@ -183,17 +184,20 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         fb[2 * i] = (int)((w & 0x0F0F0F0Fu) ^ 0x08080808u);
         fb[2 * i + 1] = (int)(((w >> 4) & 0x0F0F0F0Fu) ^ 0x08080808u);
     };
-    // this lane's activation fragment of row block i with the start values of its four results, and the
-    // scale of its column in block j, of the group at `gp`
+    // this lane's activation fragment of row block i of the group at `gp`, the start values of its four
+    // results, and the scale of its column in block j
     const int fr = c16 * 8, fx = c16 & 7;
-    auto read_a = [&](const uint4 *gp, int i, i32x8 &fa, f32x4 &k4) {
+    const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
+                               (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
+    auto read_a = [&](const uint4 *gp, int i, i32x8 &fa) {
         const uint4 a0 = gp[i * 128 + fr + ((2 * q) ^ fx)], a1 = gp[i * 128 + fr + ((2 * q + 1) ^ fx)];
         fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
-        k4 = *reinterpret_cast<const f32x4 *>(gp + CST + 4 * i + q);
     };
-    auto read_scale = [&](const uint4 *gp, int g, int j) {
-        const f16 s = reinterpret_cast<const f16 *>(gp + AST + BM / 4)[wave * WN + 16 * j + c16];
-        return g < G ? (float)s : 0.0f;
+    auto start_of = [&](const i32x8 &fa) {
+        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{0, 0, 0, 0}, 0, 0, 0, 0, 0, 0);
+    };
+    auto read_scale = [&](const uint4 *sp, int c, int j) {
+        return (float)reinterpret_cast<const f16 *>(sp + GST)[c * BN + wave * WN + 16 * j + c16];
     };
     // The group scale of a result is applied LAG results later, so that the matrix core's latency is
     // covered; the last ones of a group are finished during the next.
@@ -201,20 +205,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     static_assert(T % LAG == 0, "the carried results keep their order");
     f32x4 pend[LAG];
     float pscale[LAG];
-    bool plive = false;
 #pragma unroll
     for (int i = 0; i < LAG; ++i) { pend[i] = f32x4{0, 0, 0, 0}; pscale[i] = 0.0f; }
-    auto scale_in = [&](int t, const f32x4 &a, float s, bool live) {
+    auto scale_in = [&](int t, const f32x4 &a, float s) {
         const int i = t / CT, j = t % CT;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             yacc[i][j][r] = __builtin_fmaf(a[r], s, yacc[i][j][r]);
-            if (ACC_OUT) tot[i][j][r] += live ? (int)(a[r] * F8_UNIT) : 0;
+            if (ACC_OUT) tot[i][j][r] += (int)(a[r] * F8_UNIT);
         }
     };
 
 #pragma unroll
-    for (int k = 0; k < LOADS; ++k) load(k, 0, 0, 0);
+    for (int k = 0; k < LOADS; ++k) load(k, 0, 0);
     drain();
     store_packed(0);
     __syncthreads();
@@ -228,28 +231,31 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     constexpr int SU = PIPE && CH % 2 ? 2 : WS;          // stages per loop body (parities are compile-time)
     const int stages = (G + CH - 1) / CH;
     i32x8 fa[2];
-    f32x4 k4[2];
 #pragma unroll 1
     for (int st0 = 0; st0 < stages; st0 += SU) {
 #pragma unroll
         for (int su = 0; su < SU; ++su) {
             const int g0 = (st0 + su) * CH, half = SU == 2 ? su : st0 & 1, set = su % WS;
-            const uint4 *gp = lds_raw + half * CH * GST;
-            read_a(gp, 0, fa[0], k4[0]);
+            if (SU == 2 && su && g0 >= G) break;
+            const uint4 *sp = lds_raw + half * STG;
+            read_a(sp, 0, fa[0]);
             if (!PIPE && CH == 1) {
 #pragma unroll
                 for (int j = 0; j < CT; ++j)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[0][j]);
             }
+            gstage = g0 + CH;
 #pragma unroll
-            for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1, g0 + CH);
+            for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1);
 #pragma unroll
-            for (int c = 0; c < CH; ++c, gp += GST) {
-                const int g = g0 + c, cur = PIPE ? (su * CH + c) & 1 : 0;
+            for (int c = 0; c < CH; ++c) {
+                if (c && g0 + c >= G) break;             // uniform: the last stage may hold fewer groups
+                const uint4 *gp = sp + c * AST;
+                const int cur = PIPE ? (su * CH + c) & 1 : 0;
                 float sc[CT];
 #pragma unroll
-                for (int j = 0; j < CT; ++j) sc[j] = read_scale(gp, g, j);
+                for (int j = 0; j < CT; ++j) sc[j] = read_scale(sp, c, j);
                 if (!PIPE && CH > 1) {
 #pragma unroll
                     for (int j = 0; j < CT; ++j)
@@ -261,22 +267,25 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 // every row block's fragments up front, which does not fit the registers): one MFMA, the
                 // chain of the result LAG places back, a share of the next group's unpacking (PIPE).  The
                 // next row block's fragments are read at the start of a row block.
+                f32x4 k4[2];
+                k4[0] = start_of(fa[0]);
 #pragma unroll
                 for (int i = 0; i < RT; ++i) {
-                    if (i + 1 < RT) read_a(gp, i + 1, fa[(i + 1) & 1], k4[(i + 1) & 1]);
-                    else if (c + 1 < CH) read_a(gp + GST, 0, fa[0], k4[0]);
+                    if (i + 1 < RT) read_a(gp, i + 1, fa[(i + 1) & 1]);
+                    else if (c + 1 < CH) read_a(gp + AST, 0, fa[0]);
 #pragma unroll
                     for (int j = 0; j < CT; ++j) {
                         __builtin_amdgcn_sched_barrier(0);
                         const int t = i * CT + j;
                         const f32x4 a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 1], fb[cur][j], k4[i & 1], 0, 0, 0, 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
-                        if (t < LAG) scale_in(T - LAG + t, pend[t], pscale[t], plive);
-                        else scale_in(t - LAG, pend[t % LAG], sc[(t - LAG) % CT], g < G);
+                        if (t < LAG) scale_in(T - LAG + t, pend[t], pscale[t]);
+                        else scale_in(t - LAG, pend[t % LAG], sc[(t - LAG) % CT]);
                         pend[t % LAG] = a;
+                        if (j == CT - 1 && i + 1 < RT) k4[(i + 1) & 1] = start_of(fa[(i + 1) & 1]);
 #pragma unroll
                         for (int k = 0; k < (SP ? LOADS : 0); ++k)
-                            if (k * (CH * T * SP / 8) / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1, g0 + CH);
+                            if (k * (CH * T * SP / 8) / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1);
                         if (PIPE && c + 1 < CH) {
 #pragma unroll
                             for (int u = t * 4 * CT / T; u < (t + 1) * 4 * CT / T; ++u)
@@ -287,7 +296,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int i = 0; i < LAG; ++i) pscale[i] = sc[(T - LAG + i) % CT];
-                plive = g < G;
             }
             drain();
             store_packed(half ^ 1);
@@ -300,7 +308,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         }
     }
 #pragma unroll
-    for (int i = 0; i < LAG; ++i) scale_in(T - LAG + i, pend[i], pscale[i], plive);
+    for (int i = 0; i < LAG; ++i) scale_in(T - LAG + i, pend[i], pscale[i]);
 
     // epilogue: token scale (with the 2^18 of the operands' e4m3 units), residual, fp16
     if constexpr (QKV) {
@@ -548,14 +556,14 @@ int launch_gemv16(const uint8_t *qa, const float *sa, int M, const quota_weights
 #define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, false, P, A, QK, 2>  // 64 x 128
 #define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, false, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, false, P, A, QK, 2>  // 32 x 64
-#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 0, false, P, A, QK, 2>  // 128 x 256
+#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, false, P, A, QK, 2>  // 128 x 256
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
                              {128, 256, 256, QUOTA_K_GEMM_128X256}};
 
-typedef void (*f8_kernel)(const uint8_t *, const float *, const float *, int, int, int, const uint4 *, const f16 *,
+typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
 
 template <bool P, bool QK>
@@ -570,7 +578,7 @@ f8_kernel tile_kernel(int v)
     }
 }
 
-int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const float *corr, const float *sa, int M,
+int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const float *sa, int M,
               const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int32_t *acc, hipStream_t st,
               const quota_qkv_epilogue *qe = nullptr)
 {
@@ -584,7 +592,7 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
     static const quota_qkv_epilogue no_qe = {};
     auto aligned = [](const void *p, int ld) { return ld % 8 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     const int vec = (y && aligned(y, ldy) ? 1 : 0) | (res && aligned(res, ldr) ? 2 : 0);
-    kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>(qa, corr, sa, M, W->K, G, (const uint4 *)W->packed,
+    kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>(qa, sa, M, W->K, G, (const uint4 *)W->packed,
                                                            (const f16 *)W->scales, W->N, y, ldy, res, ldr, acc, tiles_m,
                                                            tiles_n, vec, qe ? *qe : no_qe);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -602,11 +610,11 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn)
 {
     struct Cost { float c0, u[4], slope; };
     static const Cost cost[5] = {
-        {3.0f, {0.80f, 1.12f, 1.65f, 2.15f}, 0.56f},
-        {3.0f, {0.58f, 0.95f, 1.03f, 1.08f}, 0.30f},
-        {2.5f, {0.31f, 0.48f, 0.76f, 0.96f}, 0.235f},
-        {2.0f, {0.25f, 0.345f, 0.46f, 0.66f}, 0.165f},
-        {5.0f, {1.20f, 1.90f, 2.90f, 3.90f}, 0.97f},
+        {3.0f, {0.75f, 1.08f, 1.65f, 2.15f}, 0.53f},
+        {3.0f, {0.54f, 0.95f, 1.00f, 1.08f}, 0.285f},
+        {2.5f, {0.30f, 0.47f, 0.73f, 0.92f}, 0.225f},
+        {2.0f, {0.23f, 0.30f, 0.43f, 0.62f}, 0.155f},
+        {5.0f, {1.02f, 1.90f, 2.90f, 3.90f}, 0.92f},
     };
     auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn; };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
@@ -633,14 +641,14 @@ extern "C" int quota_set_gemm_variant(int variant)
 }
 
 // GEMM on activations in the internal A8 format (M > 16 rows of a layer).
-int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *corr, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
                                 void *y_f16, int ldy, const void *residual_opt, int ldr, hipStream_t st)
 {
-    if (!qa8 || !corr || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
+    if (!qa8 || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
     if (W->N % 64 != 0 || W->K % 32 != 0) return QUOTA_ERR_SHAPE;
     if (M <= 0) return QUOTA_OK;
     const int v = choose_tile(M, W->N, W->K, 0, 256);
-    return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, corr, sa, M, W, (f16 *)y_f16, ldy,
+    return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
 }
 
@@ -659,19 +667,19 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     f16 *y = (f16 *)y_f16;
     const f16 *res = (const f16 *)residual_opt;
     if (acc_i32_opt)
-        return launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, nullptr, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
+        return launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
     if (M <= 16)            // the decode step: stream the weights once, groups spread over 8 waves
         return W->N <= 8192 ? launch_gemv16<1, 2>(qa, sa, M, W, y, ldy, res, ldr, st)
                             : launch_gemv16<2, 2>(qa, sa, M, W, y, ldy, res, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
-    return launch_f8(tile_kernel<true, false>(v), v, kTiles[v].kernel_id, qa, nullptr, sa, M, W, y, ldy, res, ldr, nullptr, st);
+    return launch_f8(tile_kernel<true, false>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
 // QKV projection with the RoPE + 4-bit K/V quantizer fused into the epilogue (see the kernel).
-// corr: null for packed int4 activations (few rows: the 32-row tile), else qa is in the A8 format.
+// a8: qa is in the A8 format; otherwise packed int4 (few rows: the 32-row tile).
 // y_opt, when not null, also receives the plain fp16 q | k | v.  Returns QUOTA_ERR_SHAPE when the
 // shape does not fit the fused form (the caller then runs the two kernels separately).
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, const float *corr, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st)
 {
     if (!qa || !sa || !W || !W->packed || !W->scales || !qe || !qe->pos || !qe->cosT || !qe->sinT ||
@@ -683,7 +691,7 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, const float *corr, const flo
         W->N != d + 2 * dkv || W->K % 32 != 0)
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
-    const int v = corr ? choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128) : 2;
-    f8_kernel kernel = corr ? tile_kernel<false, true>(v) : F8_TILE_2(true, false, true);
-    return launch_f8(kernel, v, kTiles[v].kernel_id, qa, corr, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0, nullptr, st, qe);
+    const int v = a8 ? choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128) : 2;
+    f8_kernel kernel = a8 ? tile_kernel<false, true>(v) : F8_TILE_2(true, false, true);
+    return launch_f8(kernel, v, kTiles[v].kernel_id, qa, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0, nullptr, st, qe);
 }

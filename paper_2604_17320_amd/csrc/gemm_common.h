@@ -13,7 +13,7 @@ __device__ __forceinline__ void unpack16(const uint4 &v, uint4 &lo, uint4 &hi)
     lo.w = (v.w << 4) & 0xF0F0F0F0u; hi.w = v.w & 0xF0F0F0F0u;
 }
 // 32 packed int4 codes (one 16-byte piece) as signed e4m3 bytes in the A8 order -- every 8 codes as evens
-// then odds -- and their sum.  With u = code & 15 and b its sign bit the e4m3 byte is u for b = 0 and
+// then odds.  With u = code & 15 and b its sign bit the e4m3 byte is u for b = 0 and
 // 0x90 - u = (u ^ 15) + 0x81 for b = 1, IN UNITS OF 1/512 (the linear range of e4m3), so that no
 // table is needed; v_xad_u32 does the last step.
 __device__ __forceinline__ uint32_t nibbles_to_e4m3(uint32_t u)
@@ -21,14 +21,12 @@ __device__ __forceinline__ uint32_t nibbles_to_e4m3(uint32_t u)
     const uint32_t t = u & 0x08080808u, b = t >> 3;
     return (u ^ (t | (t - b))) + ((t << 4) | b);
 }
-__device__ __forceinline__ void codes_to_e4m3(const uint4 &v, uint4 &e0, uint4 &e1, int &sum)
+__device__ __forceinline__ void codes_to_e4m3(const uint4 &v, uint4 &e0, uint4 &e1)
 {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     uint32_t e[8];
-    sum = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        sum = __builtin_amdgcn_sdot8((int)w[i], 0x11111111, sum, false);
         e[2 * i] = nibbles_to_e4m3(w[i] & 0x0F0F0F0Fu);
         e[2 * i + 1] = nibbles_to_e4m3((w[i] >> 4) & 0x0F0F0F0Fu);
     }

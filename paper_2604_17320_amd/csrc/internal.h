@@ -31,7 +31,7 @@ struct quota_compact_args {
     const void *skc, *sks, *svc, *svs;     // staged 4-bit K/V of all N rows
     void *x_out, *o_out;                   // o_out optional (fp16 copy of the kept attention rows)
     uint8_t *oq_out;                       // optional: int4 codes of the kept attention rows ...
-    float *ocorr_out;                      // ... in the A8 format with these group sums, packed when null ...
+    bool oq_a8;                            // ... in the A8 format, or packed ...
     float *os_out;                         // ... and their per-token scales (the quantizer Q)
     int32_t *pos_out, *rows_out;
     quota_kv_cache *cache;
@@ -59,20 +59,19 @@ struct quota_qkv_epilogue {
     const int32_t *row_step;                 // optional (device): ... + clamp(*row_step, 0, max_steps - 1)
     int max_steps;
 };
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, const float *corr, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st);
 
-// The layer's row quantizers and GEMM on activations in the A8 format (gemm.hip): qa8 has M rows of
-// quota_a8_row_bytes(K) bytes, corr is M * quota_a8_corr_floats(K) floats.
-inline size_t quota_a8_row_bytes(int K) { return ((size_t)K + 127) / 128 * 128; }
-inline size_t quota_a8_corr_floats(int K) { return ((size_t)K + 511) / 512 * 4; }
+// The layer's row quantizers and GEMM on activations in the A8 format (gemm.hip): M rows of
+// quota_a8_row_bytes(K) bytes.
+inline size_t quota_a8_row_bytes(int K) { return ((((size_t)K + 127) / 128) | 1) * 128; }
 int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa8,
-                                       float *corr, float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st);
-int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *corr, float *scale,
-                                        void *z_opt, const void *z_inject_opt, hipStream_t st);
-int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *corr, float *scale, hipStream_t st);
-int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *corr, const float *sa, int M, const quota_weights *W,
-                                void *y_f16, int ldy, const void *residual_opt, int ldr, hipStream_t st);
+                                       float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st);
+int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *scale, void *z_opt,
+                                        const void *z_inject_opt, hipStream_t st);
+int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st);
+int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *y_f16, int ldy,
+                                const void *residual_opt, int ldr, hipStream_t st);
 
 // quota_rope_kv_quant with Hkv K/V heads: qkv rows are q (H*dh) | k (Hkv*dh) | v (Hkv*dh).
 int quota_internal_rope_kv_quant(const void *qkv_f16, int M, int H, int Hkv, int dh, const int32_t *pos,

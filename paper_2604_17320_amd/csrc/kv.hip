@@ -258,8 +258,8 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
             c->capacity, c->len, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,
             (f16 *)c->v_scales);
     };
-    if (a->ocorr_out) {
-        const RowOutA8 oq{(uint2 *)a->oq_out, a->ocorr_out, a->B * a->n_keep};
+    if (a->oq_a8) {
+        const RowOutA8 oq{(uint2 *)a->oq_out};
         if (a->d <= 4096) launch(compact_rows_kernel<2, RowOutA8>, oq);
         else launch(compact_rows_kernel<8, RowOutA8>, oq);
     } else {

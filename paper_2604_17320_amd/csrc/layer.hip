@@ -25,7 +25,7 @@ struct Carver {
 
 struct LayerWs {
     uint8_t *qa;        // int4 activations of the current GEMM input, A8 format (packed for at most 16 rows)
-    float *corr, *sa;
+    float *sa;
     f16 *qkv, *q_rot, *khat, *vhat, *o;
     uint8_t *skc, *svc; // staged 4-bit K/V of all rows
     f16 *sks, *svs;
@@ -43,7 +43,6 @@ LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
     size_t M = (size_t)B * N, d = (size_t)H * dh, dkv = (size_t)Hkv * dh;
     size_t kmax = d > (size_t)F ? d : (size_t)F;
     w.qa = c.take<uint8_t>(M * quota_a8_row_bytes((int)kmax));
-    w.corr = c.take<float>(M * quota_a8_corr_floats((int)kmax));
     w.sa = c.take<float>(M);
     w.qkv = c.take<f16>(M * (d + 2 * dkv));
     w.q_rot = c.take<f16>(M * d);
@@ -104,17 +103,17 @@ static int rmsnorm_quantize(const LayerWs &w, const void *x, int M, int d, const
 {
     if (M <= ROWS_PACKED)
         return quota_rmsnorm_quantize_act(x, M, d, d, gamma, eps, w.qa, w.sa, sumsq, ressq, nullptr, st);
-    return quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.corr, w.sa, sumsq, ressq, st);
+    return quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, sumsq, ressq, st);
 }
 static int silu_mul_quantize(const LayerWs &w, int M, int F, void *z, const void *z_inject, hipStream_t st)
 {
     if (M <= ROWS_PACKED) return quota_silu_mul_quantize_act(w.gu, M, F, w.qa, w.sa, z, z_inject, st);
-    return quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.corr, w.sa, z, z_inject, st);
+    return quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, z, z_inject, st);
 }
 static int gemm(const LayerWs &w, int M, const quota_weights *W, void *y, int ldy, const void *res, int ldr, hipStream_t st)
 {
     if (M <= ROWS_PACKED) return quota_w4a4_gemm(w.qa, w.sa, M, W, y, ldy, res, ldr, nullptr, st);
-    return quota_internal_w4a4_gemm_a8(w.qa, w.corr, w.sa, M, W, y, ldy, res, ldr, st);
+    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
 
 // QKV projection of the quantized rows in w.qa, RoPE at `pos`, 4-bit K/V of every row: one
@@ -139,7 +138,7 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
         qe.code_row_stride = append_to->capacity; qe.code_row_offset = append_to->len;
         qe.row_step = append_to->step_dev; qe.max_steps = append_to->max_steps;
     }
-    int rc = quota_internal_w4a4_gemm_qkv(w.qa, M <= ROWS_PACKED ? nullptr : w.corr, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
+    int rc = quota_internal_w4a4_gemm_qkv(w.qa, M > ROWS_PACKED, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
     if (rc != QUOTA_ERR_SHAPE) return rc;
     if (append_to && append_to->step_dev) return QUOTA_ERR_SHAPE;      // the device-side step needs the fused form
     TRY(gemm(w, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, st));
@@ -250,7 +249,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     ca.d = d; ca.dkv = dkv; ca.keep_idx = score ? w.keep_idx : nullptr; ca.x = s->x; ca.o = o_used; ca.pos = s->pos;
     ca.skc = w.skc; ca.sks = w.sks; ca.svc = w.svc; ca.svs = w.svs;
     ca.x_out = w.x_keep; ca.o_out = nullptr; ca.oq_out = w.qa; ca.os_out = w.sa;
-    ca.ocorr_out = Mk <= ROWS_PACKED ? nullptr : w.corr;
+    ca.oq_a8 = Mk > ROWS_PACKED;
     ca.pos_out = s->pos_out; ca.rows_out = w.rows;
     ca.cache = cache;
     TRY(quota_internal_compact(&ca, st));
@@ -310,7 +309,7 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
 
     if (B <= ROWS_PACKED) TRY(quota_quantize_act(o_used, B, d, d, w.qa, w.sa, nullptr, nullptr, st));
-    else TRY(quota_internal_quantize_a8(o_used, B, d, w.qa, w.corr, w.sa, st));
+    else TRY(quota_internal_quantize_a8(o_used, B, d, w.qa, w.sa, st));
     TRY(gemm(w, B, &L->o, w.x1, d, x_f16, d, st));
     TRY(dump(t->x1, w.x1, (size_t)B * d * 2, st));
     TRY(rmsnorm_quantize(w, w.x1, B, d, L->gamma2, L->eps, nullptr, nullptr, st));

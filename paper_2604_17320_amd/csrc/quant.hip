@@ -392,12 +392,12 @@ extern "C" int quota_rmsnorm_quantize_act(const void *x_f16, int M, int d, int l
 }
 
 int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa8,
-                                       float *corr, float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st)
+                                       float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st)
 {
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, RowOutA8{(uint2 *)qa8, corr, M}, scale, sumsq_opt, ressq_opt,
+    return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, RowOutA8{(uint2 *)qa8}, scale, sumsq_opt, ressq_opt,
                             nullptr, st);
 }
 
@@ -437,17 +437,17 @@ extern "C" int quota_silu_mul_quantize_act(const void *gu_f16, int M, int F, uin
                              (hipStream_t)stream);
 }
 
-int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *corr, float *scale,
+int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *scale,
                                         void *z_opt, const void *z_inject_opt, hipStream_t st)
 {
     int rc = check_rows(gu_f16, M, F, F, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    return silu_mul_quantize(gu_f16, M, F, RowOutA8{(uint2 *)qa8, corr, M}, scale, z_opt, z_inject_opt, st);
+    return silu_mul_quantize(gu_f16, M, F, RowOutA8{(uint2 *)qa8}, scale, z_opt, z_inject_opt, st);
 }
 
 // Per-token quantizer of a dense fp16 [M][d] into the A8 format.
-int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *corr, float *scale, hipStream_t st)
+int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st)
 {
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK) return rc;
@@ -456,7 +456,7 @@ int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, fl
     const bool many = d > 16384, few = (d >> 3) <= 512;
     auto kernel = many ? quantize_act_kernel<false, 256, 16, RowOutA8>
                        : few ? quantize_act_kernel<false, 256, 2, RowOutA8> : quantize_act_kernel<false, 256, 8, RowOutA8>;
-    kernel<<<dim3(M), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, RowOutA8{(uint2 *)qa8, corr, M}, scale,
+    kernel<<<dim3(M), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, RowOutA8{(uint2 *)qa8}, scale,
                                                   nullptr, nullptr);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
