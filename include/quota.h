@@ -407,8 +407,8 @@ size_t quota_fp_block_workspace_bytes(const quota_fp_layer *L, int B, int N);
  * q|k|v projection, rotate-half RoPE at pos, causal softmax attention with
  * grouped K/V heads, output projection + residual, RMSNorm, SwiGLU, +
  * residual) on x fp16 [B][N][d], fp16 storage between the steps, fp32
- * accumulation, nothing quantized.  x_out fp16 [B][N][d].  Calibration-time
- * code, not tuned.  ws: quota_fp_block_workspace_bytes bytes.
+ * accumulation, nothing quantized.  x_out fp16 [B][N][d].
+ * ws: quota_fp_block_workspace_bytes bytes.
  * QUOTA_ERR_SHAPE for dh not 64 / 128, H % Hkv != 0, F % 32 != 0. */
 int quota_fp_block(const quota_fp_layer *L, const void *x_f16, const int32_t *pos,
                    int B, int N, void *x_out_f16, void *ws, void *stream);

@@ -1,60 +1,124 @@
 // Sensitivity profiling for the offline allocator (Eq. 1): the full-precision counterpart of a
 // decoder block -- fp16 storage, fp32 accumulation, no quantizer anywhere -- the per-sample
 // deviation norms ||x^q - x||_2 and ||x||_2, and the call that runs a block both ways on one
-// input.  This is calibration-time code, outside the deployed forward pass: the kernels are
-// plain (the GEMM reads its operands straight from global memory into fp16 MFMA fragments) and
-// are not tuned.
+// input.  Calibration-time code, outside the deployed forward pass, but a calibration runs it for
+// every layer and sample: its time is the fp16 GEMMs'.
 #include "common.h"
 #include "internal.h"
+#include "gemm_common.h"
+#include "ldscopy.h"
 
 namespace {
 
 // ---- y = x W^T (+ residual): fp16 operands, fp32 accumulation, fp16 result ------------------
 // A workgroup of 4 waves covers 128 x 128 outputs, a wave 64 x 64 as 2 x 2 tiles of
-// v_mfma_f32_32x32x16_f16.  Lane l supplies 8 consecutive k of row (l % 32) to both operands
-// (k slots 8 (l / 32) .. +7 of the step), and receives column l % 32 of the tile, rows
-// 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.  Rows beyond M are read from row M - 1 and not
-// stored.  Needs N % 64 == 0, K % 16 == 0.
-__global__ __launch_bounds__(256) void fp_gemm_kernel(const f16 *__restrict__ x, int M, int K,
-                                                       const f16 *__restrict__ W, int N,
-                                                       const f16 *__restrict__ residual,
-                                                       f16 *__restrict__ y)
+// v_mfma_f32_32x32x16_f16.  Both operands come to LDS 64 channels at a time by asynchronous copies,
+// the next 64 on their way while the current ones are multiplied (one wait and one barrier per 64);
+// the plain form, every fragment straight from global memory, ran at 0.2 PFLOP/s because each wave
+// fetched both operands for itself.  Bound by LDS reads: 16 KB per wave and 64 channels against
+// 16 MFMAs = 512 cycles.  LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
+// Lane l supplies 8 consecutive k of row (l % 32) to both operands (k slots 8 (l / 32) .. +7 of the
+// step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.
+// Rows beyond M and N repeat the last one and are not stored.  Needs N % 64 == 0, K % 16 == 0.
+__global__ __launch_bounds__(256, 2) void fp_gemm_kernel(const f16 *__restrict__ x, int M, int K,
+                                                         const f16 *__restrict__ W, int N,
+                                                         const f16 *__restrict__ residual,
+                                                         f16 *__restrict__ y, int tiles_m, int tiles_n)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int m0 = blockIdx.y * 128 + (wave >> 1) * 64, n0 = blockIdx.x * 128 + (wave & 1) * 64;
-    if (m0 >= M || n0 >= N) return;
-    const int l32 = lane & 31, half = lane >> 5;
-    const f16 *pa[2], *pb[2];
-    for (int i = 0; i < 2; ++i) {
-        const int row = min(m0 + 32 * i + l32, M - 1);
-        pa[i] = x + (size_t)row * K + 8 * half;
-        pb[i] = W + (size_t)(n0 + 32 * i + l32) * K + 8 * half;
+    constexpr int TILE = 128 * 8;                   // 16-byte pieces of one operand per stage
+    constexpr int FROW = 128 + 4;                   // floats per staged output row
+    __shared__ uint4 lds[2][2][TILE];               // [buffer][x, W]
+    static_assert(64 * FROW * 4 <= (int)sizeof(lds), "the output strip fits");
+    const unsigned lds0 = lds_address(lds);
+    int tm, tn;
+    tile_of(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
+    const int m0 = tm * 128, n0 = tn * 128;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+    // this thread's pieces of a stage: rows (tid + 256 j) / 8 of both operands
+    unsigned ox[4], ow[4], pk[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int row = (tid + 256 * j) >> 3, p = (tid & 7) ^ (row & 7);
+        ox[j] = 2u * (unsigned)(min(m0 + row, M - 1) - m0) * (unsigned)K;
+        ow[j] = 2u * (unsigned)(min(n0 + row, N - 1) - n0) * (unsigned)K;
+        pk[j] = 16 * p;
     }
-    f32x16 acc[2][2];
-    for (int i = 0; i < 2; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        f16x8 a[2], b[2];
-        for (int i = 0; i < 2; ++i) {
-            a[i] = *(const f16x8 *)(pa[i] + k0);
-            b[i] = *(const f16x8 *)(pb[i] + k0);
+    const f16 *xb = x + (size_t)m0 * K, *wb = W + (size_t)n0 * K;
+    auto load = [&](int buf, int k0) {
+        const unsigned left = 2u * (unsigned)(K - k0) - 16;      // last whole piece of a row (a ragged end repeats it)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const unsigned dst = lds0 + (unsigned)(buf * 2 * TILE * 16 + (wave + 4 * j) * 1024);
+            copy16_to_lds(xb + k0, ox[j] + min(pk[j], left), dst);
+            copy16_to_lds(wb + k0, ow[j] + min(pk[j], left), dst + TILE * 16);
         }
-        for (int i = 0; i < 2; ++i)
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
+    };
+    f32x16 acc[2][2];
+#pragma unroll
     for (int i = 0; i < 2; ++i)
+#pragma unroll
         for (int j = 0; j < 2; ++j)
-            for (int r = 0; r < 16; ++r) {
-                const int row = m0 + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3);
-                const int col = n0 + 32 * j + l32;
-                if (row < M) {
-                    float v = acc[i][j][r];
-                    if (residual) v += (float)residual[(size_t)row * N + col];
-                    y[(size_t)row * N + col] = (f16)v;
-                }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    load(0, 0);
+    drain();
+    __syncthreads();
+    int buf = 0;
+#pragma unroll 1
+    for (int k0 = 0; k0 < K; k0 += 64) {
+        if (k0 + 64 < K) load(buf ^ 1, k0 + 64);
+        const uint4 *ax = lds[buf][0] + (64 * wm + l32) * 8, *bx = lds[buf][1] + (64 * wn + l32) * 8;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s && k0 + 16 * s >= K) break;
+            const int p = (2 * s + half) ^ (l32 & 7);
+            f16x8 a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[i] = *reinterpret_cast<const f16x8 *>(ax + 256 * i + p);
+                b[i] = *reinterpret_cast<const f16x8 *>(bx + 256 * i + p);
             }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+        drain();
+        __syncthreads();
+        buf ^= 1;
+    }
+    // 2 x 32 rows at a time through LDS, so that a thread finishes 8 neighbouring columns of a row
+    float *stage = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (i) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                stage[(32 * wm + 8 * (r >> 2) + 4 * half + (r & 3)) * FROW + 64 * wn + 32 * j + l32] = acc[i][j][r];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int idx = k * 256 + tid, row = idx >> 4, c = 8 * (idx & 15);
+            const int m = m0 + 64 * (row >> 5) + 32 * i + (row & 31), n = n0 + c;
+            if (m >= M || n >= N) continue;
+            const float4 lo = *reinterpret_cast<const float4 *>(stage + row * FROW + c);
+            const float4 hi = *reinterpret_cast<const float4 *>(stage + row * FROW + c + 4);
+            float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            Pack16 o, rv;
+            if (residual) {
+                rv.u = *reinterpret_cast<const uint4 *>(residual + (size_t)m * N + n);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += (float)rv.h[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o.h[e] = (f16)v[e];
+            *reinterpret_cast<uint4 *>(y + (size_t)m * N + n) = o.u;
+        }
+    }
 }
 
 // ---- h = x / sqrt(mean(x^2) + eps) * gamma, one workgroup per row ------------------------------
@@ -63,23 +127,32 @@ __global__ __launch_bounds__(256) void fp_rmsnorm_kernel(const f16 *__restrict__
                                                           f16 *__restrict__ h)
 {
     __shared__ float part[4];
-    const f16 *row = x + (size_t)blockIdx.x * d;
+    const uint4 *row = reinterpret_cast<const uint4 *>(x + (size_t)blockIdx.x * d);
+    uint4 *out = reinterpret_cast<uint4 *>(h + (size_t)blockIdx.x * d);
     float s = 0.0f;
-    for (int c = threadIdx.x; c < d; c += 256) {
-        const float v = (float)row[c];
-        s += v * v;
+    for (int c = threadIdx.x; c < d >> 3; c += 256) {
+        Pack16 v;
+        v.u = row[c];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += (float)v.h[e] * (float)v.h[e];
     }
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
     const float inv = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)d + eps);
-    for (int c = threadIdx.x; c < d; c += 256)
-        h[(size_t)blockIdx.x * d + c] = (f16)((float)row[c] * inv * gamma[c]);
+    for (int c = threadIdx.x; c < d >> 3; c += 256) {
+        Pack16 v;
+        v.u = row[c];
+        const float4 g0 = *reinterpret_cast<const float4 *>(gamma + 8 * c), g1 = *reinterpret_cast<const float4 *>(gamma + 8 * c + 4);
+        const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v.h[e] = (f16)((float)v.h[e] * inv * gm[e]);
+        out[c] = v.u;
+    }
 }
 
 // ---- rotate-half RoPE of q and k at the tokens' position ids; v is copied --------------------
-// qkv [M][d + 2 dkv] -> q [M][d], k [M][dkv], v [M][dkv].  One thread per (row, pair) of q | k and
-// per element pair of v.
+// qkv [M][d + 2 dkv] -> q [M][d], k [M][dkv], v [M][dkv].  One thread per 8 channels.
 __global__ __launch_bounds__(256) void fp_rope_kernel(const f16 *__restrict__ qkv, int M, int d, int dkv,
                                                        int dh, const int32_t *__restrict__ pos,
                                                        const float *__restrict__ cosT,
@@ -87,57 +160,82 @@ __global__ __launch_bounds__(256) void fp_rope_kernel(const f16 *__restrict__ qk
                                                        f16 *__restrict__ q, f16 *__restrict__ k,
                                                        f16 *__restrict__ v)
 {
-    const int hd = dh / 2, per_row = (d + 2 * dkv) / 2;
+    const int hd = dh / 2, per_row = (d + 2 * dkv) / 8;
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (long)M * per_row) return;
-    const int m = (int)(idx / per_row), t = (int)(idx % per_row);
+    const int m = (int)(idx / per_row), c = 8 * (int)(idx % per_row);
     const f16 *src = qkv + (size_t)m * (d + 2 * dkv);
-    if (t < (d + dkv) / 2) {                       // a rotated pair of q or k
-        const int head = t / hd, i = t % hd;
+    Pack16 x;
+    x.u = *reinterpret_cast<const uint4 *>(src + c);
+    if (c < d + dkv) {                             // 8 rotated channels of q or k
+        const int in = c % dh, i = in % hd;        // place inside the head, first pair
+        const bool second = in >= hd;
+        Pack16 xp;
+        xp.u = *reinterpret_cast<const uint4 *>(src + (second ? c - hd : c + hd));
         const int p = min(max(pos[m], 0), n_pos - 1);
-        const float c = cosT[(size_t)p * hd + i], s = sinT[(size_t)p * hd + i];
-        const float lo = (float)src[head * dh + i], hi = (float)src[head * dh + i + hd];
-        const f16 rlo = (f16)(lo * c - hi * s), rhi = (f16)(hi * c + lo * s);
-        const int col = head * dh + i;
-        if (col < d) {
-            q[(size_t)m * d + col] = rlo;
-            q[(size_t)m * d + col + hd] = rhi;
-        } else {
-            k[(size_t)m * dkv + col - d] = rlo;
-            k[(size_t)m * dkv + col - d + hd] = rhi;
+        const float *cp = cosT + (size_t)p * hd + i, *sp = sinT + (size_t)p * hd + i;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float a = (float)x.h[e] * cp[e], b = (float)xp.h[e] * sp[e];
+            x.h[e] = (f16)(second ? a + b : a - b);
         }
+        if (c < d) *reinterpret_cast<uint4 *>(q + (size_t)m * d + c) = x.u;
+        else *reinterpret_cast<uint4 *>(k + (size_t)m * dkv + c - d) = x.u;
     } else {
-        const int e = 2 * (t - (d + dkv) / 2);
-        v[(size_t)m * dkv + e] = src[d + dkv + e];
-        v[(size_t)m * dkv + e + 1] = src[d + dkv + e + 1];
+        *reinterpret_cast<uint4 *>(v + (size_t)m * dkv + c - d - dkv) = x.u;
     }
 }
 
-// ---- z = silu(gate) * up, gu [M][2F] rows gate | up ------------------------------------------
+// ---- z = silu(gate) * up, gu [M][2F] rows gate | up; one thread per 8 channels ------------------
 __global__ __launch_bounds__(256) void fp_silu_mul_kernel(const f16 *__restrict__ gu, long M, int F,
                                                            f16 *__restrict__ z)
 {
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * F) return;
-    const long m = idx / F;
-    const int f = (int)(idx % F);
-    const float g = (float)gu[m * 2 * F + f], u = (float)gu[m * 2 * F + F + f];
-    z[idx] = (f16)(g / (1.0f + expf(-g)) * u);
+    if (idx >= M * (F / 8)) return;
+    const long m = idx / (F / 8);
+    const int f = 8 * (int)(idx % (F / 8));
+    Pack16 g, u;
+    g.u = *reinterpret_cast<const uint4 *>(gu + m * 2 * F + f);
+    u.u = *reinterpret_cast<const uint4 *>(gu + m * 2 * F + F + f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float gv = (float)g.h[e];
+        g.h[e] = (f16)(gv / (1.0f + expf(-gv)) * (float)u.h[e]);
+    }
+    *reinterpret_cast<uint4 *>(z + m * F + f) = g.u;
 }
 
 // ---- Eq. 1 per sample: ||x^q - x||_2 and ||x||_2 over the n values of sample blockIdx.x --------
+// gridDim.y workgroups share a sample: with `part` they leave their sums in part[sample][workgroup]
+// for deviation_finish_kernel; without it one workgroup does the sample alone (one workgroup pulls
+// some 20 GB/s out of memory with 2-byte loads: 1.2 ms for two 640 x 4096 samples, 0.01 ms shared).
+constexpr int DEV_PARTS = 64;
 __global__ __launch_bounds__(1024) void deviation_kernel(const f16 *__restrict__ xq,
-                                                          const f16 *__restrict__ x, long n,
+                                                          const f16 *__restrict__ x, long n, int vec,
+                                                          double *__restrict__ part_out,
                                                           double *__restrict__ diff_norm,
                                                           double *__restrict__ ref_norm)
 {
     __shared__ double part[2][16];
     const f16 *a = xq + (size_t)blockIdx.x * n, *b = x + (size_t)blockIdx.x * n;
     double sd = 0.0, sr = 0.0;
-    for (long i = threadIdx.x; i < n; i += 1024) {
-        const double r = (double)(float)b[i], e = (double)(float)a[i] - r;
+    auto add = [&](f16 av, f16 bv) {
+        const double r = (double)(float)bv, e = (double)(float)av - r;
         sd += e * e;
         sr += r * r;
+    };
+    const long first = (long)blockIdx.y * 1024 + threadIdx.x, step = (long)gridDim.y * 1024;
+    if (vec) {
+#pragma unroll 4
+        for (long i = first; i < n / 8; i += step) {
+            Pack16 av, bv;
+            av.u = reinterpret_cast<const uint4 *>(a)[i];
+            bv.u = reinterpret_cast<const uint4 *>(b)[i];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) add(av.h[e], bv.h[e]);
+        }
+    } else {
+        for (long i = first; i < n; i += step) add(a[i], b[i]);
     }
     sd = wave_sum(sd);
     sr = wave_sum(sr);
@@ -152,17 +250,44 @@ __global__ __launch_bounds__(1024) void deviation_kernel(const f16 *__restrict__
             td += part[0][w];
             tr += part[1][w];
         }
+        if (part_out) {
+            double *o = part_out + 2 * ((size_t)blockIdx.x * gridDim.y + blockIdx.y);
+            o[0] = td;
+            o[1] = tr;
+        } else {
+            diff_norm[blockIdx.x] = sqrt(td);
+            ref_norm[blockIdx.x] = sqrt(tr);
+        }
+    }
+}
+__global__ __launch_bounds__(64) void deviation_finish_kernel(const double *__restrict__ part,
+                                                               double *__restrict__ diff_norm,
+                                                               double *__restrict__ ref_norm)
+{
+    const double *p = part + 2 * ((size_t)blockIdx.x * DEV_PARTS + threadIdx.x);
+    const double td = wave_sum(p[0]), tr = wave_sum(p[1]);
+    if (threadIdx.x == 0) {
         diff_norm[blockIdx.x] = sqrt(td);
         ref_norm[blockIdx.x] = sqrt(tr);
     }
+}
+// part: B * DEV_PARTS * 2 doubles, or null for callers without scratch memory
+int deviation(const f16 *xq, const f16 *x, int B, long n, double *part, double *diff_norm, double *ref_norm, hipStream_t st)
+{
+    const int vec = n % 8 == 0 && ((reinterpret_cast<uintptr_t>(xq) | reinterpret_cast<uintptr_t>(x)) & 15) == 0;
+    deviation_kernel<<<dim3(B, part ? DEV_PARTS : 1), dim3(1024), 0, st>>>(xq, x, n, vec, part, diff_norm, ref_norm);
+    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    if (part) deviation_finish_kernel<<<dim3(B), dim3(64), 0, st>>>(part, diff_norm, ref_norm);
+    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    return QUOTA_OK;
 }
 
 inline size_t up256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 int fp_gemm(const f16 *x, int M, int K, const void *W, int N, const f16 *residual, f16 *y, hipStream_t st)
 {
-    fp_gemm_kernel<<<dim3((N + 127) / 128, (M + 127) / 128), dim3(256), 0, st>>>(x, M, K, (const f16 *)W, N,
-                                                                                residual, y);
+    const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
+    fp_gemm_kernel<<<dim3(tiles_m * tiles_n), dim3(256), 0, st>>>(x, M, K, (const f16 *)W, N, residual, y, tiles_m, tiles_n);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -228,8 +353,8 @@ extern "C" int quota_fp_block(const quota_fp_layer *L, const void *x_f16, const 
     fp_rmsnorm_kernel<<<dim3(M), dim3(256), 0, st>>>(x, d, L->gamma1, L->eps, w.h);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if ((rc = fp_gemm(w.h, M, d, L->wqkv, d + 2 * dkv, nullptr, w.qkv, st)) != QUOTA_OK) return rc;
-    const long pairs = (long)M * ((d + 2 * dkv) / 2);
-    fp_rope_kernel<<<dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, st>>>(
+    const long pieces = (long)M * ((d + 2 * dkv) / 8);
+    fp_rope_kernel<<<dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st>>>(
         w.qkv, M, d, dkv, dh, pos, L->cosT, L->sinT, L->n_pos, w.q, w.k, w.v);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if ((rc = quota_attention_prefill_gqa(w.q, w.k, w.v, B, N, H, Hkv, dh, 0, 0, w.o, nullptr, nullptr, w.attn,
@@ -239,7 +364,7 @@ extern "C" int quota_fp_block(const quota_fp_layer *L, const void *x_f16, const 
     fp_rmsnorm_kernel<<<dim3(M), dim3(256), 0, st>>>(w.x1, d, L->gamma2, L->eps, w.h);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if ((rc = fp_gemm(w.h, M, d, L->wgu, 2 * F, nullptr, w.gu, st)) != QUOTA_OK) return rc;
-    const long nz = (long)M * F;
+    const long nz = (long)M * (F / 8);
     fp_silu_mul_kernel<<<dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st>>>(w.gu, M, F, w.z);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return fp_gemm(w.z, M, F, L->wdown, d, w.x1, (f16 *)x_out_f16, st);
@@ -250,16 +375,15 @@ extern "C" int quota_activation_deviation(const void *xq_f16, const void *x_f16,
 {
     if (!xq_f16 || !x_f16 || !diff_norm || !ref_norm) return QUOTA_ERR_NULL;
     if (B <= 0 || n_per_sample < 0) return QUOTA_ERR_INVALID_ARG;
-    deviation_kernel<<<dim3(B), dim3(1024), 0, (hipStream_t)stream>>>((const f16 *)xq_f16, (const f16 *)x_f16,
-                                                                     n_per_sample, diff_norm, ref_norm);
-    QUOTA_RETURN_IF_LAUNCH_FAILED();
-    return QUOTA_OK;
+    return deviation((const f16 *)xq_f16, (const f16 *)x_f16, B, n_per_sample, nullptr, diff_norm, ref_norm,
+                     (hipStream_t)stream);
 }
 
 namespace {
 struct ProfileWs {
     f16 *xq, *xf;
     int32_t *pos_out;
+    double *part;
     void *rest;
     size_t bytes;
 };
@@ -272,6 +396,7 @@ ProfileWs carve_profile(void *ws, const quota_layer *Lq, const quota_fp_layer *L
     w.xq = (f16 *)take(M * d * 2);
     w.xf = (f16 *)take(M * d * 2);
     w.pos_out = (int32_t *)take(M * 4);
+    w.part = (double *)take((size_t)B * DEV_PARTS * 2 * sizeof(double));
     const size_t a = quota_prefill_workspace_bytes(Lq, B, N), b = quota_fp_block_workspace_bytes(Lf, B, N);
     w.rest = take(a > b ? a : b);           // the two runs are ordered on one stream and share it
     w.bytes = (size_t)(p - (char *)ws);
@@ -308,5 +433,5 @@ extern "C" int quota_profile_block(const quota_layer *Lq, const quota_fp_layer *
     scratch_cache->len = len0;              // the rows written are scratch: the cache is handed back as it came
     if (rc != QUOTA_OK) return rc;
     if ((rc = quota_fp_block(Lf, x_f16, pos, B, N, w.xf, w.rest, stream)) != QUOTA_OK) return rc;
-    return quota_activation_deviation(w.xq, w.xf, B, (long)N * Lf->H * Lf->dh, diff_norm, ref_norm, stream);
+    return deviation(w.xq, w.xf, B, (long)N * Lf->H * Lf->dh, w.part, diff_norm, ref_norm, (hipStream_t)stream);
 }

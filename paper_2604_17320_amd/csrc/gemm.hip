@@ -23,32 +23,13 @@
 #include "internal.h"
 #include "ropequant.h"
 #include "gemm_common.h"
+#include "ldscopy.h"
 
 namespace {
 
 // Lane l of a wave owns row (A) or column (B) l % 16 and the 32 channels number l / 16 of the group for
 // both operands, so the order of channels inside a group cancels; it receives column l % 16, rows
 // 4 (l / 16) .. + 3 of the 16 x 16 result.
-
-// 16 (4) bytes per lane from global memory to LDS, lane l at lds + 16 l (4 l), without passing registers.
-// In assembly because the compiler, which cannot tell the LDS buffers apart, would make every LDS read
-// wait for the copies just started; the kernel waits for them itself (drain) before the barrier that
-// hands the buffer over.
-__device__ __forceinline__ void copy16_to_lds(const void *base, unsigned off, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
-}
-__device__ __forceinline__ void copy4_to_lds(const void *base, unsigned off, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
-}
-// All of this wave's loads and copies have arrived.  In assembly, because the compiler drops a wait that
-// it thinks has nothing to wait for; the builtin as well, so that it knows its own loads have arrived.
-__device__ __forceinline__ void drain()
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-}
 
 // Workgroup tile (16 RT) x (16 CT NW): NW waves side by side, each with all rows and its own 16 CT
 // columns, so a weight is read and unpacked by exactly one wave and never touches LDS, while activations
@@ -79,7 +60,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
     constexpr int LDS_A = 2 * STG, LDS_Q = QKV ? 32 * TROW / 8 : 32 * FROW / 4;
     __shared__ uint4 lds_raw[LDS_A > LDS_Q ? LDS_A : LDS_Q];
-    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)lds_raw;
+    const unsigned lds0 = lds_address(lds_raw);
 
     int tile_m, tile_n;
     tile_of(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tile_m, tile_n);
