@@ -33,6 +33,83 @@ __global__ __launch_bounds__(256) void quantize_weights_kernel(
     if (k + 1 < K) codes[(size_t)n * K + k + 1] = (int8_t)code_from(rintf(v1 / s));
 }
 
+// The same for rows of whole 8-channel chunks: a thread owns chunks of 8 channels (two 16-byte loads,
+// one 8-byte store), the 16 chunks of a group are 16 neighbouring lanes that share their absmax by row
+// rotations.  Four chunks per thread are loaded before the first is used: bound by HBM (5 bytes per
+// weight); 22016 x 4096: 159 us with 2 channels per lane and one load in flight.
+constexpr int QW_UN = 4;
+__global__ __launch_bounds__(256) void quantize_weights8_kernel(
+    const float *__restrict__ w, int K, int G, long total, int8_t *__restrict__ codes,
+    f16 *__restrict__ scales)
+{
+    float v[QW_UN][8];
+    long item[QW_UN];
+#pragma unroll
+    for (int u = 0; u < QW_UN; ++u) {
+        item[u] = ((long)blockIdx.x * QW_UN + u) * 256 + threadIdx.x;         // (row, group, chunk) in order
+        const long ng = min(item[u], total - 1) >> 4;
+        const int n = (int)(ng / G), k = (int)(ng % G) * QUOTA_GROUP_W + 8 * (threadIdx.x & 15);
+        const float4 *src = reinterpret_cast<const float4 *>(w + (size_t)n * K + min(k, K - 8));
+        *reinterpret_cast<float4 *>(v[u]) = src[0];
+        *reinterpret_cast<float4 *>(v[u] + 4) = src[1];
+    }
+#pragma unroll
+    for (int u = 0; u < QW_UN; ++u) {
+        const long ng = item[u] >> 4;
+        const int n = (int)(ng / G), g = (int)(ng % G), k = g * QUOTA_GROUP_W + 8 * (threadIdx.x & 15);
+        float a = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(v[u][e]));      // (a clamped chunk repeats one of the group's)
+#define STEP(ctrl)                                                                                        \
+    a = fmaxf(a, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(a), __float_as_int(a), ctrl, 0xf, 0xf, false)))
+        STEP(0x121); STEP(0x122); STEP(0x124); STEP(0x128);            // rotations of a row of 16 lanes
+#undef STEP
+        f16 sh = to_f16(a / 7.0f);
+        float s = (float)sh;
+        if (a == 0.0f || s == 0.0f) { sh = (f16)1.0f; s = 1.0f; }
+        if (item[u] >= total) continue;
+        if ((threadIdx.x & 15) == 0) scales[ng] = sh;
+        if (k < K) {
+            uint32_t o[2] = {0, 0};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e >> 2] |= (uint32_t)(uint8_t)(int8_t)code_from(rintf(v[u][e] / s)) << (8 * (e & 3));
+            *reinterpret_cast<uint2 *>(codes + (size_t)n * K + k) = make_uint2(o[0], o[1]);
+        }
+    }
+}
+
+// four int8 codes (bytes) -> four nibbles in the low half
+__device__ __forceinline__ uint32_t nibbles4(uint32_t b)
+{
+    b &= 0x0F0F0F0Fu;
+    b |= b >> 4;                                    // nibble pairs in bytes 0 and 2
+    return (b & 0xFFu) | ((b >> 8) & 0xFF00u);
+}
+
+// The repack for aligned codes: a thread turns 32 codes (two 16-byte loads, K is a multiple of 32) into
+// the 16-byte piece number t % 4 of row n in group g.
+__global__ __launch_bounds__(256) void pack_weights16_kernel(
+    const int8_t *__restrict__ codes, const f16 *__restrict__ scales, int N, int K, int G,
+    uint4 *__restrict__ packed, f16 *__restrict__ scales_t)
+{
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    if (t >= (long)G * N * 4) return;
+    const int i = (int)(t & 3);
+    const long gn = t >> 2;
+    const int n = (int)(gn % N), g = (int)(gn / N), k = g * QUOTA_GROUP_W + 32 * i;
+    uint4 o = make_uint4(0, 0, 0, 0);
+    if (k < K) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(codes + (size_t)n * K + k);
+        const uint4 a = src[0], b = src[1];
+        o.x = nibbles4(a.x) | nibbles4(a.y) << 16;
+        o.y = nibbles4(a.z) | nibbles4(a.w) << 16;
+        o.z = nibbles4(b.x) | nibbles4(b.y) << 16;
+        o.w = nibbles4(b.z) | nibbles4(b.w) << 16;
+    }
+    packed[t] = o;
+    if (i == 0) scales_t[(size_t)g * N + n] = scales[(size_t)n * G + g];
+}
+
 // codes int8 [N][K] -> packed [G][N][16 dwords]; scales [N][G] -> [G][N]
 __global__ __launch_bounds__(256) void pack_weights_kernel(
     const int8_t *__restrict__ codes, const f16 *__restrict__ scales, int N, int K, int G,
@@ -290,8 +367,12 @@ extern "C" int quota_quantize_weights(const float *w, int N, int K, int8_t *code
     int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     long waves = (long)N * G;
     ProfScope prof(QUOTA_K_QUANTIZE_WEIGHTS, 0, 5.0 * N * K + 2.0 * N * G, (hipStream_t)stream);
-    quantize_weights_kernel<<<dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, (hipStream_t)stream>>>(
-        w, N, K, G, codes, (f16 *)scales_f16);
+    if (K % 8 == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0 && (reinterpret_cast<uintptr_t>(codes) & 7) == 0)
+        quantize_weights8_kernel<<<dim3((unsigned)((16 * waves + 256 * QW_UN - 1) / (256 * QW_UN))), dim3(256), 0,
+                                   (hipStream_t)stream>>>(w, K, G, 16 * waves, codes, (f16 *)scales_f16);
+    else
+        quantize_weights_kernel<<<dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, (hipStream_t)stream>>>(
+            w, N, K, G, codes, (f16 *)scales_f16);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -305,8 +386,12 @@ extern "C" int quota_pack_weights(const int8_t *codes, const void *scales_f16,
     int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     long total = (long)G * W->N * 16;
     ProfScope prof(QUOTA_K_PACK_WEIGHTS, 0, 1.5 * W->N * W->K + 4.0 * W->N * G, (hipStream_t)stream);
-    pack_weights_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
-        codes, (const f16 *)scales_f16, W->N, W->K, G, (uint32_t *)W->packed, (f16 *)W->scales);
+    if (((reinterpret_cast<uintptr_t>(codes) | reinterpret_cast<uintptr_t>(W->packed)) & 15) == 0)
+        pack_weights16_kernel<<<dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
+            codes, (const f16 *)scales_f16, W->N, W->K, G, (uint4 *)W->packed, (f16 *)W->scales);
+    else
+        pack_weights_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
+            codes, (const f16 *)scales_f16, W->N, W->K, G, (uint32_t *)W->packed, (f16 *)W->scales);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

@@ -61,7 +61,9 @@ CLASSES = [
     ("compact_rows_kernel", "compact_rows"),
     ("decode_attention_kernel", "attention_decode"),
     ("kv_append_rows_kernel", "kv_append_rows"),
+    ("quantize_weights8_kernel", "quantize_weights"),
     ("quantize_weights_kernel", "quantize_weights"),
+    ("pack_weights16_kernel", "pack_weights"),
     ("pack_weights_kernel", "pack_weights"),
 ]
 
