@@ -117,5 +117,18 @@ __device__ __forceinline__ uint32_t code_bits(float t)
 // Units of the fp8 GEMM operands: code / 512 is an e4m3 number for every int4 code, so a group's
 // accumulator counts in 2^-18 (see gemm.hip).
 #define F8_UNIT 262144.0f
+__device__ __forceinline__ float code_unit(uint32_t bits)       // code / 512, exact
+{
+    return __builtin_fmaf(__uint_as_float(bits), 1.0f / 512.0f, -ROW_MAGIC / 512.0f);
+}
+// 8 such units as e4m3 bytes, evens then odds
+__device__ __forceinline__ uint2 units_to_e4m3(const float unit[8])
+{
+    int lo = __builtin_amdgcn_cvt_pk_fp8_f32(unit[0], unit[2], 0, false);
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(unit[4], unit[6], lo, true);
+    int hi = __builtin_amdgcn_cvt_pk_fp8_f32(unit[1], unit[3], 0, false);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(unit[5], unit[7], hi, true);
+    return make_uint2((uint32_t)lo, (uint32_t)hi);
+}
 __device__ __forceinline__ float code_float(uint32_t bits) { return __uint_as_float(bits) - ROW_MAGIC; }
 

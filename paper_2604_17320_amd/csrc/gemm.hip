@@ -303,7 +303,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         const int region = n0 < d ? 0 : (n0 < d + dkv ? 1 : 2);          // tile-uniform
         const int c0 = n0 - (region == 0 ? 0 : (region == 1 ? d : d + dkv));
         const int CPH = qe.dh >> 3, HALF = CPH >> 1, cpr = dkv >> 3, gpr = dkv >> 6;
-        const int row_step = qe.row_step ? min(max(*qe.row_step, 0), qe.max_steps - 1) : 0;
 #pragma unroll
         for (int ib = 0; ib < RT / 2; ++ib) {
             if (ib) __syncthreads();                  // the previous 32 rows have been read
@@ -357,9 +356,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                         uint32_t *codes = region == 1 ? qe.k_codes : qe.v_codes;
                         f16 *scales = region == 1 ? qe.k_scales : qe.v_scales;
                         *reinterpret_cast<uint4 *>(xh + (size_t)m * dkv + col) = hat.u;
-                        const size_t orow = (size_t)m * qe.code_row_stride + qe.code_row_offset + row_step;
-                        codes[orow * cpr + (col >> 3)] = word;
-                        if ((c & 7) == 0) scales[orow * gpr + (col >> 6)] = sc8;
+                        codes[(size_t)m * cpr + (col >> 3)] = word;
+                        if ((c & 7) == 0) scales[(size_t)m * gpr + (col >> 6)] = sc8;
                     }
                 }
             }
@@ -414,121 +412,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 for (int e = 0; e < 8; ++e) yp[e] = o.h[e];
         }
     }
-}
-
-// ---- at most 16 rows (the decode step): weight streaming -------------------------------
-// With M <= 16 the GEMM has too few outputs to fill the chip with one accumulation chain per
-// wave, and the fp32 chain over groups cannot be split.  The exact int32 group sums can: in a round
-// the 8 waves of a workgroup take U groups each (group r0 + 8 u + w for wave w: all their loads in
-// flight together, U * 8 groups = 2 KB of weights per column block and round), park their 16 x 16
-// int32 results in LDS, and one thread per output then runs the fp32 chain over those 8 U groups in
-// ascending order.  Operands need no LDS: for v_mfma_i32_16x16x64_i8 a lane owns (row or column
-// l % 16, 16 k-slots l / 16), so lane l loads the 16 packed bytes (32 codes) number l / 16 of its
-// row's group for A and of its column's group for B, and the even / odd nibble vectors feed two
-// MFMAs.  NB = 16-column blocks per workgroup.
-template <int NB, int U>
-__global__ __launch_bounds__(512) void w4a4_gemv16_kernel(
-    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
-    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr)
-{
-    constexpr int R = 8 * U;                    // groups per round
-    __shared__ int accs[R][NB][4][64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, q = lane >> 4;
-    const int n0 = blockIdx.x * 16 * NB, Kb = K >> 1;
-    const uint8_t *arow = qa + (size_t)min(c, M - 1) * Kb;
-
-    // chain ownership: thread t < 256 * NB owns the output held by (block j, register reg, lane ol)
-    const int oj = tid >> 8, oreg = (tid >> 6) & 3, ol = tid & 63;
-    const bool owner = tid < 256 * NB;
-    const int om = 4 * (ol >> 4) + oreg, on = n0 + 16 * oj + (ol & 15);
-    float y32 = 0.0f;
-
-    // The R x (16 NB) group scales of a round come in with ONE 8-byte load per lane of waves 0..NB-1
-    // (lane l: group l / 4 of the round, 4 columns) and reach the chain owners through LDS, transposed
-    // so that an owner reads its column's R scales as two 16-byte pieces: a vector-memory instruction
-    // costs a wave tens of issue cycles, and R of them per owner and round were a third of the round.
-    static_assert(R == 16, "the scale staging below is laid out for 16 groups per round");
-    __shared__ __align__(16) f16 scs[16 * NB][R];
-    uint4 ra[U], rb[U][NB];
-    uint2 rsv = make_uint2(0, 0);
-    auto fetch = [&](int r0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int g = min(r0 + 8 * u + wave, G - 1);
-            ra[u] = *reinterpret_cast<const uint4 *>(arow + min(g * 64 + q * 16, Kb - 16));
-#pragma unroll
-            for (int j = 0; j < NB; ++j) rb[u][j] = wp[((size_t)g * N + n0 + 16 * j + c) * 4 + q];
-        }
-        if (wave < NB)
-            rsv = *reinterpret_cast<const uint2 *>(sw + (size_t)min(r0 + (lane >> 2), G - 1) * N + n0 + 16 * wave +
-                                                   4 * (lane & 3));
-    };
-    fetch(0);
-    for (int r0 = 0; r0 < G; r0 += R) {
-        i32x4 acc[U][NB];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            uint4 alo, ahi;
-            unpack16(ra[u], alo, ahi);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                uint4 blo, bhi;
-                unpack16(rb[u][j], blo, bhi);
-                acc[u][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_i32x4(alo), as_i32x4(blo), i32x4{0, 0, 0, 0}, 0, 0, 0);
-                acc[u][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(as_i32x4(ahi), as_i32x4(bhi), acc[u][j], 0, 0, 0);
-            }
-        }
-        if (wave < NB) {                            // this round's scales -> LDS, [column][group]
-            const int col = 16 * wave + 4 * (lane & 3), gi = lane >> 2;
-            Pack16 t;
-            t.u = make_uint4(rsv.x, rsv.y, 0, 0);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) scs[col + e][gi] = t.h[e];
-        }
-        bool live[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) live[u] = r0 + 8 * u + wave < G;
-        if (r0 + R < G) fetch(r0 + R);              // next round's loads fly during the exchange
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) accs[8 * u + wave][j][i][lane] = live[u] ? acc[u][j][i] : 0;
-        __syncthreads();
-        if (owner) {
-            Pack16 s0, s1;
-            const uint4 *sp = reinterpret_cast<const uint4 *>(&scs[16 * oj + (ol & 15)][0]);
-            s0.u = sp[0];
-            s1.u = sp[1];
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const float sc = r0 + i < G ? (float)(i < 8 ? s0.h[i] : s1.h[i - 8]) : 0.0f;
-                y32 = __builtin_fmaf((float)accs[i][oj][oreg][ol], sc, y32);
-            }
-        }
-        __syncthreads();
-    }
-    if (owner && om < M) {
-        float v = y32 * (sa[om] * 0.00390625f);
-        if (res) v = v + (float)res[(size_t)om * ldr + on];
-        y[(size_t)om * ldy + on] = to_f16(v);
-    }
-}
-
-template <int NB, int U>
-int launch_gemv16(const uint8_t *qa, const float *sa, int M, const quota_weights *W, f16 *y, int ldy,
-                  const f16 *res, int ldr, hipStream_t st)
-{
-    const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    const double Md = M, Nd = W->N, Kd = W->K;
-    ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
-                   Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + 2.0 * Md * Nd * (res ? 2 : 1), st);
-    w4a4_gemv16_kernel<NB, U><<<dim3(W->N / (16 * NB)), dim3(512), 0, st>>>(
-        qa, sa, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr);
-    QUOTA_RETURN_IF_LAUNCH_FAILED();
-    return QUOTA_OK;
 }
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
@@ -628,6 +511,7 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
     if (!qa8 || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
     if (W->N % 64 != 0 || W->K % 32 != 0) return QUOTA_ERR_SHAPE;
     if (M <= 0) return QUOTA_OK;
+    if (M <= 16) return quota_internal_rows16(qa8, true, sa, M, W, y_f16, ldy, residual_opt, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
     return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
@@ -649,21 +533,20 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     const f16 *res = (const f16 *)residual_opt;
     if (acc_i32_opt)
         return launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
-    if (M <= 16)            // the decode step: stream the weights once, groups spread over 8 waves
-        return W->N <= 8192 ? launch_gemv16<1, 2>(qa, sa, M, W, y, ldy, res, ldr, st)
-                            : launch_gemv16<2, 2>(qa, sa, M, W, y, ldy, res, ldr, st);
+    if (M <= 16)            // the decode step: stream the weights once
+        return quota_internal_rows16(qa, false, sa, M, W, y, ldy, res, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
     return launch_f8(tile_kernel<true, false>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
 // QKV projection with the RoPE + 4-bit K/V quantizer fused into the epilogue (see the kernel).
-// a8: qa is in the A8 format; otherwise packed int4 (few rows: the 32-row tile).
+// qa8 is in the A8 format.
 // y_opt, when not null, also receives the plain fp16 q | k | v.  Returns QUOTA_ERR_SHAPE when the
 // shape does not fit the fused form (the caller then runs the two kernels separately).
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st)
 {
-    if (!qa || !sa || !W || !W->packed || !W->scales || !qe || !qe->pos || !qe->cosT || !qe->sinT ||
+    if (!qa8 || !sa || !W || !W->packed || !W->scales || !qe || !qe->pos || !qe->cosT || !qe->sinT ||
         !qe->q_rot || !qe->khat || !qe->vhat || !qe->k_codes || !qe->k_scales || !qe->v_codes || !qe->v_scales)
         return QUOTA_ERR_NULL;
     if (M < 0 || qe->n_pos <= 0) return QUOTA_ERR_INVALID_ARG;
@@ -672,7 +555,7 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, bool a8, const float *sa, in
         W->N != d + 2 * dkv || W->K % 32 != 0)
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
-    const int v = a8 ? choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128) : 2;
-    f8_kernel kernel = a8 ? tile_kernel<false, true>(v) : F8_TILE_2(true, false, true);
-    return launch_f8(kernel, v, kTiles[v].kernel_id, qa, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0, nullptr, st, qe);
+    const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128);
+    return launch_f8(tile_kernel<false, true>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
+                     nullptr, st, qe);
 }

@@ -30,8 +30,7 @@ struct quota_compact_args {
     const int32_t *pos;
     const void *skc, *sks, *svc, *svs;     // staged 4-bit K/V of all N rows
     void *x_out, *o_out;                   // o_out optional (fp16 copy of the kept attention rows)
-    uint8_t *oq_out;                       // optional: int4 codes of the kept attention rows ...
-    bool oq_a8;                            // ... in the A8 format, or packed ...
+    uint8_t *oq_out;                       // optional: int4 codes of the kept attention rows (A8 format) ...
     float *os_out;                         // ... and their per-token scales (the quantizer Q)
     int32_t *pos_out, *rows_out;
     quota_kv_cache *cache;
@@ -42,10 +41,13 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st);
 int quota_internal_vector_metrics(const void *v_f16, int B, int Nv, int d, int ldv, long stride_b,
                                   float *sumsq, float *ressq, hipStream_t st);
 
-// Moves the B staged (dense) 4-bit K/V rows of a decode step to row cache->len of each
-// sequence (the caller advances cache->len).  QUOTA_ERR_CAPACITY if the cache is full.
-int quota_internal_kv_append_rows(int d, const uint8_t *skc, const void *sks, const uint8_t *svc,
-                                  const void *svs, quota_kv_cache *cache, hipStream_t st);
+// Decode attention of one new token per sequence straight from its QKV projection [B][d + 2 dkv]: RoPE, 4-bit K/V
+// of the new row (appended at row cache->len, + *step_dev; len does not move), attention over the grown cache.
+// part: quota_internal_decode_part_bytes bytes.
+size_t quota_internal_decode_part_bytes(int B, int H, int Hkv, int dh);
+int quota_internal_attention_decode_new(const void *qkv_f16, const int32_t *pos, const float *cosT, const float *sinT,
+                                        int n_pos, int Hq, const quota_kv_cache *cache, void *q_rot_opt, void *o_f16,
+                                        void *part, hipStream_t st);
 
 // Arguments of the fused QKV epilogue: what quota_rope_kv_quant takes, minus the qkv input.
 struct quota_qkv_epilogue {
@@ -55,11 +57,8 @@ struct quota_qkv_epilogue {
     f16 *q_rot, *khat, *vhat;
     uint32_t *k_codes, *v_codes;
     f16 *k_scales, *v_scales;
-    long code_row_stride, code_row_offset;   // codes / scales of token row m go to row m * stride + offset
-    const int32_t *row_step;                 // optional (device): ... + clamp(*row_step, 0, max_steps - 1)
-    int max_steps;
 };
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st);
 
 // The layer's row quantizers and GEMM on activations in the A8 format (gemm.hip): M rows of
@@ -72,6 +71,18 @@ int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_
 int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st);
 int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *y_f16, int ldy,
                                 const void *residual_opt, int ldr, hipStream_t st);
+
+// GEMM of at most 16 rows (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
+// quota_internal_rows16_quantizes accepts: as they are, through RMSNorm, or gate | up rows through SwiGLU.
+int quota_internal_rows16(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W, void *y, int ldy,
+                          const void *res, int ldr, hipStream_t st);
+bool quota_internal_rows16_quantizes(int M, int K);
+int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
+                                   int ldr, hipStream_t st);
+int quota_internal_rows16_rmsnorm(const void *x, const float *gamma, float eps, int M, const quota_weights *W, void *y,
+                                  int ldy, hipStream_t st);
+int quota_internal_rows16_silu(const void *gu, void *z_out, const void *z_inject, int M, const quota_weights *W, void *y,
+                               int ldy, const void *res, int ldr, hipStream_t st);
 
 // quota_rope_kv_quant with Hkv K/V heads: qkv rows are q (H*dh) | k (Hkv*dh) | v (Hkv*dh).
 int quota_internal_rope_kv_quant(const void *qkv_f16, int M, int H, int Hkv, int dh, const int32_t *pos,

@@ -24,7 +24,7 @@ struct Carver {
 };
 
 struct LayerWs {
-    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format (packed for at most 16 rows)
+    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format
     float *sa;
     f16 *qkv, *q_rot, *khat, *vhat, *o;
     uint8_t *skc, *svc; // staged 4-bit K/V of all rows
@@ -87,41 +87,18 @@ int dump(void *dst, const void *src, size_t bytes, hipStream_t st)
 
 }  // namespace
 
-// At most this many rows take the weight-streaming GEMM, which reads packed int4 activations; more rows
-// use the A8 format end to end.
-#define ROWS_PACKED 16
-
 #define TRY(expr)                         \
     do {                                  \
         int rc_ = (expr);                 \
         if (rc_ != QUOTA_OK) return rc_;  \
     } while (0)
 
-// The four GEMM inputs of a layer: quantize M rows in the format the M-row GEMM reads, then multiply.
-static int rmsnorm_quantize(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps, float *sumsq,
-                            float *ressq, hipStream_t st)
-{
-    if (M <= ROWS_PACKED)
-        return quota_rmsnorm_quantize_act(x, M, d, d, gamma, eps, w.qa, w.sa, sumsq, ressq, nullptr, st);
-    return quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, sumsq, ressq, st);
-}
-static int silu_mul_quantize(const LayerWs &w, int M, int F, void *z, const void *z_inject, hipStream_t st)
-{
-    if (M <= ROWS_PACKED) return quota_silu_mul_quantize_act(w.gu, M, F, w.qa, w.sa, z, z_inject, st);
-    return quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, z, z_inject, st);
-}
-static int gemm(const LayerWs &w, int M, const quota_weights *W, void *y, int ldy, const void *res, int ldr, hipStream_t st)
-{
-    if (M <= ROWS_PACKED) return quota_w4a4_gemm(w.qa, w.sa, M, W, y, ldy, res, ldr, nullptr, st);
-    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
-}
-
 // QKV projection of the quantized rows in w.qa, RoPE at `pos`, 4-bit K/V of every row: one
 // kernel (the GEMM with the fused epilogue) when the shape allows it, else the GEMM followed by
 // the stand-alone RoPE/KV kernel.  Both give the same bits.  want_qkv: also keep the plain
 // projection output in w.qkv.
 static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, const int32_t *pos,
-                             bool want_qkv, hipStream_t st, quota_kv_cache *append_to = nullptr)
+                             bool want_qkv, hipStream_t st)
 {
     const int d = L->H * L->dh, Hkv = kv_heads(L), dkv = Hkv * L->dh;
     quota_qkv_epilogue qe;
@@ -130,21 +107,28 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
     qe.q_rot = w.q_rot; qe.khat = w.khat; qe.vhat = w.vhat;
     qe.k_codes = (uint32_t *)w.skc; qe.v_codes = (uint32_t *)w.svc;
     qe.k_scales = w.sks; qe.v_scales = w.svs;
-    qe.code_row_stride = 1; qe.code_row_offset = 0;
-    qe.row_step = nullptr; qe.max_steps = 1;
-    if (append_to) {        // decode: row b is sequence b's new token; its K/V go straight to cache row len
-        qe.k_codes = (uint32_t *)append_to->k_codes; qe.v_codes = (uint32_t *)append_to->v_codes;
-        qe.k_scales = (f16 *)append_to->k_scales; qe.v_scales = (f16 *)append_to->v_scales;
-        qe.code_row_stride = append_to->capacity; qe.code_row_offset = append_to->len;
-        qe.row_step = append_to->step_dev; qe.max_steps = append_to->max_steps;
-    }
-    int rc = quota_internal_w4a4_gemm_qkv(w.qa, M > ROWS_PACKED, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
+    int rc = quota_internal_w4a4_gemm_qkv(w.qa, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
     if (rc != QUOTA_ERR_SHAPE) return rc;
-    if (append_to && append_to->step_dev) return QUOTA_ERR_SHAPE;      // the device-side step needs the fused form
-    TRY(gemm(w, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, st));
-    TRY(quota_internal_rope_kv_quant(w.qkv, M, L->H, Hkv, L->dh, pos, L->cosT, L->sinT, L->n_pos, w.q_rot,
-                                     w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st));
-    return append_to ? quota_internal_kv_append_rows(dkv, w.skc, w.sks, w.svc, w.svs, append_to, st) : QUOTA_OK;
+    TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, st));
+    return quota_internal_rope_kv_quant(w.qkv, M, L->H, Hkv, L->dh, pos, L->cosT, L->sinT, L->n_pos, w.q_rot,
+                                        w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st);
+}
+
+// RMSNorm, quantizer, GEMM; and SwiGLU product, quantizer, GEMM.  A few rows leave the first two to the GEMM.
+static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
+                        const quota_weights *W, void *y, int ldy, hipStream_t st)
+{
+    if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_rmsnorm(x, gamma, eps, M, W, y, ldy, st);
+    TRY(quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
+    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
+}
+static int silu_mul_gemm(const LayerWs &w, int M, int F, void *z, const void *z_inject, const quota_weights *W, void *y,
+                         int ldy, const void *res, int ldr, hipStream_t st)
+{
+    if (quota_internal_rows16_quantizes(M, F))
+        return quota_internal_rows16_silu(w.gu, z, z_inject, M, W, y, ldy, res, ldr, st);
+    TRY(quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
+    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
 
 extern "C" size_t quota_prefill_workspace_bytes(const quota_layer *L, int B, int N)
@@ -202,7 +186,8 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
     // attention half on every token that entered the layer (the two vector cues of Eq. 6 are side
     // outputs of the first quantizer, taken only where they are used)
-    TRY(rmsnorm_quantize(w, s->x, M, d, L->gamma1, L->eps, score ? w.sumsq : nullptr, score ? w.ressq : nullptr, st));
+    TRY(quota_internal_rmsnorm_quantize_a8(s->x, M, d, L->gamma1, L->eps, w.qa, w.sa, score ? w.sumsq : nullptr,
+                                           score ? w.ressq : nullptr, st));
     TRY(qkv_rope_kv_quant(L, w, M, s->pos, t->qkv != nullptr, st));
     TRY(dump(t->qkv, w.qkv, (size_t)M * (d + 2 * dkv) * 2, st));
     TRY(dump(t->q_rot, w.q_rot, (size_t)M * d * 2, st));
@@ -249,7 +234,6 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     ca.d = d; ca.dkv = dkv; ca.keep_idx = score ? w.keep_idx : nullptr; ca.x = s->x; ca.o = o_used; ca.pos = s->pos;
     ca.skc = w.skc; ca.sks = w.sks; ca.svc = w.svc; ca.svs = w.svs;
     ca.x_out = w.x_keep; ca.o_out = nullptr; ca.oq_out = w.qa; ca.os_out = w.sa;
-    ca.oq_a8 = Mk > ROWS_PACKED;
     ca.pos_out = s->pos_out; ca.rows_out = w.rows;
     ca.cache = cache;
     TRY(quota_internal_compact(&ca, st));
@@ -257,13 +241,11 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
     // token-wise rest of the block on the kept rows only
     if (Mk > 0) {
-        TRY(gemm(w, Mk, &L->o, w.x1, d, w.x_keep, d, st));
+        TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, Mk, &L->o, w.x1, d, w.x_keep, d, st));
         TRY(dump(t->x1, w.x1, (size_t)Mk * d * 2, st));
-        TRY(rmsnorm_quantize(w, w.x1, Mk, d, L->gamma2, L->eps, nullptr, nullptr, st));
-        TRY(gemm(w, Mk, &L->gu, w.gu, 2 * F, nullptr, 0, st));
+        TRY(rmsnorm_gemm(w, w.x1, Mk, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
         TRY(dump(t->gu, w.gu, (size_t)Mk * 2 * F * 2, st));
-        TRY(silu_mul_quantize(w, Mk, F, t->z, t->inject_z, st));
-        TRY(gemm(w, Mk, &L->down, s->x_out, d, w.x1, d, st));
+        TRY(silu_mul_gemm(w, Mk, F, t->z, t->inject_z, &L->down, s->x_out, d, w.x1, d, st));
     }
     // the descriptors move only now that every step has been enqueued
     cache->len += n_keep;
@@ -274,7 +256,8 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
 extern "C" size_t quota_decode_workspace_bytes(const quota_layer *L, int B)
 {
-    return quota_prefill_workspace_bytes(L, B, 1);
+    const size_t bytes = quota_prefill_workspace_bytes(L, B, 1);
+    return bytes ? bytes + quota_internal_decode_part_bytes(B, L->H, kv_heads(L), L->dh) : 0;
 }
 
 extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const int32_t *pos, int B,
@@ -289,34 +272,32 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
     const int longest = cache->len + (stepped ? cache->max_steps : 1);
     if (longest > cache->capacity) return QUOTA_ERR_CAPACITY;
     if (longest > QUOTA_MAX_DECODE_ROWS) return QUOTA_ERR_SHAPE;
-    if (stepped && (d % 128 != 0 || dkv % 128 != 0)) return QUOTA_ERR_SHAPE;   // needs the fused QKV epilogue
+    if (stepped && (d % 128 != 0 || dkv % 128 != 0)) return QUOTA_ERR_SHAPE;
 
     hipStream_t st = (hipStream_t)stream;
     LayerWs w = carve(ws, B, 1, H, Hkv, dh, F);
     static const quota_taps no_taps = {};
     const quota_taps *t = taps ? taps : &no_taps;
 
-    TRY(rmsnorm_quantize(w, x_f16, B, d, L->gamma1, L->eps, nullptr, nullptr, st));
-    // the new token's K/V join the cache first (written by the QKV epilogue itself, or by the
-    // append kernel on the unfused path); attention then reads all of it in 4-bit form
-    TRY(qkv_rope_kv_quant(L, w, B, pos, t->qkv != nullptr, st, cache));
+    TRY(rmsnorm_gemm(w, x_f16, B, d, L->gamma1, L->eps, &L->qkv, w.qkv, d + 2 * dkv, st));
     TRY(dump(t->qkv, w.qkv, (size_t)B * (d + 2 * dkv) * 2, st));
+    // the new token's K/V join the cache inside the attention, which reads the rest of it in 4-bit form
+    TRY(quota_internal_attention_decode_new(w.qkv, pos, L->cosT, L->sinT, L->n_pos, H, cache, t->q_rot ? w.q_rot : nullptr,
+                                            w.o, (char *)ws + w.bytes, st));
     TRY(dump(t->q_rot, w.q_rot, (size_t)B * d * 2, st));
-    quota_kv_cache grown = *cache;      // what the attention reads: the row just written included
-    if (!stepped) grown.len += 1;       // (with a device-side step the kernel adds step + 1 itself)
-    TRY(quota_attention_decode_gqa(w.q_rot, H, &grown, w.o, st));
     TRY(dump(t->o, w.o, (size_t)B * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
 
-    if (B <= ROWS_PACKED) TRY(quota_quantize_act(o_used, B, d, d, w.qa, w.sa, nullptr, nullptr, st));
-    else TRY(quota_internal_quantize_a8(o_used, B, d, w.qa, w.sa, st));
-    TRY(gemm(w, B, &L->o, w.x1, d, x_f16, d, st));
+    if (quota_internal_rows16_quantizes(B, d)) {
+        TRY(quota_internal_rows16_quantize(o_used, B, &L->o, w.x1, d, x_f16, d, st));
+    } else {
+        TRY(quota_internal_quantize_a8(o_used, B, d, w.qa, w.sa, st));
+        TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, B, &L->o, w.x1, d, x_f16, d, st));
+    }
     TRY(dump(t->x1, w.x1, (size_t)B * d * 2, st));
-    TRY(rmsnorm_quantize(w, w.x1, B, d, L->gamma2, L->eps, nullptr, nullptr, st));
-    TRY(gemm(w, B, &L->gu, w.gu, 2 * F, nullptr, 0, st));
+    TRY(rmsnorm_gemm(w, w.x1, B, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
     TRY(dump(t->gu, w.gu, (size_t)B * 2 * F * 2, st));
-    TRY(silu_mul_quantize(w, B, F, t->z, t->inject_z, st));
-    TRY(gemm(w, B, &L->down, x_out_f16, d, w.x1, d, st));
+    TRY(silu_mul_gemm(w, B, F, t->z, t->inject_z, &L->down, x_out_f16, d, w.x1, d, st));
     if (!stepped) cache->len += 1;      // only now that every step has been enqueued
     return QUOTA_OK;
 }

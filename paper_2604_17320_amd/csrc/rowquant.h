@@ -52,7 +52,7 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
                 float f = live ? (float)v[r].h[e] : 0.0f;
                 const uint32_t cb = code_bits(f * inv);
                 if (OUT::A8) {
-                    unit[e] = __builtin_fmaf(__uint_as_float(cb), 1.0f / 512.0f, -ROW_MAGIC / 512.0f);  // code / 512, exact
+                    unit[e] = code_unit(cb);
                 } else {
                     word |= (cb & 0xFu) << (4 * e);
                 }
@@ -63,11 +63,7 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
                 }
             }
             if constexpr (OUT::A8) {
-                int lo = __builtin_amdgcn_cvt_pk_fp8_f32(unit[0], unit[2], 0, false);
-                lo = __builtin_amdgcn_cvt_pk_fp8_f32(unit[4], unit[6], lo, true);
-                int hi = __builtin_amdgcn_cvt_pk_fp8_f32(unit[1], unit[3], 0, false);
-                hi = __builtin_amdgcn_cvt_pk_fp8_f32(unit[5], unit[7], hi, true);
-                out.q[c] = make_uint2((uint32_t)lo, (uint32_t)hi);
+                out.q[c] = units_to_e4m3(unit);
             } else {
                 if (out.q) out.q[c] = word;
             }

@@ -1,0 +1,366 @@
+// W4A4 GEMM for at most 16 rows (the decode step): weight streaming, bound by HBM (0.52 bytes per weight).
+//
+// There are too few outputs to fill the chip with one accumulation chain per wave, and the fp32 chain over
+// groups cannot be split.  The exact group sums can: in a round the 8 waves of a workgroup take U groups
+// each (group r0 + 8 u + w for wave w: all their loads in flight together), park their 16 x 16 sums in
+// LDS, and one thread per output then runs the fp32 chain over those 8 U groups in ascending order -- the
+// same bits as the tiled kernel.  Weights and activations are fp8 operands as there (gemm.hip): one
+// v_mfma_f32_16x16x128_f8f6f4 per group and 16 columns, one more against the constant -8 / 512 per group.
+// NB = 16-column blocks per workgroup.
+//
+// Few rows (MODE > PACKED) also bring their own quantizer: every workgroup normalises / multiplies / quantizes
+// the whole rows for itself while its first weights are on their way.  That is a few thousand elements per
+// row, read from L2, against a launch and a pass of 16 workgroups that cost 4 to 5 us; from five rows on
+// the repeated work costs more than the launch.
+#include "common.h"
+#include "internal.h"
+#include "gemm_common.h"
+#include "ldsgrant.h"
+
+namespace {
+
+enum { ROWS_A8 = 0, ROWS_PACKED, ROWS_QUANT, ROWS_RMSNORM, ROWS_SILU };
+
+struct RowsIn {
+    const uint8_t *qa;          // A8 / PACKED: activations and token scales
+    const float *sa;
+    const f16 *x;               // QUANT, RMSNORM: rows [M][K]; SILU: gate | up rows [M][2K]
+    const float *gamma;         // RMSNORM
+    float eps;
+    f16 *z_out;                 // SILU: optional dump of / replacement for the product
+    const f16 *z_inject;
+};
+
+constexpr int RT_THREADS = 512;
+
+// The rows' quantizer: 8 / rows (rounded to a power of two) waves per row, a thread caches its NC chunks of 8
+// channels; the same arithmetic as the row kernels in quant.hip.  Leaves e4m3 rows of `stride` bytes and
+// the token scales in LDS.
+template <int MODE, int NC>
+__device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, int G, uint8_t *codes, int stride,
+                                              float *scales, double *red)
+{
+    const int wpr = M == 1 ? 8 : M == 2 ? 4 : 2;            // waves per row
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = wave / wpr, part = wave % wpr;
+    const int T = 64 * wpr, idx = part * 64 + lane, nchunk = K >> 3;
+    const bool live = row < M;
+    const int r = live ? row : M - 1;
+    auto combine = [&](float &mx, double &s) {              // over the waves of a row
+        mx = wave_max(mx);
+        if (MODE == ROWS_RMSNORM) s = wave_sum(s);
+        __syncthreads();
+        if (lane == 0) { red[2 * wave] = (double)mx; red[2 * wave + 1] = s; }
+        __syncthreads();
+        mx = 0.0f;
+        s = 0.0;
+        for (int w = 0; w < wpr; ++w) {
+            mx = fmaxf(mx, (float)red[2 * (row * wpr + w)]);
+            s += red[2 * (row * wpr + w) + 1];
+        }
+    };
+    Pack16 v[NC];
+    float a = 0.0f;
+    double ss = 0.0;
+    if (MODE == ROWS_SILU) {
+        const uint4 *gr = reinterpret_cast<const uint4 *>(in.x + (size_t)r * 2 * K), *ur = gr + nchunk;
+        constexpr int CB = NC > 3 ? 3 : NC;                 // chunks in flight: registers
+#pragma unroll
+        for (int c0 = 0; c0 < NC; c0 += CB) {
+            Pack16 u[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                const int i = min(idx + T * (c0 + c), nchunk - 1);
+                if (in.z_inject) v[c0 + c].u = reinterpret_cast<const uint4 *>(in.z_inject + (size_t)r * K)[i];
+                else { v[c0 + c].u = gr[i]; u[c].u = ur[i]; }
+            }
+            if (!in.z_inject)
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float gt = (float)v[c0 + c].h[e], up = (float)u[c].h[e];
+                        const float sg = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt));
+                        v[c0 + c].h[e] = to_f16(sg * up);
+                    }
+        }
+        if (in.z_out && live && blockIdx.x == 0)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (idx + T * c < nchunk) reinterpret_cast<uint4 *>(in.z_out + (size_t)r * K)[idx + T * c] = v[c].u;
+    } else {
+        const uint4 *xr = reinterpret_cast<const uint4 *>(in.x + (size_t)r * K);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c].u = xr[min(idx + T * c, nchunk - 1)];
+    }
+    // (a clamped chunk repeats one of the row's: harmless for a maximum, left out of the sum)
+    if (MODE == ROWS_RMSNORM) {
+        constexpr bool EARLY = NC <= 3;                     // the gains of wider shares do not fit beside the rows
+        float4 ga[NC][2];
+#pragma unroll
+        for (int c = 0; EARLY && c < NC; ++c) {
+            const float4 *gp = reinterpret_cast<const float4 *>(in.gamma + 8 * min(idx + T * c, nchunk - 1));
+            ga[c][0] = gp[0];
+            ga[c][1] = gp[1];
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (idx + T * c < nchunk)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const double f = (double)(float)v[c].h[e];
+                    ss = __builtin_fma(f, f, ss);
+                }
+        float dummy = 0.0f;
+        combine(dummy, ss);
+        const float rn = (float)(1.0 / sqrt(ss / (double)K + (double)in.eps));
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (!EARLY) {
+                const float4 *gp = reinterpret_cast<const float4 *>(in.gamma + 8 * min(idx + T * c, nchunk - 1));
+                ga[c][0] = gp[0];
+                ga[c][1] = gp[1];
+            }
+            const float gm[8] = {ga[c][0].x, ga[c][0].y, ga[c][0].z, ga[c][0].w, ga[c][1].x, ga[c][1].y, ga[c][1].z, ga[c][1].w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float hn = (float)v[c].h[e] * rn;
+                hn = hn * gm[e];
+                v[c].h[e] = to_f16(hn);
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf((float)v[c].h[e]));
+    combine(a, ss);
+    float s = 1.0f, inv = 0.0f;
+    if (a != 0.0f) { s = a / 7.0f; inv = 7.0f / a; }
+    if (live) {
+        if (idx == 0) scales[row] = s;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int i = idx + T * c;
+            if (i < 16 * G) {
+                float unit[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    unit[e] = i < nchunk ? code_unit(code_bits((float)v[c].h[e] * inv)) : 0.0f;
+                *reinterpret_cast<uint2 *>(codes + (size_t)row * stride + 8 * i) = units_to_e4m3(unit);
+            }
+        }
+    }
+    __syncthreads();
+}
+
+template <int NB, int U, int MODE, int NC>
+__global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
+    RowsIn in, int M, int K, int G, const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N,
+    f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, int code_stride)
+{
+    constexpr int R = 8 * U;                        // groups per round
+    constexpr int SD = 8 * NB * R;                  // scale dwords (two columns of a group) per round
+    constexpr int SPT = (SD + RT_THREADS - 1) / RT_THREADS;
+    constexpr int SROW = R + 8;                     // halves per column of staged scales (16-byte pieces, padded)
+    extern __shared__ __align__(16) uint4 lds_rows[];
+    float *accs = reinterpret_cast<float *>(lds_rows);                            // [R][NB][4][64]
+    f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * 256);                      // [16 NB][SROW]
+    float *row_scale = reinterpret_cast<float *>(scs + 16 * NB * SROW);           // [16]
+    double *red = reinterpret_cast<double *>(row_scale + 16);                     // [16]
+    uint8_t *codes = reinterpret_cast<uint8_t *>(red + 16);                       // [M][code_stride], MODE > PACKED
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = blockIdx.x * 16 * NB;
+
+    // chain ownership: thread t < 256 * NB owns the output held by (block j, register reg, lane ol)
+    const int oj = tid >> 8, oreg = (tid >> 6) & 3, ol = tid & 63;
+    const bool owner = tid < 256 * NB;
+    const int om = 4 * (ol >> 4) + oreg, on = n0 + 16 * oj + (ol & 15);
+    float y32 = 0.0f;
+
+    const size_t arow_bytes = MODE == ROWS_PACKED ? (size_t)(K >> 1) : (size_t)128 * (G | 1);
+    const uint8_t *arow = MODE <= ROWS_PACKED ? in.qa + (size_t)min(c16, M - 1) * arow_bytes : nullptr;
+    uint4 ra[U][MODE == ROWS_A8 ? 2 : 1], rb[U][NB];
+    uint32_t rsv[SPT];
+    auto fetch = [&](int r0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int g = min(r0 + 8 * u + wave, G - 1);
+            const uint4 *wg = wp + ((size_t)g * N + n0) * 4;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) rb[u][j] = wg[64 * j + 4 * c16 + q];
+            if (MODE == ROWS_A8) {
+                const uint4 *ag = reinterpret_cast<const uint4 *>(arow + g * 128 + 32 * q);
+                ra[u][0] = ag[0];
+                ra[u][MODE == ROWS_A8 ? 1 : 0] = ag[1];
+            } else if (MODE == ROWS_PACKED) {
+                ra[u][0] = *reinterpret_cast<const uint4 *>(arow + min(g * 64 + q * 16, (K >> 1) - 16));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < SPT; ++k) {
+            const int d = min(tid + RT_THREADS * k, SD - 1), g = min(r0 + d / (8 * NB), G - 1);
+            rsv[k] = *reinterpret_cast<const uint32_t *>(sw + (size_t)g * N + n0 + 2 * (d % (8 * NB)));
+        }
+    };
+    fetch(0);
+    if constexpr (MODE > ROWS_PACKED) quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red);
+    const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
+                               (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
+    for (int r0 = 0; r0 < G; r0 += R) {
+        f32x4 acc[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint4 a0, a1;
+            if constexpr (MODE == ROWS_A8) {
+                a0 = ra[u][0];
+                a1 = ra[u][1];
+            } else if constexpr (MODE == ROWS_PACKED) {
+                codes_to_e4m3(ra[u][0], a0, a1);
+            } else {
+                const int g = min(r0 + 8 * u + wave, G - 1);
+                const uint4 *ag = reinterpret_cast<const uint4 *>(codes + (size_t)min(c16, M - 1) * code_stride + g * 128 + 32 * q);
+                a0 = ag[0];
+                a1 = ag[1];
+            }
+            const i32x8 fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
+            const f32x4 k4 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{0, 0, 0, 0}, 0, 0, 0, 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const uint32_t w[4] = {rb[u][j].x, rb[u][j].y, rb[u][j].z, rb[u][j].w};
+                i32x8 fb;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    fb[2 * i] = (int)((w[i] & 0x0F0F0F0Fu) ^ 0x08080808u);
+                    fb[2 * i + 1] = (int)(((w[i] >> 4) & 0x0F0F0F0Fu) ^ 0x08080808u);
+                }
+                acc[u][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, fb, k4, 0, 0, 0, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < SPT; ++k) {             // this round's scales -> LDS, [column][group]
+            const int d = tid + RT_THREADS * k;
+            if (SD % RT_THREADS == 0 || d < SD) {
+                union { uint32_t w; f16 h[2]; } t;
+                t.w = rsv[k];
+                const int col = 2 * (d % (8 * NB)), gi = d / (8 * NB);
+                scs[col * SROW + gi] = t.h[0];
+                scs[(col + 1) * SROW + gi] = t.h[1];
+            }
+        }
+        if (r0 + R < G) fetch(r0 + R);              // next round's loads fly during the exchange
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) accs[((8 * u + wave) * NB + j) * 256 + i * 64 + lane] = acc[u][j][i];
+        __syncthreads();
+        if (owner) {
+            const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + (16 * oj + (ol & 15)) * SROW);
+            const float *ap = accs + oj * 256 + oreg * 64 + ol;
+#pragma unroll
+            for (int i8 = 0; i8 < U; ++i8) {
+                if (r0 + 8 * i8 >= G) break;
+                const Pack16 s8 = sp[i8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float sc = r0 + 8 * i8 + i < G ? (float)s8.h[i] : 0.0f;
+                    y32 = __builtin_fmaf(ap[(8 * i8 + i) * NB * 256], sc, y32);
+                }
+            }
+        }
+        if (r0 + R < G) __syncthreads();
+    }
+    if (owner && om < M) {
+        const float sa = MODE <= ROWS_PACKED ? in.sa[om] : row_scale[om];
+        float v = y32 * (sa * F8_UNIT);
+        if (res) v = v + (float)res[(size_t)om * ldr + on];
+        y[(size_t)om * ldy + on] = to_f16(v);
+    }
+}
+
+template <int NB, int U, int MODE, int NC>
+int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
+                  int code_stride, hipStream_t st)
+{
+    constexpr int R = 8 * U;
+    const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
+    const size_t lds = R * NB * 1024 + 16 * NB * (R + 8) * 2 + 64 + 128 + (MODE > ROWS_PACKED ? (size_t)M * code_stride : 0);
+    if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC>>()) return QUOTA_ERR_HIP;
+    const double Md = M, Nd = W->N, Kd = W->K;
+    ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
+                   Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + 2.0 * Md * Nd * (res ? 2 : 1), st);
+    w4a4_rows16_kernel<NB, U, MODE, NC><<<dim3(W->N / (16 * NB)), dim3(RT_THREADS), lds, st>>>(
+        in, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr, code_stride);
+    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    return QUOTA_OK;
+}
+
+// 16 columns per workgroup up to 8192 columns (256 or more workgroups from 4096 on, and twice the groups in
+// flight per wave), 32 beyond
+template <int MODE, int NC>
+int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int code_stride,
+           hipStream_t st)
+{
+    return W->N <= 8192 ? launch_rows16<1, 4, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st)
+                        : launch_rows16<2, 2, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+}
+
+template <int MODE>
+int rows16_quantizing(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
+                      hipStream_t st)
+{
+    const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W, T = M == 1 ? 512 : M == 2 ? 256 : 128;
+    const int nc = (16 * G + T - 1) / T;                  // 8-channel chunks per thread
+    const int stride = G * 128 + 16;                      // 16 more: rows start on different LDS banks
+    if (nc <= 1) return rows16<MODE, 1>(in, M, W, y, ldy, res, ldr, stride, st);
+    if (nc <= 3) return rows16<MODE, 3>(in, M, W, y, ldy, res, ldr, stride, st);
+    return rows16<MODE, 6>(in, M, W, y, ldy, res, ldr, stride, st);
+}
+
+}  // namespace
+
+bool quota_internal_rows16_quantizes(int M, int K)
+{
+    const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W, T = M == 1 ? 512 : M == 2 ? 256 : 128;
+    return M <= 4 && (16 * G + T - 1) / T <= 6;            // six chunks of a row per thread fit in registers
+}
+
+int quota_internal_rows16(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W, void *y, int ldy,
+                          const void *res, int ldr, hipStream_t st)
+{
+    RowsIn in = {};
+    in.qa = qa;
+    in.sa = sa;
+    return a8 ? rows16<ROWS_A8, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st)
+              : rows16<ROWS_PACKED, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+}
+
+int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
+                                   int ldr, hipStream_t st)
+{
+    RowsIn in = {};
+    in.x = (const f16 *)x;
+    return rows16_quantizing<ROWS_QUANT>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, st);
+}
+
+int quota_internal_rows16_rmsnorm(const void *x, const float *gamma, float eps, int M, const quota_weights *W, void *y,
+                                  int ldy, hipStream_t st)
+{
+    RowsIn in = {};
+    in.x = (const f16 *)x;
+    in.gamma = gamma;
+    in.eps = eps;
+    return rows16_quantizing<ROWS_RMSNORM>(in, M, W, (f16 *)y, ldy, nullptr, 0, st);
+}
+
+int quota_internal_rows16_silu(const void *gu, void *z_out, const void *z_inject, int M, const quota_weights *W, void *y,
+                               int ldy, const void *res, int ldr, hipStream_t st)
+{
+    RowsIn in = {};
+    in.x = (const f16 *)gu;
+    in.z_out = (f16 *)z_out;
+    in.z_inject = (const f16 *)z_inject;
+    return rows16_quantizing<ROWS_SILU>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, st);
+}
