@@ -16,16 +16,33 @@ constexpr int DEC_LMAX = QUOTA_MAX_DECODE_ROWS;      // cached rows per sequence
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
-// Dequantizes codes e and e+4 (e = 0..3) of a packed dword to x_hat = fp16(code * s) as a half
-// pair.  wx = w ^ 0x88888888 turns each two's-complement nibble c into c + 8 in [0, 15];
-// 0x6400 | (c + 8) is the fp16 number 1024 + c + 8, so subtracting 1032 leaves the code exactly,
-// and the fp16 multiply rounds code * s once, to nearest -- the value the quantizer defines.
-__device__ __forceinline__ h2 dequant_pair(uint32_t wx, int e, h2 s2)
+// Dequantizes a packed dword to x_hat = fp16(code * s): pair e holds codes e and e + 4.  A two's-complement nibble c
+// under 0x6400 | . ^ 8 is the fp16 number 1024 + c + 8, a nibble one place up (0x6400 | . ^ 0x80) is 1024 +
+// 16 (c + 8): one subtraction, or one multiply-add by 1/16, leaves the code exactly, and the fp16 multiply
+// rounds code * s once, to nearest -- the value the quantizer defines.  13 instructions per 8 codes
+// (the masks sit in registers, so that and + xor is one instruction).
+struct Dequant {
+    uint32_t m0 = 0x000F000Fu, m1 = 0x00F000F0u, x0 = 0x64086408u, x1 = 0x64806480u;
+    __device__ __forceinline__ Dequant() { asm volatile("" : "+v"(m0), "+v"(m1), "+v"(x0), "+v"(x1)); }
+    __device__ __forceinline__ void operator()(uint32_t w, h2 s2, h2 out[4]) const
+    {
+        const h2 sixteenth = h2{(_Float16)0.0625f, (_Float16)0.0625f};
+        const uint32_t hi = w >> 8;
+        const uint32_t b[4] = {(w & m0) ^ x0, (w & m1) ^ x1, (hi & m0) ^ x0, (hi & m1) ^ x1};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const h2 v = __builtin_bit_cast(h2, b[e]);
+            out[e] = (e & 1 ? __builtin_elementwise_fma(v, sixteenth, h2{(_Float16)-72.0f, (_Float16)-72.0f})
+                            : v - h2{(_Float16)1032.0f, (_Float16)1032.0f}) * s2;
+        }
+    }
+};
+
+// The value of another lane of the quad
+template <int CTRL>
+__device__ __forceinline__ float quad_swap(float v)
 {
-    const uint32_t bits = ((wx >> (4 * e)) & 0x000F000Fu) | 0x64006400u;
-    h2 c = __builtin_bit_cast(h2, bits);
-    c = c - h2{(_Float16)1032.0f, (_Float16)1032.0f};
-    return c * s2;
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 
 // The new token of a decode step, as the QKV projection left it (null qkv: the cache is read as it is).
@@ -62,8 +79,8 @@ constexpr int DEC_TILE = 512;
 constexpr int DEC_THREADS = 512;     // 8 waves: with two workgroups on a CU every SIMD has four waves to interleave
 constexpr int DEC_RED_ROW = DEC_THREADS + 1;
 
-template <int DH, int RC, bool FUSED, bool SPLIT>
-__global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention_kernel(
+template <int DH, int RC, int HP, bool MULTI, bool FUSED, bool SPLIT>
+__global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void decode_attention_kernel(
     const f16 *__restrict__ q, int d, int dkv, int rep, uint32_t *__restrict__ kc, f16 *__restrict__ ks,
     uint32_t *__restrict__ vc, f16 *__restrict__ vs, int capacity, int len,
     const int32_t *__restrict__ step_dev, int max_steps, f16 *__restrict__ o, int n_kv_heads, DecodeNew nw,
@@ -74,13 +91,15 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
     constexpr int UN = DEC_TILE / TP;       // passes per tile
     constexpr int WPT = DH / 8;             // packed dwords per token and head
     constexpr int GPT = DH / 64;            // scale groups per token and head
-    constexpr int NW = DEC_THREADS / 64;    // waves
-    extern __shared__ float red[];          // [32 channels][512 token lanes], padded
-    __shared__ h2 qp[RC][DH / 2];           // q as pairs: qp[r][4 i + e] = (q[8 i + e], q[8 i + e + 4])
-    __shared__ float sc[RC][DEC_TILE];
-    __shared__ float wred[2][RC][NW];
-    __shared__ __align__(16) uint32_t new_codes[2][WPT];
-    __shared__ f16 new_scales[2][GPT];
+    constexpr int NW = HP * DEC_THREADS / 64;       // waves
+    static_assert(HP == 1 || (RC == 1 && !SPLIT), "");
+    extern __shared__ float red[];          // per head: [32 channels][512 token lanes], padded
+    __shared__ h2 qp[HP * RC][DH / 2];      // q as pairs: qp[r][4 i + e] = (q[8 i + e], q[8 i + e + 4])
+    __shared__ float sc[HP * RC][DEC_TILE];
+    __shared__ float lsum[HP];
+    __shared__ float wmax[HP * RC][NW], wsum[HP * RC][NW / HP];
+    __shared__ __align__(16) uint32_t new_codes[2][HP * WPT];
+    __shared__ __align__(4) f16 new_scales[2][HP * GPT];
     // (sequence, head) pairs are dealt to the 8 XCDs in contiguous ranges: the heads of a sequence
     // share the 128-byte lines of its cache rows (two heads' codes, all heads' scales), and each
     // XCD has its own L2
@@ -88,10 +107,11 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
     const int work = xcd_remap(blockIdx.x, gridDim.x);
     const int r0 = (work % n_pass) * RC;
     const int sp = SPLIT ? work / n_pass % n_split : 0;
-    const int bh = work / (SPLIT ? n_pass * n_split : n_pass), h = bh % n_kv_heads, b = bh / n_kv_heads;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int piece = tid % PPT, tl = tid / PPT;
-    const int wave_t0 = (tid & ~63) / PPT;  // first token of this wave within a pass
+    const int bh = work / (SPLIT ? n_pass * n_split : n_pass) * HP, h = bh % n_kv_heads, b = bh / n_kv_heads;  // (first) K/V head
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int piece = tid % PPT, hs = tid / PPT % HP, tl = tid / (PPT * HP);
+    constexpr int TPW = 64 / (PPT * HP);    // tokens per pass of a wave
+    const int wave_t0 = wave * TPW;         // first token of this wave within a pass
     const int n32 = dkv >> 3, ng = dkv >> 6;
     int L = len;
     if (step_dev) L += min(max(*step_dev, 0), max_steps - 1) + 1;      // the row this step appends included
@@ -100,37 +120,60 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
     const float scale = 1.0f / sqrtf((float)DH);
     const size_t row0 = (size_t)b * capacity;
     const int nr = min(RC, rep - r0);
+    const Dequant dequant;
 
-    uint4 kq[UN], vq[UN];
-    f16 ksc[UN], vsc[UN];
-    auto load_k = [&](int t0) {
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int t = t0 + u * TP + tl;
-            const size_t row = row0 + (t < stored ? t : 0);
-            kq[u] = *reinterpret_cast<const uint4 *>(kc + row * n32 + h * WPT + 4 * piece);
-            ksc[u] = ks[row * ng + h * GPT + (piece >> 1)];
-        }
+    // Loads are buffer loads that fetch nothing past the last row, so that every pass issues the same instructions
+    // and waits count exactly.  The scales of a wave's tokens come 64 / HP tokens to a load (lane l: head l % HP, the
+    // (l / HP)-th of the tokens of a tile) and are handed round the wave.
+    const int rows = SPLIT ? min(stored, t_end) : stored;
+    auto buffer = [&](const void *base, size_t row_bytes, int bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0,
+                                                 rows > 0 ? (int)((rows - 1) * row_bytes + bytes) : 0, 0x00020000);
     };
-    auto load_v = [&](int t0) {
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int t = t0 + u * TP + tl;
-            const size_t row = row0 + (t < stored ? t : 0);
-            vq[u] = *reinterpret_cast<const uint4 *>(vc + row * n32 + h * WPT + 4 * piece);
-            vsc[u] = vs[row * ng + h * GPT + (piece >> 1)];
-        }
+    const auto kbuf = buffer(kc + row0 * n32 + h * WPT, 4 * n32, HP * WPT * 4);
+    const auto vbuf = buffer(vc + row0 * n32 + h * WPT, 4 * n32, HP * WPT * 4);
+    const auto ksbuf = buffer(ks + row0 * ng + h * GPT, 2 * ng, HP * GPT * 2);
+    const auto vsbuf = buffer(vs + row0 * ng + h * GPT, 2 * ng, HP * GPT * 2);
+    i32x4 slot[UN];                     // codes of a pass: K until its scores are taken, then V
+    uint32_t ksw, vsw;
+    const int scale_t = (lane / HP / TPW) * TP + wave_t0 + lane / HP % TPW;
+    const int code_off = tl * (4 * n32) + 16 * (tid % (PPT * HP)), scale_off = scale_t * (2 * ng) + lane % HP * (2 * GPT);
+    // (the opaque token number keeps the compiler from carrying every pass's offset in a register of its own)
+    auto load_codes = [&](auto buf, int t) {
+        asm volatile("" : "+s"(t));
+        return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, code_off + t * (4 * n32), 0, 0));
+    };
+    auto load_scales = [&](auto buf, int t) -> uint32_t {
+        asm volatile("" : "+s"(t));
+        if constexpr (GPT == 2) return __builtin_amdgcn_raw_buffer_load_b32(buf, scale_off + t * (2 * ng), 0, 0);
+        else return __builtin_amdgcn_raw_buffer_load_b16(buf, scale_off + t * (2 * ng), 0, 0);
+    };
+    const uint32_t scale_sel = GPT == 2 && piece >= 2 ? 0x03020302u : 0x01000100u;
+    const int scale_from = 4 * (HP * (lane / (PPT * HP)) + hs);
+    auto scale_of = [&](uint32_t sw, int u) {       // of pass u's token, as a pair
+        int from = scale_from;
+        asm volatile("" : "+v"(from));              // (recomputed per pass, not kept for each)
+        const uint32_t v = (uint32_t)__builtin_amdgcn_ds_bpermute(from + 4 * HP * TPW * u, (int)sw);
+        return __builtin_bit_cast(h2, __builtin_amdgcn_perm(v, v, scale_sel));
     };
     Pack16 x, xp, xo;
     float cs[8], sn[8];
     constexpr int CPH = DH / 8, HALF = CPH / 2;
-    const int item = tid / CPH, cc = tid % CPH;         // wave 0: head vectors k, v, q[0], q[1]
+    const int item = tid / CPH % (2 + RC), cc = tid % CPH;          // head vectors k, v, q[0], q[1] ...
+    const int ph = tid / CPH / (2 + RC);                            // ... of head h + ph
+    const bool preparing = tid < HP * (2 + RC) * CPH;
     if (FUSED) {
-        // its loads go first: they head the longest chain
-        if (tid < (2 + RC) * CPH) {
-            const int hq = h * rep + min(r0 + max(item - 2, 0), rep - 1);
-            const int first = item == 0 ? d + h * DH : item == 1 ? d + dkv + h * DH : hq * DH;
+        if (preparing) {
+            const int hq = (h + ph) * rep + min(r0 + max(item - 2, 0), rep - 1);
+            const int first = item == 0 ? d + (h + ph) * DH : item == 1 ? d + dkv + (h + ph) * DH : hq * DH;
             x.u = *reinterpret_cast<const uint4 *>(nw.qkv + (size_t)b * (d + 2 * dkv) + first + 8 * cc);
+        }
+    }
+    ksw = load_scales(ksbuf, t_begin);
+#pragma unroll
+    for (int u = 0; u < UN; ++u) slot[u] = load_codes(kbuf, t_begin + u * TP);
+    if (FUSED) {
+        if (preparing) {
             const int pr = min(max(nw.pos[b], 0), nw.n_pos - 1);     // never index outside the tables
             const float *cp = nw.cosT + (size_t)pr * (DH / 2) + 8 * (cc % HALF);
             const float *ssp = nw.sinT + (size_t)pr * (DH / 2) + 8 * (cc % HALF);
@@ -138,12 +181,6 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
             *reinterpret_cast<float4 *>(cs + 4) = *reinterpret_cast<const float4 *>(cp + 4);
             *reinterpret_cast<float4 *>(sn) = *reinterpret_cast<const float4 *>(ssp);
             *reinterpret_cast<float4 *>(sn + 4) = *reinterpret_cast<const float4 *>(ssp + 4);
-        }
-    }
-    load_k(t_begin);
-    load_v(t_begin);
-    if (FUSED) {
-        if (tid < (2 + RC) * CPH) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) xp.w[i] = __shfl_xor(x.w[i], HALF, 64);     // rotate-half partner chunk
             if (item == 1) xo = x;
@@ -154,23 +191,23 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
                 for (int e = 0; e < 8; ++e) f[e] = (float)xo.h[e];
                 f16 s8;
                 const uint32_t word = kv_quant8(f, &s8, nullptr);
-                new_codes[item][cc] = word;
-                if ((cc & 7) == 0) new_scales[item][cc >> 3] = s8;
+                new_codes[item][ph * WPT + cc] = word;
+                if ((cc & 7) == 0) new_scales[item][ph * GPT + (cc >> 3)] = s8;
                 if (r0 == 0 && L > t_begin && L <= t_end) {
                     const size_t row = row0 + L - 1;
-                    (item == 0 ? kc : vc)[row * n32 + h * WPT + cc] = word;
-                    if ((cc & 7) == 0) (item == 0 ? ks : vs)[row * ng + h * GPT + (cc >> 3)] = s8;
+                    (item == 0 ? kc : vc)[row * n32 + (h + ph) * WPT + cc] = word;
+                    if ((cc & 7) == 0) (item == 0 ? ks : vs)[row * ng + (h + ph) * GPT + (cc >> 3)] = s8;
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) qp[item - 2][4 * cc + e] = h2{xo.h[e], xo.h[e + 4]};
+                for (int e = 0; e < 4; ++e) qp[ph * RC + item - 2][4 * cc + e] = h2{xo.h[e], xo.h[e + 4]};
                 if (nw.q_rot && sp == 0 && item - 2 < nr)
-                    *reinterpret_cast<uint4 *>(nw.q_rot + (size_t)b * d + (h * rep + r0 + item - 2) * DH + 8 * cc) = xo.u;
+                    *reinterpret_cast<uint4 *>(nw.q_rot + (size_t)b * d + ((h + ph) * rep + r0 + item - 2) * DH + 8 * cc) = xo.u;
             }
         }
-    } else if (tid < RC * (DH / 2)) {
+    } else if (tid < HP * RC * (DH / 2)) {
         const int r = tid / (DH / 2), i = tid % (DH / 2);
-        const int hq = min(h * rep + r0 + r, h * rep + rep - 1);
+        const int hq = (h + r / RC) * rep + min(r0 + r % RC, rep - 1);
         const f16 *qh = q + (size_t)b * d + hq * DH + 8 * (i >> 2) + (i & 3);
         qp[r][i] = h2{qh[0], qh[4]};
     }
@@ -179,127 +216,139 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
 #pragma unroll
     for (int r = 0; r < RC; ++r)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) qr[r][i] = qp[r][16 * piece + i];
-    float m_run[RC], l_run[RC], acc[RC][32];
+        for (int i = 0; i < 16; ++i) qr[r][i] = qp[hs * RC + r][16 * piece + i];
+    float m_run[HP * RC], l_run[RC], acc[RC][32];
+#pragma unroll
+    for (int r = 0; r < HP * RC; ++r) m_run[r] = -INFINITY;
 #pragma unroll
     for (int r = 0; r < RC; ++r) {
-        m_run[r] = -INFINITY;
         l_run[r] = 0.0f;
 #pragma unroll
         for (int e = 0; e < 32; ++e) acc[r][e] = 0.0f;
     }
     for (int t0 = t_begin; t0 < t_end; t0 += DEC_TILE) {
         const int tn = min(DEC_TILE, t_end - t0);
-        if (FUSED && t0 + tn == L) {    // the new row is in this tile
-#pragma unroll
-            for (int u = 0; u < UN; ++u)
-                if (t0 + u * TP + tl == L - 1) {
-                    kq[u] = *reinterpret_cast<const uint4 *>(&new_codes[0][4 * piece]);
-                    vq[u] = *reinterpret_cast<const uint4 *>(&new_codes[1][4 * piece]);
-                    ksc[u] = new_scales[0][piece >> 1];
-                    vsc[u] = new_scales[1][piece >> 1];
-                }
-        }
-        // ---- scores of the tile
+        // the new row, if this tile and this wave have it
+        const bool has_new = FUSED && t0 + tn == L;
+        const int new_pass = has_new && (L - 1 - t0) % TP / TPW == wave ? (L - 1 - t0) / TP : -1;
+        auto patch = [&](i32x4 &codes, int kv) {
+            if (tl == (L - 1 - t0) % TP) codes = *reinterpret_cast<const i32x4 *>(&new_codes[kv][4 * (tid % (PPT * HP))]);
+        };
+        auto patch_scales = [&](uint32_t &sw, int kv) {
+            if (has_new && t0 + scale_t == L - 1) {
+                const f16 *p = &new_scales[kv][lane % HP * GPT];
+                sw = GPT == 2 ? *reinterpret_cast<const uint32_t *>(p) : *reinterpret_cast<const uint16_t *>(p);
+            }
+        };
+        patch_scales(ksw, 0);
+        vsw = load_scales(vsbuf, t0);
+        // ---- scores
         float mx[RC];
 #pragma unroll
         for (int r = 0; r < RC; ++r) mx[r] = -INFINITY;
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            if (u * TP + wave_t0 >= tn) continue;       // the whole wave is past the end
-            const int t = u * TP + tl;
-            const bool ok = t < tn;
-            const h2 s2 = h2{ksc[u], ksc[u]};
-            const uint32_t ww[4] = {kq[u].x ^ 0x88888888u, kq[u].y ^ 0x88888888u, kq[u].z ^ 0x88888888u,
-                                    kq[u].w ^ 0x88888888u};
-            float dot[RC][4];           // four independent chains: the dot instruction accumulates in place
+            if (u * TP + wave_t0 < tn) {                // (else the whole wave is past the end)
+                const int t = u * TP + tl;
+                const bool ok = t < tn;
+                if (FUSED && new_pass == u) patch(slot[u], 0);
+                const h2 s2 = scale_of(ksw, u);
+                float dot[RC][4];           // independent chains: the dot instruction accumulates in place
 #pragma unroll
-            for (int r = 0; r < RC; ++r)
+                for (int r = 0; r < RC; ++r)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) dot[r][i] = 0.0f;
+                    for (int i = 0; i < 4; ++i) dot[r][i] = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+                for (int i2 = 0; i2 < 4; i2 += 2) {         // two dwords at a time: registers
+                    h2 kh[2][4];
+                    dequant(slot[u][i2], s2, kh[0]);
+                    dequant(slot[u][i2 + 1], s2, kh[1]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {       // channels (8 id + e, 8 id + e + 4), id = 4 piece + i
-                    const h2 kh = dequant_pair(ww[i], e, s2);
+                    for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int r = 0; r < RC; ++r)
-                        dot[r][i] = __builtin_amdgcn_fdot2(qr[r][4 * i + e], kh, dot[r][i], false);
+                        for (int i = i2; i < i2 + 2; ++i)   // channels (8 id + e, 8 id + e + 4), id = 4 piece + i
+#pragma unroll
+                            for (int r = 0; r < RC; ++r)
+                                dot[r][i] = __builtin_amdgcn_fdot2(qr[r][4 * i + e], kh[i - i2][e], dot[r][i], false);
                 }
 #pragma unroll
-            for (int r = 0; r < RC; ++r) {
-                float v = (dot[r][0] + dot[r][1]) + (dot[r][2] + dot[r][3]);
-                v += __shfl_xor(v, 1, 64);
-                if (PPT == 4) v += __shfl_xor(v, 2, 64);
-                v *= scale;
-                if (ok && piece == 0) sc[r][t] = v;
-                if (ok) mx[r] = fmaxf(mx[r], v);
+                for (int r = 0; r < RC; ++r) {
+                    float v = (dot[r][0] + dot[r][1]) + (dot[r][2] + dot[r][3]);
+                    v += quad_swap<0xB1>(v);                    // lane ^ 1
+                    if (PPT == 4) v += quad_swap<0x4E>(v);      // lane ^ 2
+                    v *= scale;
+                    if (ok && piece == 0) sc[hs * RC + r][t] = v;
+                    if (ok) mx[r] = fmaxf(mx[r], v);
+                }
             }
+            slot[u] = load_codes(vbuf, t0 + u * TP);        // the freed slot takes V
         }
-        const bool more = t0 + DEC_TILE < t_end;
-        if (more) load_k(t0 + DEC_TILE);
 #pragma unroll
-        for (int r = 0; r < RC; ++r) {
-            mx[r] = wave_max(mx[r]);
-            if ((tid & 63) == 0) wred[0][r][wave] = mx[r];
+        for (int r = 0; r < HP * RC; ++r) {
+            const float m = wave_max(HP == 1 || hs == r ? mx[HP == 1 ? r : 0] : -INFINITY);
+            if (lane == 0) wmax[r][wave] = m;
         }
         __syncthreads();                // scores and wave maxima visible
-        float alpha[RC], m_new[RC], sum[RC];
+        float alpha[RC];
 #pragma unroll
-        for (int r = 0; r < RC; ++r) {
-            float tm = wred[0][r][0];
+        for (int r = 0; r < HP * RC; ++r) {
+            float tm = wmax[r][0];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) tm = fmaxf(tm, wred[0][r][w]);
-            m_new[r] = fmaxf(m_run[r], tm);
-            alpha[r] = __expf(m_run[r] - m_new[r]);      // 0 on the first tile
-            m_run[r] = m_new[r];
-            sum[r] = 0.0f;
-            for (int t = tid; t < tn; t += DEC_THREADS) {
-                const float p = __expf(sc[r][t] - m_new[r]);
-                sc[r][t] = p;
-                sum[r] += p;
+            for (int w = 1; w < NW; ++w) tm = fmaxf(tm, wmax[r][w]);
+            const float m_new = fmaxf(m_run[r], tm);
+            const float a = __expf(m_run[r] - m_new);           // 0 on the first tile
+            if (HP == 1) alpha[r] = a;
+            else alpha[0] = r == 0 || hs == r ? a : alpha[0];
+            m_run[r] = m_new;
+            if (HP > 1 && wave / (NW / HP) != r) continue;      // 512 threads per head
+            const int t = tid % DEC_THREADS;
+            float sum = 0.0f;
+            if (t < tn) {
+                sum = __expf(sc[r][t] - m_new);
+                sc[r][t] = sum;
             }
-            sum[r] = wave_sum(sum[r]);
-            if ((tid & 63) == 0) wred[1][r][wave] = sum[r];
+            sum = wave_sum(sum);
+            if (lane == 0) wsum[r][wave % (NW / HP)] = sum;
         }
         __syncthreads();                // probabilities and wave sums visible
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
-            float ts = wred[1][r][0];
+            float ts = wsum[hs * RC + r][0];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) ts += wred[1][r][w];
+            for (int w = 1; w < NW / HP; ++w) ts += wsum[hs * RC + r][w];
             l_run[r] = l_run[r] * alpha[r] + ts;
 #pragma unroll
             for (int e = 0; e < 32; ++e) acc[r][e] *= alpha[r];
         }
-        // ---- p * v_hat of the tile
+        // ---- p * v_hat; the freed slots take the next tile's K
+        patch_scales(vsw, 1);
+        if (MULTI) ksw = load_scales(ksbuf, t0 + DEC_TILE);
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            if (u * TP + wave_t0 >= tn) continue;
-            const int t = u * TP + tl;
-            const bool ok = t < tn;
-            const h2 s2 = h2{vsc[u], vsc[u]};
-            const uint32_t ww[4] = {vq[u].x ^ 0x88888888u, vq[u].y ^ 0x88888888u, vq[u].z ^ 0x88888888u,
-                                    vq[u].w ^ 0x88888888u};
-            float pv[RC];
+            if (u * TP + wave_t0 < tn) {
+                const int t = u * TP + tl;
+                const bool ok = t < tn;
+                if (FUSED && new_pass == u) patch(slot[u], 1);
+                const h2 s2 = scale_of(vsw, u);
+                float pv[RC];
 #pragma unroll
-            for (int r = 0; r < RC; ++r) pv[r] = ok ? sc[r][t] : 0.0f;
+                for (int r = 0; r < RC; ++r) pv[r] = ok ? sc[hs * RC + r][t] : 0.0f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i) {
+                    h2 vh[4];
+                    dequant(slot[u][i], s2, vh);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const h2 vh = dequant_pair(ww[i], e, s2);
+                    for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int r = 0; r < RC; ++r) {
-                        acc[r][8 * i + e] = fmaf(pv[r], (float)vh[0], acc[r][8 * i + e]);
-                        acc[r][8 * i + e + 4] = fmaf(pv[r], (float)vh[1], acc[r][8 * i + e + 4]);
-                    }
+                        for (int r = 0; r < RC; ++r) {
+                            acc[r][8 * i + e] = fmaf(pv[r], (float)vh[e][0], acc[r][8 * i + e]);
+                            acc[r][8 * i + e + 4] = fmaf(pv[r], (float)vh[e][1], acc[r][8 * i + e + 4]);
+                        }
                 }
+            }
+            if (MULTI) slot[u] = load_codes(kbuf, t0 + DEC_TILE + u * TP);
         }
-        if (more) {
-            load_v(t0 + DEC_TILE);
-            __syncthreads();            // the tile's scores have been consumed
-        }
+        if (MULTI) __syncthreads();     // the tile's scores have been consumed
     }
     // ---- the token lanes meet in LDS, summed in lane order (red is laid out [channel][token lane] so that
     // the lanes of a wave write consecutive words; the loop over r is unrolled to keep acc in registers)
@@ -308,20 +357,23 @@ __global__ __launch_bounds__(DEC_THREADS, RC == 1 ? 4 : 2) void decode_attention
         if (r >= nr) break;
         if (r) __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 32; ++e) red[e * DEC_RED_ROW + tid] = acc[r][e];
+        for (int e = 0; e < 32; ++e) red[(32 * hs + e) * DEC_RED_ROW + tl * PPT + piece] = acc[r][e];
+        if (HP > 1 && lane < PPT * HP && piece == 0) lsum[hs] = l_run[r];       // (every lane has its head's)
         __syncthreads();
-        if (tid < DH) {
+        if (tid < HP * DH) {
+            const int hd = tid / DH, c = tid % DH;
             float out = 0.0f;
-            const float *rp = red + (tid & 31) * DEC_RED_ROW + (tid >> 5);
+            const float *rp = red + (32 * hd + (c & 31)) * DEC_RED_ROW + (c >> 5);
 #pragma unroll 32
             for (int i = 0; i < TP; ++i) out += rp[i * PPT];
-            const int hq = h * rep + r0 + r;
+            const int hq = (h + hd) * rep + r0 + r;
+            const float l = HP > 1 ? lsum[hd] : l_run[r];
             if (SPLIT) {
                 float *p = part + ((size_t)(b * n_kv_heads * rep + hq) * n_split + sp) * (DH + 2);
-                p[tid] = out;
-                if (tid == 0) { p[DH] = m_run[r]; p[DH + 1] = l_run[r]; }
+                p[c] = out;
+                if (c == 0) { p[DH] = m_run[r]; p[DH + 1] = l; }
             } else {
-                o[(size_t)b * d + hq * DH + tid] = (f16)(out / l_run[r]);
+                o[(size_t)b * d + hq * DH + c] = (f16)(out / l);
             }
         }
     }
@@ -353,34 +405,41 @@ int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o
     const int longest = stepped ? c->len + c->max_steps : len;
     const double rows = (double)c->B * longest;
     ProfScope prof(QUOTA_K_ATTENTION_DECODE, 4.0 * rows * d, rows * (dkv + dkv / 16.0) + 4.0 * c->B * d, st);
-    const int heads = c->H * c->B * ((rep + rc - 1) / rc), n_tiles = (longest + DEC_TILE - 1) / DEC_TILE;
+    const int heads = c->H * c->B * ((rep + rc - 1) / rc);
+    // two heads per workgroup where that still leaves one for every CU
+    const bool pairs = rep == 1 && c->H % 2 == 0 && heads >= 2 * DEC_SPLIT_GRID;
+    const int n_tiles = (longest + DEC_TILE - 1) / DEC_TILE;
     int n_split = 1, tiles = n_tiles;
     if (part && longest > DEC_SPLIT_ROWS && heads < DEC_SPLIT_GRID) {
-        tiles = max(1, n_tiles * heads / (2 * DEC_SPLIT_GRID));
+        tiles = max(1, n_tiles * heads / (2 * DEC_SPLIT_GRID));       // 512 workgroups or more, if there are the rows
         n_split = (n_tiles + tiles - 1) / tiles;
     }
-    auto run = [&](auto kernel_tag) {
+    const bool one_tile = longest <= DEC_TILE;
+    auto run = [&](auto kernel_tag, int hp) {
         constexpr auto kernel = decltype(kernel_tag)::value;
-        constexpr size_t lds = 32 * DEC_RED_ROW * sizeof(float);
+        const size_t lds = hp * 32 * DEC_RED_ROW * sizeof(float);
         if (!grant_lds<kernel>()) return QUOTA_ERR_HIP;
-        kernel<<<dim3(heads * n_split), dim3(DEC_THREADS), lds, st>>>(
+        kernel<<<dim3(heads * n_split / hp), dim3(hp * DEC_THREADS), lds, st>>>(
             q, d, dkv, rep, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes, (f16 *)c->v_scales,
             c->capacity, stepped ? c->len : len, c->step_dev, c->max_steps, o, c->H, nw, n_split, tiles, part);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
     };
-#define KERNEL(RC, SPLIT) std::integral_constant<decltype(&decode_attention_kernel<DH, RC, FUSED, SPLIT>), \
-                                                 &decode_attention_kernel<DH, RC, FUSED, SPLIT>>()
+#define KERNEL(RC, HP, MULTI, SPLIT)                                                                   \
+    std::integral_constant<decltype(&decode_attention_kernel<DH, RC, HP, MULTI, FUSED, SPLIT>),        \
+                           &decode_attention_kernel<DH, RC, HP, MULTI, FUSED, SPLIT>>()
     if constexpr (FUSED) {
         if (n_split > 1) {
-            const int rcode = rep == 1 ? run(KERNEL(1, true)) : run(KERNEL(2, true));
+            const int rcode = rep == 1 ? run(KERNEL(1, 1, true, true), 1) : run(KERNEL(2, 1, true, true), 1);
             if (rcode != QUOTA_OK) return rcode;
             decode_combine_kernel<DH><<<dim3(c->B * Hq), dim3(DH), 0, st>>>(part, n_split, o);
             QUOTA_RETURN_IF_LAUNCH_FAILED();
             return QUOTA_OK;
         }
     }
-    return rep == 1 ? run(KERNEL(1, false)) : run(KERNEL(2, false));
+    if (pairs) return one_tile ? run(KERNEL(1, 2, false, false), 2) : run(KERNEL(1, 2, true, false), 2);
+    if (rep == 1) return one_tile ? run(KERNEL(1, 1, false, false), 1) : run(KERNEL(1, 1, true, false), 1);
+    return one_tile ? run(KERNEL(2, 1, false, false), 1) : run(KERNEL(2, 1, true, false), 1);
 #undef KERNEL
 }
 

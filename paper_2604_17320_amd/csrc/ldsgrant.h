@@ -11,7 +11,7 @@ bool grant_lds()
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
     if (granted.load(std::memory_order_relaxed) >> dev & 1) return true;
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            128 * 1024) != hipSuccess)
+                            144 * 1024) != hipSuccess)
         return false;
     granted.fetch_or(uint64_t(1) << dev, std::memory_order_relaxed);
     return true;

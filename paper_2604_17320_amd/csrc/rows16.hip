@@ -162,27 +162,29 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     constexpr int SD = 8 * NB * R;                  // scale dwords (two columns of a group) per round
     constexpr int SPT = (SD + RT_THREADS - 1) / RT_THREADS;
     constexpr int SROW = R + 8;                     // halves per column of staged scales (16-byte pieces, padded)
+    constexpr int OPT = NB > 2 ? NB / 2 : 1;        // outputs per owner thread
+    constexpr int BUF = R * NB * 256 + 8 * NB * SROW;       // floats of one exchange buffer
     extern __shared__ __align__(16) uint4 lds_rows[];
-    float *accs = reinterpret_cast<float *>(lds_rows);                            // [R][NB][4][64]
-    f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * 256);                      // [16 NB][SROW]
-    float *row_scale = reinterpret_cast<float *>(scs + 16 * NB * SROW);           // [16]
+    float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
+    float *row_scale = xbuf + 2 * BUF;                                            // [16]
     double *red = reinterpret_cast<double *>(row_scale + 16);                     // [16]
     uint8_t *codes = reinterpret_cast<uint8_t *>(red + 16);                       // [M][code_stride], MODE > PACKED
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n0 = blockIdx.x * 16 * NB;
 
-    // chain ownership: thread t < 256 * NB owns the output held by (block j, register reg, lane ol)
+    // chain ownership: thread t < 256 * NB owns the outputs held by (block 2 o + t / 256, register oreg, lane ol)
     const int oj = tid >> 8, oreg = (tid >> 6) & 3, ol = tid & 63;
-    const bool owner = tid < 256 * NB;
-    const int om = 4 * (ol >> 4) + oreg, on = n0 + 16 * oj + (ol & 15);
-    float y32 = 0.0f;
+    const bool owner = NB >= 2 || tid < 256;
+    const int om = 4 * (ol >> 4) + oreg;
+    float y32[OPT];
+#pragma unroll
+    for (int o = 0; o < OPT; ++o) y32[o] = 0.0f;
 
     const size_t arow_bytes = MODE == ROWS_PACKED ? (size_t)(K >> 1) : (size_t)128 * (G | 1);
     const uint8_t *arow = MODE <= ROWS_PACKED ? in.qa + (size_t)min(c16, M - 1) * arow_bytes : nullptr;
     uint4 ra[U][MODE == ROWS_A8 ? 2 : 1], rb[U][NB];
     uint32_t rsv[SPT];
-    auto fetch = [&](int r0) {
+    auto fetch = [&](int n0, int r0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int g = min(r0 + 8 * u + wave, G - 1);
@@ -203,11 +205,15 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             rsv[k] = *reinterpret_cast<const uint32_t *>(sw + (size_t)g * N + n0 + 2 * (d % (8 * NB)));
         }
     };
-    fetch(0);
+    const int nblk = N / (16 * NB);
+    int blk = blockIdx.x, r0 = 0, par = 0;
+    fetch(blk * 16 * NB, 0);
     if constexpr (MODE > ROWS_PACKED) quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red);
     const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
-    for (int r0 = 0; r0 < G; r0 += R) {
+    while (true) {                                  // rounds of this workgroup's column blocks
+        float *accs = xbuf + par * BUF;
+        f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * 256);
         f32x4 acc[U][NB];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -248,63 +254,84 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                 scs[(col + 1) * SROW + gi] = t.h[1];
             }
         }
-        if (r0 + R < G) fetch(r0 + R);              // next round's loads fly during the exchange
+        const bool last = r0 + R >= G;
+        const int nblk_next = last ? blk + (int)gridDim.x : blk, r_next = last ? 0 : r0 + R;
+        if (nblk_next < nblk) fetch(nblk_next * 16 * NB, r_next);       // the next loads fly during the exchange
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) accs[((8 * u + wave) * NB + j) * 256 + i * 64 + lane] = acc[u][j][i];
-        __syncthreads();
+        __syncthreads();        // (the other buffer's readers passed the one before)
         if (owner) {
-            const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + (16 * oj + (ol & 15)) * SROW);
-            const float *ap = accs + oj * 256 + oreg * 64 + ol;
 #pragma unroll
-            for (int i8 = 0; i8 < U; ++i8) {
-                if (r0 + 8 * i8 >= G) break;
-                const Pack16 s8 = sp[i8];
+            for (int o = 0; o < OPT; ++o) {
+                const int j = 2 * o + oj;
+                const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + (16 * j + (ol & 15)) * SROW);
+                const float *ap = accs + j * 256 + oreg * 64 + ol;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float sc = r0 + 8 * i8 + i < G ? (float)s8.h[i] : 0.0f;
-                    y32 = __builtin_fmaf(ap[(8 * i8 + i) * NB * 256], sc, y32);
+                for (int i8 = 0; i8 < U; ++i8) {
+                    if (r0 + 8 * i8 >= G) break;
+                    const Pack16 s8 = sp[i8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float sc = r0 + 8 * i8 + i < G ? (float)s8.h[i] : 0.0f;
+                        y32[o] = __builtin_fmaf(ap[(8 * i8 + i) * NB * 256], sc, y32[o]);
+                    }
+                }
+            }
+            if (last) {
+#pragma unroll
+                for (int o = 0; o < OPT; ++o) {
+                    const int on = blk * 16 * NB + 16 * (2 * o + oj) + (ol & 15);
+                    if (om < M) {
+                        const float sa = MODE <= ROWS_PACKED ? in.sa[om] : row_scale[om];
+                        float v = y32[o] * (sa * F8_UNIT);
+                        if (res) v = v + (float)res[(size_t)om * ldr + on];
+                        y[(size_t)om * ldy + on] = to_f16(v);
+                    }
+                    y32[o] = 0.0f;
                 }
             }
         }
-        if (r0 + R < G) __syncthreads();
-    }
-    if (owner && om < M) {
-        const float sa = MODE <= ROWS_PACKED ? in.sa[om] : row_scale[om];
-        float v = y32 * (sa * F8_UNIT);
-        if (res) v = v + (float)res[(size_t)om * ldr + on];
-        y[(size_t)om * ldy + on] = to_f16(v);
+        if (nblk_next >= nblk) break;
+        blk = nblk_next;
+        r0 = r_next;
+        par ^= 1;
     }
 }
 
-template <int NB, int U, int MODE, int NC>
+template <int NB, int U, int GRID, int MODE, int NC>
 int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
                   int code_stride, hipStream_t st)
 {
     constexpr int R = 8 * U;
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    const size_t lds = R * NB * 1024 + 16 * NB * (R + 8) * 2 + 64 + 128 + (MODE > ROWS_PACKED ? (size_t)M * code_stride : 0);
+    const size_t lds = 2 * (R * NB * 1024 + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_PACKED ? (size_t)M * code_stride : 0);
     if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC>>()) return QUOTA_ERR_HIP;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + 2.0 * Md * Nd * (res ? 2 : 1), st);
-    w4a4_rows16_kernel<NB, U, MODE, NC><<<dim3(W->N / (16 * NB)), dim3(RT_THREADS), lds, st>>>(
+    w4a4_rows16_kernel<NB, U, MODE, NC><<<dim3(min(W->N / (16 * NB), GRID)), dim3(RT_THREADS), lds, st>>>(
         in, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr, code_stride);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
 
-// 16 columns per workgroup up to 8192 columns (256 or more workgroups from 4096 on, and twice the groups in
-// flight per wave), 32 beyond
+// 16 columns per workgroup up to 4096 columns (256 workgroups: one per CU), with two groups per wave in flight;
+// 32 beyond, where workgroups share a CU and every workgroup reads all the activations: three per CU with
+// one group per wave, or, with a quantizer in front, two per CU with two, so that fewer repeat its work.
+// Workgroups walk over the columns (RowsIn and the quantized rows are set up once).
 template <int MODE, int NC>
 int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int code_stride,
            hipStream_t st)
 {
-    return W->N <= 8192 ? launch_rows16<1, 4, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st)
-                        : launch_rows16<2, 2, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    if (W->N <= 4096) return launch_rows16<1, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    if constexpr (MODE <= ROWS_PACKED)
+        return launch_rows16<2, 1, 768, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    else
+        return launch_rows16<2, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
 }
 
 template <int MODE>
