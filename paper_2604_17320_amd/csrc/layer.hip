@@ -24,7 +24,7 @@ struct Carver {
 };
 
 struct LayerWs {
-    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format
+    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format or packed
     float *sa;
     f16 *qkv, *q_rot, *khat, *vhat, *o;
     uint8_t *skc, *svc; // staged 4-bit K/V of all rows
@@ -114,11 +114,17 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
                                         w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st);
 }
 
-// RMSNorm, quantizer, GEMM; and SwiGLU product, quantizer, GEMM.  A few rows leave the first two to the GEMM.
+// RMSNorm, quantizer, GEMM; SwiGLU product, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_PACKED rows stay packed
+// int4 in between (the GEMM of a few rows reads them faster so), and a few leave the quantizer to the GEMM.
+#define ROWS_PACKED 16
 static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
                         const quota_weights *W, void *y, int ldy, hipStream_t st)
 {
     if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_rmsnorm(x, gamma, eps, M, W, y, ldy, st);
+    if (M <= ROWS_PACKED) {
+        TRY(quota_rmsnorm_quantize_act(x, M, d, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, nullptr, st));
+        return quota_internal_rows16(w.qa, false, w.sa, M, W, y, ldy, nullptr, 0, st);
+    }
     TRY(quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
 }
@@ -127,7 +133,22 @@ static int silu_mul_gemm(const LayerWs &w, int M, int F, void *z, const void *z_
 {
     if (quota_internal_rows16_quantizes(M, F))
         return quota_internal_rows16_silu(w.gu, z, z_inject, M, W, y, ldy, res, ldr, st);
+    if (M <= ROWS_PACKED) {
+        TRY(quota_silu_mul_quantize_act(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
+        return quota_internal_rows16(w.qa, false, w.sa, M, W, y, ldy, res, ldr, st);
+    }
     TRY(quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
+    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
+}
+static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const quota_weights *W, void *y, int ldy,
+                         const void *res, int ldr, hipStream_t st)
+{
+    if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_quantize(x, M, W, y, ldy, res, ldr, st);
+    if (M <= ROWS_PACKED) {
+        TRY(quota_quantize_act(x, M, d, d, w.qa, w.sa, nullptr, nullptr, st));
+        return quota_internal_rows16(w.qa, false, w.sa, M, W, y, ldy, res, ldr, st);
+    }
+    TRY(quota_internal_quantize_a8(x, M, d, w.qa, w.sa, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
 
@@ -288,12 +309,7 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
     TRY(dump(t->o, w.o, (size_t)B * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
 
-    if (quota_internal_rows16_quantizes(B, d)) {
-        TRY(quota_internal_rows16_quantize(o_used, B, &L->o, w.x1, d, x_f16, d, st));
-    } else {
-        TRY(quota_internal_quantize_a8(o_used, B, d, w.qa, w.sa, st));
-        TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, B, &L->o, w.x1, d, x_f16, d, st));
-    }
+    TRY(quantize_gemm(w, o_used, B, d, &L->o, w.x1, d, x_f16, d, st));
     TRY(dump(t->x1, w.x1, (size_t)B * d * 2, st));
     TRY(rmsnorm_gemm(w, w.x1, B, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
     TRY(dump(t->gu, w.gu, (size_t)B * 2 * F * 2, st));
