@@ -335,19 +335,24 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
     return QUOTA_OK;
 }
 
-// 16 columns per workgroup up to 4096 columns (256 workgroups: one per CU), with two groups per wave in flight;
-// 32 beyond, where workgroups share a CU and every workgroup reads all the activations: three per CU with
-// one group per wave, or, with a quantizer in front, two per CU with two, so that fewer repeat its work.
-// Workgroups walk over the columns (RowsIn and the quantized rows are set up once).
+// 16 columns per workgroup up to 4096 columns (256 workgroups: one per CU), with two groups per wave in flight, four
+// over long rows, which stream longer than they start up; 32 beyond, two groups up to 8192 columns (at
+// most one workgroup per CU again), else three workgroups per CU with one group per wave, or, with a quantizer in
+// front, two per CU with two, so that fewer repeat its work.  Workgroups walk over the columns.
+// Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
+// <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
 template <int MODE, int NC>
 int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int code_stride,
            hipStream_t st)
 {
-    if (W->N <= 4096) return launch_rows16<1, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    if (W->N <= 4096) {
+        if constexpr (MODE <= ROWS_PACKED)
+            if (W->K > 8192) return launch_rows16<1, 4, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        return launch_rows16<1, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    }
     if constexpr (MODE <= ROWS_PACKED)
-        return launch_rows16<2, 1, 768, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
-    else
-        return launch_rows16<2, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        if (W->N > 8192) return launch_rows16<2, 1, 768, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    return launch_rows16<2, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
 }
 
 template <int MODE>
