@@ -12,8 +12,18 @@
 // Pass 2 owns key columns instead: S = Q K^T puts the key on the lane, so the
 // column sums over queries are in-lane adds in a fixed order (deterministic,
 // no atomics).  It needs the final log-sum-exp of every query row from pass 1.
+//
+// Both are bound by the matrix cores, the exponentials and LDS about equally (a wave's 64-key tile: 32 matrix
+// instructions = 1024 cycles, 32 exponentials and 100 other vector instructions = 900), so they run two
+// or more unsynchronised workgroups per SIMD and keep the rest away: tiles go from global memory to LDS without
+// passing registers, double-buffered, one barrier a tile; rows are unpadded and their 16-byte pieces
+// permuted so that every access spreads over all banks; V stays row-major and is transposed by the LDS read;
+// the output is rescaled only when a maximum moved.  4 x 2944 tokens, 40 heads of 128: 562 us (V transposed
+// by 2-byte LDS stores, tiles through registers) -> 442 us; column masses 358 -> 247 us.
 #include "common.h"
 #include "internal.h"
+#include "gemm_common.h"
+#include "ldscopy.h"
 
 namespace {
 
@@ -23,91 +33,100 @@ constexpr int KT = 64;       // keys per tile (pass 1), queries per tile (pass 2
 // matter for results below the smallest normal number, which are zero for a softmax anyway)
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// A tile in LDS: KT rows of DH halves; 16-byte piece c of row r sits at piece c ^ tile_swizzle(r).  Eight rows in a
+// row (a b128 read of one column of pieces) and four rows x four neighbouring pieces (a transposing read)
+// each cover all banks.
 template <int DH>
-struct AttnSmem {
-    alignas(16) f16 k[KT][DH + 8];       // row stride = odd number of 16-byte units: conflict-free 16-byte reads
-    alignas(16) f16 vt[DH][KT + 4];      // V transposed: [channel][key]
-};
+__device__ __forceinline__ int tile_swizzle(int r)
+{
+    return DH == 128 ? ((r & 3) << 2 | (r >> 2 & 3)) : ((r >> 1 & 1) << 2 | (r >> 2 & 1) << 1);
+}
+// Starts the copy of rows row0 .. row0 + KT - 1 (clamped to last) of a matrix into a tile: 256 threads
+template <int DH>
+__device__ __forceinline__ void copy_tile(const f16 *base, int stride, int row0, int last, unsigned lds)
+{
+    constexpr int CPR = DH / 8, PER = KT * CPR / 256;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int r = (4 * j + wave) * (64 / CPR) + lane / CPR, c = lane % CPR ^ tile_swizzle<DH>(r);
+        copy16_to_lds(base + (size_t)row0 * stride, (unsigned)min(r, last - row0) * (unsigned)(2 * stride) + 16 * c,
+                      lds + (4 * j + wave) * 1024);
+    }
+}
+// The 16-byte pieces 2 t + hl of row r of a tile, t = 0, 1, ...: piece t is at first ^ (32 t) bytes
+template <int DH>
+__device__ __forceinline__ int piece_address(int r, int hl) { return r * (2 * DH) + ((hl ^ tile_swizzle<DH>(r)) << 4); }
+
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 template <int DH>
-__global__ __launch_bounds__(256) void attn_fwd_kernel(
+__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
-    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2)
+    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int *__restrict__ counters,
+    int n_counters)
 {
     constexpr int T = DH / 16;       // k-steps (16 channels each) of the QK product
     constexpr int DB = DH / 32;      // 32-channel blocks of the output
-    constexpr int CPR = DH / 8;      // 16-byte chunks per head row
-    __shared__ AttnSmem<DH> sm;
+    constexpr int TB = KT * DH * 2;  // bytes of a tile
+    __shared__ __align__(16) char sm[2][2][TB];         // [buffer][K, V]
+    // the cue pass counts its workgroups
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0;
+    // XCD-aware order: a head's workgroups, longest first, run on one XCD, whose L2 holds its K and V
+    const int nq = (N + 127) / 128, work = xcd_remap(blockIdx.x, gridDim.x), bh = work / nq;
+    const int b = bh / H, h = bh % H, q0 = (nq - 1 - work % nq) * 128;
     const int d = H * DH;
-    const int b = blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 128;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hl = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hl = lane >> 5;
     const int qw0 = q0 + wave * 32, qi = qw0 + l32;       // this lane's query
     const size_t base = (size_t)b * N * d + (size_t)h * DH;
     // K/V rows have Hkv heads; query head h reads K/V head h / (H / Hkv)
     const int dkv = Hkv * DH;
     const size_t kvbase = (size_t)b * N * dkv + (size_t)(h / (H / Hkv)) * DH;
+    const int q_last_wg = min(q0 + 127, N - 1);
+    auto copy = [&](int kt0, int buf) {
+        copy_tile<DH>(khat + kvbase, dkv, kt0, N - 1, lds_address(sm[buf][0]));
+        copy_tile<DH>(vhat + kvbase, dkv, kt0, N - 1, lds_address(sm[buf][1]));
+    };
+    copy(0, 0);
 
     f16x8 qf[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        if (qi < N)
-            qf[t] = *reinterpret_cast<const f16x8 *>(q + base + (size_t)qi * d + 16 * t + 8 * hl);
-        else
-            qf[t] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
-    f32x16 oacc[DB];
+    for (int t = 0; t < T; ++t)
+        qf[t] = *reinterpret_cast<const f16x8 *>(q + base + (size_t)min(qi, N - 1) * d + 16 * t + 8 * hl);
+    f32x16 oacc[DB], zero;
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
+    for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+    asm volatile("" : "+v"(zero));           // (a register operand, instead of zeroing every accumulator)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[i][r] = 0.0f;
+    for (int i = 0; i < DB; ++i) oacc[i] = zero;
     float m_run = -INFINITY, l_run = 0.0f;
 
-    const int q_last_wg = min(q0 + 127, N - 1);
-    // Each thread stages 4 + 4 sixteen-byte pieces of a 64-key tile.  The pieces of the
-    // NEXT tile are fetched into registers before the current tile is consumed, so the
-    // global-memory latency overlaps the MFMAs instead of preceding them.
-    constexpr int PER = KT * CPR / 256;
-    Pack16 rk[PER], rv[PER];
-    auto fetch = [&](int kt0) {
+    const int k_at = piece_address<DH>(l32, hl);
+    // V^T: lanes s of a group of 16 read 4 keys x 16 channels (lane s: key s / 4, channels 4 (s % 4) ..) and get channel s
+    int v_at[2];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = tid + 256 * j;
-            const int keyk = i / CPR, ck = i % CPR, keyv = i % KT, cv = i / KT;
-            rk[j].u = make_uint4(0, 0, 0, 0);
-            rv[j].u = make_uint4(0, 0, 0, 0);
-            if (kt0 + keyk < N)
-                rk[j].u = *reinterpret_cast<const uint4 *>(khat + kvbase + (size_t)(kt0 + keyk) * dkv + 8 * ck);
-            if (kt0 + keyv < N)
-                rv[j].u = *reinterpret_cast<const uint4 *>(vhat + kvbase + (size_t)(kt0 + keyv) * dkv + 8 * cv);
-        }
-    };
-    fetch(0);
-    for (int kt0 = 0; kt0 <= q_last_wg; kt0 += KT) {
-        __syncthreads();
-        // K rows (16-byte stores) and V transposed (2-byte stores, lane = key)
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = tid + 256 * j;
-            const int keyk = i / CPR, ck = i % CPR, keyv = i % KT, cv = i / KT;
-            *reinterpret_cast<uint4 *>(&sm.k[keyk][8 * ck]) = rk[j].u;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sm.vt[8 * cv + e][keyv] = rv[j].h[e];
-        }
-        __syncthreads();
-        if (kt0 + KT <= q_last_wg) fetch(kt0 + KT);
+    for (int half = 0; half < 2; ++half) {
+        const int sl = lane & 15, r = 8 * half + 4 * hl + (sl >> 2), c = 2 * (lane >> 4 & 1) + (sl >> 1 & 1);
+        v_at[half] = r * (2 * DH) + ((c ^ tile_swizzle<DH>(r)) << 4) + 8 * (sl & 1);
+    }
+    int buf = 0;
+    for (int kt0 = 0; kt0 <= q_last_wg; kt0 += KT, buf ^= 1) {
+        drain();
+        __syncthreads();                     // the tile is here, the other buffer has been read
+        if (kt0 + KT <= q_last_wg) copy(kt0 + KT, buf ^ 1);
         if (kt0 > qw0 + 31) continue;        // tile entirely above this wave's diagonal
+        const char *kt = sm[buf][0], *vt = sm[buf][1];
 
         f32x16 s[2];
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
+        for (int t = 0; t < T; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[sb][r] = 0.0f;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                f16x8 kf = *reinterpret_cast<const f16x8 *>(&sm.k[32 * sb + l32][16 * t + 8 * hl]);
-                s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[t], s[sb], 0, 0, 0);
+            for (int sb = 0; sb < 2; ++sb) {
+                f16x8 kf = *reinterpret_cast<const f16x8 *>(kt + (k_at ^ 32 * t) + 32 * sb * (2 * DH));
+                s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[t], t ? s[sb] : zero, 0, 0, 0);
             }
-        }
         // the maximum is taken on the raw logits (the scale is positive) and the scale is folded into
         // the exponent's fused multiply-add: exp2(s * scale - m), one instruction per score less
         float mx = -INFINITY;
@@ -118,16 +137,13 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     int key = kt0 + 32 * sb + 8 * (r >> 2) + 4 * hl + (r & 3);
-                    float v = (key <= qi && key < N) ? s[sb][r] : -INFINITY;
-                    s[sb][r] = v;
-                    mx = fmaxf(mx, v);
+                    s[sb][r] = (key <= qi && key < N) ? s[sb][r] : -INFINITY;
                 }
-        } else {
-#pragma unroll
-            for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
         }
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         float m_new = fmaxf(m_run, mx * scale_log2);
         float alpha = fast_exp2(m_run - m_new);
@@ -147,21 +163,24 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(
                                   (f16)p[4], (f16)p[5], (f16)p[6], (f16)p[7]};
             }
         l_run = l_run * alpha + psum;
+        if (__ballot(alpha != 1.0f)) {       // (times one changes nothing)
 #pragma unroll
-        for (int i = 0; i < DB; ++i) {
+            for (int i = 0; i < DB; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+                for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+        }
 #pragma unroll
-            for (int sb = 0; sb < 2; ++sb)
+        for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const f16 *vrow = &sm.vt[32 * i + l32][32 * sb + 16 * u + 4 * hl];
-                    f16x4 v0 = *reinterpret_cast<const f16x4 *>(vrow);
-                    f16x4 v1 = *reinterpret_cast<const f16x4 *>(vrow + 8);
-                    f16x8 vf = f16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < DB; ++i) {
+                    const char *vb = vt + (32 * sb + 16 * u) * (2 * DH);
+                    const f16x4 v0 = __builtin_bit_cast(f16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(vb + (v_at[0] ^ 64 * i))));
+                    const f16x4 v1 = __builtin_bit_cast(f16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)(vb + (v_at[1] ^ 64 * i))));
+                    const f16x8 vf = f16x8{v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
                     oacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf[sb][u], oacc[i], 0, 0, 0);
                 }
-        }
     }
     float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     if (qi < N) {
@@ -178,96 +197,86 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(
     }
 }
 
+// One workgroup per 128 visual keys of a (sequence, head); wave w owns the 32 keys kb .. kb+31.  cm_inter (optional,
+// with cm_intra): the workgroup that is the last of its key block to finish, over the heads, also takes the
+// head means (counters: one per key block and sequence, zero on entry).  No workgroup waits for another.
 template <int DH>
-struct CmSmem {
-    alignas(16) f16 q[KT][DH + 8];
-    float lse[KT];
-};
-
-// grid: (ceil(Nv/128), H, B); wave w owns the 32 visual keys kb .. kb+31
-template <int DH>
-__global__ __launch_bounds__(256) void colmass_kernel(
+__global__ __launch_bounds__(256, 3) void colmass_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
-    int H, int Hkv, int vis_begin, int Nv, float *__restrict__ partial, float scale_log2)
+    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, float *__restrict__ cm_inter,
+    float *__restrict__ cm_intra, int *__restrict__ counters)
 {
-    constexpr int T = DH / 16, CPR = DH / 8;
-    __shared__ CmSmem<DH> sm;
+    constexpr int T = DH / 16, TB = KT * DH * 2;
+    __shared__ __align__(16) char sm_q[2][TB];
+    __shared__ __align__(16) float sm_lse[2][KT];
+    __shared__ int sm_last;
+    // XCD-aware order, as in pass 1; the first keys have the most queries
+    const int nk = (Nv + 127) / 128, work = xcd_remap(blockIdx.x, gridDim.x), bh = work / nk, kb = work % nk;
     const int d = H * DH;
-    const int b = blockIdx.z, h = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hl = lane >> 5;
-    const int kwg = vis_begin + blockIdx.x * 128;         // first key of the workgroup
+    const int b = bh / H, h = bh % H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hl = lane >> 5;
+    const int kwg = vis_begin + kb * 128;                 // first key of the workgroup
     const int key = kwg + wave * 32 + l32;                // this lane's key column
     const bool key_ok = key < vis_begin + Nv;
     const size_t base = (size_t)b * N * d + (size_t)h * DH;
+    const float *lse = lse2 + ((size_t)b * H + h) * N;
 
-    f16x8 kf[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        if (key_ok)
-            kf[t] = *reinterpret_cast<const f16x8 *>(khat + (size_t)b * N * (Hkv * DH) + (size_t)(h / (H / Hkv)) * DH +
-                                                     (size_t)key * (Hkv * DH) + 16 * t + 8 * hl);
-        else
-            kf[t] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
-    float acc_txt = 0.0f, acc_vis = 0.0f;
-    constexpr int PER = KT * CPR / 256;
-    Pack16 rq[PER];
-    float rl = 0.0f;
-    auto fetch = [&](int qt0) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = tid + 256 * j, r = i / CPR, c = i % CPR;
-            rq[j].u = make_uint4(0, 0, 0, 0);
-            if (qt0 + r < N)
-                rq[j].u = *reinterpret_cast<const uint4 *>(q + base + (size_t)(qt0 + r) * d + 8 * c);
-        }
-        if (tid < KT) rl = qt0 + tid < N ? lse2[((size_t)b * H + h) * N + qt0 + tid] : 0.0f;
+    auto copy = [&](int qt0, int buf) {
+        copy_tile<DH>(q + base, d, qt0, N - 1, lds_address(sm_q[buf]));
+        if (wave == 0) copy4_to_lds(lse, 4 * min(qt0 + lane, N - 1), lds_address(sm_lse[buf]));
     };
     const int qt_first = (kwg / KT) * KT;
-    fetch(qt_first);
-    for (int qt0 = qt_first; qt0 < N; qt0 += KT) {
-        __syncthreads();
+    copy(qt_first, 0);
+    f16x8 kf[T];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = tid + 256 * j, r = i / CPR, c = i % CPR;
-            *reinterpret_cast<uint4 *>(&sm.q[r][8 * c]) = rq[j].u;
-        }
-        if (tid < KT) sm.lse[tid] = rl;
+    for (int t = 0; t < T; ++t)
+        kf[t] = *reinterpret_cast<const f16x8 *>(khat + (size_t)b * N * (Hkv * DH) + (size_t)(h / (H / Hkv)) * DH +
+                                                 (size_t)(key_ok ? key : N - 1) * (Hkv * DH) + 16 * t + 8 * hl);
+    f32x16 zero;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+    asm volatile("" : "+v"(zero));
+    float acc_txt = 0.0f, acc_vis = 0.0f;
+    const int q_at = piece_address<DH>(l32, hl);
+    int buf = 0;
+    for (int qt0 = qt_first; qt0 < N; qt0 += KT, buf ^= 1) {
+        drain();
         __syncthreads();
-        if (qt0 + KT < N) fetch(qt0 + KT);
+        if (qt0 + KT < N) copy(qt0 + KT, buf ^ 1);
         if (qt0 + KT - 1 < kwg + wave * 32) continue;     // all queries before this wave's keys
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
             f32x16 s;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-#pragma unroll
             for (int t = 0; t < T; ++t) {
-                f16x8 qf = *reinterpret_cast<const f16x8 *>(&sm.q[32 * sb + l32][16 * t + 8 * hl]);
-                s = __builtin_amdgcn_mfma_f32_32x32x16_f16(qf, kf[t], s, 0, 0, 0);
+                f16x8 qf = *reinterpret_cast<const f16x8 *>(sm_q[buf] + (q_at ^ 32 * t) + 32 * sb * (2 * DH));
+                s = __builtin_amdgcn_mfma_f32_32x32x16_f16(qf, kf[t], t ? s : zero, 0, 0, 0);
             }
+            // queries qb0 .. qb0 + 31; register r holds query qb0 + 8 (r / 4) + 4 hl + r % 4
+            const int qb0 = qt0 + 32 * sb, vis_end = vis_begin + Nv;
+            const float *ls = sm_lse[buf] + 32 * sb + 4 * hl;
             // the causal / end-of-sequence mask is only needed when the query block reaches this
             // wave's keys or the end of the sequence (lanes without a key accumulate values that
-            // are never stored)
-            const int qb0 = qt0 + 32 * sb;
-            if (qb0 < kwg + wave * 32 + 31 || qb0 + 32 > N) {
+            // are never stored); a block of one kind of query adds to one sum
+            const bool masked = qb0 < kwg + wave * 32 + 31 || qb0 + 32 > N;
+            const bool all_vis = qb0 >= vis_begin && qb0 + 32 <= vis_end, all_txt = qb0 + 32 <= vis_begin || qb0 >= vis_end;
+            if (!masked && (all_vis || all_txt)) {
+                float a = all_vis ? acc_vis : acc_txt;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    int ql = 32 * sb + 8 * (r >> 2) + 4 * hl + (r & 3);
-                    int qi = qt0 + ql;
-                    float p = fast_exp2(__builtin_fmaf(s[r], scale_log2, -sm.lse[ql]));
-                    p = (key <= qi && qi < N) ? p : 0.0f;
-                    bool vis = qi >= vis_begin && qi < vis_begin + Nv;
-                    acc_vis += vis ? p : 0.0f;
-                    acc_txt += vis ? 0.0f : p;
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const f32x4 l4 = *reinterpret_cast<const f32x4 *>(ls + 8 * r4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a += fast_exp2(__builtin_fmaf(s[4 * r4 + e], scale_log2, -l4[e]));
                 }
+                if (all_vis) acc_vis = a;
+                else acc_txt = a;
             } else {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    int ql = 32 * sb + 8 * (r >> 2) + 4 * hl + (r & 3);
-                    int qi = qt0 + ql;
-                    float p = fast_exp2(__builtin_fmaf(s[r], scale_log2, -sm.lse[ql]));
-                    bool vis = qi >= vis_begin && qi < vis_begin + Nv;
+                    const int qi = qb0 + 8 * (r >> 2) + 4 * hl + (r & 3);
+                    float p = fast_exp2(__builtin_fmaf(s[r], scale_log2, -ls[8 * (r >> 2) + (r & 3)]));
+                    p = (key <= qi && qi < N) ? p : 0.0f;
+                    bool vis = qi >= vis_begin && qi < vis_end;
                     acc_vis += vis ? p : 0.0f;
                     acc_txt += vis ? 0.0f : p;
                 }
@@ -276,10 +285,50 @@ __global__ __launch_bounds__(256) void colmass_kernel(
     }
     acc_txt += __shfl_xor(acc_txt, 32, 64);
     acc_vis += __shfl_xor(acc_vis, 32, 64);
-    if (key_ok && hl == 0) {
-        size_t oidx = (((size_t)b * H + h) * Nv + (key - vis_begin)) * 2;
-        partial[oidx] = acc_txt;
-        partial[oidx + 1] = acc_vis;
+    const bool store = key_ok && hl == 0;
+    float2 *mine = partial + ((size_t)b * H + h) * Nv + (key - vis_begin);
+    if (!cm_inter) {
+        if (store) *mine = make_float2(acc_txt, acc_vis);
+        return;
+    }
+    // head means: the masses pass through memory (device-scope stores and loads), the counter says who is last
+    if (store)
+        __hip_atomic_store(reinterpret_cast<unsigned long long *>(mine),
+                           (unsigned long long)__float_as_uint(acc_vis) << 32 | __float_as_uint(acc_txt),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    drain();                                 // the stores have reached memory
+    __syncthreads();
+    if (tid == 0)
+        sm_last = __hip_atomic_fetch_add(counters + b * nk + kb, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == H - 1;
+    __syncthreads();
+    if (!sm_last) return;
+    // lane quarter hq sums heads [hq*H/4 .. ) in head order, the four partial sums are combined as
+    // (s0 + s1) + (s2 + s3), then * (1/H)
+    const int hq = tid & 3, hper = (H + 3) / 4, h_lo = hq * hper, h_hi = min(h_lo + hper, H);
+    const float invH = 1.0f / (float)H;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int i = kb * 128 + k * 64 + (tid >> 2);
+        const unsigned long long *pp = reinterpret_cast<const unsigned long long *>(partial) + (size_t)b * H * Nv + min(i, Nv - 1);
+        float st = 0.0f, sv = 0.0f;
+        for (int h0 = h_lo; h0 < h_hi; h0 += 8) {
+            unsigned long long v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = __hip_atomic_load(pp + (size_t)min(h0 + u, h_hi - 1) * Nv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (h0 + u < h_hi) {
+                    st += __uint_as_float((uint32_t)v[u]);
+                    sv += __uint_as_float((uint32_t)(v[u] >> 32));
+                }
+        }
+        st += __shfl_xor(st, 1, 64); sv += __shfl_xor(sv, 1, 64);
+        st += __shfl_xor(st, 2, 64); sv += __shfl_xor(sv, 2, 64);
+        if (i < Nv && hq == 0) {
+            cm_inter[(size_t)b * Nv + i] = st * invH;
+            cm_intra[(size_t)b * Nv + i] = sv * invH;
+        }
     }
 }
 
@@ -308,13 +357,14 @@ extern "C" size_t quota_attention_workspace_bytes(int B, int N, int H, int dh)
 {
     (void)dh;
     if (B <= 0 || N <= 0 || H <= 0) return 0;
-    // row log-sum-exp [B][H][N] + per-head column masses [B][H][N][2]
-    return (size_t)B * H * N * sizeof(float) * 3;
+    // row log-sum-exp [B][H][N] + per-head column masses [B][H][N][2] + counters of the key blocks
+    return (size_t)B * H * N * sizeof(float) * 3 + (size_t)B * ((N + 127) / 128) * sizeof(int) + 8;
 }
 
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             bool want_cues, void *ws, const float **partial_out, hipStream_t st)
+                             bool want_cues, void *ws, const float **partial_out, float *cm_inter, float *cm_intra,
+                             hipStream_t st)
 {
     if (!q_f16 || !khat_f16 || !vhat_f16 || !o_f16 || !ws) return QUOTA_ERR_NULL;
     if (B <= 0 || N < 0 || H <= 0 || Hkv <= 0 || vis_begin < 0 || Nv < 0 || vis_begin + Nv > N)
@@ -323,29 +373,32 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     if (partial_out) *partial_out = nullptr;
     if (N == 0) return QUOTA_OK;
     float *lse2 = (float *)ws;
-    float *partial = lse2 + (size_t)B * H * N;
+    size_t rows = (size_t)B * H * N;
+    rows += rows & 1;                        // the masses are pairs
+    float *partial = lse2 + rows;
+    int *counters = (int *)(partial + 2 * (size_t)B * H * N);
     float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
-    dim3 g1((N + 127) / 128, H, B), blk(256);
+    const bool cues = Nv > 0 && want_cues;
+    const int nk = (Nv + 127) / 128;
+    dim3 g1((unsigned)((N + 127) / 128) * H * B), blk(256);
     const f16 *q = (const f16 *)q_f16, *k = (const f16 *)khat_f16, *v = (const f16 *)vhat_f16;
     const double dM = (double)B * N, dd = (double)H * dh;
     {
         ProfScope prof(QUOTA_K_ATTENTION_FWD, 4.0 * B * dd * ((double)N * (N + 1) / 2),
                        4.0 * dM * dd + 4.0 * dM * Hkv * dh, st);
-        if (dh == 128)
-            attn_fwd_kernel<128><<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, lse2, scale_log2);
-        else
-            attn_fwd_kernel<64><<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, lse2, scale_log2);
+        auto kernel = dh == 128 ? attn_fwd_kernel<128> : attn_fwd_kernel<64>;
+        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, lse2, scale_log2, counters,
+                                   cues && cm_inter ? B * nk : 0);
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
-    if (Nv > 0 && want_cues) {
-        dim3 g2((Nv + 127) / 128, H, B);
+    if (cues) {
+        dim3 g2((unsigned)nk * H * B);
         // (query, visual key) pairs under the causal mask
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
-        if (dh == 128)
-            colmass_kernel<128><<<g2, blk, 0, st>>>(q, k, lse2, N, H, Hkv, vis_begin, Nv, partial, scale_log2);
-        else
-            colmass_kernel<64><<<g2, blk, 0, st>>>(q, k, lse2, N, H, Hkv, vis_begin, Nv, partial, scale_log2);
+        auto kernel = dh == 128 ? colmass_kernel<128> : colmass_kernel<64>;
+        kernel<<<g2, blk, 0, st>>>(q, k, lse2, N, H, Hkv, vis_begin, Nv, (float2 *)partial, scale_log2, cm_inter,
+                                   cm_intra, counters);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         if (partial_out) *partial_out = partial;
     }
@@ -360,7 +413,7 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
     hipStream_t st = (hipStream_t)stream;
     const float *partial = nullptr;
     int rc = quota_internal_attention(q_f16, khat_f16, vhat_f16, B, N, H, Hkv, dh, vis_begin, Nv, o_f16,
-                                      cm_inter || cm_intra, ws, &partial, st);
+                                      cm_inter || cm_intra, ws, &partial, nullptr, nullptr, st);
     if (rc != QUOTA_OK) return rc;
     if (partial) {
         colmass_reduce_kernel<<<dim3((B * Nv + 255) / 256), dim3(256), 0, st>>>(partial, B, H, Nv,
@@ -377,7 +430,7 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
 // that device current, and the kernels receive the looked-up pointer like any other buffer.
 // Every element the cue pass and the head mean read has been written earlier in the same call,
 // so nothing needs clearing between calls.
-static __device__ __align__(256) float attn_scratch[3 * QUOTA_ATTENTION_STATIC_MAX_ROWS];
+static __device__ __align__(256) float attn_scratch[4 * QUOTA_ATTENTION_STATIC_MAX_ROWS + 2];
 
 namespace {
 constexpr int kMaxDevices = 64;

@@ -212,29 +212,17 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     TRY(qkv_rope_kv_quant(L, w, M, s->pos, t->qkv != nullptr, st));
     TRY(dump(t->qkv, w.qkv, (size_t)M * (d + 2 * dkv) * 2, st));
     TRY(dump(t->q_rot, w.q_rot, (size_t)M * d * 2, st));
-    const float *partial = nullptr;     // per-head column masses; their head mean is taken by the score kernel
     TRY(quota_internal_attention(w.q_rot, w.khat, w.vhat, B, N, H, Hkv, dh, vb, Nv, w.o, score, w.attn_ws,
-                                 &partial, st));
+                                 nullptr, w.cm_inter, w.cm_intra, st));
     TRY(dump(t->o, w.o, (size_t)M * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
     const bool inject_cm = t->inject_cm_inter && t->inject_cm_intra;
 
     // Eq. 6-9: cues -> G -> fused score -> top-K_l over the visual tokens (candidate layers only)
     if (score) {
-        if (inject_cm) {
-            // the library's own cues are still produced for the dump taps
-            if (t->cm_inter || t->cm_intra) {
-                TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, nullptr, nullptr, partial, H,
-                                              w.cm_inter, w.cm_intra, B, Nv, p, w.score, 0, w.keep_idx, st));
-            }
-            TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, t->inject_cm_inter,
-                                          t->inject_cm_intra, nullptr, 0, nullptr, nullptr, B, Nv, p,
-                                          w.score, k_keep, w.keep_idx, st));
-        } else {
-            TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, nullptr, nullptr, partial, H,
-                                          w.cm_inter, w.cm_intra, B, Nv, p, w.score, k_keep, w.keep_idx,
-                                          st));
-        }
+        TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, inject_cm ? t->inject_cm_inter : w.cm_inter,
+                                      inject_cm ? t->inject_cm_intra : w.cm_intra, B, Nv, p, w.score, k_keep,
+                                      w.keep_idx, st));
         if (t->sumsq || t->ressq) {
             long n = (long)B * Nv;
             dim3 g((unsigned)((n + 255) / 256)), blk(256);

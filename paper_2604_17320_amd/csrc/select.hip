@@ -1,10 +1,12 @@
 // Token scoring (Eq. 6-8) and deterministic budgeted top-k (Eq. 9).
-// One workgroup per sequence.  Order statistics and the top-k threshold come
-// from an exact 4-pass, 8-bit radix select on order-preserving uint32 keys,
-// run by ONE WAVE with a private 256-bin LDS histogram (integer atomics, so
-// the result does not depend on execution order; no workgroup barrier inside
-// the select).  The eight percentile bounds of the four metrics are found in
-// parallel, one wave each; the top-k runs on wave 0.
+// One workgroup per sequence: a chain of small steps, bound by their latencies.  Order statistics and the top-k
+// threshold come from an exact radix select on order-preserving uint32 keys, 8 bits a pass from the highest bit
+// in which any two keys differ (a float key's top byte is nearly constant: taken as the first digit, all lanes of
+// a wave add to the same few counters, one after the other).  All waves take part, with their keys in
+// registers: four per metric, both percentile bounds in the same passes, then all sixteen for the top-k; the
+// counters are integers, so the result does not depend on execution order.  576 / 2880 tokens (32 / 40
+// heads): 25 / 113 us with one wave per bound and per top-k and the head means of the attention cues taken here,
+// 10 / 19 us so, with the head means taken by the cue pass.
 #include "common.h"
 #include "internal.h"
 
@@ -39,41 +41,105 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     return v;
 }
 
-// Exact k-th smallest (0-based rank) of the n keys key_at(i), computed by the
-// calling wave alone.  hist: 256 ints of LDS private to the wave.  All lanes
-// return the key.
-template <typename KeyAt>
-__device__ uint32_t wave_radix_select(KeyAt key_at, int n, int rank, volatile int *hist)
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v)
 {
-    const int lane = threadIdx.x & 63;
-    uint32_t prefix = 0, mask = 0;
-    int remaining = rank;
-    for (int shift = 24; shift >= 0; shift -= 8) {
+#define STEP(ctrl, rows) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, rows, 0xf, false));
+    QUOTA_DPP_STEPS(STEP)
+#undef STEP
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+constexpr int SCORE_THREADS = 1024, SCORE_WAVES = SCORE_THREADS / 64, SELECT_RANGE = 2 * SCORE_WAVES + 16;
+
+// Exact rank[r]-th smallest (0-based) of the n keys of a group of GT threads (key j of thread t of the group is number
+// t + GT j), for NR ranks at once; all SCORE_THREADS threads call this, SCORE_THREADS / GT groups work side by
+// side.  hist: 3 NR 256 ints of LDS per group (a pass clears the next one's counters), range: SELECT_RANGE
+// words of LDS.  Every thread of the group gets its results.
+template <int GT, int PERG, int NR>
+__device__ void group_select(const uint32_t (&key)[PERG], int n, const int (&rank)[NR], uint32_t (&result)[NR],
+                             int *hist, uint32_t *range)
+{
+    const int tid = threadIdx.x, lane = tid & 63, gt = tid % GT;
+    constexpr int WPG = GT / 64;                    // waves per group
+    uint32_t kmax = 0, kinv = 0;                    // largest key, largest complement of a key
 #pragma unroll
-        for (int b = 0; b < 4; ++b) hist[4 * lane + b] = 0;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        for (int i = lane; i < n; i += 64) {
-            uint32_t k = key_at(i);
-            if ((k & mask) == prefix) atomicAdd(const_cast<int *>(&hist[(k >> shift) & 0xFF]), 1);
+    for (int j = 0; j < PERG; ++j)
+        if (gt + GT * j < n) {
+            kmax = max(kmax, key[j]);
+            kinv = max(kinv, ~key[j]);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        int c0 = hist[4 * lane], c1 = hist[4 * lane + 1], c2 = hist[4 * lane + 2], c3 = hist[4 * lane + 3];
-        const int s = c0 + c1 + c2 + c3, incl = wave_incl_scan(s);
-        int excl = incl - s;
-        bool mine = remaining >= excl && remaining < incl;      // exactly one lane
-        int r = remaining - excl, digit = 4 * lane;
-        if (r >= c0) { r -= c0; ++digit;
-            if (r >= c1) { r -= c1; ++digit;
-                if (r >= c2) { r -= c2; ++digit; } } }
-        unsigned long long who = __ballot(mine);
-        int src = __ffsll((long long)who) - 1;
-        digit = __shfl(digit, src, 64);
-        remaining = __shfl(r, src, 64);
-        prefix |= (uint32_t)digit << shift;
-        mask |= 0xFFu << shift;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    kmax = wave_umax(kmax);
+    kinv = wave_umax(kinv);
+    if (lane == 0) {
+        range[2 * (tid >> 6)] = kmax;
+        range[2 * (tid >> 6) + 1] = kinv;
     }
-    return prefix;
+    for (int i = gt; i < NR * 256; i += GT) hist[i] = 0;
+    __syncthreads();
+    int bits = 0, most = 0;                         // low bits in which this group's / any group's keys differ
+    uint32_t kmin = 0;
+#pragma unroll
+    for (int g = 0; g < SCORE_WAVES / WPG; ++g) {
+        uint32_t hi = 0, lo = 0;
+#pragma unroll
+        for (int w = 0; w < WPG; ++w) {
+            hi = max(hi, range[2 * (g * WPG + w)]);
+            lo = max(lo, range[2 * (g * WPG + w) + 1]);
+        }
+        const int differ = hi == ~lo ? 0 : 32 - __clz((int)(hi ^ ~lo));
+        most = max(most, differ);
+        if (g == tid / GT) { bits = differ; kmin = ~lo; }
+    }
+    uint32_t mask = bits == 32 ? 0u : ~0u << bits, prefix[NR];
+    int remaining[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) { prefix[r] = kmin & mask; remaining[r] = rank[r]; }
+    for (int pass = 0, at = 0; 8 * pass < most; ++pass) {
+        const int next = at == 2 ? 0 : at + 1, width = min(8, bits), shift = bits - width;
+        int *h = hist + at * NR * 256, *hn = hist + next * NR * 256;
+        const uint32_t digits = (1u << width) - 1;
+        const bool split = NR > 1 && prefix[NR - 1] != prefix[0];
+        if (width > 0) {
+#pragma unroll
+            for (int j = 0; j < PERG; ++j) {
+                if (gt + GT * j >= n) continue;
+                if ((key[j] & mask) == prefix[0]) atomicAdd(&h[(key[j] >> shift) & digits], 1);
+                if (split && (key[j] & mask) == prefix[NR - 1]) atomicAdd(&h[256 + ((key[j] >> shift) & digits)], 1);
+            }
+        }
+        for (int i = gt; i < NR * 256; i += GT) hn[i] = 0;
+        __syncthreads();
+        // one wave per rank finds the digit (spread over the SIMDs)
+        int *found = reinterpret_cast<int *>(range) + 2 * SCORE_WAVES + 2 * NR * (tid / GT);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            if (width == 0 || (tid >> 6) % WPG != (NR * (tid / GT) + r) % WPG) continue;
+            const i32x4 c = *reinterpret_cast<const i32x4 *>(h + (split ? 256 * r : 0) + 4 * lane);
+            const int sum = c[0] + c[1] + c[2] + c[3], incl = wave_incl_scan(sum), excl = incl - sum;
+            int left = remaining[r] - excl, digit = 4 * lane;
+            const bool mine = left >= 0 && remaining[r] < incl;         // exactly one lane
+            if (left >= c[0]) { left -= c[0]; ++digit;
+                if (left >= c[1]) { left -= c[1]; ++digit;
+                    if (left >= c[2]) { left -= c[2]; ++digit; } } }
+            if (mine) {
+                found[2 * r] = digit;
+                found[2 * r + 1] = left;
+            }
+        }
+        __syncthreads();
+        if (width > 0) {
+            mask |= digits << shift;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                prefix[r] |= (uint32_t)found[2 * r] << shift;
+                remaining[r] = found[2 * r + 1];
+            }
+            bits = shift;
+        }
+        at = next;
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) result[r] = prefix[r];
 }
 
 // G (Eq. 7): clip to the nearest-rank percentiles and rescale to [0, 1]
@@ -88,81 +154,40 @@ __device__ __forceinline__ float robust_unit(float m, float lo, float hi)
 
 struct MetricSrc {
     const float *sumsq, *ressq, *cm_inter, *cm_intra;
-    const float *partial;   // optional per-head column masses [B][H][Nv][2] (text, visual)
-    int H;
-    float *cm_out_inter, *cm_out_intra;     // optional [B][Nv] outputs of the head means
     size_t osq, ocm;        // offsets of this sequence in the sumsq/ressq and cm arrays
 };
 
-constexpr int SCORE_THREADS = 1024;
-
 // Loads the four Eq. 6 metrics of sequence b into LDS as order-preserving keys, finds the
-// eight percentile bounds (one wave per bound, keys in LDS), then fuses the score of every
-// token.  1024 threads: the load phase is one memory round trip deep -- a thread owns a
-// quarter of the heads of up to three tokens and issues all those loads back to back.
-// mk: 4*cap keys (cap >= Nv: the stride between the four metrics), hist: 8*256 ints, lohi: 8 floats.
+// eight percentile bounds, then fuses the score of every token; key[r] is the order-preserving key of the score
+// of token tid + 1024 r (0 for NaN: ranks lowest).
+// mk: 4*cap keys (cap >= Nv: the stride between the four metrics), hist: 4 * 3 * 2 * 256 ints, range: SELECT_RANGE words.
 template <int PER>      // tokens per thread of the fusion pass: Nv <= PER * SCORE_THREADS
 __device__ void score_phase(const MetricSrc &src, int B, int Nv, int b, const quota_score_params &p,
                             float *__restrict__ score, float *__restrict__ normed, uint32_t *mk, int cap,
-                            int *hist, float *lohi)
+                            int *hist, uint32_t *range, float *lohi, uint32_t (&key)[PER])
 {
-    const int tid = threadIdx.x, wave = tid >> 6;
-    if (src.partial) {
-        // head mean: lane quarter hq sums heads [hq*H/4 .. ) in head order, the four partial
-        // sums are combined as (s0 + s1) + (s2 + s3), then * (1/H)
-        const int hq = tid & 3, hper = (src.H + 3) / 4, h_lo = hq * hper, h_hi = min(h_lo + hper, src.H);
-        const float2 *pp = reinterpret_cast<const float2 *>(src.partial) + (size_t)b * src.H * Nv;
-        const float invH = 1.0f / (float)src.H;
-        for (int i0 = 0; i0 < Nv; i0 += 3 * (SCORE_THREADS / 4)) {
-            float st[3] = {0.0f, 0.0f, 0.0f}, sv[3] = {0.0f, 0.0f, 0.0f};
-            for (int h0 = h_lo; h0 < h_hi; h0 += 8) {
-                float2 v[3][8];
-#pragma unroll
-                for (int r = 0; r < 3; ++r) {
-                    const int i = i0 + (tid >> 2) + r * (SCORE_THREADS / 4);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        v[r][u] = (i < Nv && h0 + u < h_hi) ? pp[(size_t)(h0 + u) * Nv + i] : make_float2(0.0f, 0.0f);
-                }
-#pragma unroll
-                for (int r = 0; r < 3; ++r)
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) { st[r] += v[r][u].x; sv[r] += v[r][u].y; }
-            }
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                const int i = i0 + (tid >> 2) + r * (SCORE_THREADS / 4);
-                float a = st[r], c = sv[r];
-                a += __shfl_xor(a, 1, 64); c += __shfl_xor(c, 1, 64);
-                a += __shfl_xor(a, 2, 64); c += __shfl_xor(c, 2, 64);
-                if (i < Nv && hq == 0) {
-                    const float m_inter = a * invH, m_intra = c * invH;
-                    if (src.cm_out_inter) src.cm_out_inter[src.ocm + i] = m_inter;
-                    if (src.cm_out_intra) src.cm_out_intra[src.ocm + i] = m_intra;
-                    mk[1 * cap + i] = float_key(m_inter);
-                    mk[2 * cap + i] = float_key(m_intra);
-                }
-            }
-        }
-    }
+    const int tid = threadIdx.x;
     for (int i = tid; i < Nv; i += SCORE_THREADS) {
-        if (!src.partial) {
-            mk[1 * cap + i] = float_key(src.cm_inter[src.ocm + i]);
-            mk[2 * cap + i] = float_key(src.cm_intra[src.ocm + i]);
-        }
+        mk[1 * cap + i] = float_key(src.cm_inter[src.ocm + i]);
+        mk[2 * cap + i] = float_key(src.cm_intra[src.ocm + i]);
         mk[0 * cap + i] = float_key(sqrtf(src.sumsq[src.osq + i]));    // m_mag
         mk[3 * cap + i] = float_key(sqrtf(src.ressq[src.osq + i]));    // m_res
     }
     __syncthreads();
     const int r_lo = (p.pct_lo * (Nv - 1) + 50) / 100, r_hi = (p.pct_hi * (Nv - 1) + 50) / 100;
-    if (wave < 8) {                                 // wave 2m: low bound of metric m, wave 2m+1: high bound
-        const uint32_t *keys = mk + (wave >> 1) * cap;
-        auto key_at = [&](int i) { return keys[i]; };
-        uint32_t kb = wave_radix_select(key_at, Nv, (wave & 1) ? r_hi : r_lo, hist + 256 * wave);
-        if ((tid & 63) == 0) lohi[wave] = key_float(kb);
+    {
+        constexpr int GT = SCORE_THREADS / 4;
+        const int m = tid / GT, rank[2] = {r_lo, r_hi};
+        uint32_t mkey[4 * PER], bound[2];
+#pragma unroll
+        for (int j = 0; j < 4 * PER; ++j) mkey[j] = mk[m * cap + min(tid % GT + GT * j, Nv - 1)];
+        group_select<GT, 4 * PER, 2>(mkey, Nv, rank, bound, hist + m * 3 * 2 * 256, range);
+        if (tid % GT == 0) {
+            lohi[2 * m] = key_float(bound[0]);
+            lohi[2 * m + 1] = key_float(bound[1]);
+        }
     }
     __syncthreads();
-    float sc[PER];
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
         const int i = tid + SCORE_THREADS * r;
@@ -180,7 +205,7 @@ __device__ void score_phase(const MetricSrc &src, int B, int Nv, int b, const qu
             acc = acc + rr;
             size_t o = (size_t)b * Nv + i;
             score[o] = acc;
-            sc[r] = acc;
+            key[r] = acc != acc ? 0u : float_key(acc);
             if (normed) {
                 size_t plane = (size_t)B * Nv;
                 normed[0 * plane + o] = g0;
@@ -190,56 +215,52 @@ __device__ void score_phase(const MetricSrc &src, int B, int Nv, int b, const qu
             }
         }
     }
-    __syncthreads();            // every metric key has been read: slot 0 becomes the score keys
+}
+
+// Indices of the K largest of the Nv keys (key r of thread t is number t + 1024 r), ties to the lower index, ascending.
+// Requires 0 < K < Nv.  counts: 2 * PER * SCORE_WAVES ints of LDS.
+template <int PER>
+__device__ void topk_phase(const uint32_t (&key)[PER], int Nv, int K, int32_t *__restrict__ out, int *hist,
+                           uint32_t *range, int *counts)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // threshold = K-th largest = rank (Nv - K) in ascending order
+    const int rank[1] = {Nv - K};
+    uint32_t thr[1];
+    group_select<SCORE_THREADS, PER, 1>(key, Nv, rank, thr, hist, range);
+    // 64 consecutive tokens per wave and r: how many are above / at the threshold
+    unsigned long long gt[PER], eq[PER];
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
-        const int i = tid + SCORE_THREADS * r;
-        if (i < Nv) mk[i] = (sc[r] != sc[r]) ? 0u : float_key(sc[r]);
+        const bool live = tid + SCORE_THREADS * r < Nv;
+        gt[r] = __ballot(live && key[r] > thr[0]);
+        eq[r] = __ballot(live && key[r] == thr[0]);
+        if (lane == 0) {
+            counts[2 * (r * SCORE_WAVES + wave)] = __popcll(gt[r]);
+            counts[2 * (r * SCORE_WAVES + wave) + 1] = __popcll(eq[r]);
+        }
+    }
+    __syncthreads();
+    // counts before each run of 64, by every wave for itself: lane l holds runs 2 l, 2 l + 1
+    constexpr int RUNS = PER * SCORE_WAVES;
+    int g0 = 0, g1 = 0, e0 = 0, e1 = 0;
+    if (2 * lane < RUNS) { g0 = counts[4 * lane]; e0 = counts[4 * lane + 1]; g1 = counts[4 * lane + 2]; e1 = counts[4 * lane + 3]; }
+    const int gi = wave_incl_scan(g0 + g1), ei = wave_incl_scan(e0 + e1);
+    const int need = K - __builtin_amdgcn_readlane(gi, 63);        // ties taken, lowest indices first
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const int run = r * SCORE_WAVES + wave, from = run >> 1;
+        int gb = __shfl(gi - g0 - g1, from, 64), eb = __shfl(ei - e0 - e1, from, 64);
+        if (run & 1) { gb += __shfl(g0, from, 64); eb += __shfl(e0, from, 64); }
+        const unsigned long long below = (1ull << lane) - 1;
+        gb += __popcll(gt[r] & below);
+        eb += __popcll(eq[r] & below);
+        const bool above = gt[r] >> lane & 1, at = eq[r] >> lane & 1;
+        if (above || (at && eb < need)) out[gb + min(eb, need)] = tid + SCORE_THREADS * r;
     }
 }
 
-__device__ __forceinline__ int wave_excl_scan(int v, int *total)
-{
-    const int incl = wave_incl_scan(v);
-    *total = __shfl(incl, 63, 64);
-    return incl - v;
-}
-
-// Top-k of keys[0..Nv) (LDS) by the calling wave: K largest, ties to the lower
-// index, ascending output.  Requires 0 < K < Nv.
-__device__ void topk_phase(const uint32_t *keys, int Nv, int K, int32_t *__restrict__ out, int *hist)
-{
-    const int lane = threadIdx.x & 63;
-    auto key_at = [&](int i) { return keys[i]; };
-    // threshold = K-th largest = rank (Nv - K) in ascending order
-    const uint32_t thr = wave_radix_select(key_at, Nv, Nv - K, hist);
-    // each lane owns a contiguous index range so the scans follow index order
-    const int per = (Nv + 63) / 64;
-    const int i0 = min(lane * per, Nv), i1 = min(i0 + per, Nv);
-    int n_gt = 0, n_eq = 0;
-    for (int i = i0; i < i1; ++i) {
-        n_gt += keys[i] > thr;
-        n_eq += keys[i] == thr;
-    }
-    int tot_gt, tot_eq;
-    const int eq_before = wave_excl_scan(n_eq, &tot_eq);
-    wave_excl_scan(n_gt, &tot_gt);
-    const int need = K - tot_gt;                       // ties taken, lowest indices first
-    int n_sel = 0, e = eq_before;
-    for (int i = i0; i < i1; ++i) {
-        uint32_t k = keys[i];
-        n_sel += (k > thr) || (k == thr && e < need);
-        e += k == thr;
-    }
-    int tot_sel;
-    int pos = wave_excl_scan(n_sel, &tot_sel);
-    e = eq_before;
-    for (int i = i0; i < i1; ++i) {
-        uint32_t k = keys[i];
-        if ((k > thr) || (k == thr && e < need)) out[pos++] = i;
-        e += k == thr;
-    }
-}
+constexpr int SELECT_HIST = 4 * 3 * 2 * 256;      // counters of four two-rank selects
 
 // K < 0: score only.  When K >= 0 the indices of the min(K, Nv) best tokens of
 // sequence b go to keep_idx[b][0..min(K,Nv)).
@@ -250,15 +271,17 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_topk_kernel(MetricSrc src
                                                          float *__restrict__ normed, int K,
                                                          int32_t *__restrict__ keep_idx, int cap)
 {
-    // LDS sized by the launch for this Nv: 4 * cap keys, 8 histograms of 256 bins, 8 bounds
+    // LDS sized by the launch for this Nv: counters, ranges and bounds, 4 * cap keys
     extern __shared__ __align__(16) uint32_t score_lds[];
-    uint32_t *mk = score_lds;
-    int *hist = reinterpret_cast<int *>(mk + 4 * cap);
-    float *lohi = reinterpret_cast<float *>(hist + 8 * 256);
+    int *hist = reinterpret_cast<int *>(score_lds);
+    uint32_t *range = score_lds + SELECT_HIST;
+    float *lohi = reinterpret_cast<float *>(range + SELECT_RANGE);
+    uint32_t *mk = range + SELECT_RANGE + 8;
     const int b = blockIdx.x;
     src.osq = (size_t)b * stride_sq;
     src.ocm = (size_t)b * Nv;
-    score_phase<PER>(src, B, Nv, b, p, score, normed, mk, cap, hist, lohi);
+    uint32_t key[PER];
+    score_phase<PER>(src, B, Nv, b, p, score, normed, mk, cap, hist, range, lohi, key);
     if (K < 0) return;
     const int k = K < Nv ? K : Nv;
     int32_t *out = keep_idx + (size_t)b * k;
@@ -266,45 +289,50 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_topk_kernel(MetricSrc src
         for (int i = threadIdx.x; i < Nv; i += SCORE_THREADS) out[i] = i;
         return;
     }
-    __syncthreads();
-    if (threadIdx.x < 64 && k > 0) topk_phase(mk, Nv, k, out, hist);
+    if (k == 0) return;
+    __syncthreads();            // the counters and keys have been read
+    topk_phase<PER>(key, Nv, k, out, hist, range, (int *)mk);
 }
 
-__global__ __launch_bounds__(256) void topk_kernel(const float *__restrict__ score, int Nv, int K,
-                                                   int32_t *__restrict__ keep_idx)
+template <int PER>
+__global__ __launch_bounds__(SCORE_THREADS) void topk_kernel(const float *__restrict__ score, int Nv, int K,
+                                                             int32_t *__restrict__ keep_idx)
 {
-    __shared__ uint32_t keys[MAXV];
-    __shared__ int hist[256];
+    __shared__ __align__(16) int hist[3 * 256];
+    __shared__ uint32_t range[SELECT_RANGE];
+    __shared__ int counts[2 * PER * SCORE_WAVES];
     const int b = blockIdx.x;
     int32_t *out = keep_idx + (size_t)b * K;
     if (K >= Nv) {          // host passes K <= Nv; K == Nv keeps every token
-        for (int i = threadIdx.x; i < Nv; i += 256) out[i] = i;
+        for (int i = threadIdx.x; i < Nv; i += SCORE_THREADS) out[i] = i;
         return;
     }
-    for (int i = threadIdx.x; i < Nv; i += 256) {
-        float f = score[(size_t)b * Nv + i];
-        keys[i] = (f != f) ? 0u : float_key(f);       // NaN ranks lowest
+    uint32_t key[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const float f = score[(size_t)b * Nv + min((int)threadIdx.x + SCORE_THREADS * r, Nv - 1)];
+        key[r] = f != f ? 0u : float_key(f);          // NaN ranks lowest
     }
-    __syncthreads();
-    if (threadIdx.x < 64) topk_phase(keys, Nv, K, out, hist);
+    topk_phase<PER>(key, Nv, K, out, hist, range, counts);
 }
 
-// Launches the score (+ top-k) kernel with the LDS its Nv needs: up to 136 KB at 8192 tokens, which
+// Launches the score (+ top-k) kernel with the LDS its Nv needs: up to 153 KB at 8192 tokens, which
 // is above the default limit of a launch and has to be granted once per device.
 int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const quota_score_params &p,
                       float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st)
 {
     const int cap = (Nv + 63) & ~63;
-    const size_t lds = ((size_t)4 * cap + 8 * 256 + 8) * sizeof(uint32_t);
-    if (Nv > 3 * SCORE_THREADS) {          // the widest instantiation: up to 136 KB, above a launch's default 64 KB
+    const size_t lds = ((size_t)4 * cap + SELECT_HIST + SELECT_RANGE + 8) * sizeof(uint32_t);
+    if (Nv > 2 * SCORE_THREADS) {          // the widest instantiations: up to 153 KB, above a launch's default 64 KB
         static bool granted[64];
         int dev = -1;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return QUOTA_ERR_HIP;
         if (!granted[dev]) {
-            const size_t most = ((size_t)4 * MAXV + 8 * 256 + 8) * sizeof(uint32_t);
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(score_topk_kernel<MAXV / SCORE_THREADS>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
-                return QUOTA_ERR_HIP;
+            const size_t most = ((size_t)4 * MAXV + SELECT_HIST + SELECT_RANGE + 8) * sizeof(uint32_t);
+            for (auto k : {score_topk_kernel<3>, score_topk_kernel<MAXV / SCORE_THREADS>})
+                if (hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)most) != hipSuccess)
+                    return QUOTA_ERR_HIP;
             granted[dev] = true;
         }
     }
@@ -335,30 +363,24 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
     if (rc != QUOTA_OK) return rc;
     if (Nv == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_SCORE_TOKENS, 0, 20.0 * B * Nv, st);
-    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, nullptr, 0, nullptr, nullptr, 0, 0};
+    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
     return launch_score_topk(src, stride_sq, B, Nv, *p, score, normed, -1, nullptr, st);
 }
 
-// score + top-k in one launch (the layer's path).  The attention cues come either as
-// head-averaged arrays (cm_inter / cm_intra) or, when `partial` is given, as the
-// per-head column masses [B][H][Nv][2] whose head mean is taken here; cm_out_* (optional)
-// then receive the head means.
+// score + top-k in one launch (the layer's path)
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
-                              const float *cm_inter, const float *cm_intra, const float *partial,
-                              int H, float *cm_out_inter, float *cm_out_intra, int B, int Nv,
+                              const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
                               hipStream_t st)
 {
-    if (!sumsq || !ressq || !p || !score || !keep_idx) return QUOTA_ERR_NULL;
-    if (!partial && (!cm_inter || !cm_intra)) return QUOTA_ERR_NULL;
-    if (B <= 0 || Nv < 0 || K < 0 || (partial && H <= 0) || p->pct_lo < 0 || p->pct_hi > 100 ||
-        p->pct_lo > p->pct_hi)
+    if (!sumsq || !ressq || !p || !score || !keep_idx || !cm_inter || !cm_intra) return QUOTA_ERR_NULL;
+    if (B <= 0 || Nv < 0 || K < 0 || p->pct_lo < 0 || p->pct_hi > 100 || p->pct_lo > p->pct_hi)
         return QUOTA_ERR_INVALID_ARG;
     if (Nv > MAXV) return QUOTA_ERR_SHAPE;
     if (Nv == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_SCORE_TOKENS, 0,
-                   (partial ? 8.0 * H + 8 : 20.0) * B * Nv + 4.0 * B * (K < Nv ? K : Nv), st);
-    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, partial, H, cm_out_inter, cm_out_intra, 0, 0};
+                   20.0 * B * Nv + 4.0 * B * (K < Nv ? K : Nv), st);
+    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
     return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st);
 }
 
@@ -387,7 +409,8 @@ extern "C" int quota_topk_prune(const float *score, int B, int Nv, int K, int32_
     int k = K < Nv ? K : Nv;
     if (k == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_TOPK_PRUNE, 0, 4.0 * B * Nv + 4.0 * B * k, (hipStream_t)stream);
-    topk_kernel<<<dim3(B), dim3(256), 0, (hipStream_t)stream>>>(score, Nv, k, keep_idx);
+    auto kernel = Nv <= SCORE_THREADS ? topk_kernel<1> : topk_kernel<MAXV / SCORE_THREADS>;
+    kernel<<<dim3(B), dim3(SCORE_THREADS), 0, (hipStream_t)stream>>>(score, Nv, k, keep_idx);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
