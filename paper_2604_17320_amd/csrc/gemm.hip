@@ -511,7 +511,7 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
     if (!qa8 || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
     if (W->N % 64 != 0 || W->K % 32 != 0) return QUOTA_ERR_SHAPE;
     if (M <= 0) return QUOTA_OK;
-    if (M <= 16) return quota_internal_rows16(qa8, true, sa, M, W, y_f16, ldy, residual_opt, ldr, st);
+    if (M <= 16) return quota_internal_rows16(qa8, QUOTA_ROWS16_A8, sa, M, W, y_f16, ldy, residual_opt, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
     return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
@@ -534,7 +534,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (acc_i32_opt)
         return launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
     if (M <= 16)            // the decode step: stream the weights once
-        return quota_internal_rows16(qa, false, sa, M, W, y, ldy, res, ldr, st);
+        return quota_internal_rows16(qa, QUOTA_ROWS16_PACKED, sa, M, W, y, ldy, res, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
     return launch_f8(tile_kernel<true, false>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }

@@ -74,8 +74,14 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
 
 // GEMM of at most 16 rows (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
 // quota_internal_rows16_quantizes accepts: as they are, through RMSNorm, or gate | up rows through SwiGLU.
-int quota_internal_rows16(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W, void *y, int ldy,
+enum quota_rows16_format { QUOTA_ROWS16_A8, QUOTA_ROWS16_PACKED, QUOTA_ROWS16_FRAG };
+int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const float *sa, int M, const quota_weights *W, void *y, int ldy,
                           const void *res, int ldr, hipStream_t st);
+int quota_internal_rmsnorm_quantize_frag(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qf,
+                                         float *scale, hipStream_t st);
+int quota_internal_silu_mul_quantize_frag(const void *gu_f16, int M, int F, uint8_t *qf, float *scale, void *z_opt,
+                                          const void *z_inject_opt, hipStream_t st);
+int quota_internal_quantize_frag(const void *x_f16, int M, int d, uint8_t *qf, float *scale, hipStream_t st);
 bool quota_internal_rows16_quantizes(int M, int K);
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
                                    int ldr, hipStream_t st);

@@ -24,7 +24,7 @@ struct Carver {
 };
 
 struct LayerWs {
-    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format or packed
+    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format or fragments
     float *sa;
     f16 *qkv, *q_rot, *khat, *vhat, *o;
     uint8_t *skc, *svc; // staged 4-bit K/V of all rows
@@ -42,7 +42,7 @@ LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
     LayerWs w;
     size_t M = (size_t)B * N, d = (size_t)H * dh, dkv = (size_t)Hkv * dh;
     size_t kmax = d > (size_t)F ? d : (size_t)F;
-    w.qa = c.take<uint8_t>(M * quota_a8_row_bytes((int)kmax));
+    w.qa = c.take<uint8_t>((M > 8 ? M : 8) * quota_a8_row_bytes((int)kmax));       // (fragments of a few rows: 1 KB a group)
     w.sa = c.take<float>(M);
     w.qkv = c.take<f16>(M * (d + 2 * dkv));
     w.q_rot = c.take<f16>(M * d);
@@ -114,16 +114,16 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
                                         w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st);
 }
 
-// RMSNorm, quantizer, GEMM; SwiGLU product, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_PACKED rows stay packed
-// int4 in between (the GEMM of a few rows reads them faster so), and a few leave the quantizer to the GEMM.
-#define ROWS_PACKED 16
+// RMSNorm, quantizer, GEMM; SwiGLU product, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_FRAG rows go
+// through the few-row GEMM's own format, and a few leave the quantizer to the GEMM.
+#define ROWS_FRAG 16
 static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
                         const quota_weights *W, void *y, int ldy, hipStream_t st)
 {
     if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_rmsnorm(x, gamma, eps, M, W, y, ldy, st);
-    if (M <= ROWS_PACKED) {
-        TRY(quota_rmsnorm_quantize_act(x, M, d, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, nullptr, st));
-        return quota_internal_rows16(w.qa, false, w.sa, M, W, y, ldy, nullptr, 0, st);
+    if (M <= ROWS_FRAG) {
+        TRY(quota_internal_rmsnorm_quantize_frag(x, M, d, gamma, eps, w.qa, w.sa, st));
+        return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, nullptr, 0, st);
     }
     TRY(quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
@@ -133,9 +133,9 @@ static int silu_mul_gemm(const LayerWs &w, int M, int F, void *z, const void *z_
 {
     if (quota_internal_rows16_quantizes(M, F))
         return quota_internal_rows16_silu(w.gu, z, z_inject, M, W, y, ldy, res, ldr, st);
-    if (M <= ROWS_PACKED) {
-        TRY(quota_silu_mul_quantize_act(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
-        return quota_internal_rows16(w.qa, false, w.sa, M, W, y, ldy, res, ldr, st);
+    if (M <= ROWS_FRAG) {
+        TRY(quota_internal_silu_mul_quantize_frag(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
+        return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, res, ldr, st);
     }
     TRY(quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
@@ -144,9 +144,9 @@ static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const qu
                          const void *res, int ldr, hipStream_t st)
 {
     if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_quantize(x, M, W, y, ldy, res, ldr, st);
-    if (M <= ROWS_PACKED) {
-        TRY(quota_quantize_act(x, M, d, d, w.qa, w.sa, nullptr, nullptr, st));
-        return quota_internal_rows16(w.qa, false, w.sa, M, W, y, ldy, res, ldr, st);
+    if (M <= ROWS_FRAG) {
+        TRY(quota_internal_quantize_frag(x, M, d, w.qa, w.sa, st));
+        return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, res, ldr, st);
     }
     TRY(quota_internal_quantize_a8(x, M, d, w.qa, w.sa, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);

@@ -531,20 +531,46 @@ int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_
     return silu_mul_quantize(gu_f16, M, F, RowOutA8{(uint2 *)qa8}, scale, z_opt, z_inject_opt, st);
 }
 
+template <typename OUT>
+static int quantize_rows(const void *x_f16, int M, int d, OUT q, float *scale, hipStream_t st)
+{
+    ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
+    const bool many = d > 16384, few = (d >> 3) <= 512;
+    auto kernel = many ? quantize_act_kernel<false, 256, 16, OUT>
+                       : few ? quantize_act_kernel<false, 256, 2, OUT> : quantize_act_kernel<false, 256, 8, OUT>;
+    kernel<<<dim3(M), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, q, scale, nullptr, nullptr);
+    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    return QUOTA_OK;
+}
+
 // Per-token quantizer of a dense fp16 [M][d] into the A8 format.
 int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st)
 {
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
-    if (rc != QUOTA_OK) return rc;
-    if (M == 0) return QUOTA_OK;
-    ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
-    const bool many = d > 16384, few = (d >> 3) <= 512;
-    auto kernel = many ? quantize_act_kernel<false, 256, 16, RowOutA8>
-                       : few ? quantize_act_kernel<false, 256, 2, RowOutA8> : quantize_act_kernel<false, 256, 8, RowOutA8>;
-    kernel<<<dim3(M), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, RowOutA8{(uint2 *)qa8}, scale,
-                                                  nullptr, nullptr);
-    QUOTA_RETURN_IF_LAUNCH_FAILED();
-    return QUOTA_OK;
+    if (rc != QUOTA_OK || M == 0) return rc;
+    return quantize_rows(x_f16, M, d, RowOutA8{(uint2 *)qa8}, scale, st);
+}
+
+// The three quantizers of at most 16 rows into the few-row GEMM's fragments.
+int quota_internal_rmsnorm_quantize_frag(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qf,
+                                         float *scale, hipStream_t st)
+{
+    int rc = check_rows(x_f16, M, d, d, qf, scale);
+    if (rc != QUOTA_OK || M == 0) return rc;
+    return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, RowOutFrag{(uint32_t *)qf}, scale, nullptr, nullptr, nullptr, st);
+}
+int quota_internal_silu_mul_quantize_frag(const void *gu_f16, int M, int F, uint8_t *qf, float *scale, void *z_opt,
+                                          const void *z_inject_opt, hipStream_t st)
+{
+    int rc = check_rows(gu_f16, M, F, F, qf, scale);
+    if (rc != QUOTA_OK || M == 0) return rc;
+    return silu_mul_quantize(gu_f16, M, F, RowOutFrag{(uint32_t *)qf}, scale, z_opt, z_inject_opt, st);
+}
+int quota_internal_quantize_frag(const void *x_f16, int M, int d, uint8_t *qf, float *scale, hipStream_t st)
+{
+    int rc = check_rows(x_f16, M, d, d, qf, scale);
+    if (rc != QUOTA_OK || M == 0) return rc;
+    return quantize_rows(x_f16, M, d, RowOutFrag{(uint32_t *)qf}, scale, st);
 }
 
 // Eq. 6 vector metrics only (no codes stored): sumsq/ressq [B][Nv] of the

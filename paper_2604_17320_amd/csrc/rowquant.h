@@ -8,12 +8,19 @@
 #define ROW_MAXCHUNK 16  // workgroup-per-row kernels: 16 chunks * 8 halves * 256 threads = 32768 columns
 #define ROW_MAXCOLS 32768
 
-// Where a quantized row goes: packed int4 (the public format, two codes per byte) or the GEMM's A8 format --
-// e4m3 bytes, every 8 codes as evens then odds, each row zero-padded to whole 128-channel groups.  A null
-// pointer drops the output.
+// Where a quantized row goes: packed int4 (the public format, two codes per byte), the GEMM's A8 format --
+// e4m3 bytes, every 8 codes as evens then odds, each row zero-padded to whole 128-channel groups -- or, for at
+// most 16 rows, packed int4 as the few-row GEMM's fragments: 1 KB per group, the 32 codes number q of row m's
+// 128 at 16-byte piece 16 q + m.  A null pointer drops the output.
 struct RowOutPacked {
     static constexpr bool A8 = false;
     uint32_t *q;
+    static __device__ __forceinline__ int at(int c) { return c; }
+};
+struct RowOutFrag {
+    static constexpr bool A8 = false;
+    uint32_t *q;
+    static __device__ __forceinline__ int at(int c) { return (c >> 4) * 256 + (c >> 2 & 3) * 64 + (c & 3); }
 };
 struct RowOutA8 {
     static constexpr bool A8 = true;
@@ -23,6 +30,7 @@ __host__ __device__ __forceinline__ RowOutPacked row_out(RowOutPacked o, size_t 
 {
     return RowOutPacked{o.q ? o.q + row * nchunk : nullptr};
 }
+__host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row, int) { return RowOutFrag{o.q + 4 * row}; }
 __host__ __device__ __forceinline__ RowOutA8 row_out(RowOutA8 o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
@@ -65,7 +73,7 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
             if constexpr (OUT::A8) {
                 out.q[c] = units_to_e4m3(unit);
             } else {
-                if (out.q) out.q[c] = word;
+                if (out.q) out.q[OUT::at(c)] = word;
             }
         }
     }

@@ -8,10 +8,12 @@
 // v_mfma_f32_16x16x128_f8f6f4 per group and 16 columns, one more against the constant -8 / 512 per group.
 // Packed activations carry the same offset, (a + 8)(w + 8) - 8 (a + 8) - 8 (w + 8) + 64 = a w, and need one more
 // constant product per group and 16 columns: that costs less than reading them as bytes (every CU reads all
-// of them; 16 x 4096 x 11008: 11.0 us with byte activations, 9.7 packed).
+// of them; 16 x 4096 x 11008: 11.0 us with byte activations, 9.7 packed).  Inside a layer the quantizer leaves
+// them as the fragments that the lanes want: a KB of 16 different rows takes the CU 27 ns to load, a contiguous
+// one 7 (16 x 12288 x 4096: 8.6 -> 7.8 us).
 // NB = 16-column blocks per workgroup.
 //
-// Few rows (MODE > PACKED) also bring their own quantizer: every workgroup normalises / multiplies / quantizes
+// Few rows (MODE > FRAG) also bring their own quantizer: every workgroup normalises / multiplies / quantizes
 // the whole rows for itself while its first weights are on their way.  That is a few thousand elements per
 // row, read from L2, against a launch and a pass of 16 workgroups that cost 4 to 5 us; from five rows on
 // the repeated work costs more than the launch.
@@ -22,10 +24,10 @@
 
 namespace {
 
-enum { ROWS_A8 = 0, ROWS_PACKED, ROWS_QUANT, ROWS_RMSNORM, ROWS_SILU };
+enum { ROWS_A8 = 0, ROWS_PACKED, ROWS_FRAG, ROWS_QUANT, ROWS_RMSNORM, ROWS_SILU };
 
 struct RowsIn {
-    const uint8_t *qa;          // A8 / PACKED: activations and token scales
+    const uint8_t *qa;          // A8 / PACKED / FRAG: activations and token scales
     const float *sa;
     const f16 *x;               // QUANT, RMSNORM: rows [M][K]; SILU: gate | up rows [M][2K]
     const float *gamma;         // RMSNORM
@@ -38,10 +40,10 @@ constexpr int RT_THREADS = 512;
 
 // The rows' quantizer: 8 / rows (rounded to a power of two) waves per row, a thread caches its NC chunks of 8
 // channels; the same arithmetic as the row kernels in quant.hip.  Leaves e4m3 rows of `stride` bytes and
-// the token scales in LDS.
-template <int MODE, int NC>
+// the token scales in LDS.  fetch() sets off the first weights, behind the loads that the rows wait for.
+template <int MODE, int NC, typename Fetch>
 __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, int G, uint8_t *codes, int stride,
-                                              float *scales, double *red)
+                                              float *scales, double *red, Fetch fetch)
 {
     const int wpr = M == 1 ? 8 : M == 2 ? 4 : 2;            // waves per row
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = wave / wpr, part = wave % wpr;
@@ -76,6 +78,7 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
                 if (in.z_inject) v[c0 + c].u = reinterpret_cast<const uint4 *>(in.z_inject + (size_t)r * K)[i];
                 else { v[c0 + c].u = gr[i]; u[c].u = ur[i]; }
             }
+            if (c0 == 0) fetch();
             if (!in.z_inject)
 #pragma unroll
                 for (int c = 0; c < CB; ++c)
@@ -94,6 +97,7 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
         const uint4 *xr = reinterpret_cast<const uint4 *>(in.x + (size_t)r * K);
 #pragma unroll
         for (int c = 0; c < NC; ++c) v[c].u = xr[min(idx + T * c, nchunk - 1)];
+        if (MODE != ROWS_RMSNORM) fetch();
     }
     // (a clamped chunk repeats one of the row's: harmless for a maximum, left out of the sum)
     if (MODE == ROWS_RMSNORM) {
@@ -105,6 +109,7 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
             ga[c][0] = gp[0];
             ga[c][1] = gp[1];
         }
+        fetch();
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (idx + T * c < nchunk)
@@ -185,7 +190,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
     float *row_scale = xbuf + 2 * BUF;                                            // [16]
     double *red = reinterpret_cast<double *>(row_scale + 16);                     // [16]
-    uint8_t *codes = reinterpret_cast<uint8_t *>(red + 16);                       // [M][code_stride], MODE > PACKED
+    uint8_t *codes = reinterpret_cast<uint8_t *>(red + 16);                       // [M][code_stride], MODE > FRAG
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -208,7 +213,9 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             const uint4 *wg = wp + ((size_t)g * N + n0) * 4;
 #pragma unroll
             for (int j = 0; j < NB; ++j) rb[u][j] = wg[64 * j + 4 * c16 + q];
-            if (MODE == ROWS_A8) {
+            if (MODE == ROWS_FRAG) {
+                ra[u][0] = *reinterpret_cast<const uint4 *>(in.qa + (size_t)g * 1024 + 16 * lane);
+            } else if (MODE == ROWS_A8) {
                 const uint4 *ag = reinterpret_cast<const uint4 *>(arow + g * 128 + 32 * q);
                 ra[u][0] = ag[0];
                 ra[u][MODE == ROWS_A8 ? 1 : 0] = ag[1];
@@ -224,8 +231,10 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     };
     const int nblk = N / (16 * NB);
     int blk = blockIdx.x, r0 = 0, par = 0;
-    fetch(blk * 16 * NB, 0);
-    if constexpr (MODE > ROWS_PACKED) quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red);
+    if constexpr (MODE > ROWS_FRAG)
+        quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] { fetch(blk * 16 * NB, 0); });
+    else
+        fetch(blk * 16 * NB, 0);
     const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
     while (true) {                                  // rounds of this workgroup's column blocks
@@ -238,7 +247,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             if constexpr (MODE == ROWS_A8) {
                 a0 = ra[u][0];
                 a1 = ra[u][1];
-            } else if constexpr (MODE == ROWS_PACKED) {
+            } else if constexpr (MODE == ROWS_PACKED || MODE == ROWS_FRAG) {
                 unsigned_e4m3(ra[u][0], a0, a1);
             } else {
                 const int g = min(r0 + 8 * u + wave, G - 1);
@@ -247,7 +256,8 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                 a1 = ag[1];
             }
             const i32x8 fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
-            const float c0 = MODE == ROWS_PACKED ? 64.0f * 128.0f / F8_UNIT : 0.0f;
+            constexpr bool OFFSET_A = MODE == ROWS_PACKED || MODE == ROWS_FRAG;
+            const float c0 = OFFSET_A ? 64.0f * 128.0f / F8_UNIT : 0.0f;
             const f32x4 k4 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{c0, c0, c0, c0}, 0, 0, 0, 0, 0, 0);
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
@@ -255,7 +265,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                 unsigned_e4m3(rb[u][j], b0, b1);
                 const i32x8 fb = i32x8{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, (int)b1.x, (int)b1.y, (int)b1.z, (int)b1.w};
                 f32x4 k = k4;
-                if (MODE == ROWS_PACKED) k = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(minus8, fb, k, 0, 0, 0, 0, 0, 0);
+                if (OFFSET_A) k = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(minus8, fb, k, 0, 0, 0, 0, 0, 0);
                 acc[u][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, fb, k, 0, 0, 0, 0, 0, 0);
             }
         }
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                 for (int o = 0; o < OPT; ++o) {
                     const int on = blk * 16 * NB + 16 * (2 * o + oj) + (ol & 15);
                     if (om < M) {
-                        const float sa = MODE <= ROWS_PACKED ? in.sa[om] : row_scale[om];
+                        const float sa = MODE <= ROWS_FRAG ? in.sa[om] : row_scale[om];
                         float v = y32[o] * (sa * F8_UNIT);
                         if (res) v = v + (float)res[(size_t)om * ldr + on];
                         y[(size_t)om * ldy + on] = to_f16(v);
@@ -324,7 +334,7 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 {
     constexpr int R = 8 * U;
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    const size_t lds = 2 * (R * NB * 1024 + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_PACKED ? (size_t)M * code_stride : 0);
+    const size_t lds = 2 * (R * NB * 1024 + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
     if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC>>()) return QUOTA_ERR_HIP;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
@@ -346,11 +356,11 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
            hipStream_t st)
 {
     if (W->N <= 4096) {
-        if constexpr (MODE <= ROWS_PACKED)
+        if constexpr (MODE <= ROWS_FRAG)
             if (W->K > 8192) return launch_rows16<1, 4, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
         return launch_rows16<1, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }
-    if constexpr (MODE <= ROWS_PACKED)
+    if constexpr (MODE <= ROWS_FRAG)
         if (W->N > 8192) return launch_rows16<2, 1, 768, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
     return launch_rows16<2, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
 }
@@ -375,14 +385,17 @@ bool quota_internal_rows16_quantizes(int M, int K)
     return M <= 4 && (16 * G + T - 1) / T <= 6;            // six chunks of a row per thread fit in registers
 }
 
-int quota_internal_rows16(const uint8_t *qa, bool a8, const float *sa, int M, const quota_weights *W, void *y, int ldy,
+int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const float *sa, int M, const quota_weights *W, void *y, int ldy,
                           const void *res, int ldr, hipStream_t st)
 {
     RowsIn in = {};
     in.qa = qa;
     in.sa = sa;
-    return a8 ? rows16<ROWS_A8, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st)
-              : rows16<ROWS_PACKED, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+    switch (format) {
+    case QUOTA_ROWS16_A8: return rows16<ROWS_A8, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+    case QUOTA_ROWS16_FRAG: return rows16<ROWS_FRAG, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+    default: return rows16<ROWS_PACKED, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+    }
 }
 
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
