@@ -69,6 +69,10 @@ size_t quota_weights_scale_bytes(int N, int K);
 int quota_quantize_weights(const float *w, int N, int K, int8_t *codes,
                            void *scales_f16, void *stream);
 
+/* The two calls above and below in one pass, for weights whose plain codes nobody keeps: w fp32 [N][K] with
+ * W's N and K, 16-byte aligned (QUOTA_ERR_INVALID_ARG otherwise) -> W->packed / W->scales, the same bytes. */
+int quota_quantize_pack_weights(const float *w, const quota_weights *W, void *stream);
+
 /* Repack plain row-major codes (int8, one per byte, values in [-8,7]) and
  * scales (fp16 [N][ceil(K/128)]) into W->packed / W->scales.  Requires
  * N % 64 == 0 and K % 32 == 0 (QUOTA_ERR_SHAPE otherwise). */

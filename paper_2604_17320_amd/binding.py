@@ -134,6 +134,13 @@ def quota_quantize_weights(w, codes, scales):
                                         _ptr(scales, torch.float16), _stream()), "quota_quantize_weights")
 
 
+def quota_quantize_pack_weights(w, W: Weights):
+    if tuple(w.shape) != (W.N, W.K):
+        raise ValueError("w is not [N, K] of the descriptor")
+    _check(lib().quota_quantize_pack_weights(_ptr(w, torch.float32), C.byref(W), _stream()),
+           "quota_quantize_pack_weights")
+
+
 def quota_pack_weights(codes, scales, W: Weights):
     _check(lib().quota_pack_weights(_ptr(codes, torch.int8), _ptr(scales, torch.float16),
                                     C.byref(W), _stream()), "quota_pack_weights")

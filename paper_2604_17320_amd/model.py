@@ -38,10 +38,15 @@ class PackedLinear:
     def from_fp32(cls, w: torch.Tensor, keep_plain: bool = False) -> "PackedLinear":
         """Quantize an fp32 [N,K] device matrix on the GPU, then pack it."""
         N, K = w.shape
+        w = w.contiguous()
+        if not keep_plain and w.data_ptr() % 16 == 0:
+            self = cls(N, K)
+            qb.quota_quantize_pack_weights(w, self.desc)
+            return self
         G = (K + 127) // 128
         codes = torch.empty((N, K), dtype=torch.int8, device=w.device)
         scales = torch.empty((N, G), dtype=torch.float16, device=w.device)
-        qb.quota_quantize_weights(w.contiguous(), codes, scales)
+        qb.quota_quantize_weights(w, codes, scales)
         self = cls.from_codes(codes, scales)
         if keep_plain:
             self.codes, self.plain_scales = codes, scales

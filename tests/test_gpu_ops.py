@@ -65,6 +65,20 @@ def test_quantize_and_pack_weights(qb, N, K):
     assert np.array_equal(host(lin.scales).reshape(G, N).view(np.uint16), scales.T.view(np.uint16))
 
 
+@pytest.mark.parametrize("N,K", [(64, 32), (64, 1376), (192, 4096), (576, 11008), (128, 160)])
+def test_one_pass_weight_packing_equals_the_two_calls(qb, N, K):
+    from paper_2604_17320_amd.model import PackedLinear
+    w = wl.rng(4, "w", N, K).standard_normal((N, K), dtype=np.float32) * np.float32(0.02)
+    w[1, :128] = 0
+    w[N - 1, K - 1] = 1e-9
+    w[2, :32] = 3.5 * np.arange(-16, 16)                # ties of the rounding
+    one, two = PackedLinear.from_fp32(dev(w)), PackedLinear.from_fp32(dev(w), keep_plain=True)
+    assert torch.equal(one.packed, two.packed) and torch.equal(one.scales, two.scales)
+    off = dev(np.concatenate([np.zeros(1, np.float32), w.ravel()]))[1:].view(N, K)      # not 16-byte aligned
+    three = PackedLinear.from_fp32(off)
+    assert torch.equal(three.packed, two.packed) and torch.equal(three.scales, two.scales)
+
+
 def test_pack_weights_rejects_bad_shapes(qb):
     W = qb.Weights(48, 512, 1, 1)
     z = torch.zeros(8, dtype=torch.int8, device="cuda")
