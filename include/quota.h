@@ -14,6 +14,9 @@
  *     that stream; none synchronises.  Calls on one stream are ordered.
  *   - Every call returns QUOTA_OK or a negative error code and enqueues
  *     nothing when it returns an error.  No exceptions cross the boundary.
+ *   - Device buffers start at multiples of 16 bytes (every allocator's do).
+ *     Where a call says "any address" for one of them, the alignment of its
+ *     elements is enough.
  *   - fp16 = IEEE binary16.  int4 data is two's complement, two codes per
  *     byte, element 2j in bits 0-3 and element 2j+1 in bits 4-7.
  *   - Weight groups are 128 input channels (QUOTA_GROUP_W), KV groups are 64
@@ -411,7 +414,8 @@ size_t quota_fp_block_workspace_bytes(const quota_fp_layer *L, int B, int N);
  * q|k|v projection, rotate-half RoPE at pos, causal softmax attention with
  * grouped K/V heads, output projection + residual, RMSNorm, SwiGLU, +
  * residual) on x fp16 [B][N][d], fp16 storage between the steps, fp32
- * accumulation, nothing quantized.  x_out fp16 [B][N][d].
+ * accumulation, nothing quantized.  x_out fp16 [B][N][d].  x, x_out, the
+ * gammas and the angle tables may lie at any address.
  * ws: quota_fp_block_workspace_bytes bytes.
  * QUOTA_ERR_SHAPE for dh not 64 / 128, H % Hkv != 0, F % 32 != 0. */
 int quota_fp_block(const quota_fp_layer *L, const void *x_f16, const int32_t *pos,
@@ -420,8 +424,8 @@ int quota_fp_block(const quota_fp_layer *L, const void *x_f16, const int32_t *po
 /* Numerator and denominator of Eq. 1 for each of B samples: diff_norm[b] =
  * ||x^q_b - x_b||_2, ref_norm[b] = ||x_b||_2 over the n_per_sample fp16 values
  * of sample b (all its tokens and channels), accumulated in fp64.  xq, x fp16
- * [B][n_per_sample]; diff_norm, ref_norm fp64 [B] (device).  Copy them to the
- * host for quota_sensitivity. */
+ * [B][n_per_sample], at any address; diff_norm, ref_norm fp64 [B] (device).
+ * Copy them to the host for quota_sensitivity. */
 int quota_activation_deviation(const void *xq_f16, const void *x_f16, int B,
                                long n_per_sample, double *diff_norm,
                                double *ref_norm, void *stream);

@@ -23,6 +23,19 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
+// Vectors at addresses aligned as their elements are: the chip takes them with the same 16-byte instructions.
+// For tensors whose caller promises no more than that.
+typedef f16x8 f16x8_at2 __attribute__((aligned(2)));
+typedef f32x4 f32x4_at4 __attribute__((aligned(4)));
+__device__ __forceinline__ uint4 load16_at2(const f16 *p)
+{
+    return __builtin_bit_cast(uint4, *reinterpret_cast<const f16x8_at2 *>(p));
+}
+__device__ __forceinline__ void store16_at2(f16 *p, const uint4 &v)
+{
+    *reinterpret_cast<f16x8_at2 *>(p) = __builtin_bit_cast(f16x8, v);
+}
+
 union Pack16 {           // 16 bytes seen as halves, dwords or one vector load
     uint4 u;
     f16 h[8];

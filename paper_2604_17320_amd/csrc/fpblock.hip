@@ -19,7 +19,8 @@ namespace {
 // 16 MFMAs = 512 cycles.  LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
 // Lane l supplies 8 consecutive k of row (l % 32) to both operands (k slots 8 (l / 32) .. +7 of the
 // step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.
-// Rows beyond M and N repeat the last one and are not stored.  Needs N % 64 == 0, K % 16 == 0.
+// Rows beyond M and N repeat the last one and are not stored.  Needs N % 64 == 0, K % 16 == 0, x and W at
+// multiples of 16 bytes; residual and y may lie anywhere.
 __global__ __launch_bounds__(256, 2) void fp_gemm_kernel(const f16 *__restrict__ x, int M, int K,
                                                          const f16 *__restrict__ W, int N,
                                                          const f16 *__restrict__ residual,
@@ -110,29 +111,29 @@ __global__ __launch_bounds__(256, 2) void fp_gemm_kernel(const f16 *__restrict__
             float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             Pack16 o, rv;
             if (residual) {
-                rv.u = *reinterpret_cast<const uint4 *>(residual + (size_t)m * N + n);
+                rv.u = load16_at2(residual + (size_t)m * N + n);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] += (float)rv.h[e];
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) o.h[e] = (f16)v[e];
-            *reinterpret_cast<uint4 *>(y + (size_t)m * N + n) = o.u;
+            store16_at2(y + (size_t)m * N + n, o.u);
         }
     }
 }
 
-// ---- h = x / sqrt(mean(x^2) + eps) * gamma, one workgroup per row ------------------------------
+// ---- h = x / sqrt(mean(x^2) + eps) * gamma, one workgroup per row; x and gamma may lie anywhere ----
 __global__ __launch_bounds__(256) void fp_rmsnorm_kernel(const f16 *__restrict__ x, int d,
                                                           const float *__restrict__ gamma, float eps,
                                                           f16 *__restrict__ h)
 {
     __shared__ float part[4];
-    const uint4 *row = reinterpret_cast<const uint4 *>(x + (size_t)blockIdx.x * d);
+    const f16 *row = x + (size_t)blockIdx.x * d;
     uint4 *out = reinterpret_cast<uint4 *>(h + (size_t)blockIdx.x * d);
     float s = 0.0f;
     for (int c = threadIdx.x; c < d >> 3; c += 256) {
         Pack16 v;
-        v.u = row[c];
+        v.u = load16_at2(row + 8 * c);
 #pragma unroll
         for (int e = 0; e < 8; ++e) s += (float)v.h[e] * (float)v.h[e];
     }
@@ -142,11 +143,11 @@ __global__ __launch_bounds__(256) void fp_rmsnorm_kernel(const f16 *__restrict__
     const float inv = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)d + eps);
     for (int c = threadIdx.x; c < d >> 3; c += 256) {
         Pack16 v;
-        v.u = row[c];
-        const float4 g0 = *reinterpret_cast<const float4 *>(gamma + 8 * c), g1 = *reinterpret_cast<const float4 *>(gamma + 8 * c + 4);
-        const float gm[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        v.u = load16_at2(row + 8 * c);
+        const f32x4_at4 *gm = reinterpret_cast<const f32x4_at4 *>(gamma + 8 * c);
+        const f32x4 g[2] = {gm[0], gm[1]};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v.h[e] = (f16)((float)v.h[e] * inv * gm[e]);
+        for (int e = 0; e < 8; ++e) v.h[e] = (f16)((float)v.h[e] * inv * g[e >> 2][e & 3]);
         out[c] = v.u;
     }
 }

@@ -80,6 +80,27 @@ def test_fp_block_against_oracle(qb, d, H, Hkv, dh, F, B, N):
     assert abs(np.linalg.norm(got) / np.linalg.norm(want) - 1.0) < 1e-3
 
 
+@pytest.mark.parametrize("off", [1, 4, 7])
+def test_fp_block_takes_tensors_at_any_address(qb, off):
+    """x, x_out and the gammas that start `off` elements behind an aligned address (2-byte, 8-byte and odd offsets
+    of a row): the bits of the aligned call, and nothing written beside x_out."""
+    from paper_2604_17320_amd.model import FullPrecisionLayer
+    d, H, Hkv, dh, F, B, N = CASES[1]
+    _, _, _, Lf, _, _ = build_pair(d, H, Hkv, dh, F, 2 * N + 8, seed=d + N)
+    x, pos = inputs(B, N, d, seed=N)
+    want = host(Lf.forward(dev(x), dev(pos), B, N))
+    shifted = lambda t: torch.cat([t.new_zeros(off), t.flatten(), t.new_zeros(16)])[off: off + t.numel()]
+    moved = FullPrecisionLayer(H, dh, F, *Lf.w, shifted(Lf.gamma1), shifted(Lf.gamma2), 1e-5, Lf.cosT, Lf.sinT, Hkv)
+    xs = shifted(dev(x)).view(B * N, d)
+    room = torch.full((off + x.size + 16,), 7.0, dtype=torch.float16, device="cuda")
+    out = room[off: off + x.size].view(B * N, d)
+    assert xs.data_ptr() % 16 == out.data_ptr() % 16 == 2 * off % 16
+    ws = torch.empty(qb.quota_fp_block_workspace_bytes(moved.desc, B, N), dtype=torch.uint8, device="cuda")
+    qb.quota_fp_block(moved.desc, xs, dev(pos), B, N, out, ws)
+    assert np.array_equal(host(out).view(np.uint16), want.view(np.uint16))
+    assert bool((room[:off] == 7.0).all()) and bool((room[off + x.size:] == 7.0).all())
+
+
 def test_activation_deviation_against_oracle(qb):
     r = np.random.default_rng(5)
     B, n = 5, 3 * 1000 + 7                       # not a multiple of the workgroup size
