@@ -201,7 +201,8 @@ size_t quota_attention_workspace_bytes(int B, int N, int H, int dh);
  * [vis_begin, vis_begin+Nv): cm_inter[b][i] = mean over heads of the total
  * probability that text queries put on key i, cm_intra the same for visual
  * queries (fp32 [B][Nv]); pass both null to skip the cue pass.
- * ws: quota_attention_workspace_bytes bytes.  Requires dh == 64 or 128. */
+ * ws: quota_attention_workspace_bytes bytes, at any multiple of 4.  Requires
+ * dh == 64 or 128. */
 int quota_attention_prefill(const void *q_f16, const void *khat_f16,
                             const void *vhat_f16, int B, int N, int H, int dh,
                             int vis_begin, int Nv, void *o_f16,

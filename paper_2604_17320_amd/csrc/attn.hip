@@ -353,11 +353,26 @@ __global__ __launch_bounds__(256) void colmass_reduce_kernel(
 
 }  // namespace
 
+// The scratch of an attention call, at any 4-byte address: row log-sum-exp [B][H][N], per-head column masses
+// [B][H][N] as pairs (8-byte aligned: they are stored and, by the last workgroup of a key block, loaded whole), counters
+// of the key blocks.
+namespace {
+struct AttnWs {
+    float *lse2;
+    float2 *partial;
+    int *counters;
+    AttnWs(void *ws, size_t rows) : lse2((float *)ws)
+    {
+        partial = reinterpret_cast<float2 *>((reinterpret_cast<uintptr_t>(lse2 + rows) + 7) & ~(uintptr_t)7);
+        counters = reinterpret_cast<int *>(partial + rows);
+    }
+};
+}  // namespace
+
 extern "C" size_t quota_attention_workspace_bytes(int B, int N, int H, int dh)
 {
     (void)dh;
     if (B <= 0 || N <= 0 || H <= 0) return 0;
-    // row log-sum-exp [B][H][N] + per-head column masses [B][H][N][2] + counters of the key blocks
     return (size_t)B * H * N * sizeof(float) * 3 + (size_t)B * ((N + 127) / 128) * sizeof(int) + 8;
 }
 
@@ -372,11 +387,7 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     if ((dh != 64 && dh != 128) || H % Hkv != 0) return QUOTA_ERR_SHAPE;
     if (partial_out) *partial_out = nullptr;
     if (N == 0) return QUOTA_OK;
-    float *lse2 = (float *)ws;
-    size_t rows = (size_t)B * H * N;
-    rows += rows & 1;                        // the masses are pairs
-    float *partial = lse2 + rows;
-    int *counters = (int *)(partial + 2 * (size_t)B * H * N);
+    const AttnWs w(ws, (size_t)B * H * N);
     float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
     const bool cues = Nv > 0 && want_cues;
     const int nk = (Nv + 127) / 128;
@@ -387,7 +398,7 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
         ProfScope prof(QUOTA_K_ATTENTION_FWD, 4.0 * B * dd * ((double)N * (N + 1) / 2),
                        4.0 * dM * dd + 4.0 * dM * Hkv * dh, st);
         auto kernel = dh == 128 ? attn_fwd_kernel<128> : attn_fwd_kernel<64>;
-        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, lse2, scale_log2, counters,
+        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, w.counters,
                                    cues && cm_inter ? B * nk : 0);
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -397,10 +408,10 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
         auto kernel = dh == 128 ? colmass_kernel<128> : colmass_kernel<64>;
-        kernel<<<g2, blk, 0, st>>>(q, k, lse2, N, H, Hkv, vis_begin, Nv, (float2 *)partial, scale_log2, cm_inter,
-                                   cm_intra, counters);
+        kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, cm_inter, cm_intra,
+                                   w.counters);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
-        if (partial_out) *partial_out = partial;
+        if (partial_out) *partial_out = reinterpret_cast<const float *>(w.partial);
     }
     return QUOTA_OK;
 }
@@ -429,8 +440,10 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
 // array's name as an address: each device's copy is looked up once with hipGetSymbolAddress, with
 // that device current, and the kernels receive the looked-up pointer like any other buffer.
 // Every element the cue pass and the head mean read has been written earlier in the same call,
-// so nothing needs clearing between calls.
-static __device__ __align__(256) float attn_scratch[4 * QUOTA_ATTENTION_STATIC_MAX_ROWS + 2];
+// so nothing needs clearing between calls.  That call takes no head means in the cue pass, so it has no
+// counters: 12 bytes a row, and an odd row count, which costs 4 more, is below the limit.
+static_assert(QUOTA_ATTENTION_STATIC_MAX_ROWS % 2 == 0, "");
+static __device__ __align__(256) float attn_scratch[3 * QUOTA_ATTENTION_STATIC_MAX_ROWS];
 
 namespace {
 constexpr int kMaxDevices = 64;

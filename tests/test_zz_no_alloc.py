@@ -64,3 +64,40 @@ def test_static_scratch_attention_rejects_oversize():
     with pytest.raises(qb.QuotaError) as e:          # 4 * 64 * 1025 rows > 262144: rejected on the host
         qb.quota_attention_prefill_static(t, t, t, 4, 1025, 64, 64, 128, 0, 8, t, f, f)
     assert e.value.code == qb.ERR_CAPACITY
+
+
+def test_static_scratch_at_its_row_limit():
+    """B*H*N equal to the limit, and one odd row count: the shared array's last elements are in use."""
+    from paper_2604_17320_amd import binding as qb
+    for B, N, H, dh, vb, Nv in [(1, 4096, 64, 64, 30, 4000), (1, 4095, 63, 64, 0, 4095)]:
+        print(f"static-scratch attention of {B * N * H} rows", flush=True)
+        g = torch.Generator(device="cuda").manual_seed(N)
+        q, k, v = (torch.randn((B * N, H * dh), generator=g, device="cuda").to(torch.float16) for _ in range(3))
+        outs = []
+        for static in (False, True):
+            o = torch.zeros((B * N, H * dh), dtype=torch.float16, device="cuda")
+            ci, cv = (torch.zeros((B, Nv), dtype=torch.float32, device="cuda") for _ in range(2))
+            if static:
+                qb.quota_attention_prefill_static(q, k, v, B, N, H, H, dh, vb, Nv, o, ci, cv)
+            else:
+                ws = torch.empty(qb.quota_attention_workspace_bytes(B, N, H, dh), dtype=torch.uint8, device="cuda")
+                qb.quota_attention_prefill(q, k, v, B, N, H, dh, vb, Nv, o, ci, cv, ws)
+            outs.append((o.view(torch.int16), ci.view(torch.int32), cv.view(torch.int32)))
+        assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+def test_attention_workspace_at_any_word():
+    """An odd number of rows in a workspace that starts 4 bytes behind a multiple of 8: same bits, and not a byte
+    touched outside the stated size."""
+    from paper_2604_17320_amd import binding as qb
+    B, N, H, Hkv, dh, vb, Nv = 1, 141, 3, 1, 64, 5, 131
+    q, khat, vhat = (torch.from_numpy(a).cuda() for a in _inputs(B, N, H, Hkv, dh, 77))
+    nbytes, outs = qb.quota_attention_workspace_bytes(B, N, H, dh), []
+    for off in (0, 4, 8, 12):
+        room = torch.full((off + nbytes + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        o = torch.zeros((B * N, H * dh), dtype=torch.float16, device="cuda")
+        ci, cv = (torch.zeros((B, Nv), dtype=torch.float32, device="cuda") for _ in range(2))
+        qb.quota_attention_prefill_gqa(q, khat, vhat, B, N, H, Hkv, dh, vb, Nv, o, ci, cv, room[off: off + nbytes])
+        assert bool((room[:off] == 0xA5).all()) and bool((room[off + nbytes:] == 0xA5).all())
+        outs.append((o.view(torch.int16), ci.view(torch.int32), cv.view(torch.int32)))
+    assert all(torch.equal(a, b) for other in outs[1:] for a, b in zip(outs[0], other))
