@@ -11,7 +11,8 @@
 //
 // Pass 2 owns key columns instead: S = Q K^T puts the key on the lane, so the
 // column sums over queries are in-lane adds in a fixed order (deterministic,
-// no atomics).  It needs the final log-sum-exp of every query row from pass 1.
+// no atomics).  It needs the final log-sum-exp of every query row from pass 1.  A third, small pass takes
+// the means over the heads.
 //
 // Both are bound by the matrix cores, the exponentials and LDS about equally (a wave's 64-key tile: 32 matrix
 // instructions = 1024 cycles, 32 exponentials and 100 other vector instructions = 900), so they run two
@@ -64,16 +65,12 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 template <int DH>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
-    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int *__restrict__ counters,
-    int n_counters)
+    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2)
 {
     constexpr int T = DH / 16;       // k-steps (16 channels each) of the QK product
     constexpr int DB = DH / 32;      // 32-channel blocks of the output
     constexpr int TB = KT * DH * 2;  // bytes of a tile
     __shared__ __align__(16) char sm[2][2][TB];         // [buffer][K, V]
-    // the cue pass counts its workgroups
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0;
     // XCD-aware order: a head's workgroups, longest first, run on one XCD, whose L2 holds its K and V
     const int nq = (N + 127) / 128, work = xcd_remap(blockIdx.x, gridDim.x), bh = work / nq;
     const int b = bh / H, h = bh % H, q0 = (nq - 1 - work % nq) * 128;
@@ -197,19 +194,15 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     }
 }
 
-// One workgroup per 128 visual keys of a (sequence, head); wave w owns the 32 keys kb .. kb+31.  cm_inter (optional,
-// with cm_intra): the workgroup that is the last of its key block to finish, over the heads, also takes the
-// head means (counters: one per key block and sequence, zero on entry).  No workgroup waits for another.
+// One workgroup per 128 visual keys of a (sequence, head); wave w owns the 32 keys kb .. kb+31.
 template <int DH>
 __global__ __launch_bounds__(256, 3) void colmass_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
-    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, float *__restrict__ cm_inter,
-    float *__restrict__ cm_intra, int *__restrict__ counters)
+    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2)
 {
     constexpr int T = DH / 16, TB = KT * DH * 2;
     __shared__ __align__(16) char sm_q[2][TB];
     __shared__ __align__(16) float sm_lse[2][KT];
-    __shared__ int sm_last;
     // XCD-aware order, as in pass 1; the first keys have the most queries
     const int nk = (Nv + 127) / 128, work = xcd_remap(blockIdx.x, gridDim.x), bh = work / nk, kb = work % nk;
     const int d = H * DH;
@@ -285,86 +278,52 @@ __global__ __launch_bounds__(256, 3) void colmass_kernel(
     }
     acc_txt += __shfl_xor(acc_txt, 32, 64);
     acc_vis += __shfl_xor(acc_vis, 32, 64);
-    const bool store = key_ok && hl == 0;
-    float2 *mine = partial + ((size_t)b * H + h) * Nv + (key - vis_begin);
-    if (!cm_inter) {
-        if (store) *mine = make_float2(acc_txt, acc_vis);
-        return;
-    }
-    // head means: the masses pass through memory (device-scope stores and loads), the counter says who is last
-    if (store)
-        __hip_atomic_store(reinterpret_cast<unsigned long long *>(mine),
-                           (unsigned long long)__float_as_uint(acc_vis) << 32 | __float_as_uint(acc_txt),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    drain();                                 // the stores have reached memory
-    __syncthreads();
-    if (tid == 0)
-        sm_last = __hip_atomic_fetch_add(counters + b * nk + kb, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == H - 1;
-    __syncthreads();
-    if (!sm_last) return;
-    // lane quarter hq sums heads [hq*H/4 .. ) in head order, the four partial sums are combined as
-    // (s0 + s1) + (s2 + s3), then * (1/H)
-    const int hq = tid & 3, hper = (H + 3) / 4, h_lo = hq * hper, h_hi = min(h_lo + hper, H);
-    const float invH = 1.0f / (float)H;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int i = kb * 128 + k * 64 + (tid >> 2);
-        const unsigned long long *pp = reinterpret_cast<const unsigned long long *>(partial) + (size_t)b * H * Nv + min(i, Nv - 1);
-        float st = 0.0f, sv = 0.0f;
-        for (int h0 = h_lo; h0 < h_hi; h0 += 8) {
-            unsigned long long v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                v[u] = __hip_atomic_load(pp + (size_t)min(h0 + u, h_hi - 1) * Nv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (h0 + u < h_hi) {
-                    st += __uint_as_float((uint32_t)v[u]);
-                    sv += __uint_as_float((uint32_t)(v[u] >> 32));
-                }
-        }
-        st += __shfl_xor(st, 1, 64); sv += __shfl_xor(sv, 1, 64);
-        st += __shfl_xor(st, 2, 64); sv += __shfl_xor(sv, 2, 64);
-        if (i < Nv && hq == 0) {
-            cm_inter[(size_t)b * Nv + i] = st * invH;
-            cm_intra[(size_t)b * Nv + i] = sv * invH;
-        }
-    }
+    if (key_ok && hl == 0) partial[((size_t)b * H + h) * Nv + (key - vis_begin)] = make_float2(acc_txt, acc_vis);
 }
 
-// head mean in head order: cm[b][i] = (1/H) * sum_h partial[b][h][i]
+// Head means of the masses, [B][H][Nv] -> [B][Nv]: 64 keys of a sequence per workgroup, a quad of lanes per key.  Lane hq sums
+// heads [hq H/4 .. ) in head order, the four sums are combined as (s0 + s1) + (s2 + s3), then * (1/H).  A launch of its own:
+// left to the last workgroup of a key block in the pass above, behind a count that releases and acquires, it
+// costs more (forward, cues and means: 16 x 704 tokens, 32 heads 262 us against 196; 1 x 640 34.8 against 34.2), since
+// every release writes back the L2 of its XCD.
 __global__ __launch_bounds__(256) void colmass_reduce_kernel(
-    const float *__restrict__ partial, int B, int H, int Nv, float *__restrict__ cm_inter,
-    float *__restrict__ cm_intra)
+    const float2 *__restrict__ partial, int H, int Nv, float *__restrict__ cm_inter, float *__restrict__ cm_intra)
 {
-    int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= B * Nv) return;
-    int b = t / Nv, i = t % Nv;
+    const int n64 = (Nv + 63) / 64, b = blockIdx.x / n64, i = blockIdx.x % n64 * 64 + (threadIdx.x >> 2), hq = threadIdx.x & 3;
+    const int hper = (H + 3) / 4, h_lo = hq * hper, h_hi = min(h_lo + hper, H);
+    const float invH = 1.0f / (float)H;
+    const float2 *pp = partial + (size_t)b * H * Nv + min(i, Nv - 1);
     float st = 0.0f, sv = 0.0f;
-    for (int h = 0; h < H; ++h) {
-        size_t idx = (((size_t)b * H + h) * Nv + i) * 2;
-        st += partial[idx];
-        sv += partial[idx + 1];
+    for (int h0 = h_lo; h0 < h_hi; h0 += 8) {
+        float2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = pp[(size_t)min(h0 + u, h_hi - 1) * Nv];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (h0 + u < h_hi) {
+                st += v[u].x;
+                sv += v[u].y;
+            }
     }
-    float invH = 1.0f / (float)H;
-    if (cm_inter) cm_inter[t] = st * invH;
-    if (cm_intra) cm_intra[t] = sv * invH;
+    st += __shfl_xor(st, 1, 64); sv += __shfl_xor(sv, 1, 64);
+    st += __shfl_xor(st, 2, 64); sv += __shfl_xor(sv, 2, 64);
+    if (i < Nv && hq == 0) {
+        if (cm_inter) cm_inter[(size_t)b * Nv + i] = st * invH;
+        if (cm_intra) cm_intra[(size_t)b * Nv + i] = sv * invH;
+    }
 }
 
 }  // namespace
 
 // The scratch of an attention call, at any 4-byte address: row log-sum-exp [B][H][N], per-head column masses
-// [B][H][N] as pairs (8-byte aligned: they are stored and, by the last workgroup of a key block, loaded whole), counters
-// of the key blocks.
+// [B][H][Nv] as pairs (8-byte aligned: they are stored and loaded whole).
 namespace {
 struct AttnWs {
     float *lse2;
     float2 *partial;
-    int *counters;
     AttnWs(void *ws, size_t rows) : lse2((float *)ws)
     {
         partial = reinterpret_cast<float2 *>((reinterpret_cast<uintptr_t>(lse2 + rows) + 7) & ~(uintptr_t)7);
-        counters = reinterpret_cast<int *>(partial + rows);
     }
 };
 }  // namespace
@@ -373,24 +332,21 @@ extern "C" size_t quota_attention_workspace_bytes(int B, int N, int H, int dh)
 {
     (void)dh;
     if (B <= 0 || N <= 0 || H <= 0) return 0;
-    return (size_t)B * H * N * sizeof(float) * 3 + (size_t)B * ((N + 127) / 128) * sizeof(int) + 8;
+    return (size_t)B * H * N * sizeof(float) * 3 + 8;
 }
 
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             bool want_cues, void *ws, const float **partial_out, float *cm_inter, float *cm_intra,
-                             hipStream_t st)
+                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st)
 {
     if (!q_f16 || !khat_f16 || !vhat_f16 || !o_f16 || !ws) return QUOTA_ERR_NULL;
     if (B <= 0 || N < 0 || H <= 0 || Hkv <= 0 || vis_begin < 0 || Nv < 0 || vis_begin + Nv > N)
         return QUOTA_ERR_INVALID_ARG;
     if ((dh != 64 && dh != 128) || H % Hkv != 0) return QUOTA_ERR_SHAPE;
-    if (partial_out) *partial_out = nullptr;
     if (N == 0) return QUOTA_OK;
     const AttnWs w(ws, (size_t)B * H * N);
     float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
-    const bool cues = Nv > 0 && want_cues;
-    const int nk = (Nv + 127) / 128;
+    const bool cues = Nv > 0 && (cm_inter || cm_intra);
     dim3 g1((unsigned)((N + 127) / 128) * H * B), blk(256);
     const f16 *q = (const f16 *)q_f16, *k = (const f16 *)khat_f16, *v = (const f16 *)vhat_f16;
     const double dM = (double)B * N, dd = (double)H * dh;
@@ -398,20 +354,19 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
         ProfScope prof(QUOTA_K_ATTENTION_FWD, 4.0 * B * dd * ((double)N * (N + 1) / 2),
                        4.0 * dM * dd + 4.0 * dM * Hkv * dh, st);
         auto kernel = dh == 128 ? attn_fwd_kernel<128> : attn_fwd_kernel<64>;
-        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, w.counters,
-                                   cues && cm_inter ? B * nk : 0);
+        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2);
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if (cues) {
-        dim3 g2((unsigned)nk * H * B);
+        dim3 g2((unsigned)((Nv + 127) / 128) * H * B);
         // (query, visual key) pairs under the causal mask
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
         auto kernel = dh == 128 ? colmass_kernel<128> : colmass_kernel<64>;
-        kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, cm_inter, cm_intra,
-                                   w.counters);
+        kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
-        if (partial_out) *partial_out = reinterpret_cast<const float *>(w.partial);
+        colmass_reduce_kernel<<<dim3((unsigned)((Nv + 63) / 64) * B), blk, 0, st>>>(w.partial, H, Nv, cm_inter, cm_intra);
+        QUOTA_RETURN_IF_LAUNCH_FAILED();
     }
     return QUOTA_OK;
 }
@@ -421,17 +376,8 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
                                            int vis_begin, int Nv, void *o_f16, float *cm_inter,
                                            float *cm_intra, void *ws, void *stream)
 {
-    hipStream_t st = (hipStream_t)stream;
-    const float *partial = nullptr;
-    int rc = quota_internal_attention(q_f16, khat_f16, vhat_f16, B, N, H, Hkv, dh, vis_begin, Nv, o_f16,
-                                      cm_inter || cm_intra, ws, &partial, nullptr, nullptr, st);
-    if (rc != QUOTA_OK) return rc;
-    if (partial) {
-        colmass_reduce_kernel<<<dim3((B * Nv + 255) / 256), dim3(256), 0, st>>>(partial, B, H, Nv,
-                                                                                cm_inter, cm_intra);
-        QUOTA_RETURN_IF_LAUNCH_FAILED();
-    }
-    return QUOTA_OK;
+    return quota_internal_attention(q_f16, khat_f16, vhat_f16, B, N, H, Hkv, dh, vis_begin, Nv, o_f16, cm_inter, cm_intra,
+                                    ws, (hipStream_t)stream);
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------
@@ -440,8 +386,8 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
 // array's name as an address: each device's copy is looked up once with hipGetSymbolAddress, with
 // that device current, and the kernels receive the looked-up pointer like any other buffer.
 // Every element the cue pass and the head mean read has been written earlier in the same call,
-// so nothing needs clearing between calls.  That call takes no head means in the cue pass, so it has no
-// counters: 12 bytes a row, and an odd row count, which costs 4 more, is below the limit.
+// so nothing needs clearing between calls.  12 bytes a row; an odd row count, which costs 4 more, is
+// below the limit.
 static_assert(QUOTA_ATTENTION_STATIC_MAX_ROWS % 2 == 0, "");
 static __device__ __align__(256) float attn_scratch[3 * QUOTA_ATTENTION_STATIC_MAX_ROWS];
 

@@ -16,12 +16,10 @@ int quota_internal_score_topk(const float *sumsq, const float *ressq, long strid
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
                               hipStream_t st);
 
-// attention + per-head column masses (partial_out, optional: [B][H][Nv][2] in the workspace) and, if cm_inter and
-// cm_intra are given, their head means [B][Nv]
+// attention and, if cm_inter or cm_intra is given, the cue pass with its head means [B][Nv]
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             bool want_cues, void *ws, const float **partial_out, float *cm_inter, float *cm_intra,
-                             hipStream_t st);
+                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st);
 
 struct quota_compact_args {
     int B, N, vis_begin, Nv, k_keep, n_keep, d, dkv;      // dkv: width of a K or V row (Hkv * dh)

@@ -212,8 +212,8 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     TRY(qkv_rope_kv_quant(L, w, M, s->pos, t->qkv != nullptr, st));
     TRY(dump(t->qkv, w.qkv, (size_t)M * (d + 2 * dkv) * 2, st));
     TRY(dump(t->q_rot, w.q_rot, (size_t)M * d * 2, st));
-    TRY(quota_internal_attention(w.q_rot, w.khat, w.vhat, B, N, H, Hkv, dh, vb, Nv, w.o, score, w.attn_ws,
-                                 nullptr, w.cm_inter, w.cm_intra, st));
+    TRY(quota_internal_attention(w.q_rot, w.khat, w.vhat, B, N, H, Hkv, dh, vb, Nv, w.o,
+                                 score ? w.cm_inter : nullptr, score ? w.cm_intra : nullptr, w.attn_ws, st));
     TRY(dump(t->o, w.o, (size_t)M * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
     const bool inject_cm = t->inject_cm_inter && t->inject_cm_intra;
