@@ -5,14 +5,15 @@
 // 16 (4) bytes per lane from global memory to LDS, lane l at lds + 16 l (4 l), without passing registers.
 // In assembly because the compiler, which cannot tell the LDS buffers apart, would make every LDS read
 // wait for the copies just started; the kernel waits for them itself (drain) before the barrier that
-// hands the buffer over.
+// hands the buffer over.  The LDS base goes into m0 as an operand, so that the compiler knows m0 taken; the
+// chip wants one wait state between that write and the copy.
 __device__ __forceinline__ void copy16_to_lds(const void *base, unsigned off, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(off), "s"(base) : "memory");
 }
 __device__ __forceinline__ void copy4_to_lds(const void *base, unsigned off, unsigned lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, %2" ::"{m0}"(lds), "v"(off), "s"(base) : "memory");
 }
 // All of this wave's loads and copies have arrived.  In assembly, because the compiler drops a wait that
 // it thinks has nothing to wait for; the builtin as well, so that it knows its own loads have arrived.
