@@ -328,7 +328,11 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     }
 }
 
-template <int NB, int U, int GRID, int MODE, int NC>
+// PER_CU: workgroups wanted per CU.  A launch asks for no more than the LDS has room for: what is left over would run in a
+// second round and quantize the rows once more.  <2, 2> takes 68.8 KB and 128 G + 16 bytes a row: two fit up to 13120
+// bytes of rows, one beyond (4 rows of 4096, through RMSNorm, captured: 12288 columns 16.7 us in 384 workgroups,
+// 11.9 in 256; 22016 columns 20.0 in 512, 16.1 in 256; 3 x 5120, 27648 columns 27.6 -> 22.8).
+template <int NB, int U, int PER_CU, int MODE, int NC>
 int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
                   int code_stride, hipStream_t st)
 {
@@ -339,7 +343,8 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + 2.0 * Md * Nd * (res ? 2 : 1), st);
-    w4a4_rows16_kernel<NB, U, MODE, NC><<<dim3(min(W->N / (16 * NB), GRID)), dim3(RT_THREADS), lds, st>>>(
+    const int per_cu = min(PER_CU, (int)(160 * 1024 / lds));
+    w4a4_rows16_kernel<NB, U, MODE, NC><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
         in, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr, code_stride);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
@@ -348,7 +353,8 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 // 16 columns per workgroup up to 4096 columns (256 workgroups: one per CU), with two groups per wave in flight, four
 // over long rows, which stream longer than they start up; 32 beyond, two groups up to 8192 columns (at
 // most one workgroup per CU again), else three workgroups per CU with one group per wave, or, with a quantizer in
-// front, two per CU with two, so that fewer repeat its work.  Workgroups walk over the columns.
+// front, two per CU (one, where the rows leave no room for two) with two, so that fewer repeat its work.
+// Workgroups walk over the columns.
 // Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
 // <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
 template <int MODE, int NC>
@@ -357,12 +363,12 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
 {
     if (W->N <= 4096) {
         if constexpr (MODE <= ROWS_FRAG)
-            if (W->K > 8192) return launch_rows16<1, 4, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
-        return launch_rows16<1, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+            if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        return launch_rows16<1, 2, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }
     if constexpr (MODE <= ROWS_FRAG)
-        if (W->N > 8192) return launch_rows16<2, 1, 768, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
-    return launch_rows16<2, 2, 512, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    return launch_rows16<2, 2, 2, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
 }
 
 template <int MODE>
