@@ -40,10 +40,9 @@ namespace {
 //   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
 //   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
 //   32-row tiles have no time to spare and lose by it).
-//   PIPE: weights of group g+1 are unpacked between the MFMAs of group g (twice the fragment registers).
 // LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that the 8 lanes of one LDS
 // cycle (8 rows, same piece) cover all banks.
-template <int RT, int CT, int NW, int CH, int SP, bool PIPE, bool PACKED, bool ACC_OUT, bool QKV, int OCC>
+template <int RT, int CT, int NW, int CH, int SP, bool PACKED, bool ACC_OUT, bool QKV, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
@@ -96,7 +95,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         os[k] = 4u * (unsigned)min((n0 >> 1) + d % (BN / 2), (N >> 1) - 1);
     }
 
-    constexpr int WS = CH > 1 || PIPE ? 2 : 1;           // register sets of packed weights
+    constexpr int WS = CH > 1 ? 2 : 1;                   // register sets of packed weights = stages per loop body
     uint4 rw[WS][CH][CT];
     i32x4 ra[CH][LA];                                    // PACKED staging (struct uint4 here would live in scratch memory)
     // What a stage needs, load by load: for each of its groups CT weight pieces and LA activation pieces, then
@@ -203,28 +202,22 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     store_packed(0);
     __syncthreads();
 
-    i32x8 fb[PIPE ? 2 : 1][CT];
-    if (PIPE)
-#pragma unroll
-        for (int j = 0; j < CT; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[0][j]);
-    constexpr int SU = PIPE && CH % 2 ? 2 : WS;          // stages per loop body (parities are compile-time)
+    i32x8 fb[CT];
     const int stages = (G + CH - 1) / CH;
     i32x8 fa[2];
 #pragma unroll 1
-    for (int st0 = 0; st0 < stages; st0 += SU) {
+    for (int st0 = 0; st0 < stages; st0 += WS) {
 #pragma unroll
-        for (int su = 0; su < SU; ++su) {
-            const int g0 = (st0 + su) * CH, half = SU == 2 ? su : st0 & 1, set = su % WS;
-            if (SU == 2 && su && g0 >= G) break;
+        for (int su = 0; su < WS; ++su) {
+            const int g0 = (st0 + su) * CH, half = WS == 2 ? su : st0 & 1, set = su;
+            if (su && g0 >= G) break;
             const uint4 *sp = lds_raw + half * STG;
             read_a(sp, 0, fa[0]);
-            if (!PIPE && CH == 1) {
+            if (CH == 1) {
 #pragma unroll
                 for (int j = 0; j < CT; ++j)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[0][j]);
+                    for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[j]);
             }
             gstage = g0 + CH;
 #pragma unroll
@@ -233,21 +226,20 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             for (int c = 0; c < CH; ++c) {
                 if (c && g0 + c >= G) break;             // uniform: the last stage may hold fewer groups
                 const uint4 *gp = sp + c * AST;
-                const int cur = PIPE ? (su * CH + c) & 1 : 0;
                 float sc[CT];
 #pragma unroll
                 for (int j = 0; j < CT; ++j) sc[j] = read_scale(sp, c, j);
-                if (!PIPE && CH > 1) {
+                if (CH > 1) {
 #pragma unroll
                     for (int j = 0; j < CT; ++j)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) unpack_w(rw[set][c][j], i, fb[0][j]);
+                        for (int i = 0; i < 4; ++i) unpack_w(rw[set][c][j], i, fb[j]);
                 }
                 // The issue order is pinned result by result (left alone the scheduler puts the scale chain
                 // of a result right behind its own MFMA and waits out the matrix core's latency, and reads
                 // every row block's fragments up front, which does not fit the registers): one MFMA, the
-                // chain of the result LAG places back, a share of the next group's unpacking (PIPE).  The
-                // next row block's fragments are read at the start of a row block.
+                // chain of the result LAG places back.  The next row block's fragments are read at the start of
+                // a row block.
                 f32x4 k4[2];
                 k4[0] = start_of(fa[0]);
 #pragma unroll
@@ -258,7 +250,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                     for (int j = 0; j < CT; ++j) {
                         __builtin_amdgcn_sched_barrier(0);
                         const int t = i * CT + j;
-                        const f32x4 a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 1], fb[cur][j], k4[i & 1], 0, 0, 0, 0, 0, 0);
+                        const f32x4 a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 1], fb[j], k4[i & 1], 0, 0, 0, 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
                         if (t < LAG) scale_in(T - LAG + t, pend[t], pscale[t]);
                         else scale_in(t - LAG, pend[t % LAG], sc[(t - LAG) % CT]);
@@ -267,11 +259,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #pragma unroll
                         for (int k = 0; k < (SP ? LOADS : 0); ++k)
                             if (k * (CH * T * SP / 8) / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1);
-                        if (PIPE && c + 1 < CH) {
-#pragma unroll
-                            for (int u = t * 4 * CT / T; u < (t + 1) * 4 * CT / T; ++u)
-                                unpack_w(rw[set][c + 1][u / 4], u % 4, fb[cur ^ 1][u / 4]);
-                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -281,11 +268,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             drain();
             store_packed(half ^ 1);
             __syncthreads();
-            if (PIPE)
-#pragma unroll
-                for (int j = 0; j < CT; ++j)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) unpack_w(rw[(set + 1) % WS][0][j], i, fb[((su + 1) * CH) & 1][j]);
         }
     }
 #pragma unroll
@@ -415,12 +397,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 }
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
-//                                            RT CT NW CH SP PIPE          OCC
-#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, false, P, A, QK, 2>  // 64 x 256
-#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, false, P, A, QK, 2>  // 64 x 128
-#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, false, P, A, QK, 2>  // 32 x 128
-#define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, false, P, A, QK, 2>  // 32 x 64
-#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, false, P, A, QK, 2>  // 128 x 256
+//                                            RT CT NW CH SP          OCC
+#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>  // 64 x 256
+#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, P, A, QK, 2>  // 64 x 128
+#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, QK, 2>  // 32 x 128
+#define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
+#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128, QUOTA_K_GEMM_64X128},

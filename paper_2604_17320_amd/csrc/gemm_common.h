@@ -1,17 +1,7 @@
-// Pieces shared by the W4A4 GEMM kernels: the int4 -> int8 unpack and the XCD-aware tile order.
+// Pieces shared by the GEMM and attention kernels: int4 codes as e4m3 bytes, and the XCD-aware tile order.
 #pragma once
 #include "common.h"
 
-// A nibble placed in the HIGH half of a byte is the int8 value 16*code (two's complement carries
-// the sign), so "(w << 4) & 0xF0F0F0F0" and "w & 0xF0F0F0F0" turn one packed dword into two dwords
-// of int8 without any sign-extension arithmetic: lo holds the even elements, hi the odd ones.
-__device__ __forceinline__ void unpack16(const uint4 &v, uint4 &lo, uint4 &hi)
-{
-    lo.x = (v.x << 4) & 0xF0F0F0F0u; hi.x = v.x & 0xF0F0F0F0u;
-    lo.y = (v.y << 4) & 0xF0F0F0F0u; hi.y = v.y & 0xF0F0F0F0u;
-    lo.z = (v.z << 4) & 0xF0F0F0F0u; hi.z = v.z & 0xF0F0F0F0u;
-    lo.w = (v.w << 4) & 0xF0F0F0F0u; hi.w = v.w & 0xF0F0F0F0u;
-}
 // 32 packed int4 codes (one 16-byte piece) as signed e4m3 bytes in the A8 order -- every 8 codes as evens
 // then odds.  With u = code & 15 and b its sign bit the e4m3 byte is u for b = 0 and
 // 0x90 - u = (u ^ 15) + 0x81 for b = 1, IN UNITS OF 1/512 (the linear range of e4m3), so that no
@@ -32,10 +22,6 @@ __device__ __forceinline__ void codes_to_e4m3(const uint4 &v, uint4 &e0, uint4 &
     }
     e0 = make_uint4(e[0], e[1], e[2], e[3]);
     e1 = make_uint4(e[4], e[5], e[6], e[7]);
-}
-__device__ __forceinline__ i32x4 as_i32x4(const uint4 &t)
-{
-    return i32x4{(int)t.x, (int)t.y, (int)t.z, (int)t.w};
 }
 
 // XCD-aware tile id: consecutive dispatch ids go round-robin over the 8 XCDs
