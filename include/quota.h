@@ -53,7 +53,9 @@ int quota_version(void);
  * int4 codes in the library's GEMM layout ([K/128 groups][N rows][64 bytes],
  * K zero-padded to a multiple of 128), `scales` the fp16 group scales in
  * [group][N] order.  Both buffers are caller-allocated device memory of
- * quota_weights_packed_bytes / quota_weights_scale_bytes bytes. */
+ * quota_weights_packed_bytes / quota_weights_scale_bytes bytes; scales may
+ * lie at any address (the GEMM is slow where that is no multiple of 4, and
+ * quota_quantize_pack_weights wants a multiple of 8). */
 typedef struct quota_weights {
     int N;
     int K;
@@ -72,8 +74,10 @@ size_t quota_weights_scale_bytes(int N, int K);
 int quota_quantize_weights(const float *w, int N, int K, int8_t *codes,
                            void *scales_f16, void *stream);
 
-/* The two calls above and below in one pass, for weights whose plain codes nobody keeps: w fp32 [N][K] with
- * W's N and K, 16-byte aligned (QUOTA_ERR_INVALID_ARG otherwise) -> W->packed / W->scales, the same bytes. */
+/* The two calls above and below in one pass, for weights whose plain codes
+ * nobody keeps: w fp32 [N][K] with W's N and K -> W->packed / W->scales, the
+ * same bytes.  w 16-byte and W->scales 8-byte aligned
+ * (QUOTA_ERR_INVALID_ARG otherwise). */
 int quota_quantize_pack_weights(const float *w, const quota_weights *W, void *stream);
 
 /* Repack plain row-major codes (int8, one per byte, values in [-8,7]) and

@@ -26,6 +26,7 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 // For tensors whose caller promises no more than that.
 typedef f16x8 f16x8_at2 __attribute__((aligned(2)));
 typedef f32x4 f32x4_at4 __attribute__((aligned(4)));
+typedef uint32_t u32_at2 __attribute__((aligned(2), may_alias));
 __device__ __forceinline__ uint4 load16_at2(const f16 *p)
 {
     return __builtin_bit_cast(uint4, *reinterpret_cast<const f16x8_at2 *>(p));

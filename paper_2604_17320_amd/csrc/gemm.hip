@@ -486,6 +486,21 @@ extern "C" int quota_set_gemm_variant(int variant)
     return QUOTA_OK;
 }
 
+// The tiles bring two neighbouring columns' scales to LDS as one dword, which has to lie on a dword's address.  Weights
+// whose scales start at an odd halfword go through the few-row kernel 16 rows at a time (its scales pass
+// registers): the same bits, slowly.
+static bool scales_on_dwords(const quota_weights *W) { return (reinterpret_cast<uintptr_t>(W->scales) & 3) == 0; }
+static int gemm_16_rows_at_a_time(const uint8_t *qa, quota_rows16_format format, size_t row_bytes, const float *sa, int M,
+                                  const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, hipStream_t st)
+{
+    for (int m = 0; m < M; m += 16) {
+        const int rc = quota_internal_rows16(qa + m * row_bytes, format, sa + m, M - m < 16 ? M - m : 16, W, y + (size_t)m * ldy,
+                                             ldy, res ? res + (size_t)m * ldr : nullptr, ldr, st);
+        if (rc != QUOTA_OK) return rc;
+    }
+    return QUOTA_OK;
+}
+
 // GEMM on activations in the internal A8 format (M > 16 rows of a layer).
 int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
                                 void *y_f16, int ldy, const void *residual_opt, int ldr, hipStream_t st)
@@ -494,6 +509,9 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
     if (W->N % 64 != 0 || W->K % 32 != 0) return QUOTA_ERR_SHAPE;
     if (M <= 0) return QUOTA_OK;
     if (M <= 16) return quota_internal_rows16(qa8, QUOTA_ROWS16_A8, sa, M, W, y_f16, ldy, residual_opt, ldr, st);
+    if (!scales_on_dwords(W))
+        return gemm_16_rows_at_a_time(qa8, QUOTA_ROWS16_A8, quota_a8_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
+                                      (const f16 *)residual_opt, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
     return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
@@ -513,8 +531,15 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     hipStream_t st = (hipStream_t)stream;
     f16 *y = (f16 *)y_f16;
     const f16 *res = (const f16 *)residual_opt;
-    if (acc_i32_opt)
-        return launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, W, y, ldy, res, ldr, acc_i32_opt, st);
+    const bool dwords = scales_on_dwords(W);
+    if (acc_i32_opt) {
+        quota_weights Wi = *W;
+        if (!dwords) Wi.scales = W->packed;      // (the integer sums need no scales: any readable ones do)
+        const int rc = launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, &Wi, dwords ? y : nullptr, ldy,
+                                 res, ldr, acc_i32_opt, st);
+        if (rc != QUOTA_OK || dwords || !y) return rc;
+    }
+    if (!dwords) return gemm_16_rows_at_a_time(qa, QUOTA_ROWS16_PACKED, W->K / 2, sa, M, W, y, ldy, res, ldr, st);
     if (M <= 16)            // the decode step: stream the weights once
         return quota_internal_rows16(qa, QUOTA_ROWS16_PACKED, sa, M, W, y, ldy, res, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
@@ -534,7 +559,7 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, con
     if (M < 0 || qe->n_pos <= 0) return QUOTA_ERR_INVALID_ARG;
     const int d = qe->d, dkv = qe->dkv;
     if ((qe->dh != 64 && qe->dh != 128) || d <= 0 || d % 128 != 0 || dkv <= 0 || dkv % 128 != 0 ||
-        W->N != d + 2 * dkv || W->K % 32 != 0)
+        W->N != d + 2 * dkv || W->K % 32 != 0 || !scales_on_dwords(W))
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
     const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128);

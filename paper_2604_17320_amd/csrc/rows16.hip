@@ -226,7 +226,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const int d = min(tid + RT_THREADS * k, SD - 1), g = min(r0 + d / (8 * NB), G - 1);
-            rsv[k] = *reinterpret_cast<const uint32_t *>(sw + (size_t)g * N + n0 + 2 * (d % (8 * NB)));
+            rsv[k] = *reinterpret_cast<const u32_at2 *>(sw + (size_t)g * N + n0 + 2 * (d % (8 * NB)));
         }
     };
     const int nblk = N / (16 * NB);

@@ -345,3 +345,25 @@ def test_layer_every_tile_with_fused_qkv_epilogue(qb, tile, pinned_gemm):
     got = run_gpu(qb, L, shape, x, pos, K, dict(o=ref["o"], z=ref["z"], cm_inter=ref["cm_inter"],
                                                 cm_intra=ref["cm_intra"]))
     assert_teacher_forced_exact(ref, got, shape, K)
+
+
+def test_layer_with_weight_scales_at_an_odd_halfword(qb):
+    """Weight scales that start between two dwords: a prefill layer and its decode-sized remainder give the bits of the
+    aligned layer (the fused QKV epilogue and the tiles step aside)."""
+    from paper_2604_17320_amd.model import PrefillLayer
+    base = wl.CONFIGS[0]
+    shape = wl.Shape("odd", d=base.d, H=base.H, F=base.F, layers=1, B=2, Nv=base.Nv, Nt=21, n_outlier=base.n_outlier,
+                     vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 4, gamma_random=True)
+    x, pos = wl.hidden_state(shape, 4), wl.positions(shape)
+    want = run_gpu(qb, L, shape, x, pos, 19)
+    keep = []
+    for name in ("qkv", "o", "gu", "down"):
+        lin = getattr(L, name)
+        keep.append(torch.cat([lin.scales.new_zeros(1), lin.scales]))
+        lin.desc.scales = keep[-1][1:].data_ptr()
+        assert lin.desc.scales % 4 == 2
+    odd = PrefillLayer(L.H, L.dh, L.F, L.qkv, L.o, L.gu, L.down, L.gamma1, L.gamma2, 1e-5, L.cosT, L.sinT)
+    got = run_gpu(qb, odd, shape, x, pos, 19)
+    for name in want:
+        assert np.array_equal(want[name], got[name]), name

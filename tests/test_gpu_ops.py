@@ -227,6 +227,31 @@ def test_w4a4_gemm_every_tile_bit_exact(qb, tile, pinned_gemm):
         assert np.array_equal(host(y).view(np.uint16), y_ref.view(np.uint16)), (tile, M, N, K)
 
 
+@pytest.mark.parametrize("M", [1, 16, 17, 45, 160])
+def test_w4a4_gemm_with_scales_at_an_odd_halfword(qb, M):
+    """Weight scales that start between two dwords: the bits of the aligned call, output and integer sums."""
+    from paper_2604_17320_amd.model import PackedLinear
+    N, K = 192, 416
+    q, s, qw, sw, res = _gemm_case(M, N, K, 31)
+    lin = PackedLinear.from_codes(dev(qw), dev(sw))
+    room = torch.cat([lin.scales.new_zeros(1), lin.scales])
+    odd = qb.Weights(N, K, lin.packed.data_ptr(), room[1:].data_ptr())
+    assert odd.scales % 4 == 2
+    outs = []
+    for W in (lin.desc, odd):
+        y, yr, ya = (torch.zeros((M, N), dtype=torch.float16, device="cuda") for _ in range(3))
+        acc, alone = (torch.zeros((M, N), dtype=torch.int32, device="cuda") for _ in range(2))
+        qad, sad, resd = dev(_pack4(q)), dev(s), dev(res)
+        args = (qad, sad, M, W)
+        qb.quota_w4a4_gemm(*args, y, N)
+        qb.quota_w4a4_gemm(*args, yr, N, resd, N)
+        qb.quota_w4a4_gemm(*args, ya, N, acc_i32=acc)
+        qb.quota_w4a4_gemm(*args, None, N, acc_i32=alone)
+        outs.append([t.view(torch.int16) for t in (y, yr, ya)] + [acc, alone])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    assert torch.equal(outs[0][0], outs[0][2])
+
+
 def test_w4a4_gemm_unit_scales_give_exact_integers(qb):
     from paper_2604_17320_amd.model import PackedLinear
     r = wl.rng(5, "unit")
