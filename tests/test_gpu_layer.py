@@ -330,7 +330,7 @@ def test_layer_without_taps_equals_layer_with_taps(qb):
     assert np.array_equal(host(cache.v_scales)[0, :n_keep].view(np.uint16), tapped["cache_vs"].view(np.uint16))
 
 
-@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
 def test_layer_every_tile_with_fused_qkv_epilogue(qb, tile, pinned_gemm):
     """The QKV projection with its fused RoPE / KV-quantizer epilogue on each tile that carries it
     (and every other GEMM of the layer on the same tile), teacher-forced bit-exact."""
