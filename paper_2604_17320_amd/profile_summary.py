@@ -23,9 +23,9 @@ passes read per launch, the algorithmic bytes, and the rate against the HBM peak
 
 `mfma` condenses one `--pmc` pass of SQ counters (SQ_INSTS_MFMA SQ_INSTS_VALU
 SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_ACTIVE_INST_VALU SQ_WAVE_CYCLES SQ_WAIT_INST_ANY
-SQ_WAVES) into one line per GEMM kernel class: MFMA instructions issued per launch and what they
-amount to against the int8 dense peak over the dispatch's own duration, vector instructions per
-MFMA, and the busy / wait shares the counters give.
+SQ_WAVES) into one line per kernel class that uses the matrix cores: MFMA instructions issued per
+launch and what they amount to against the dense peak of their type over the dispatch's own
+duration, vector instructions per MFMA, and the busy / wait shares the counters give.
 """
 import collections
 import csv
@@ -33,20 +33,16 @@ import json
 import re
 import sys
 
-# profiler kernel name (substring) -> kernel class name used by the library's own timing
+# profiler kernel name (substring, first match counts) -> kernel class name used by the library's own timing; kernels
+# that it does not time go by their own names
 CLASSES = [
-    ("w4a4_gemm_kernelILi2ELi2E", "w4a4_gemm_64x256"),
-    ("w4a4_gemm_kernelILi2ELi1ELi4ELi2ELb1ELb0E", "w4a4_gemm_64x128"),
-    ("w4a4_gemm_kernelILi2ELi1ELi3ELi0ELb0ELb0E", "w4a4_gemm_64x128_lean"),
-    ("w4a4_gemm_kernelILi1ELi1ELi4E", "w4a4_gemm_32x128"),
-    ("w4a4_gemm_kernelILi1ELi1ELi8E", "w4a4_gemm_32x128_deep"),
-    ("w4a4_gemm_kernel", "w4a4_gemm_other"),
+    ("w4a4_f8_kernelILi4ELi4ELi2ELi2ELi6ELb1ELb1E", "w4a4_gemm_other"),      # with the integer sums
     ("w4a4_f8_kernelILi4ELi4ELi4E", "w4a4_gemm_64x256"),
     ("w4a4_f8_kernelILi4ELi4ELi2E", "w4a4_gemm_64x128"),
     ("w4a4_f8_kernelILi2ELi2ELi4E", "w4a4_gemm_32x128"),
     ("w4a4_f8_kernelILi2ELi1ELi4E", "w4a4_gemm_32x64"),
     ("w4a4_f8_kernelILi8ELi4ELi4E", "w4a4_gemm_128x256"),
-    ("w4a4_gemv16_kernel", "w4a4_gemm_rows16"),
+    ("w4a4_rows16_kernel", "w4a4_gemm_rows16"),
     ("silu_mul_quantize_act_kernel", "silu_mul_quantize_act"),
     ("rmsnorm_quantize_act_kernel", "rmsnorm_quantize_act"),
     ("quantize_act_kernel", "quantize_act"),
@@ -60,12 +56,34 @@ CLASSES = [
     ("topk_kernel", "topk_prune"),
     ("compact_rows_kernel", "compact_rows"),
     ("decode_attention_kernel", "attention_decode"),
-    ("kv_append_rows_kernel", "kv_append_rows"),
+    ("decode_combine_kernel", "attention_decode_combine"),
+    ("quantize_pack_weights_kernel", "pack_weights"),
     ("quantize_weights8_kernel", "quantize_weights"),
     ("quantize_weights_kernel", "quantize_weights"),
     ("pack_weights16_kernel", "pack_weights"),
     ("pack_weights_kernel", "pack_weights"),
+    ("fp_gemm_kernel", "fp_gemm"),
+    ("fp_rmsnorm_kernel", "fp_rmsnorm"),
+    ("fp_rope_kernel", "fp_rope"),
+    ("fp_silu_mul_kernel", "fp_silu_mul"),
+    ("deviation_finish_kernel", "deviation_finish"),
+    ("deviation_kernel", "deviation"),
+    ("advance_step_kernel", "advance_step"),
+    ("copy_f32_kernel", "copy_f32"),
 ]
+
+# operations of one matrix instruction of a class and the dense peak of its type: v_mfma_f32_16x16x128_f8f6f4 on e4m3
+# operands, v_mfma_f32_32x32x16_f16
+FP8 = (2 * 16 * 16 * 128, 5000.0)
+FP16 = (2 * 32 * 32 * 16, 2500.0)
+
+
+def matrix_type(cls):
+    if cls is None:
+        return None
+    if cls.startswith("w4a4_gemm"):
+        return FP8
+    return FP16 if cls in ("fp_gemm", "attention_fwd", "attention_colmass") else None
 
 
 def classify(name):
@@ -206,31 +224,34 @@ def mfma(csv_path, bench_path=None):
     dur = collections.defaultdict(dict)                                      # class -> dispatch id -> ns
     for r in csv.DictReader(open(csv_path)):
         cls = classify(r["Kernel_Name"])
-        if cls is None or not cls.startswith("w4a4_gemm"):
+        if matrix_type(cls) is None:
             continue
         per[cls][r["Counter_Name"]].append(float(r["Counter_Value"]))
         dur[cls][r["Dispatch_Id"]] = float(r["End_Timestamp"]) - float(r["Start_Timestamp"])
     mean = lambda v: sum(v) / len(v) if v else float("nan")
-    print("per launch, mean over the dispatches of each GEMM kernel class (durations are those of the counter run, "
+    print("per launch, mean over the dispatches of each kernel class (durations are those of the counter run, "
           "which serialises kernels and is slower than a plain run)")
-    print(f"{'kernel':24s} {'launches':>8s} {'us':>7s} {'MFMA inst':>10s} {'issued TOP/s':>12s} {'of int8 peak':>12s} "
+    print(f"{'kernel':24s} {'launches':>8s} {'us':>7s} {'MFMA inst':>10s} {'issued TOP/s':>12s} {'of the peak':>12s} "
           f"{'VALU/MFMA':>9s} {'MFMA busy':>9s} {'VALU active':>11s} {'waiting':>8s}")
     for cls, c in sorted(per.items()):
         n = len(dur[cls])
         us = mean(list(dur[cls].values())) / 1e3
         m, v = mean(c["SQ_INSTS_MFMA"]), mean(c["SQ_INSTS_VALU"])
-        tops = m * 65536.0 / (us * 1e-6) / 1e12            # one v_mfma_i32_32x32x32_i8 = 32*32*32 MACs
+        ops, peak = matrix_type(cls)
+        tops = m * ops / (us * 1e-6) / 1e12
         busy_cu, wave_cyc = mean(c["SQ_BUSY_CU_CYCLES"]), mean(c["SQ_WAVE_CYCLES"])
-        print(f"{cls:24s} {n:8d} {us:7.1f} {m:10.0f} {tops:12.1f} {tops / 5000.0:12.3f} {(v - m) / m:9.1f} "
+        print(f"{cls:24s} {n:8d} {us:7.1f} {m:10.0f} {tops:12.1f} {tops / peak:12.3f} {(v - m) / m:9.1f} "
               f"{mean(c['SQ_VALU_MFMA_BUSY_CYCLES']) / (4.0 * busy_cu):9.3f} {mean(c['SQ_ACTIVE_INST_VALU']) / wave_cyc:11.3f} "
               f"{mean(c['SQ_WAIT_INST_ANY']) / wave_cyc:8.3f}")
-    print("\nMFMA inst: v_mfma_i32_32x32x32_i8 issued (all waves); issued TOP/s = MFMA inst * 65536 ops / duration (includes the\n"
-          "rows and columns a tile pads); VALU/MFMA: other vector instructions per MFMA (SQ_INSTS_VALU counts the MFMAs too);\n"
+    print("\nMFMA inst: issued by all waves; issued TOP/s = MFMA inst * operations of one / duration, against 5.0 (fp8: the W4A4\n"
+          "GEMMs, v_mfma_f32_16x16x128_f8f6f4) or 2.5 (fp16, v_mfma_f32_32x32x16_f16) POP/s.  Included are the rows and columns\n"
+          "that a tile pads and, in the W4A4 GEMMs, the constant products that take the code offset out again (one to every\n"
+          "1, 2 or 4 others, by tile); VALU/MFMA: other vector instructions per MFMA (SQ_INSTS_VALU counts the MFMAs too);\n"
           "MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs * SQ_BUSY_CU_CYCLES); VALU active, waiting = SQ_ACTIVE_INST_VALU, SQ_WAIT_INST_ANY\n"
           "over SQ_WAVE_CYCLES (share of wave lifetime).")
     if bench:
         g = bench.get("gemm_all", {})
-        print(f"\nplain run of bench.py: GEMMs {g.get('TOPs')} TOP/s algorithmic = {g.get('frac_int8_peak')} of the int8 peak, "
+        print(f"\nplain run of bench.py: GEMMs {g.get('TOPs')} TOP/s algorithmic = {g.get('frac_fp8_peak')} of the fp8 peak, "
               f"{g.get('step_ms')} ms of a {bench['ms_per_step']} ms step")
 
 

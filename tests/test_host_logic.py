@@ -2,9 +2,9 @@
 definitions (shapes, the keep schedules the benchmark and the stack tests run) and the tool that
 condenses profiler CSVs into the summaries under profiles/."""
 import csv
-import io
-import json
+import glob
 import os
+import re
 import subprocess
 import sys
 
@@ -45,13 +45,39 @@ def test_generators_are_seeded_and_shaped():
 
 
 def test_profile_summary_classifies_library_kernels():
-    assert ps.classify("_ZN12_GLOBAL__N_116w4a4_gemm_kernelILi2ELi1ELi4ELi2ELb1ELb0ELb0ELi1EEEvPKh") == "w4a4_gemm_64x128"
-    assert ps.classify("_ZN12_GLOBAL__N_116w4a4_gemm_kernelILi1ELi1ELi8ELi4ELb1ELb0ELb1ELi1EEEv") == "w4a4_gemm_32x128_deep"
+    f8 = "_ZN12_GLOBAL__N_114w4a4_f8_kernelILi%dELi%dELi%dELi%dELi%dELb%dELb%dELb%dELi2EEEvPKh"
+    assert ps.classify(f8 % (4, 4, 2, 2, 6, 0, 0, 1)) == "w4a4_gemm_64x128"
+    assert ps.classify(f8 % (4, 4, 2, 2, 6, 1, 1, 0)) == "w4a4_gemm_other"
+    assert ps.classify(f8 % (2, 1, 4, 4, 0, 0, 0, 0)) == "w4a4_gemm_32x64"
+    assert ps.classify("_ZN12_GLOBAL__N_118w4a4_rows16_kernelILi2ELi1ELi2ELi1EEEvNS_6RowsInE") == "w4a4_gemm_rows16"
     assert ps.classify("_Z27rmsnorm_quantize_act_kernelILb0ELi64ELi8EEv") == "rmsnorm_quantize_act"
     assert ps.classify("_Z19quantize_act_kernelILb1ELi64ELi8EEv") == "quantize_act"
     assert ps.bandwidth_case("_Z19quantize_act_kernelILb1ELi64ELi8EEv") == "quantize_act (+ m_mag, m_res)"
     assert ps.bandwidth_case("_Z27rmsnorm_quantize_act_kernelILb0ELi64ELi8EEv") == "rmsnorm_quantize_act"
     assert ps.classify("void at::native::elementwise_kernel<...>") is None
+
+
+def test_profile_summary_knows_the_kernels_there_are():
+    """Every kernel of the sources has a class, every class a kernel, and the classes that the library times
+    carry the library's names."""
+    names = set()
+    for path in glob.glob(os.path.join(ROOT, "paper_2604_17320_amd", "csrc", "*.hip")):
+        with open(path) as f:
+            for head in re.findall(r"__global__(.*?)\{", f.read(), re.S):
+                names.add(re.search(r"\b(\w+_kernel)\s*\(", head).group(1))
+    mangled = {n: ps.classify(f"_ZN12_GLOBAL__N_1{len(n)}{n}EPKh") for n in names}
+    unknown = {n for n, cls in mangled.items() if cls is None}
+    assert unknown == {"empty_kernel", "w4a4_f8_kernel"}                       # (the latter: by its template arguments)
+    assert {re.match(r"\w+?_kernel", key).group(0) for key, _ in ps.CLASSES} == names - {"empty_kernel"}
+    gemm = set()
+    with open(os.path.join(ROOT, "paper_2604_17320_amd", "csrc", "gemm.hip")) as f:
+        for args in re.findall(r"#define F8_TILE_\d\(P, A, QK\)\s*w4a4_f8_kernel<([^>]*)>", f.read()):
+            v = [a.strip() for a in args.split(",")]
+            gemm.add(ps.classify("w4a4_f8_kernelI" + "".join(f"Li{a}E" if a.isdigit() else "Lb0E" for a in v)))
+    assert len(gemm) == 5 and None not in gemm
+    from paper_2604_17320_amd import binding
+    timed = {binding.quota_kernel_name(i) for i in range(binding.KERNEL_COUNT)}
+    assert gemm | {"w4a4_gemm_other", "w4a4_gemm_rows16", "attention_decode", "score_tokens", "pack_weights"} <= timed
 
 
 def test_profile_summary_stats_table(tmp_path, capsys):
