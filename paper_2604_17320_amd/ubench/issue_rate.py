@@ -1,12 +1,12 @@
 #!/usr/bin/env python3
-"""Issue-rate probe for gfx950: what one v_mfma_i32_32x32x32_i8 and one fp32 vector instruction cost
-a SIMD's issue, alone and interleaved, at one and two waves per SIMD.
+"""Issue-rate probe for gfx950: what the matrix instruction of the W4A4 GEMM (v_mfma_f32_16x16x128_f8f6f4) and the
+vector instructions that it needs beside it cost a SIMD, alone and interleaved, at one and two waves per SIMD.
 
-The W4A4 GEMM needs, per 32x32x32 MFMA, 8 vector instructions for the per-group fp32 scale (one
-convert + one fma per output element and 128-deep group) and about 6 more to unpack int4 operands.
-This probe places exactly that mix by hand (one asm block, fixed registers, register-to-register
-only, no memory access in the timed loop, results meaningless) so that the compiler's scheduling is
-out of the picture, and prints ns per block of 16 MFMAs.
+A 128-channel group of a wave's RT x CT blocks of 16 x 16 outputs takes RT CT products, RT products against the
+constant that removes the codes' offset, 4 RT CT fp32 multiply-adds for the group's scale and 12 CT integer
+instructions that unpack its weights.  This probe places exactly those mixes by hand (one asm block, fixed registers,
+register-to-register only, no memory access in the timed loop, results meaningless) so that the compiler's scheduling is out
+of the picture, and prints ns per group and the share of the matrix rate that the products alone reach.
 
     python -m paper_2604_17320_amd.ubench.issue_rate        # needs hipcc and a GPU
 """
@@ -14,6 +14,9 @@ import os
 import subprocess
 import sys
 import tempfile
+
+SHAPES = [("128 x 256 tile, wave 8 x 4 blocks", 8, 4), ("64 x 256 and 64 x 128, wave 4 x 4", 4, 4),
+          ("32 x 128, wave 2 x 2", 2, 2), ("32 x 64, wave 2 x 1", 2, 1)]
 
 TEMPLATE = r'''
 #include <hip/hip_runtime.h>
@@ -24,15 +27,12 @@ __global__ __launch_bounds__(256) void k(float *out, int iters)
     float s = threadIdx.x;
 #pragma unroll 1
     for (int it = 0; it < iters; ++it) {
-        if (MODE == 0) asm volatile("@@M@@" ::: @@CLOB@@);
-        else if (MODE == 1) asm volatile("@@V@@" ::: @@CLOB@@);
-        else if (MODE == 2) asm volatile("@@B8@@" ::: @@CLOB@@);
-        else asm volatile("@@B14@@" ::: @@CLOB@@);
+@@CASES@@
     }
     out[blockIdx.x * 256 + threadIdx.x] = s;
 }
 template <int MODE>
-void run(const char *what, float *d, int wgs)
+float run(float *d, int wgs)
 {
     const int iters = 4000;
     hipEvent_t e0, e1;
@@ -43,55 +43,80 @@ void run(const char *what, float *d, int wgs)
     k<MODE><<<wgs, 256>>>(d, iters);
     (void)hipEventRecord(e1);
     (void)hipEventSynchronize(e1);
-    float ms; (void)hipEventElapsedTime(&ms, e0, e1);
-    printf("%-44s workgroups=%4d (%d wave(s) per SIMD)  %7.1f ns per block\n", what, wgs, wgs / 256, ms * 1e6 / iters);
+    float ms = 0.0f; (void)hipEventElapsedTime(&ms, e0, e1);
+    return ms * 1e6f / iters;
 }
 int main()
 {
     float *d;
     if (hipMalloc(&d, 4096 * 256 * 4) != hipSuccess) return 2;
     for (int wgs : {256, 512}) {
-        run<0>("16 MFMA", d, wgs);
-        run<1>("128 VALU (64 x convert + fma)", d, wgs);
-        run<2>("16 x (1 MFMA + 8 VALU)", d, wgs);
-        run<3>("16 x (1 MFMA + 14 VALU)", d, wgs);
+        printf("%d wave(s) per SIMD: ns per group (of each wave), and the products alone against it\n", wgs / 256);
+@@RUNS@@
     }
     return 0;
 }
 '''
 
+MFMA, FMA, UNPACK = "mfma", "fma", "unpack"
 
-def block(with_mfma, chain, extra):
-    """16 slots; per slot optionally one MFMA (two accumulator sets take turns, the vector work reads the
-    other one), `chain` convert+fma pairs and `extra` integer instructions."""
-    lines, accs = [], [(64, 79), (80, 95)]
-    for t in range(4):
-        a, p = accs[t & 1], accs[(t + 1) & 1]
-        r = 0
-        for k in range(4):
-            if with_mfma:
-                c = "0" if k == 0 else f"v[{a[0]}:{a[1]}]"
-                lines.append(f"v_mfma_i32_32x32x32_i8 v[{a[0]}:{a[1]}], v[160:163], v[164:167], {c}")
-            for _ in range(chain):
-                lines.append(f"v_cvt_f32_i32_e32 v168, v{p[0] + r}")
-                lines.append(f"v_fmac_f32_e32 v{96 + 16 * t + r}, v168, v169")
-                r += 1
-            for q in range(extra):
-                reg = 170 + q % 8
-                lines.append(f"v_and_b32_e32 v{reg}, 0xf0f0f0f0, v{reg}" if q % 3 else f"v_lshlrev_b32_e32 v{reg}, 4, v{reg}")
+
+def mix(rt, ct, offset, scale, unpack):
+    """The instructions of a group, vector work spread evenly behind the matrix instructions."""
+    mats = rt * ct + (rt if offset else 0)
+    vec = [FMA] * (4 * rt * ct if scale else 0) + [UNPACK] * (12 * ct if unpack else 0)
+    order, done = [], 0
+    for m in range(mats):
+        order.append(MFMA)
+        upto = len(vec) * (m + 1) // mats
+        order += vec[done:upto]
+        done = upto
+    return order
+
+
+def block(order):
+    lines, m, f, u = [], 0, 0, 0
+    for what in order:
+        if what == MFMA:                                   # eight results take turns; the chain reads one four places back
+            a = 64 + 4 * (m % 8)
+            lines.append(f"v_mfma_f32_16x16x128_f8f6f4 v[{a}:{a + 3}], v[160:167], v[168:175], v[96:99]")
+            m += 1
+        elif what == FMA:
+            lines.append(f"v_fmac_f32_e32 v{100 + f % 48}, v{64 + (4 * (m + 3) + f) % 32}, v148")
+            f += 1
+        else:
+            reg = 150 + u % 8
+            lines.append((f"v_lshrrev_b32_e32 v{reg}, 4, v{reg}", f"v_and_b32_e32 v{reg}, 0x0f0f0f0f, v{reg}",
+                          f"v_xor_b32_e32 v{reg}, 0x08080808, v{reg}")[u % 3])
+            u += 1
     return "\\n\\t".join(lines)
 
 
 def main():
-    src = (TEMPLATE.replace("@@M@@", block(True, 0, 0)).replace("@@V@@", block(False, 4, 0))
-           .replace("@@B8@@", block(True, 4, 0)).replace("@@B14@@", block(True, 4, 6))
-           .replace("@@CLOB@@", ",".join(f'"v{i}"' for i in range(64, 180))))
+    cases, runs, mode = [], [], 0
+    clobber = ",".join(f'"v{i}"' for i in range(64, 176))
+    for name, rt, ct in SHAPES:
+        steps = [("products", (False, False, False)), ("+ offset products", (True, False, False)),
+                 ("+ scale chain", (True, True, False)), ("+ unpack: the whole group", (True, True, True))]
+        runs.append(f'        {{ float t, t0 = 0; (void)t0; printf("  {name}\\n");')
+        for i, (what, flags) in enumerate(steps):
+            cases.append(f'        {"else " if mode else ""}if (MODE == {mode}) asm volatile("{block(mix(rt, ct, *flags))}" ::: {clobber});')
+            keep = " t0 = t;" if i == 0 else ""
+            runs.append(f'        t = run<{mode}>(d, wgs);{keep} printf("    %-28s %8.1f ns   %5.1f %%\\n", "{what}", t, 100 * t0 / t);')
+            mode += 1
+        runs.append("        }")
+    src = TEMPLATE.replace("@@CASES@@", "\n".join(cases)).replace("@@RUNS@@", "\n".join(runs))
     with tempfile.TemporaryDirectory() as tmp:
         path, exe = os.path.join(tmp, "issue_rate.hip"), os.path.join(tmp, "issue_rate")
         with open(path, "w") as f:
             f.write(src)
-        subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O3", path, "-o", exe],
-                       check=True)
+        cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O3", "-Xclang", "-target-feature",
+               "-Xclang", "-packed-fp32-ops", path, "-o", exe]
+        done = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+        if done.returncode != 0:
+            sys.exit(done.stderr)
+        if "--build-only" in sys.argv:
+            return 0
         return subprocess.run([exe]).returncode
 
 
