@@ -59,10 +59,10 @@ struct DecodeNew {
 // head are neighbours on one XCD, so its rows come from HBM once and from that XCD's L2 afterwards.  The
 // cached rows are walked in tiles of DEC_TILE tokens with a running softmax (maximum, sum, rescaled
 // output), so the scores of one tile are all the LDS the walk needs, whatever the cache length.
-//   new row: FUSED calls are handed the plain projection of the new token: wave 0 rotates q and k and
-//            quantizes k and v while the first tile is on its way; the row is used from LDS, and one
-//            workgroup per K/V head appends it to the cache (a launch less per layer, and the QKV GEMM
-//            needs no epilogue);
+//   new row: FUSED calls are handed the plain projection of the new token: a workgroup's first
+//            threads rotate q and k and quantize k and v while the first tile is on its way; the row is
+//            used from LDS, and one workgroup per K/V head appends it to the cache (a launch less per
+//            layer, and the QKV GEMM needs no epilogue);
 //   loads:   the walk is latency-bound (a workgroup owns a few tens of KB), so every K and V load of a
 //            tile is issued before the first use -- UN passes of 512 lanes x 16 bytes each -- and the next
 //            tile's as soon as the registers of this one's are free;

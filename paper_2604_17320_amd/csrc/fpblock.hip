@@ -15,8 +15,11 @@ namespace {
 // v_mfma_f32_32x32x16_f16.  Both operands come to LDS 64 channels at a time by asynchronous copies,
 // the next 64 on their way while the current ones are multiplied (one wait and one barrier per 64);
 // the plain form, every fragment straight from global memory, ran at 0.2 PFLOP/s because each wave
-// fetched both operands for itself.  Bound by LDS reads: 16 KB per wave and 64 channels against
-// 16 MFMAs = 512 cycles.  LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
+// fetched both operands for itself.  1280 rows: 0.89 PFLOP/s at 12288 x 4096, 0.84 at 22016 x 4096, 0.60 and
+// 0.65 at 4096 x 4096 and 4096 x 11008, whose 320 workgroups do not fill the 512 places.  Neither the matrix
+// cores (42 % busy) nor the LDS (its reads, 3.9 ns each per CU, fill 37 % of the time) bind it: two
+// workgroups on a CU, each with one stage on its way, leave the waves waiting for 44 % of their lives.
+// LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
 // Lane l supplies 8 consecutive k of row (l % 32) to both operands (k slots 8 (l / 32) .. +7 of the
 // step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.
 // Rows beyond M and N repeat the last one and are not stored.  Needs N % 64 == 0, K % 16 == 0, x and W at

@@ -3,9 +3,9 @@
 //
 // Small integers are exact in fp8 (e4m3), and the fp32 accumulator of v_mfma_f32_16x16x128_f8f6f4 is
 // exact for sums below 2^24 units, so one such instruction returns the exact integer dot product of a
-// whole 128-deep group -- already as a float.  That halves the scale chain against an int8 contraction
-// (one fma per element and group instead of a convert and an fma) and that chain is what bounds the
-// kernel: every element needs y = fma(acc_g, s_g, y) group after group.
+// whole 128-deep group -- already as a float.  Every element needs
+// y = fma(acc_g, s_g, y), group after group; against an int8 contraction, which that chain bounds, it is half as
+// long (no conversion in front of the fma).
 //
 // Weights: a nibble c + 8 in 0..15 placed in the low half of a byte IS the e4m3 number (c + 8) / 512
 // (the subnormals and the first binade of e4m3 are one linear range), so the unpack stays at 3 vector
@@ -14,6 +14,12 @@
 // accumulator's start value, -8 / 2^18 * sum of the group's activation codes: one more MFMA per 16 rows and
 // group, against a constant -8 / 512, whose result already lies where the C operand wants it.  The 2^18
 // of the operands' units goes into the token scale (exact).
+//
+// What bounds it: issued register to register, offset products, scale chain and unpack leave 78 % of the matrix rate to
+// the products at 8 x 4 blocks per wave, 71 at 4 x 4, 39 to 47 on the 32-row tiles.  At a thousand rows and more
+// the kernels come near that (1280 x 22016 x 4096: matrix cores 57 % busy); on the rows of a pruned
+// prompt they are busy for 32 to 45 % and the waves wait for 25 to 47 % of their lives: one stage of
+// lookahead, and a wait for all of it.
 //
 // Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes, row stride 128 (G | 1) (an
 // odd number of 128-byte lines: with a power of two the rows a tile reads together share one L2 channel), every 8
@@ -40,8 +46,9 @@ namespace {
 //   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
 //   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
 //   32-row tiles have no time to spare and lose by it).
-// LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that the 8 lanes of one LDS
-// cycle (8 rows, same piece) cover all banks.
+// LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that 8 neighbouring rows' pieces
+// do not share banks (a CU with 8 waves reading takes 3.9 ns per read instruction so, 3.3 from consecutive
+// addresses, 13.4 unpermuted).
 template <int RT, int CT, int NW, int CH, int SP, bool PACKED, bool ACC_OUT, bool QKV, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,

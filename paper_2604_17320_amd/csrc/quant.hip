@@ -1,10 +1,10 @@
 // Quantizers of the W4A4 execution form: weight group quantizer + repack,
 // per-token int4 activation quantizer (the Q of Eq. 6) and its fused variants
 // (RMSNorm in front of QKV / gate-up, SwiGLU product in front of down).
-// All are row kernels: one wave per row (four rows per workgroup) up to 4096
-// columns, one workgroup per row beyond; the row is cached in registers as
-// 16-byte chunks, absmax / sums of squares are wave or block reductions, one
-// packed dword (8 codes) is stored per chunk.  HBM-bound by design.
+// All are row kernels: in launches of 2048 rows and more of up to 4096 columns one wave per row
+// (four rows per workgroup), else one workgroup per row; the row is cached in registers as
+// 16-byte chunks, absmax / sums of squares are wave or block reductions, 8 codes are stored per
+// chunk: a packed dword, or 8 e4m3 bytes for the GEMM.  HBM-bound by design.
 #include "common.h"
 #include "internal.h"
 #include "rowquant.h"
@@ -180,12 +180,12 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
 
 // ------------------------------------------------- activation quantizers
 
-// A row is owned by GROUP threads, each caching NCH chunks (2 or 8).  Every load of a thread is
+// A row is owned by GROUP threads, each caching NCH chunks (2, 8 or 16).  Every load of a thread is
 // issued before the first use (unconditional loads at clamped indices instead of guarded ones, so
 // that nothing separates them): one memory round trip per kernel.  GROUP = 64 (rows of up to 4096
 // columns): one WAVE per row, four rows per workgroup -- a lane issues all its 16-byte loads back
 // to back, the reductions are wave shuffles and there is no workgroup barrier.  GROUP = 256 (up to
-// 16384 columns): the whole workgroup owns the row and reduces through LDS.
+// 32768 columns): the whole workgroup owns the row and reduces through LDS.
 // Below this many rows the launch cannot fill the chip with one wave per row, and a row is
 // finished sooner by a whole workgroup.
 #define ROW_WAVE_MIN_ROWS 2048

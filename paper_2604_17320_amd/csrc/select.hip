@@ -6,7 +6,7 @@
 // registers: four per metric, both percentile bounds in the same passes, then all sixteen for the top-k; the
 // counters are integers, so the result does not depend on execution order.  576 / 2880 tokens (32 / 40
 // heads): 25 / 113 us with one wave per bound and per top-k and the head means of the attention cues taken here,
-// 10 / 19 us so, with the head means taken by the cue pass.
+// 10 / 19 us so, with the head means taken before it.
 #include "common.h"
 #include "internal.h"
 
