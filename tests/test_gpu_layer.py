@@ -112,6 +112,11 @@ CASES = [
     ("keep_none", dict(), 0),
     ("batch2_prefix", dict(B=2, vis_begin=3, Nt=9), 19),
     ("no_visual", dict(Nv=0, Nt=40), 5),
+    ("one_row_left", dict(Nt=1), 0),                   # rows behind the compaction: the few-row GEMM quantizes its input,
+    ("three_rows_left", dict(Nt=2), 1),
+    ("nine_rows_left", dict(B=3, Nt=2), 1),            # reads fragments of 9 and 15 rows,
+    ("fifteen_rows_left", dict(Nt=9), 6),
+    ("seventeen_rows_left", dict(Nt=9), 8),            # and gives way to the tiles
     ("long_visual_prefix", dict(Nv=4100, Nt=28), 1000),   # more scored tokens than fit the default LDS limit of a launch
 ]
 
