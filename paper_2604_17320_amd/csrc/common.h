@@ -80,6 +80,15 @@ __device__ __forceinline__ float wave_sum(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// sum over each row of 16 lanes, in its last lane
+__device__ __forceinline__ float row16_sum(float v)
+{
+#define STEP(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false));
+    STEP(0x111) STEP(0x112) STEP(0x114) STEP(0x118)
+#undef STEP
+    return v;
+}
+
 // block-wide (blockDim.x = 64*NW) max of a float and sum of up to two doubles;
 // every thread gets the result.  `sm` needs 3*NW doubles of LDS.
 template <int NW>
@@ -97,6 +106,15 @@ __device__ __forceinline__ void block_max_sum2(float &mx, double &s0, double &s1
 #pragma unroll
     for (int i = 1; i < NW; ++i) { m = fmaxf(m, (float)sm[i]); a += sm[NW + i]; b += sm[2 * NW + i]; }
     mx = m; s0 = a; s1 = b;
+}
+
+// Consecutive workgroups go round-robin over the 8 XCDs, each with its own L2: this gives each XCD a contiguous range
+// of ids.
+__device__ __forceinline__ int xcd_remap(int pid, int total)
+{
+    int x = pid & 7, idx = pid >> 3;
+    int per = total >> 3, rem = total & 7;
+    return x * per + (x < rem ? x : rem) + idx;
 }
 
 // fp32 -> fp16 with the fp32 value materialised first.  Without the barrier

@@ -11,20 +11,23 @@
 // (the subnormals and the first binade of e4m3 are one linear range), so the unpack stays at 3 vector
 // instructions per 8 codes: lo = (w & 0x0f..) ^ 0x08.., hi = (w >> 4 & 0x0f..) ^ 0x08...
 // Activations are signed e4m3 numbers a / 512.  The weights' offset of 8 comes back out through the
-// accumulator's start value, -8 / 2^18 * sum of the group's activation codes: one more MFMA per 16 rows and
-// group, against a constant -8 / 512, whose result already lies where the C operand wants it.  The 2^18
-// of the operands' units goes into the token scale (exact).
+// accumulator's start value, -8 / 2^18 * sum of the group's activation codes.  With few rows every wave makes it by
+// one more MFMA per 16 rows and group, against a constant -8 / 512, whose result already lies where the C operand wants
+// it; with many (quota_a8_starts) the quantizer has written it beside the rows and it comes along through LDS (all
+// waves of all column tiles made the same ones).  The 2^18 of the operands' units goes into the token scale (exact).
 //
 // What bounds it: issued register to register, offset products, scale chain and unpack leave 78 % of the matrix rate to
-// the products at 8 x 4 blocks per wave, 71 at 4 x 4, 39 to 47 on the 32-row tiles.  At a thousand rows and more
+// the products at 8 x 4 blocks per wave, 71 at 4 x 4, 39 to 47 on the 32-row tiles; without the offset products the
+// launches of 1100 to 11264 rows take 2 to 9 % less (11264 x 12288 x 4096: 553 -> 532 us).  At a thousand rows and more
 // the kernels come near that (1280 x 22016 x 4096: matrix cores 57 % busy); on the rows of a pruned
 // prompt they are busy for 32 to 45 % and the waves wait for 25 to 47 % of their lives: one stage of
 // lookahead, and a wait for all of it.
 //
 // Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes, row stride 128 (G | 1) (an
 // odd number of 128-byte lines: with a power of two the rows a tile reads together share one L2 channel), every 8
-// codes stored as evens then odds (the order the weight unpack produces).  The public entry point takes
-// packed int4 rows and converts them while staging (PACKED).
+// codes stored as evens then odds (the order the weight unpack produces); behind the rows, if there are
+// many of them, the start values as floats, [group][row].  The public entry point takes
+// packed int4 rows and converts them while staging (PACKED_INT4).
 #include "common.h"
 #include "internal.h"
 #include "ropequant.h"
@@ -49,7 +52,8 @@ namespace {
 // LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that 8 neighbouring rows' pieces
 // do not share banks (a CU with 8 waves reading takes 3.9 ns per read instruction so, 3.3 from consecutive
 // addresses, 13.4 unpermuted).
-template <int RT, int CT, int NW, int CH, int SP, bool PACKED, bool ACC_OUT, bool QKV, int OCC>
+enum ActFormat { A8, A8_STARTS, PACKED_INT4 };
+template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, bool QKV, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
@@ -57,11 +61,13 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     int vec_store, quota_qkv_epilogue qe)
 {
     constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
+    constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A8_STARTS;
     constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : BM * 8 / NT;    // 16-byte pieces per thread and group
-    constexpr int KD = (CH * BN / 2 + NT - 1) / NT;                      // scale dwords per thread and stage
+    // dwords per stage, 64 to a copy: the group scales, then (STARTS) the rows' start values
+    constexpr int SCOPY = CH * BN / 128, ICOPY = STARTS ? CH * BM / 64 : 0, KD = (SCOPY + ICOPY + NW - 1) / NW;
     static_assert(RT % 2 == 0 && (PACKED || BM * 8 % NT == 0), "whole rows per copy, fragment double buffer");
     // one stage in LDS (in uint4): CH groups of activations (+ a spare piece for PACKED threads without one),
-    // then the group scales, up to whole waves
+    // then the dwords, up to whole waves
     constexpr int AST = BM * 8 + (PACKED ? 2 : 0), GST = CH * AST, STG = GST + KD * NT / 4;
     constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
     constexpr int LDS_A = 2 * STG, LDS_Q = QKV ? 32 * TROW / 8 : 32 * FROW / 4;
@@ -92,21 +98,23 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const int nw = min(n0 + wave * WN, N - WN);          // this wave's first column (N is a multiple of 64)
     const bool n_ok = n0 + wave * WN < N;
     const unsigned wl = (unsigned)(c16 * 4 + q);         // this lane's uint4 of a 16-column block
-    // scale dword tid + NT k of a stage: two neighbouring columns of one of its groups
+    // dword tid + NT k of a stage: the scales of two neighbouring columns, or the start value of a row, in one of its groups
+    const float *starts = reinterpret_cast<const float *>(qa + (size_t)M * Kb);
     unsigned os[KD];
     int gs[KD];
 #pragma unroll
     for (int k = 0; k < KD; ++k) {
-        const int d = min(tid + NT * k, CH * BN / 2 - 1);
-        gs[k] = d / (BN / 2);
-        os[k] = 4u * (unsigned)min((n0 >> 1) + d % (BN / 2), (N >> 1) - 1);
+        const bool scale = !STARTS || wave + NW * k < SCOPY;
+        const int d = scale ? min(tid + NT * k, CH * BN / 2 - 1) : min(tid + NT * k - 64 * SCOPY, CH * BM - 1);
+        gs[k] = scale ? d / (BN / 2) : d / BM;
+        os[k] = 4u * (unsigned)(scale ? min((n0 >> 1) + d % (BN / 2), (N >> 1) - 1) : min(m0 + d % BM, M - 1));
     }
 
     constexpr int WS = CH > 1 ? 2 : 1;                   // register sets of packed weights = stages per loop body
     uint4 rw[WS][CH][CT];
     i32x4 ra[CH][LA];                                    // PACKED staging (struct uint4 here would live in scratch memory)
     // What a stage needs, load by load: for each of its groups CT weight pieces and LA activation pieces, then
-    // KD dwords of scales.  The pointers (uniform, of the next group to load) stop at the last group:
+    // KD dwords.  The pointers (uniform, of the next group to load) stop at the last group:
     // groups past it are loaded but never used.
     constexpr int LG = CT + LA, LOADS = CH * LG + KD;
     const uint4 *wnext = wp + (size_t)nw * 4;
@@ -135,7 +143,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             }
         } else {
             const int j = k - CH * LG;
-            copy4_to_lds(sw, os[j] + (unsigned)min(gstage + gs[j], G - 1) * (unsigned)(2 * N), dst + (unsigned)(GST * 16 + (wave + NW * j) * 256));
+            const bool scale = !STARTS || wave + NW * j < SCOPY;
+            const unsigned g = (unsigned)min(gstage + gs[j], G - 1);
+            copy4_to_lds(scale ? (const void *)sw : starts, os[j] + g * (unsigned)(scale ? 2 * N : 4 * M),
+                         dst + (unsigned)(GST * 16 + (wave + NW * j) * 256));
         }
     };
     auto store_packed = [&](int half) {                  // convert and store what the loads brought
@@ -180,8 +191,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         const uint4 a0 = gp[i * 128 + fr + ((2 * q) ^ fx)], a1 = gp[i * 128 + fr + ((2 * q + 1) ^ fx)];
         fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
     };
-    auto start_of = [&](const i32x8 &fa) {
-        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{0, 0, 0, 0}, 0, 0, 0, 0, 0, 0);
+    // the start values of row block i's results in group c of the stage
+    auto start_of = [&](const uint4 *sp, int c, int i, const i32x8 &fa) {
+        if constexpr (!STARTS) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{0, 0, 0, 0}, 0, 0, 0, 0, 0, 0);
+        else return *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(sp + GST) + 64 * SCOPY + c * BM + 16 * i + 4 * q);
     };
     auto read_scale = [&](const uint4 *sp, int c, int j) {
         return (float)reinterpret_cast<const f16 *>(sp + GST)[c * BN + wave * WN + 16 * j + c16];
@@ -248,11 +261,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 // chain of the result LAG places back.  The next row block's fragments are read at the start of
                 // a row block.
                 f32x4 k4[2];
-                k4[0] = start_of(fa[0]);
+                k4[0] = start_of(sp, c, 0, fa[0]);
 #pragma unroll
                 for (int i = 0; i < RT; ++i) {
                     if (i + 1 < RT) read_a(gp, i + 1, fa[(i + 1) & 1]);
                     else if (c + 1 < CH) read_a(gp + AST, 0, fa[0]);
+                    if (STARTS && i + 1 < RT) k4[(i + 1) & 1] = start_of(sp, c, i + 1, fa[0]);
 #pragma unroll
                     for (int j = 0; j < CT; ++j) {
                         __builtin_amdgcn_sched_barrier(0);
@@ -262,7 +276,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                         if (t < LAG) scale_in(T - LAG + t, pend[t], pscale[t]);
                         else scale_in(t - LAG, pend[t % LAG], sc[(t - LAG) % CT]);
                         pend[t % LAG] = a;
-                        if (j == CT - 1 && i + 1 < RT) k4[(i + 1) & 1] = start_of(fa[(i + 1) & 1]);
+                        if (!STARTS && j == CT - 1 && i + 1 < RT) k4[(i + 1) & 1] = start_of(sp, c, i + 1, fa[(i + 1) & 1]);
 #pragma unroll
                         for (int k = 0; k < (SP ? LOADS : 0); ++k)
                             if (k * (CH * T * SP / 8) / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1);
@@ -419,7 +433,7 @@ const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128,
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
 
-template <bool P, bool QK>
+template <ActFormat P, bool QK>
 f8_kernel tile_kernel(int v)
 {
     switch (v) {
@@ -520,7 +534,7 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
         return gemm_16_rows_at_a_time(qa8, QUOTA_ROWS16_A8, quota_a8_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
                                       (const f16 *)residual_opt, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
-    return launch_f8(tile_kernel<false, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
+    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, false>(v) : tile_kernel<A8, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
 }
 
@@ -542,7 +556,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (acc_i32_opt) {
         quota_weights Wi = *W;
         if (!dwords) Wi.scales = W->packed;      // (the integer sums need no scales: any readable ones do)
-        const int rc = launch_f8(F8_TILE_1(true, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, &Wi, dwords ? y : nullptr, ldy,
+        const int rc = launch_f8(F8_TILE_1(PACKED_INT4, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, &Wi, dwords ? y : nullptr, ldy,
                                  res, ldr, acc_i32_opt, st);
         if (rc != QUOTA_OK || dwords || !y) return rc;
     }
@@ -550,7 +564,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (M <= 16)            // the decode step: stream the weights once
         return quota_internal_rows16(qa, QUOTA_ROWS16_PACKED, sa, M, W, y, ldy, res, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
-    return launch_f8(tile_kernel<true, false>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
+    return launch_f8(tile_kernel<PACKED_INT4, false>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
 // QKV projection with the RoPE + 4-bit K/V quantizer fused into the epilogue (see the kernel).
@@ -570,6 +584,6 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, con
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
     const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128);
-    return launch_f8(tile_kernel<false, true>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
+    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, true>(v) : tile_kernel<A8, true>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
                      nullptr, st, qe);
 }

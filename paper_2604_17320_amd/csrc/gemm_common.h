@@ -24,15 +24,6 @@ __device__ __forceinline__ void codes_to_e4m3(const uint4 &v, uint4 &e0, uint4 &
     e1 = make_uint4(e[4], e[5], e[6], e[7]);
 }
 
-// XCD-aware tile id: consecutive dispatch ids go round-robin over the 8 XCDs
-// (each with its own L2), so give each XCD a contiguous range of tiles.
-__device__ __forceinline__ int xcd_remap(int pid, int total)
-{
-    int x = pid & 7, idx = pid >> 3;
-    int per = total >> 3, rem = total & 7;
-    return x * per + (x < rem ? x : rem) + idx;
-}
-
 // Tile order inside an XCD's range: bands of 8 row tiles, column by column, so that the 64 or so workgroups
 // an XCD runs at a time cover about 8 x 8 tiles and share their operands in its L2 (row tiles first
 // would give every workgroup its own activations: at 11264 rows that cost 2x in traffic beyond L2).

@@ -60,8 +60,16 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, con
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st);
 
 // The layer's row quantizers and GEMM on activations in the A8 format (gemm.hip): M rows of
-// quota_a8_row_bytes(K) bytes.
+// quota_a8_row_bytes(K) bytes, then, if quota_a8_starts(M), [groups][M] floats, quota_a8_bytes in all.
 inline size_t quota_a8_row_bytes(int K) { return ((((size_t)K + 127) / 128) | 1) * 128; }
+// The sums cost the quantizers more than the GEMMs gain where those wait for memory anyway.  A 7B layer with and
+// without: all its products at 160 to 237 rows 147.0 and 146.1 us, first product at 640 rows 188.9 and 189.8,
+// 11264 and 5808 rows 1609 and 1656.
+inline bool quota_a8_starts(size_t M) { return M >= 512; }
+inline size_t quota_a8_bytes(size_t M, int K)
+{
+    return M * (quota_a8_row_bytes(K) + (quota_a8_starts(M) ? ((size_t)K + 127) / 128 * sizeof(float) : 0));
+}
 int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa8,
                                        float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st);
 int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *scale, void *z_opt,

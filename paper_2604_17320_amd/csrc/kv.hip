@@ -162,18 +162,24 @@ __global__ __launch_bounds__(256) void kv_quant_append_kernel(
 // of a thread that do not depend on each other are issued together (unconditional, at clamped
 // indices): after the one dependent step -- the kept index, then the rows it names -- the kernel
 // needs a single memory round trip.
-template <int NCH>
+template <int NCH, typename OUT>
 __global__ __launch_bounds__(256) void compact_rows_kernel(
     int N, int vis_begin, int Nv, int k_keep, int n_keep, const int32_t *__restrict__ keep_idx,
     int d, int dkv, const f16 *__restrict__ x, const f16 *__restrict__ o, const int32_t *__restrict__ pos,
     const uint32_t *__restrict__ skc, const f16 *__restrict__ sks, const uint32_t *__restrict__ svc,
     const f16 *__restrict__ svs, f16 *__restrict__ x_out, f16 *__restrict__ o_out,
-    RowOutA8 oq_out, float *__restrict__ os_out,
+    OUT oq_out, float *__restrict__ os_out,
     int32_t *__restrict__ pos_out, int32_t *__restrict__ rows_out, int capacity, int len,
     uint32_t *__restrict__ ckc, f16 *__restrict__ cks, uint32_t *__restrict__ cvc,
     f16 *__restrict__ cvs)
 {
-    const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+    int j = blockIdx.x, b = blockIdx.y;
+    if (OUT::STARTS) {
+        const int wg = row_wg<OUT>(b * n_keep + j, n_keep * gridDim.y);
+        b = wg / n_keep;
+        j = wg - b * n_keep;
+    }
+    const int tid = threadIdx.x;
     int src;
     if (j < vis_begin) src = j;
     else if (j < vis_begin + k_keep) src = vis_begin + (keep_idx ? keep_idx[(size_t)b * k_keep + (j - vis_begin)] : j - vis_begin);
@@ -250,13 +256,21 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
     if (a->n_keep == 0) return QUOTA_OK;
     const double rows = (double)a->n_keep * a->B, dd = a->d, dk = a->dkv;
     ProfScope prof(QUOTA_K_COMPACT_ROWS, 0, rows * (2 * (4 * dd + dk + dk / 16) + 8), st);
-    auto kernel = a->d <= 4096 ? compact_rows_kernel<2> : compact_rows_kernel<8>;
-    kernel<<<dim3(a->n_keep, a->B), dim3(256), 0, st>>>(
-        a->N, a->vis_begin, a->Nv, a->k_keep, a->n_keep, a->keep_idx, a->d, a->dkv, (const f16 *)a->x,
-        (const f16 *)a->o, a->pos, (const uint32_t *)a->skc, (const f16 *)a->sks, (const uint32_t *)a->svc,
-        (const f16 *)a->svs, (f16 *)a->x_out, (f16 *)a->o_out, RowOutA8{(uint2 *)a->oq_out}, a->os_out, a->pos_out,
-        a->rows_out, c->capacity, c->len, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,
-        (f16 *)c->v_scales);
+    const auto launch = [&](auto kernel, auto out) {
+        kernel<<<dim3(a->n_keep, a->B), dim3(256), 0, st>>>(
+            a->N, a->vis_begin, a->Nv, a->k_keep, a->n_keep, a->keep_idx, a->d, a->dkv, (const f16 *)a->x,
+            (const f16 *)a->o, a->pos, (const uint32_t *)a->skc, (const f16 *)a->sks, (const uint32_t *)a->svc,
+            (const f16 *)a->svs, (f16 *)a->x_out, (f16 *)a->o_out, out, a->os_out, a->pos_out,
+            a->rows_out, c->capacity, c->len, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,
+            (f16 *)c->v_scales);
+    };
+    const int M = a->n_keep * a->B;
+    typedef RowOutA8<false> Rows;
+    typedef RowOutA8<true> RowsStarts;
+    if (quota_a8_starts(M))
+        launch(a->d <= 4096 ? compact_rows_kernel<2, RowsStarts> : compact_rows_kernel<8, RowsStarts>, RowsStarts{(uint2 *)a->oq_out, M});
+    else
+        launch(a->d <= 4096 ? compact_rows_kernel<2, Rows> : compact_rows_kernel<8, Rows>, Rows{(uint2 *)a->oq_out, M});
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;         // the caller advances cache->len once the whole layer is enqueued
 }

@@ -199,7 +199,7 @@ __device__ __forceinline__ void group_reduce(float &mx, double &s0, double &s1, 
 #define ROW_PROLOGUE()                                                                         \
     __shared__ double sm[12];                                                                  \
     const int lane = threadIdx.x % GROUP;                                                      \
-    const int row = blockIdx.x * (ROW_THREADS / GROUP) + threadIdx.x / GROUP;                  \
+    const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (ROW_THREADS / GROUP) + threadIdx.x / GROUP; \
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
     (void)sm
 
@@ -544,8 +544,8 @@ int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const fl
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, RowOutA8{(uint2 *)qa8}, scale, sumsq_opt, ressq_opt,
-                            nullptr, st);
+    const auto run = [&](auto out) { return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, out, scale, sumsq_opt, ressq_opt, nullptr, st); };
+    return quota_a8_starts(M) ? run(RowOutA8<true>{(uint2 *)qa8, M}) : run(RowOutA8<false>{(uint2 *)qa8, M});
 }
 
 template <typename OUT>
@@ -590,7 +590,8 @@ int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_
     int rc = check_rows(gu_f16, M, F, F, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    return silu_mul_quantize(gu_f16, M, F, RowOutA8{(uint2 *)qa8}, scale, z_opt, z_inject_opt, st);
+    const auto run = [&](auto out) { return silu_mul_quantize(gu_f16, M, F, out, scale, z_opt, z_inject_opt, st); };
+    return quota_a8_starts(M) ? run(RowOutA8<true>{(uint2 *)qa8, M}) : run(RowOutA8<false>{(uint2 *)qa8, M});
 }
 
 template <typename OUT>
@@ -610,7 +611,8 @@ int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, fl
 {
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK || M == 0) return rc;
-    return quantize_rows(x_f16, M, d, RowOutA8{(uint2 *)qa8}, scale, st);
+    const auto run = [&](auto out) { return quantize_rows(x_f16, M, d, out, scale, st); };
+    return quota_a8_starts(M) ? run(RowOutA8<true>{(uint2 *)qa8, M}) : run(RowOutA8<false>{(uint2 *)qa8, M});
 }
 
 // The three quantizers of at most 16 rows into the few-row GEMM's fragments.

@@ -9,32 +9,45 @@
 #define ROW_MAXCOLS 32768
 
 // Where a quantized row goes: packed int4 (the public format, two codes per byte), the GEMM's A8 format --
-// e4m3 bytes, every 8 codes as evens then odds, each row zero-padded to whole 128-channel groups -- or, for at
+// e4m3 bytes, every 8 codes as evens then odds, each row zero-padded to whole 128-channel groups, and behind the rows
+// (if quota_a8_starts) what a sum of products with weights c + 8 starts from, [group][row] -- or, for at
 // most 16 rows, packed int4 as the few-row GEMM's fragments: 1 KB per group, the 32 codes number q of row m's
 // 128 at 16-byte piece 16 q + m.  A null pointer drops the output.
 struct RowOutPacked {
-    static constexpr bool A8 = false;
+    static constexpr bool A8 = false, STARTS = false;
     uint32_t *q;
     static __device__ __forceinline__ int at(int c) { return c; }
 };
 struct RowOutFrag {
-    static constexpr bool A8 = false;
+    static constexpr bool A8 = false, STARTS = false;
     uint32_t *q;
     static __device__ __forceinline__ int at(int c) { return (c >> 4) * 256 + (c >> 2 & 3) * 64 + (c & 3); }
 };
+template <bool S>
 struct RowOutA8 {
-    static constexpr bool A8 = true;
+    static constexpr bool A8 = true, STARTS = S;
     uint2 *q;
+    int rows;            // of the launch
+    float *starts;       // of this row
 };
+// The row (or rows) that workgroup `wg` takes: with start values, 4 bytes per row and group, neighbouring rows belong on one XCD, whose L2
+// puts them together (5808 rows and 11008 columns: 0.4 % of a layer's time).
+template <typename OUT>
+__device__ __forceinline__ int row_wg(int wg, int wgs)
+{
+    if constexpr (OUT::STARTS) return xcd_remap(wg, wgs);
+    return wg;
+}
 __host__ __device__ __forceinline__ RowOutPacked row_out(RowOutPacked o, size_t row, int nchunk)
 {
     return RowOutPacked{o.q ? o.q + row * nchunk : nullptr};
 }
 __host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row, int) { return RowOutFrag{o.q + 4 * row}; }
-__host__ __device__ __forceinline__ RowOutA8 row_out(RowOutA8 o, size_t row, int nchunk)
+template <bool S>
+__host__ __device__ __forceinline__ RowOutA8<S> row_out(RowOutA8<S> o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
-    return RowOutA8{o.q + row * (G | 1) * 16};
+    return RowOutA8<S>{o.q + row * (G | 1) * 16, o.rows, reinterpret_cast<float *>(o.q + (size_t)o.rows * (G | 1) * 16) + row};
 }
 
 // final phase shared by the row kernels: quantize the cached row `v` with absmax `a`, store the
@@ -72,6 +85,11 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
             }
             if constexpr (OUT::A8) {
                 out.q[c] = units_to_e4m3(unit);
+                if constexpr (OUT::STARTS) {         // the 16 lanes of a group add up in its last one
+                    float u = ((unit[0] + unit[1]) + (unit[2] + unit[3])) + ((unit[4] + unit[5]) + (unit[6] + unit[7]));
+                    u = row16_sum(u);
+                    if ((c & 15) == 15) out.starts[(size_t)(c >> 4) * out.rows] = u * (-8.0f / 512.0f);
+                }
             } else {
                 if (out.q) out.q[OUT::at(c)] = word;
             }

@@ -352,6 +352,21 @@ def test_layer_every_tile_with_fused_qkv_epilogue(qb, tile, pinned_gemm):
     assert_teacher_forced_exact(ref, got, shape, K)
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("Nv,Nt,K", [(500, 13, 499), (560, 17, 494)], ids=["513_to_512", "577_to_511"])
+def test_layer_start_values_from_the_quantizer(qb, tile, Nv, Nt, K, pinned_gemm):
+    """From 512 rows on the quantizers write the group sums' start values and the tiles read them: rows that end inside
+    a tile, a last group of 96 channels, and a layer that falls below the line by pruning; teacher-forced bit-exact."""
+    pinned_gemm(tile)
+    base = wl.CONFIGS[0]
+    shape = wl.Shape("starts", d=base.d, H=base.H, F=1376, layers=1, B=1, Nv=Nv, Nt=Nt, n_outlier=base.n_outlier, vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 6, gamma_random=True)
+    x, pos = wl.hidden_state(shape, 6), wl.positions(shape)
+    ref = oracle.prefill_layer(W, x, pos, 1, shape.N, 0, Nv, K, cos, sin, prune_mid=True)
+    got = run_gpu(qb, L, shape, x, pos, K, dict(o=ref["o"], z=ref["z"], cm_inter=ref["cm_inter"], cm_intra=ref["cm_intra"]))
+    assert_teacher_forced_exact(ref, got, shape, K)
+
+
 def test_layer_with_weight_scales_at_an_odd_halfword(qb):
     """Weight scales that start between two dwords: a prefill layer and its decode-sized remainder give the bits of the
     aligned layer (the fused QKV epilogue and the tiles step aside)."""
