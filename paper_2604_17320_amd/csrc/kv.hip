@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void kv_quant_append_kernel(
 // kept rows of the hidden state and the positions, moves their staged 4-bit
 // K/V rows into the layer's cache, and gathers the attention-output row --
 // copied (o_out) and/or quantized for the output projection (oq_out, os_out).
-// NCH = 16-byte chunks of a row per thread (2 covers 4096 columns, 8 covers 16384).  All loads
+// NCH = 16-byte chunks of a row per thread (2 covers 4096 columns, 4 8192, 8 16384).  All loads
 // of a thread that do not depend on each other are issued together (unconditional, at clamped
 // indices): after the one dependent step -- the kept index, then the rows it names -- the kernel
 // needs a single memory round trip.
@@ -256,7 +256,11 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
     if (a->n_keep == 0) return QUOTA_OK;
     const double rows = (double)a->n_keep * a->B, dd = a->d, dk = a->dkv;
     ProfScope prof(QUOTA_K_COMPACT_ROWS, 0, rows * (2 * (4 * dd + dk + dk / 16) + 8), st);
-    const auto launch = [&](auto kernel, auto out) {
+    const int M = a->n_keep * a->B;
+    const auto launch = [&](auto out) {
+        typedef decltype(out) OUT;
+        auto kernel = a->d <= 4096 ? compact_rows_kernel<2, OUT> : a->d <= 8192 ? compact_rows_kernel<4, OUT>
+                                                                                : compact_rows_kernel<8, OUT>;
         kernel<<<dim3(a->n_keep, a->B), dim3(256), 0, st>>>(
             a->N, a->vis_begin, a->Nv, a->k_keep, a->n_keep, a->keep_idx, a->d, a->dkv, (const f16 *)a->x,
             (const f16 *)a->o, a->pos, (const uint32_t *)a->skc, (const f16 *)a->sks, (const uint32_t *)a->svc,
@@ -264,13 +268,8 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
             a->rows_out, c->capacity, c->len, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,
             (f16 *)c->v_scales);
     };
-    const int M = a->n_keep * a->B;
-    typedef RowOutA8<false> Rows;
-    typedef RowOutA8<true> RowsStarts;
-    if (quota_a8_starts(M))
-        launch(a->d <= 4096 ? compact_rows_kernel<2, RowsStarts> : compact_rows_kernel<8, RowsStarts>, RowsStarts{(uint2 *)a->oq_out, M});
-    else
-        launch(a->d <= 4096 ? compact_rows_kernel<2, Rows> : compact_rows_kernel<8, Rows>, Rows{(uint2 *)a->oq_out, M});
+    if (quota_a8_starts(M)) launch(RowOutA8<true>{(uint2 *)a->oq_out, M});
+    else launch(RowOutA8<false>{(uint2 *)a->oq_out, M});
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;         // the caller advances cache->len once the whole layer is enqueued
 }

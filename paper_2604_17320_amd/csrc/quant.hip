@@ -1,10 +1,12 @@
 // Quantizers of the W4A4 execution form: weight group quantizer + repack,
 // per-token int4 activation quantizer (the Q of Eq. 6) and its fused variants
 // (RMSNorm in front of QKV / gate-up, SwiGLU product in front of down).
-// All are row kernels: in launches of 2048 rows and more of up to 4096 columns one wave per row
+// All are row kernels: in launches of 2048 rows and more of up to 6144 columns one wave per row
 // (four rows per workgroup), else one workgroup per row; the row is cached in registers as
 // 16-byte chunks, absmax / sums of squares are wave or block reductions, 8 codes are stored per
 // chunk: a packed dword, or 8 e4m3 bytes for the GEMM.  HBM-bound by design.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 #include "rowquant.h"
@@ -180,9 +182,9 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
 
 // ------------------------------------------------- activation quantizers
 
-// A row is owned by GROUP threads, each caching NCH chunks (2, 8 or 16).  Every load of a thread is
+// A row is owned by GROUP threads, each caching NCH chunks (2 to 16).  Every load of a thread is
 // issued before the first use (unconditional loads at clamped indices instead of guarded ones, so
-// that nothing separates them): one memory round trip per kernel.  GROUP = 64 (rows of up to 4096
+// that nothing separates them): one memory round trip per kernel.  GROUP = 64 (rows of up to 6144
 // columns): one WAVE per row, four rows per workgroup -- a lane issues all its 16-byte loads back
 // to back, the reductions are wave shuffles and there is no workgroup barrier.  GROUP = 256 (up to
 // 32768 columns): the whole workgroup owns the row and reduces through LDS.
@@ -390,6 +392,27 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
 
 // ------------------------------------------------------------ host side
 
+// Calls launch(GROUP, NCH, grid) with the smallest cache that holds d columns: a thread's registers are what limits the
+// rows in flight.  RMSNorm quantizer with metrics, 11776 rows of 5120 columns: 61 us with 12 chunks per lane, of which 10
+// are used, 113 with 8 per thread of a workgroup, of which 2.5 are used.
+template <typename LAUNCH>
+static void with_row_shape(int M, int d, LAUNCH launch)
+{
+    const auto go = [&](auto group, auto nch) { launch(group, nch, dim3(group() == 64 ? (M + 3) / 4 : M)); };
+    const std::integral_constant<int, 64> wave;
+    const std::integral_constant<int, 256> workgroup;
+    if (M >= ROW_WAVE_MIN_ROWS && d <= 6144) {
+        if (d <= 64 * 8 * 2) go(wave, std::integral_constant<int, 2>());
+        else if (d <= 64 * 8 * 8) go(wave, std::integral_constant<int, 8>());
+        else go(wave, std::integral_constant<int, 12>());
+    } else {
+        if (d <= 256 * 8 * 2) go(workgroup, std::integral_constant<int, 2>());
+        else if (d <= 256 * 8 * 4) go(workgroup, std::integral_constant<int, 4>());
+        else if (d <= 256 * 8 * 8) go(workgroup, std::integral_constant<int, 8>());
+        else go(workgroup, std::integral_constant<int, 16>());
+    }
+}
+
 extern "C" size_t quota_weights_packed_bytes(int N, int K)
 {
     if (N <= 0 || K <= 0) return 0;
@@ -474,24 +497,12 @@ extern "C" int quota_quantize_act(const void *x_f16, int M, int d, int ldx, uint
     if (M == 0) return QUOTA_OK;
     hipStream_t st = (hipStream_t)stream;
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
-    const bool metrics = sumsq_opt || ressq_opt, small = d <= 4096 && M >= ROW_WAVE_MIN_ROWS;
-    const dim3 grid(small ? (M + 3) / 4 : M), blk(ROW_THREADS);
-    const f16 *x = (const f16 *)x_f16;
-    const RowOutPacked q{(uint32_t *)q_packed};
-    const bool few = (d >> 3) <= 2 * (small ? 64 : 256);      // two chunks per thread are enough
-    const bool many = d > 16384;                              // sixteen chunks per thread
-#define QUOTA_LAUNCH_Q(MET, GRP, NCH) \
-    quantize_act_kernel<MET, GRP, NCH, RowOutPacked><<<grid, blk, 0, st>>>(x, M, d, ldx, M, 0, q, scale, sumsq_opt, ressq_opt)
-    if (metrics) {
-        if (small) { if (few) QUOTA_LAUNCH_Q(true, 64, 2); else QUOTA_LAUNCH_Q(true, 64, 8); }
-        else if (many) QUOTA_LAUNCH_Q(true, 256, 16);
-        else { if (few) QUOTA_LAUNCH_Q(true, 256, 2); else QUOTA_LAUNCH_Q(true, 256, 8); }
-    } else {
-        if (small) { if (few) QUOTA_LAUNCH_Q(false, 64, 2); else QUOTA_LAUNCH_Q(false, 64, 8); }
-        else if (many) QUOTA_LAUNCH_Q(false, 256, 16);
-        else { if (few) QUOTA_LAUNCH_Q(false, 256, 2); else QUOTA_LAUNCH_Q(false, 256, 8); }
-    }
-#undef QUOTA_LAUNCH_Q
+    with_row_shape(M, d, [&](auto group, auto nch, dim3 grid) {
+        auto kernel = sumsq_opt || ressq_opt ? quantize_act_kernel<true, group(), nch(), RowOutPacked>
+                                             : quantize_act_kernel<false, group(), nch(), RowOutPacked>;
+        kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, M, 0, RowOutPacked{(uint32_t *)q_packed},
+                                                   scale, sumsq_opt, ressq_opt);
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -501,25 +512,12 @@ static int rmsnorm_quantize(const void *x_f16, int M, int d, int ldx, const floa
                             float *scale, float *sumsq_opt, float *ressq_opt, void *h_opt, hipStream_t st)
 {
     ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
-    const bool metrics = sumsq_opt || ressq_opt, small = d <= 4096 && M >= ROW_WAVE_MIN_ROWS;
-    const dim3 grid(small ? (M + 3) / 4 : M), blk(ROW_THREADS);
-    const f16 *x = (const f16 *)x_f16;
-    f16 *h = (f16 *)h_opt;
-    const bool few = (d >> 3) <= 2 * (small ? 64 : 256);      // two chunks per thread are enough
-    const bool many = d > 16384;                              // sixteen chunks per thread
-#define QUOTA_LAUNCH_R(MET, GRP, NCH)                                                                       \
-    rmsnorm_quantize_act_kernel<MET, GRP, NCH, OUT><<<grid, blk, 0, st>>>(x, M, d, ldx, gamma, eps, q, scale, \
-                                                                          sumsq_opt, ressq_opt, h)
-    if (metrics) {
-        if (small) { if (few) QUOTA_LAUNCH_R(true, 64, 2); else QUOTA_LAUNCH_R(true, 64, 8); }
-        else if (many) QUOTA_LAUNCH_R(true, 256, 16);
-        else { if (few) QUOTA_LAUNCH_R(true, 256, 2); else QUOTA_LAUNCH_R(true, 256, 8); }
-    } else {
-        if (small) { if (few) QUOTA_LAUNCH_R(false, 64, 2); else QUOTA_LAUNCH_R(false, 64, 8); }
-        else if (many) QUOTA_LAUNCH_R(false, 256, 16);
-        else { if (few) QUOTA_LAUNCH_R(false, 256, 2); else QUOTA_LAUNCH_R(false, 256, 8); }
-    }
-#undef QUOTA_LAUNCH_R
+    with_row_shape(M, d, [&](auto group, auto nch, dim3 grid) {
+        auto kernel = sumsq_opt || ressq_opt ? rmsnorm_quantize_act_kernel<true, group(), nch(), OUT>
+                                             : rmsnorm_quantize_act_kernel<false, group(), nch(), OUT>;
+        kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, gamma, eps, q, scale, sumsq_opt, ressq_opt,
+                                                   (f16 *)h_opt);
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -553,22 +551,12 @@ static int silu_mul_quantize(const void *gu_f16, int M, int F, OUT q, float *sca
                              const void *z_inject_opt, hipStream_t st)
 {
     ProfScope prof(QUOTA_K_SILU_MUL_QUANTIZE_ACT, 0, 4.5 * M * F + 4.0 * M, st);
-    const bool small = F <= 4096 && M >= ROW_WAVE_MIN_ROWS;
-    const dim3 grid(small ? (M + 3) / 4 : M), blk(ROW_THREADS);
-    const bool few = (F >> 3) <= 2 * (small ? 64 : 256);
-    const bool many = F > 16384;          // sixteen chunks per thread, loaded chunk by chunk
-#define QUOTA_LAUNCH_S(GRP, NCH, EARLY)                                              \
-    silu_mul_quantize_act_kernel<GRP, NCH, EARLY, OUT><<<grid, blk, 0, st>>>(        \
-        (const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt)
-    if (many) QUOTA_LAUNCH_S(256, 16, false);
-    else if (M >= ROW_WAVE_MIN_ROWS) {
-        if (small) { if (few) QUOTA_LAUNCH_S(64, 2, false); else QUOTA_LAUNCH_S(64, 8, false); }
-        else { if (few) QUOTA_LAUNCH_S(256, 2, false); else QUOTA_LAUNCH_S(256, 8, false); }
-    } else {
-        if (small) { if (few) QUOTA_LAUNCH_S(64, 2, true); else QUOTA_LAUNCH_S(64, 8, true); }
-        else { if (few) QUOTA_LAUNCH_S(256, 2, true); else QUOTA_LAUNCH_S(256, 8, true); }
-    }
-#undef QUOTA_LAUNCH_S
+    with_row_shape(M, F, [&](auto group, auto nch, dim3 grid) {
+        constexpr bool can_be_early = nch() < 16;
+        auto kernel = can_be_early && M < ROW_WAVE_MIN_ROWS ? silu_mul_quantize_act_kernel<group(), nch(), can_be_early, OUT>
+                                                            : silu_mul_quantize_act_kernel<group(), nch(), false, OUT>;
+        kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt);
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -598,10 +586,10 @@ template <typename OUT>
 static int quantize_rows(const void *x_f16, int M, int d, OUT q, float *scale, hipStream_t st)
 {
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
-    const bool many = d > 16384, few = (d >> 3) <= 512;
-    auto kernel = many ? quantize_act_kernel<false, 256, 16, OUT>
-                       : few ? quantize_act_kernel<false, 256, 2, OUT> : quantize_act_kernel<false, 256, 8, OUT>;
-    kernel<<<dim3(M), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, q, scale, nullptr, nullptr);
+    with_row_shape(M, d, [&](auto group, auto nch, dim3 grid) {
+        quantize_act_kernel<false, group(), nch(), OUT><<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, q,
+                                                                                            scale, nullptr, nullptr);
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -648,16 +636,10 @@ int quota_internal_vector_metrics(const void *v_f16, int B, int Nv, int d, int l
         return QUOTA_ERR_SHAPE;
     if (Nv == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.0 * B * Nv * d + 8.0 * B * Nv, st);
-    const bool small = d <= 4096 && B * Nv >= ROW_WAVE_MIN_ROWS;
-    const dim3 grid(small ? (B * Nv + 3) / 4 : B * Nv), blk(ROW_THREADS);
-    const bool few = (d >> 3) <= 2 * (small ? 64 : 256);
-#define QUOTA_LAUNCH_V(GRP, NCH)                                                                           \
-    quantize_act_kernel<true, GRP, NCH, RowOutPacked><<<grid, blk, 0, st>>>(                               \
-        (const f16 *)v_f16, B * Nv, d, ldv, Nv, stride_b, RowOutPacked{nullptr}, nullptr, sumsq, ressq)
-    if (small) { if (few) QUOTA_LAUNCH_V(64, 2); else QUOTA_LAUNCH_V(64, 8); }
-    else if (d > 16384) QUOTA_LAUNCH_V(256, 16);
-    else { if (few) QUOTA_LAUNCH_V(256, 2); else QUOTA_LAUNCH_V(256, 8); }
-#undef QUOTA_LAUNCH_V
+    with_row_shape(B * Nv, d, [&](auto group, auto nch, dim3 grid) {
+        quantize_act_kernel<true, group(), nch(), RowOutPacked><<<grid, dim3(ROW_THREADS), 0, st>>>(
+            (const f16 *)v_f16, B * Nv, d, ldv, Nv, stride_b, RowOutPacked{nullptr}, nullptr, sumsq, ressq);
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

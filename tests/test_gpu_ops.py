@@ -173,6 +173,15 @@ def test_silu_mul_quantize_act(qb, M, F):
     assert np.array_equal(unpack4(host(qp)), q) and np.array_equal(host(sc), s)
 
 
+@pytest.mark.parametrize("M,d", [(2047, 6144), (2048, 6144), (2049, 6160), (2050, 4112), (2048, 1040), (4, 8192), (4, 8208)])
+def test_row_kernels_at_the_edges_of_their_caches(qb, M, d):
+    """Rows that just fill, and just miss, each register cache of a wave or workgroup, on both sides of the row count
+    that tells them apart."""
+    test_quantize_act_bit_exact(qb, M, d)
+    test_rmsnorm_quantize_act(qb, M, d)
+    test_silu_mul_quantize_act(qb, M, d)
+
+
 # ------------------------------------------------------------------ GEMM
 def _gemm_case(M, N, K, seed):
     r = wl.rng(seed, "gemm", M, N, K)
