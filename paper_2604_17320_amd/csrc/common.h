@@ -127,6 +127,14 @@ __device__ __forceinline__ f16 to_f16(float v)
     return (f16)v;
 }
 
+// silu(gate) * up, silu(g) = g / (1 + e^-g) with the hardware exp2 and reciprocal (a few fp32 ulp, far inside the fp16
+// rounding that follows)
+__device__ __forceinline__ f16 silu_mul(float gate, float up)
+{
+    const float s = gate * __builtin_amdgcn_rcpf(1.0f + __expf(-gate));
+    return to_f16(s * up);
+}
+
 // int4 code from a rounded fp32 value: clamp to [-8, 7]
 __device__ __forceinline__ int code_from(float r)
 {

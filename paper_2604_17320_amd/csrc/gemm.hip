@@ -53,7 +53,8 @@ namespace {
 // do not share banks (a CU with 8 waves reading takes 3.9 ns per read instruction so, 3.3 from consecutive
 // addresses, 13.4 unpermuted).
 enum ActFormat { A8, A8_STARTS, PACKED_INT4 };
-template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, bool QKV, int OCC>
+enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL };
+template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
@@ -61,7 +62,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     int vec_store, quota_qkv_epilogue qe)
 {
     constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
-    constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A8_STARTS;
+    constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A8_STARTS, QKV = EPI == QKV_ROPE_KV, SILU = EPI == SILU_MUL;
+    static_assert(!SILU || (CT % 2 == 0 && !ACC_OUT), "as many blocks of gate as of up columns");
     constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : BM * 8 / NT;    // 16-byte pieces per thread and group
     // dwords per stage, 64 to a copy: the group scales, then (STARTS) the rows' start values
     constexpr int SCOPY = CH * BN / 128, ICOPY = STARTS ? CH * BM / 64 : 0, KD = (SCOPY + ICOPY + NW - 1) / NW;
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     // then the dwords, up to whole waves
     constexpr int AST = BM * 8 + (PACKED ? 2 : 0), GST = CH * AST, STG = GST + KD * NT / 4;
     constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
-    constexpr int LDS_A = 2 * STG, LDS_Q = QKV ? 32 * TROW / 8 : 32 * FROW / 4;
+    constexpr int LDS_A = 2 * STG, LDS_Q = QKV || SILU ? 32 * TROW / 8 : 32 * FROW / 4;
     __shared__ uint4 lds_raw[LDS_A > LDS_Q ? LDS_A : LDS_Q];
     const unsigned lds0 = lds_address(lds_raw);
 
@@ -95,9 +97,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         pa[j] = 16 * p;
         la[j] = row < BM ? row * 8 + ((2 * p) ^ (row & 7)) : BM * 8;
     }
-    const int nw = min(n0 + wave * WN, N - WN);          // this wave's first column (N is a multiple of 64)
+    // SILU: columns are gate | up, F = N / 2 of each, and a tile takes BN / 2 of either: a wave's first CT / 2 blocks are gate
+    // columns, the others up columns of the same channels.
+    constexpr int WC = SILU ? WN / 2 : WN, BC = SILU ? BN / 2 : BN, CB = WC / 16;       // neighbouring columns of a wave, of a tile
+    const int NC = SILU ? N >> 1 : N, nc0 = tile_n * BC;
+    const int nw = min(nc0 + wave * WC, NC - WC);        // this wave's first column (N is a multiple of 64)
     const bool n_ok = n0 + wave * WN < N;
-    const unsigned wl = (unsigned)(c16 * 4 + q);         // this lane's uint4 of a 16-column block
+    // this lane's uint4 of a wave's first 16-column block, and of its first block of up columns
+    const unsigned wl = (unsigned)(c16 * 4 + q), wl_up = wl + (unsigned)NC * 4;
     // dword tid + NT k of a stage: the scales of two neighbouring columns, or the start value of a row, in one of its groups
     const float *starts = reinterpret_cast<const float *>(qa + (size_t)M * Kb);
     unsigned os[KD];
@@ -107,7 +114,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         const bool scale = !STARTS || wave + NW * k < SCOPY;
         const int d = scale ? min(tid + NT * k, CH * BN / 2 - 1) : min(tid + NT * k - 64 * SCOPY, CH * BM - 1);
         gs[k] = scale ? d / (BN / 2) : d / BM;
-        os[k] = 4u * (unsigned)(scale ? min((n0 >> 1) + d % (BN / 2), (N >> 1) - 1) : min(m0 + d % BM, M - 1));
+        int pair = d % (BN / 2), first = 0;              // pair of columns: in its run of neighbouring ones, and the run's first
+        if (SILU) {
+            first = pair / (WC / 2) % 2 * (NC >> 1);
+            pair = pair / WC * (WC / 2) + pair % (WC / 2);
+        }
+        os[k] = 4u * (unsigned)(scale ? first + min((nc0 >> 1) + pair, (NC >> 1) - 1) : min(m0 + d % BM, M - 1));
     }
 
     constexpr int WS = CH > 1 ? 2 : 1;                   // register sets of packed weights = stages per loop body
@@ -125,7 +137,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         if (k < CH * LG) {
             const int c = k / LG, r = k % LG;
             if (r < CT) {
-                rw[set][c][r] = wnext[wl + 64 * r];
+                rw[set][c][r] = wnext[(r < CB ? wl : wl_up) + 64 * (r % CB)];
             } else {
                 const int j = r - CT;
                 if constexpr (PACKED) {
@@ -367,6 +379,37 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         }
         return;
     }
+    if constexpr (SILU) {
+        // Gate and up of a channel lie in the same lane: the product, of their fp16 roundings, is made in registers
+        // and only it is stored (5808 x 22016 x 4096: 403 us, 427 with gate | up stored, and the quantizer behind it,
+        // which reads half as much, 34 instead of 60).
+        constexpr int ZROW = BC + 8;
+        f16 *stage = reinterpret_cast<f16 *>(lds_raw);
+#pragma unroll
+        for (int ib = 0; ib < RT / 2; ++ib) {
+            if (ib) __syncthreads();                  // the previous 32 rows have been read
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * h + 4 * q + r, m = m0 + 32 * ib + row;
+                    const float sam = sa[m < M ? m : M - 1] * F8_UNIT;
+                    f16 *p = stage + row * ZROW + wave * WC + c16;
+#pragma unroll
+                    for (int j = 0; j < CB; ++j)
+                        p[16 * j] = silu_mul((float)to_f16(yacc[2 * ib + h][j][r] * sam),
+                                             (float)to_f16(yacc[2 * ib + h][j + CB][r] * sam));
+                }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 32 * (BC / 8) / NT; ++k) {
+                const int idx = k * NT + tid, row = idx / (BC / 8), n = nc0 + 8 * (idx % (BC / 8)), m = m0 + 32 * ib + row;
+                const uint4 z = *reinterpret_cast<const uint4 *>(stage + row * ZROW + 8 * (idx % (BC / 8)));
+                if (m < M && n < NC) *reinterpret_cast<uint4 *>(y + (size_t)m * ldy + n) = z;
+            }
+        }
+        return;
+    }
     // 32 rows at a time through LDS as fp32, so that a thread finishes 8 neighbouring columns of a row: one
     // 16-byte residual load, one 16-byte store
     float *stage = reinterpret_cast<float *>(lds_raw);
@@ -419,11 +462,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
 //                                            RT CT NW CH SP          OCC
-#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>  // 64 x 256
-#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, P, A, QK, 2>  // 64 x 128
-#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, QK, 2>  // 32 x 128
-#define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
-#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
+#define F8_TILE_0(P, A, E) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, E, 2>  // 64 x 256
+#define F8_TILE_1(P, A, E) w4a4_f8_kernel<4, 4, 2, 2, 6, P, A, E, 2>  // 64 x 128
+#define F8_TILE_2(P, A, E) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, E, 2>  // 32 x 128
+#define F8_TILE_3(P, A, E) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, E, 2>  // 32 x 64
+#define F8_TILE_4(P, A, E) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, E, 2>  // 128 x 256
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128, QUOTA_K_GEMM_64X128},
@@ -433,15 +476,17 @@ const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128,
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
 
-template <ActFormat P, bool QK>
+template <ActFormat P, Epilogue E>
 f8_kernel tile_kernel(int v)
 {
     switch (v) {
-    case 0: return F8_TILE_0(P, false, QK);
-    case 1: return F8_TILE_1(P, false, QK);
-    case 2: return F8_TILE_2(P, false, QK);
-    case 3: return F8_TILE_3(P, false, QK);
-    default: return F8_TILE_4(P, false, QK);
+    case 0: return F8_TILE_0(P, false, E);
+    case 1: return F8_TILE_1(P, false, E);
+    case 2: return F8_TILE_2(P, false, E);
+    case 3:
+        if constexpr (E == SILU_MUL) return nullptr;         // (one block of columns per wave: never chosen)
+        else return F8_TILE_3(P, false, E);
+    default: return F8_TILE_4(P, false, E);
     }
 }
 
@@ -534,8 +579,24 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
         return gemm_16_rows_at_a_time(qa8, QUOTA_ROWS16_A8, quota_a8_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
                                       (const f16 *)residual_opt, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
-    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, false>(v) : tile_kernel<A8, false>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
+    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, PLAIN>(v) : tile_kernel<A8, PLAIN>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
+}
+
+// Gate/up projection with SiLU(gate) * up in the epilogue: z [M][N / 2], the bits of the plain projection and the
+// stand-alone product.  Returns QUOTA_ERR_SHAPE when the fused form does not fit (the caller then runs the two kernels
+// separately): with unaligned scales, or where the tile of choice has one block of columns per wave (projections
+// that leave the chip part idle, 37 x 2752 x 512: 4 us each way).
+int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *z_f16,
+                                  hipStream_t st)
+{
+    if (!qa8 || !sa || !W || !W->packed || !W->scales || !z_f16) return QUOTA_ERR_NULL;
+    if (M <= 16 || W->N % 64 != 0 || W->K % 32 != 0 || !scales_on_dwords(W) || (reinterpret_cast<uintptr_t>(z_f16) & 15))
+        return QUOTA_ERR_SHAPE;
+    const int v = choose_tile(M, W->N, W->K, 0, 256);
+    if (kTiles[v].bn < 128) return QUOTA_ERR_SHAPE;
+    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, SILU_MUL>(v) : tile_kernel<A8, SILU_MUL>(v), v, kTiles[v].kernel_id,
+                     qa8, sa, M, W, (f16 *)z_f16, W->N / 2, nullptr, 0, nullptr, st);
 }
 
 extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const quota_weights *W,
@@ -556,7 +617,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (acc_i32_opt) {
         quota_weights Wi = *W;
         if (!dwords) Wi.scales = W->packed;      // (the integer sums need no scales: any readable ones do)
-        const int rc = launch_f8(F8_TILE_1(PACKED_INT4, true, false), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, &Wi, dwords ? y : nullptr, ldy,
+        const int rc = launch_f8(F8_TILE_1(PACKED_INT4, true, PLAIN), 1, QUOTA_K_GEMM_OTHER, qa, sa, M, &Wi, dwords ? y : nullptr, ldy,
                                  res, ldr, acc_i32_opt, st);
         if (rc != QUOTA_OK || dwords || !y) return rc;
     }
@@ -564,7 +625,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (M <= 16)            // the decode step: stream the weights once
         return quota_internal_rows16(qa, QUOTA_ROWS16_PACKED, sa, M, W, y, ldy, res, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256);
-    return launch_f8(tile_kernel<PACKED_INT4, false>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
+    return launch_f8(tile_kernel<PACKED_INT4, PLAIN>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
 // QKV projection with the RoPE + 4-bit K/V quantizer fused into the epilogue (see the kernel).
@@ -584,6 +645,6 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, con
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
     const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128);
-    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, true>(v) : tile_kernel<A8, true>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
+    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, QKV_ROPE_KV>(v) : tile_kernel<A8, QKV_ROPE_KV>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
                      nullptr, st, qe);
 }

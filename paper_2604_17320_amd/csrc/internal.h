@@ -77,6 +77,7 @@ int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_
 int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st);
 int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *y_f16, int ldy,
                                 const void *residual_opt, int ldr, hipStream_t st);
+int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *z_f16, hipStream_t st);
 
 // GEMM of at most 16 rows (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
 // quota_internal_rows16_quantizes accepts: as they are, through RMSNorm, or gate | up rows through SwiGLU.

@@ -256,8 +256,7 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
     if (a->n_keep == 0) return QUOTA_OK;
     const double rows = (double)a->n_keep * a->B, dd = a->d, dk = a->dkv;
     ProfScope prof(QUOTA_K_COMPACT_ROWS, 0, rows * (2 * (4 * dd + dk + dk / 16) + 8), st);
-    const int M = a->n_keep * a->B;
-    const auto launch = [&](auto out) {
+    with_a8_out(a->oq_out, a->n_keep * a->B, [&](auto out) {
         typedef decltype(out) OUT;
         auto kernel = a->d <= 4096 ? compact_rows_kernel<2, OUT> : a->d <= 8192 ? compact_rows_kernel<4, OUT>
                                                                                 : compact_rows_kernel<8, OUT>;
@@ -267,9 +266,8 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
             (const f16 *)a->svs, (f16 *)a->x_out, (f16 *)a->o_out, out, a->os_out, a->pos_out,
             a->rows_out, c->capacity, c->len, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,
             (f16 *)c->v_scales);
-    };
-    if (quota_a8_starts(M)) launch(RowOutA8<true>{(uint2 *)a->oq_out, M});
-    else launch(RowOutA8<false>{(uint2 *)a->oq_out, M});
+        return QUOTA_OK;
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;         // the caller advances cache->len once the whole layer is enqueued
 }

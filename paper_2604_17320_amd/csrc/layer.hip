@@ -151,6 +151,23 @@ static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const qu
     TRY(quota_internal_quantize_a8(x, M, d, w.qa, w.sa, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
+// The SwiGLU block on rows x1, added to them: RMSNorm, quantizer, gate/up, SiLU product, quantizer, down.  Without taps that
+// want the gate | up rows or z, the gate/up projection makes the product itself and w.gu holds z.
+static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1, const quota_taps *t, void *x_out, hipStream_t st)
+{
+    const int d = L->H * L->dh, F = L->F;
+    if (M > ROWS_FRAG && !t->gu && !t->z && !t->inject_z) {
+        TRY(quota_internal_rmsnorm_quantize_a8(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st));
+        const int rc = quota_internal_w4a4_gemm_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
+        if (rc == QUOTA_OK) return quantize_gemm(w, w.gu, M, F, &L->down, x_out, d, x1, d, st);
+        if (rc != QUOTA_ERR_SHAPE) return rc;
+        TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->gu, w.gu, 2 * F, nullptr, 0, st));
+    } else {
+        TRY(rmsnorm_gemm(w, x1, M, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
+        TRY(dump(t->gu, w.gu, (size_t)M * 2 * F * 2, st));
+    }
+    return silu_mul_gemm(w, M, F, t->z, t->inject_z, &L->down, x_out, d, x1, d, st);
+}
 
 extern "C" size_t quota_prefill_workspace_bytes(const quota_layer *L, int B, int N)
 {
@@ -252,9 +269,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     if (Mk > 0) {
         TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, Mk, &L->o, w.x1, d, w.x_keep, d, st));
         TRY(dump(t->x1, w.x1, (size_t)Mk * d * 2, st));
-        TRY(rmsnorm_gemm(w, w.x1, Mk, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
-        TRY(dump(t->gu, w.gu, (size_t)Mk * 2 * F * 2, st));
-        TRY(silu_mul_gemm(w, Mk, F, t->z, t->inject_z, &L->down, s->x_out, d, w.x1, d, st));
+        TRY(swiglu(L, w, Mk, w.x1, t, s->x_out, st));
     }
     // the descriptors move only now that every step has been enqueued
     cache->len += n_keep;
@@ -299,9 +314,7 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
 
     TRY(quantize_gemm(w, o_used, B, d, &L->o, w.x1, d, x_f16, d, st));
     TRY(dump(t->x1, w.x1, (size_t)B * d * 2, st));
-    TRY(rmsnorm_gemm(w, w.x1, B, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
-    TRY(dump(t->gu, w.gu, (size_t)B * 2 * F * 2, st));
-    TRY(silu_mul_gemm(w, B, F, t->z, t->inject_z, &L->down, x_out_f16, d, w.x1, d, st));
+    TRY(swiglu(L, w, B, w.x1, t, x_out_f16, st));
     if (!stepped) cache->len += 1;      // only now that every step has been enqueued
     return QUOTA_OK;
 }

@@ -371,11 +371,7 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
                 if (!EARLY) { gg[r].u = gr[c]; uu[r].u = ur[c]; }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    float gt = (float)gg[r].h[e], up = (float)uu[r].h[e];
-                    // silu(g) = g / (1 + e^-g) with the hardware exp2 and reciprocal (a few fp32 ulp,
-                    // far inside the fp16 rounding that follows)
-                    float sg = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt));
-                    v[r].h[e] = to_f16(sg * up);
+                    v[r].h[e] = silu_mul((float)gg[r].h[e], (float)uu[r].h[e]);
                 }
             }
 #pragma unroll
@@ -395,22 +391,24 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
 // Calls launch(GROUP, NCH, grid) with the smallest cache that holds d columns: a thread's registers are what limits the
 // rows in flight.  RMSNorm quantizer with metrics, 11776 rows of 5120 columns: 61 us with 12 chunks per lane, of which 10
 // are used, 113 with 8 per thread of a workgroup, of which 2.5 are used.
-template <typename LAUNCH>
+template <typename OUT, typename LAUNCH>
 static void with_row_shape(int M, int d, LAUNCH launch)
 {
     const auto go = [&](auto group, auto nch) { launch(group, nch, dim3(group() == 64 ? (M + 3) / 4 : M)); };
     const std::integral_constant<int, 64> wave;
     const std::integral_constant<int, 256> workgroup;
-    if (M >= ROW_WAVE_MIN_ROWS && d <= 6144) {
-        if (d <= 64 * 8 * 2) go(wave, std::integral_constant<int, 2>());
-        else if (d <= 64 * 8 * 8) go(wave, std::integral_constant<int, 8>());
-        else go(wave, std::integral_constant<int, 12>());
-    } else {
-        if (d <= 256 * 8 * 2) go(workgroup, std::integral_constant<int, 2>());
-        else if (d <= 256 * 8 * 4) go(workgroup, std::integral_constant<int, 4>());
-        else if (d <= 256 * 8 * 8) go(workgroup, std::integral_constant<int, 8>());
-        else go(workgroup, std::integral_constant<int, 16>());
+    if constexpr (OUT::MANY) {
+        if (M >= ROW_WAVE_MIN_ROWS && d <= 64 * 8 * 12) {
+            if (d <= 64 * 8 * 2) go(wave, std::integral_constant<int, 2>());
+            else if (d <= 64 * 8 * 8) go(wave, std::integral_constant<int, 8>());
+            else go(wave, std::integral_constant<int, 12>());
+            return;
+        }
     }
+    if (d <= 256 * 8 * 2) go(workgroup, std::integral_constant<int, 2>());
+    else if (d <= 256 * 8 * 4) go(workgroup, std::integral_constant<int, 4>());
+    else if (d <= 256 * 8 * 8) go(workgroup, std::integral_constant<int, 8>());
+    else go(workgroup, std::integral_constant<int, 16>());
 }
 
 extern "C" size_t quota_weights_packed_bytes(int N, int K)
@@ -497,7 +495,7 @@ extern "C" int quota_quantize_act(const void *x_f16, int M, int d, int ldx, uint
     if (M == 0) return QUOTA_OK;
     hipStream_t st = (hipStream_t)stream;
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
-    with_row_shape(M, d, [&](auto group, auto nch, dim3 grid) {
+    with_row_shape<RowOutPacked>(M, d, [&](auto group, auto nch, dim3 grid) {
         auto kernel = sumsq_opt || ressq_opt ? quantize_act_kernel<true, group(), nch(), RowOutPacked>
                                              : quantize_act_kernel<false, group(), nch(), RowOutPacked>;
         kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, M, 0, RowOutPacked{(uint32_t *)q_packed},
@@ -512,7 +510,7 @@ static int rmsnorm_quantize(const void *x_f16, int M, int d, int ldx, const floa
                             float *scale, float *sumsq_opt, float *ressq_opt, void *h_opt, hipStream_t st)
 {
     ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
-    with_row_shape(M, d, [&](auto group, auto nch, dim3 grid) {
+    with_row_shape<OUT>(M, d, [&](auto group, auto nch, dim3 grid) {
         auto kernel = sumsq_opt || ressq_opt ? rmsnorm_quantize_act_kernel<true, group(), nch(), OUT>
                                              : rmsnorm_quantize_act_kernel<false, group(), nch(), OUT>;
         kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, gamma, eps, q, scale, sumsq_opt, ressq_opt,
@@ -542,8 +540,7 @@ int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const fl
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    const auto run = [&](auto out) { return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, out, scale, sumsq_opt, ressq_opt, nullptr, st); };
-    return quota_a8_starts(M) ? run(RowOutA8<true>{(uint2 *)qa8, M}) : run(RowOutA8<false>{(uint2 *)qa8, M});
+    return with_a8_out(qa8, M, [&](auto out) { return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, out, scale, sumsq_opt, ressq_opt, nullptr, st); });
 }
 
 template <typename OUT>
@@ -551,10 +548,12 @@ static int silu_mul_quantize(const void *gu_f16, int M, int F, OUT q, float *sca
                              const void *z_inject_opt, hipStream_t st)
 {
     ProfScope prof(QUOTA_K_SILU_MUL_QUANTIZE_ACT, 0, 4.5 * M * F + 4.0 * M, st);
-    with_row_shape(M, F, [&](auto group, auto nch, dim3 grid) {
+    with_row_shape<OUT>(M, F, [&](auto group, auto nch, dim3 grid) {
         constexpr bool can_be_early = nch() < 16;
-        auto kernel = can_be_early && M < ROW_WAVE_MIN_ROWS ? silu_mul_quantize_act_kernel<group(), nch(), can_be_early, OUT>
-                                                            : silu_mul_quantize_act_kernel<group(), nch(), false, OUT>;
+        auto kernel = silu_mul_quantize_act_kernel<group(), nch(), can_be_early, OUT>;
+        if constexpr (OUT::MANY) {
+            if (M >= ROW_WAVE_MIN_ROWS) kernel = silu_mul_quantize_act_kernel<group(), nch(), false, OUT>;
+        }
         kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt);
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -578,15 +577,14 @@ int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_
     int rc = check_rows(gu_f16, M, F, F, qa8, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    const auto run = [&](auto out) { return silu_mul_quantize(gu_f16, M, F, out, scale, z_opt, z_inject_opt, st); };
-    return quota_a8_starts(M) ? run(RowOutA8<true>{(uint2 *)qa8, M}) : run(RowOutA8<false>{(uint2 *)qa8, M});
+    return with_a8_out(qa8, M, [&](auto out) { return silu_mul_quantize(gu_f16, M, F, out, scale, z_opt, z_inject_opt, st); });
 }
 
 template <typename OUT>
 static int quantize_rows(const void *x_f16, int M, int d, OUT q, float *scale, hipStream_t st)
 {
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
-    with_row_shape(M, d, [&](auto group, auto nch, dim3 grid) {
+    with_row_shape<OUT>(M, d, [&](auto group, auto nch, dim3 grid) {
         quantize_act_kernel<false, group(), nch(), OUT><<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, q,
                                                                                             scale, nullptr, nullptr);
     });
@@ -599,8 +597,7 @@ int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, fl
 {
     int rc = check_rows(x_f16, M, d, d, qa8, scale);
     if (rc != QUOTA_OK || M == 0) return rc;
-    const auto run = [&](auto out) { return quantize_rows(x_f16, M, d, out, scale, st); };
-    return quota_a8_starts(M) ? run(RowOutA8<true>{(uint2 *)qa8, M}) : run(RowOutA8<false>{(uint2 *)qa8, M});
+    return with_a8_out(qa8, M, [&](auto out) { return quantize_rows(x_f16, M, d, out, scale, st); });
 }
 
 // The three quantizers of at most 16 rows into the few-row GEMM's fragments.
@@ -636,7 +633,7 @@ int quota_internal_vector_metrics(const void *v_f16, int B, int Nv, int d, int l
         return QUOTA_ERR_SHAPE;
     if (Nv == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.0 * B * Nv * d + 8.0 * B * Nv, st);
-    with_row_shape(B * Nv, d, [&](auto group, auto nch, dim3 grid) {
+    with_row_shape<RowOutPacked>(B * Nv, d, [&](auto group, auto nch, dim3 grid) {
         quantize_act_kernel<true, group(), nch(), RowOutPacked><<<grid, dim3(ROW_THREADS), 0, st>>>(
             (const f16 *)v_f16, B * Nv, d, ldv, Nv, stride_b, RowOutPacked{nullptr}, nullptr, sumsq, ressq);
     });

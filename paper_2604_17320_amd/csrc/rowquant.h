@@ -3,6 +3,7 @@
 // thread c % GROUP of the group, as its (c / GROUP)-th chunk.
 #pragma once
 #include "common.h"
+#include "internal.h"
 
 #define ROW_THREADS 256
 #define ROW_MAXCHUNK 16  // workgroup-per-row kernels: 16 chunks * 8 halves * 256 threads = 32768 columns
@@ -14,22 +15,32 @@
 // most 16 rows, packed int4 as the few-row GEMM's fragments: 1 KB per group, the 32 codes number q of row m's
 // 128 at 16-byte piece 16 q + m.  A null pointer drops the output.
 struct RowOutPacked {
-    static constexpr bool A8 = false, STARTS = false;
+    static constexpr bool A8 = false, STARTS = false, MANY = true;       // MANY: launches of any number of rows
     uint32_t *q;
     static __device__ __forceinline__ int at(int c) { return c; }
 };
 struct RowOutFrag {
-    static constexpr bool A8 = false, STARTS = false;
+    static constexpr bool A8 = false, STARTS = false, MANY = false;
     uint32_t *q;
     static __device__ __forceinline__ int at(int c) { return (c >> 4) * 256 + (c >> 2 & 3) * 64 + (c & 3); }
 };
-template <bool S>
 struct RowOutA8 {
-    static constexpr bool A8 = true, STARTS = S;
+    static constexpr bool A8 = true, STARTS = false, MANY = false;       // (with_a8_out: less than quota_a8_starts)
+    uint2 *q;
+};
+struct RowOutA8Starts {
+    static constexpr bool A8 = true, STARTS = true, MANY = true;
     uint2 *q;
     int rows;            // of the launch
     float *starts;       // of this row
 };
+// run(the output of M rows in the A8 format)
+template <typename RUN>
+static inline int with_a8_out(void *qa8, int M, RUN run)
+{
+    if (quota_a8_starts(M)) return run(RowOutA8Starts{(uint2 *)qa8, M, nullptr});
+    return run(RowOutA8{(uint2 *)qa8});
+}
 // The row (or rows) that workgroup `wg` takes: with start values, 4 bytes per row and group, neighbouring rows belong on one XCD, whose L2
 // puts them together (5808 rows and 11008 columns: 0.4 % of a layer's time).
 template <typename OUT>
@@ -43,11 +54,15 @@ __host__ __device__ __forceinline__ RowOutPacked row_out(RowOutPacked o, size_t 
     return RowOutPacked{o.q ? o.q + row * nchunk : nullptr};
 }
 __host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row, int) { return RowOutFrag{o.q + 4 * row}; }
-template <bool S>
-__host__ __device__ __forceinline__ RowOutA8<S> row_out(RowOutA8<S> o, size_t row, int nchunk)
+__host__ __device__ __forceinline__ RowOutA8 row_out(RowOutA8 o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
-    return RowOutA8<S>{o.q + row * (G | 1) * 16, o.rows, reinterpret_cast<float *>(o.q + (size_t)o.rows * (G | 1) * 16) + row};
+    return RowOutA8{o.q + row * (G | 1) * 16};
+}
+__host__ __device__ __forceinline__ RowOutA8Starts row_out(RowOutA8Starts o, size_t row, int nchunk)
+{
+    const int G = (nchunk + 15) >> 4;
+    return RowOutA8Starts{o.q + row * (G | 1) * 16, o.rows, reinterpret_cast<float *>(o.q + (size_t)o.rows * (G | 1) * 16) + row};
 }
 
 // final phase shared by the row kernels: quantize the cached row `v` with absmax `a`, store the

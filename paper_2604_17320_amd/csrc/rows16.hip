@@ -83,11 +83,7 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
 #pragma unroll
                 for (int c = 0; c < CB; ++c)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float gt = (float)v[c0 + c].h[e], up = (float)u[c].h[e];
-                        const float sg = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt));
-                        v[c0 + c].h[e] = to_f16(sg * up);
-                    }
+                    for (int e = 0; e < 8; ++e) v[c0 + c].h[e] = silu_mul((float)v[c0 + c].h[e], (float)u[c].h[e]);
         }
         if (in.z_out && live && blockIdx.x == 0)
 #pragma unroll

@@ -367,6 +367,29 @@ def test_layer_start_values_from_the_quantizer(qb, tile, Nv, Nt, K, pinned_gemm)
     assert_teacher_forced_exact(ref, got, shape, K)
 
 
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4])
+@pytest.mark.parametrize("F,Nt,K", [(1376, 9, 8), (1376, 21, 19), (96, 30, 500), (2080, 30, 500)])
+def test_layer_silu_product_in_the_gate_up_projection(qb, tile, F, Nt, K, pinned_gemm):
+    """Without taps the gate/up projection makes SiLU(gate) * up itself: the bits of the run whose taps keep the two
+    kernels apart, for channels that end inside a tile, 17 rows, ragged ones and start values (530 rows)."""
+    from paper_2604_17320_amd.model import KVCache4
+    pinned_gemm(tile)
+    base = wl.CONFIGS[0]
+    shape = wl.Shape("silu", d=base.d, H=base.H, F=F, layers=1, B=1, Nv=500, Nt=Nt, n_outlier=base.n_outlier, vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 7)
+    x, pos = wl.hidden_state(shape, 7), wl.positions(shape)
+    tapped = run_gpu(qb, L, shape, x, pos, K)
+    n_keep = shape.N - 500 + K
+    cache = KVCache4(1, n_keep, shape.H, shape.dh)
+    x_out = torch.zeros((n_keep, shape.d), dtype=torch.float16, device="cuda")
+    pos_out = torch.zeros((n_keep,), dtype=torch.int32, device="cuda")
+    ws = torch.empty(L.workspace_bytes(1, shape.N), dtype=torch.uint8, device="cuda")
+    xd, pd = dev(x), dev(pos)
+    st = qb.State(1, shape.N, 0, 500, xd.data_ptr(), pd.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+    qb.quota_prefill_layer(L.desc, st, K, qb.quota_score_params_default(), cache.desc, None, ws)
+    assert np.array_equal(host(x_out).view(np.uint16), tapped["x_next"][:n_keep].view(np.uint16))
+
+
 def test_layer_with_weight_scales_at_an_odd_halfword(qb):
     """Weight scales that start between two dwords: a prefill layer and its decode-sized remainder give the bits of the
     aligned layer (the fused QKV epilogue and the tiles step aside)."""
