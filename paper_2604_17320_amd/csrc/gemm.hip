@@ -462,11 +462,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
 //                                            RT CT NW CH SP          OCC
-#define F8_TILE_0(P, A, E) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, E, 2>  // 64 x 256
-#define F8_TILE_1(P, A, E) w4a4_f8_kernel<4, 4, 2, 2, 6, P, A, E, 2>  // 64 x 128
-#define F8_TILE_2(P, A, E) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, E, 2>  // 32 x 128
-#define F8_TILE_3(P, A, E) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, E, 2>  // 32 x 64
-#define F8_TILE_4(P, A, E) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, E, 2>  // 128 x 256
+#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>  // 64 x 256
+#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, P, A, QK, 2>  // 64 x 128
+#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, QK, 2>  // 32 x 128
+#define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
+#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128, QUOTA_K_GEMM_64X128},
