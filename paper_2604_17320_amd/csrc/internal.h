@@ -80,10 +80,12 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
 int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *z_f16, hipStream_t st);
 
 // GEMM of at most 16 rows (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
-// quota_internal_rows16_quantizes accepts: as they are, through RMSNorm, or gate | up rows through SwiGLU.
+// quota_internal_rows16_quantizes accepts: as they are, or through RMSNorm.  frag_silu and glu: the gate/up projection,
+// z [M][N / 2] = SiLU(gate) * up.
 enum quota_rows16_format { QUOTA_ROWS16_A8, QUOTA_ROWS16_PACKED, QUOTA_ROWS16_FRAG };
 int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const float *sa, int M, const quota_weights *W, void *y, int ldy,
                           const void *res, int ldr, hipStream_t st);
+int quota_internal_rows16_frag_silu(const uint8_t *qf, const float *sa, int M, const quota_weights *W, void *z, hipStream_t st);
 int quota_internal_rmsnorm_quantize_frag(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qf,
                                          float *scale, hipStream_t st);
 int quota_internal_silu_mul_quantize_frag(const void *gu_f16, int M, int F, uint8_t *qf, float *scale, void *z_opt,
@@ -93,9 +95,7 @@ bool quota_internal_rows16_quantizes(int M, int K);
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
                                    int ldr, hipStream_t st);
 int quota_internal_rows16_rmsnorm(const void *x, const float *gamma, float eps, int M, const quota_weights *W, void *y,
-                                  int ldy, hipStream_t st);
-int quota_internal_rows16_silu(const void *gu, void *z_out, const void *z_inject, int M, const quota_weights *W, void *y,
-                               int ldy, const void *res, int ldr, hipStream_t st);
+                                  int ldy, bool glu, hipStream_t st);
 
 // quota_rope_kv_quant with Hkv K/V heads: qkv rows are q (H*dh) | k (Hkv*dh) | v (Hkv*dh).
 int quota_internal_rope_kv_quant(const void *qkv_f16, int M, int H, int Hkv, int dh, const int32_t *pos,

@@ -120,7 +120,7 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
 static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
                         const quota_weights *W, void *y, int ldy, hipStream_t st)
 {
-    if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_rmsnorm(x, gamma, eps, M, W, y, ldy, st);
+    if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_rmsnorm(x, gamma, eps, M, W, y, ldy, false, st);
     if (M <= ROWS_FRAG) {
         TRY(quota_internal_rmsnorm_quantize_frag(x, M, d, gamma, eps, w.qa, w.sa, st));
         return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, nullptr, 0, st);
@@ -131,8 +131,6 @@ static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const flo
 static int silu_mul_gemm(const LayerWs &w, int M, int F, void *z, const void *z_inject, const quota_weights *W, void *y,
                          int ldy, const void *res, int ldr, hipStream_t st)
 {
-    if (quota_internal_rows16_quantizes(M, F))
-        return quota_internal_rows16_silu(w.gu, z, z_inject, M, W, y, ldy, res, ldr, st);
     if (M <= ROWS_FRAG) {
         TRY(quota_internal_silu_mul_quantize_frag(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
         return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, res, ldr, st);
@@ -156,9 +154,17 @@ static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const qu
 static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1, const quota_taps *t, void *x_out, hipStream_t st)
 {
     const int d = L->H * L->dh, F = L->F;
-    if (M > ROWS_FRAG && !t->gu && !t->z && !t->inject_z) {
-        TRY(quota_internal_rmsnorm_quantize_a8(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st));
-        const int rc = quota_internal_w4a4_gemm_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
+    if (!t->gu && !t->z && !t->inject_z) {
+        int rc;
+        if (quota_internal_rows16_quantizes(M, d)) {
+            rc = quota_internal_rows16_rmsnorm(x1, L->gamma2, L->eps, M, &L->gu, w.gu, F, true, st);
+        } else if (M <= ROWS_FRAG) {
+            TRY(quota_internal_rmsnorm_quantize_frag(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, st));
+            rc = quota_internal_rows16_frag_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
+        } else {
+            TRY(quota_internal_rmsnorm_quantize_a8(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st));
+            rc = quota_internal_w4a4_gemm_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
+        }
         if (rc == QUOTA_OK) return quantize_gemm(w, w.gu, M, F, &L->down, x_out, d, x1, d, st);
         if (rc != QUOTA_ERR_SHAPE) return rc;
         TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->gu, w.gu, 2 * F, nullptr, 0, st));

@@ -13,10 +13,19 @@
 // one 7 (16 x 12288 x 4096: 8.6 -> 7.8 us).
 // NB = 16-column blocks per workgroup.
 //
-// Few rows (MODE > FRAG) also bring their own quantizer: every workgroup normalises / multiplies / quantizes
+// Few rows (MODE > FRAG) also bring their own quantizer: every workgroup normalises / quantizes
 // the whole rows for itself while its first weights are on their way.  That is a few thousand elements per
 // row, read from L2, against a launch and a pass of 16 workgroups that cost 4 to 5 us; from five rows on
-// the repeated work costs more than the launch.
+// the repeated work costs more than the launch.  SiLU(gate) * up is not among it: 256 workgroups made the same 11008
+// products in front of the down projection, 4.7 us of its 11; the gate/up projection makes each once (GLU).
+//
+// A row's 101 MB of weights of a 7B layer would pass in 18 us: what is left of the 33 that the four launches take is their
+// latencies, in this order the rows, their quantizer, the weights, the exchange and the chain.  Rows first
+// (weights()), sums and scales of 8 groups in one trip to LDS, and four groups per wave in flight over long rows: down
+// 11.2 -> 7.9 us, O 5.4 -> 4.8.  More than 32 KB of weights in flight per workgroup holds the rows up
+// instead (QKV 96 KB: 9.6 us, 64 KB 9.4; gate/up 192 KB: 13.5 and 11.4).
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 #include "gemm_common.h"
@@ -24,16 +33,14 @@
 
 namespace {
 
-enum { ROWS_A8 = 0, ROWS_PACKED, ROWS_FRAG, ROWS_QUANT, ROWS_RMSNORM, ROWS_SILU };
+enum { ROWS_A8 = 0, ROWS_PACKED, ROWS_FRAG, ROWS_QUANT, ROWS_RMSNORM };
 
 struct RowsIn {
     const uint8_t *qa;          // A8 / PACKED / FRAG: activations and token scales
     const float *sa;
-    const f16 *x;               // QUANT, RMSNORM: rows [M][K]; SILU: gate | up rows [M][2K]
+    const f16 *x;               // QUANT, RMSNORM: rows [M][K]
     const float *gamma;         // RMSNORM
     float eps;
-    f16 *z_out;                 // SILU: optional dump of / replacement for the product
-    const f16 *z_inject;
 };
 
 constexpr int RT_THREADS = 512;
@@ -58,43 +65,30 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
         __syncthreads();
         mx = 0.0f;
         s = 0.0;
-        for (int w = 0; w < wpr; ++w) {
-            mx = fmaxf(mx, (float)red[2 * (row * wpr + w)]);
-            s += red[2 * (row * wpr + w) + 1];
-        }
+        double all[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) all[i] = red[i];       // (all at once: one trip to LDS)
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+            if (w / wpr == row) {
+                mx = fmaxf(mx, (float)all[2 * w]);
+                s += all[2 * w + 1];
+            }
+    };
+    // The weights are asked for behind all waves' loads of the rows, which would else queue behind other waves' weights.
+    auto weights = [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        fetch();
     };
     Pack16 v[NC];
     float a = 0.0f;
     double ss = 0.0;
-    if (MODE == ROWS_SILU) {
-        const uint4 *gr = reinterpret_cast<const uint4 *>(in.x + (size_t)r * 2 * K), *ur = gr + nchunk;
-        constexpr int CB = NC > 3 ? 3 : NC;                 // chunks in flight: registers
+    const uint4 *xr = reinterpret_cast<const uint4 *>(in.x + (size_t)r * K);
 #pragma unroll
-        for (int c0 = 0; c0 < NC; c0 += CB) {
-            Pack16 u[CB];
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int i = min(idx + T * (c0 + c), nchunk - 1);
-                if (in.z_inject) v[c0 + c].u = reinterpret_cast<const uint4 *>(in.z_inject + (size_t)r * K)[i];
-                else { v[c0 + c].u = gr[i]; u[c].u = ur[i]; }
-            }
-            if (c0 == 0) fetch();
-            if (!in.z_inject)
-#pragma unroll
-                for (int c = 0; c < CB; ++c)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[c0 + c].h[e] = silu_mul((float)v[c0 + c].h[e], (float)u[c].h[e]);
-        }
-        if (in.z_out && live && blockIdx.x == 0)
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if (idx + T * c < nchunk) reinterpret_cast<uint4 *>(in.z_out + (size_t)r * K)[idx + T * c] = v[c].u;
-    } else {
-        const uint4 *xr = reinterpret_cast<const uint4 *>(in.x + (size_t)r * K);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) v[c].u = xr[min(idx + T * c, nchunk - 1)];
-        if (MODE != ROWS_RMSNORM) fetch();
-    }
+    for (int c = 0; c < NC; ++c) v[c].u = xr[min(idx + T * c, nchunk - 1)];
+    if (MODE != ROWS_RMSNORM) weights();
     // (a clamped chunk repeats one of the row's: harmless for a maximum, left out of the sum)
     if (MODE == ROWS_RMSNORM) {
         constexpr bool EARLY = NC <= 3;                     // the gains of wider shares do not fit beside the rows
@@ -105,7 +99,7 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
             ga[c][0] = gp[0];
             ga[c][1] = gp[1];
         }
-        fetch();
+        weights();
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (idx + T * c < nchunk)
@@ -171,7 +165,9 @@ __device__ __forceinline__ void unsigned_e4m3(const uint4 &p, uint4 &lo, uint4 &
     hi = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
-template <int NB, int U, int MODE, int NC>
+// GLU: the columns are gate | up, NB = 2 and a workgroup has 16 of each, of the same channels: it stores SiLU(gate) * up of
+// their fp16 roundings, y is [M][N / 2].
+template <int NB, int U, int MODE, int NC, bool GLU>
 __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     RowsIn in, int M, int K, int G, const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N,
     f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, int code_stride)
@@ -180,8 +176,11 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     constexpr int SD = 8 * NB * R;                  // scale dwords (two columns of a group) per round
     constexpr int SPT = (SD + RT_THREADS - 1) / RT_THREADS;
     constexpr int SROW = R + 8;                     // halves per column of staged scales (16-byte pieces, padded)
-    constexpr int OPT = NB > 2 ? NB / 2 : 1;        // outputs per owner thread
-    constexpr int BUF = R * NB * 256 + 8 * NB * SROW;       // floats of one exchange buffer
+    constexpr bool FEW = MODE > ROWS_FRAG;          // at most 4 rows: lanes 0 to 15 hold the sums that count
+    constexpr int XS = FEW ? 64 : 256;              // sums of a group and block
+    constexpr int OPT = GLU ? 2 : 1;                // outputs per owner thread
+    constexpr int BUF = R * NB * XS + 8 * NB * SROW;        // floats of one exchange buffer
+    static_assert(NB <= 2 && (!GLU || NB == 2), "an owner per output");
     extern __shared__ __align__(16) uint4 lds_rows[];
     float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
     float *row_scale = xbuf + 2 * BUF;                                            // [16]
@@ -190,10 +189,12 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // chain ownership: thread t < 256 * NB owns the outputs held by (block 2 o + t / 256, register oreg, lane ol)
-    const int oj = tid >> 8, oreg = (tid >> 6) & 3, ol = tid & 63;
-    const bool owner = NB >= 2 || tid < 256;
+    // chain ownership: thread t owns the output(s) held by (block t / XS, or both for GLU; register oreg, lane ol)
+    const int oj = GLU ? 0 : tid / XS, oreg = tid / (XS / 4) & 3, ol = tid % (XS / 4);
+    const bool owner = XS * NB / OPT >= RT_THREADS || tid < XS * NB / OPT;
     const int om = 4 * (ol >> 4) + oreg;
+    const int C = GLU ? N >> 1 : N;                 // output columns
+    const int up = GLU ? C : 16;                    // from a column of the first block to the second's
     float y32[OPT];
 #pragma unroll
     for (int o = 0; o < OPT; ++o) y32[o] = 0.0f;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             const int g = min(r0 + 8 * u + wave, G - 1);
             const uint4 *wg = wp + ((size_t)g * N + n0) * 4;
 #pragma unroll
-            for (int j = 0; j < NB; ++j) rb[u][j] = wg[64 * j + 4 * c16 + q];
+            for (int j = 0; j < NB; ++j) rb[u][j] = wg[4 * j * up + 4 * c16 + q];
             if (MODE == ROWS_FRAG) {
                 ra[u][0] = *reinterpret_cast<const uint4 *>(in.qa + (size_t)g * 1024 + 16 * lane);
             } else if (MODE == ROWS_A8) {
@@ -222,20 +223,21 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const int d = min(tid + RT_THREADS * k, SD - 1), g = min(r0 + d / (8 * NB), G - 1);
-            rsv[k] = *reinterpret_cast<const u32_at2 *>(sw + (size_t)g * N + n0 + 2 * (d % (8 * NB)));
+            rsv[k] = *reinterpret_cast<const u32_at2 *>(sw + (size_t)g * N + n0 + (GLU ? d / 8 % NB * up + 2 * (d % 8) : 2 * (d % (8 * NB))));
         }
     };
-    const int nblk = N / (16 * NB);
+    constexpr int BC = GLU ? 16 : 16 * NB;          // output columns per workgroup
+    const int nblk = C / BC;
     int blk = blockIdx.x, r0 = 0, par = 0;
     if constexpr (MODE > ROWS_FRAG)
-        quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] { fetch(blk * 16 * NB, 0); });
+        quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] { fetch(blk * BC, 0); });
     else
-        fetch(blk * 16 * NB, 0);
+        fetch(blk * BC, 0);
     const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
     while (true) {                                  // rounds of this workgroup's column blocks
         float *accs = xbuf + par * BUF;
-        f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * 256);
+        f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * XS);
         f32x4 acc[U][NB];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -278,43 +280,46 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
         }
         const bool last = r0 + R >= G;
         const int nblk_next = last ? blk + (int)gridDim.x : blk, r_next = last ? 0 : r0 + R;
-        if (nblk_next < nblk) fetch(nblk_next * 16 * NB, r_next);       // the next loads fly during the exchange
+        if (nblk_next < nblk) fetch(nblk_next * BC, r_next);       // the next loads fly during the exchange
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) accs[((8 * u + wave) * NB + j) * 256 + i * 64 + lane] = acc[u][j][i];
+                for (int i = 0; i < 4; ++i)
+                    if (!FEW || lane < 16) accs[((8 * u + wave) * NB + j) * XS + i * (XS / 4) + lane] = acc[u][j][i];
         __syncthreads();        // (the other buffer's readers passed the one before)
         if (owner) {
 #pragma unroll
             for (int o = 0; o < OPT; ++o) {
-                const int j = 2 * o + oj;
+                const int j = o + oj;
                 const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + (16 * j + (ol & 15)) * SROW);
-                const float *ap = accs + j * 256 + oreg * 64 + ol;
+                const float *ap = accs + j * XS + oreg * (XS / 4) + ol;
 #pragma unroll
                 for (int i8 = 0; i8 < U; ++i8) {
-                    if (r0 + 8 * i8 >= G) break;
+                    if (!FEW && r0 + 8 * i8 >= G) break;
                     const Pack16 s8 = sp[i8];
+                    float sum[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const float sc = r0 + 8 * i8 + i < G ? (float)s8.h[i] : 0.0f;
-                        y32[o] = __builtin_fmaf(ap[(8 * i8 + i) * NB * 256], sc, y32[o]);
-                    }
+                    for (int i = 0; i < 8; ++i) sum[i] = ap[(8 * i8 + i) * NB * XS];
+                    __builtin_amdgcn_sched_barrier(0);          // one trip to LDS, not one per pair
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        y32[o] = __builtin_fmaf(sum[i], r0 + 8 * i8 + i < G ? (float)s8.h[i] : 0.0f, y32[o]);
                 }
             }
             if (last) {
-#pragma unroll
-                for (int o = 0; o < OPT; ++o) {
-                    const int on = blk * 16 * NB + 16 * (2 * o + oj) + (ol & 15);
-                    if (om < M) {
-                        const float sa = MODE <= ROWS_FRAG ? in.sa[om] : row_scale[om];
-                        float v = y32[o] * (sa * F8_UNIT);
-                        if (res) v = v + (float)res[(size_t)om * ldr + on];
-                        y[(size_t)om * ldy + on] = to_f16(v);
-                    }
-                    y32[o] = 0.0f;
+                const int on = blk * BC + 16 * oj + (ol & 15);
+                if (om < M) {
+                    const float sa = MODE <= ROWS_FRAG ? in.sa[om] : row_scale[om];
+                    float v = y32[0] * (sa * F8_UNIT);
+                    if (res) v = v + (float)res[(size_t)om * ldr + on];
+                    f16 out = to_f16(v);
+                    if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * F8_UNIT)));
+                    y[(size_t)om * ldy + on] = out;
                 }
+#pragma unroll
+                for (int o = 0; o < OPT; ++o) y32[o] = 0.0f;
             }
         }
         if (nblk_next >= nblk) break;
@@ -325,22 +330,21 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 }
 
 // PER_CU: workgroups wanted per CU.  A launch asks for no more than the LDS has room for: what is left over would run in a
-// second round and quantize the rows once more.  <2, 2> takes 68.8 KB and 128 G + 16 bytes a row: two fit up to 13120
-// bytes of rows, one beyond (4 rows of 4096, through RMSNorm, captured: 12288 columns 16.7 us in 384 workgroups,
-// 11.9 in 256; 22016 columns 20.0 in 512, 16.1 in 256; 3 x 5120, 27648 columns 27.6 -> 22.8).
-template <int NB, int U, int PER_CU, int MODE, int NC>
+// second round and quantize the rows once more.  <2, 2> takes 19.6 KB, 68.8 without a quantizer, and 128 G + 16
+// bytes a row.
+template <int NB, int U, int PER_CU, int MODE, int NC, bool GLU = false>
 int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
                   int code_stride, hipStream_t st)
 {
     constexpr int R = 8 * U;
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    const size_t lds = 2 * (R * NB * 1024 + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
-    if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC>>()) return QUOTA_ERR_HIP;
+    const size_t lds = 2 * (R * NB * (MODE > ROWS_FRAG ? 256 : 1024) + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
+    if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC, GLU>>()) return QUOTA_ERR_HIP;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + 2.0 * Md * Nd * (res ? 2 : 1), st);
     const int per_cu = min(PER_CU, (int)(160 * 1024 / lds));
-    w4a4_rows16_kernel<NB, U, MODE, NC><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
+    w4a4_rows16_kernel<NB, U, MODE, NC, GLU><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
         in, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr, code_stride);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
@@ -349,7 +353,8 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 // 16 columns per workgroup up to 4096 columns (256 workgroups: one per CU), with two groups per wave in flight, four
 // over long rows, which stream longer than they start up; 32 beyond, two groups up to 8192 columns (at
 // most one workgroup per CU again), else three workgroups per CU with one group per wave, or, with a quantizer in
-// front, two per CU (one, where the rows leave no room for two) with two, so that fewer repeat its work.
+// front, two per CU (one, where the rows leave no room for two) with two, so that fewer repeat its work (one row, gate/up
+// of 22016 columns: 10.8 us inside with two per CU, 12.8 with one, 13.8 with three).
 // Workgroups walk over the columns.
 // Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
 // <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
@@ -358,7 +363,7 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
            hipStream_t st)
 {
     if (W->N <= 4096) {
-        if constexpr (MODE <= ROWS_FRAG)
+        if constexpr (MODE != ROWS_RMSNORM)
             if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
         return launch_rows16<1, 2, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }
@@ -367,16 +372,25 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
     return launch_rows16<2, 2, 2, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
 }
 
-template <int MODE>
-int rows16_quantizing(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
-                      hipStream_t st)
+template <int MODE, int NC>
+int rows16_glu(const RowsIn &in, int M, const quota_weights *W, f16 *z, int code_stride, hipStream_t st)
 {
-    const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W, T = M == 1 ? 512 : M == 2 ? 256 : 128;
+    const int F = W->N / 2;
+    if constexpr (MODE <= ROWS_FRAG)
+        if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC, true>(in, M, W, z, F, nullptr, 0, code_stride, st);
+    return launch_rows16<2, 2, 2, MODE, NC, true>(in, M, W, z, F, nullptr, 0, code_stride, st);
+}
+
+// run(chunks per thread, bytes of a row of codes in LDS)
+template <typename RUN>
+int rows16_quantizing(int M, int K, RUN run)
+{
+    const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W, T = M == 1 ? 512 : M == 2 ? 256 : 128;
     const int nc = (16 * G + T - 1) / T;                  // 8-channel chunks per thread
     const int stride = G * 128 + 16;                      // 16 more: rows start on different LDS banks
-    if (nc <= 1) return rows16<MODE, 1>(in, M, W, y, ldy, res, ldr, stride, st);
-    if (nc <= 3) return rows16<MODE, 3>(in, M, W, y, ldy, res, ldr, stride, st);
-    return rows16<MODE, 6>(in, M, W, y, ldy, res, ldr, stride, st);
+    if (nc <= 1) return run(std::integral_constant<int, 1>(), stride);
+    if (nc <= 3) return run(std::integral_constant<int, 3>(), stride);
+    return run(std::integral_constant<int, 6>(), stride);
 }
 
 }  // namespace
@@ -400,30 +414,33 @@ int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const f
     }
 }
 
+int quota_internal_rows16_frag_silu(const uint8_t *qf, const float *sa, int M, const quota_weights *W, void *z, hipStream_t st)
+{
+    RowsIn in = {};
+    in.qa = qf;
+    in.sa = sa;
+    return rows16_glu<ROWS_FRAG, 1>(in, M, W, (f16 *)z, 0, st);
+}
+
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
                                    int ldr, hipStream_t st)
 {
     RowsIn in = {};
     in.x = (const f16 *)x;
-    return rows16_quantizing<ROWS_QUANT>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, st);
+    return rows16_quantizing(M, W->K, [&](auto nc, int stride) {
+        return rows16<ROWS_QUANT, nc()>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, stride, st);
+    });
 }
 
 int quota_internal_rows16_rmsnorm(const void *x, const float *gamma, float eps, int M, const quota_weights *W, void *y,
-                                  int ldy, hipStream_t st)
+                                  int ldy, bool glu, hipStream_t st)
 {
     RowsIn in = {};
     in.x = (const f16 *)x;
     in.gamma = gamma;
     in.eps = eps;
-    return rows16_quantizing<ROWS_RMSNORM>(in, M, W, (f16 *)y, ldy, nullptr, 0, st);
-}
-
-int quota_internal_rows16_silu(const void *gu, void *z_out, const void *z_inject, int M, const quota_weights *W, void *y,
-                               int ldy, const void *res, int ldr, hipStream_t st)
-{
-    RowsIn in = {};
-    in.x = (const f16 *)gu;
-    in.z_out = (f16 *)z_out;
-    in.z_inject = (const f16 *)z_inject;
-    return rows16_quantizing<ROWS_SILU>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, st);
+    return rows16_quantizing(M, W->K, [&](auto nc, int stride) {
+        if (glu) return rows16_glu<ROWS_RMSNORM, nc()>(in, M, W, (f16 *)y, stride, st);
+        return rows16<ROWS_RMSNORM, nc()>(in, M, W, (f16 *)y, ldy, nullptr, 0, stride, st);
+    });
 }

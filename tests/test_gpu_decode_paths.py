@@ -156,3 +156,24 @@ def test_decode_layer_captured_across_a_tile_boundary(qb, H, Hkv, dh, rows, most
     for name in ("k_codes", "v_codes", "k_scales", "v_scales"):
         a, b = (getattr(k, name)[:, : rows + steps].contiguous().view(torch.uint8) for k in caches)
         assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("F", [96, 2720, 4128, 8736])  # gate/up of 192 to 17472 columns: both widths of a workgroup's share
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 15, 16, 17, 32])
+def test_decode_layer_silu_product_in_the_gate_up_projection(qb, F, B):
+    """Without taps on gate | up or z the projection makes the product itself: the bits of the step whose tap keeps the
+    two kernels apart."""
+    from paper_2604_17320_amd.model import make_taps
+    H, Hkv, dh, rows = 8, 2, 64, 20
+    W, L, cos, sin = layer(H, Hkv, dh, F)
+    c = random_cache(rows, B, rows, Hkv, dh)
+    r = wl.rng(F, "decode-silu", B)
+    x, pos = dev(r.standard_normal((B, H * dh)).astype(np.float16)), dev((7 + np.arange(B) % 50).astype(np.int32))
+    outs = []
+    for taps in (dict(gu=torch.empty((B, 2 * F), dtype=torch.float16, device="cuda")), {}):
+        cache = poisoned_cache(c, B, rows, rows + 1, Hkv, dh)
+        y = torch.full((B, H * dh), float("nan"), dtype=torch.float16, device="cuda")
+        ws = torch.full((L.decode_workspace_bytes(B),), 0xFF, dtype=torch.uint8, device="cuda")
+        L.decode(x, pos, cache, y, ws, make_taps(**taps))
+        outs.append(host(y))
+    assert np.isfinite(outs[0].astype(np.float32)).all() and eq16(outs[0], outs[1])
