@@ -462,14 +462,16 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
 //                                            RT CT NW CH SP          OCC
+// (64 x 128 as four waves of 64 x 32, three workgroups per CU, against two waves of 64 x 64: 237 x 22016 x 4096 40.2 ->
+// 35.2 us, 1101 x 4608 x 3584 35.0 -> 30.3, 1280 x 4096 x 11008 and x 4096 57.0 -> 52.8 in the mean; a weight still belongs to one wave)
 #define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>  // 64 x 256
-#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 4, 2, 2, 6, P, A, QK, 2>  // 64 x 128
+#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 2, 4, 2, 6, P, A, QK, 3>  // 64 x 128
 #define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
 #define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
 
 struct TileShape { int bm, bn, nt, kernel_id; };
-const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 128, QUOTA_K_GEMM_64X128},
+const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 256, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
                              {128, 256, 256, QUOTA_K_GEMM_128X256}};
 
@@ -513,20 +515,22 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
 
 int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
 
-// Tile choice by a cost model fitted to measured kernel times on this GPU (us).  With x workgroups per CU a
-// group of the K loop takes u[ceil(x) - 1] for x <= 4 and slope * x beyond; c0 is the prologue and epilogue.
+// Tile choice by a cost model fitted to measured kernel times on this GPU (us; 88 shapes of 24 to 1101 rows, 3584 to
+// 37888 columns and 3584 to 18944 channels, all five tiles: the choice costs 0.15 % over the best of each on average, 6 % at
+// most).  With x workgroups per CU a group of the K loop takes u[ceil(x) - 1] for x <= n and slope * x beyond; c0
+// is the launch, prologue and epilogue.
 // Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
 // tiles spread small problems over more waves.  Columns of a tile lie in [min_bn, max_bn] (the QKV
 // epilogue needs whole heads that stay inside q, k or v).
 int choose_tile(int M, int N, int K, int min_bn, int max_bn)
 {
-    struct Cost { float c0, u[4], slope; };
+    struct Cost { float c0; int n; float u[6], slope; };
     static const Cost cost[5] = {
-        {3.0f, {0.75f, 1.08f, 1.65f, 2.15f}, 0.53f},
-        {3.0f, {0.54f, 0.95f, 1.00f, 1.08f}, 0.285f},
-        {2.5f, {0.30f, 0.47f, 0.73f, 0.92f}, 0.225f},
-        {2.0f, {0.23f, 0.30f, 0.43f, 0.62f}, 0.155f},
-        {5.0f, {1.02f, 1.90f, 2.90f, 3.90f}, 0.92f},
+        {7.15f, 4, {0.715f, 1.011f, 1.660f, 2.033f}, 0.584f},
+        {7.30f, 6, {0.528f, 0.627f, 0.795f, 1.360f, 1.510f, 1.694f}, 0.305f},
+        {6.65f, 4, {0.280f, 0.415f, 0.612f, 0.820f}, 0.215f},
+        {5.24f, 4, {0.232f, 0.282f, 0.401f, 0.505f}, 0.137f},
+        {9.17f, 4, {1.062f, 1.578f, 2.543f, 3.313f}, 0.960f},
     };
     auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn; };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
@@ -537,7 +541,7 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn)
         if (!fits(v)) continue;
         const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn);
         const float x = (float)wgs / 256.0f;
-        const float t = cost[v].c0 + G * (x <= 4.0f ? cost[v].u[(wgs + 255) / 256 - 1] : cost[v].slope * x);
+        const float t = cost[v].c0 + G * (x <= (float)cost[v].n ? cost[v].u[(wgs + 255) / 256 - 1] : cost[v].slope * x);
         if (best < 0 || t < best_t) { best = v; best_t = t; }
     }
     return best;
