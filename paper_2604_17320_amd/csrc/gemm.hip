@@ -67,7 +67,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : BM * 8 / NT;    // 16-byte pieces per thread and group
     // dwords per stage, 64 to a copy: the group scales, then (STARTS) the rows' start values
     constexpr int SCOPY = CH * BN / 128, ICOPY = STARTS ? CH * BM / 64 : 0, KD = (SCOPY + ICOPY + NW - 1) / NW;
-    static_assert(RT % 2 == 0 && (PACKED || BM * 8 % NT == 0), "whole rows per copy, fragment double buffer");
+    static_assert(RT % 2 == 0 && (PACKED || BM * 8 % NT == 0) && (!STARTS || CH * BM % 64 == 0) && CH * BN % 128 == 0,
+                  "whole rows per copy, whole copies of dwords, fragment double buffer");
     // one stage in LDS (in uint4): CH groups of activations (+ a spare piece for PACKED threads without one),
     // then the dwords, up to whole waves
     constexpr int AST = BM * 8 + (PACKED ? 2 : 0), GST = CH * AST, STG = GST + KD * NT / 4;
@@ -469,11 +470,18 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
 #define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
+// Tiles 1 and 3 once more in longer stages, for launches that leave a CU with two workgroups at most, where a stage is
+// a round trip to memory (366 x 4096 x 11008 38.2 us, 53.7 in stages of two groups; 128 x 4096 x 11008 23.3,
+// 26.6 in stages of four); with more workgroups their LDS is in the way (640 x 22016 x 4096 77 us and 60).  Activations of a layer only, not pinned.
+#define F8_TILE_5(P, A, QK) w4a4_f8_kernel<4, 2, 4, 4, 6, P, A, QK, 2>  // 64 x 128
+#define F8_TILE_6(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 0, P, A, QK, 2>  // 32 x 64
 
 struct TileShape { int bm, bn, nt, kernel_id; };
-const TileShape kTiles[5] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 256, QUOTA_K_GEMM_64X128},
+constexpr int TILES = 7, PINNED_TILES = 5;
+const TileShape kTiles[TILES] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 256, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
-                             {128, 256, 256, QUOTA_K_GEMM_128X256}};
+                             {128, 256, 256, QUOTA_K_GEMM_128X256}, {64, 128, 256, QUOTA_K_GEMM_64X128},
+                                  {32, 64, 256, QUOTA_K_GEMM_32X64}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
@@ -488,7 +496,13 @@ f8_kernel tile_kernel(int v)
     case 3:
         if constexpr (E == SILU_MUL) return nullptr;         // (one block of columns per wave: never chosen)
         else return F8_TILE_3(P, false, E);
-    default: return F8_TILE_4(P, false, E);
+    case 4: return F8_TILE_4(P, false, E);
+    case 5:
+        if constexpr (P == PACKED_INT4) return nullptr;
+        else return F8_TILE_5(P, false, E);
+    default:
+        if constexpr (P != A8 || E == SILU_MUL) return nullptr;
+        else return F8_TILE_6(P, false, E);
     }
 }
 
@@ -516,32 +530,35 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
 int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
 
 // Tile choice by a cost model fitted to measured kernel times on this GPU (us; 88 shapes of 24 to 1101 rows, 3584 to
-// 37888 columns and 3584 to 18944 channels, all five tiles: the choice costs 0.15 % over the best of each on average, 6 % at
-// most).  With x workgroups per CU a group of the K loop takes u[ceil(x) - 1] for x <= n and slope * x beyond; c0
-// is the launch, prologue and epilogue.
+// 37888 columns and 3584 to 18944 channels, all tiles: the choice costs 0.15 % over the best of each on average, 6 % at
+// most).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
+// slope * x beyond; c0 is the launch, prologue and epilogue.
 // Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
 // tiles spread small problems over more waves.  Columns of a tile lie in [min_bn, max_bn] (the QKV
-// epilogue needs whole heads that stay inside q, k or v).
-int choose_tile(int M, int N, int K, int min_bn, int max_bn)
+// epilogue needs whole heads that stay inside q, k or v), its number below `tiles`.
+int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
 {
-    struct Cost { float c0; int n; float u[6], slope; };
-    static const Cost cost[5] = {
-        {7.15f, 4, {0.715f, 1.011f, 1.660f, 2.033f}, 0.584f},
-        {7.30f, 6, {0.528f, 0.627f, 0.795f, 1.360f, 1.510f, 1.694f}, 0.305f},
-        {6.65f, 4, {0.280f, 0.415f, 0.612f, 0.820f}, 0.215f},
-        {5.24f, 4, {0.232f, 0.282f, 0.401f, 0.505f}, 0.137f},
-        {9.17f, 4, {1.062f, 1.578f, 2.543f, 3.313f}, 0.960f},
+    struct Cost { int ch; float c0; int n; float u[6], slope; };
+    static const Cost cost[TILES] = {
+        {2, 7.15f, 4, {0.715f, 1.011f, 1.660f, 2.033f}, 0.584f},
+        {2, 7.30f, 6, {0.528f, 0.627f, 0.795f, 1.360f, 1.510f, 1.694f}, 0.305f},
+        {4, 6.65f, 4, {0.280f, 0.415f, 0.612f, 0.820f}, 0.215f},
+        {4, 5.24f, 4, {0.232f, 0.282f, 0.401f, 0.505f}, 0.137f},
+        {1, 9.17f, 4, {1.062f, 1.578f, 2.543f, 3.313f}, 0.960f},
+        {4, 6.76f, 4, {0.364f, 0.565f, 0.861f, 1.243f}, 0.340f},
+        {8, 5.12f, 1, {0.198f}, 0.350f},
     };
-    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn; };
+    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < 6 || !quota_a8_starts(M)); };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
     const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     int best = -1;
     float best_t = 0.0f;
-    for (int v = 0; v < 5; ++v) {
+    for (int v = 0; v < tiles; ++v) {
         if (!fits(v)) continue;
         const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn);
         const float x = (float)wgs / 256.0f;
-        const float t = cost[v].c0 + G * (x <= (float)cost[v].n ? cost[v].u[(wgs + 255) / 256 - 1] : cost[v].slope * x);
+        const int groups = (G + cost[v].ch - 1) / cost[v].ch * cost[v].ch;
+        const float t = cost[v].c0 + groups * (x <= (float)cost[v].n ? cost[v].u[(wgs + 255) / 256 - 1] : cost[v].slope * x);
         if (best < 0 || t < best_t) { best = v; best_t = t; }
     }
     return best;
@@ -551,7 +568,7 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn)
 
 extern "C" int quota_set_gemm_variant(int variant)
 {
-    if (variant < -1 || variant > 4) return QUOTA_ERR_INVALID_ARG;
+    if (variant < -1 || variant >= PINNED_TILES) return QUOTA_ERR_INVALID_ARG;
     g_gemm_variant = variant;
     return QUOTA_OK;
 }
@@ -582,7 +599,7 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
     if (!scales_on_dwords(W))
         return gemm_16_rows_at_a_time(qa8, QUOTA_ROWS16_A8, quota_a8_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
                                       (const f16 *)residual_opt, ldr, st);
-    const int v = choose_tile(M, W->N, W->K, 0, 256);
+    const int v = choose_tile(M, W->N, W->K, 0, 256, TILES);
     return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, PLAIN>(v) : tile_kernel<A8, PLAIN>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
 }
@@ -597,7 +614,7 @@ int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, co
     if (!qa8 || !sa || !W || !W->packed || !W->scales || !z_f16) return QUOTA_ERR_NULL;
     if (M <= 16 || W->N % 64 != 0 || W->K % 32 != 0 || !scales_on_dwords(W) || (reinterpret_cast<uintptr_t>(z_f16) & 15))
         return QUOTA_ERR_SHAPE;
-    const int v = choose_tile(M, W->N, W->K, 0, 256);
+    const int v = choose_tile(M, W->N, W->K, 0, 256, TILES);
     if (kTiles[v].bn < 128) return QUOTA_ERR_SHAPE;
     return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, SILU_MUL>(v) : tile_kernel<A8, SILU_MUL>(v), v, kTiles[v].kernel_id,
                      qa8, sa, M, W, (f16 *)z_f16, W->N / 2, nullptr, 0, nullptr, st);
@@ -628,7 +645,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (!dwords) return gemm_16_rows_at_a_time(qa, QUOTA_ROWS16_PACKED, W->K / 2, sa, M, W, y, ldy, res, ldr, st);
     if (M <= 16)            // the decode step: stream the weights once
         return quota_internal_rows16(qa, QUOTA_ROWS16_PACKED, sa, M, W, y, ldy, res, ldr, st);
-    const int v = choose_tile(M, W->N, W->K, 0, 256);
+    const int v = choose_tile(M, W->N, W->K, 0, 256, PINNED_TILES);
     return launch_f8(tile_kernel<PACKED_INT4, PLAIN>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
@@ -648,7 +665,7 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, con
         W->N != d + 2 * dkv || W->K % 32 != 0 || !scales_on_dwords(W))
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
-    const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128);
+    const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128, TILES);
     return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, QKV_ROPE_KV>(v) : tile_kernel<A8, QKV_ROPE_KV>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
                      nullptr, st, qe);
 }

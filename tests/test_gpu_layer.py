@@ -390,6 +390,31 @@ def test_layer_silu_product_in_the_gate_up_projection(qb, tile, F, Nt, K, pinned
     assert np.array_equal(host(x_out).view(np.uint16), tapped["x_next"][:n_keep].view(np.uint16))
 
 
+@pytest.mark.parametrize("d,dh,F,N", [(2048, 128, 2048, 480), (2048, 128, 2048, 641), (1024, 128, 1376, 1000), (1024, 64, 1376, 100),
+                                      (1024, 64, 96, 33)])
+def test_layer_tiles_in_long_stages(qb, d, dh, F, N, pinned_gemm):
+    """The tiles that only the choice takes (64 x 128 in stages of 4 groups from 480 rows, with and without start values;
+    32 x 64 in stages of 8 below, over whole and ragged numbers of groups): the bits of the pinned 64 x 256 tile."""
+    from paper_2604_17320_amd.model import KVCache4
+    shape = wl.Shape("stages", d=d, H=d // dh, F=F, layers=1, B=1, Nv=N - 8, Nt=8, n_outlier=4, vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 9)
+    x, pos = wl.hidden_state(shape, 9), wl.positions(shape)
+    K = N - 11
+    got = []
+    for tile in (0, -1):
+        pinned_gemm(tile)
+        tapped = run_gpu(qb, L, shape, x, pos, K)
+        cache = KVCache4(1, K + 8, shape.H, dh)
+        x_out, pos_out = torch.zeros((K + 8, d), dtype=torch.float16, device="cuda"), torch.zeros((K + 8,), dtype=torch.int32, device="cuda")
+        ws = torch.empty(L.workspace_bytes(1, N), dtype=torch.uint8, device="cuda")
+        xd, pd = dev(x), dev(pos)
+        st = qb.State(1, N, 0, N - 8, xd.data_ptr(), pd.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+        qb.quota_prefill_layer(L.desc, st, K, qb.quota_score_params_default(), cache.desc, None, ws)
+        got.append([tapped[k] for k in ("qkv", "q_rot", "x1", "gu", "x_next")] + [host(x_out)])
+    for a, b in zip(*got):
+        assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
+
+
 def test_layer_with_weight_scales_at_an_odd_halfword(qb):
     """Weight scales that start between two dwords: a prefill layer and its decode-sized remainder give the bits of the
     aligned layer (the fused QKV epilogue and the tiles step aside)."""
