@@ -11,103 +11,120 @@
 namespace {
 
 // ---- y = x W^T (+ residual): fp16 operands, fp32 accumulation, fp16 result ------------------
-// A workgroup of 4 waves covers 128 x 128 outputs, a wave 64 x 64 as 2 x 2 tiles of
-// v_mfma_f32_32x32x16_f16.  Both operands come to LDS 64 channels at a time by asynchronous copies,
-// the next 64 on their way while the current ones are multiplied (one wait and one barrier per 64);
-// the plain form, every fragment straight from global memory, ran at 0.2 PFLOP/s because each wave
-// fetched both operands for itself.  1280 rows: 0.89 PFLOP/s at 12288 x 4096, 0.84 at 22016 x 4096, 0.60 and
-// 0.65 at 4096 x 4096 and 4096 x 11008, whose 320 workgroups do not fill the 512 places.  Neither the matrix
-// cores (42 % busy) nor the LDS (its reads, 3.9 ns each per CU, fill 37 % of the time) bind it: two
-// workgroups on a CU, each with one stage on its way, leave the waves waiting for 44 % of their lives.
+// WM x WN waves cover a tile, each 32 RT x 32 CT of it by v_mfma_f32_32x32x16_f16.  Both operands come to LDS 64
+// channels at a time by asynchronous copies into a ring of RING stages, all but the current one on their way while it
+// is multiplied; a stage costs one counted wait and one barrier.  What binds it is the round trip of a stage:
+// two workgroups of 128 x 128 on a CU with one stage on its way each left the waves waiting for 44 % of their
+// lives, and a launch that gives a CU one took as long as two (640 x 4096 x 4096 65 us).  A workgroup that has the
+// CU to itself, 8 waves and three to five stages on their way does it in 39, and leaves the choice of the tile to the
+// number of workgroups.  The next step's fragments are read, and a stage's copies started, between the products of
+// the current one (SPREAD: over how many of the stage's 4 steps; all at once they hold the address unit up: 1280 x 4096 x
+// 11008 178 us with one stage on its way, 160 spread over three steps and two on their way).  1280 rows: 1.12 PFLOP/s at 12288 x 4096,
+// 1.03 at 22016 x 4096, 0.69 and 0.73 at 4096 x 4096 and 4096 x 11008 (0.91, 0.86, 0.62 and 0.67 before).
 // LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
 // Lane l supplies 8 consecutive k of row (l % 32) to both operands (k slots 8 (l / 32) .. +7 of the
 // step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.
 // Rows beyond M and N repeat the last one and are not stored.  Needs N % 64 == 0, K % 16 == 0, x and W at
 // multiples of 16 bytes; residual and y may lie anywhere.
-__global__ __launch_bounds__(256, 2) void fp_gemm_kernel(const f16 *__restrict__ x, int M, int K,
-                                                         const f16 *__restrict__ W, int N,
-                                                         const f16 *__restrict__ residual,
-                                                         f16 *__restrict__ y, int tiles_m, int tiles_n)
+template <int WM, int WN, int RT, int CT, int RING, int SPREAD>
+__global__ __launch_bounds__(64 * WM * WN, 2) void fp_gemm_kernel(const f16 *__restrict__ x, int M, int K,
+                                                                    const f16 *__restrict__ W, int N,
+                                                                    const f16 *__restrict__ residual,
+                                                                    f16 *__restrict__ y, int tiles_m, int tiles_n)
 {
-    constexpr int TILE = 128 * 8;                   // 16-byte pieces of one operand per stage
-    constexpr int FROW = 128 + 4;                   // floats per staged output row
-    __shared__ uint4 lds[2][2][TILE];               // [buffer][x, W]
-    static_assert(64 * FROW * 4 <= (int)sizeof(lds), "the output strip fits");
+    constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * RT * WM, BN = 32 * CT * WN;
+    constexpr int KS = 64, PR = KS / 8, STG = (BM + BN) * PR, COPIES = STG / NT;       // a stage in 16-byte pieces, pieces per thread
+    constexpr int FROW = BN + 4;                                // floats per staged output row
+    static_assert(STG % NT == 0 && RING >= 2 && 32 * WM * (BN / 8) % NT == 0, "whole pieces per thread, copies in flight");
+    constexpr int STRIP = 32 * WM * FROW / 4;
+    __shared__ uint4 lds[RING * STG > STRIP ? RING * STG : STRIP];      // [stage][x rows, W rows][8]
     const unsigned lds0 = lds_address(lds);
     int tm, tn;
     tile_of(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tm, tn);
-    const int m0 = tm * 128, n0 = tn * 128;
+    const int m0 = tm * BM, n0 = tn * BN;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-    // this thread's pieces of a stage: rows (tid + 256 j) / 8 of both operands
-    unsigned ox[4], ow[4], pk[4];
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+    // this thread's pieces of a stage: rows (tid + NT j) / 8 of x, then W
+    unsigned row_at[COPIES], piece[COPIES];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = (tid + 256 * j) >> 3, p = (tid & 7) ^ (row & 7);
-        ox[j] = 2u * (unsigned)(min(m0 + row, M - 1) - m0) * (unsigned)K;
-        ow[j] = 2u * (unsigned)(min(n0 + row, N - 1) - n0) * (unsigned)K;
-        pk[j] = 16 * p;
+    for (int j = 0; j < COPIES; ++j) {
+        const int r = (tid + NT * j) / PR;
+        row_at[j] = 2u * (unsigned)(r < BM ? min(m0 + r, M - 1) - m0 : min(n0 + r - BM, N - 1) - n0) * (unsigned)K;
+        piece[j] = 16 * ((tid & 7) ^ (r & 7));
     }
     const f16 *xb = x + (size_t)m0 * K, *wb = W + (size_t)n0 * K;
-    auto load = [&](int buf, int k0) {
-        const unsigned left = 2u * (unsigned)(K - k0) - 16;      // last whole piece of a row (a ragged end repeats it)
+    const int stages = (K + KS - 1) / KS;
+    auto load = [&](int stage, int slot, int from, int to) {
+        const int k0 = KS * min(stage, stages - 1);                     // (stages past the end keep the count of copies)
+        const unsigned left = 2u * (unsigned)(K - k0) - 16;             // last whole piece of a row (a ragged end repeats it)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const unsigned dst = lds0 + (unsigned)(buf * 2 * TILE * 16 + (wave + 4 * j) * 1024);
-            copy16_to_lds(xb + k0, ox[j] + min(pk[j], left), dst);
-            copy16_to_lds(wb + k0, ow[j] + min(pk[j], left), dst + TILE * 16);
-        }
+        for (int j = from; j < to; ++j)
+            copy16_to_lds((64 / PR * (wave + NW * j) < BM ? xb : wb) + k0, row_at[j] + min(piece[j], left),
+                          lds0 + (unsigned)(slot * STG * 16 + (wave + NW * j) * 1024));
     };
-    f32x16 acc[2][2];
+    f32x16 acc[RT][CT];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < CT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    load(0, 0);
-    drain();
-    __syncthreads();
-    int buf = 0;
+#pragma unroll
+    for (int st = 0; st < RING - 1; ++st) load(st, st, 0, COPIES);
+    int slot = 0;
 #pragma unroll 1
-    for (int k0 = 0; k0 < K; k0 += 64) {
-        if (k0 + 64 < K) load(buf ^ 1, k0 + 64);
-        const uint4 *ax = lds[buf][0] + (64 * wm + l32) * 8, *bx = lds[buf][1] + (64 * wn + l32) * 8;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            if (s && k0 + 16 * s >= K) break;
-            const int p = (2 * s + half) ^ (l32 & 7);
-            f16x8 a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = *reinterpret_cast<const f16x8 *>(ax + 256 * i + p);
-                b[i] = *reinterpret_cast<const f16x8 *>(bx + 256 * i + p);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        drain();
+    for (int st = 0; st < stages; ++st) {
+        // this wave's copies of the stage have arrived, RING - 2 later stages may be on their way; behind the barrier so have
+        // all waves', and the slot read before it is free
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * COPIES) : "memory");
         __syncthreads();
-        buf ^= 1;
+        const int free = slot ? slot - 1 : RING - 1;
+        const uint4 *ax = lds + slot * STG + (32 * RT * wm + l32) * PR, *bx = lds + slot * STG + (BM + 32 * CT * wn + l32) * PR;
+        f16x8 a[2][RT], b[2][CT];
+        auto fragments = [&](int s) {
+            const int p = (2 * s + half) ^ (l32 & 7);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) b[s & 1][j] = *reinterpret_cast<const f16x8 *>(bx + 32 * PR * j + p);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) a[s & 1][i] = *reinterpret_cast<const f16x8 *>(ax + 32 * PR * i + p);
+        };
+        fragments(0);
+#pragma unroll
+        for (int s = 0; s < KS / 16; ++s) {
+            if (s && KS * st + 16 * s >= K) break;
+            if (s + 1 < KS / 16) fragments(s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+#pragma unroll
+                for (int j = 0; j < CT; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[s & 1][i], b[s & 1][j], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                constexpr int AT = RT * SPREAD;
+                const int t = s * RT + i;
+                if (t < AT) load(st + RING - 1, free, COPIES * t / AT, COPIES * (t + 1) / AT);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        slot = slot + 1 < RING ? slot + 1 : 0;
     }
-    // 2 x 32 rows at a time through LDS, so that a thread finishes 8 neighbouring columns of a row
+    drain();                                          // (the copies past the end)
+    __syncthreads();
+    // WM x 32 rows at a time through LDS, so that a thread finishes 8 neighbouring columns of a row
     float *stage = reinterpret_cast<float *>(lds);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < RT; ++i) {
         if (i) __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < CT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                stage[(32 * wm + 8 * (r >> 2) + 4 * half + (r & 3)) * FROW + 64 * wn + 32 * j + l32] = acc[i][j][r];
+                stage[(32 * wm + 8 * (r >> 2) + 4 * half + (r & 3)) * FROW + 32 * CT * wn + 32 * j + l32] = acc[i][j][r];
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int idx = k * 256 + tid, row = idx >> 4, c = 8 * (idx & 15);
-            const int m = m0 + 64 * (row >> 5) + 32 * i + (row & 31), n = n0 + c;
+        for (int k = 0; k < 32 * WM * (BN / 8) / NT; ++k) {
+            const int idx = k * NT + tid, row = idx / (BN / 8), c = 8 * (idx % (BN / 8));
+            const int m = m0 + 32 * RT * (row >> 5) + 32 * i + (row & 31), n = n0 + c;
             if (m >= M || n >= N) continue;
             const float4 lo = *reinterpret_cast<const float4 *>(stage + row * FROW + c);
             const float4 hi = *reinterpret_cast<const float4 *>(stage + row * FROW + c + 4);
@@ -290,8 +307,20 @@ inline size_t up256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 int fp_gemm(const f16 *x, int M, int K, const void *W, int N, const f16 *residual, f16 *y, hipStream_t st)
 {
-    const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
-    fp_gemm_kernel<<<dim3(tiles_m * tiles_n), dim3(256), 0, st>>>(x, M, K, (const f16 *)W, N, residual, y, tiles_m, tiles_n);
+    const auto launch = [&](auto kernel, int bm, int bn) {
+        const int tiles_m = (M + bm - 1) / bm, tiles_n = (N + bn - 1) / bn;
+        kernel<<<dim3(tiles_m * tiles_n), dim3(512), 0, st>>>(x, M, K, (const f16 *)W, N, residual, y, tiles_m, tiles_n);
+    };
+    // By rounds of 256 workgroups, in us for 4096 channels (measured over 64 to 2560 rows, 4096 to 22016 columns and both
+    // depths of a 7B block: a round of the smaller tiles is shorter by less than they are smaller)
+    const auto rounds = [&](int bm, int bn) {
+        return (int)(((long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256);
+    };
+    const int t64 = 30 * rounds(64, 128), t128 = 38 * rounds(128, 128), t256 = 57 * rounds(128, 256), t512 = 108 * rounds(256, 256);
+    if (t64 <= min(min(t128, t256), t512)) launch(fp_gemm_kernel<2, 4, 1, 1, 6, 3>, 64, 128);
+    else if (t128 <= min(t256, t512)) launch(fp_gemm_kernel<2, 4, 2, 1, 4, 3>, 128, 128);
+    else if (t256 <= t512) launch(fp_gemm_kernel<2, 4, 2, 2, 3, 3>, 128, 256);
+    else launch(fp_gemm_kernel<2, 4, 4, 2, 2, 1>, 256, 256);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

@@ -80,6 +80,20 @@ def test_fp_block_against_oracle(qb, d, H, Hkv, dh, F, B, N):
     assert abs(np.linalg.norm(got) / np.linalg.norm(want) - 1.0) < 1e-3
 
 
+@pytest.mark.parametrize("B", [3, 20, 41])
+def test_fp_block_tiles_give_the_same_bits(qb, B):
+    """A sequence of 125 tokens alone (64 x 128 tiles) and in a batch, whose 375 to 5125 rows take the other tiles, up to 256 x
+    256: sums run over the channels in one order in all of them.  1376 channels end inside a stage."""
+    d, H, Hkv, dh, F, N = 1024, 8, 8, 128, 1376, 125
+    _, _, _, Lf, _, _ = build_pair(d, H, Hkv, dh, F, 2 * N + 8, seed=77)
+    x, pos = inputs(B, N, d, seed=B)
+    batch = host(Lf.forward(dev(x), dev(pos), B, N)).view(np.uint16).reshape(B, N, d)
+    for b in (0, B // 2, B - 1):
+        rows = slice(b * N, (b + 1) * N)
+        alone = host(Lf.forward(dev(np.ascontiguousarray(x.reshape(B * N, d)[rows])), dev(pos[rows]), 1, N))
+        assert np.array_equal(alone.view(np.uint16).reshape(N, d), batch[b])
+
+
 @pytest.mark.parametrize("off", [1, 4, 7])
 def test_fp_block_takes_tensors_at_any_address(qb, off):
     """x, x_out and the gammas that start `off` elements behind an aligned address (2-byte, 8-byte and odd offsets
