@@ -89,23 +89,27 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
-// block-wide (blockDim.x = 64*NW) max of a float and sum of up to two doubles;
-// every thread gets the result.  `sm` needs 3*NW doubles of LDS.
-template <int NW>
-__device__ __forceinline__ void block_max_sum2(float &mx, double &s0, double &s1, double *sm)
+// block-wide (blockDim.x = 64*NW) max of a float and/or sum of a double; every thread gets the result.  `sm` needs
+// 2*NW doubles of LDS.
+template <int NW, bool MAX, bool SUM>
+__device__ __forceinline__ void block_max_sum(float &mx, double &sum, double *sm)
 {
-    mx = wave_max(mx);
-    s0 = wave_sum(s0);
-    s1 = wave_sum(s1);
-    int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if (MAX) mx = wave_max(mx);
+    if (SUM) sum = wave_sum(sum);
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     __syncthreads();          // protect sm against the previous use
-    if (l == 0) { sm[w] = (double)mx; sm[NW + w] = s0; sm[2 * NW + w] = s1; }
+    if (l == 0) {
+        if (MAX) sm[w] = (double)mx;
+        if (SUM) sm[NW + w] = sum;
+    }
     __syncthreads();
-    float m = (float)sm[0];
-    double a = sm[NW], b = sm[2 * NW];
+    if (MAX) mx = (float)sm[0];
+    if (SUM) sum = sm[NW];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) { m = fmaxf(m, (float)sm[i]); a += sm[NW + i]; b += sm[2 * NW + i]; }
-    mx = m; s0 = a; s1 = b;
+    for (int i = 1; i < NW; ++i) {
+        if (MAX) mx = fmaxf(mx, (float)sm[i]);
+        if (SUM) sum += sm[NW + i];
+    }
 }
 
 // Consecutive workgroups go round-robin over the 8 XCDs, each with its own L2: this gives each XCD a contiguous range

@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
     const uint4 *xs = reinterpret_cast<const uint4 *>(x + srow * d);
     const uint4 *os = reinterpret_cast<const uint4 *>(o + srow * d);
     const bool want_o = o_out || oq_out.q;
-    __shared__ double sm[12];
+    __shared__ double sm[8];
     uint4 xv[NCH];
     Pack16 v[NCH];
     uint32_t kw[NCH], vw[NCH];
@@ -236,8 +236,8 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
         if (rows_out) rows_out[drow] = src;
     }
     if (oq_out.q) {
-        double z0 = 0.0, z1 = 0.0;
-        block_max_sum2<4>(a, z0, z1, sm);
+        double none = 0.0;
+        block_max_sum<4, true, false>(a, none, sm);
         float s;
         quantize_cached_row<false, ROW_THREADS, NCH>(v, n16, tid, a, row_out(oq_out, drow, n16), s);
         if (tid == 0) os_out[drow] = s;

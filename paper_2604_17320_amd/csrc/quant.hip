@@ -192,14 +192,18 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
 // finished sooner by a whole workgroup.
 #define ROW_WAVE_MIN_ROWS 2048
 
-template <int GROUP>
-__device__ __forceinline__ void group_reduce(float &mx, double &s0, double &s1, double *sm)
+template <int GROUP, bool MAX, bool SUM>
+__device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
 {
-    if (GROUP == 64) { mx = wave_max(mx); s0 = wave_sum(s0); s1 = wave_sum(s1); }
-    else block_max_sum2<4>(mx, s0, s1, sm);
+    if (GROUP == 64) {
+        if (MAX) mx = wave_max(mx);
+        if (SUM) sum = wave_sum(sum);
+    } else {
+        block_max_sum<4, MAX, SUM>(mx, sum, sm);
+    }
 }
 #define ROW_PROLOGUE()                                                                         \
-    __shared__ double sm[12];                                                                  \
+    __shared__ double sm[8];                                                                   \
     const int lane = threadIdx.x % GROUP;                                                      \
     const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (ROW_THREADS / GROUP) + threadIdx.x / GROUP; \
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
@@ -232,11 +236,10 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
             }
         }
     }
-    double zero = 0.0;
-    group_reduce<GROUP>(a, ss, zero, sm);
+    group_reduce<GROUP, true, WANT_METRICS>(a, ss, sm);
     float s;
     double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
-    if (WANT_METRICS) { float dummy = 0.0f; group_reduce<GROUP>(dummy, rs, zero, sm); }
+    if (WANT_METRICS) { float dummy = 0.0f; group_reduce<GROUP, false, true>(dummy, rs, sm); }
     if (lane == 0) {
         if (scale) scale[row] = s;
         if (WANT_METRICS) {
@@ -285,8 +288,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
             }
         }
     }
-    double zero = 0.0;
-    group_reduce<GROUP>(a_raw, ss, zero, sm);
+    group_reduce<GROUP, WANT_METRICS, true>(a_raw, ss, sm);
     if (!GAINS_EARLY) {
         // the row stays packed (32 registers for 4096 columns): without this the compiler keeps the 64
         // converted floats of the first pass alive for the second one
@@ -326,7 +328,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
         // keep the compiler from hoisting every chunk's gain loads to the top (that costs 64 registers)
         if (!GAINS_EARLY) __builtin_amdgcn_sched_barrier(0);
     }
-    group_reduce<GROUP>(a, rs, zero, sm);
+    group_reduce<GROUP, true, WANT_METRICS>(a, rs, sm);
     float s;
     quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
     if (lane == 0) {
@@ -379,8 +381,8 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
             if (z_out) reinterpret_cast<uint4 *>(z_out + (size_t)row * F)[c] = v[r].u;
         }
     }
-    double z0 = 0.0, z1 = 0.0;
-    group_reduce<GROUP>(a, z0, z1, sm);
+    double none = 0.0;
+    group_reduce<GROUP, true, false>(a, none, sm);
     float s;
     quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
     if (lane == 0) scale[row] = s;
