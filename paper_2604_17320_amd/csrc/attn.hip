@@ -62,6 +62,13 @@ __device__ __forceinline__ int piece_address(int r, int hl) { return r * (2 * DH
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
+// the larger of a lane's value and that of the lane 32 away, without the trip through LDS of a shuffle
+__device__ __forceinline__ float halves_max(float v)
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+
 template <int DH>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
@@ -117,13 +124,24 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
         const char *kt = sm[buf][0], *vt = sm[buf][1];
 
         f32x16 s[2];
+        // (fragments a step ahead of their products, and the row maximum without LDS: they are on the wave's one chain; 640
+        // tokens, 32 heads 18.5 -> 17.2 us, 4 x 2944, 40 heads 440 -> 434)
+        f16x8 kf[2][2];
+        auto fragments = [&](int t) {
 #pragma unroll
-        for (int t = 0; t < T; ++t)
+            for (int sb = 0; sb < 2; ++sb)
+                kf[t & 1][sb] = *reinterpret_cast<const f16x8 *>(kt + (k_at ^ 32 * t) + 32 * sb * (2 * DH));
+        };
+        fragments(0);
 #pragma unroll
-            for (int sb = 0; sb < 2; ++sb) {
-                f16x8 kf = *reinterpret_cast<const f16x8 *>(kt + (k_at ^ 32 * t) + 32 * sb * (2 * DH));
-                s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[t], t ? s[sb] : zero, 0, 0, 0);
-            }
+        for (int t = 0; t < T; ++t) {
+            if (t + 1 < T) fragments(t + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+                s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf[t & 1][sb], qf[t], t ? s[sb] : zero, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         // the maximum is taken on the raw logits (the scale is positive) and the scale is folded into
         // the exponent's fused multiply-add: exp2(s * scale - m), one instruction per score less
         float mx = -INFINITY;
@@ -141,7 +159,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = halves_max(mx);
         float m_new = fmaxf(m_run, mx * scale_log2);
         float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
