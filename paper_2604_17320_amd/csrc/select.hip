@@ -6,7 +6,8 @@
 // registers: four per metric, both percentile bounds in the same passes, then all sixteen for the top-k; the
 // counters are integers, so the result does not depend on execution order.  576 / 2880 tokens (32 / 40
 // heads): 25 / 113 us with one wave per bound and per top-k and the head means of the attention cues taken here,
-// 10 / 19 us so, with the head means taken before it.
+// 10 / 19 us so, with the head means taken before it.  A select ends as soon as at most 64 keys share a rank's digits: one
+// wave ranks those (104 / 576 / 2880 tokens 8.6 / 9.7 / 19.1 -> 7.0 / 9.0 / 18.8 us).
 #include "common.h"
 #include "internal.h"
 
@@ -49,7 +50,7 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-constexpr int SCORE_THREADS = 1024, SCORE_WAVES = SCORE_THREADS / 64, SELECT_RANGE = 2 * SCORE_WAVES + 16;
+constexpr int SCORE_THREADS = 1024, SCORE_WAVES = SCORE_THREADS / 64, SELECT_RANGE = 2 * SCORE_WAVES + 32;
 
 // Exact rank[r]-th smallest (0-based) of the n keys of a group of GT threads (key j of thread t of the group is number
 // t + GT j), for NR ranks at once; all SCORE_THREADS threads call this, SCORE_THREADS / GT groups work side by
@@ -94,7 +95,14 @@ __device__ void group_select(const uint32_t (&key)[PERG], int n, const int (&ran
     int remaining[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) { prefix[r] = kmin & mask; remaining[r] = rank[r]; }
-    for (int pass = 0, at = 0; 8 * pass < most; ++pass) {
+    // per rank of every group: digit and rank among its keys, whether those are too many for a wave, the result
+    int *found = reinterpret_cast<int *>(range) + 2 * SCORE_WAVES + 2 * NR * (tid / GT);
+    int *many = reinterpret_cast<int *>(range) + 2 * SCORE_WAVES + 16;
+    uint32_t *chosen = range + 2 * SCORE_WAVES + 24 + NR * (tid / GT);
+    constexpr int RANKS = NR * SCORE_WAVES / WPG;
+    bool few = false;
+    int *list = hist;                                // the counters cleared last
+    for (int pass = 0, at = 0; 8 * pass < most && !few; ++pass) {
         const int next = at == 2 ? 0 : at + 1, width = min(8, bits), shift = bits - width;
         int *h = hist + at * NR * 256, *hn = hist + next * NR * 256;
         const uint32_t digits = (1u << width) - 1;
@@ -110,20 +118,24 @@ __device__ void group_select(const uint32_t (&key)[PERG], int n, const int (&ran
         for (int i = gt; i < NR * 256; i += GT) hn[i] = 0;
         __syncthreads();
         // one wave per rank finds the digit (spread over the SIMDs)
-        int *found = reinterpret_cast<int *>(range) + 2 * SCORE_WAVES + 2 * NR * (tid / GT);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            if (width == 0 || (tid >> 6) % WPG != (NR * (tid / GT) + r) % WPG) continue;
+            if ((tid >> 6) % WPG != (NR * (tid / GT) + r) % WPG) continue;
+            if (width == 0) {                       // (all bits known: the key is the prefix)
+                if (lane == 0) many[NR * (tid / GT) + r] = 0;
+                continue;
+            }
             const i32x4 c = *reinterpret_cast<const i32x4 *>(h + (split ? 256 * r : 0) + 4 * lane);
             const int sum = c[0] + c[1] + c[2] + c[3], incl = wave_incl_scan(sum), excl = incl - sum;
-            int left = remaining[r] - excl, digit = 4 * lane;
+            int left = remaining[r] - excl, digit = 4 * lane, keys = c[0];
             const bool mine = left >= 0 && remaining[r] < incl;         // exactly one lane
-            if (left >= c[0]) { left -= c[0]; ++digit;
-                if (left >= c[1]) { left -= c[1]; ++digit;
-                    if (left >= c[2]) { left -= c[2]; ++digit; } } }
+            if (left >= c[0]) { left -= c[0]; ++digit; keys = c[1];
+                if (left >= c[1]) { left -= c[1]; ++digit; keys = c[2];
+                    if (left >= c[2]) { left -= c[2]; ++digit; keys = c[3]; } } }
             if (mine) {
                 found[2 * r] = digit;
                 found[2 * r + 1] = left;
+                many[NR * (tid / GT) + r] = keys > 64 && shift > 0;
             }
         }
         __syncthreads();
@@ -136,10 +148,43 @@ __device__ void group_select(const uint32_t (&key)[PERG], int n, const int (&ran
             }
             bits = shift;
         }
+        few = true;
+#pragma unroll
+        for (int i = 0; i < RANKS; ++i) few = few && !many[i];
+        list = hn;
         at = next;
     }
+    // At most 64 keys share a rank's digits, mostly after one or two of four passes: a wave ranks them among each other
+    if (few) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) result[r] = prefix[r];
+        for (int r = 0; r < NR; ++r) {
+            if (bits == 0) {
+                if (gt == 0) chosen[r] = prefix[r];
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < PERG; ++j)
+                if (gt + GT * j < n && (key[j] & mask) == prefix[r])
+                    list[256 * r + atomicAdd(&list[256 * r + 255], 1)] = (int)key[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            if (bits == 0 || (tid >> 6) % WPG != (NR * (tid / GT) + r) % WPG) continue;
+            const int keys = __builtin_amdgcn_readfirstlane(list[256 * r + 255]);
+            const uint32_t mine = (uint32_t)list[256 * r + min(lane, keys - 1)];
+            int below = 0, upto = 0;
+            for (int i = 0; i < keys; ++i) {
+                const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+                below += k < mine;
+                upto += k <= mine;
+            }
+            if (below <= remaining[r] && remaining[r] < upto) chosen[r] = mine;      // (lanes of equal keys agree)
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) result[r] = few ? chosen[r] : prefix[r];
 }
 
 // G (Eq. 7): clip to the nearest-rank percentiles and rescale to [0, 1]

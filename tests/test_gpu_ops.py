@@ -410,3 +410,18 @@ def test_topk_prune_bit_exact(qb, B, Nv):
     assert np.array_equal(host(out), np.tile(np.arange(k, dtype=np.int32), (B, 1)))
     with pytest.raises(qb.QuotaError):
         qb.quota_topk_prune(scd, B, 8200, 3, out)
+
+
+@pytest.mark.parametrize("close,copies", [(63, 1), (64, 1), (65, 1), (64, 4), (200, 1), (200, 150)])
+def test_topk_prune_where_many_keys_share_their_digits(qb, close, copies):
+    """Keys that agree in their first digits, around the 64 that one wave ranks and more, with ties among them."""
+    r = wl.rng(72, "topk-close", close, copies)
+    Nv = 500
+    sc = np.concatenate([np.float32(0.75) + np.arange(close, dtype=np.float32) // copies * np.float32(2.0 ** -24),
+                         r.uniform(-3e4, 3e4, Nv - close).astype(np.float32)])
+    sc = r.permutation(sc).astype(np.float32)[None]
+    above = int((sc > 0.8).sum())
+    for K in (above, above + 1, above + close // 2, above + close - 1, above + close, above + close + 1):
+        out = torch.full((1, K), -1, dtype=torch.int32, device="cuda")
+        qb.quota_topk_prune(dev(sc), 1, Nv, K, out)
+        assert np.array_equal(host(out), oracle.topk(sc, K))
