@@ -516,7 +516,7 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(kernel_id, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md +
-                       (qe ? Md * (Nd / 3) * (7 + 1.0 / 16) + 4 * Md : 2.0 * Md * Nd * (res ? 2 : 1)), st);
+                       (qe ? Md * (Nd / 3) * (7 + 1.0 / 16) + 4 * Md : 2.0 * Md * (ldy < W->N ? ldy : Nd) * (res ? 2 : 1)), st);
     static const quota_qkv_epilogue no_qe = {};
     auto aligned = [](const void *p, int ld) { return ld % 8 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
     const int vec = (y && aligned(y, ldy) ? 1 : 0) | (res && aligned(res, ldr) ? 2 : 0);

@@ -79,7 +79,7 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
                                 const void *residual_opt, int ldr, hipStream_t st);
 int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *z_f16, hipStream_t st);
 
-// GEMM of at most 16 rows (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
+// GEMM of at most 16 rows, or as fragments 32 (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
 // quota_internal_rows16_quantizes accepts: as they are, or through RMSNorm.  frag_silu and glu: the gate/up projection,
 // z [M][N / 2] = SiLU(gate) * up.
 enum quota_rows16_format { QUOTA_ROWS16_A8, QUOTA_ROWS16_PACKED, QUOTA_ROWS16_FRAG };

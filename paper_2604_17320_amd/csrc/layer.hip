@@ -114,9 +114,9 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
                                         w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st);
 }
 
-// RMSNorm, quantizer, GEMM; SwiGLU product, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_FRAG rows go
+// RMSNorm, quantizer, GEMM; SwiGLU product, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_FRAG rows (rows16.hip: why) go
 // through the few-row GEMM's own format, and a few leave the quantizer to the GEMM.
-#define ROWS_FRAG 16
+#define ROWS_FRAG 32
 static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
                         const quota_weights *W, void *y, int ldy, hipStream_t st)
 {

@@ -12,8 +12,8 @@
 // Where a quantized row goes: packed int4 (the public format, two codes per byte), the GEMM's A8 format --
 // e4m3 bytes, every 8 codes as evens then odds, each row zero-padded to whole 128-channel groups, and behind the rows
 // (if quota_a8_starts) what a sum of products with weights c + 8 starts from, [group][row] -- or, for at
-// most 16 rows, packed int4 as the few-row GEMM's fragments: 1 KB per group, the 32 codes number q of row m's
-// 128 at 16-byte piece 16 q + m.  A null pointer drops the output.
+// most 32 rows, packed int4 as the few-row GEMM's fragments: per 16 rows 1 KB per group, the 32 codes number q of row m's
+// 128 at 16-byte piece 16 q + m % 16.  A null pointer drops the output.
 struct RowOutPacked {
     static constexpr bool A8 = false, STARTS = false, MANY = true;       // MANY: launches of any number of rows
     uint32_t *q;
@@ -53,7 +53,10 @@ __host__ __device__ __forceinline__ RowOutPacked row_out(RowOutPacked o, size_t 
 {
     return RowOutPacked{o.q ? o.q + row * nchunk : nullptr};
 }
-__host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row, int) { return RowOutFrag{o.q + 4 * row}; }
+__host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row, int nchunk)
+{
+    return RowOutFrag{o.q + (row >> 4) * ((nchunk + 15) >> 4) * 256 + 4 * (row & 15)};
+}
 __host__ __device__ __forceinline__ RowOutA8 row_out(RowOutA8 o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;

@@ -1,4 +1,4 @@
-// W4A4 GEMM for at most 16 rows (the decode step): weight streaming, bound by HBM (0.52 bytes per weight).
+// W4A4 GEMM for at most 16 rows, as fragments 32 (the decode step): weight streaming, 0.52 bytes per weight.
 //
 // There are too few outputs to fill the chip with one accumulation chain per wave, and the fp32 chain over
 // groups cannot be split.  The exact group sums can: in a round the 8 waves of a workgroup take U groups
@@ -11,7 +11,9 @@
 // of them; 16 x 4096 x 11008: 11.0 us with byte activations, 9.7 packed).  Inside a layer the quantizer leaves
 // them as the fragments that the lanes want: a KB of 16 different rows takes the CU 27 ns to load, a contiguous
 // one 7 (16 x 12288 x 4096: 8.6 -> 7.8 us).
-// NB = 16-column blocks per workgroup.
+// NB = 16-column blocks per workgroup, RB = 16-row blocks.  With 17 to 32 rows the tiles of gemm.hip start 64 workgroups for
+// 4096 columns: 32 x 4096 x 11008 22 us and 13.7 here, 32 x 4096 x 4096 11.0 and 8.5; a 7B decode layer at batch 32 100 -> 71 us
+// (a GQA one of 3584 channels 118 -> 79).
 //
 // Few rows (MODE > FRAG) also bring their own quantizer: every workgroup normalises / quantizes
 // the whole rows for itself while its first weights are on their way.  That is a few thousand elements per
@@ -167,7 +169,8 @@ __device__ __forceinline__ void unsigned_e4m3(const uint4 &p, uint4 &lo, uint4 &
 
 // GLU: the columns are gate | up, NB = 2 and a workgroup has 16 of each, of the same channels: it stores SiLU(gate) * up of
 // their fp16 roundings, y is [M][N / 2].
-template <int NB, int U, int MODE, int NC, bool GLU>
+// RB: 16-row blocks, 2 for fragments of 17 to 32 rows: a weight read serves both.
+template <int NB, int U, int MODE, int NC, bool GLU, int RB>
 __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     RowsIn in, int M, int K, int G, const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N,
     f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, int code_stride)
@@ -178,9 +181,9 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     constexpr int SROW = R + 8;                     // halves per column of staged scales (16-byte pieces, padded)
     constexpr bool FEW = MODE > ROWS_FRAG;          // at most 4 rows: lanes 0 to 15 hold the sums that count
     constexpr int XS = FEW ? 64 : 256;              // sums of a group and block
-    constexpr int OPT = GLU ? 2 : 1;                // outputs per owner thread
-    constexpr int BUF = R * NB * XS + 8 * NB * SROW;        // floats of one exchange buffer
-    static_assert(NB <= 2 && (!GLU || NB == 2), "an owner per output");
+    constexpr int OPT = GLU || RB == 2 ? NB : 1;    // outputs per owner thread
+    constexpr int BUF = R * NB * RB * XS + 8 * NB * SROW;   // floats of one exchange buffer
+    static_assert(NB <= 2 && (!GLU || NB == 2) && (RB == 1 || (RB == 2 && MODE == ROWS_FRAG)), "an owner per output");
     extern __shared__ __align__(16) uint4 lds_rows[];
     float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
     float *row_scale = xbuf + 2 * BUF;                                            // [16]
@@ -189,10 +192,11 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // chain ownership: thread t owns the output(s) held by (block t / XS, or both for GLU; register oreg, lane ol)
-    const int oj = GLU ? 0 : tid / XS, oreg = tid / (XS / 4) & 3, ol = tid % (XS / 4);
-    const bool owner = XS * NB / OPT >= RT_THREADS || tid < XS * NB / OPT;
-    const int om = 4 * (ol >> 4) + oreg;
+    // chain ownership: thread t owns the output(s) held by (block t / XS, or both for GLU and of row block t / XS for RB = 2;
+    // register oreg, lane ol)
+    const int oi = RB == 2 ? tid / XS : 0, oj = GLU || RB == 2 ? 0 : tid / XS, oreg = tid / (XS / 4) & 3, ol = tid % (XS / 4);
+    const bool owner = XS * NB * RB / OPT >= RT_THREADS || tid < XS * NB * RB / OPT;
+    const int om = 16 * oi + 4 * (ol >> 4) + oreg;
     const int C = GLU ? N >> 1 : N;                 // output columns
     const int up = GLU ? C : 16;                    // from a column of the first block to the second's
     float y32[OPT];
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 
     const size_t arow_bytes = MODE == ROWS_PACKED ? (size_t)(K >> 1) : (size_t)128 * (G | 1);
     const uint8_t *arow = MODE <= ROWS_PACKED ? in.qa + (size_t)min(c16, M - 1) * arow_bytes : nullptr;
-    uint4 ra[U][MODE == ROWS_A8 ? 2 : 1], rb[U][NB];
+    uint4 ra[U][MODE == ROWS_A8 ? 2 : RB], rb[U][NB];
     uint32_t rsv[SPT];
     auto fetch = [&](int n0, int r0) {
 #pragma unroll
@@ -211,7 +215,8 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
             for (int j = 0; j < NB; ++j) rb[u][j] = wg[4 * j * up + 4 * c16 + q];
             if (MODE == ROWS_FRAG) {
-                ra[u][0] = *reinterpret_cast<const uint4 *>(in.qa + (size_t)g * 1024 + 16 * lane);
+#pragma unroll
+                for (int i = 0; i < RB; ++i) ra[u][i] = *reinterpret_cast<const uint4 *>(in.qa + (size_t)(i * G + g) * 1024 + 16 * lane);
             } else if (MODE == ROWS_A8) {
                 const uint4 *ag = reinterpret_cast<const uint4 *>(arow + g * 128 + 32 * q);
                 ra[u][0] = ag[0];
@@ -237,34 +242,42 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
     while (true) {                                  // rounds of this workgroup's column blocks
         float *accs = xbuf + par * BUF;
-        f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * XS);
-        f32x4 acc[U][NB];
+        f16 *scs = reinterpret_cast<f16 *>(accs + R * NB * RB * XS);
+        f32x4 acc[U][NB][RB];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            uint4 a0, a1;
-            if constexpr (MODE == ROWS_A8) {
-                a0 = ra[u][0];
-                a1 = ra[u][1];
-            } else if constexpr (MODE == ROWS_PACKED || MODE == ROWS_FRAG) {
-                unsigned_e4m3(ra[u][0], a0, a1);
-            } else {
-                const int g = min(r0 + 8 * u + wave, G - 1);
-                const uint4 *ag = reinterpret_cast<const uint4 *>(codes + (size_t)min(c16, M - 1) * code_stride + g * 128 + 32 * q);
-                a0 = ag[0];
-                a1 = ag[1];
-            }
-            const i32x8 fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
             constexpr bool OFFSET_A = MODE == ROWS_PACKED || MODE == ROWS_FRAG;
             const float c0 = OFFSET_A ? 64.0f * 128.0f / F8_UNIT : 0.0f;
-            const f32x4 k4 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{c0, c0, c0, c0}, 0, 0, 0, 0, 0, 0);
+            i32x8 fa[RB];
+            f32x4 k4[RB];
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                uint4 a0, a1;
+                if constexpr (MODE == ROWS_A8) {
+                    a0 = ra[u][0];
+                    a1 = ra[u][1];
+                } else if constexpr (OFFSET_A) {
+                    unsigned_e4m3(ra[u][i], a0, a1);
+                } else {
+                    const int g = min(r0 + 8 * u + wave, G - 1);
+                    const uint4 *ag = reinterpret_cast<const uint4 *>(codes + (size_t)min(c16, M - 1) * code_stride + g * 128 + 32 * q);
+                    a0 = ag[0];
+                    a1 = ag[1];
+                }
+                fa[i] = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
+                k4[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i], minus8, f32x4{c0, c0, c0, c0}, 0, 0, 0, 0, 0, 0);
+            }
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
                 uint4 b0, b1;
                 unsigned_e4m3(rb[u][j], b0, b1);
                 const i32x8 fb = i32x8{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, (int)b1.x, (int)b1.y, (int)b1.z, (int)b1.w};
-                f32x4 k = k4;
-                if (OFFSET_A) k = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(minus8, fb, k, 0, 0, 0, 0, 0, 0);
-                acc[u][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, fb, k, 0, 0, 0, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    f32x4 k = k4[i];
+                    if (OFFSET_A) k = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(minus8, fb, k, 0, 0, 0, 0, 0, 0);
+                    acc[u][j][i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i], fb, k, 0, 0, 0, 0, 0, 0);
+                }
             }
         }
 #pragma unroll
@@ -286,22 +299,24 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (!FEW || lane < 16) accs[((8 * u + wave) * NB + j) * XS + i * (XS / 4) + lane] = acc[u][j][i];
+                for (int b = 0; b < RB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (!FEW || lane < 16) accs[(((8 * u + wave) * NB + j) * RB + b) * XS + i * (XS / 4) + lane] = acc[u][j][b][i];
         __syncthreads();        // (the other buffer's readers passed the one before)
         if (owner) {
 #pragma unroll
             for (int o = 0; o < OPT; ++o) {
                 const int j = o + oj;
                 const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + (16 * j + (ol & 15)) * SROW);
-                const float *ap = accs + j * XS + oreg * (XS / 4) + ol;
+                const float *ap = accs + (j * RB + oi) * XS + oreg * (XS / 4) + ol;
 #pragma unroll
                 for (int i8 = 0; i8 < U; ++i8) {
                     if (!FEW && r0 + 8 * i8 >= G) break;
                     const Pack16 s8 = sp[i8];
                     float sum[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) sum[i] = ap[(8 * i8 + i) * NB * XS];
+                    for (int i = 0; i < 8; ++i) sum[i] = ap[(8 * i8 + i) * NB * RB * XS];
                     __builtin_amdgcn_sched_barrier(0);          // one trip to LDS, not one per pair
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
@@ -309,14 +324,17 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                 }
             }
             if (last) {
-                const int on = blk * BC + 16 * oj + (ol & 15);
                 if (om < M) {
                     const float sa = MODE <= ROWS_FRAG ? in.sa[om] : row_scale[om];
-                    float v = y32[0] * (sa * F8_UNIT);
-                    if (res) v = v + (float)res[(size_t)om * ldr + on];
-                    f16 out = to_f16(v);
-                    if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * F8_UNIT)));
-                    y[(size_t)om * ldy + on] = out;
+#pragma unroll
+                    for (int o = 0; o < (GLU ? 1 : OPT); ++o) {
+                        const int on = blk * BC + 16 * (o + oj) + (ol & 15);
+                        float v = y32[o] * (sa * F8_UNIT);
+                        if (res) v = v + (float)res[(size_t)om * ldr + on];
+                        f16 out = to_f16(v);
+                        if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * F8_UNIT)));
+                        y[(size_t)om * ldy + on] = out;
+                    }
                 }
 #pragma unroll
                 for (int o = 0; o < OPT; ++o) y32[o] = 0.0f;
@@ -332,19 +350,19 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 // PER_CU: workgroups wanted per CU.  A launch asks for no more than the LDS has room for: what is left over would run in a
 // second round and quantize the rows once more.  <2, 2> takes 19.6 KB, 68.8 without a quantizer, and 128 G + 16
 // bytes a row.
-template <int NB, int U, int PER_CU, int MODE, int NC, bool GLU = false>
+template <int NB, int U, int PER_CU, int MODE, int NC, bool GLU = false, int RB = 1>
 int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr,
                   int code_stride, hipStream_t st)
 {
     constexpr int R = 8 * U;
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    const size_t lds = 2 * (R * NB * (MODE > ROWS_FRAG ? 256 : 1024) + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
-    if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC, GLU>>()) return QUOTA_ERR_HIP;
+    const size_t lds = 2 * (R * NB * RB * (MODE > ROWS_FRAG ? 256 : 1024) + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
+    if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB>>()) return QUOTA_ERR_HIP;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
-                   Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + 2.0 * Md * Nd * (res ? 2 : 1), st);
+                   Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + (GLU ? 1.0 : 2.0) * Md * Nd * (res ? 2 : 1), st);
     const int per_cu = min(PER_CU, (int)(160 * 1024 / lds));
-    w4a4_rows16_kernel<NB, U, MODE, NC, GLU><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
+    w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
         in, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr, code_stride);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
@@ -358,27 +376,27 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 // Workgroups walk over the columns.
 // Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
 // <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
-template <int MODE, int NC>
+template <int MODE, int NC, int RB = 1>
 int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int code_stride,
            hipStream_t st)
 {
     if (W->N <= 4096) {
         if constexpr (MODE != ROWS_RMSNORM)
-            if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
-        return launch_rows16<1, 2, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+            if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        return launch_rows16<1, 2, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }
     if constexpr (MODE <= ROWS_FRAG)
-        if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
-    return launch_rows16<2, 2, 2, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
+    return launch_rows16<2, 2, 2, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
 }
 
-template <int MODE, int NC>
+template <int MODE, int NC, int RB = 1>
 int rows16_glu(const RowsIn &in, int M, const quota_weights *W, f16 *z, int code_stride, hipStream_t st)
 {
     const int F = W->N / 2;
     if constexpr (MODE <= ROWS_FRAG)
-        if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC, true>(in, M, W, z, F, nullptr, 0, code_stride, st);
-    return launch_rows16<2, 2, 2, MODE, NC, true>(in, M, W, z, F, nullptr, 0, code_stride, st);
+        if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC, true, RB>(in, M, W, z, F, nullptr, 0, code_stride, st);
+    return launch_rows16<2, 2, 2, MODE, NC, true, RB>(in, M, W, z, F, nullptr, 0, code_stride, st);
 }
 
 // run(chunks per thread, bytes of a row of codes in LDS)
@@ -409,7 +427,9 @@ int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const f
     in.sa = sa;
     switch (format) {
     case QUOTA_ROWS16_A8: return rows16<ROWS_A8, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
-    case QUOTA_ROWS16_FRAG: return rows16<ROWS_FRAG, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+    case QUOTA_ROWS16_FRAG:
+        if (M > 16) return rows16<ROWS_FRAG, 1, 2>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+        return rows16<ROWS_FRAG, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
     default: return rows16<ROWS_PACKED, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
     }
 }
@@ -419,7 +439,7 @@ int quota_internal_rows16_frag_silu(const uint8_t *qf, const float *sa, int M, c
     RowsIn in = {};
     in.qa = qf;
     in.sa = sa;
-    return rows16_glu<ROWS_FRAG, 1>(in, M, W, (f16 *)z, 0, st);
+    return M > 16 ? rows16_glu<ROWS_FRAG, 1, 2>(in, M, W, (f16 *)z, 0, st) : rows16_glu<ROWS_FRAG, 1>(in, M, W, (f16 *)z, 0, st);
 }
 
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
