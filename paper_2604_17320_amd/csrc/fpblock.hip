@@ -16,11 +16,11 @@ namespace {
 // is multiplied; a stage costs one counted wait and one barrier.  What binds it is the round trip of a stage:
 // two workgroups of 128 x 128 on a CU with one stage on its way each left the waves waiting for 44 % of their
 // lives, and a launch that gives a CU one took as long as two (640 x 4096 x 4096 65 us).  A workgroup that has the
-// CU to itself, 8 waves and three to five stages on their way does it in 39, and leaves the choice of the tile to the
+// CU to itself, 8 waves and two to five stages on their way (one for 256 x 256) does it in 39, and leaves the choice of the tile to the
 // number of workgroups.  The next step's fragments are read, and a stage's copies started, between the products of
 // the current one (SPREAD: over how many of the stage's 4 steps; all at once they hold the address unit up: 1280 x 4096 x
-// 11008 178 us with one stage on its way, 160 spread over three steps and two on their way).  1280 rows: 1.12 PFLOP/s at 12288 x 4096,
-// 1.03 at 22016 x 4096, 0.69 and 0.73 at 4096 x 4096 and 4096 x 11008 (0.91, 0.86, 0.62 and 0.67 before).
+// 11008 178 us with one stage on its way, 160 spread over three steps and two on their way).  1280 rows: 1.06 PFLOP/s at 12288 x 4096,
+// 0.99 at 22016 x 4096, 0.70 and 0.73 at 4096 x 4096 and 4096 x 11008 (0.91, 0.86, 0.62 and 0.67 before).
 // LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
 // Lane l supplies 8 consecutive k of row (l % 32) to both operands (k slots 8 (l / 32) .. +7 of the
 // step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.

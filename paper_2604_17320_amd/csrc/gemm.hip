@@ -19,9 +19,8 @@
 // What bounds it: issued register to register, offset products, scale chain and unpack leave 78 % of the matrix rate to
 // the products at 8 x 4 blocks per wave, 71 at 4 x 4, 39 to 47 on the 32-row tiles; without the offset products the
 // launches of 1100 to 11264 rows take 2 to 9 % less (11264 x 12288 x 4096: 553 -> 532 us).  At a thousand rows and more
-// the kernels come near that (1280 x 22016 x 4096: matrix cores 57 % busy); on the rows of a pruned
-// prompt they are busy for 32 to 45 % and the waves wait for 25 to 47 % of their lives: one stage of
-// lookahead, and a wait for all of it.
+// the matrix cores are busy about half of the time; on the rows of a pruned prompt for 28 to 46 % of it, and the
+// waves wait for 24 to 38 % of their lives: one stage of lookahead, and a wait for all of it.
 //
 // Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes, row stride 128 (G | 1) (an
 // odd number of 128-byte lines: with a power of two the rows a tile reads together share one L2 channel), every 8
