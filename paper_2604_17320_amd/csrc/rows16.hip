@@ -183,7 +183,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     constexpr int XS = FEW ? 64 : 256;              // sums of a group and block
     constexpr int OPT = GLU || RB == 2 ? NB : 1;    // outputs per owner thread
     constexpr int BUF = R * NB * RB * XS + 8 * NB * SROW;   // floats of one exchange buffer
-    static_assert(NB <= 2 && (!GLU || NB == 2) && (RB == 1 || (RB == 2 && MODE == ROWS_FRAG)), "an owner per output");
+    static_assert((NB <= 2 || (FEW && !GLU)) && (!GLU || NB == 2) && (RB == 1 || (RB == 2 && MODE == ROWS_FRAG)), "an owner per output");
     extern __shared__ __align__(16) uint4 lds_rows[];
     float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
     float *row_scale = xbuf + 2 * BUF;                                            // [16]
@@ -372,7 +372,9 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 // over long rows, which stream longer than they start up; 32 beyond, two groups up to 8192 columns (at
 // most one workgroup per CU again), else three workgroups per CU with one group per wave, or, with a quantizer in
 // front, two per CU (one, where the rows leave no room for two) with two, so that fewer repeat its work (one row, gate/up
-// of 22016 columns: 10.8 us inside with two per CU, 12.8 with one, 13.8 with three).
+// of 22016 columns: 10.8 us inside with two per CU, 12.8 with one, 13.8 with three).  One or two rows take 48 columns where
+// that is one share for every CU and 32 are more, so that no CU has two (1 x 12288 x 4096 9.6 -> 8.4 us; with three rows
+// whose quantizer one workgroup per CU does alone a layer takes 1 % longer).
 // Workgroups walk over the columns.
 // Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
 // <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
@@ -385,6 +387,9 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
             if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
         return launch_rows16<1, 2, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }
+    if constexpr (MODE == ROWS_RMSNORM)
+        if (M <= 2 && W->N > 8192 && W->N <= 48 * 256 && W->N % 48 == 0)
+            return launch_rows16<3, 2, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
     if constexpr (MODE <= ROWS_FRAG)
         if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
     return launch_rows16<2, 2, 2, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
