@@ -73,9 +73,21 @@ struct DecodeNew {
 //            the tokens; the token lanes are summed through LDS in a fixed order at the end.
 // step_dev (optional): the cache length is len + *step_dev + 1 (a HIP-graph-captured decode loop keeps
 // its step count on the device).
-// SPLIT: n_split workgroups share a K/V head's rows, `tiles` tiles each; they leave unnormalized outputs,
+// SPLIT: n_split workgroups share a K/V head's rows, split_tiles() tiles each; they leave unnormalized outputs,
 // maxima and sums in `part` for decode_combine_kernel.
 constexpr int DEC_TILE = 512;
+constexpr int DEC_SPLIT_GRID = 256;
+// Tiles per workgroup when rows of n_tiles tiles are walked by `heads` workgroups, or by more where they are split.
+// Few heads over long caches: split so that every workgroup still has a CU to itself, if that saves two tiles of the walk or
+// more (a tile takes 4.5 us, the combining launch 3: 3 sequences of 4003 rows, 4 K/V heads: 44 us unsplit, 25 in
+// 384 workgroups of one tile, 19 in 192 of two).  The split is the order of the sums: it goes by the rows there are, on
+// the device too, so that a step of a captured loop leaves the bits of the call with a host-side length.  (A first part that
+// holds all the rows leaves the bits of the unsplit walk, the empty ones behind it count as nothing.)
+__host__ __device__ inline int split_tiles(int n_tiles, int heads)
+{
+    const int t = (n_tiles * heads + DEC_SPLIT_GRID - 1) / DEC_SPLIT_GRID;
+    return n_tiles - t >= 2 ? t : n_tiles;
+}
 constexpr int DEC_THREADS = 512;     // 8 waves: with two workgroups on a CU every SIMD has four waves to interleave
 // A head's sums per token lane on their way to one thread per channel: a row of token lanes per channel, read 16 bytes
 // at a time (4 bytes at a time 128 reads were 0.3 us longer), its start moved on by piece so that a wave's 64 writes
@@ -88,7 +100,7 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     const f16 *__restrict__ q, int d, int dkv, int rep, uint32_t *__restrict__ kc, f16 *__restrict__ ks,
     uint32_t *__restrict__ vc, f16 *__restrict__ vs, int capacity, int len,
     const int32_t *__restrict__ step_dev, int max_steps, f16 *__restrict__ o, int n_kv_heads, DecodeNew nw,
-    int n_split, int tiles, float *__restrict__ part)
+    int n_split, int heads, float *__restrict__ part)
 {
     constexpr int PPT = DH / 32;            // 16-byte pieces (lanes) per token and head
     constexpr int TP = DEC_THREADS / PPT;   // tokens per pass of the workgroup
@@ -121,7 +133,8 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     int L = len;
     if (step_dev) L += min(max(*step_dev, 0), max_steps - 1) + 1;      // the row this step appends included
     const int stored = FUSED ? L - 1 : L;   // rows read from the cache
-    const int t_begin = SPLIT ? sp * tiles * DEC_TILE : 0, t_end = SPLIT ? min(t_begin + tiles * DEC_TILE, L) : L;
+    const int share = SPLIT ? split_tiles((L + DEC_TILE - 1) / DEC_TILE, heads) * DEC_TILE : L;
+    const int t_begin = SPLIT ? sp * share : 0, t_end = SPLIT ? min(t_begin + share, L) : L;
     const float scale = 1.0f / sqrtf((float)DH);
     const size_t row0 = (size_t)b * capacity;
     const int nr = min(RC, rep - r0);
@@ -407,8 +420,6 @@ __global__ __launch_bounds__(DH) void decode_combine_kernel(const float *__restr
     o[(size_t)blockIdx.x * DH + threadIdx.x] = (f16)(out / l);
 }
 
-constexpr int DEC_SPLIT_ROWS = 1024, DEC_SPLIT_GRID = 256;
-
 template <int DH, bool FUSED>
 int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o, const DecodeNew &nw, float *part,
                   hipStream_t st)
@@ -421,17 +432,11 @@ int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o
     const int heads = c->H * c->B * ((rep + rc - 1) / rc);
     // two heads per workgroup where that still leaves one for every CU
     const bool pairs = rep == 1 && c->H % 2 == 0 && heads >= 2 * DEC_SPLIT_GRID;
-    const int n_tiles = (longest + DEC_TILE - 1) / DEC_TILE;
-    // Few heads over long caches: split the rows so that every workgroup still has a CU to itself, if that saves
-    // two tiles of the walk or more (a tile takes 4.5 us, the combining launch 3: 3 sequences of 4003 rows, 4
-    // K/V heads: 44 us unsplit, 25 in 384 workgroups of one tile, 19 in 192 of two).
-    int n_split = 1, tiles = n_tiles;
-    if (part && longest > DEC_SPLIT_ROWS && heads < DEC_SPLIT_GRID) {
-        const int t = (n_tiles * heads + DEC_SPLIT_GRID - 1) / DEC_SPLIT_GRID;
-        if (n_tiles - t >= 2) {
-            tiles = t;
-            n_split = (n_tiles + tiles - 1) / tiles;
-        }
+    // as many parts as any length within the loop is split into
+    int n_split = 1;
+    for (int n = ((stepped ? c->len + 1 : len) + DEC_TILE - 1) / DEC_TILE; part && n <= (longest + DEC_TILE - 1) / DEC_TILE; ++n) {
+        const int t = split_tiles(n, heads);
+        n_split = max(n_split, (n + t - 1) / t);
     }
     const bool one_tile = longest <= DEC_TILE;
     auto run = [&](auto kernel_tag, int hp) {
@@ -440,7 +445,7 @@ int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o
         if (!grant_lds<kernel>()) return QUOTA_ERR_HIP;
         kernel<<<dim3(heads * n_split / hp), dim3(hp * DEC_THREADS), lds, st>>>(
             q, d, dkv, rep, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes, (f16 *)c->v_scales,
-            c->capacity, stepped ? c->len : len, c->step_dev, c->max_steps, o, c->H, nw, n_split, tiles, part);
+            c->capacity, stepped ? c->len : len, c->step_dev, c->max_steps, o, c->H, nw, n_split, heads, part);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
     };

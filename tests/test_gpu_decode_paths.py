@@ -111,6 +111,33 @@ def test_decode_layer_many_heads(qb, H, Hkv, dh, B, rows, stepped):
     step_and_check(H, Hkv, dh, 160, B, rows, stepped)
 
 
+@pytest.mark.parametrize("H,Hkv,dh,B,rows,most", [
+    (8, 8, 64, 2, 700, 1000), (4, 4, 128, 2, 1020, 600), (8, 2, 128, 2, 1023, 400),     # one part, in loops that end in parts
+    (8, 8, 64, 12, 1300, 2000),                                 # too few tiles to split, in a loop that ends in parts of two
+    (8, 8, 64, 12, 2900, 2100), (8, 4, 128, 20, 2100, 1500),    # parts that grow within the loop
+])
+def test_decode_layer_stepped_has_the_eager_bits(qb, H, Hkv, dh, B, rows, most):
+    """How the cached rows are split over workgroups, hence the order of the sums, depends on the rows there are and not on
+    the loop's length: a step whose count lies on the device leaves the bits of the call with a host-side length."""
+    from paper_2604_17320_amd.model import make_taps
+    print(f"decode layer, {H}/{Hkv} heads of {dh}, {B} sequences of {rows} cached rows, eager and fourth of {most}", flush=True)
+    W, L, cos, sin = layer(H, Hkv, dh, 160)
+    c = random_cache(rows, B, rows, Hkv, dh)
+    r = wl.rng(rows, "decode-eager", B)
+    x, pos = dev(r.standard_normal((B, H * dh)).astype(np.float16)), dev((7 + np.arange(B) % 50).astype(np.int32))
+    got = []
+    for stepped in (False, True):
+        cache, n = poisoned_cache(c, B, rows, rows + most, Hkv, dh), torch.full((1,), 3, dtype=torch.int32, device="cuda")
+        if stepped:
+            cache.desc.len, cache.desc.step_dev, cache.desc.max_steps = rows - 3, n.data_ptr(), most
+        o, y = (torch.full((B, H * dh), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+        ws = torch.full((L.decode_workspace_bytes(B),), 0xFF, dtype=torch.uint8, device="cuda")
+        L.decode(x, pos, cache, y, ws, make_taps(o=o))
+        got.append((host(o), host(y)))
+    assert np.isfinite(got[0][0].astype(np.float32)).all()
+    assert eq16(got[0][0], got[1][0]) and eq16(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("F", [1376, 2720, 8736])      # gate/up 2752, 5440, 17472 columns; ragged rows into down, one of them long
 @pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 7, 11, 15, 16, 17, 32])
 def test_decode_layer_row_counts(qb, F, B):
