@@ -12,11 +12,41 @@ def sources():
             yield os.path.basename(path), re.sub(r"//[^\n]*", "", f.read())
 
 
+# the atomics there are: counters in LDS (the selects' histograms and candidate lists, whose memory all comes from `hist`)
+LDS_COUNTERS = {("select.hip", "&h["), ("select.hip", "&list[")}
+
+
+def handed_over(name, text):
+    """What in a source could pass a result from workgroup to workgroup: atomics on anything but the counters in LDS,
+    scoped atomics, fences, and reads or writes past the caches that only such a hand-over needs."""
+    found = re.findall(r"__(?:hip|scoped|opencl)_atomic_\w+|__atomic_\w+|__sync_\w+|__threadfence\w*|MEMORY_SCOPE_\w+"
+                       r"|__builtin_amdgcn_(?:fence|(?:global|flat|ds|raw\w*_buffer|struct\w*_buffer)_atomic)\w*"
+                       r"|\b(?:global|flat|buffer)_atomic_\w+|\bvolatile\s+(?!\()(?!\")\w+", text)
+    for call, operand in re.findall(r"\b(atomic[A-Z]\w*)\s*\(\s*(&?\s*\w+\s*\[?)", text):
+        if (name, operand.replace(" ", "")) not in LDS_COUNTERS:
+            found.append(f"{call}({operand}")
+    return found
+
+
 def test_workgroups_of_a_launch_hand_each_other_nothing():
     """Results pass from workgroup to workgroup at launch boundaries only: no counters, flags or fences in device
     memory whose order would have to be argued."""
     for name, text in sources():
-        assert not re.findall(r"__hip_atomic_\w+|__threadfence\w*|MEMORY_SCOPE_\w+|__builtin_amdgcn_fence", text), name
+        assert not handed_over(name, text), (name, handed_over(name, text))
+        if name == "select.hip":                     # ... and `hist` is LDS
+            for line in ("int *h = hist + at * NR * 256, *hn = hist + next * NR * 256;", "int *list = hist;", "list = hn;",
+                         "extern __shared__ __align__(16) uint32_t score_lds[];", "int *hist = reinterpret_cast<int *>(score_lds);",
+                         "__shared__ __align__(16) int hist[3 * 256];"):
+                assert text.count(line) == 1, line
+            assert len(re.findall(r"\b(?:hist|h|list) =", text)) == 4
+
+
+def test_the_rule_sees_a_hand_over():
+    for planted in ("if (atomicAdd(done, 1) == last) reduce();", "atomicMax(&best[b], v);", "atomicCAS (flag, 0, 1);",
+                    "__hip_atomic_fetch_add(p, 1, x, y);", "__atomic_load_n(p, 2);", "volatile int *flag = f;",
+                    "__builtin_amdgcn_global_atomic_fadd_f32(p, v);", "global_atomic_add_u32 v0"):
+        assert handed_over("kernel.hip", planted), planted
+    assert handed_over("kernel.hip", "atomicAdd(&h[i], 1);") and not handed_over("select.hip", "atomicAdd(&h[i], 1);")
 
 
 def test_assembly_leaves_m0_to_the_compiler():
