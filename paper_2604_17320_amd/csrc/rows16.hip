@@ -373,8 +373,9 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 // most one workgroup per CU again), else three workgroups per CU with one group per wave, or, with a quantizer in
 // front, two per CU (one, where the rows leave no room for two) with two, so that fewer repeat its work (one row, gate/up
 // of 22016 columns: 10.8 us inside with two per CU, 12.8 with one, 13.8 with three).  One or two rows take 48 columns where
-// that is one share for every CU and 32 are more, so that no CU has two (1 x 12288 x 4096 9.6 -> 8.4 us; with three rows
-// whose quantizer one workgroup per CU does alone a layer takes 1 % longer).
+// that is one share for every CU and 32 are more, so that no CU has two (1 x 12288 x 4096 9.6 -> 8.4 us, 2 x 9216 x 6144
+// 12.4 -> 10.9, 1 x 8448 x 8192 13.2 -> 11.6; with three rows whose quantizer one workgroup per CU does alone a layer takes 1 %
+// longer; six chunks of a row per thread leave no registers for it: 2 x 12288 x 8192 18.0 us, 17.0 to 17.7 with 32 columns).
 // Workgroups walk over the columns.
 // Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
 // <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
@@ -387,7 +388,7 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
             if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
         return launch_rows16<1, 2, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }
-    if constexpr (MODE == ROWS_RMSNORM)
+    if constexpr (MODE == ROWS_RMSNORM && NC <= 3)
         if (M <= 2 && W->N > 8192 && W->N <= 48 * 256 && W->N % 48 == 0)
             return launch_rows16<3, 2, 1, MODE, NC>(in, M, W, y, ldy, res, ldr, code_stride, st);
     if constexpr (MODE <= ROWS_FRAG)

@@ -147,6 +147,15 @@ def test_decode_layer_row_counts(qb, F, B):
     step_and_check(8, 2, 64, F, B, 20)
 
 
+@pytest.mark.parametrize("H,Hkv", [(32, 32), (48, 12), (64, 1)])       # QKV of 12288 x 4096, 9216 x 6144, 8448 x 8192
+@pytest.mark.parametrize("B", [1, 2, 3])
+def test_decode_layer_one_share_of_the_projection_per_cu(qb, H, Hkv, B):
+    """One or two rows of at most three chunks per thread: a workgroup takes 48 columns where those are at most 256 shares.
+    Beyond them it takes 32."""
+    print(f"decode layer, {B} rows, {H}/{Hkv} heads of 128", flush=True)
+    step_and_check(H, Hkv, 128, 160, B, 20)
+
+
 @pytest.mark.parametrize("H,Hkv,dh,rows,most", [(8, 8, 64, 509, 8), (8, 2, 128, 1021, 1500)])
 def test_decode_layer_captured_across_a_tile_boundary(qb, H, Hkv, dh, rows, most):
     """One captured step replayed while the cache grows past a 512-row tile (and, split, past a workgroup's share): every
