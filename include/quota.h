@@ -16,7 +16,10 @@
  *     nothing when it returns an error.  No exceptions cross the boundary.
  *   - Device buffers start at multiples of 16 bytes (every allocator's do).
  *     Where a call says "any address" for one of them, the alignment of its
- *     elements is enough.
+ *     elements is enough.  Buffers that go to LDS without passing registers
+ *     (q, khat, vhat of the attention, the weights of quota_fp_block) are
+ *     checked: QUOTA_ERR_INVALID_ARG.  The workspaces of the layer and block
+ *     calls may start anywhere.
  *   - fp16 = IEEE binary16.  int4 data is two's complement, two codes per
  *     byte, element 2j in bits 0-3 and element 2j+1 in bits 4-7.
  *   - Weight groups are 128 input channels (QUOTA_GROUP_W), KV groups are 64
@@ -205,7 +208,7 @@ size_t quota_attention_workspace_bytes(int B, int N, int H, int dh);
  * [vis_begin, vis_begin+Nv): cm_inter[b][i] = mean over heads of the total
  * probability that text queries put on key i, cm_intra the same for visual
  * queries (fp32 [B][Nv]); pass both null to skip the cue pass.
- * ws: quota_attention_workspace_bytes bytes, at any multiple of 4.  Requires
+ * ws: quota_attention_workspace_bytes bytes, at any multiple of 4 (checked).  Requires
  * dh == 64 or 128. */
 int quota_attention_prefill(const void *q_f16, const void *khat_f16,
                             const void *vhat_f16, int B, int N, int H, int dh,

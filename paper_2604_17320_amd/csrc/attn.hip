@@ -361,6 +361,8 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     if (B <= 0 || N < 0 || H <= 0 || Hkv <= 0 || vis_begin < 0 || Nv < 0 || vis_begin + Nv > N)
         return QUOTA_ERR_INVALID_ARG;
     if ((dh != 64 && dh != 128) || H % Hkv != 0) return QUOTA_ERR_SHAPE;
+    if (!on_lds_copies(q_f16) || !on_lds_copies(khat_f16) || !on_lds_copies(vhat_f16) || (reinterpret_cast<uintptr_t>(ws) & 3))
+        return QUOTA_ERR_INVALID_ARG;
     if (N == 0) return QUOTA_OK;
     const AttnWs w(ws, (size_t)B * H * N);
     float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);

@@ -333,6 +333,8 @@ int check_fp_layer(const quota_fp_layer *L, int B, int N)
     if (B <= 0 || N <= 0 || L->H <= 0 || L->F <= 0 || L->n_pos <= 0 || !(L->eps >= 0.0f)) return QUOTA_ERR_INVALID_ARG;
     const int Hkv = L->Hkv > 0 ? L->Hkv : L->H;
     if ((L->dh != 64 && L->dh != 128) || L->H % Hkv != 0 || L->F % 32 != 0) return QUOTA_ERR_SHAPE;
+    if (!on_lds_copies(L->wqkv) || !on_lds_copies(L->wo) || !on_lds_copies(L->wgu) || !on_lds_copies(L->wdown))
+        return QUOTA_ERR_INVALID_ARG;
     return QUOTA_OK;
 }
 
@@ -346,7 +348,7 @@ FpWs carve_fp(void *ws, const quota_fp_layer *L, int B, int N)
 {
     const int Hkv = L->Hkv > 0 ? L->Hkv : L->H;
     const size_t M = (size_t)B * N, d = (size_t)L->H * L->dh, dkv = (size_t)Hkv * L->dh, F = L->F;
-    char *p = (char *)ws;
+    char *const start = quota_ws_start(ws), *p = start;
     FpWs w;
     auto take = [&](size_t bytes) { void *r = p; p += up256(bytes); return r; };
     w.h = (f16 *)take(M * d * 2);
@@ -359,7 +361,7 @@ FpWs carve_fp(void *ws, const quota_fp_layer *L, int B, int N)
     w.gu = (f16 *)take(M * 2 * F * 2);
     w.z = (f16 *)take(M * F * 2);
     w.attn = take(quota_attention_workspace_bytes(B, N, L->H, L->dh));
-    w.bytes = (size_t)(p - (char *)ws);
+    w.bytes = (size_t)(p - start) + QUOTA_WS_SLACK;
     return w;
 }
 
@@ -423,7 +425,7 @@ struct ProfileWs {
 ProfileWs carve_profile(void *ws, const quota_layer *Lq, const quota_fp_layer *Lf, int B, int N)
 {
     const size_t M = (size_t)B * N, d = (size_t)Lf->H * Lf->dh;
-    char *p = (char *)ws;
+    char *const start = quota_ws_start(ws), *p = start;
     ProfileWs w;
     auto take = [&](size_t bytes) { void *r = p; p += up256(bytes); return r; };
     w.xq = (f16 *)take(M * d * 2);
@@ -432,7 +434,7 @@ ProfileWs carve_profile(void *ws, const quota_layer *Lq, const quota_fp_layer *L
     w.part = (double *)take((size_t)B * DEV_PARTS * 2 * sizeof(double));
     const size_t a = quota_prefill_workspace_bytes(Lq, B, N), b = quota_fp_block_workspace_bytes(Lf, B, N);
     w.rest = take(a > b ? a : b);           // the two runs are ordered on one stream and share it
-    w.bytes = (size_t)(p - (char *)ws);
+    w.bytes = (size_t)(p - start) + QUOTA_WS_SLACK;
     return w;
 }
 }  // namespace

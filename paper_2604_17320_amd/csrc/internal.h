@@ -103,6 +103,11 @@ int quota_internal_rope_kv_quant(const void *qkv_f16, int M, int H, int Hkv, int
                                  void *khat_f16, void *vhat_f16, uint8_t *k_codes, void *k_scales,
                                  uint8_t *v_codes, void *v_scales, hipStream_t st);
 
+// A workspace may start anywhere: its parts lie behind the first multiple of 16 (asynchronous copies read them), so that
+// it holds QUOTA_WS_SLACK bytes more than they take.
+#define QUOTA_WS_SLACK 16
+inline char *quota_ws_start(void *ws) { return (char *)(((uintptr_t)ws + 15) & ~(uintptr_t)15); }
+
 // *step_dev += 1 (one thread; capturable)
 int quota_internal_advance_step(int32_t *step_dev, hipStream_t st);
 

@@ -33,12 +33,13 @@ struct LayerWs {
     int32_t *keep_idx, *rows;
     f16 *x_keep, *x1, *gu;
     void *attn_ws;
+    char *end;          // of the parts
     size_t bytes;
 };
 
 LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
 {
-    Carver c{(char *)ws, 0};
+    Carver c{quota_ws_start(ws), 0};
     LayerWs w;
     size_t M = (size_t)B * N, d = (size_t)H * dh, dkv = (size_t)Hkv * dh;
     size_t kmax = d > (size_t)F ? d : (size_t)F;
@@ -64,7 +65,8 @@ LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
     w.x1 = c.take<f16>(M * d);
     w.gu = c.take<f16>(M * 2 * (size_t)F);
     w.attn_ws = c.take<char>(quota_attention_workspace_bytes(B, N, H, dh));
-    w.bytes = c.off;
+    w.end = c.base ? c.base + c.off : nullptr;
+    w.bytes = c.off + QUOTA_WS_SLACK;
     return w;
 }
 
@@ -313,7 +315,7 @@ extern "C" int quota_decode_layer(const quota_layer *L, const void *x_f16, const
     TRY(dump(t->qkv, w.qkv, (size_t)B * (d + 2 * dkv) * 2, st));
     // the new token's K/V join the cache inside the attention, which reads the rest of it in 4-bit form
     TRY(quota_internal_attention_decode_new(w.qkv, pos, L->cosT, L->sinT, L->n_pos, H, cache, t->q_rot ? w.q_rot : nullptr,
-                                            w.o, (char *)ws + w.bytes, st));
+                                            w.o, w.end, st));
     TRY(dump(t->q_rot, w.q_rot, (size_t)B * d * 2, st));
     TRY(dump(t->o, w.o, (size_t)B * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;

@@ -6,7 +6,9 @@
 // In assembly because the compiler, which cannot tell the LDS buffers apart, would make every LDS read
 // wait for the copies just started; the kernel waits for them itself (drain) before the barrier that
 // hands the buffer over.  The LDS base goes into m0 as an operand, so that the compiler knows m0 taken; the
-// chip wants one wait state between that write and the copy.
+// chip wants one wait state between that write and the copy.  Both sides lie at multiples of what a lane copies: what a
+// caller hands in is checked with on_lds_copies.
+inline bool on_lds_copies(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 __device__ __forceinline__ void copy16_to_lds(const void *base, unsigned off, unsigned lds)
 {
     asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(off), "s"(base) : "memory");

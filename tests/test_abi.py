@@ -70,6 +70,24 @@ def test_null_and_shape_checks_come_before_device_work(lib):
     assert lib.quota_attention_workspace_bytes(1, 640, 32, 128) > 0
 
 
+def test_buffers_that_go_straight_to_lds_are_checked(lib):
+    """16-byte copies into LDS take multiples of 16 bytes (the workspace's row sums 4): refused before any device work."""
+    ERR_INVALID = -2
+    P = C.c_void_p
+    lib.quota_attention_prefill_gqa.argtypes = [P] * 3 + [C.c_int] * 7 + [P] * 5
+    for off in (2, 4, 8):
+        for at in range(3):
+            bufs = [0x1000 + off * (i == at) for i in range(3)]
+            assert lib.quota_attention_prefill_gqa(*bufs, 1, 16, 2, 2, 64, 0, 8, 0x1000, 0x1000, 0x1000, 0x1000, None) == ERR_INVALID
+    assert lib.quota_attention_prefill_gqa(0x1000, 0x1000, 0x1000, 1, 16, 2, 2, 64, 0, 8, 0x1000, 0x1000, 0x1000, 0x1002, None) == ERR_INVALID
+    from paper_2604_17320_amd import binding as qb
+    x = P(0x1000)
+    for at in range(4):
+        w = [0x1000 + 8 * (i == at) for i in range(4)]
+        bad = qb.FpLayer(8, 64, 1376, 0, 1e-5, 0x1000, 0x1000, *w, 0x1000, 0x1000, 64)
+        assert lib.quota_fp_block(C.byref(bad), x, x, 2, 80, x, x, None) == ERR_INVALID
+
+
 def test_recipe_matches_the_oracle():
     """Host-only entry points (Eq. 1-5): the library's recipe against the oracle's, on the CPU."""
     import numpy as np

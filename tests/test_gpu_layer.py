@@ -435,3 +435,43 @@ def test_layer_with_weight_scales_at_an_odd_halfword(qb):
     got = run_gpu(qb, odd, shape, x, pos, 19)
     for name in want:
         assert np.array_equal(want[name], got[name]), name
+
+
+@pytest.mark.parametrize("off", [1, 4, 8, 15])
+def test_layer_workspace_anywhere(qb, off):
+    """A workspace that starts `off` bytes behind a multiple of 16: the bits of one that starts there, in a pruned prefill
+    layer and in a decode step whose cached rows are split over workgroups, and not a byte touched outside its size."""
+    from paper_2604_17320_amd.model import KVCache4
+    base = wl.CONFIGS[0]
+    shape = wl.Shape("ws", d=base.d, H=base.H, F=base.F, layers=1, B=2, Nv=base.Nv, Nt=21, n_outlier=base.n_outlier, vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 3)
+    B, N, K, rows = shape.B, shape.N, 30, 1700
+    n = N - shape.Nv + K
+    xd, pd = dev(wl.hidden_state(shape, 3)), dev(wl.positions(shape))
+    long_cache = [torch.from_numpy(wl.rng(3, "ws", i).integers(0, 256, s, dtype=np.uint8)).cuda()
+                  for i, s in enumerate([(B, rows + 1, shape.d // 2)] * 2)]
+    outs = []
+    for o in (0, off):
+        def room(nbytes):
+            t = torch.full((o + nbytes + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+            rooms.append((t, nbytes))
+            return t[o: o + nbytes]
+        rooms = []
+        cache = KVCache4(B, n, shape.H, shape.dh)
+        x_out = torch.zeros((B * n, shape.d), dtype=torch.float16, device="cuda")
+        pos_out = torch.zeros((B * n,), dtype=torch.int32, device="cuda")
+        st = qb.State(B, N, 0, shape.Nv, xd.data_ptr(), pd.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+        qb.quota_prefill_layer(L.desc, st, K, qb.quota_score_params_default(), cache.desc, None, room(L.workspace_bytes(B, N)))
+        grown = KVCache4(B, rows + 1, shape.H, shape.dh)
+        grown.k_codes.copy_(long_cache[0])
+        grown.v_codes.copy_(long_cache[1])
+        grown.k_scales.fill_(0.25)
+        grown.v_scales.fill_(0.25)
+        grown.desc.len = rows
+        y = torch.zeros((B, shape.d), dtype=torch.float16, device="cuda")
+        L.decode(x_out[:B], pos_out[:B], grown, y, room(L.decode_workspace_bytes(B)))
+        for t, nbytes in rooms:
+            assert bool((t[:o] == 0xA5).all()) and bool((t[o + nbytes:] == 0xA5).all())
+        outs.append([t.view(torch.uint8) for t in (x_out, cache.k_codes, cache.k_scales, cache.v_codes, cache.v_scales, y)])
+    assert bool(torch.isfinite(outs[0][-1].view(torch.float16)).all())
+    assert all(torch.equal(a, b) for a, b in zip(*outs))

@@ -166,6 +166,23 @@ def test_profile_block_errors_and_scratch_cache(qb):
     assert e.value.code == qb.ERR_CAPACITY and small.len == 0
 
 
+@pytest.mark.parametrize("off", [1, 8])
+def test_profile_block_workspace_anywhere(qb, off):
+    """The workspace of the two blocks `off` bytes behind a multiple of 16: the same norms, nothing written beside it."""
+    from paper_2604_17320_amd.model import KVCache4
+    d, H, Hkv, dh, F, B, N = CASES[0]
+    _, _, Lq, Lf, _, _ = build_pair(d, H, Hkv, dh, F, 2 * N + 8, seed=4)
+    x, pos = (dev(t) for t in inputs(B, N, d, seed=4))
+    nbytes, got = qb.quota_profile_block_workspace_bytes(Lq.desc, Lf.desc, B, N), []
+    for o in (0, off):
+        dn, rn = (torch.empty(B, dtype=torch.float64, device="cuda") for _ in range(2))
+        room = torch.full((o + nbytes + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        qb.quota_profile_block(Lq.desc, Lf.desc, x, pos, B, N, KVCache4(B, N, Hkv, dh).desc, dn, rn, room[o: o + nbytes])
+        assert bool((room[:o] == 0xA5).all()) and bool((room[o + nbytes:] == 0xA5).all())
+        got.append((host(dn), host(rn)))
+    assert all(np.array_equal(a, b) for a, b in zip(*got)) and (got[0][1] > 0).all()
+
+
 def test_recipe_from_profiled_sensitivities(qb):
     """The whole offline path on synthetic calibration data: profile m candidate layers (different
     weights each, weight scale growing with depth so that the layers differ in sensitivity), then
