@@ -330,7 +330,7 @@ extern "C" int quota_kv_quant_append(const void *k_f16, const void *v_f16, int B
         return QUOTA_ERR_NULL;
     if (B <= 0 || N < 0 || H <= 0 || n_keep < 0 || cache->len < 0) return QUOTA_ERR_INVALID_ARG;
     if (dh % 64 != 0 || cache->H != H || cache->dh != dh || cache->B != B) return QUOTA_ERR_SHAPE;
-    if (!keep_rows && n_keep > N) return QUOTA_ERR_INVALID_ARG;
+    if ((!keep_rows && n_keep > N) || (N == 0 && n_keep > 0)) return QUOTA_ERR_INVALID_ARG;
     if (cache->len + n_keep > cache->capacity) return QUOTA_ERR_CAPACITY;
     if (n_keep == 0) return QUOTA_OK;
     int d = H * dh;

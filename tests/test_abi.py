@@ -88,6 +88,15 @@ def test_buffers_that_go_straight_to_lds_are_checked(lib):
         assert lib.quota_fp_block(C.byref(bad), x, x, 2, 80, x, x, None) == ERR_INVALID
 
 
+def test_append_from_empty_sequences_is_refused(lib):
+    """Kept rows are clamped into the sequence; one without rows has none to clamp to."""
+    from paper_2604_17320_amd import binding as qb
+    cache = qb.KVCache(2, 50, 4, 64, 0, 0x1000, 0x1000, 0x1000, 0x1000)
+    x = C.c_void_p(0x1000)
+    assert lib.quota_kv_quant_append(x, x, 2, 0, 4, 64, x, 3, C.byref(cache), None) == -2 and cache.len == 0
+    assert lib.quota_kv_quant_append(x, x, 2, 0, 4, 64, x, 0, C.byref(cache), None) == 0 and cache.len == 0
+
+
 def test_recipe_matches_the_oracle():
     """Host-only entry points (Eq. 1-5): the library's recipe against the oracle's, on the CPU."""
     import numpy as np
