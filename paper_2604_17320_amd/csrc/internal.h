@@ -88,8 +88,6 @@ int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const f
 int quota_internal_rows16_frag_silu(const uint8_t *qf, const float *sa, int M, const quota_weights *W, void *z, hipStream_t st);
 int quota_internal_rmsnorm_quantize_frag(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qf,
                                          float *scale, hipStream_t st);
-int quota_internal_silu_mul_quantize_frag(const void *gu_f16, int M, int F, uint8_t *qf, float *scale, void *z_opt,
-                                          const void *z_inject_opt, hipStream_t st);
 int quota_internal_quantize_frag(const void *x_f16, int M, int d, uint8_t *qf, float *scale, hipStream_t st);
 bool quota_internal_rows16_quantizes(int M, int K);
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,

@@ -116,8 +116,8 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
                                         w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st);
 }
 
-// RMSNorm, quantizer, GEMM; SwiGLU product, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_FRAG rows (rows16.hip: why) go
-// through the few-row GEMM's own format, and a few leave the quantizer to the GEMM.
+// RMSNorm, quantizer, GEMM; quantizer, GEMM.  Up to ROWS_FRAG rows (rows16.hip: why) go through the few-row GEMM's own
+// format, and a few leave the quantizer to the GEMM.
 #define ROWS_FRAG 32
 static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
                         const quota_weights *W, void *y, int ldy, hipStream_t st)
@@ -129,16 +129,6 @@ static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const flo
     }
     TRY(quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
-}
-static int silu_mul_gemm(const LayerWs &w, int M, int F, void *z, const void *z_inject, const quota_weights *W, void *y,
-                         int ldy, const void *res, int ldr, hipStream_t st)
-{
-    if (M <= ROWS_FRAG) {
-        TRY(quota_internal_silu_mul_quantize_frag(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
-        return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, res, ldr, st);
-    }
-    TRY(quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, z, z_inject, st));
-    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
 static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const quota_weights *W, void *y, int ldy,
                          const void *res, int ldr, hipStream_t st)
@@ -152,7 +142,8 @@ static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const qu
     return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
 // The SwiGLU block on rows x1, added to them: RMSNorm, quantizer, gate/up, SiLU product, quantizer, down.  Without taps that
-// want the gate | up rows or z, the gate/up projection makes the product itself and w.gu holds z.
+// want the gate | up rows or z, the gate/up projection makes the product itself, where its tile can, and w.gu holds z.
+// Else it stores gate | up and the quantizer in front of down makes the product (any number of rows, in the A8 format).
 static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1, const quota_taps *t, void *x_out, hipStream_t st)
 {
     const int d = L->H * L->dh, F = L->F;
@@ -174,7 +165,8 @@ static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1,
         TRY(rmsnorm_gemm(w, x1, M, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
         TRY(dump(t->gu, w.gu, (size_t)M * 2 * F * 2, st));
     }
-    return silu_mul_gemm(w, M, F, t->z, t->inject_z, &L->down, x_out, d, x1, d, st);
+    TRY(quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, t->z, t->inject_z, st));
+    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->down, x_out, d, x1, d, st);
 }
 
 extern "C" size_t quota_prefill_workspace_bytes(const quota_layer *L, int B, int N)

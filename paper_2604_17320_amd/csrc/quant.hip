@@ -602,20 +602,13 @@ int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, fl
     return with_a8_out(qa8, M, [&](auto out) { return quantize_rows(x_f16, M, d, out, scale, st); });
 }
 
-// The three quantizers of at most 16 rows into the few-row GEMM's fragments.
+// The two quantizers of at most 32 rows into the few-row GEMM's fragments.
 int quota_internal_rmsnorm_quantize_frag(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qf,
                                          float *scale, hipStream_t st)
 {
     int rc = check_rows(x_f16, M, d, d, qf, scale);
     if (rc != QUOTA_OK || M == 0) return rc;
     return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, RowOutFrag{(uint32_t *)qf}, scale, nullptr, nullptr, nullptr, st);
-}
-int quota_internal_silu_mul_quantize_frag(const void *gu_f16, int M, int F, uint8_t *qf, float *scale, void *z_opt,
-                                          const void *z_inject_opt, hipStream_t st)
-{
-    int rc = check_rows(gu_f16, M, F, F, qf, scale);
-    if (rc != QUOTA_OK || M == 0) return rc;
-    return silu_mul_quantize(gu_f16, M, F, RowOutFrag{(uint32_t *)qf}, scale, z_opt, z_inject_opt, st);
 }
 int quota_internal_quantize_frag(const void *x_f16, int M, int d, uint8_t *qf, float *scale, hipStream_t st)
 {

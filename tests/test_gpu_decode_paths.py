@@ -142,7 +142,7 @@ def test_decode_layer_stepped_has_the_eager_bits(qb, H, Hkv, dh, B, rows, most):
 @pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 7, 11, 15, 16, 17, 32, 33, 70])
 def test_decode_layer_row_counts(qb, F, B):
     """Up to 4 rows the GEMM quantizes its input, up to 16 it reads fragments of which it owns B rows, up to 32 two blocks of
-    them; beyond that the projections go through the tiles."""
+    them; beyond that the projections go through the tiles.  (Down, behind the taps, reads rows of bytes.)"""
     print(f"decode layer, {B} rows, F = {F}", flush=True)
     step_and_check(8, 2, 64, F, B, 20)
 
@@ -194,11 +194,11 @@ def test_decode_layer_captured_across_a_tile_boundary(qb, H, Hkv, dh, rows, most
         assert torch.equal(a, b), name
 
 
-@pytest.mark.parametrize("F", [96, 2720, 4128, 8736])  # gate/up of 192 to 17472 columns: both widths of a workgroup's share
-@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("F", [96, 1376, 2720, 4128, 8736])  # gate/up of 192 to 17472 columns: both widths of a workgroup's share
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 7, 11, 15, 16, 17, 32, 33])
 def test_decode_layer_silu_product_in_the_gate_up_projection(qb, F, B):
-    """Without taps on gate | up or z the projection makes the product itself: the bits of the step whose tap keeps the
-    two kernels apart."""
+    """Without taps on gate | up or z the projection makes the product itself and down reads it as fragments or
+    quantizes it: the bits of the step whose tap keeps the two kernels apart and whose down reads rows of bytes."""
     from paper_2604_17320_amd.model import make_taps
     H, Hkv, dh, rows = 8, 2, 64, 20
     W, L, cos, sin = layer(H, Hkv, dh, F)
