@@ -392,8 +392,8 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
 
 // Calls launch(GROUP, NCH, grid) with the smallest cache that holds d columns: a thread's registers are what limits the
 // rows in flight.  RMSNorm quantizer with metrics, 11776 rows of 5120 columns: 61 us with 12 chunks per lane, of which 10
-// are used, 113 with 8 per thread of a workgroup, of which 2.5 are used.
-template <typename OUT, typename LAUNCH>
+// are used, 113 with 8 per thread of a workgroup, of which 2.5 are used.  MOST: the most columns that the caller lets by.
+template <typename OUT, int MOST = ROW_MAXCOLS, typename LAUNCH>
 static void with_row_shape(int M, int d, LAUNCH launch)
 {
     const auto go = [&](auto group, auto nch) { launch(group, nch, dim3(group() == 64 ? (M + 3) / 4 : M)); };
@@ -410,7 +410,7 @@ static void with_row_shape(int M, int d, LAUNCH launch)
     if (d <= 256 * 8 * 2) go(workgroup, std::integral_constant<int, 2>());
     else if (d <= 256 * 8 * 4) go(workgroup, std::integral_constant<int, 4>());
     else if (d <= 256 * 8 * 8) go(workgroup, std::integral_constant<int, 8>());
-    else go(workgroup, std::integral_constant<int, 16>());
+    else if constexpr (MOST > 256 * 8 * 8) go(workgroup, std::integral_constant<int, 16>());
 }
 
 extern "C" size_t quota_weights_packed_bytes(int N, int K)
@@ -511,10 +511,14 @@ template <typename OUT>
 static int rmsnorm_quantize(const void *x_f16, int M, int d, int ldx, const float *gamma, float eps, OUT q,
                             float *scale, float *sumsq_opt, float *ressq_opt, void *h_opt, hipStream_t st)
 {
+    // a layer's rows have the model's width, and the few of a decode step no metrics
+    constexpr bool LAYER = !std::is_same_v<OUT, RowOutPacked>, METRICS = !std::is_same_v<OUT, RowOutFrag>;
+    if (LAYER && d > QUOTA_MAX_MODEL_WIDTH) return QUOTA_ERR_SHAPE;
     ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
-    with_row_shape<OUT>(M, d, [&](auto group, auto nch, dim3 grid) {
-        auto kernel = sumsq_opt || ressq_opt ? rmsnorm_quantize_act_kernel<true, group(), nch(), OUT>
-                                             : rmsnorm_quantize_act_kernel<false, group(), nch(), OUT>;
+    with_row_shape<OUT, LAYER ? QUOTA_MAX_MODEL_WIDTH : ROW_MAXCOLS>(M, d, [&](auto group, auto nch, dim3 grid) {
+        auto kernel = rmsnorm_quantize_act_kernel<false, group(), nch(), OUT>;
+        if constexpr (METRICS)
+            if (sumsq_opt || ressq_opt) kernel = rmsnorm_quantize_act_kernel<true, group(), nch(), OUT>;
         kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, gamma, eps, q, scale, sumsq_opt, ressq_opt,
                                                    (f16 *)h_opt);
     });
@@ -551,9 +555,9 @@ static int silu_mul_quantize(const void *gu_f16, int M, int F, OUT q, float *sca
 {
     ProfScope prof(QUOTA_K_SILU_MUL_QUANTIZE_ACT, 0, 4.5 * M * F + 4.0 * M, st);
     with_row_shape<OUT>(M, F, [&](auto group, auto nch, dim3 grid) {
-        constexpr bool can_be_early = nch() < 16;
+        constexpr bool can_be_early = group() == 256 && nch() < 16;
         auto kernel = silu_mul_quantize_act_kernel<group(), nch(), can_be_early, OUT>;
-        if constexpr (OUT::MANY) {
+        if constexpr (OUT::MANY && nch() > 2) {              // (two chunks: such a launch is the waves')
             if (M >= ROW_WAVE_MIN_ROWS) kernel = silu_mul_quantize_act_kernel<group(), nch(), false, OUT>;
         }
         kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt);

@@ -384,7 +384,7 @@ int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, con
            hipStream_t st)
 {
     if (W->N <= 4096) {
-        if constexpr (MODE != ROWS_RMSNORM)
+        if constexpr (MODE != ROWS_RMSNORM && !(MODE == ROWS_QUANT && NC == 1))      // (one chunk: 4096 channels at most)
             if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
         return launch_rows16<1, 2, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
     }

@@ -57,6 +57,21 @@ def test_kernel_names_and_strerror(lib):
     assert lib.quota_strerror(-99).decode() not in msgs
 
 
+def test_kernels_that_no_call_reaches_are_not_built():
+    """The library holds no instantiation beyond the shapes that the calls' own limits let by."""
+    built = open(LIB, "rb").read()
+    for shape, why in [(rb"silu_mul_quantize_act_kernelILi\d+ELi\d+ELb[01]E10RowOutFrag", "the few-row GEMM makes the product"),
+                       (rb"silu_mul_quantize_act_kernelILi64ELi\d+ELb1E", "waves take long launches only"),
+                       (rb"silu_mul_quantize_act_kernelILi256ELi2ELb0E", "long launches of two chunks are the waves'"),
+                       (rb"rmsnorm_quantize_act_kernelILb1ELi\d+ELi\d+E10RowOutFrag", "no metrics of a decode step"),
+                       (rb"rmsnorm_quantize_act_kernelILb[01]ELi\d+ELi16E(?:8RowOutA8|10RowOutFrag|14RowOutA8Starts)", "a layer is 16384 wide at most"),
+                       (rb"w4a4_rows16_kernelILi1ELi4ELi3ELi1E", "rows of one chunk per thread are no longer than 4096"),
+                       (rb"w4a4_rows16_kernelILi3ELi2ELi\d+ELi6E", "48 columns: three chunks at most")]:
+        assert not re.search(shape, built), (shape, why)
+    assert re.search(rb"rmsnorm_quantize_act_kernelILb0ELi256ELi2E10RowOutFrag", built)         # (names are as expected)
+    assert re.search(rb"w4a4_rows16_kernelILi3ELi2ELi4ELi3E", built)
+
+
 def test_null_and_shape_checks_come_before_device_work(lib):
     # every call below must be rejected on the host: there is no GPU in this process
     ERR_NULL = -1
