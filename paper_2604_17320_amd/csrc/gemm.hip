@@ -49,8 +49,8 @@ namespace {
 //   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
 //   32-row tiles have no time to spare and lose by it).
 // LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that 8 neighbouring rows' pieces
-// do not share banks (a CU with 8 waves reading takes 3.9 ns per read instruction so, 3.3 from consecutive
-// addresses, 13.4 unpermuted).
+// do not share banks (a CU with 8 waves reading takes 3.7 ns per read instruction so, 3.3 from consecutive
+// addresses, 13.4 unpermuted: ubench/load_rate.py).
 enum ActFormat { A8, A8_STARTS, PACKED_INT4 };
 enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL };
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
-    // ones and are never stored; groups past G repeat the last one and meet a zero scale.
+    // ones and are never stored; groups past G repeat the last one and are not used.
     const int Kb = PACKED ? K >> 1 : 128 * (G | 1);      // bytes per activation row
     unsigned oa[LA];                                     // byte offset of this thread's piece of group 0
     int la[LA], pa[LA];                                  // PACKED: LDS slot of the piece

@@ -43,7 +43,7 @@ LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
     LayerWs w;
     size_t M = (size_t)B * N, d = (size_t)H * dh, dkv = (size_t)Hkv * dh;
     size_t kmax = d > (size_t)F ? d : (size_t)F;
-    w.qa = c.take<uint8_t>(quota_a8_bytes(M > 8 ? M : 8, (int)kmax));       // (fragments of a few rows: 1 KB a group)
+    w.qa = c.take<uint8_t>(quota_a8_bytes(M > 8 ? M : 8, (int)kmax));       // (fragments: 1 KB a group and 16 rows, for 32 at most)
     w.sa = c.take<float>(M);
     w.qkv = c.take<f16>(M * (d + 2 * dkv));
     w.q_rot = c.take<f16>(M * d);

@@ -247,7 +247,7 @@ def mfma(csv_path, bench_path=None):
               f"{mean(c['SQ_WAIT_INST_ANY']) / wave_cyc:8.3f}")
     print("\nMFMA inst: issued by all waves; issued TOP/s = MFMA inst * operations of one / duration, against 5.0 (fp8: the W4A4\n"
           "GEMMs, v_mfma_f32_16x16x128_f8f6f4) or 2.5 (fp16, v_mfma_f32_32x32x16_f16) POP/s.  Included are the rows and columns\n"
-          "that a tile pads and, in the W4A4 GEMMs, the constant products that take the code offset out again (one to every\n"
+          "that a tile pads and, in the W4A4 GEMMs below 512 rows, the constant products that take the code offset out again (one to every\n"
           "1, 2 or 4 others, by tile); VALU/MFMA: other vector instructions per MFMA (SQ_INSTS_VALU counts the MFMAs too);\n"
           "MFMA busy = SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs * SQ_BUSY_CU_CYCLES); VALU active, waiting = SQ_ACTIVE_INST_VALU, SQ_WAIT_INST_ANY\n"
           "over SQ_WAVE_CYCLES (share of wave lifetime).")
