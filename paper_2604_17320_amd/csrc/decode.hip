@@ -207,11 +207,8 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
             if (item == 1) xo = x;
             else rope8(x, xp, cs, sn, cc >= HALF, xo);
             if (item < 2) {
-                float f[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) f[e] = (float)xo.h[e];
                 f16 s8;
-                const uint32_t word = kv_quant8(f, &s8, nullptr);
+                const uint32_t word = kv_quant8(xo, &s8, nullptr);
                 new_codes[item][ph * WPT + cc] = word;
                 if ((cc & 7) == 0) new_scales[item][ph * GPT + (cc >> 3)] = s8;
                 if (r0 == 0 && L > t_begin && L <= t_end) {

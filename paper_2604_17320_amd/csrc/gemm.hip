@@ -74,6 +74,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
     constexpr int LDS_A = 2 * STG, LDS_Q = QKV || SILU ? 32 * TROW / 8 : 32 * FROW / 4;
     __shared__ uint4 lds_raw[LDS_A > LDS_Q ? LDS_A : LDS_Q];
+    __shared__ __align__(16) float row_scale[BM];        // for the epilogue: token scales, with the 2^18 of the operands' units
+    __shared__ int row_pos[QKV ? BM : 1];                // and rows of the angle tables
     const unsigned lds0 = lds_address(lds_raw);
 
     int tile_m, tile_n;
@@ -81,6 +83,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid < BM) {
+        const int m = min(m0 + tid, M - 1);
+        row_scale[tid] = sa[m] * F8_UNIT;
+        if constexpr (QKV) row_pos[tid] = min(max(qe.pos[m], 0), qe.n_pos - 1);
+    }
 
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
     // ones and are never stored; groups past G repeat the last one and are not used.
@@ -306,73 +313,73 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #pragma unroll
     for (int i = 0; i < LAG; ++i) scale_in(T - LAG + i, pend[i], pscale[i]);
 
-    // epilogue: token scale (with the 2^18 of the operands' e4m3 units), residual, fp16
+    // epilogue: token scale (with the 2^18 of the operands' e4m3 units), residual, fp16.  What it needs from memory for 32
+    // rows is asked for before they are staged.
     if constexpr (QKV) {
         // Fused epilogue of the QKV projection: 32 rows of the fp16 tile (whole heads: the tile width divides
         // the model width and is a multiple of the head size) at a time are staged in LDS by all waves; then
-        // every thread takes (row, 8-channel chunk) items and applies RoPE at the token's position id (q
+        // every thread takes (row, 8-channel chunk) items, of one chunk, and applies RoPE at the token's position id (q
         // and k tiles) and the 4-bit K/V group quantizer (k and v tiles) exactly as the stand-alone kernel
         // does.  q | k | v are column ranges [0,d) [d,d+dkv) [d+dkv,d+2dkv), so a tile lies in one of them.
+        constexpr int RPI = NT / (BN / 8), KI = 32 / RPI;                // rows of a round of items, rounds
+        const MixMul mul;
         f16 *stage = reinterpret_cast<f16 *>(lds_raw);
         const int d = qe.d, dkv = qe.dkv;
         const int region = n0 < d ? 0 : (n0 < d + dkv ? 1 : 2);          // tile-uniform
-        const int c0 = n0 - (region == 0 ? 0 : (region == 1 ? d : d + dkv));
-        const int CPH = qe.dh >> 3, HALF = CPH >> 1, cpr = dkv >> 3, gpr = dkv >> 6;
+        const int half = qe.dh >> 4, c = tid % (BN / 8), row0 = tid / (BN / 8);        // chunks per half head (4 or 8)
+        const bool second = c & half;
+        const int width = region == 0 ? d : dkv, col = n0 - (region == 0 ? 0 : (region == 1 ? d : d + dkv)) + 8 * c;
+        f16 *out16 = (region == 0 ? qe.q_rot : region == 1 ? qe.khat : qe.vhat) + (size_t)m0 * width + col;
+        uint32_t *codes = (region == 1 ? qe.k_codes : qe.v_codes) + (((size_t)m0 * width + col) >> 3);
+        f16 *scales = (region == 1 ? qe.k_scales : qe.v_scales) + (((size_t)m0 * width + col) >> 6);
 #pragma unroll
         for (int ib = 0; ib < RT / 2; ++ib) {
+            float cs[KI][8], sn[KI][8];
+            if (region < 2) {
+#pragma unroll
+                for (int k = 0; k < KI; ++k) {
+                    const unsigned at = (unsigned)(row_pos[32 * ib + RPI * k + row0] * 8 * half + 8 * (c & (half - 1)));
+                    *reinterpret_cast<float4 *>(cs[k]) = *reinterpret_cast<const float4 *>(qe.cosT + at);
+                    *reinterpret_cast<float4 *>(cs[k] + 4) = *reinterpret_cast<const float4 *>(qe.cosT + at + 4);
+                    *reinterpret_cast<float4 *>(sn[k]) = *reinterpret_cast<const float4 *>(qe.sinT + at);
+                    *reinterpret_cast<float4 *>(sn[k] + 4) = *reinterpret_cast<const float4 *>(qe.sinT + at + 4);
+                }
+            }
             if (ib) __syncthreads();                  // the previous 32 rows have been read
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 sam = *reinterpret_cast<const f32x4 *>(row_scale + 32 * ib + 16 * h + 4 * q);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * h + 4 * q + r, m = m0 + 32 * ib + row;
-                    const float sam = sa[m < M ? m : M - 1] * F8_UNIT;
-                    f16 *p = stage + row * TROW + wave * WN + c16;
+                    f16 *p = stage + (16 * h + 4 * q + r) * TROW + wave * WN + c16;
 #pragma unroll
-                    for (int j = 0; j < CT; ++j) p[16 * j] = to_f16(yacc[2 * ib + h][j][r] * sam);
+                    for (int j = 0; j < CT; ++j) p[16 * j] = to_f16(yacc[2 * ib + h][j][r] * sam[r]);
                 }
+            }
             __syncthreads();
 #pragma unroll
-            for (int k = 0; k < 32 * (BN / 8) / NT; ++k) {
-                const int idx = k * NT + tid, row = idx / (BN / 8), c = idx % (BN / 8);
-                const int m = m0 + 32 * ib + row;
-                const bool m_ok = m < M;
-                const int mm = m_ok ? m : M - 1;
+            for (int k = 0; k < KI; ++k) {
+                const int row = RPI * k + row0, m = 32 * ib + row;       // in the 32 rows, in the tile
+                const bool m_ok = m0 + m < M;
                 Pack16 x, xp, out;
                 x.u = *reinterpret_cast<const uint4 *>(stage + row * TROW + 8 * c);
-                if (y && m_ok) *reinterpret_cast<uint4 *>(y + (size_t)m * ldy + n0 + 8 * c) = x.u;
-                const int col = c0 + 8 * c;           // first channel of the chunk inside q, k or v
+                if (y && m_ok) *reinterpret_cast<uint4 *>(y + (size_t)(m0 + m) * ldy + n0 + 8 * c) = x.u;
+                out = x;
                 if (region < 2) {
-                    const int cc = c % CPH;
-                    xp.u = *reinterpret_cast<const uint4 *>(stage + row * TROW + 8 * (c ^ HALF));
-                    const int pr = min(max(qe.pos[mm], 0), qe.n_pos - 1);
-                    const float *cp = qe.cosT + (size_t)pr * (qe.dh >> 1) + 8 * (cc % HALF);
-                    const float *sp = qe.sinT + (size_t)pr * (qe.dh >> 1) + 8 * (cc % HALF);
-                    float cs[8], sn[8];
-                    *reinterpret_cast<float4 *>(cs) = *reinterpret_cast<const float4 *>(cp);
-                    *reinterpret_cast<float4 *>(cs + 4) = *reinterpret_cast<const float4 *>(cp + 4);
-                    *reinterpret_cast<float4 *>(sn) = *reinterpret_cast<const float4 *>(sp);
-                    *reinterpret_cast<float4 *>(sn + 4) = *reinterpret_cast<const float4 *>(sp + 4);
-                    rope8(x, xp, cs, sn, cc >= HALF, out);
-                } else {
-                    out = x;
+                    xp.u = *reinterpret_cast<const uint4 *>(stage + row * TROW + 8 * (c ^ half));
+                    rope8(x, xp, cs[k], sn[k], second, out, mul);
                 }
+                const unsigned at = (unsigned)(m * width);               // elements from the tile's first row
                 if (region == 0) {
-                    if (m_ok) *reinterpret_cast<uint4 *>(qe.q_rot + (size_t)m * d + col) = out.u;
+                    if (m_ok) *reinterpret_cast<uint4 *>(out16 + at) = out.u;
                 } else {
-                    float f[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) f[e] = (float)out.h[e];
                     Pack16 hat;
                     f16 sc8;
-                    const uint32_t word = kv_quant8(f, &sc8, &hat);    // all 8 lanes of a group take part
+                    const uint32_t word = kv_quant8(out, &sc8, &hat, mul);    // all 8 lanes of a group take part
                     if (m_ok) {
-                        f16 *xh = region == 1 ? qe.khat : qe.vhat;
-                        uint32_t *codes = region == 1 ? qe.k_codes : qe.v_codes;
-                        f16 *scales = region == 1 ? qe.k_scales : qe.v_scales;
-                        *reinterpret_cast<uint4 *>(xh + (size_t)m * dkv + col) = hat.u;
-                        codes[(size_t)m * cpr + (col >> 3)] = word;
-                        if ((c & 7) == 0) scales[(size_t)m * gpr + (col >> 6)] = sc8;
+                        *reinterpret_cast<uint4 *>(out16 + at) = hat.u;
+                        codes[at >> 3] = word;
+                        if ((c & 7) == 0) scales[at >> 6] = sc8;
                     }
                 }
             }
@@ -389,17 +396,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         for (int ib = 0; ib < RT / 2; ++ib) {
             if (ib) __syncthreads();                  // the previous 32 rows have been read
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < 2; ++h) {
+                const f32x4 sam = *reinterpret_cast<const f32x4 *>(row_scale + 32 * ib + 16 * h + 4 * q);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * h + 4 * q + r, m = m0 + 32 * ib + row;
-                    const float sam = sa[m < M ? m : M - 1] * F8_UNIT;
-                    f16 *p = stage + row * ZROW + wave * WC + c16;
+                    f16 *p = stage + (16 * h + 4 * q + r) * ZROW + wave * WC + c16;
 #pragma unroll
                     for (int j = 0; j < CB; ++j)
-                        p[16 * j] = silu_mul((float)to_f16(yacc[2 * ib + h][j][r] * sam),
-                                             (float)to_f16(yacc[2 * ib + h][j + CB][r] * sam));
+                        p[16 * j] = silu_mul((float)to_f16(yacc[2 * ib + h][j][r] * sam[r]),
+                                             (float)to_f16(yacc[2 * ib + h][j + CB][r] * sam[r]));
                 }
+            }
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 32 * (BC / 8) / NT; ++k) {
@@ -412,42 +419,49 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     }
     // 32 rows at a time through LDS as fp32, so that a thread finishes 8 neighbouring columns of a row: one
     // 16-byte residual load, one 16-byte store
+    constexpr int RPI = NT / (BN / 8), KI = 32 / RPI;
     float *stage = reinterpret_cast<float *>(lds_raw);
+    const int n = n0 + 8 * (tid % (BN / 8)), row0 = tid / (BN / 8);
 #pragma unroll
     for (int ib = 0; ib < RT / 2; ++ib) {
+        Pack16 rv[KI];
+        if (res && n < N) {
+#pragma unroll
+            for (int k = 0; k < KI; ++k) {
+                const f16 *rp = res + (size_t)min(m0 + 32 * ib + RPI * k + row0, M - 1) * ldr + n;
+                if (vec_store & 2) rv[k].u = *reinterpret_cast<const uint4 *>(rp);
+                else
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) rv[k].h[e] = rp[e];
+            }
+        }
         if (ib) __syncthreads();                      // the previous 32 rows have been read
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            const f32x4 sam = *reinterpret_cast<const f32x4 *>(row_scale + 32 * ib + 16 * h + 4 * q);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = 16 * h + 4 * q + r, m = m0 + 32 * ib + row;
-                const float sam = sa[m < M ? m : M - 1] * F8_UNIT;
                 float *p = stage + row * FROW + wave * WN + c16;
 #pragma unroll
                 for (int j = 0; j < CT; ++j) {
-                    p[16 * j] = yacc[2 * ib + h][j][r] * sam;
+                    p[16 * j] = yacc[2 * ib + h][j][r] * sam[r];
                     if (ACC_OUT && m < M && n_ok) acc_out[(size_t)m * N + nw + 16 * j + c16] = tot[2 * ib + h][j][r];
                 }
             }
+        }
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 32 * (BN / 8) / NT; ++k) {
-            const int idx = k * NT + tid, row = idx / (BN / 8), n = n0 + 8 * (idx % (BN / 8));
-            const int m = m0 + 32 * ib + row;
-            const float4 *p = reinterpret_cast<const float4 *>(stage + row * FROW + 8 * (idx % (BN / 8)));
+        for (int k = 0; k < KI; ++k) {
+            const int row = RPI * k + row0, m = m0 + 32 * ib + row;
+            const float4 *p = reinterpret_cast<const float4 *>(stage + row * FROW + (n - n0));
             const float4 lo = p[0], hi = p[1];
             float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             if (!y || m >= M || n >= N) continue;
             Pack16 o;
             if (res) {
-                const f16 *rp = res + (size_t)m * ldr + n;
-                Pack16 rv;
-                if (vec_store & 2) rv.u = *reinterpret_cast<const uint4 *>(rp);
-                else
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) rv.h[e] = rp[e];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv.h[e];
+                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv[k].h[e];
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) o.h[e] = to_f16(v[e]);

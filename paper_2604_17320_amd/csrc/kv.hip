@@ -45,19 +45,13 @@ __global__ __launch_bounds__(256) void rope_kv_quant_mha_kernel(
     *reinterpret_cast<float4 *>(sn) = *reinterpret_cast<const float4 *>(sp);
     *reinterpret_cast<float4 *>(sn + 4) = *reinterpret_cast<const float4 *>(sp + 4);
     Pack16 qo, ko;
-    float kf[8], vf[8];
     rope8(q, qp, cs, sn, second, qo);
     rope8(k, kp, cs, sn, second, ko);            // rotated k is an fp16 tensor
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        kf[e] = (float)ko.h[e];
-        vf[e] = (float)v.h[e];
-    }
     *reinterpret_cast<uint4 *>(q_rot + (size_t)row * d + 8 * c) = qo.u;
     Pack16 kh, vh;
     f16 ksc, vsc;
-    uint32_t kw = kv_quant8(kf, &ksc, &kh);
-    uint32_t vw = kv_quant8(vf, &vsc, &vh);
+    uint32_t kw = kv_quant8(ko, &ksc, &kh);
+    uint32_t vw = kv_quant8(v, &vsc, &vh);
     *reinterpret_cast<uint4 *>(khat + (size_t)row * d + 8 * c) = kh.u;
     *reinterpret_cast<uint4 *>(vhat + (size_t)row * d + 8 * c) = vh.u;
     kc[(size_t)row * cpr + c] = kw;
@@ -109,12 +103,9 @@ __global__ __launch_bounds__(256) void rope_kv_quant_kernel(
         *reinterpret_cast<uint4 *>(q_rot + (size_t)row * d + 8 * cr) = xo.u;
         return;
     }
-    float f[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = (float)xo.h[e];
     Pack16 hat;
     f16 sc;
-    const uint32_t word = kv_quant8(f, &sc, &hat);
+    const uint32_t word = kv_quant8(xo, &sc, &hat);
     f16 *xh = region == 1 ? khat : vhat;
     uint32_t *codes = region == 1 ? kc : vc;
     f16 *scales = region == 1 ? ks : vs;
@@ -140,12 +131,9 @@ __global__ __launch_bounds__(256) void kv_quant_append_kernel(
     Pack16 kk, vv;
     kk.u = *reinterpret_cast<const uint4 *>(k + srow * d + 8 * c);
     vv.u = *reinterpret_cast<const uint4 *>(v + srow * d + 8 * c);
-    float kf[8], vf[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { kf[e] = (float)kk.h[e]; vf[e] = (float)vv.h[e]; }
     f16 ksc, vsc;
-    uint32_t kw = kv_quant8(kf, &ksc, nullptr);
-    uint32_t vw = kv_quant8(vf, &vsc, nullptr);
+    uint32_t kw = kv_quant8(kk, &ksc, nullptr);
+    uint32_t vw = kv_quant8(vv, &vsc, nullptr);
     kc[drow * cpr + c] = kw;
     vc[drow * cpr + c] = vw;
     if ((c & 7) == 0) {

@@ -301,6 +301,31 @@ def test_rope_kv_quant_bit_exact(qb, H, dh, M):
     assert np.array_equal(host(vh).view(np.uint16), vhat.view(np.uint16))
 
 
+def test_kv_quant_of_every_group_maximum(qb):
+    """The quantizer's scale and reciprocal are made without IEEE divisions: bit-exact for each of the 31744 finite fp16
+    maxima a group can have, zero and the subnormals included."""
+    H, dh = 64, 128
+    d = H * dh
+    top = np.arange(31744, dtype=np.uint16).view(np.float16).reshape(-1, d // 64, 1).astype(np.float32)
+    M = top.shape[0]
+    r = wl.rng(40, "groups")
+    part = r.uniform(-1, 1, (M, d // 64, 64))
+    part[:, :, ::4] = np.round(part[:, :, ::4] * 14) / 14            # multiples of half a step
+    part[np.arange(M)[:, None], np.arange(d // 64)[None], r.integers(0, 64, (M, d // 64))] = 1.0
+    v = (top * part).astype(np.float16).reshape(M, d)
+    codes, scales, vhat = oracle.kv_quant(v)
+    qkv = np.concatenate([np.zeros_like(v), np.zeros_like(v), v], axis=1)
+    f16 = lambda *shape: torch.empty(shape, dtype=torch.float16, device="cuda")
+    q8 = lambda: torch.empty((M, d // 2), dtype=torch.uint8, device="cuda")
+    out = dict(q=f16(M, d), k=f16(M, d), v=f16(M, d), kc=q8(), ks=f16(M, d // 64), vc=q8(), vs=f16(M, d // 64))
+    cos, sin = wl.rope_tables(dh, 1)
+    qb.quota_rope_kv_quant(dev(qkv), M, H, dh, torch.zeros(M, dtype=torch.int32, device="cuda"), dev(cos), dev(sin), 1,
+                           out["q"], out["k"], out["v"], out["kc"], out["ks"], out["vc"], out["vs"])
+    assert np.array_equal(host(out["vs"]).view(np.uint16), scales.view(np.uint16))
+    assert np.array_equal(unpack4(host(out["vc"])), codes)
+    assert np.array_equal(host(out["v"]).view(np.uint16), vhat.view(np.uint16))
+
+
 def test_kv_quant_append(qb):
     from paper_2604_17320_amd.model import KVCache4
     B, N, H, dh = 2, 24, 4, 128
