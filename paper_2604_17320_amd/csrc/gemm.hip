@@ -114,6 +114,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const unsigned wl = (unsigned)(c16 * 4 + q), wl_up = wl + (unsigned)NC * 4;
     // dword tid + NT k of a stage: the scales of two neighbouring columns, or the start value of a row, in one of its groups
     const float *starts = reinterpret_cast<const float *>(qa + (size_t)M * Kb);
+    constexpr bool ONE_GROUP = BN / 2 % 64 == 0 && (!STARTS || BM % 64 == 0);            // a wave's dwords are of one group
     unsigned os[KD];
     int gs[KD];
 #pragma unroll
@@ -121,6 +122,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         const bool scale = !STARTS || wave + NW * k < SCOPY;
         const int d = scale ? min(tid + NT * k, CH * BN / 2 - 1) : min(tid + NT * k - 64 * SCOPY, CH * BM - 1);
         gs[k] = scale ? d / (BN / 2) : d / BM;
+        if (ONE_GROUP) gs[k] = __builtin_amdgcn_readfirstlane(gs[k]);
         int pair = d % (BN / 2), first = 0;              // pair of columns: in its run of neighbouring ones, and the run's first
         if (SILU) {
             first = pair / (WC / 2) % 2 * (NC >> 1);
@@ -163,8 +165,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         } else {
             const int j = k - CH * LG;
             const bool scale = !STARTS || wave + NW * j < SCOPY;
-            const unsigned g = (unsigned)min(gstage + gs[j], G - 1);
-            copy4_to_lds(scale ? (const void *)sw : starts, os[j] + g * (unsigned)(scale ? 2 * N : 4 * M),
+            const unsigned g = (unsigned)min(gstage + gs[j], G - 1), row = (unsigned)(scale ? 2 * N : 4 * M);
+            const char *base = scale ? (const char *)sw : (const char *)starts;
+            copy4_to_lds(ONE_GROUP ? base + (size_t)g * row : base, ONE_GROUP ? os[j] : os[j] + g * row,
                          dst + (unsigned)(GST * 16 + (wave + NW * j) * 256));
         }
     };
@@ -235,6 +238,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         }
     };
 
+    // A wave's priority rises with every quarter of a stage's row blocks and falls at its end, so that of two workgroups of
+    // a CU the one that is ahead finishes its products while the other waits, unpacks or reads: with equal ones they fall into
+    // step, multiply together and wait together (237 x 4096 x 11008 25.6 -> 23.4 us, 160 x 22016 x 4096 28.0 -> 26.0, 1280 x
+    // 4096 x 11008 64.1 -> 61.2, 5808 x 22016 x 4096 400 -> 396; lowest at products, highest around the barrier: nothing).
+    static_assert(CH >= 4 ? CH % 4 == 0 : RT % (4 / CH) == 0, "whole row blocks, or groups, per quarter");
 #pragma unroll
     for (int k = 0; k < LOADS; ++k) load(k, 0, 0);
     drain();
@@ -265,6 +273,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             for (int c = 0; c < CH; ++c) {
                 if (c && g0 + c >= G) break;             // uniform: the last stage may hold fewer groups
                 const uint4 *gp = sp + c * AST;
+                if (CH >= 4 && c == CH / 4) __builtin_amdgcn_s_setprio(1);
+                if (CH >= 2 && c == CH / 2) __builtin_amdgcn_s_setprio(2);
+                if (CH >= 4 && c == 3 * CH / 4) __builtin_amdgcn_s_setprio(3);
                 float sc[CT];
 #pragma unroll
                 for (int j = 0; j < CT; ++j) sc[j] = read_scale(sp, c, j);
@@ -286,6 +297,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                     if (i + 1 < RT) read_a(gp, i + 1, fa[(i + 1) & 1]);
                     else if (c + 1 < CH) read_a(gp + AST, 0, fa[0]);
                     if (STARTS && i + 1 < RT) k4[(i + 1) & 1] = start_of(sp, c, i + 1, fa[0]);
+                    if (CH == 1 && i == RT / 4 || CH == 2 && c == 0 && i == RT / 2) __builtin_amdgcn_s_setprio(1);
+                    if (CH == 1 && i == RT / 2) __builtin_amdgcn_s_setprio(2);
+                    if (CH == 1 && i == 3 * RT / 4 || CH == 2 && c == 1 && i == RT / 2) __builtin_amdgcn_s_setprio(3);
 #pragma unroll
                     for (int j = 0; j < CT; ++j) {
                         __builtin_amdgcn_sched_barrier(0);
@@ -305,6 +319,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #pragma unroll
                 for (int i = 0; i < LAG; ++i) pscale[i] = sc[(T - LAG + i) % CT];
             }
+            __builtin_amdgcn_s_setprio(0);
             drain();
             store_packed(half ^ 1);
             __syncthreads();

@@ -72,6 +72,18 @@ def test_kernels_that_no_call_reaches_are_not_built():
     assert re.search(rb"w4a4_rows16_kernelILi3ELi2ELi4ELi3E", built)
 
 
+def test_kernels_hold_their_arrays_in_registers():
+    """No kernel of the library uses scratch memory (an array that the compiler has not unrolled, or registers it had to
+    spill: a GEMM tile with its sums there takes three times as long), but the one that only returns integer sums."""
+    built = open(LIB, "rb").read()
+    entry = re.compile(rb"\xa5\.name(?:\xd9.|\xda..|[\xa0-\xbf])(\w+)\xbb\.private_segment_fixed_size"
+                       rb"(\xcd..|\xcc.|\xce....|[\x00-\x7f])", re.S)
+    size = {m[1].decode(): int.from_bytes(m[2][1:] or m[2], "big") for m in entry.finditer(built)}
+    assert len(size) > 200 and any("w4a4_f8" in k for k in size)
+    spills = {k: v for k, v in size.items() if v and not re.search("ActFormatE2ELb1E", k)}
+    assert not spills, spills
+
+
 def test_null_and_shape_checks_come_before_device_work(lib):
     # every call below must be rejected on the host: there is no GPU in this process
     ERR_NULL = -1
