@@ -157,8 +157,9 @@ __device__ __forceinline__ uint32_t code_bits(float t)
     t = fminf(fmaxf(t, -8.0f), 7.0f);          // NaN -> -8, as in code_from
     return __float_as_uint(t + ROW_MAGIC);
 }
-// Units of the fp8 GEMM operands: code / 512 is an e4m3 number for every int4 code, so a group's
-// accumulator counts in 2^-18 (see gemm.hip).
+// Units of the GEMM operands: code / 8 is an e2m3 number for every int4 code, so a group's accumulator counts in 2^-6 (see
+// gemm.hip); as e4m3 numbers (rows16.hip), code / 512, it counts in 2^-18.
+#define F6_UNIT 64.0f
 #define F8_UNIT 262144.0f
 __device__ __forceinline__ float code_unit(uint32_t bits)       // code / 512, exact
 {

@@ -1,20 +1,20 @@
-// W4A4 GEMM for gfx950 on the fp8 matrix cores: y = (int4 activations) x (int4 weights)^T with an
+// W4A4 GEMM for gfx950 on the fp6 matrix cores: y = (int4 activations) x (int4 weights)^T with an
 // fp32 scale per 128-channel weight group.
 //
-// Small integers are exact in fp8 (e4m3), and the fp32 accumulator of v_mfma_f32_16x16x128_f8f6f4 is
+// Small integers are exact in fp6 (e2m3), and the fp32 accumulator of v_mfma_f32_16x16x128_f8f6f4 is
 // exact for sums below 2^24 units, so one such instruction returns the exact integer dot product of a
 // whole 128-deep group -- already as a float.  Every element needs
 // y = fma(acc_g, s_g, y), group after group; against an int8 contraction, which that chain bounds, it is half as
 // long (no conversion in front of the fma).
 //
-// Weights: a nibble c + 8 in 0..15 placed in the low half of a byte IS the e4m3 number (c + 8) / 512
-// (the subnormals and the first binade of e4m3 are one linear range), so the unpack stays at 3 vector
-// instructions per 8 codes: lo = (w & 0x0f..) ^ 0x08.., hi = (w >> 4 & 0x0f..) ^ 0x08...
-// Activations are signed e4m3 numbers a / 512.  The weights' offset of 8 comes back out through the
-// accumulator's start value, -8 / 2^18 * sum of the group's activation codes.  With few rows every wave makes it by
-// one more MFMA per 16 rows and group, against a constant -8 / 512, whose result already lies where the C operand wants
-// it; with many (quota_a8_starts) the quantizer has written it beside the rows and it comes along through LDS (all
-// waves of all column tiles made the same ones).  The 2^18 of the operands' units goes into the token scale (exact).
+// fp6 operands multiply in half the time of fp8 ones (16 cycles), and fragments are a quarter smaller.  Weights: the
+// bits of c + 8 in 0..15 ARE those of the e2m3 number (c + 8) / 8, so that 16 codes take 8 vector instructions
+// (gemm_common.h), two more than as e4m3 bytes.  Activations are signed e2m3 numbers a / 8, made by the row quantizers.
+// The weights' offset of 8 comes back out through the
+// accumulator's start value, -8 / 64 * sum of the group's activation codes.  With few rows every wave makes it by
+// one more MFMA per 16 rows and group, against a constant -8 / 8, whose result already lies where the C operand wants
+// it; with many (quota_a6_starts) the quantizer has written it beside the rows and it comes along through LDS (all
+// waves of all column tiles made the same ones).  The 2^6 of the operands' units goes into the token scale (exact).
 //
 // What bounds it: issued register to register, offset products, scale chain and unpack leave 78 % of the matrix rate to
 // the products at 8 x 4 blocks per wave, 71 at 4 x 4, 39 to 47 on the 32-row tiles; without the offset products the
@@ -22,9 +22,10 @@
 // the matrix cores are busy about half of the time; on the rows of a pruned prompt for 28 to 46 % of it, and the
 // waves wait for 24 to 38 % of their lives: one stage of lookahead, and a wait for all of it.
 //
-// Activation format inside a layer ("A8", written by the row quantizers): e4m3 bytes, row stride 128 (G | 1) (an
-// odd number of 128-byte lines: with a power of two the rows a tile reads together share one L2 channel), every 8
-// codes stored as evens then odds (the order the weight unpack produces); behind the rows, if there are
+// Activation format inside a layer ("A6", written by the row quantizers): four rows at a time, 384 bytes per group, of row r
+// 64 bytes from 64 r on -- the first four of the six dwords of each 32 channels -- and 32 from 256 + 32 r on, the other two;
+// all lines that a tile reads are read whole.  G | 1 groups are laid out (an odd number: with a power of two the rows a tile reads
+// together share one L2 channel); behind the rows, if there are
 // many of them, the start values as floats, [group][row].  The public entry point takes
 // packed int4 rows and converts them while staging (PACKED_INT4).
 #include "common.h"
@@ -48,10 +49,10 @@ namespace {
 //   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
 //   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
 //   32-row tiles have no time to spare and lose by it).
-// LDS rows are 128 bytes; 16-byte piece p of row r sits at p ^ (r % 8), so that 8 neighbouring rows' pieces
-// do not share banks (a CU with 8 waves reading takes 3.7 ns per read instruction so, 3.3 from consecutive
-// addresses, 13.4 unpermuted: ubench/load_rate.py).
-enum ActFormat { A8, A8_STARTS, PACKED_INT4 };
+// A group in LDS: the rows' 64-byte parts, then their 32-byte parts.  Lane (row c, channels 32 q ..) reads 16 bytes of the first
+// and 8 of the second; 16-byte piece q of row r's first part sits at q ^ {0, 2, 3, 1}[r / 4 % 4], and the halves of the second
+// are swapped in rows 8 to 15 of 16, so that the lanes of a read do not share banks.
+enum ActFormat { A6, A6_STARTS, PACKED_INT4 };
 enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL };
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
@@ -61,20 +62,22 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     int vec_store, quota_qkv_epilogue qe)
 {
     constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
-    constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A8_STARTS, QKV = EPI == QKV_ROPE_KV, SILU = EPI == SILU_MUL;
+    constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A6_STARTS, QKV = EPI == QKV_ROPE_KV, SILU = EPI == SILU_MUL;
     static_assert(!SILU || (CT % 2 == 0 && !ACC_OUT), "as many blocks of gate as of up columns");
-    constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : BM * 8 / NT;    // 16-byte pieces per thread and group
+    constexpr int LA = PACKED ? (BM * 4 + NT - 1) / NT : 0;              // PACKED: 16-byte pieces per thread and group
+    // else wave-wide copies of 16 bytes a lane, per wave and stage: of first parts (16 rows each) and of second ones (32 rows)
+    constexpr int MC = PACKED ? 0 : CH * BM / 16 / NW, TC = PACKED ? 0 : CH * BM / 32 / NW;
     // dwords per stage, 64 to a copy: the group scales, then (STARTS) the rows' start values
     constexpr int SCOPY = CH * BN / 128, ICOPY = STARTS ? CH * BM / 64 : 0, KD = (SCOPY + ICOPY + NW - 1) / NW;
-    static_assert(RT % 2 == 0 && (PACKED || BM * 8 % NT == 0) && (!STARTS || CH * BM % 64 == 0) && CH * BN % 128 == 0,
+    static_assert(RT % 2 == 0 && (PACKED || CH * BM % (32 * NW) == 0) && (!STARTS || CH * BM % 64 == 0) && CH * BN % 128 == 0,
                   "whole rows per copy, whole copies of dwords, fragment double buffer");
     // one stage in LDS (in uint4): CH groups of activations (+ a spare piece for PACKED threads without one),
     // then the dwords, up to whole waves
-    constexpr int AST = BM * 8 + (PACKED ? 2 : 0), GST = CH * AST, STG = GST + KD * NT / 4;
+    constexpr int AST = BM * 6 + (PACKED ? 2 : 0), GST = CH * AST, STG = GST + KD * NT / 4;
     constexpr int TROW = BN + 8, FROW = BN + 4;                          // staged output rows: fp16 (QKV), fp32
     constexpr int LDS_A = 2 * STG, LDS_Q = QKV || SILU ? 32 * TROW / 8 : 32 * FROW / 4;
     __shared__ uint4 lds_raw[LDS_A > LDS_Q ? LDS_A : LDS_Q];
-    __shared__ __align__(16) float row_scale[BM];        // for the epilogue: token scales, with the 2^18 of the operands' units
+    __shared__ __align__(16) float row_scale[BM];        // for the epilogue: token scales, with the 2^6 of the operands' units
     __shared__ int row_pos[QKV ? BM : 1];                // and rows of the angle tables
     const unsigned lds0 = lds_address(lds_raw);
 
@@ -85,24 +88,38 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < BM) {
         const int m = min(m0 + tid, M - 1);
-        row_scale[tid] = sa[m] * F8_UNIT;
+        row_scale[tid] = sa[m] * F6_UNIT;
         if constexpr (QKV) row_pos[tid] = min(max(qe.pos[m], 0), qe.n_pos - 1);
     }
 
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
     // ones and are never stored; groups past G repeat the last one and are not used.
-    const int Kb = PACKED ? K >> 1 : 128 * (G | 1);      // bytes per activation row
-    unsigned oa[LA];                                     // byte offset of this thread's piece of group 0
-    int la[LA], pa[LA];                                  // PACKED: LDS slot of the piece
+    const int Kb = K >> 1, fours = (M + 3) >> 2;         // PACKED: bytes per row; A6: fours of rows, bytes of one
+    const unsigned four_bytes = (unsigned)(G | 1) * 384u;
+    constexpr int BB = BM / 16, TB = BM / 32;            // copies of a group's first parts, of its second ones
+    // where the 16-byte piece of channels 32 p .. of a row's first part lies among four
+    auto piece_of = [](int p, int row) { return p ^ (0x1320 >> (row & 12) & 3); };
+    unsigned oa[PACKED ? LA : 1], om = 0, ot = 0;        // byte offsets of this thread's pieces, in group 0 or (A6) a group
+    unsigned om2 = 0;
+    int la[LA ? LA : 1], lt[LA ? LA : 1], pa[LA ? LA : 1];       // PACKED: LDS slots (16 bytes, 8 bytes) of the piece
     // (threads without one write a spare slot: a branch would let the compiler sink the scale chain behind it)
+    if constexpr (PACKED) {
 #pragma unroll
-    for (int j = 0; j < LA; ++j) {
-        const int i = tid + NT * j;
-        const int row = PACKED ? i >> 2 : i >> 3, p = PACKED ? i & 3 : (i & 7) ^ (row & 7);
-        oa[j] = (unsigned)(min(m0 + min(row, BM - 1), M - 1) - m0) * (unsigned)Kb;
-        if (!PACKED) oa[j] += 16 * p;
-        pa[j] = 16 * p;
-        la[j] = row < BM ? row * 8 + ((2 * p) ^ (row & 7)) : BM * 8;
+        for (int j = 0; j < LA; ++j) {
+            const int i = tid + NT * j, row = i >> 2, p = i & 3;
+            oa[j] = (unsigned)(min(m0 + min(row, BM - 1), M - 1) - m0) * (unsigned)Kb;
+            pa[j] = 16 * p;
+            la[j] = row < BM ? row * 4 + piece_of(p, row) : BM * 6;
+            lt[j] = row < BM ? BM * 8 + row * 4 + ((p >> 1 ^ (row >> 3 & 1)) << 1) + (p & 1) : BM * 12 + 2;
+        }
+    } else {
+        // A copy of first parts: lane l brings row l / 4 of 16 to piece l % 4; of second ones: row l / 2 of 32 to half l % 2
+        static_assert(BB <= 2 * NW && (BB % NW == 0 || NW % BB == 0) && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
+        const int last = fours - 1 - (m0 >> 2), row = lane >> 2, row2 = lane >> 1;
+        const unsigned at = (row & 3) * 64 + 16 * piece_of(lane & 3, row);
+        om = (unsigned)min(4 * (wave % BB) + (row >> 2), last) * four_bytes + at;
+        if (BB > NW) om2 = (unsigned)min(4 * (wave + NW) + (row >> 2), last) * four_bytes + at;
+        ot = (unsigned)min(8 * (wave % TB) + (row2 >> 2), last) * four_bytes + 256 + (row2 & 3) * 32 + 16 * ((lane ^ row2 >> 3) & 1);
     }
     // SILU: columns are gate | up, F = N / 2 of each, and a tile takes BN / 2 of either: a wave's first CT / 2 blocks are gate
     // columns, the others up columns of the same channels.
@@ -113,7 +130,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     // this lane's uint4 of a wave's first 16-column block, and of its first block of up columns
     const unsigned wl = (unsigned)(c16 * 4 + q), wl_up = wl + (unsigned)NC * 4;
     // dword tid + NT k of a stage: the scales of two neighbouring columns, or the start value of a row, in one of its groups
-    const float *starts = reinterpret_cast<const float *>(qa + (size_t)M * Kb);
+    const float *starts = reinterpret_cast<const float *>(qa + (size_t)fours * four_bytes);
     constexpr bool ONE_GROUP = BN / 2 % 64 == 0 && (!STARTS || BM % 64 == 0);            // a wave's dwords are of one group
     unsigned os[KD];
     int gs[KD];
@@ -133,13 +150,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 
     constexpr int WS = CH > 1 ? 2 : 1;                   // register sets of packed weights = stages per loop body
     uint4 rw[WS][CH][CT];
-    i32x4 ra[CH][LA];                                    // PACKED staging (struct uint4 here would live in scratch memory)
-    // What a stage needs, load by load: for each of its groups CT weight pieces and LA activation pieces, then
-    // KD dwords.  The pointers (uniform, of the next group to load) stop at the last group:
-    // groups past it are loaded but never used.
-    constexpr int LG = CT + LA, LOADS = CH * LG + KD;
+    i32x4 ra[CH][LA ? LA : 1];                           // PACKED staging (struct uint4 here would live in scratch memory)
+    // What a stage needs, load by load: for each of its groups CT weight pieces and (PACKED) LA activation pieces, then
+    // the wave's copies of activations, then KD dwords.  The weights' pointer (uniform, of the next group to load) stops at the
+    // last group: groups past it are loaded but never used.
+    constexpr int SPAN = SP ? CH * T * SP / 8 : 1;        // products that the loads are spread over
+    constexpr int LG = CT + LA, LC = CH * LG + MC + TC, LOADS = LC + KD;
     const uint4 *wnext = wp + (size_t)nw * 4;
-    const uint8_t *anext = qa + (size_t)m0 * Kb;
+    const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : qa + (size_t)(m0 >> 2) * four_bytes;
     int gnext = 0, gstage = 0;                            // next group to load, first group of the stage being loaded
     auto load = [&](int k, int set, int half) {
         const unsigned dst = lds0 + (unsigned)half * (STG * 16);
@@ -147,23 +165,28 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             const int c = k / LG, r = k % LG;
             if (r < CT) {
                 rw[set][c][r] = wnext[(r < CB ? wl : wl_up) + 64 * (r % CB)];
-            } else {
-                const int j = r - CT;
-                if constexpr (PACKED) {
-                    const unsigned kb = (unsigned)min(gnext * 64 + pa[j], Kb - 16);
-                    ra[c][j] = *reinterpret_cast<const i32x4 *>(qa + (size_t)m0 * Kb + (oa[j] + kb));
-                } else {
-                    copy16_to_lds(anext, oa[j], dst + (unsigned)(c * AST * 16 + (wave + NW * j) * 1024));
-                }
+            } else if constexpr (PACKED) {
+                const unsigned kb = (unsigned)min(gnext * 64 + pa[r - CT], Kb - 16);
+                ra[c][r - CT] = *reinterpret_cast<const i32x4 *>(a0 + (oa[r - CT] + kb));
             }
             if (r == LG - 1) {
                 const bool more = gnext + 1 < G;
                 wnext += more ? (size_t)N * 4 : 0;
-                anext += more ? 128 : 0;
                 gnext += more;
             }
-        } else {
+        } else if (k < LC) {
             const int j = k - CH * LG;
+            if (j < MC) {                                // block wave + NW j of the stage's, BB to a group
+                const int c = BB >= NW ? j * NW / BB : j * (NW / BB) + wave / BB, b = BB >= NW ? wave + j * NW % BB : wave % BB;
+                copy16_to_lds(a0 + (unsigned)min(gstage + c, G - 1) * 384u, BB > NW && j % 2 ? om2 : om,
+                              dst + (unsigned)(c * AST * 16 + b * 1024));
+            } else {
+                const int c = (j - MC) * (NW / TB) + wave / TB;
+                copy16_to_lds(a0 + (unsigned)min(gstage + c, G - 1) * 384u, ot,
+                              dst + (unsigned)(c * AST * 16 + BM * 64 + wave % TB * 1024));
+            }
+        } else {
+            const int j = k - LC;
             const bool scale = !STARTS || wave + NW * j < SCOPY;
             const unsigned g = (unsigned)min(gstage + gs[j], G - 1), row = (unsigned)(scale ? 2 * N : 4 * M);
             const char *base = scale ? (const char *)sw : (const char *)starts;
@@ -178,10 +201,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 uint4 *dst = lds_raw + half * STG + c * AST;
 #pragma unroll
                 for (int j = 0; j < LA; ++j) {
-                    uint4 e0, e1;
-                    codes_to_e4m3(make_uint4(ra[c][j][0], ra[c][j][1], ra[c][j][2], ra[c][j][3]), e0, e1);
-                    dst[la[j]] = e0;
-                    dst[la[j] ^ 1] = e1;
+                    uint32_t e[6];
+                    codes_e2m3(ra[c][j], e);
+                    dst[la[j]] = make_uint4(e[0], e[1], e[2], e[3]);
+                    reinterpret_cast<uint2 *>(dst)[lt[j]] = make_uint2(e[4], e[5]);
                 }
             }
         }
@@ -198,28 +221,26 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 yacc[i][j][r] = 0.0f;
                 if (ACC_OUT) tot[i][j][r] = 0;
             }
-    // dword i (8 codes) of a packed piece
-    auto unpack_w = [&](const uint4 &w4, int i, i32x8 &fb) {
-        const uint32_t w = i == 0 ? w4.x : i == 1 ? w4.y : i == 2 ? w4.z : w4.w;
-        fb[2 * i] = (int)((w & 0x0F0F0F0Fu) ^ 0x08080808u);
-        fb[2 * i + 1] = (int)(((w >> 4) & 0x0F0F0F0Fu) ^ 0x08080808u);
-    };
+    uint32_t flip[3];
+    e2m3_flips(flip);
     // this lane's activation fragment of row block i of the group at `gp`, the start values of its four
     // results, and the scale of its column in block j
-    const int fr = c16 * 8, fx = c16 & 7;
-    const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
-                               (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
+    const int fr = c16 * 4 + piece_of(q, c16), ft = c16 * 4 + ((q >> 1 ^ c16 >> 3) << 1) + (q & 1);
+    const i32x8 minus8 = i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0};
     auto read_a = [&](const uint4 *gp, int i, i32x8 &fa) {
-        const uint4 a0 = gp[i * 128 + fr + ((2 * q) ^ fx)], a1 = gp[i * 128 + fr + ((2 * q + 1) ^ fx)];
-        fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
+        const uint4 a0 = gp[i * 64 + fr];
+        const uint2 a1 = reinterpret_cast<const uint2 *>(gp + BM * 4)[i * 64 + ft];
+        fa = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, 0, 0};
     };
     // the start values of row block i's results in group c of the stage
     auto start_of = [&](const uint4 *sp, int c, int i, const i32x8 &fa) {
-        if constexpr (!STARTS) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{0, 0, 0, 0}, 0, 0, 0, 0, 0, 0);
+        if constexpr (!STARTS) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, minus8, f32x4{0, 0, 0, 0}, 2, 2, 0, 0, 0, 0);
         else return *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(sp + GST) + 64 * SCOPY + c * BM + 16 * i + 4 * q);
     };
     auto read_scale = [&](const uint4 *sp, int c, int j) {
-        return (float)reinterpret_cast<const f16 *>(sp + GST)[c * BN + wave * WN + 16 * j + c16];
+        float s = (float)reinterpret_cast<const f16 *>(sp + GST)[c * BN + wave * WN + 16 * j + c16];
+        asm("" : "+v"(s));           // (converted once: multiply-adds that take the half itself issue a third slower)
+        return s;
     };
     // The group scale of a result is applied LAG results later, so that the matrix core's latency is
     // covered; the last ones of a group are finished during the next.
@@ -234,7 +255,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             yacc[i][j][r] = __builtin_fmaf(a[r], s, yacc[i][j][r]);
-            if (ACC_OUT) tot[i][j][r] += (int)(a[r] * F8_UNIT);
+            if (ACC_OUT) tot[i][j][r] += (int)(a[r] * F6_UNIT);
         }
     };
 
@@ -262,9 +283,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             read_a(sp, 0, fa[0]);
             if (CH == 1) {
 #pragma unroll
-                for (int j = 0; j < CT; ++j)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) unpack_w(rw[0][0][j], i, fb[j]);
+                for (int j = 0; j < CT; ++j) weights_e2m3(rw[0][0][j], flip, fb[j]);
             }
             gstage = g0 + CH;
 #pragma unroll
@@ -281,9 +300,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 for (int j = 0; j < CT; ++j) sc[j] = read_scale(sp, c, j);
                 if (CH > 1) {
 #pragma unroll
-                    for (int j = 0; j < CT; ++j)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) unpack_w(rw[set][c][j], i, fb[j]);
+                    for (int j = 0; j < CT; ++j) weights_e2m3(rw[set][c][j], flip, fb[j]);
                 }
                 // The issue order is pinned result by result (left alone the scheduler puts the scale chain
                 // of a result right behind its own MFMA and waits out the matrix core's latency, and reads
@@ -304,15 +321,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                     for (int j = 0; j < CT; ++j) {
                         __builtin_amdgcn_sched_barrier(0);
                         const int t = i * CT + j;
-                        const f32x4 a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 1], fb[j], k4[i & 1], 0, 0, 0, 0, 0, 0);
+                        const f32x4 a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i & 1], fb[j], k4[i & 1], 2, 2, 0, 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
                         if (t < LAG) scale_in(T - LAG + t, pend[t], pscale[t]);
                         else scale_in(t - LAG, pend[t % LAG], sc[(t - LAG) % CT]);
                         pend[t % LAG] = a;
                         if (!STARTS && j == CT - 1 && i + 1 < RT) k4[(i + 1) & 1] = start_of(sp, c, i + 1, fa[(i + 1) & 1]);
 #pragma unroll
-                        for (int k = 0; k < (SP ? LOADS : 0); ++k)
-                            if (k * (CH * T * SP / 8) / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1);
+                        for (int e = 0; e < (SP ? (LOADS - 1) / SPAN + 1 : 0); ++e) {
+                            const int k = ((c * T + t) * LOADS + SPAN - 1) / SPAN + e;
+                            if (k < LOADS && k * SPAN / LOADS == c * T + t) load(k, (set + 1) % WS, half ^ 1);
+                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -328,7 +347,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #pragma unroll
     for (int i = 0; i < LAG; ++i) scale_in(T - LAG + i, pend[i], pscale[i]);
 
-    // epilogue: token scale (with the 2^18 of the operands' e4m3 units), residual, fp16.  What it needs from memory for 32
+    // epilogue: token scale (with the 2^6 of the operands' units), residual, fp16.  What it needs from memory for 32
     // rows is asked for before they are staged.
     if constexpr (QKV) {
         // Fused epilogue of the QKV projection: 32 rows of the fp16 tile (whole heads: the tile width divides
@@ -529,7 +548,7 @@ f8_kernel tile_kernel(int v)
         if constexpr (P == PACKED_INT4) return nullptr;
         else return F8_TILE_5(P, false, E);
     default:
-        if constexpr (P != A8 || E == SILU_MUL) return nullptr;
+        if constexpr (P != A6 || E == SILU_MUL) return nullptr;
         else return F8_TILE_6(P, false, E);
     }
 }
@@ -576,7 +595,7 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
         {4, 6.76f, 4, {0.364f, 0.565f, 0.861f, 1.243f}, 0.340f},
         {8, 5.12f, 1, {0.198f}, 0.350f},
     };
-    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < 6 || !quota_a8_starts(M)); };
+    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < 6 || !quota_a6_starts(M)); };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
     const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     int best = -1;
@@ -616,19 +635,19 @@ static int gemm_16_rows_at_a_time(const uint8_t *qa, quota_rows16_format format,
     return QUOTA_OK;
 }
 
-// GEMM on activations in the internal A8 format (M > 16 rows of a layer).
-int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
+// GEMM on activations in the internal A6 format (M > 16 rows of a layer).
+int quota_internal_w4a4_gemm_a6(const uint8_t *qa6, const float *sa, int M, const quota_weights *W,
                                 void *y_f16, int ldy, const void *residual_opt, int ldr, hipStream_t st)
 {
-    if (!qa8 || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
+    if (!qa6 || !sa || !W || !W->packed || !W->scales || !y_f16) return QUOTA_ERR_NULL;
     if (W->N % 64 != 0 || W->K % 32 != 0) return QUOTA_ERR_SHAPE;
     if (M <= 0) return QUOTA_OK;
-    if (M <= 16) return quota_internal_rows16(qa8, QUOTA_ROWS16_A8, sa, M, W, y_f16, ldy, residual_opt, ldr, st);
+    if (M <= 16) return quota_internal_rows16(qa6, QUOTA_ROWS16_A6, sa, M, W, y_f16, ldy, residual_opt, ldr, st);
     if (!scales_on_dwords(W))
-        return gemm_16_rows_at_a_time(qa8, QUOTA_ROWS16_A8, quota_a8_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
+        return gemm_16_rows_at_a_time(qa6, QUOTA_ROWS16_A6, quota_a6_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
                                       (const f16 *)residual_opt, ldr, st);
     const int v = choose_tile(M, W->N, W->K, 0, 256, TILES);
-    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, PLAIN>(v) : tile_kernel<A8, PLAIN>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_f16, ldy,
+    return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, PLAIN>(v) : tile_kernel<A6, PLAIN>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
 }
 
@@ -636,16 +655,16 @@ int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, cons
 // stand-alone product.  Returns QUOTA_ERR_SHAPE when the fused form does not fit (the caller then runs the two kernels
 // separately): with unaligned scales, or where the tile of choice has one block of columns per wave (projections
 // that leave the chip part idle, 37 x 2752 x 512: 4 us each way).
-int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *z_f16,
+int quota_internal_w4a4_gemm_silu(const uint8_t *qa6, const float *sa, int M, const quota_weights *W, void *z_f16,
                                   hipStream_t st)
 {
-    if (!qa8 || !sa || !W || !W->packed || !W->scales || !z_f16) return QUOTA_ERR_NULL;
+    if (!qa6 || !sa || !W || !W->packed || !W->scales || !z_f16) return QUOTA_ERR_NULL;
     if (M <= 16 || W->N % 64 != 0 || W->K % 32 != 0 || !scales_on_dwords(W) || (reinterpret_cast<uintptr_t>(z_f16) & 15))
         return QUOTA_ERR_SHAPE;
     const int v = choose_tile(M, W->N, W->K, 0, 256, TILES);
     if (kTiles[v].bn < 128) return QUOTA_ERR_SHAPE;
-    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, SILU_MUL>(v) : tile_kernel<A8, SILU_MUL>(v), v, kTiles[v].kernel_id,
-                     qa8, sa, M, W, (f16 *)z_f16, W->N / 2, nullptr, 0, nullptr, st);
+    return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, SILU_MUL>(v) : tile_kernel<A6, SILU_MUL>(v), v, kTiles[v].kernel_id,
+                     qa6, sa, M, W, (f16 *)z_f16, W->N / 2, nullptr, 0, nullptr, st);
 }
 
 extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const quota_weights *W,
@@ -678,13 +697,13 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
 }
 
 // QKV projection with the RoPE + 4-bit K/V quantizer fused into the epilogue (see the kernel).
-// qa8 is in the A8 format.
+// qa6 is in the A6 format.
 // y_opt, when not null, also receives the plain fp16 q | k | v.  Returns QUOTA_ERR_SHAPE when the
 // shape does not fit the fused form (the caller then runs the two kernels separately).
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa6, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st)
 {
-    if (!qa8 || !sa || !W || !W->packed || !W->scales || !qe || !qe->pos || !qe->cosT || !qe->sinT ||
+    if (!qa6 || !sa || !W || !W->packed || !W->scales || !qe || !qe->pos || !qe->cosT || !qe->sinT ||
         !qe->q_rot || !qe->khat || !qe->vhat || !qe->k_codes || !qe->k_scales || !qe->v_codes || !qe->v_scales)
         return QUOTA_ERR_NULL;
     if (M < 0 || qe->n_pos <= 0) return QUOTA_ERR_INVALID_ARG;
@@ -694,6 +713,6 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, con
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
     const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128, TILES);
-    return launch_f8(quota_a8_starts(M) ? tile_kernel<A8_STARTS, QKV_ROPE_KV>(v) : tile_kernel<A8, QKV_ROPE_KV>(v), v, kTiles[v].kernel_id, qa8, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
+    return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, QKV_ROPE_KV>(v) : tile_kernel<A6, QKV_ROPE_KV>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
                      nullptr, st, qe);
 }

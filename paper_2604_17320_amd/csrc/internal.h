@@ -28,7 +28,7 @@ struct quota_compact_args {
     const int32_t *pos;
     const void *skc, *sks, *svc, *svs;     // staged 4-bit K/V of all N rows
     void *x_out, *o_out;                   // o_out optional (fp16 copy of the kept attention rows)
-    uint8_t *oq_out;                       // optional: int4 codes of the kept attention rows (A8 format) ...
+    uint8_t *oq_out;                       // optional: int4 codes of the kept attention rows (A6 format) ...
     float *os_out;                         // ... and their per-token scales (the quantizer Q)
     int32_t *pos_out, *rows_out;
     quota_kv_cache *cache;
@@ -56,33 +56,36 @@ struct quota_qkv_epilogue {
     uint32_t *k_codes, *v_codes;
     f16 *k_scales, *v_scales;
 };
-int quota_internal_w4a4_gemm_qkv(const uint8_t *qa8, const float *sa, int M, const quota_weights *W,
+int quota_internal_w4a4_gemm_qkv(const uint8_t *qa6, const float *sa, int M, const quota_weights *W,
                                  void *y_opt, const quota_qkv_epilogue *qe, hipStream_t st);
 
-// The layer's row quantizers and GEMM on activations in the A8 format (gemm.hip): M rows of
-// quota_a8_row_bytes(K) bytes, then, if quota_a8_starts(M), [groups][M] floats, quota_a8_bytes in all.
-inline size_t quota_a8_row_bytes(int K) { return ((((size_t)K + 127) / 128) | 1) * 128; }
+// The layer's row quantizers and GEMM on activations in the A6 format (gemm.hip): four rows at a time, quota_a6_row_bytes(K)
+// bytes for each (padded to whole fours), then, if quota_a6_starts(M), [groups][M] floats.
+inline size_t quota_a6_row_bytes(int K) { return ((((size_t)K + 127) / 128) | 1) * 96; }
 // The sums cost the quantizers more than the GEMMs gain where those wait for memory anyway.  A 7B layer with and
 // without: all its products at 160 to 237 rows 147.0 and 146.1 us, first product at 640 rows 188.9 and 189.8,
 // 11264 and 5808 rows 1609 and 1656.
-inline bool quota_a8_starts(size_t M) { return M >= 512; }
-inline size_t quota_a8_bytes(size_t M, int K)
+inline bool quota_a6_starts(size_t M) { return M >= 512; }
+// Bytes of M rows in it, or as the few-row GEMM's fragments (up to 32 rows, 1 KB a group and 16 rows).
+inline size_t quota_a6_bytes(size_t M, int K)
 {
-    return M * (quota_a8_row_bytes(K) + (quota_a8_starts(M) ? ((size_t)K + 127) / 128 * sizeof(float) : 0));
+    const size_t G = ((size_t)K + 127) / 128, rows = (M + 3) / 4 * 4 * quota_a6_row_bytes(K);
+    const size_t frag = M <= 32 ? (M + 15) / 16 * G * 1024 : 0;
+    return (rows > frag ? rows : frag) + (quota_a6_starts(M) ? M * G * sizeof(float) : 0);
 }
-int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa8,
+int quota_internal_rmsnorm_quantize_a6(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa6,
                                        float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st);
-int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *scale, void *z_opt,
+int quota_internal_silu_mul_quantize_a6(const void *gu_f16, int M, int F, uint8_t *qa6, float *scale, void *z_opt,
                                         const void *z_inject_opt, hipStream_t st);
-int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st);
-int quota_internal_w4a4_gemm_a8(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *y_f16, int ldy,
+int quota_internal_quantize_a6(const void *x_f16, int M, int d, uint8_t *qa6, float *scale, hipStream_t st);
+int quota_internal_w4a4_gemm_a6(const uint8_t *qa6, const float *sa, int M, const quota_weights *W, void *y_f16, int ldy,
                                 const void *residual_opt, int ldr, hipStream_t st);
-int quota_internal_w4a4_gemm_silu(const uint8_t *qa8, const float *sa, int M, const quota_weights *W, void *z_f16, hipStream_t st);
+int quota_internal_w4a4_gemm_silu(const uint8_t *qa6, const float *sa, int M, const quota_weights *W, void *z_f16, hipStream_t st);
 
 // GEMM of at most 16 rows, or as fragments 32 (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that
 // quota_internal_rows16_quantizes accepts: as they are, or through RMSNorm.  frag_silu and glu: the gate/up projection,
 // z [M][N / 2] = SiLU(gate) * up.
-enum quota_rows16_format { QUOTA_ROWS16_A8, QUOTA_ROWS16_PACKED, QUOTA_ROWS16_FRAG };
+enum quota_rows16_format { QUOTA_ROWS16_A6, QUOTA_ROWS16_PACKED, QUOTA_ROWS16_FRAG };
 int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const float *sa, int M, const quota_weights *W, void *y, int ldy,
                           const void *res, int ldr, hipStream_t st);
 int quota_internal_rows16_frag_silu(const uint8_t *qf, const float *sa, int M, const quota_weights *W, void *z, hipStream_t st);

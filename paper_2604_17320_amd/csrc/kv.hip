@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
         double none = 0.0;
         block_max_sum<4, true, false>(a, none, sm);
         float s;
-        quantize_cached_row<false, ROW_THREADS, NCH>(v, n16, tid, a, row_out(oq_out, drow, n16), s);
+        quantize_cached_row<false, ROW_THREADS, NCH>(v, n16, tid, a, row_out(oq_out, drow, n16), (int)(drow & 3), s);
         if (tid == 0) os_out[drow] = s;
     }
 }
@@ -244,7 +244,7 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
     if (a->n_keep == 0) return QUOTA_OK;
     const double rows = (double)a->n_keep * a->B, dd = a->d, dk = a->dkv;
     ProfScope prof(QUOTA_K_COMPACT_ROWS, 0, rows * (2 * (4 * dd + dk + dk / 16) + 8), st);
-    with_a8_out(a->oq_out, a->n_keep * a->B, [&](auto out) {
+    with_a6_out(a->oq_out, a->n_keep * a->B, [&](auto out) {
         typedef decltype(out) OUT;
         auto kernel = a->d <= 4096 ? compact_rows_kernel<2, OUT> : a->d <= 8192 ? compact_rows_kernel<4, OUT>
                                                                                 : compact_rows_kernel<8, OUT>;

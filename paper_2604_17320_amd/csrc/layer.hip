@@ -24,7 +24,7 @@ struct Carver {
 };
 
 struct LayerWs {
-    uint8_t *qa;        // int4 activations of the current GEMM input, A8 format or fragments
+    uint8_t *qa;        // int4 activations of the current GEMM input, A6 format or fragments
     float *sa;
     f16 *qkv, *q_rot, *khat, *vhat, *o;
     uint8_t *skc, *svc; // staged 4-bit K/V of all rows
@@ -43,7 +43,7 @@ LayerWs carve(void *ws, int B, int N, int H, int Hkv, int dh, int F)
     LayerWs w;
     size_t M = (size_t)B * N, d = (size_t)H * dh, dkv = (size_t)Hkv * dh;
     size_t kmax = d > (size_t)F ? d : (size_t)F;
-    w.qa = c.take<uint8_t>(quota_a8_bytes(M > 8 ? M : 8, (int)kmax));       // (fragments: 1 KB a group and 16 rows, for 32 at most)
+    w.qa = c.take<uint8_t>(quota_a6_bytes(M, (int)kmax));
     w.sa = c.take<float>(M);
     w.qkv = c.take<f16>(M * (d + 2 * dkv));
     w.q_rot = c.take<f16>(M * d);
@@ -111,7 +111,7 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
     qe.k_scales = w.sks; qe.v_scales = w.svs;
     int rc = quota_internal_w4a4_gemm_qkv(w.qa, w.sa, M, &L->qkv, want_qkv ? w.qkv : nullptr, &qe, st);
     if (rc != QUOTA_ERR_SHAPE) return rc;
-    TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, st));
+    TRY(quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, &L->qkv, w.qkv, d + 2 * dkv, nullptr, 0, st));
     return quota_internal_rope_kv_quant(w.qkv, M, L->H, Hkv, L->dh, pos, L->cosT, L->sinT, L->n_pos, w.q_rot,
                                         w.khat, w.vhat, w.skc, w.sks, w.svc, w.svs, st);
 }
@@ -127,8 +127,8 @@ static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const flo
         TRY(quota_internal_rmsnorm_quantize_frag(x, M, d, gamma, eps, w.qa, w.sa, st));
         return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, nullptr, 0, st);
     }
-    TRY(quota_internal_rmsnorm_quantize_a8(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
-    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
+    TRY(quota_internal_rmsnorm_quantize_a6(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
+    return quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
 }
 static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const quota_weights *W, void *y, int ldy,
                          const void *res, int ldr, hipStream_t st)
@@ -138,12 +138,12 @@ static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const qu
         TRY(quota_internal_quantize_frag(x, M, d, w.qa, w.sa, st));
         return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, res, ldr, st);
     }
-    TRY(quota_internal_quantize_a8(x, M, d, w.qa, w.sa, st));
-    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
+    TRY(quota_internal_quantize_a6(x, M, d, w.qa, w.sa, st));
+    return quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, W, y, ldy, res, ldr, st);
 }
 // The SwiGLU block on rows x1, added to them: RMSNorm, quantizer, gate/up, SiLU product, quantizer, down.  Without taps that
 // want the gate | up rows or z, the gate/up projection makes the product itself, where its tile can, and w.gu holds z.
-// Else it stores gate | up and the quantizer in front of down makes the product (any number of rows, in the A8 format).
+// Else it stores gate | up and the quantizer in front of down makes the product (any number of rows, in the A6 format).
 static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1, const quota_taps *t, void *x_out, hipStream_t st)
 {
     const int d = L->H * L->dh, F = L->F;
@@ -155,18 +155,18 @@ static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1,
             TRY(quota_internal_rmsnorm_quantize_frag(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, st));
             rc = quota_internal_rows16_frag_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
         } else {
-            TRY(quota_internal_rmsnorm_quantize_a8(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st));
+            TRY(quota_internal_rmsnorm_quantize_a6(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st));
             rc = quota_internal_w4a4_gemm_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
         }
         if (rc == QUOTA_OK) return quantize_gemm(w, w.gu, M, F, &L->down, x_out, d, x1, d, st);
         if (rc != QUOTA_ERR_SHAPE) return rc;
-        TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->gu, w.gu, 2 * F, nullptr, 0, st));
+        TRY(quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, &L->gu, w.gu, 2 * F, nullptr, 0, st));
     } else {
         TRY(rmsnorm_gemm(w, x1, M, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
         TRY(dump(t->gu, w.gu, (size_t)M * 2 * F * 2, st));
     }
-    TRY(quota_internal_silu_mul_quantize_a8(w.gu, M, F, w.qa, w.sa, t->z, t->inject_z, st));
-    return quota_internal_w4a4_gemm_a8(w.qa, w.sa, M, &L->down, x_out, d, x1, d, st);
+    TRY(quota_internal_silu_mul_quantize_a6(w.gu, M, F, w.qa, w.sa, t->z, t->inject_z, st));
+    return quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, &L->down, x_out, d, x1, d, st);
 }
 
 extern "C" size_t quota_prefill_workspace_bytes(const quota_layer *L, int B, int N)
@@ -224,7 +224,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
     // attention half on every token that entered the layer (the two vector cues of Eq. 6 are side
     // outputs of the first quantizer, taken only where they are used)
-    TRY(quota_internal_rmsnorm_quantize_a8(s->x, M, d, L->gamma1, L->eps, w.qa, w.sa, score ? w.sumsq : nullptr,
+    TRY(quota_internal_rmsnorm_quantize_a6(s->x, M, d, L->gamma1, L->eps, w.qa, w.sa, score ? w.sumsq : nullptr,
                                            score ? w.ressq : nullptr, st));
     TRY(qkv_rope_kv_quant(L, w, M, s->pos, t->qkv != nullptr, st));
     TRY(dump(t->qkv, w.qkv, (size_t)M * (d + 2 * dkv) * 2, st));
@@ -267,7 +267,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
 
     // token-wise rest of the block on the kept rows only
     if (Mk > 0) {
-        TRY(quota_internal_w4a4_gemm_a8(w.qa, w.sa, Mk, &L->o, w.x1, d, w.x_keep, d, st));
+        TRY(quota_internal_w4a4_gemm_a6(w.qa, w.sa, Mk, &L->o, w.x1, d, w.x_keep, d, st));
         TRY(dump(t->x1, w.x1, (size_t)Mk * d * 2, st));
         TRY(swiglu(L, w, Mk, w.x1, t, s->x_out, st));
     }

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     }
     group_reduce<GROUP, true, WANT_METRICS>(a, ss, sm);
     float s;
-    double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
+    double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), (int)(row & 3), s);
     if (WANT_METRICS) { float dummy = 0.0f; group_reduce<GROUP, false, true>(dummy, rs, sm); }
     if (lane == 0) {
         if (scale) scale[row] = s;
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
     }
     group_reduce<GROUP, true, WANT_METRICS>(a, rs, sm);
     float s;
-    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
+    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), (int)(row & 3), s);
     if (lane == 0) {
         scale[row] = s;
         if (WANT_METRICS) {
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
     double none = 0.0;
     group_reduce<GROUP, true, false>(a, none, sm);
     float s;
-    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), s);
+    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), (int)(row & 3), s);
     if (lane == 0) scale[row] = s;
 }
 
@@ -540,13 +540,13 @@ extern "C" int quota_rmsnorm_quantize_act(const void *x_f16, int M, int d, int l
                             ressq_opt, h_opt, (hipStream_t)stream);
 }
 
-int quota_internal_rmsnorm_quantize_a8(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa8,
+int quota_internal_rmsnorm_quantize_a6(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa6,
                                        float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st)
 {
-    int rc = check_rows(x_f16, M, d, d, qa8, scale);
+    int rc = check_rows(x_f16, M, d, d, qa6, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    return with_a8_out(qa8, M, [&](auto out) { return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, out, scale, sumsq_opt, ressq_opt, nullptr, st); });
+    return with_a6_out(qa6, M, [&](auto out) { return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, out, scale, sumsq_opt, ressq_opt, nullptr, st); });
 }
 
 template <typename OUT>
@@ -577,13 +577,13 @@ extern "C" int quota_silu_mul_quantize_act(const void *gu_f16, int M, int F, uin
                              (hipStream_t)stream);
 }
 
-int quota_internal_silu_mul_quantize_a8(const void *gu_f16, int M, int F, uint8_t *qa8, float *scale,
+int quota_internal_silu_mul_quantize_a6(const void *gu_f16, int M, int F, uint8_t *qa6, float *scale,
                                         void *z_opt, const void *z_inject_opt, hipStream_t st)
 {
-    int rc = check_rows(gu_f16, M, F, F, qa8, scale);
+    int rc = check_rows(gu_f16, M, F, F, qa6, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
-    return with_a8_out(qa8, M, [&](auto out) { return silu_mul_quantize(gu_f16, M, F, out, scale, z_opt, z_inject_opt, st); });
+    return with_a6_out(qa6, M, [&](auto out) { return silu_mul_quantize(gu_f16, M, F, out, scale, z_opt, z_inject_opt, st); });
 }
 
 template <typename OUT>
@@ -598,12 +598,12 @@ static int quantize_rows(const void *x_f16, int M, int d, OUT q, float *scale, h
     return QUOTA_OK;
 }
 
-// Per-token quantizer of a dense fp16 [M][d] into the A8 format.
-int quota_internal_quantize_a8(const void *x_f16, int M, int d, uint8_t *qa8, float *scale, hipStream_t st)
+// Per-token quantizer of a dense fp16 [M][d] into the A6 format.
+int quota_internal_quantize_a6(const void *x_f16, int M, int d, uint8_t *qa6, float *scale, hipStream_t st)
 {
-    int rc = check_rows(x_f16, M, d, d, qa8, scale);
+    int rc = check_rows(x_f16, M, d, d, qa6, scale);
     if (rc != QUOTA_OK || M == 0) return rc;
-    return with_a8_out(qa8, M, [&](auto out) { return quantize_rows(x_f16, M, d, out, scale, st); });
+    return with_a6_out(qa6, M, [&](auto out) { return quantize_rows(x_f16, M, d, out, scale, st); });
 }
 
 // The two quantizers of at most 32 rows into the few-row GEMM's fragments.

@@ -4,42 +4,44 @@
 #pragma once
 #include "common.h"
 #include "internal.h"
+#include "gemm_common.h"
 
 #define ROW_THREADS 256
 #define ROW_MAXCHUNK 16  // workgroup-per-row kernels: 16 chunks * 8 halves * 256 threads = 32768 columns
 #define ROW_MAXCOLS 32768
 
-// Where a quantized row goes: packed int4 (the public format, two codes per byte), the GEMM's A8 format --
-// e4m3 bytes, every 8 codes as evens then odds, each row zero-padded to whole 128-channel groups, and behind the rows
-// (if quota_a8_starts) what a sum of products with weights c + 8 starts from, [group][row] -- or, for at
+// Where a quantized row goes: packed int4 (the public format, two codes per byte), the GEMM's A6 format -- e2m3 numbers,
+// zero-padded to whole 128-channel groups; for every four rows and group 384 bytes, of row r from 64 r on the first four of the six
+// dwords of each 32 channels, from 256 + 32 r on the others -- and behind the rows
+// (if quota_a6_starts) what a sum of products with weights c + 8 starts from, [group][row] -- or, for at
 // most 32 rows, packed int4 as the few-row GEMM's fragments: per 16 rows 1 KB per group, the 32 codes number q of row m's
 // 128 at 16-byte piece 16 q + m % 16.  A null pointer drops the output.
 struct RowOutPacked {
-    static constexpr bool A8 = false, STARTS = false, MANY = true;       // MANY: launches of any number of rows
+    static constexpr bool A6 = false, STARTS = false, MANY = true;       // MANY: launches of any number of rows
     uint32_t *q;
     static __device__ __forceinline__ int at(int c) { return c; }
 };
 struct RowOutFrag {
-    static constexpr bool A8 = false, STARTS = false, MANY = false;
+    static constexpr bool A6 = false, STARTS = false, MANY = false;
     uint32_t *q;
     static __device__ __forceinline__ int at(int c) { return (c >> 4) * 256 + (c >> 2 & 3) * 64 + (c & 3); }
 };
-struct RowOutA8 {
-    static constexpr bool A8 = true, STARTS = false, MANY = false;       // (with_a8_out: less than quota_a8_starts)
-    uint2 *q;
+struct RowOutA6 {
+    static constexpr bool A6 = true, STARTS = false, MANY = false;       // (with_a6_out: less than quota_a6_starts)
+    uint32_t *q;
 };
-struct RowOutA8Starts {
-    static constexpr bool A8 = true, STARTS = true, MANY = true;
-    uint2 *q;
+struct RowOutA6Starts {
+    static constexpr bool A6 = true, STARTS = true, MANY = true;
+    uint32_t *q;
     int rows;            // of the launch
     float *starts;       // of this row
 };
-// run(the output of M rows in the A8 format)
+// run(the output of M rows in the A6 format)
 template <typename RUN>
-static inline int with_a8_out(void *qa8, int M, RUN run)
+static inline int with_a6_out(void *qa6, int M, RUN run)
 {
-    if (quota_a8_starts(M)) return run(RowOutA8Starts{(uint2 *)qa8, M, nullptr});
-    return run(RowOutA8{(uint2 *)qa8});
+    if (quota_a6_starts(M)) return run(RowOutA6Starts{(uint32_t *)qa6, M, nullptr});
+    return run(RowOutA6{(uint32_t *)qa6});
 }
 // The row (or rows) that workgroup `wg` takes: with start values, 4 bytes per row and group, neighbouring rows belong on one XCD, whose L2
 // puts them together (5808 rows and 11008 columns: 0.4 % of a layer's time).
@@ -57,40 +59,55 @@ __host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row,
 {
     return RowOutFrag{o.q + (row >> 4) * ((nchunk + 15) >> 4) * 256 + 4 * (row & 15)};
 }
-__host__ __device__ __forceinline__ RowOutA8 row_out(RowOutA8 o, size_t row, int nchunk)
+__host__ __device__ __forceinline__ RowOutA6 row_out(RowOutA6 o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
-    return RowOutA8{o.q + row * (G | 1) * 16};
+    return RowOutA6{o.q + (row >> 2) * (G | 1) * 96 + (row & 3) * 16};
 }
-__host__ __device__ __forceinline__ RowOutA8Starts row_out(RowOutA8Starts o, size_t row, int nchunk)
+__host__ __device__ __forceinline__ RowOutA6Starts row_out(RowOutA6Starts o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
-    return RowOutA8Starts{o.q + row * (G | 1) * 16, o.rows, reinterpret_cast<float *>(o.q + (size_t)o.rows * (G | 1) * 16) + row};
+    return RowOutA6Starts{o.q + (row >> 2) * (G | 1) * 96 + (row & 3) * 16, o.rows,
+                          reinterpret_cast<float *>(o.q + (((size_t)o.rows + 3) >> 2) * (G | 1) * 96) + row};
+}
+// Stores chunk c (8 channels) of a row in the A6 format; four neighbouring lanes hold the chunks of 32 channels.  A pair's d0 is
+// its first lane's; its second takes what the first one adds to d1 and d2.
+typedef uint32_t u32x2_at4 __attribute__((ext_vector_type(2), aligned(4), may_alias));
+__device__ __forceinline__ void store_e2m3(uint32_t *row_q, int row, int c, const float unit[8])
+{
+    uint32_t own, d2, d1;
+    codes_e2m3(codes_of_e4m3(units_to_e4m3(unit)), c & 1, own, d2, d1);
+    d1 = own | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d1, 0xA0, 0xf, 0xf, false);       // quad lanes 0 0 2 2
+    const uint32_t d2s = d2 | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d2, 0xA0, 0xf, 0xf, false);
+    uint32_t *main = row_q + (c >> 4) * 96 + (c >> 2 & 3) * 4;
+    uint32_t *tail = row_q + (c >> 4) * 96 + 64 - 8 * (row & 3) + (c >> 2 & 3) * 2;
+    if (c & 1) *reinterpret_cast<u32x2_at4 *>(c & 2 ? tail : main + 1) = u32x2_at4{d1, d2s};
+    else main[c & 2 ? 3 : 0] = own;
 }
 
 // final phase shared by the row kernels: quantize the cached row `v` with absmax `a`, store the
 // codes, return this thread's share of the residual sum of squares.
 template <bool WANT_RES, int GROUP, int NCH, typename OUT>
 __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchunk, int idx, float a,
-                                                      OUT out, float &s_out)
+                                                      OUT out, int row, float &s_out)
 {
     float s = 1.0f, inv = 0.0f;
     if (a != 0.0f) { s = a / 7.0f; inv = 7.0f / a; }
     s_out = s;
     double rs = 0.0;
-    const int nout = OUT::A8 ? (nchunk + 15) & ~15 : nchunk;
+    const int nout = OUT::A6 ? (nchunk + 15) & ~15 : nchunk;
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
         int c = idx + GROUP * r;
         if (c < nout) {
-            const bool live = !OUT::A8 || c < nchunk;
+            const bool live = !OUT::A6 || c < nchunk;
             uint32_t word = 0;
             float unit[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float f = live ? (float)v[r].h[e] : 0.0f;
                 const uint32_t cb = code_bits(f * inv);
-                if (OUT::A8) {
+                if (OUT::A6) {
                     unit[e] = code_unit(cb);
                 } else {
                     word |= (cb & 0xFu) << (4 * e);
@@ -101,12 +118,12 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
                     rs = __builtin_fma((double)rr, (double)rr, rs);     // product exact in fp64
                 }
             }
-            if constexpr (OUT::A8) {
-                out.q[c] = units_to_e4m3(unit);
+            if constexpr (OUT::A6) {
+                store_e2m3(out.q, row, c, unit);
                 if constexpr (OUT::STARTS) {         // the 16 lanes of a group add up in its last one
                     float u = ((unit[0] + unit[1]) + (unit[2] + unit[3])) + ((unit[4] + unit[5]) + (unit[6] + unit[7]));
                     u = row16_sum(u);
-                    if ((c & 15) == 15) out.starts[(size_t)(c >> 4) * out.rows] = u * (-8.0f / 512.0f);
+                    if ((c & 15) == 15) out.starts[(size_t)(c >> 4) * out.rows] = u * (-8.0f * 512.0f / 64.0f);     // -8 / 8 times the sum of codes / 8
                 }
             } else {
                 if (out.q) out.q[OUT::at(c)] = word;

@@ -4,8 +4,10 @@
 // groups cannot be split.  The exact group sums can: in a round the 8 waves of a workgroup take U groups
 // each (group r0 + 8 u + w for wave w: all their loads in flight together), park their 16 x 16 sums in
 // LDS, and one thread per output then runs the fp32 chain over those 8 U groups in ascending order -- the
-// same bits as the tiled kernel.  Weights and activations are fp8 operands as there (gemm.hip): one
-// v_mfma_f32_16x16x128_f8f6f4 per group and 16 columns, one more against the constant -8 / 512 per group.
+// same bits as the tiled kernel.  Weights and activations are e4m3 numbers, (c + 8) / 512 and a / 512 (rows in the A6 format
+// e2m3 ones, as in gemm.hip; the products wait for the weights either way): one
+// v_mfma_f32_16x16x128_f8f6f4 per group and 16 columns, one more against the constant -8 per group.  A nibble c + 8 in the low half of
+// a byte is the e4m3 number (c + 8) / 512.
 // Packed activations carry the same offset, (a + 8)(w + 8) - 8 (a + 8) - 8 (w + 8) + 64 = a w, and need one more
 // constant product per group and 16 columns: that costs less than reading them as bytes (every CU reads all
 // of them; 16 x 4096 x 11008: 11.0 us with byte activations, 9.7 packed).  Inside a layer the quantizer leaves
@@ -35,10 +37,10 @@
 
 namespace {
 
-enum { ROWS_A8 = 0, ROWS_PACKED, ROWS_FRAG, ROWS_QUANT, ROWS_RMSNORM };
+enum { ROWS_A6 = 0, ROWS_PACKED, ROWS_FRAG, ROWS_QUANT, ROWS_RMSNORM };
 
 struct RowsIn {
-    const uint8_t *qa;          // A8 / PACKED / FRAG: activations and token scales
+    const uint8_t *qa;          // A6 / PACKED / FRAG: activations and token scales
     const float *sa;
     const f16 *x;               // QUANT, RMSNORM: rows [M][K]
     const float *gamma;         // RMSNORM
@@ -203,9 +205,15 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
     for (int o = 0; o < OPT; ++o) y32[o] = 0.0f;
 
-    const size_t arow_bytes = MODE == ROWS_PACKED ? (size_t)(K >> 1) : (size_t)128 * (G | 1);
-    const uint8_t *arow = MODE <= ROWS_PACKED ? in.qa + (size_t)min(c16, M - 1) * arow_bytes : nullptr;
-    uint4 ra[U][MODE == ROWS_A8 ? 2 : RB], rb[U][NB];
+    constexpr bool E2M3 = MODE == ROWS_A6;
+    constexpr float UNIT = E2M3 ? F6_UNIT : F8_UNIT;
+    constexpr int FMT = E2M3 ? 2 : 0;               // of the matrix instruction's operands
+    const int arow_at = min(c16, M - 1);
+    const uint8_t *arow = MODE == ROWS_PACKED ? in.qa + (size_t)arow_at * (K >> 1)
+                          : E2M3 ? in.qa + (size_t)(arow_at >> 2) * (G | 1) * 384 + (arow_at & 3) * 64 : nullptr;
+    uint32_t flip[3];
+    if (E2M3) e2m3_flips(flip);
+    uint4 ra[U][MODE == ROWS_A6 ? 2 : RB], rb[U][NB];
     uint32_t rsv[SPT];
     auto fetch = [&](int n0, int r0) {
 #pragma unroll
@@ -217,10 +225,10 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             if (MODE == ROWS_FRAG) {
 #pragma unroll
                 for (int i = 0; i < RB; ++i) ra[u][i] = *reinterpret_cast<const uint4 *>(in.qa + (size_t)(i * G + g) * 1024 + 16 * lane);
-            } else if (MODE == ROWS_A8) {
-                const uint4 *ag = reinterpret_cast<const uint4 *>(arow + g * 128 + 32 * q);
-                ra[u][0] = ag[0];
-                ra[u][MODE == ROWS_A8 ? 1 : 0] = ag[1];
+            } else if (MODE == ROWS_A6) {
+                ra[u][0] = *reinterpret_cast<const uint4 *>(arow + g * 384 + 16 * q);
+                const uint2 t = *reinterpret_cast<const uint2 *>(arow + g * 384 + 256 - 32 * (arow_at & 3) + 8 * q);
+                ra[u][MODE == ROWS_A6 ? 1 : 0] = make_uint4(t.x, t.y, 0, 0);
             } else if (MODE == ROWS_PACKED) {
                 ra[u][0] = *reinterpret_cast<const uint4 *>(arow + min(g * 64 + q * 16, (K >> 1) - 16));
             }
@@ -238,7 +246,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
         quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] { fetch(blk * BC, 0); });
     else
         fetch(blk * BC, 0);
-    const i32x8 minus8 = i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
+    const i32x8 minus8 = E2M3 ? i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0} : i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
     while (true) {                                  // rounds of this workgroup's column blocks
         float *accs = xbuf + par * BUF;
@@ -253,7 +261,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
                 uint4 a0, a1;
-                if constexpr (MODE == ROWS_A8) {
+                if constexpr (MODE == ROWS_A6) {
                     a0 = ra[u][0];
                     a1 = ra[u][1];
                 } else if constexpr (OFFSET_A) {
@@ -265,18 +273,23 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                     a1 = ag[1];
                 }
                 fa[i] = i32x8{(int)a0.x, (int)a0.y, (int)a0.z, (int)a0.w, (int)a1.x, (int)a1.y, (int)a1.z, (int)a1.w};
-                k4[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i], minus8, f32x4{c0, c0, c0, c0}, 0, 0, 0, 0, 0, 0);
+                k4[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i], minus8, f32x4{c0, c0, c0, c0}, FMT, FMT, 0, 0, 0, 0);
             }
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                uint4 b0, b1;
-                unsigned_e4m3(rb[u][j], b0, b1);
-                const i32x8 fb = i32x8{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, (int)b1.x, (int)b1.y, (int)b1.z, (int)b1.w};
+                i32x8 fb;
+                if constexpr (E2M3) {
+                    weights_e2m3(rb[u][j], flip, fb);
+                } else {
+                    uint4 b0, b1;
+                    unsigned_e4m3(rb[u][j], b0, b1);
+                    fb = i32x8{(int)b0.x, (int)b0.y, (int)b0.z, (int)b0.w, (int)b1.x, (int)b1.y, (int)b1.z, (int)b1.w};
+                }
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
                     f32x4 k = k4[i];
                     if (OFFSET_A) k = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(minus8, fb, k, 0, 0, 0, 0, 0, 0);
-                    acc[u][j][i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i], fb, k, 0, 0, 0, 0, 0, 0);
+                    acc[u][j][i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa[i], fb, k, FMT, FMT, 0, 0, 0, 0);
                 }
             }
         }
@@ -329,10 +342,10 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
 #pragma unroll
                     for (int o = 0; o < (GLU ? 1 : OPT); ++o) {
                         const int on = blk * BC + 16 * (o + oj) + (ol & 15);
-                        float v = y32[o] * (sa * F8_UNIT);
+                        float v = y32[o] * (sa * UNIT);
                         if (res) v = v + (float)res[(size_t)om * ldr + on];
                         f16 out = to_f16(v);
-                        if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * F8_UNIT)));
+                        if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * UNIT)));
                         y[(size_t)om * ldy + on] = out;
                     }
                 }
@@ -432,7 +445,7 @@ int quota_internal_rows16(const uint8_t *qa, quota_rows16_format format, const f
     in.qa = qa;
     in.sa = sa;
     switch (format) {
-    case QUOTA_ROWS16_A8: return rows16<ROWS_A8, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
+    case QUOTA_ROWS16_A6: return rows16<ROWS_A6, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
     case QUOTA_ROWS16_FRAG:
         if (M > 16) return rows16<ROWS_FRAG, 1, 2>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
         return rows16<ROWS_FRAG, 1>(in, M, W, (f16 *)y, ldy, (const f16 *)res, ldr, 0, st);
