@@ -138,7 +138,7 @@ int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M,
 
 /* Pins the GEMM kernel variant that quota_w4a4_gemm and the layer calls use
  * from now on (process-wide; for tests and tuning): -1 = chosen per launch
- * (default); 0..4 = the workgroup tiles (rows x columns) 64x256, 64x128,
+ * (default); 0..4 = the workgroup tiles (rows x columns) 128x128, 64x128,
  * 32x128, 32x64, 128x256.  Launches a variant cannot take (at most 16 rows,
  * the int32 output, tiles that would straddle q | k | v or cut a head with the
  * fused QKV epilogue) ignore the pin.  QUOTA_ERR_INVALID_ARG for other values. */
@@ -507,7 +507,8 @@ enum {
     QUOTA_K_GEMM_OTHER, QUOTA_K_ROPE_KV_QUANT,
     QUOTA_K_KV_QUANT_APPEND, QUOTA_K_ATTENTION_FWD, QUOTA_K_ATTENTION_COLMASS,
     QUOTA_K_SCORE_TOKENS, QUOTA_K_TOPK_PRUNE, QUOTA_K_COMPACT_ROWS, QUOTA_K_QUANTIZE_WEIGHTS,
-    QUOTA_K_PACK_WEIGHTS, QUOTA_K_ATTENTION_DECODE, QUOTA_K_KV_APPEND_ROWS, QUOTA_K_GEMM_ROWS16, QUOTA_KERNEL_COUNT
+    QUOTA_K_PACK_WEIGHTS, QUOTA_K_ATTENTION_DECODE, QUOTA_K_KV_APPEND_ROWS, QUOTA_K_GEMM_ROWS16,
+    QUOTA_K_GEMM_128X128, QUOTA_KERNEL_COUNT
 };
 
 /* Per kernel class: launches seen, summed HIP-event time around them (ms) and

@@ -243,8 +243,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         return s;
     };
     // The group scale of a result is applied LAG results later, so that the matrix core's latency is
-    // covered; the last ones of a group are finished during the next.
-    constexpr int LAG = 2;
+    // covered; the last ones of a group are finished during the next.  (One covers a 16-cycle product; two take as long
+    // and five registers more, which the 128 x 128 tile does not have.)
+    constexpr int LAG = 1;
     static_assert(T % LAG == 0, "the carried results keep their order");
     f32x4 pend[LAG];
     float pscale[LAG];
@@ -510,25 +511,25 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
 //                                            RT CT NW CH SP          OCC
-// (64 x 128 as four waves of 64 x 32, three workgroups per CU, against two waves of 64 x 64: 237 x 22016 x 4096 40.2 ->
-// 35.2 us, 1101 x 4608 x 3584 35.0 -> 30.3, 1280 x 4096 x 11008 and x 4096 57.0 -> 52.8 in the mean; a weight still belongs to one wave)
-#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>  // 64 x 256
-#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 2, 4, 2, 6, P, A, QK, 3>  // 64 x 128
-#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 0, P, A, QK, 2>  // 32 x 128
+// 128 x 128 as waves of 128 x 32: three workgroups per CU, so that a launch's last round is finer than with 128 x 256 (5808 x
+// 4096 x 11008 213 -> 189 us, 3324 x 5120 x 13824 237 -> 187, 640 x 12288 x 4096 38 -> 33, 11264 x 12288 x 4096 443 and 468).
+// 64 x 128 as four waves of 64 x 32, three workgroups per CU; a weight belongs to one wave.  Stages of four groups are long enough for
+// a round trip to memory (400 x 22016 x 4096 49 us, 45 so); the packed entry point's rows, which pass registers, leave no
+// room for more than two.
+#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<8, 2, 4, 2, 6, P, A, QK, P == PACKED_INT4 ? 2 : 3>   // 128 x 128
+#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 2, 4, P == PACKED_INT4 ? 2 : 4, 6, P, A, QK, 3>   // 64 x 128
+#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 6, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
 #define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
-// Tiles 1 and 3 once more in longer stages, for launches that leave a CU with two workgroups at most, where a stage is
-// a round trip to memory (366 x 4096 x 11008 38.2 us, 53.7 in stages of two groups; 128 x 4096 x 11008 23.3,
-// 26.6 in stages of four); with more workgroups their LDS is in the way (640 x 22016 x 4096 77 us and 60).  Activations of a layer only, not pinned.
-#define F8_TILE_5(P, A, QK) w4a4_f8_kernel<4, 2, 4, 4, 6, P, A, QK, 2>  // 64 x 128
-#define F8_TILE_6(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 0, P, A, QK, 2>  // 32 x 64
+// 32 x 64 once more in longer stages, for launches that leave a CU with three workgroups at most (101 x 4096 x 11008 22.4 -> 19.5
+// us, 237 x 4096 x 11008 25.4 -> 24.4).  Activations of a layer only, not pinned.
+#define F8_TILE_5(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 6, P, A, QK, 2>  // 32 x 64
 
 struct TileShape { int bm, bn, nt, kernel_id; };
-constexpr int TILES = 7, PINNED_TILES = 5;
-const TileShape kTiles[TILES] = {{64, 256, 256, QUOTA_K_GEMM_64X256}, {64, 128, 256, QUOTA_K_GEMM_64X128},
+constexpr int TILES = 6, PINNED_TILES = 5;
+const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128, 256, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
-                             {128, 256, 256, QUOTA_K_GEMM_128X256}, {64, 128, 256, QUOTA_K_GEMM_64X128},
-                                  {32, 64, 256, QUOTA_K_GEMM_32X64}};
+                             {128, 256, 256, QUOTA_K_GEMM_128X256}, {32, 64, 256, QUOTA_K_GEMM_32X64}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
@@ -544,12 +545,9 @@ f8_kernel tile_kernel(int v)
         if constexpr (E == SILU_MUL) return nullptr;         // (one block of columns per wave: never chosen)
         else return F8_TILE_3(P, false, E);
     case 4: return F8_TILE_4(P, false, E);
-    case 5:
-        if constexpr (P == PACKED_INT4) return nullptr;
-        else return F8_TILE_5(P, false, E);
     default:
         if constexpr (P != A6 || E == SILU_MUL) return nullptr;
-        else return F8_TILE_6(P, false, E);
+        else return F8_TILE_5(P, false, E);
     }
 }
 
@@ -576,8 +574,8 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
 
 int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
 
-// Tile choice by a cost model fitted to measured kernel times on this GPU (us; 88 shapes of 24 to 1101 rows, 3584 to
-// 37888 columns and 3584 to 18944 channels, all tiles: the choice costs 0.15 % over the best of each on average, 6 % at
+// Tile choice by a cost model fitted to measured kernel times on this GPU (us; 75 shapes of 40 to 11264 rows, 3584 to
+// 37888 columns and 3584 to 18944 channels, all tiles: the choice costs 0.4 % over the best of each on average, 7 % at
 // most).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
 // slope * x beyond; c0 is the launch, prologue and epilogue.
 // Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
@@ -587,15 +585,14 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
 {
     struct Cost { int ch; float c0; int n; float u[6], slope; };
     static const Cost cost[TILES] = {
-        {2, 7.15f, 4, {0.715f, 1.011f, 1.660f, 2.033f}, 0.584f},
-        {2, 7.30f, 6, {0.528f, 0.627f, 0.795f, 1.360f, 1.510f, 1.694f}, 0.305f},
-        {4, 6.65f, 4, {0.280f, 0.415f, 0.612f, 0.820f}, 0.215f},
-        {4, 5.24f, 4, {0.232f, 0.282f, 0.401f, 0.505f}, 0.137f},
-        {1, 9.17f, 4, {1.062f, 1.578f, 2.543f, 3.313f}, 0.960f},
-        {4, 6.76f, 4, {0.364f, 0.565f, 0.861f, 1.243f}, 0.340f},
-        {8, 5.12f, 1, {0.198f}, 0.350f},
+        {2, 6.09f, 6, {0.557f, 0.722f, 1.080f, 1.793f, 1.855f, 2.212f}, 0.421f},
+        {4, 5.13f, 6, {0.308f, 0.470f, 0.662f, 1.032f, 1.255f, 1.461f}, 0.250f},
+        {4, 4.64f, 4, {0.258f, 0.351f, 0.518f, 0.829f}, 0.186f},
+        {4, 4.39f, 4, {0.193f, 0.230f, 0.352f, 0.455f}, 0.110f},
+        {1, 6.94f, 4, {0.957f, 1.270f, 2.406f, 2.549f}, 0.794f},
+        {8, 5.21f, 3, {0.143f, 0.208f, 0.323f}, 0.119f},
     };
-    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < 6 || !quota_a6_starts(M)); };
+    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < PINNED_TILES || !quota_a6_starts(M)); };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
     const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     int best = -1;

@@ -198,3 +198,30 @@ def test_layer_qwen25_vl_7b_shape(qb):
         assert eq16(host(cache.v_scales)[:, :n_keep].reshape(B * n_keep, -1), ref["cache_vs"])
         assert eq16(host(out["x1"]), ref["x1"]) and eq16(host(out["gu"]), ref["gu"]) and eq16(host(x_out), ref["x_next"])
         assert close_f16(host(out["o"]), ref["o"])
+
+
+@pytest.mark.parametrize("N", [17, 33, 35, 62, 130, 257, 513, 516])
+def test_layer_rows_and_packed_rows_give_the_same_projection(qb, N):
+    """The row quantizers' own GEMM format against packed rows, which the GEMM converts: the same bits, at rows that end
+    inside a four, a block of 16 and a tile, with start values (512 and more) and without, and a ragged last group.  Rows of a NaN
+    (all codes -8, the only way to that code), of an infinity, of zeros and of one value (codes 7) among them."""
+    from paper_2604_17320_amd.model import KVCache4, make_taps
+    d, H, Hkv, dh, F = 512 + 128, 10, 2, 64, 160
+    W, L, cos, sin = build_gqa_layer(d, H, Hkv, dh, F, 77, 640)
+    dkv = Hkv * dh
+    x = wl.rng(N, "rows").standard_normal((N, d)).astype(np.float16)
+    x[0, 5], x[N // 2, 9], x[N - 1], x[N - 2] = np.nan, np.inf, 0.0, 3.0
+    xd, pos = dev(x), dev(np.arange(N, dtype=np.int32))
+    t16 = lambda *s: torch.full(s, float("nan"), dtype=torch.float16, device="cuda")
+    qkv, y, x_out = t16(N, d + 2 * dkv), t16(N, d + 2 * dkv), t16(N, d)
+    cache, pos_out = KVCache4(1, N, Hkv, dh), torch.zeros(N, dtype=torch.int32, device="cuda")
+    ws = torch.full((L.workspace_bytes(1, N),), 0xFF, dtype=torch.uint8, device="cuda")
+    st = qb.State(1, N, 0, 0, xd.data_ptr(), pos.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+    qb.quota_prefill_layer(L.desc, st, qb.KEEP_ALL, qb.quota_score_params_default(), cache.desc, make_taps(qkv=qkv), ws)
+    codes, scale = torch.zeros((N, d // 2), dtype=torch.uint8, device="cuda"), torch.zeros(N, device="cuda")
+    qb.quota_rmsnorm_quantize_act(xd, N, d, d, L.gamma1, W.eps, codes, scale)
+    c = unpack4(host(codes))
+    assert (c[0] == -8).all() and (c[N - 1] == 0).all() and c.max() == 7
+    qb.quota_w4a4_gemm(codes, scale, N, L.qkv.desc, y, d + 2 * dkv)
+    assert torch.equal(qkv.view(torch.int16), y.view(torch.int16))
+    assert np.array_equal(host(y).view(np.uint16), oracle.w4a4_gemm(c, host(scale), *W.qkv).view(np.uint16))
