@@ -24,8 +24,8 @@
 //
 // Activation format inside a layer ("A6", written by the row quantizers): four rows at a time, 384 bytes per group, of row r
 // 64 bytes from 64 r on -- the first four of the six dwords of each 32 channels -- and 32 from 256 + 32 r on, the other two;
-// all lines that a tile reads are read whole.  G | 1 groups are laid out (an odd number: with a power of two the rows a tile reads
-// together share one L2 channel); behind the rows, if there are
+// all lines that a tile reads are read whole.  G is laid out as a whole number of stages, and one more (an odd number: with a
+// power of two the rows a tile reads together share one L2 channel); behind the rows, if there are
 // many of them, the start values as floats, [group][row].  The public entry point takes
 // packed int4 rows and converts them while staging (PACKED_INT4).
 #include "common.h"
@@ -95,12 +95,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
     // ones and are never stored; groups past G repeat the last one and are not used.
     const int Kb = K >> 1, fours = (M + 3) >> 2;         // PACKED: bytes per row; A6: fours of rows, bytes of one
-    const unsigned four_bytes = (unsigned)(G | 1) * 384u;
+    const unsigned four_bytes = (unsigned)quota_a6_groups(G) * 384u;
     constexpr int BB = BM / 16, TB = BM / 32;            // copies of a group's first parts, of its second ones
     // where the 16-byte piece of channels 32 p .. of a row's first part lies among four
     auto piece_of = [](int p, int row) { return p ^ (0x1320 >> (row & 12) & 3); };
     unsigned oa[PACKED ? LA : 1], om = 0, ot = 0;        // byte offsets of this thread's pieces, in group 0 or (A6) a group
-    unsigned om2 = 0;
+    unsigned om2 = 0, dm = 0, dt = 0;                    // ... and where its wave's pieces go in LDS
     int la[LA ? LA : 1], lt[LA ? LA : 1], pa[LA ? LA : 1];       // PACKED: LDS slots (16 bytes, 8 bytes) of the piece
     // (threads without one write a spare slot: a branch would let the compiler sink the scale chain behind it)
     if constexpr (PACKED) {
@@ -117,9 +117,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         static_assert(BB <= 2 * NW && (BB % NW == 0 || NW % BB == 0) && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
         const int last = fours - 1 - (m0 >> 2), row = lane >> 2, row2 = lane >> 1;
         const unsigned at = (row & 3) * 64 + 16 * piece_of(lane & 3, row);
-        om = (unsigned)min(4 * (wave % BB) + (row >> 2), last) * four_bytes + at;
+        om = (unsigned)min(4 * (wave % BB) + (row >> 2), last) * four_bytes + at + wave / BB % NW * 384;
         if (BB > NW) om2 = (unsigned)min(4 * (wave + NW) + (row >> 2), last) * four_bytes + at;
-        ot = (unsigned)min(8 * (wave % TB) + (row2 >> 2), last) * four_bytes + 256 + (row2 & 3) * 32 + 16 * ((lane ^ row2 >> 3) & 1);
+        ot = (unsigned)min(8 * (wave % TB) + (row2 >> 2), last) * four_bytes + 256 + (row2 & 3) * 32 + 16 * ((lane ^ row2 >> 3) & 1) +
+             wave / TB % NW * 384;
+        dm = lds0 + wave / BB % NW * (AST * 16) + wave % BB * 1024;
+        dt = lds0 + wave / TB % NW * (AST * 16) + BM * 64 + wave % TB * 1024;
     }
     // SILU: columns are gate | up, F = N / 2 of each, and a tile takes BN / 2 of either: a wave's first CT / 2 blocks are gate
     // columns, the others up columns of the same channels.
@@ -153,37 +156,33 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     i32x4 ra[CH][LA ? LA : 1];                           // PACKED staging (struct uint4 here would live in scratch memory)
     // What a stage needs, load by load: for each of its groups CT weight pieces and (PACKED) LA activation pieces, then
     // the wave's copies of activations, then KD dwords.  The weights' pointer (uniform, of the next group to load) stops at the
-    // last group: groups past it are loaded but never used.
+    // last group, the activations' at the last stage (whose groups past G are in memory): what lies past them is loaded
+    // but never used.  Scalar instructions count: a wave issues one of any kind at a time.
     constexpr int SPAN = SP ? CH * T * SP / 8 : 1;        // products that the loads are spread over
     constexpr int LG = CT + LA, LC = CH * LG + MC + TC, LOADS = LC + KD;
     const uint4 *wnext = wp + (size_t)nw * 4;
+    const unsigned wstep = (unsigned)N * 64u;
     const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : qa + (size_t)(m0 >> 2) * four_bytes;
-    int gnext = 0, gstage = 0;                            // next group to load, first group of the stage being loaded
+    int gstage = 0;                                       // first group of the stage being loaded
     auto load = [&](int k, int set, int half) {
-        const unsigned dst = lds0 + (unsigned)half * (STG * 16);
+        const unsigned to = (unsigned)half * (STG * 16);
         if (k < CH * LG) {
             const int c = k / LG, r = k % LG;
             if (r < CT) {
                 rw[set][c][r] = wnext[(r < CB ? wl : wl_up) + 64 * (r % CB)];
             } else if constexpr (PACKED) {
-                const unsigned kb = (unsigned)min(gnext * 64 + pa[r - CT], Kb - 16);
+                const unsigned kb = (unsigned)min(min(gstage + c, G - 1) * 64 + pa[r - CT], Kb - 16);
                 ra[c][r - CT] = *reinterpret_cast<const i32x4 *>(a0 + (oa[r - CT] + kb));
             }
-            if (r == LG - 1) {
-                const bool more = gnext + 1 < G;
-                wnext += more ? (size_t)N * 4 : 0;
-                gnext += more;
-            }
+            if (r == LG - 1) wnext = (const uint4 *)((const char *)wnext + (G - gstage > c + 1 ? wstep : 0u));
         } else if (k < LC) {
             const int j = k - CH * LG;
             if (j < MC) {                                // block wave + NW j of the stage's, BB to a group
-                const int c = BB >= NW ? j * NW / BB : j * (NW / BB) + wave / BB, b = BB >= NW ? wave + j * NW % BB : wave % BB;
-                copy16_to_lds(a0 + (unsigned)min(gstage + c, G - 1) * 384u, BB > NW && j % 2 ? om2 : om,
-                              dst + (unsigned)(c * AST * 16 + b * 1024));
+                const int c = BB >= NW ? j * NW / BB : j * (NW / BB), b = BB >= NW ? j * NW % BB : 0;
+                copy16_to_lds(a0 + c * 384, BB > NW && j % 2 ? om2 : om, dm + (to + (unsigned)(c * AST * 16 + b * 1024)));
             } else {
-                const int c = (j - MC) * (NW / TB) + wave / TB;
-                copy16_to_lds(a0 + (unsigned)min(gstage + c, G - 1) * 384u, ot,
-                              dst + (unsigned)(c * AST * 16 + BM * 64 + wave % TB * 1024));
+                const int c = (j - MC) * (NW / TB);
+                copy16_to_lds(a0 + c * 384, ot, dt + (to + (unsigned)(c * AST * 16)));
             }
         } else {
             const int j = k - LC;
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             const unsigned g = (unsigned)min(gstage + gs[j], G - 1), row = (unsigned)(scale ? 2 * N : 4 * M);
             const char *base = scale ? (const char *)sw : (const char *)starts;
             copy4_to_lds(ONE_GROUP ? base + (size_t)g * row : base, ONE_GROUP ? os[j] : os[j] + g * row,
-                         dst + (unsigned)(GST * 16 + (wave + NW * j) * 256));
+                         lds0 + (to + (unsigned)(GST * 16 + (wave + NW * j) * 256)));
         }
     };
     auto store_packed = [&](int half) {                  // convert and store what the loads brought
@@ -226,7 +225,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     // this lane's activation fragment of row block i of the group at `gp`, the start values of its four
     // results, and the scale of its column in block j
     const int fr = c16 * 4 + piece_of(q, c16), ft = c16 * 4 + ((q >> 1 ^ c16 >> 3) << 1) + (q & 1);
-    const i32x8 minus8 = i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0};
+    i32x8 minus8 = i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0};
+    if (!STARTS) asm("" : "+v"(minus8));       // (held, not made anew for every group)
     auto read_a = [&](const uint4 *gp, int i, i32x8 &fa) {
         const uint4 a0 = gp[i * 64 + fr];
         const uint2 a1 = reinterpret_cast<const uint2 *>(gp + BM * 4)[i * 64 + ft];
@@ -287,6 +287,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 for (int j = 0; j < CT; ++j) weights_e2m3(rw[0][0][j], flip, fb[j]);
             }
             gstage = g0 + CH;
+            if (!PACKED) a0 += gstage < G ? CH * 384 : 0;
 #pragma unroll
             for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1);
 #pragma unroll

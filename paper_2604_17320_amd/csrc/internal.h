@@ -61,7 +61,9 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa6, const float *sa, int M, con
 
 // The layer's row quantizers and GEMM on activations in the A6 format (gemm.hip): four rows at a time, quota_a6_row_bytes(K)
 // bytes for each (padded to whole fours), then, if quota_a6_starts(M), [groups][M] floats.
-inline size_t quota_a6_row_bytes(int K) { return ((((size_t)K + 127) / 128) | 1) * 96; }
+// (groups of a row in memory: stages of up to 8 groups may read past the last)
+__host__ __device__ inline int quota_a6_groups(int G) { return ((G + 7) & ~7) | 1; }
+inline size_t quota_a6_row_bytes(int K) { return (size_t)quota_a6_groups((K + 127) / 128) * 96; }
 // The sums cost the quantizers more than the GEMMs gain where those wait for memory anyway.  A 7B layer with and
 // without: all its products at 160 to 237 rows 147.0 and 146.1 us, first product at 640 rows 188.9 and 189.8,
 // 11264 and 5808 rows 1609 and 1656.

@@ -62,13 +62,13 @@ __host__ __device__ __forceinline__ RowOutFrag row_out(RowOutFrag o, size_t row,
 __host__ __device__ __forceinline__ RowOutA6 row_out(RowOutA6 o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
-    return RowOutA6{o.q + (row >> 2) * (G | 1) * 96 + (row & 3) * 16};
+    return RowOutA6{o.q + (row >> 2) * quota_a6_groups(G) * 96 + (row & 3) * 16};
 }
 __host__ __device__ __forceinline__ RowOutA6Starts row_out(RowOutA6Starts o, size_t row, int nchunk)
 {
     const int G = (nchunk + 15) >> 4;
-    return RowOutA6Starts{o.q + (row >> 2) * (G | 1) * 96 + (row & 3) * 16, o.rows,
-                          reinterpret_cast<float *>(o.q + (((size_t)o.rows + 3) >> 2) * (G | 1) * 96) + row};
+    return RowOutA6Starts{o.q + (row >> 2) * quota_a6_groups(G) * 96 + (row & 3) * 16, o.rows,
+                          reinterpret_cast<float *>(o.q + (((size_t)o.rows + 3) >> 2) * quota_a6_groups(G) * 96) + row};
 }
 // Stores chunk c (8 channels) of a row in the A6 format; four neighbouring lanes hold the chunks of 32 channels.  A pair's d0 is
 // its first lane's; its second takes what the first one adds to d1 and d2.

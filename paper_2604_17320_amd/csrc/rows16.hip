@@ -210,7 +210,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     constexpr int FMT = E2M3 ? 2 : 0;               // of the matrix instruction's operands
     const int arow_at = min(c16, M - 1);
     const uint8_t *arow = MODE == ROWS_PACKED ? in.qa + (size_t)arow_at * (K >> 1)
-                          : E2M3 ? in.qa + (size_t)(arow_at >> 2) * (G | 1) * 384 + (arow_at & 3) * 64 : nullptr;
+                          : E2M3 ? in.qa + (size_t)(arow_at >> 2) * quota_a6_groups(G) * 384 + (arow_at & 3) * 64 : nullptr;
     uint32_t flip[3];
     if (E2M3) e2m3_flips(flip);
     uint4 ra[U][MODE == ROWS_A6 ? 2 : RB], rb[U][NB];
