@@ -47,8 +47,8 @@ namespace {
 // registers, the rest into the other LDS buffer -- and a stage ends with one wait for all of it and one
 // barrier; nothing in between waits for memory.
 //   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
-//   do not queue for the address unit all at once (64 x 256 tile, 640 x 12288 x 4096: 40.4 -> 37.2 us; the
-//   32-row tiles have no time to spare and lose by it).
+//   do not queue for the address unit all at once, nor wait at the end for what was asked for late (64 x 128 tile, 237 x 12288 x
+//   4096: 23.5 us over a quarter of the stage, 20.4 over half, 21.9 over three).
 // A group in LDS: the rows' 64-byte parts, then their 32-byte parts.  Lane (row c, channels 32 q ..) reads 16 bytes of the first
 // and 8 of the second; 16-byte piece q of row r's first part sits at q ^ {0, 2, 3, 1}[r / 4 % 4], and the halves of the second
 // are swapped in rows 8 to 15 of 16, so that the lanes of a read do not share banks.
@@ -517,14 +517,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 // 64 x 128 as four waves of 64 x 32, three workgroups per CU; a weight belongs to one wave.  Stages of four groups are long enough for
 // a round trip to memory (400 x 22016 x 4096 49 us, 45 so); the packed entry point's rows, which pass registers, leave no
 // room for more than two.
-#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<8, 2, 4, 2, 6, P, A, QK, P == PACKED_INT4 ? 2 : 3>   // 128 x 128
-#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 2, 4, P == PACKED_INT4 ? 2 : 4, 6, P, A, QK, 3>   // 64 x 128
-#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 6, P, A, QK, 2>  // 32 x 128
+#define F8_TILE_0(P, A, QK) w4a4_f8_kernel<8, 2, 4, 2, 3, P, A, QK, P == PACKED_INT4 ? 2 : 3>   // 128 x 128
+#define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 2, 4, P == PACKED_INT4 ? 2 : 4, 4, P, A, QK, 3>   // 64 x 128
+#define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 4, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
 #define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
 // 32 x 64 once more in longer stages, for launches that leave a CU with three workgroups at most (101 x 4096 x 11008 22.4 -> 19.5
 // us, 237 x 4096 x 11008 25.4 -> 24.4).  Activations of a layer only, not pinned.
-#define F8_TILE_5(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 6, P, A, QK, 2>  // 32 x 64
+#define F8_TILE_5(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 4, P, A, QK, 2>  // 32 x 64
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 constexpr int TILES = 6, PINNED_TILES = 5;
@@ -575,23 +575,23 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
 
 int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
 
-// Tile choice by a cost model fitted to measured kernel times on this GPU (us; 75 shapes of 40 to 11264 rows, 3584 to
-// 37888 columns and 3584 to 18944 channels, all tiles: the choice costs 0.4 % over the best of each on average, 7 % at
+// Tile choice by a cost model fitted to measured kernel times on this GPU (us; 112 shapes of 40 to 11776 rows, 512 to
+// 37888 columns and 512 to 18944 channels, all tiles: the choice costs 0.6 % over the best of each on average, 7 % at
 // most).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
-// slope * x beyond; c0 is the launch, prologue and epilogue.
+// slope * x, and more for every round of `occ` workgroups, beyond; c0 is the launch, prologue and epilogue.
 // Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
 // tiles spread small problems over more waves.  Columns of a tile lie in [min_bn, max_bn] (the QKV
 // epilogue needs whole heads that stay inside q, k or v), its number below `tiles`.
 int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
 {
-    struct Cost { int ch; float c0; int n; float u[6], slope; };
+    struct Cost { int ch; float c0; int n; float u[6], slope, round; int occ; };
     static const Cost cost[TILES] = {
-        {2, 6.09f, 6, {0.557f, 0.722f, 1.080f, 1.793f, 1.855f, 2.212f}, 0.421f},
-        {4, 5.13f, 6, {0.308f, 0.470f, 0.662f, 1.032f, 1.255f, 1.461f}, 0.250f},
-        {4, 4.64f, 4, {0.258f, 0.351f, 0.518f, 0.829f}, 0.186f},
-        {4, 4.39f, 4, {0.193f, 0.230f, 0.352f, 0.455f}, 0.110f},
-        {1, 6.94f, 4, {0.957f, 1.270f, 2.406f, 2.549f}, 0.794f},
-        {8, 5.21f, 3, {0.143f, 0.208f, 0.323f}, 0.119f},
+        {2, 5.09f, 6, {0.559f, 0.764f, 1.159f, 1.816f, 1.906f, 2.348f}, 0.311f, 0.255f, 3},
+        {4, 4.37f, 6, {0.305f, 0.447f, 0.730f, 1.060f, 1.266f, 1.588f}, 0.192f, 0.174f, 3},
+        {4, 3.62f, 4, {0.252f, 0.343f, 0.550f, 0.819f}, 0.132f, 0.150f, 3},
+        {4, 3.89f, 4, {0.174f, 0.217f, 0.349f, 0.468f}, 0.100f, 0.040f, 4},
+        {1, 6.52f, 4, {0.981f, 1.241f, 2.407f, 2.705f}, 0.440f, 0.592f, 2},
+        {8, 3.45f, 3, {0.148f, 0.220f, 0.360f}, 0.125f, 0.039f, 3},
     };
     auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < PINNED_TILES || !quota_a6_starts(M)); };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
@@ -602,8 +602,9 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
         if (!fits(v)) continue;
         const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn);
         const float x = (float)wgs / 256.0f;
-        const int groups = (G + cost[v].ch - 1) / cost[v].ch * cost[v].ch;
-        const float t = cost[v].c0 + groups * (x <= (float)cost[v].n ? cost[v].u[(wgs + 255) / 256 - 1] : cost[v].slope * x);
+        const int groups = (G + cost[v].ch - 1) / cost[v].ch * cost[v].ch, n = 256 * cost[v].occ;
+        const float t = cost[v].c0 + groups * (x <= (float)cost[v].n ? cost[v].u[(wgs + 255) / 256 - 1]
+                                                                     : cost[v].slope * x + cost[v].round * (float)((wgs + n - 1) / n));
         if (best < 0 || t < best_t) { best = v; best_t = t; }
     }
     return best;
