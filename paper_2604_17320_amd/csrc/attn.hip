@@ -25,6 +25,7 @@
 #include "internal.h"
 #include "gemm_common.h"
 #include "ldscopy.h"
+#include "prefetch.h"
 
 namespace {
 
@@ -72,14 +73,18 @@ __device__ __forceinline__ float halves_max(float v)
 template <int DH>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
-    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2)
+    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int wgs, Prefetch pre)
 {
+    if ((int)blockIdx.x >= wgs) {
+        prefetch<256>(pre, blockIdx.x - wgs, gridDim.x - wgs);
+        return;
+    }
     constexpr int T = DH / 16;       // k-steps (16 channels each) of the QK product
     constexpr int DB = DH / 32;      // 32-channel blocks of the output
     constexpr int TB = KT * DH * 2;  // bytes of a tile
     __shared__ __align__(16) char sm[2][2][TB];         // [buffer][K, V]
     // XCD-aware order: a head's workgroups, longest first, run on one XCD, whose L2 holds its K and V
-    const int nq = (N + 127) / 128, work = xcd_remap(blockIdx.x, gridDim.x), bh = work / nq;
+    const int nq = (N + 127) / 128, work = xcd_remap(blockIdx.x, wgs), bh = work / nq;
     const int b = bh / H, h = bh % H, q0 = (nq - 1 - work % nq) * 128;
     const int d = H * DH;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hl = lane >> 5;
@@ -216,13 +221,17 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
 template <int DH>
 __global__ __launch_bounds__(256, 3) void colmass_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
-    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2)
+    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, int wgs, Prefetch pre)
 {
+    if ((int)blockIdx.x >= wgs) {
+        prefetch<256>(pre, blockIdx.x - wgs, gridDim.x - wgs);
+        return;
+    }
     constexpr int T = DH / 16, TB = KT * DH * 2;
     __shared__ __align__(16) char sm_q[2][TB];
     __shared__ __align__(16) float sm_lse[2][KT];
     // XCD-aware order, as in pass 1; the first keys have the most queries
-    const int nk = (Nv + 127) / 128, work = xcd_remap(blockIdx.x, gridDim.x), bh = work / nk, kb = work % nk;
+    const int nk = (Nv + 127) / 128, work = xcd_remap(blockIdx.x, wgs), bh = work / nk, kb = work % nk;
     const int d = H * DH;
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hl = lane >> 5;
@@ -355,7 +364,7 @@ extern "C" size_t quota_attention_workspace_bytes(int B, int N, int H, int dh)
 
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st)
+                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st, PrefetchList *weights)
 {
     if (!q_f16 || !khat_f16 || !vhat_f16 || !o_f16 || !ws) return QUOTA_ERR_NULL;
     if (B <= 0 || N < 0 || H <= 0 || Hkv <= 0 || vis_begin < 0 || Nv < 0 || vis_begin + Nv > N)
@@ -367,23 +376,28 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     const AttnWs w(ws, (size_t)B * H * N);
     float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
     const bool cues = Nv > 0 && (cm_inter || cm_intra);
-    dim3 g1((unsigned)((N + 127) / 128) * H * B), blk(256);
+    const unsigned n1 = (unsigned)((N + 127) / 128) * H * B;
+    // (time by the tiles of the longest workgroup; more than 2 MB a microsecond hold its own tiles up)
+    const auto s1 = weights ? weights->take(n1, 3.0f + 1.5f * (float)((N + 63) / 64), 2.0f) : PrefetchList::Share{};
+    dim3 g1(n1 + s1.wgs), blk(256);
     const f16 *q = (const f16 *)q_f16, *k = (const f16 *)khat_f16, *v = (const f16 *)vhat_f16;
     const double dM = (double)B * N, dd = (double)H * dh;
     {
         ProfScope prof(QUOTA_K_ATTENTION_FWD, 4.0 * B * dd * ((double)N * (N + 1) / 2),
                        4.0 * dM * dd + 4.0 * dM * Hkv * dh, st);
         auto kernel = dh == 128 ? attn_fwd_kernel<128> : attn_fwd_kernel<64>;
-        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2);
+        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, (int)n1, s1.what);
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if (cues) {
-        dim3 g2((unsigned)((Nv + 127) / 128) * H * B);
+        const unsigned n2 = (unsigned)((Nv + 127) / 128) * H * B;
+        const auto s2 = weights ? weights->take(n2, 3.0f + 1.1f * (float)((N + 63) / 64), 3.5f) : PrefetchList::Share{};
+        dim3 g2(n2 + s2.wgs);
         // (query, visual key) pairs under the causal mask
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
         auto kernel = dh == 128 ? colmass_kernel<128> : colmass_kernel<64>;
-        kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2);
+        kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, (int)n2, s2.what);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         colmass_reduce_kernel<<<dim3((unsigned)((Nv + 63) / 64) * B), blk, 0, st>>>(w.partial, H, Nv, cm_inter, cm_intra);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -397,7 +411,7 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
                                            float *cm_intra, void *ws, void *stream)
 {
     return quota_internal_attention(q_f16, khat_f16, vhat_f16, B, N, H, Hkv, dh, vis_begin, Nv, o_f16, cm_inter, cm_intra,
-                                    ws, (hipStream_t)stream);
+                                    ws, (hipStream_t)stream, nullptr);
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------

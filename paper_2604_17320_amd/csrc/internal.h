@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include "../../include/quota.h"
+#include "prefetch.h"
 
 // score kernel with a separate sequence stride for the sumsq/ressq arrays, so
 // the layer can pass the per-row side outputs of the quantizer directly
@@ -14,12 +15,12 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
                               const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
-                              hipStream_t st);
+                              hipStream_t st, PrefetchList *weights);
 
 // attention and, if cm_inter or cm_intra is given, the cue pass with its head means [B][Nv]
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st);
+                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st, PrefetchList *weights);
 
 struct quota_compact_args {
     int B, N, vis_begin, Nv, k_keep, n_keep, d, dkv;      // dkv: width of a K or V row (Hkv * dh)

@@ -10,6 +10,7 @@
 // wave ranks those (104 / 576 / 2880 tokens 8.6 / 9.7 / 19.1 -> 7.0 / 9.0 / 18.8 us).
 #include "common.h"
 #include "internal.h"
+#include "prefetch.h"
 
 namespace {
 
@@ -314,8 +315,12 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_topk_kernel(MetricSrc src
                                                          quota_score_params p,
                                                          float *__restrict__ score,
                                                          float *__restrict__ normed, int K,
-                                                         int32_t *__restrict__ keep_idx, int cap)
+                                                         int32_t *__restrict__ keep_idx, int cap, Prefetch pre)
 {
+    if ((int)blockIdx.x >= B) {
+        prefetch<SCORE_THREADS>(pre, blockIdx.x - B, gridDim.x - B);
+        return;
+    }
     // LDS sized by the launch for this Nv: counters, ranges and bounds, 4 * cap keys
     extern __shared__ __align__(16) uint32_t score_lds[];
     int *hist = reinterpret_cast<int *>(score_lds);
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void topk_kernel(const float *__rest
 // Launches the score (+ top-k) kernel with the LDS its Nv needs: up to 153 KB at 8192 tokens, which
 // is above the default limit of a launch and has to be granted once per device.
 int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const quota_score_params &p,
-                      float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st)
+                      float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st, PrefetchList *weights = nullptr)
 {
     const int cap = (Nv + 63) & ~63;
     const size_t lds = ((size_t)4 * cap + SELECT_HIST + SELECT_RANGE + 8) * sizeof(uint32_t);
@@ -383,7 +388,8 @@ int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const
     }
     auto kernel = Nv <= SCORE_THREADS ? score_topk_kernel<1>
                   : Nv <= 3 * SCORE_THREADS ? score_topk_kernel<3> : score_topk_kernel<MAXV / SCORE_THREADS>;
-    kernel<<<dim3(B), dim3(SCORE_THREADS), lds, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, cap);
+    const auto share = weights ? weights->take(B, 7.0f, 4.0f) : PrefetchList::Share{};
+    kernel<<<dim3(B + share.wgs), dim3(SCORE_THREADS), lds, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, cap, share.what);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -416,7 +422,7 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
                               const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
-                              hipStream_t st)
+                              hipStream_t st, PrefetchList *weights)
 {
     if (!sumsq || !ressq || !p || !score || !keep_idx || !cm_inter || !cm_intra) return QUOTA_ERR_NULL;
     if (B <= 0 || Nv < 0 || K < 0 || p->pct_lo < 0 || p->pct_hi > 100 || p->pct_lo > p->pct_hi)
@@ -426,7 +432,7 @@ int quota_internal_score_topk(const float *sumsq, const float *ressq, long strid
     ProfScope prof(QUOTA_K_SCORE_TOKENS, 0,
                    20.0 * B * Nv + 4.0 * B * (K < Nv ? K : Nv), st);
     MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
-    return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st);
+    return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st, weights);
 }
 
 extern "C" void quota_score_params_default(quota_score_params *p)
