@@ -52,14 +52,20 @@ __device__ __forceinline__ Codes8 codes_of_e4m3(const uint2 &e)              // 
     const uint32_t low = 0x0F0F0F0Fu;
     return {(e.x & low) | (e.y << 4 & ~low), (e.x >> 4 & 0x08080808u) | (e.y & 0x80808080u)};
 }
-// What the first (second) eight codes of sixteen give to d0, d1, d2: own = to d0 (d1), d2, and of the first, to d1.
-__device__ __forceinline__ void codes_e2m3(const Codes8 &c, bool second, uint32_t &own, uint32_t &d2, uint32_t &d1)
+// What the first (second) eight codes of sixteen give to d0, d1, d2: own = to d0 (d1), d2, and of the first, to d1.  The masks of
+// a lane that always has the one or the other can be made once.
+struct E6Masks { uint32_t own[4], d2[5]; };
+__device__ __forceinline__ E6Masks e2m3_masks(bool second)
+{
+    return {{second ? E6_STAY[1] : E6_STAY[0], second ? E6_MOVE[1] & ~3u : E6_MOVE[0], second ? 0x00200200u : 0x20020020u,
+             second ? 0x08008000u : 0x00800800u},
+            {second ? 0u : E6_STAY[2], second ? E6_MOVE[2] : 0u, second ? 0u : 0x02002000u, second ? 0x80080080u : 0u, second ? 2u : 0u}};
+}
+__device__ __forceinline__ void codes_e2m3(const Codes8 &c, const E6Masks &k, uint32_t &own, uint32_t &d2, uint32_t &d1)
 {
     const uint32_t m = c.mag, m2 = m << 2, s2 = c.sign << 2, s4 = c.sign << 4;
-    own = (m & (second ? E6_STAY[1] : E6_STAY[0])) | (m2 & (second ? E6_MOVE[1] & ~3u : E6_MOVE[0])) |
-          (s2 & (second ? 0x00200200u : 0x20020020u)) | (s4 & (second ? 0x08008000u : 0x00800800u));
-    d2 = (m & (second ? 0u : E6_STAY[2])) | (m2 & (second ? E6_MOVE[2] : 0u)) | (s2 & (second ? 0u : 0x02002000u)) |
-         (s4 & (second ? 0x80080080u : 0u)) | (c.sign >> 30 & (second ? 2u : 0u));
+    own = (m & k.own[0]) | (m2 & k.own[1]) | (s2 & k.own[2]) | (s4 & k.own[3]);
+    d2 = (m & k.d2[0]) | (m2 & k.d2[1]) | (s2 & k.d2[2]) | (s4 & k.d2[3]) | (c.sign >> 30 & k.d2[4]);
     d1 = (m >> 30) | (c.sign >> 28 & 8u);
 }
 // 32 packed int4 codes (one 16-byte piece): six dwords
@@ -68,8 +74,8 @@ __device__ __forceinline__ void codes_e2m3(const i32x4 &v, uint32_t (&d)[6])
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         uint32_t o0, o1, a2, b2, a1, b1;
-        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i]), false, o0, a2, a1);
-        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i + 1]), true, o1, b2, b1);
+        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i]), e2m3_masks(false), o0, a2, a1);
+        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i + 1]), e2m3_masks(true), o1, b2, b1);
         d[3 * i] = o0;
         d[3 * i + 1] = o1 | a1;
         d[3 * i + 2] = a2 | b2;

@@ -205,7 +205,7 @@ __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
 #define ROW_PROLOGUE()                                                                         \
     __shared__ double sm[8];                                                                   \
     const int lane = threadIdx.x % GROUP;                                                      \
-    const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (ROW_THREADS / GROUP) + threadIdx.x / GROUP; \
+    const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (ROW_THREADS / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
     (void)sm
 

@@ -70,20 +70,36 @@ __host__ __device__ __forceinline__ RowOutA6Starts row_out(RowOutA6Starts o, siz
     return RowOutA6Starts{o.q + (row >> 2) * quota_a6_groups(G) * 96 + (row & 3) * 16, o.rows,
                           reinterpret_cast<float *>(o.q + (((size_t)o.rows + 3) >> 2) * quota_a6_groups(G) * 96) + row};
 }
-// Stores chunk c (8 channels) of a row in the A6 format; four neighbouring lanes hold the chunks of 32 channels.  A pair's d0 is
-// its first lane's; its second takes what the first one adds to d1 and d2.
+// Stores chunks (8 channels) of a row in the A6 format, chunk c by a thread whose chunks are all idx modulo 64; four
+// neighbouring lanes hold the chunks of 32 channels.  A pair's d0 is its first lane's; its second takes what the first one adds to d1
+// and d2.  Masks and the place inside a group are the thread's own, made once.
 typedef uint32_t u32x2_at4 __attribute__((ext_vector_type(2), aligned(4), may_alias));
-__device__ __forceinline__ void store_e2m3(uint32_t *row_q, int row, int c, const float unit[8])
-{
-    uint32_t own, d2, d1;
-    codes_e2m3(codes_of_e4m3(units_to_e4m3(unit)), c & 1, own, d2, d1);
-    d1 = own | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d1, 0xA0, 0xf, 0xf, false);       // quad lanes 0 0 2 2
-    const uint32_t d2s = d2 | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d2, 0xA0, 0xf, 0xf, false);
-    uint32_t *main = row_q + (c >> 4) * 96 + (c >> 2 & 3) * 4;
-    uint32_t *tail = row_q + (c >> 4) * 96 + 64 - 8 * (row & 3) + (c >> 2 & 3) * 2;
-    if (c & 1) *reinterpret_cast<u32x2_at4 *>(c & 2 ? tail : main + 1) = u32x2_at4{d1, d2s};
-    else main[c & 2 ? 3 : 0] = own;
-}
+struct E6Store {
+    E6Masks k;
+    unsigned at;                         // bytes from the row's first dword to this thread's place in a group
+    __device__ __forceinline__ E6Store(int idx, int row) : k(e2m3_masks(idx & 1))
+    {
+        const unsigned quarter = idx >> 2 & 3, main = quarter * 16, tail = 256 - 32 * (row & 3) + quarter * 8;
+        at = idx & 1 ? (idx & 2 ? tail : main + 4) : main + (idx & 2 ? 12 : 0);
+#pragma unroll
+        for (uint32_t &m : k.own) asm("" : "+v"(m));         // (else they are selected anew for every chunk)
+#pragma unroll
+        for (uint32_t &m : k.d2) asm("" : "+v"(m));
+    }
+    __device__ __forceinline__ void operator()(uint32_t *row_q, int c, bool live, const float unit[8]) const
+    {
+        uint32_t own, d2, d1;
+        uint2 e = units_to_e4m3(unit);
+        e = live ? e : make_uint2(0, 0);                     // (chunks that fill a group up)
+        codes_e2m3(codes_of_e4m3(e), k, own, d2, d1);
+        d1 = own | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d1, 0xA0, 0xf, 0xf, false);       // quad lanes 0 0 2 2
+        d2 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d2, 0xA0, 0xf, 0xf, false);
+        // (one lane of four storing all 16 bytes of the first part, another the second, takes longer: 5808 x 11008 42.7 us, 40.1 so)
+        char *to = (char *)row_q + (at + (unsigned)(c >> 4) * 384u);
+        if (c & 1) *reinterpret_cast<u32x2_at4 *>(to) = u32x2_at4{d1, d2};
+        else *reinterpret_cast<uint32_t *>(to) = own;
+    }
+};
 
 // final phase shared by the row kernels: quantize the cached row `v` with absmax `a`, store the
 // codes, return this thread's share of the residual sum of squares.
@@ -94,7 +110,9 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
     float s = 1.0f, inv = 0.0f;
     if (a != 0.0f) { s = a / 7.0f; inv = 7.0f / a; }
     s_out = s;
+    static_assert(!(OUT::A6 && WANT_RES), "(chunks past the row repeat one)");
     double rs = 0.0;
+    const E6Store store(idx, row);
     const int nout = OUT::A6 ? (nchunk + 15) & ~15 : nchunk;
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
@@ -105,7 +123,7 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
             float unit[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float f = live ? (float)v[r].h[e] : 0.0f;
+                float f = (float)v[r].h[e];
                 const uint32_t cb = code_bits(f * inv);
                 if (OUT::A6) {
                     unit[e] = code_unit(cb);
@@ -119,10 +137,10 @@ __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchun
                 }
             }
             if constexpr (OUT::A6) {
-                store_e2m3(out.q, row, c, unit);
+                store(out.q, c, live, unit);
                 if constexpr (OUT::STARTS) {         // the 16 lanes of a group add up in its last one
                     float u = ((unit[0] + unit[1]) + (unit[2] + unit[3])) + ((unit[4] + unit[5]) + (unit[6] + unit[7]));
-                    u = row16_sum(u);
+                    u = row16_sum(live ? u : 0.0f);
                     if ((c & 15) == 15) out.starts[(size_t)(c >> 4) * out.rows] = u * (-8.0f * 512.0f / 64.0f);     // -8 / 8 times the sum of codes / 8
                 }
             } else {
