@@ -4,7 +4,7 @@
 // All are row kernels: in launches of 2048 rows and more of up to 6144 columns one wave per row
 // (four rows per workgroup), else one workgroup per row; the row is cached in registers as
 // 16-byte chunks, absmax / sums of squares are wave or block reductions, 8 codes are stored per
-// chunk: a packed dword, or 8 e4m3 bytes for the GEMM.  HBM-bound by design.
+// chunk: a packed dword, or 6 bytes of e2m3 numbers for the GEMM.  HBM-bound by design.
 #include <type_traits>
 
 #include "common.h"

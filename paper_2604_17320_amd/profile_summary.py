@@ -75,8 +75,9 @@ CLASSES = [
     ("copy_f32_kernel", "copy_f32"),
 ]
 
-# operations of one matrix instruction of a class and the dense peak of its type: v_mfma_f32_16x16x128_f8f6f4 on e4m3
-# operands, v_mfma_f32_32x32x16_f16
+# operations of one matrix instruction of a class and the dense peak of its type: v_mfma_f32_16x16x128_f8f6f4 on e2m3
+# operands (at most 32 rows: e4m3), v_mfma_f32_32x32x16_f16
+FP6 = (2 * 16 * 16 * 128, 10000.0)
 FP8 = (2 * 16 * 16 * 128, 5000.0)
 FP16 = (2 * 32 * 32 * 16, 2500.0)
 
@@ -85,7 +86,7 @@ def matrix_type(cls):
     if cls is None:
         return None
     if cls.startswith("w4a4_gemm"):
-        return FP8
+        return FP8 if cls == "w4a4_gemm_rows16" else FP6
     return FP16 if cls in ("fp_gemm", "attention_fwd", "attention_colmass") else None
 
 
@@ -246,7 +247,7 @@ def mfma(csv_path, bench_path=None):
         print(f"{cls:24s} {n:8d} {us:7.1f} {m:10.0f} {tops:12.1f} {tops / peak:12.3f} {(v - m) / m:9.1f} "
               f"{mean(c['SQ_VALU_MFMA_BUSY_CYCLES']) / (4.0 * busy_cu):9.3f} {mean(c['SQ_ACTIVE_INST_VALU']) / wave_cyc:11.3f} "
               f"{mean(c['SQ_WAIT_INST_ANY']) / wave_cyc:8.3f}")
-    print("\nMFMA inst: issued by all waves; issued TOP/s = MFMA inst * operations of one / duration, against 5.0 (fp8: the W4A4\n"
+    print("\nMFMA inst: issued by all waves; issued TOP/s = MFMA inst * operations of one / duration, against 10.0 (fp6: the W4A4\n"
           "GEMMs, v_mfma_f32_16x16x128_f8f6f4) or 2.5 (fp16, v_mfma_f32_32x32x16_f16) POP/s.  Included are the rows and columns\n"
           "that a tile pads and, in the W4A4 GEMMs below 512 rows, the constant products that take the code offset out again (one to every\n"
           "1, 2 or 4 others, by tile); VALU/MFMA: other vector instructions per MFMA (SQ_INSTS_VALU counts the MFMAs too);\n"
@@ -254,7 +255,7 @@ def mfma(csv_path, bench_path=None):
           "over SQ_WAVE_CYCLES (share of wave lifetime).")
     if bench:
         g = bench.get("gemm_all", {})
-        print(f"\nplain run of bench.py: GEMMs {g.get('TOPs')} TOP/s algorithmic = {g.get('frac_fp8_peak')} of the fp8 peak, "
+        print(f"\nplain run of bench.py: GEMMs {g.get('TOPs')} TOP/s algorithmic = {g.get('frac_fp6_peak')} of the fp6 peak, "
               f"{g.get('step_ms')} ms of a {bench['ms_per_step']} ms step")
 
 

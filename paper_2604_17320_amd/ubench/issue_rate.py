@@ -2,9 +2,9 @@
 """Issue-rate probe for gfx950: what the matrix instruction of the W4A4 GEMM (v_mfma_f32_16x16x128_f8f6f4) and the
 vector instructions that it needs beside it cost a SIMD, alone and interleaved, at one and two waves per SIMD.
 
-A 128-channel group of a wave's RT x CT blocks of 16 x 16 outputs takes RT CT products, RT products against the
-constant that removes the codes' offset, 4 RT CT fp32 multiply-adds for the group's scale and 12 CT integer
-instructions that unpack its weights.  This probe places exactly those mixes by hand (one asm block, fixed registers,
+A 128-channel group of a wave's RT x CT blocks of 16 x 16 outputs takes RT CT products of e2m3 numbers, 4 RT CT fp32
+multiply-adds for the group's scale, 16 CT integer instructions that unpack its weights and, without start values, RT
+products against the constant that removes the codes' offset.  This probe places exactly those mixes by hand (one asm block, fixed registers,
 register-to-register only, no memory access in the timed loop, results meaningless) so that the compiler's scheduling is out
 of the picture, and prints ns per group and the share of the matrix rate that the products alone reach.
 
@@ -15,7 +15,7 @@ import subprocess
 import sys
 import tempfile
 
-SHAPES = [("128 x 256 tile, wave 8 x 4 blocks", 8, 4), ("64 x 256 and 64 x 128, wave 4 x 4", 4, 4),
+SHAPES = [("128 x 256 tile, wave 8 x 4 blocks", 8, 4), ("128 x 128, wave 8 x 2", 8, 2), ("64 x 128, wave 4 x 2", 4, 2),
           ("32 x 128, wave 2 x 2", 2, 2), ("32 x 64, wave 2 x 1", 2, 1)]
 
 TEMPLATE = r'''
@@ -64,7 +64,7 @@ MFMA, FMA, UNPACK = "mfma", "fma", "unpack"
 def mix(rt, ct, offset, scale, unpack):
     """The instructions of a group, vector work spread evenly behind the matrix instructions."""
     mats = rt * ct + (rt if offset else 0)
-    vec = [FMA] * (4 * rt * ct if scale else 0) + [UNPACK] * (12 * ct if unpack else 0)
+    vec = [FMA] * (4 * rt * ct if scale else 0) + [UNPACK] * (16 * ct if unpack else 0)
     order, done = [], 0
     for m in range(mats):
         order.append(MFMA)
@@ -79,15 +79,16 @@ def block(order):
     for what in order:
         if what == MFMA:                                   # eight results take turns; the chain reads one four places back
             a = 64 + 4 * (m % 8)
-            lines.append(f"v_mfma_f32_16x16x128_f8f6f4 v[{a}:{a + 3}], v[160:167], v[168:175], v[96:99]")
+            lines.append(f"v_mfma_f32_16x16x128_f8f6f4 v[{a}:{a + 3}], v[160:165], v[168:173], v[96:99] cbsz:2 blgp:2")
             m += 1
         elif what == FMA:
             lines.append(f"v_fmac_f32_e32 v{100 + f % 48}, v{64 + (4 * (m + 3) + f) % 32}, v148")
             f += 1
         else:
-            reg = 150 + u % 8
-            lines.append((f"v_lshrrev_b32_e32 v{reg}, 4, v{reg}", f"v_and_b32_e32 v{reg}, 0x0f0f0f0f, v{reg}",
-                          f"v_xor_b32_e32 v{reg}, 0x08080808, v{reg}")[u % 3])
+            reg, other = 150 + u % 8, 150 + (u + 3) % 8
+            lines.append(f"v_lshlrev_b32_e32 v{reg}, 2, v{reg}" if u % 8 == 0 else
+                         f"v_alignbit_b32 v{reg}, v{reg}, v{other}, 30" if u % 8 == 1 else
+                         f"v_bitop3_b32 v{reg}, v{reg}, v{other}, v148 bitop3:{'0x6a' if u % 2 else '0x78'}")
             u += 1
     return "\\n\\t".join(lines)
 
@@ -96,8 +97,8 @@ def main():
     cases, runs, mode = [], [], 0
     clobber = ",".join(f'"v{i}"' for i in range(64, 176))
     for name, rt, ct in SHAPES:
-        steps = [("products", (False, False, False)), ("+ offset products", (True, False, False)),
-                 ("+ scale chain", (True, True, False)), ("+ unpack: the whole group", (True, True, True))]
+        steps = [("products", (False, False, False)), ("+ scale chain", (False, True, False)),
+                 ("+ unpack: with start values", (False, True, True)), ("+ offset products: without", (True, True, True))]
         runs.append(f'        {{ float t, t0 = 0; (void)t0; printf("  {name}\\n");')
         for i, (what, flags) in enumerate(steps):
             cases.append(f'        {"else " if mode else ""}if (MODE == {mode}) asm volatile("{block(mix(rt, ct, *flags))}" ::: {clobber});')
