@@ -8,8 +8,8 @@
 // long (no conversion in front of the fma).
 //
 // fp6 operands multiply in half the time of fp8 ones (16 cycles), and fragments are a quarter smaller.  Weights: the
-// bits of c + 8 in 0..15 ARE those of the e2m3 number (c + 8) / 8, so that 16 codes take 8 vector instructions
-// (gemm_common.h), two more than as e4m3 bytes.  Activations are signed e2m3 numbers a / 8, made by the row quantizers.
+// bits of c + 8 in 0..15 ARE those of the e2m3 number (c + 8) / 8, so that 16 codes take 7 vector instructions
+// (gemm_common.h), one more than as e4m3 bytes.  Activations are signed e2m3 numbers a / 8, made by the row quantizers.
 // The weights' offset of 8 comes back out through the
 // accumulator's start value, -8 / 64 * sum of the group's activation codes.  With few rows every wave makes it by
 // one more MFMA per 16 rows and group, against a constant -8 / 8, whose result already lies where the C operand wants

@@ -4,24 +4,25 @@
 
 // Sixteen codes as sixteen 6-bit e2m3 numbers in three dwords.  The multiples of 1/8 up to 15/8 are e2m3's linear range: the
 // number of n / 8 has the bits 00nnnn, the sign on top.  Which of the sixteen a code becomes is free as long as weights and
-// activations agree, and is chosen so that weights take few instructions: a nibble stays at its bit or moves up by two.  Of
-// w0 (codes 0 to 7) and w1 (8 to 15), d0 takes 0 1 3 4 6 and the low half of 7, d1 the rest of 7 and 9 10 12 13 15,
-// d2 2 5 8 11 14.
-constexpr uint32_t E6_STAY[3] = {0x0F00F00Fu, 0xF00F00F0u, 0x00F00F00u};     // of w0, w1, w0
-constexpr uint32_t E6_MOVE[3] = {0xC03C03C0u, 0x03C03C03u, 0x3C03C03Cu};     // of w0, w1 (and w0), w1, two bits up
+// activations agree, and is chosen so that weights take few instructions: of the first eight codes each nibble stays at its bit,
+// of the others each moves up by two, around the dword's end.  d0 takes the nibbles 0 3 6 of w0 and 1 4 and half of 7 of w1, d1
+// 1 4 and half of 7 of w0 and the rest of 7 and 2 5 of w1, d2 the rest of 7 and 2 5 of w0 and 0 3 6 of w1.
+constexpr uint32_t E6_STAY[3] = {0x0F00F00Fu, 0xF00F00F0u, 0x00F00F00u};     // of w0
+constexpr uint32_t E6_MOVE[3] = {0xC03C03C0u, 0x03C03C03u, 0x3C03C03Cu};     // of w1, two bits up
 constexpr uint32_t E6_FLIP[3] = {0x08208208u, 0x82082082u, 0x20820820u};     // the top bits of the codes: c -> c + 8
 
-// Weights, as c + 8.  Eight instructions for 16 codes.  `flip` holds E6_FLIP in vector registers: an instruction reads one
+// Weights, as c + 8.  Seven instructions for 16 codes (eight, with the first codes moved too: a layer of 11264 rows 1349 -> 1336 us, of
+// 640 160.9 -> 159.4).  `flip` holds E6_FLIP in vector registers: an instruction reads one
 // constant from the scalar ones.
 __device__ __forceinline__ void weights_e2m3(uint32_t w0, uint32_t w1, const uint32_t (&flip)[3], int &d0, int &d1, int &d2)
 {
-    const uint32_t up0 = w0 << 2, up1 = __builtin_amdgcn_alignbit(w1, w0, 30);
-    auto pick = [&](uint32_t stay, uint32_t move, int i) {                   // (stay & STAY ^ FLIP) ^ (move & MOVE)
-        return (int)__builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(stay, E6_STAY[i], flip[i], 0x6A), move, E6_MOVE[i], 0x78);
+    const uint32_t up = __builtin_amdgcn_alignbit(w1, w1, 30);
+    auto pick = [&](int i) {                                                 // (w0 & STAY ^ FLIP) ^ (up & MOVE)
+        return (int)__builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(w0, E6_STAY[i], flip[i], 0x6A), up, E6_MOVE[i], 0x78);
     };
-    d0 = pick(w0, up0, 0);
-    d1 = pick(w1, up1, 1);
-    d2 = pick(w0, up1, 2);
+    d0 = pick(0);
+    d1 = pick(1);
+    d2 = pick(2);
 }
 __device__ __forceinline__ void e2m3_flips(uint32_t (&flip)[3])
 {
@@ -52,33 +53,40 @@ __device__ __forceinline__ Codes8 codes_of_e4m3(const uint2 &e)              // 
     const uint32_t low = 0x0F0F0F0Fu;
     return {(e.x & low) | (e.y << 4 & ~low), (e.x >> 4 & 0x08080808u) | (e.y & 0x80808080u)};
 }
-// What the first (second) eight codes of sixteen give to d0, d1, d2: own = to d0 (d1), d2, and of the first, to d1.  The masks of
-// a lane that always has the one or the other can be made once.
-struct E6Masks { uint32_t own[4], d2[5]; };
+// What the first (second) eight codes of sixteen give to d0, d1 and d2.  Masks and shifts of a lane that always has the one or the
+// other can be made once.
+struct E6Masks { uint32_t mag[3], sign[3]; int mag_right, sign_right; };
 __device__ __forceinline__ E6Masks e2m3_masks(bool second)
 {
-    return {{second ? E6_STAY[1] : E6_STAY[0], second ? E6_MOVE[1] & ~3u : E6_MOVE[0], second ? 0x00200200u : 0x20020020u,
-             second ? 0x08008000u : 0x00800800u},
-            {second ? 0u : E6_STAY[2], second ? E6_MOVE[2] : 0u, second ? 0u : 0x02002000u, second ? 0x80080080u : 0u, second ? 2u : 0u}};
+    E6Masks k;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t stay = E6_STAY[i] & 0x88888888u, top = E6_FLIP[i] & ~stay;        // top bits of the nibbles that stay, that move
+        const int before = (i + 2) % 3;                  // (a sign lies two bits above its nibble: it may be the next dword's)
+        const uint32_t stay0 = E6_STAY[before] & 0x88888888u, top0 = E6_FLIP[before] & ~stay0;
+        k.mag[i] = second ? E6_MOVE[i] : E6_STAY[i];
+        k.sign[i] = second ? (top << 2 | top0 >> 30) : (stay << 2 | stay0 >> 30);
+    }
+    k.mag_right = second ? 30 : 0;
+    k.sign_right = second ? 28 : 30;
+    return k;
 }
-__device__ __forceinline__ void codes_e2m3(const Codes8 &c, const E6Masks &k, uint32_t &own, uint32_t &d2, uint32_t &d1)
+__device__ __forceinline__ void codes_e2m3(const Codes8 &c, const E6Masks &k, uint32_t (&d)[3])
 {
-    const uint32_t m = c.mag, m2 = m << 2, s2 = c.sign << 2, s4 = c.sign << 4;
-    own = (m & k.own[0]) | (m2 & k.own[1]) | (s2 & k.own[2]) | (s4 & k.own[3]);
-    d2 = (m & k.d2[0]) | (m2 & k.d2[1]) | (s2 & k.d2[2]) | (s4 & k.d2[3]) | (c.sign >> 30 & k.d2[4]);
-    d1 = (m >> 30) | (c.sign >> 28 & 8u);
+    const uint32_t m = __builtin_amdgcn_alignbit(c.mag, c.mag, k.mag_right), s = __builtin_amdgcn_alignbit(c.sign, c.sign, k.sign_right);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) d[i] = (m & k.mag[i]) | (s & k.sign[i]);
 }
 // 32 packed int4 codes (one 16-byte piece): six dwords
 __device__ __forceinline__ void codes_e2m3(const i32x4 &v, uint32_t (&d)[6])
 {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        uint32_t o0, o1, a2, b2, a1, b1;
-        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i]), e2m3_masks(false), o0, a2, a1);
-        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i + 1]), e2m3_masks(true), o1, b2, b1);
-        d[3 * i] = o0;
-        d[3 * i + 1] = o1 | a1;
-        d[3 * i + 2] = a2 | b2;
+        uint32_t first[3], second[3];
+        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i]), e2m3_masks(false), first);
+        codes_e2m3(codes_of_nibbles((uint32_t)v[2 * i + 1]), e2m3_masks(true), second);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) d[3 * i + j] = first[j] | second[j];
     }
 }
 

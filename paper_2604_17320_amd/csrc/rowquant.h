@@ -71,8 +71,8 @@ __host__ __device__ __forceinline__ RowOutA6Starts row_out(RowOutA6Starts o, siz
                           reinterpret_cast<float *>(o.q + (((size_t)o.rows + 3) >> 2) * quota_a6_groups(G) * 96) + row};
 }
 // Stores chunks (8 channels) of a row in the A6 format, chunk c by a thread whose chunks are all idx modulo 64; four
-// neighbouring lanes hold the chunks of 32 channels.  A pair's d0 is its first lane's; its second takes what the first one adds to d1
-// and d2.  Masks and the place inside a group are the thread's own, made once.
+// neighbouring lanes hold the chunks of 32 channels.  A pair's lanes put their shares of d0, d1 and d2 together; its first stores d0, its
+// second d1 and d2.  Masks and the place inside a group are the thread's own, made once.
 typedef uint32_t u32x2_at4 __attribute__((ext_vector_type(2), aligned(4), may_alias));
 struct E6Store {
     E6Masks k;
@@ -82,22 +82,20 @@ struct E6Store {
         const unsigned quarter = idx >> 2 & 3, main = quarter * 16, tail = 256 - 32 * (row & 3) + quarter * 8;
         at = idx & 1 ? (idx & 2 ? tail : main + 4) : main + (idx & 2 ? 12 : 0);
 #pragma unroll
-        for (uint32_t &m : k.own) asm("" : "+v"(m));         // (else they are selected anew for every chunk)
-#pragma unroll
-        for (uint32_t &m : k.d2) asm("" : "+v"(m));
+        for (int i = 0; i < 3; ++i) asm("" : "+v"(k.mag[i]), "+v"(k.sign[i]));       // (else they are selected anew for every chunk)
     }
     __device__ __forceinline__ void operator()(uint32_t *row_q, int c, bool live, const float unit[8]) const
     {
-        uint32_t own, d2, d1;
         uint2 e = units_to_e4m3(unit);
         e = live ? e : make_uint2(0, 0);                     // (chunks that fill a group up)
-        codes_e2m3(codes_of_e4m3(e), k, own, d2, d1);
-        d1 = own | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d1, 0xA0, 0xf, 0xf, false);       // quad lanes 0 0 2 2
-        d2 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d2, 0xA0, 0xf, 0xf, false);
+        uint32_t d[3];
+        codes_e2m3(codes_of_e4m3(e), k, d);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) d[i] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d[i], 0xB1, 0xf, 0xf, false);    // quad lanes 1 0 3 2
         // (one lane of four storing all 16 bytes of the first part, another the second, takes longer: 5808 x 11008 42.7 us, 40.1 so)
         char *to = (char *)row_q + (at + (unsigned)(c >> 4) * 384u);
-        if (c & 1) *reinterpret_cast<u32x2_at4 *>(to) = u32x2_at4{d1, d2};
-        else *reinterpret_cast<uint32_t *>(to) = own;
+        if (c & 1) *reinterpret_cast<u32x2_at4 *>(to) = u32x2_at4{d[1], d[2]};
+        else *reinterpret_cast<uint32_t *>(to) = d[0];
     }
 };
 

@@ -3,7 +3,7 @@
 vector instructions that it needs beside it cost a SIMD, alone and interleaved, at one and two waves per SIMD.
 
 A 128-channel group of a wave's RT x CT blocks of 16 x 16 outputs takes RT CT products of e2m3 numbers, 4 RT CT fp32
-multiply-adds for the group's scale, 16 CT integer instructions that unpack its weights and, without start values, RT
+multiply-adds for the group's scale, 14 CT integer instructions that unpack its weights and, without start values, RT
 products against the constant that removes the codes' offset.  This probe places exactly those mixes by hand (one asm block, fixed registers,
 register-to-register only, no memory access in the timed loop, results meaningless) so that the compiler's scheduling is out
 of the picture, and prints ns per group and the share of the matrix rate that the products alone reach.
@@ -64,7 +64,7 @@ MFMA, FMA, UNPACK = "mfma", "fma", "unpack"
 def mix(rt, ct, offset, scale, unpack):
     """The instructions of a group, vector work spread evenly behind the matrix instructions."""
     mats = rt * ct + (rt if offset else 0)
-    vec = [FMA] * (4 * rt * ct if scale else 0) + [UNPACK] * (16 * ct if unpack else 0)
+    vec = [FMA] * (4 * rt * ct if scale else 0) + [UNPACK] * (14 * ct if unpack else 0)
     order, done = [], 0
     for m in range(mats):
         order.append(MFMA)
@@ -86,8 +86,7 @@ def block(order):
             f += 1
         else:
             reg, other = 150 + u % 8, 150 + (u + 3) % 8
-            lines.append(f"v_lshlrev_b32_e32 v{reg}, 2, v{reg}" if u % 8 == 0 else
-                         f"v_alignbit_b32 v{reg}, v{reg}, v{other}, 30" if u % 8 == 1 else
+            lines.append(f"v_alignbit_b32 v{reg}, v{reg}, v{other}, 30" if u % 7 == 0 else
                          f"v_bitop3_b32 v{reg}, v{reg}, v{other}, v148 bitop3:{'0x6a' if u % 2 else '0x78'}")
             u += 1
     return "\\n\\t".join(lines)
