@@ -154,7 +154,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         os[k] = 4u * (unsigned)(scale ? first + min((nc0 >> 1) + pair, (NC >> 1) - 1) : min(m0 + d % BM, M - 1));
     }
 
-    constexpr int WS = CH > 1 ? 2 : 1;                   // register sets of packed weights = stages per loop body
+    // Register sets of packed weights = stages per loop body.  With 8 x 4 blocks there is room for one: a group's weights are
+    // asked for when those of the same place in the last stage have been unpacked, the second group's last of all.
+    constexpr int WS = CH > 1 && T < 32 ? 2 : 1;
+    constexpr bool LATE = CH > 1 && WS == 1;
     uint4 rw[WS][CH][CT];
     i32x4 ra[CH][LA ? LA : 1];                           // PACKED staging (struct uint4 here would live in scratch memory)
     // What a stage needs, load by load: for each of its groups CT weight pieces and (PACKED) LA activation pieces, then
@@ -167,8 +170,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const unsigned wstep = (unsigned)N * 64u;
     const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : qa + (size_t)(m0 >> 2) * four_bytes;
     int gstage = 0;                                       // first group of the stage being loaded
-    auto load = [&](int k, int set, int half) {
+    static_assert(!LATE || (CH == 2 && SP && (LOADS - LG) * SPAN / LOADS >= T), "the first group's products cover what comes before");
+    auto load = [&](int at, int set, int half) {
         const unsigned to = (unsigned)half * (STG * 16);
+        const int k = !LATE || at < LG ? at : at < LOADS - LG ? at + LG : at - (LOADS - 2 * LG);
         if (k < CH * LG) {
             const int c = k / LG, r = k % LG;
             if (r < CT) {
@@ -345,6 +350,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             }
             __builtin_amdgcn_s_setprio(0);
             drain();
+            if constexpr (LATE) {                        // (else the compiler waits for them in the middle of the next stage)
+#pragma unroll
+                for (int j = 0; j < CT; ++j) asm("" : "+v"(rw[0][CH - 1][j].x), "+v"(rw[0][CH - 1][j].y), "+v"(rw[0][CH - 1][j].z), "+v"(rw[0][CH - 1][j].w));
+            }
             store_packed(half ^ 1);
             __syncthreads();
         }
@@ -517,6 +526,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 //                                            RT CT NW CH SP          OCC
 // 128 x 128 as waves of 128 x 32: three workgroups per CU, so that a launch's last round is finer than with 128 x 256 (5808 x
 // 4096 x 11008 213 -> 189 us, 3324 x 5120 x 13824 237 -> 187, 640 x 12288 x 4096 38 -> 33, 11264 x 12288 x 4096 443 and 468).
+// 128 x 256 in stages of two groups, half the barriers of one (5808 x 22016 x 4096 369 -> 353 us, 11264 x 12288 x 4096 439 -> 434, 1101 x
+// 37888 x 3584 128 -> 123); the packed entry point's rows leave no room for the second group.
 // 64 x 128 as four waves of 64 x 32, three workgroups per CU; a weight belongs to one wave.  Stages of four groups are long enough for
 // a round trip to memory (400 x 22016 x 4096 49 us, 45 so); the packed entry point's rows, which pass registers, leave no
 // room for more than two.
@@ -524,7 +535,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #define F8_TILE_1(P, A, QK) w4a4_f8_kernel<4, 2, 4, P == PACKED_INT4 ? 2 : 4, 4, P, A, QK, 3>   // 64 x 128
 #define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 4, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
-#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, 1, 3, P, A, QK, 2>  // 128 x 256
+#define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, P == PACKED_INT4 ? 1 : 2, P == PACKED_INT4 ? 3 : 6, P, A, QK, 2>  // 128 x 256
 // 32 x 64 once more in longer stages, for launches that leave a CU with three workgroups at most (101 x 4096 x 11008 22.4 -> 19.5
 // us, 237 x 4096 x 11008 25.4 -> 24.4).  Activations of a layer only, not pinned.
 #define F8_TILE_5(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 4, P, A, QK, 2>  // 32 x 64
@@ -593,7 +604,7 @@ int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
         {4, 4.37f, 6, {0.305f, 0.447f, 0.730f, 1.060f, 1.266f, 1.588f}, 0.192f, 0.174f, 3},
         {4, 3.62f, 4, {0.252f, 0.343f, 0.550f, 0.819f}, 0.132f, 0.150f, 3},
         {4, 3.89f, 4, {0.174f, 0.217f, 0.349f, 0.468f}, 0.100f, 0.040f, 4},
-        {1, 6.52f, 4, {0.981f, 1.241f, 2.407f, 2.705f}, 0.440f, 0.592f, 2},
+        {2, 6.52f, 4, {0.840f, 1.190f, 2.370f, 2.580f}, 0.430f, 0.577f, 2},
         {8, 3.45f, 3, {0.148f, 0.220f, 0.360f}, 0.125f, 0.039f, 3},
     };
     auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < PINNED_TILES || !quota_a6_starts(M)); };

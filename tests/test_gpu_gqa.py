@@ -225,3 +225,25 @@ def test_layer_rows_and_packed_rows_give_the_same_projection(qb, N):
     qb.quota_w4a4_gemm(codes, scale, N, L.qkv.desc, y, d + 2 * dkv)
     assert torch.equal(qkv.view(torch.int16), y.view(torch.int16))
     assert np.array_equal(host(y).view(np.uint16), oracle.w4a4_gemm(c, host(scale), *W.qkv).view(np.uint16))
+
+
+@pytest.mark.parametrize("N", [130, 513])
+@pytest.mark.parametrize("shape", [(512, 8, 4, 64, 1376), (256, 4, 4, 64, 32)])
+def test_layer_on_tall_tiles_equals_the_same_on_short_ones(qb, pinned_gemm, shape, N):
+    """The 128 x 256 tile's stages of two groups, one register set of weights between them, at an odd number of groups (11), at two
+    and at one, against the 64 x 128 tile: the same bits, with start values (513 rows) and without."""
+    from paper_2604_17320_amd.model import KVCache4, make_taps
+    d, H, Hkv, dh, F = shape
+    W, L, cos, sin = build_gqa_layer(d, H, Hkv, dh, F, 78, 640)
+    x, pos = dev(wl.rng(N, "rows").standard_normal((N, d)).astype(np.float16)), dev(np.arange(N, dtype=np.int32))
+    seen = []
+    for variant in (4, 1):
+        pinned_gemm(variant)
+        qkv = torch.full((N, d + 2 * Hkv * dh), float("nan"), dtype=torch.float16, device="cuda")
+        x_out = torch.full((N, d), float("nan"), dtype=torch.float16, device="cuda")
+        cache, pos_out = KVCache4(1, N, Hkv, dh), torch.zeros(N, dtype=torch.int32, device="cuda")
+        ws = torch.full((L.workspace_bytes(1, N),), 0xFF, dtype=torch.uint8, device="cuda")
+        st = qb.State(1, N, 0, 0, x.data_ptr(), pos.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+        qb.quota_prefill_layer(L.desc, st, qb.KEEP_ALL, qb.quota_score_params_default(), cache.desc, make_taps(qkv=qkv), ws)
+        seen.append((qkv, x_out))
+    assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) and bool(a.isfinite().all()) for a, b in zip(*seen))
