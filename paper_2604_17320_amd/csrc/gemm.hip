@@ -18,12 +18,12 @@
 //
 // What bounds it: the issue of vector instructions.  A product holds its SIMD's issue for 8 of its 16 cycles, every other vector
 // instruction for 4, whatever the number of waves, and each product brings four fmas: issued register to register with scale chain
-// and unpack the products reach 52 % of the matrix rate at 8 x 4 blocks per wave, 48 at 8 x 2, 34 to 43 at 4 x 2, 24 to 31 on
+// and unpack the products reach 51 % of the matrix rate at 8 x 4 and 8 x 2 blocks per wave, 37 to 47 at 4 x 2, 27 to 37 on
 // the 32-row tiles; without the offset products the
 // launches of 1100 to 11264 rows take 2 to 9 % less (fp8 operands, 11264 x 12288 x 4096: 553 -> 532 us).  With fp6 operands for
 // fp8 ones bulk launches take 5 to 11 % less.  At a thousand rows and more
-// the matrix cores are busy about a third of the time; on the rows of a pruned prompt for 14 to 32 % of it, and the
-// waves wait for 20 to 30 % of their lives: one stage of lookahead, and a wait for all of it.
+// the matrix cores are busy about a third of the time; on the rows of a pruned prompt for 15 to 34 % of it, and the
+// waves wait for 21 to 31 % of their lives: one stage of lookahead, and a wait for all of it.
 //
 // Activation format inside a layer ("A6", written by the row quantizers): four rows at a time, 384 bytes per group, of row r
 // 64 bytes from 64 r on -- the first four of the six dwords of each 32 channels -- and 32 from 256 + 32 r on, the other two;
