@@ -70,10 +70,10 @@ __device__ __forceinline__ float halves_max(float v)
     return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 
-template <int DH>
+template <int DH, typename PRE>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
-    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int wgs, Prefetch pre)
+    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int wgs, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
         prefetch<256>(pre, blockIdx.x - wgs, gridDim.x - wgs);
@@ -218,10 +218,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
 }
 
 // One workgroup per 128 visual keys of a (sequence, head); wave w owns the 32 keys kb .. kb+31.
-template <int DH>
+template <int DH, typename PRE>
 __global__ __launch_bounds__(256, 3) void colmass_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
-    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, int wgs, Prefetch pre)
+    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, int wgs, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
         prefetch<256>(pre, blockIdx.x - wgs, gridDim.x - wgs);
@@ -385,8 +385,10 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     {
         ProfScope prof(QUOTA_K_ATTENTION_FWD, 4.0 * B * dd * ((double)N * (N + 1) / 2),
                        4.0 * dM * dd + 4.0 * dM * Hkv * dh, st);
-        auto kernel = dh == 128 ? attn_fwd_kernel<128> : attn_fwd_kernel<64>;
-        kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, (int)n1, s1.what);
+        s1.run([&](auto pre) {
+            auto kernel = dh == 128 ? attn_fwd_kernel<128, decltype(pre)> : attn_fwd_kernel<64, decltype(pre)>;
+            kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, (int)n1, pre);
+        });
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if (cues) {
@@ -396,8 +398,10 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
         // (query, visual key) pairs under the causal mask
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
-        auto kernel = dh == 128 ? colmass_kernel<128> : colmass_kernel<64>;
-        kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, (int)n2, s2.what);
+        s2.run([&](auto pre) {
+            auto kernel = dh == 128 ? colmass_kernel<128, decltype(pre)> : colmass_kernel<64, decltype(pre)>;
+            kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, (int)n2, pre);
+        });
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         colmass_reduce_kernel<<<dim3((unsigned)((Nv + 63) / 64) * B), blk, 0, st>>>(w.partial, H, Nv, cm_inter, cm_intra);
         QUOTA_RETURN_IF_LAUNCH_FAILED();

@@ -14,6 +14,13 @@ struct Prefetch {                       // up to six ranges of 16-byte pieces
     unsigned n[RANGES];
 };
 
+// What a launch without a share takes in its place: the kernel is then another, without these workgroups' code and 72 bytes of
+// arguments, which cost the host 3 us a launch when its caches are cold (first pass of a layer of 512 channels 125 -> 116 us, 115 before
+// there was anything to fetch).
+struct NoPrefetch {};
+template <int NT>
+__device__ __forceinline__ void prefetch(const NoPrefetch &, int, int) {}
+
 // Workgroup `wg` of `wgs` reads its share, 8 pieces a thread in flight.
 template <int NT>
 __device__ __forceinline__ void prefetch(const Prefetch &p, int wg, int wgs)
@@ -48,7 +55,15 @@ public:
     // workgroups to bring it, 128 KB each at least.  Only where a quarter of the CUs is idle: beside 252 workgroups a GQA layer of 1101
     // tokens over changing weights takes 314 us instead of 299, beside 3072 the longer ones gain nothing (4 x 2944 tokens
     // 1966 -> 1981).  Less than 4 MB in all (a layer of 512 channels) are not worth the workgroups: 51.9 us without, 52.7 with.
-    struct Share { Prefetch what; unsigned wgs; };
+    struct Share {
+        Prefetch what;
+        unsigned wgs;
+        template <typename LAUNCH> void run(LAUNCH launch) const
+        {
+            if (wgs) launch(what);
+            else launch(NoPrefetch{});
+        }
+    };
     Share take(unsigned wgs, float us, float rate)
     {
         Share s = {};

@@ -310,12 +310,12 @@ constexpr int SELECT_HIST = 4 * 3 * 2 * 256;      // counters of four two-rank s
 
 // K < 0: score only.  When K >= 0 the indices of the min(K, Nv) best tokens of
 // sequence b go to keep_idx[b][0..min(K,Nv)).
-template <int PER>
+template <int PER, typename PRE>
 __global__ __launch_bounds__(SCORE_THREADS) void score_topk_kernel(MetricSrc src, long stride_sq, int B, int Nv,
                                                          quota_score_params p,
                                                          float *__restrict__ score,
                                                          float *__restrict__ normed, int K,
-                                                         int32_t *__restrict__ keep_idx, int cap, Prefetch pre)
+                                                         int32_t *__restrict__ keep_idx, int cap, PRE pre)
 {
     if ((int)blockIdx.x >= B) {
         prefetch<SCORE_THREADS>(pre, blockIdx.x - B, gridDim.x - B);
@@ -379,17 +379,21 @@ int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return QUOTA_ERR_HIP;
         if (!granted[dev]) {
             const size_t most = ((size_t)4 * MAXV + SELECT_HIST + SELECT_RANGE + 8) * sizeof(uint32_t);
-            for (auto k : {score_topk_kernel<3>, score_topk_kernel<MAXV / SCORE_THREADS>})
-                if (hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)most) != hipSuccess)
+            for (const void *k : {(const void *)score_topk_kernel<3, Prefetch>, (const void *)score_topk_kernel<3, NoPrefetch>,
+                                  (const void *)score_topk_kernel<MAXV / SCORE_THREADS, Prefetch>,
+                                  (const void *)score_topk_kernel<MAXV / SCORE_THREADS, NoPrefetch>})
+                if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
                     return QUOTA_ERR_HIP;
             granted[dev] = true;
         }
     }
-    auto kernel = Nv <= SCORE_THREADS ? score_topk_kernel<1>
-                  : Nv <= 3 * SCORE_THREADS ? score_topk_kernel<3> : score_topk_kernel<MAXV / SCORE_THREADS>;
     const auto share = weights ? weights->take(B, 7.0f, 4.0f) : PrefetchList::Share{};
-    kernel<<<dim3(B + share.wgs), dim3(SCORE_THREADS), lds, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, cap, share.what);
+    share.run([&](auto pre) {
+        using P = decltype(pre);
+        auto kernel = Nv <= SCORE_THREADS ? score_topk_kernel<1, P>
+                      : Nv <= 3 * SCORE_THREADS ? score_topk_kernel<3, P> : score_topk_kernel<MAXV / SCORE_THREADS, P>;
+        kernel<<<dim3(B + share.wgs), dim3(SCORE_THREADS), lds, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, cap, pre);
+    });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
