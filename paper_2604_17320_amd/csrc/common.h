@@ -58,6 +58,16 @@ __device__ __forceinline__ float wave_max(float v)
 #undef STEP
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
+// ... of values that are not negative (no NaN): their bits order as integers do, which leaves one instruction a step where the
+// float maximum takes four (it first makes a quiet NaN of a signalling one that might have come along)
+__device__ __forceinline__ float wave_absmax(float v)
+{
+    uint32_t u = __float_as_uint(v);
+#define STEP(ctrl, rows) u = max(u, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, ctrl, rows, 0xf, false));
+    QUOTA_DPP_STEPS(STEP)
+#undef STEP
+    return __int_as_float(__builtin_amdgcn_readlane((int)u, 63));
+}
 __device__ __forceinline__ double wave_sum(double v)
 {
 #define STEP(ctrl, rows)                                                                       \
@@ -89,25 +99,26 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
-// block-wide (blockDim.x = 64*NW) max of a float and/or sum of a double; every thread gets the result.  `sm` needs
-// 2*NW doubles of LDS.
+// block-wide (blockDim.x = 64*NW) max of a float that is not negative and/or sum of a double; every thread gets the result.
+// `sm` needs 2*NW doubles of LDS.
 template <int NW, bool MAX, bool SUM>
 __device__ __forceinline__ void block_max_sum(float &mx, double &sum, double *sm)
 {
-    if (MAX) mx = wave_max(mx);
+    if (MAX) mx = wave_absmax(mx);
     if (SUM) sum = wave_sum(sum);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    float *fm = reinterpret_cast<float *>(sm);
     __syncthreads();          // protect sm against the previous use
     if (l == 0) {
-        if (MAX) sm[w] = (double)mx;
+        if (MAX) fm[w] = mx;
         if (SUM) sm[NW + w] = sum;
     }
     __syncthreads();
-    if (MAX) mx = (float)sm[0];
+    if (MAX) mx = fm[0];
     if (SUM) sum = sm[NW];
 #pragma unroll
     for (int i = 1; i < NW; ++i) {
-        if (MAX) mx = fmaxf(mx, (float)sm[i]);
+        if (MAX) mx = fmaxf(mx, fm[i]);
         if (SUM) sum += sm[NW + i];
     }
 }

@@ -53,6 +53,12 @@ __device__ __forceinline__ Codes8 codes_of_e4m3(const uint2 &e)              // 
     const uint32_t low = 0x0F0F0F0Fu;
     return {(e.x & low) | (e.y << 4 & ~low), (e.x >> 4 & 0x08080808u) | (e.y & 0x80808080u)};
 }
+__device__ __forceinline__ int sum_of(const Codes8 &c)
+{
+    const uint32_t negative = c.sign | (c.sign - (c.sign >> 3));             // whole nibbles
+    return (int)__builtin_amdgcn_udot8(c.mag, 0x11111111u, 0, false) -
+           2 * (int)__builtin_amdgcn_udot8(c.mag & negative, 0x11111111u, 0, false);
+}
 // What the first (second) eight codes of sixteen give to d0, d1 and d2.  Masks and shifts of a lane that always has the one or the
 // other can be made once.
 struct E6Masks { uint32_t mag[3], sign[3]; int mag_right, sign_right; };

@@ -195,6 +195,8 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
     }
     const f16 ksv = sks[srow * ng + min(tid, ng - 1)], vsv = svs[srow * ng + min(tid, ng - 1)];
     const int32_t pv = pos[srow];
+    const RowStore<OUT> store(tid, (int)drow);
+    const OUT to = row_out(oq_out, drow, n16);
 
     // the attention-output row is copied and/or fed to the activation quantizer in front of the
     // output projection (same code path as the stand-alone quantizer)
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
         double none = 0.0;
         block_max_sum<4, true, false>(a, none, sm);
         float s;
-        quantize_cached_row<false, ROW_THREADS, NCH>(v, n16, tid, a, row_out(oq_out, drow, n16), (int)(drow & 3), s);
+        quantize_cached_row<false, ROW_THREADS, NCH>(v, n16, tid, a, to, store, s);
         if (tid == 0) os_out[drow] = s;
     }
 }

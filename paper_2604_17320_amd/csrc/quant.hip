@@ -196,7 +196,7 @@ template <int GROUP, bool MAX, bool SUM>
 __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
 {
     if (GROUP == 64) {
-        if (MAX) mx = wave_max(mx);
+        if (MAX) mx = wave_absmax(mx);
         if (SUM) sum = wave_sum(sum);
     } else {
         block_max_sum<4, MAX, SUM>(mx, sum, sm);
@@ -217,13 +217,16 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
 {
     ROW_PROLOGUE();
     const int nchunk = d >> 3;
+    const bool first = row < rows_per_seq;               // (all rows of a dense tensor: no division)
     const uint4 *xr = reinterpret_cast<const uint4 *>(
-        x + (size_t)(row / rows_per_seq) * seq_stride + (size_t)(row % rows_per_seq) * ldx);
+        x + (first ? (size_t)row * ldx : (size_t)(row / rows_per_seq) * seq_stride + (size_t)(row % rows_per_seq) * ldx));
     Pack16 v[NCH];
     float a = 0.0f;
     double ss = 0.0;
 #pragma unroll
     for (int r = 0; r < NCH; ++r) v[r].u = xr[min(lane + GROUP * r, nchunk - 1)];
+    const RowStore<OUT> store(lane, row);
+    const OUT to = row_out(q, row, nchunk);
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
         int c = lane + GROUP * r;
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     }
     group_reduce<GROUP, true, WANT_METRICS>(a, ss, sm);
     float s;
-    double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), (int)(row & 3), s);
+    double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
     if (WANT_METRICS) { float dummy = 0.0f; group_reduce<GROUP, false, true>(dummy, rs, sm); }
     if (lane == 0) {
         if (scale) scale[row] = s;
@@ -276,6 +279,8 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
             ga[r][1] = gp[1];
         }
     }
+    const RowStore<OUT> store(lane, row);
+    const OUT to = row_out(q, row, nchunk);
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
         int c = lane + GROUP * r;
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
     }
     group_reduce<GROUP, true, WANT_METRICS>(a, rs, sm);
     float s;
-    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), (int)(row & 3), s);
+    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
     if (lane == 0) {
         scale[row] = s;
         if (WANT_METRICS) {
@@ -365,6 +370,8 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
             uu[r].u = ur[c];
         }
     }
+    const RowStore<OUT> store(lane, row);
+    const OUT to = row_out(q, row, nchunk);
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
         int c = lane + GROUP * r;
@@ -384,7 +391,7 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
     double none = 0.0;
     group_reduce<GROUP, true, false>(a, none, sm);
     float s;
-    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, row_out(q, row, nchunk), (int)(row & 3), s);
+    quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
     if (lane == 0) scale[row] = s;
 }
 

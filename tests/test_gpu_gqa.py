@@ -247,3 +247,42 @@ def test_layer_on_tall_tiles_equals_the_same_on_short_ones(qb, pinned_gemm, shap
         qb.quota_prefill_layer(L.desc, st, qb.KEEP_ALL, qb.quota_score_params_default(), cache.desc, make_taps(qkv=qkv), ws)
         seen.append((qkv, x_out))
     assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) and bool(a.isfinite().all()) for a, b in zip(*seen))
+
+
+@pytest.mark.parametrize("N", [35, 515])
+def test_layer_codes_at_half_steps(qb, N):
+    """The layer's own quantizers round by a conversion to e4m3 where the public one adds 1.5 * 2^23: the same codes where a value
+    lies half a step between two (ties go to the even code), next to it, and at zero from below; rows of a scale of every size
+    among them.  O and down products of injected rows against the public quantizer and GEMM, with start values (515 rows) and without."""
+    from paper_2604_17320_amd.model import KVCache4, make_taps
+    d, H, Hkv, dh, F = 640, 10, 2, 64, 2080                    # five groups; sixteen and a ragged one, two chunks a thread
+    W, L, cos, sin = build_gqa_layer(d, H, Hkv, dh, F, 79, 640)
+    r = wl.rng(N, "half steps")
+
+    def rows(n):
+        a = np.exp2(r.integers(-9, 9, (N, 1))).astype(np.float64)
+        x = r.integers(-14, 15, (N, n)) * a / 2                  # multiples of half a step, of maximum 7 a
+        x[np.arange(N), r.integers(0, n, N)] = 7 * a[:, 0]
+        near = r.random((N, n)) < 0.25
+        x = np.where(near & (np.abs(x) < 7 * a), x * (1 + r.choice([-1, 1], (N, n)) * 2.0 ** -10), x)
+        x[::5] = x[::5] * r.uniform(0.5, 1, (len(x[::5]), 1))
+        x[1::7, ::3] = -1e-4 * a[1::7]
+        return x.astype(np.float16)
+
+    o, z, x = rows(d), rows(F), r.standard_normal((N, d)).astype(np.float16)
+    xd, od, zd, pos = dev(x), dev(o), dev(z), dev(np.arange(N, dtype=np.int32))
+    t16 = lambda *s: torch.full(s, float("nan"), dtype=torch.float16, device="cuda")
+    x1, x_out = t16(N, d), t16(N, d)
+    cache, pos_out = KVCache4(1, N, Hkv, dh), torch.zeros(N, dtype=torch.int32, device="cuda")
+    ws = torch.full((L.workspace_bytes(1, N),), 0xFF, dtype=torch.uint8, device="cuda")
+    st = qb.State(1, N, 0, 0, xd.data_ptr(), pos.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+    taps = make_taps(x1=x1, inject_o=od, inject_z=zd)
+    qb.quota_prefill_layer(L.desc, st, qb.KEEP_ALL, qb.quota_score_params_default(), cache.desc, taps, ws)
+    for rows_in, lin, res, got in ((o, L.o, xd, x1), (z, L.down, x1, x_out)):
+        K = rows_in.shape[1]
+        codes, scale, y = torch.zeros((N, K // 2), dtype=torch.uint8, device="cuda"), torch.zeros(N, device="cuda"), t16(N, d)
+        qb.quota_quantize_act(dev(rows_in), N, K, K, codes, scale)
+        want = oracle.quantize_act(rows_in)
+        assert np.array_equal(unpack4(host(codes)), want[0])
+        qb.quota_w4a4_gemm(codes, scale, N, lin.desc, y, d, res, d)
+        assert torch.equal(got.view(torch.int16), y.view(torch.int16))
