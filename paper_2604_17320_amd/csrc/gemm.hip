@@ -52,6 +52,9 @@ namespace {
 //   SP: the loads are set off at the start of the stage (0) or spread over SP / 8 of its MFMAs, so that the waves
 //   do not queue for the address unit all at once, nor wait at the end for what was asked for late (64 x 128 tile, 237 x 12288 x
 //   4096: 23.5 us over a quarter of the stage, 20.4 over half, 21.9 over three).
+//   At the start of a stage they are left out past the last one, a round trip that the launch would wait for (32 x 64 tile, 42 x 512 x 512
+//   3.72 -> 3.63 us, 165 x 9728 x 896 7.9 -> 6.8, 320 x 5632 x 1024 7.8 -> 6.8); a branch around every spread load costs longer rows more
+//   than it saves short ones (38 groups in stages of 8: 7.7 -> 8.6).
 // A group in LDS: the rows' 64-byte parts, then their 32-byte parts.  Lane (row c, channels 32 q ..) reads 16 bytes of the first
 // and 8 of the second; 16-byte piece q of row r's first part sits at q ^ {0, 2, 3, 1}[r / 4 % 4], and the halves of the second
 // are swapped in rows 8 to 15 of 16, so that the lanes of a read do not share banks.
@@ -89,10 +92,25 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid < BM) {
-        const int m = min(m0 + tid, M - 1);
-        row_scale[tid] = sa[m] * F6_UNIT;
-        if constexpr (QKV) row_pos[tid] = min(max(qe.pos[m], 0), qe.n_pos - 1);
+    // Token scale and position of row tid of the tile.  Asked for beside the first stage where its loads go out all at once (SP = 0); where they
+    // are spread the compiler starts the first stage's weights behind its barrier, and a round trip in front costs less than waiting for
+    // them there (tile 32 x 64 in stages of 8, 42 x 2688 x 896: 4.0 us, 4.4 with the scales beside the stage).
+    float own_scale = 0.0f;
+    int own_pos = 0;
+    auto own_token = [&]() {
+        const int m = min(m0 + min(tid, BM - 1), M - 1);
+        own_scale = sa[m];
+        if constexpr (QKV) own_pos = qe.pos[m];
+    };
+    auto store_own_token = [&]() {
+        if (tid < BM) {
+            row_scale[tid] = own_scale * F6_UNIT;
+            if constexpr (QKV) row_pos[tid] = min(max(own_pos, 0), qe.n_pos - 1);
+        }
+    };
+    if constexpr (SP != 0) {
+        own_token();
+        store_own_token();
     }
 
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
@@ -275,7 +293,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     static_assert(CH >= 4 ? CH % 4 == 0 : RT % (4 / CH) == 0, "whole row blocks, or groups, per quarter");
 #pragma unroll
     for (int k = 0; k < LOADS; ++k) load(k, 0, 0);
+    if constexpr (!SP) {
+        own_token();
+        asm volatile("" : "+v"(own_scale), "+v"(own_pos));               // (not behind the wait)
+    }
     drain();
+    if constexpr (!SP) store_own_token();
     store_packed(0);
     __syncthreads();
 
@@ -296,8 +319,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             }
             gstage = g0 + CH;
             if (!PACKED) a0 += gstage < G ? CH * 384 : 0;
+            if (!SP && gstage < G) {
 #pragma unroll
-            for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1);
+                for (int k = 0; k < LOADS; ++k) load(k, (set + 1) % WS, half ^ 1);
+            }
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
                 if (c && g0 + c >= G) break;             // uniform: the last stage may hold fewer groups
@@ -324,9 +349,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                     if (i + 1 < RT) read_a(gp, i + 1, fa[(i + 1) & 1]);
                     else if (c + 1 < CH) read_a(gp + AST, 0, fa[0]);
                     if (STARTS && i + 1 < RT) k4[(i + 1) & 1] = start_of(sp, c, i + 1, fa[0]);
-                    if (CH == 1 && i == RT / 4 || CH == 2 && c == 0 && i == RT / 2) __builtin_amdgcn_s_setprio(1);
+                    if ((CH == 1 && i == RT / 4) || (CH == 2 && c == 0 && i == RT / 2)) __builtin_amdgcn_s_setprio(1);
                     if (CH == 1 && i == RT / 2) __builtin_amdgcn_s_setprio(2);
-                    if (CH == 1 && i == 3 * RT / 4 || CH == 2 && c == 1 && i == RT / 2) __builtin_amdgcn_s_setprio(3);
+                    if ((CH == 1 && i == 3 * RT / 4) || (CH == 2 && c == 1 && i == RT / 2)) __builtin_amdgcn_s_setprio(3);
 #pragma unroll
                     for (int j = 0; j < CT; ++j) {
                         __builtin_amdgcn_sched_barrier(0);
