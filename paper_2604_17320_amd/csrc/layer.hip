@@ -233,8 +233,9 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     PrefetchList weights;                // of the token-wise part, fetched beside what comes before it (prefetch.h)
     for (const quota_weights *p : {&L->o, &L->gu, &L->down}) weights.add(p->scales, quota_weights_scale_bytes(p->N, p->K));
     for (const quota_weights *p : {&L->o, &L->gu, &L->down}) weights.add(p->packed, quota_weights_packed_bytes(p->N, p->K));
+    PrefetchList *fetch = Mk > 0 && weights.worth(M) ? &weights : nullptr;
     TRY(quota_internal_attention(w.q_rot, w.khat, w.vhat, B, N, H, Hkv, dh, vb, Nv, w.o,
-                                 score ? w.cm_inter : nullptr, score ? w.cm_intra : nullptr, w.attn_ws, st, &weights));
+                                 score ? w.cm_inter : nullptr, score ? w.cm_intra : nullptr, w.attn_ws, st, fetch));
     TRY(dump(t->o, w.o, (size_t)M * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
     const bool inject_cm = t->inject_cm_inter && t->inject_cm_intra;
@@ -243,7 +244,7 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     if (score) {
         TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, inject_cm ? t->inject_cm_inter : w.cm_inter,
                                       inject_cm ? t->inject_cm_intra : w.cm_intra, B, Nv, p, w.score, k_keep,
-                                      w.keep_idx, st, &weights));
+                                      w.keep_idx, st, fetch));
         if (t->sumsq || t->ressq) {
             long n = (long)B * Nv;
             dim3 g((unsigned)((n + 255) / 256)), blk(256);

@@ -2,9 +2,9 @@
 // CUs and memory idle.  Attention, cues and top-k of a short prompt run on a few workgroups for 7 to 18 us each; workgroups
 // beyond theirs read the scales and weights of the O, gate/up and down projections, in the order of their use, and drop them.  The
 // projections then wait for that cache instead of HBM, stage after stage: 32 layers of 7B, 640 to 122 tokens, each layer's weights used
-// once, 4709 -> 4430 us (gate/up 30.3 -> 28.0, O and down together 35.0 -> 31.6, attention and cues 1 us longer each);
-// one layer over changing weights, 640 tokens 166 -> 158, 165 tokens 127 -> 124.  Scales first: without them every stage
-// waits for HBM as before (4590).
+// once, 4710 -> 4505 us (gate/up 30.3 -> 28.0, O and down together 35.0 -> 31.6, attention and cues 1 us longer each);
+// one layer over changing weights, 640 tokens 164.7 -> 159.6, 165 tokens 125.7 -> 122.5.  Scales first: without them every stage
+// waits for HBM as before (4590, and 4430 with them, on the same card).
 #pragma once
 #include "common.h"
 
@@ -51,10 +51,15 @@ public:
         left.n[ranges] = e > a ? (unsigned)((e - a) / 16) : 0;
         total += left.n[ranges++];
     }
+    // Whether a layer of so many rows gains by it.  The launches of 128 rows or less are over before the bytes are there, and those of
+    // less than 512 before less than 8 MB repay the workgroups (without -> with: stacks of 7B layers, 42 rows 693 -> 719 us, 80 rows within 1 %, 165
+    // rows 1004 -> 986; 20 layers of 2048 channels, 19 MB each, 42 rows 1214 -> 1275, 165 rows 1582 -> 1525; 64 layers of 1024 channels, 5 MB,
+    // 42 rows 3135 -> 3391, 300 rows 1 % more, 640 rows 4570 -> 4531).  Less than 4 MB never do (a layer of 512 channels 51.9 -> 52.7).
+    bool worth(size_t rows) const { return rows > 128 && total >= (size_t)(rows < 512 ? 8 : 4) << 16; }
     // For a launch of `wgs` workgroups that lasts for about `us`: what `rate` MB a microsecond bring in that time, and the
-    // workgroups to bring it, 128 KB each at least.  Only where a quarter of the CUs is idle: beside 252 workgroups a GQA layer of 1101
+    // workgroups to bring it, 128 KB each at most while CUs are left.  Only where a quarter of them is idle: beside 252 workgroups a GQA layer of 1101
     // tokens over changing weights takes 314 us instead of 299, beside 3072 the longer ones gain nothing (4 x 2944 tokens
-    // 1966 -> 1981).  Less than 4 MB in all (a layer of 512 channels) are not worth the workgroups: 51.9 us without, 52.7 with.
+    // 1966 -> 1981).
     struct Share {
         Prefetch what;
         unsigned wgs;
@@ -67,7 +72,7 @@ public:
     Share take(unsigned wgs, float us, float rate)
     {
         Share s = {};
-        if (wgs > 192 || total < (4u << 16)) return s;
+        if (wgs > 192) return s;
         unsigned room = (unsigned)(us * rate * 65536.0f), all = 0;
         for (int r = 0; r < ranges; ++r) {
             const unsigned n = left.n[r] < room ? left.n[r] : room;

@@ -475,3 +475,35 @@ def test_layer_workspace_anywhere(qb, off):
         outs.append([t.view(torch.uint8) for t in (x_out, cache.k_codes, cache.k_scales, cache.v_codes, cache.v_scales, y)])
     assert bool(torch.isfinite(outs[0][-1].view(torch.float16)).all())
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+def test_layer_with_weights_fetched_ahead(qb):
+    """One sequence, whose attention and cue pass leave CUs to the fetch of the later projections' weights, and four of the same, whose
+    launches leave none: the same bits in each, with 64-channel heads and weight scales that start between two 16-byte pieces."""
+    shape = wl.Shape("ahead", d=1024, H=16, F=2816, layers=1, B=1, Nv=500, Nt=20, n_outlier=10, vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 11)
+    keep = []
+    for name in ("qkv", "o", "gu", "down"):
+        lin = getattr(L, name)
+        keep.append(torch.cat([lin.scales.new_zeros(2), lin.scales]))
+        lin.desc.scales = keep[-1][2:].data_ptr()
+        assert lin.desc.scales % 16 == 4
+    from paper_2604_17320_amd.model import PrefillLayer
+    L = PrefillLayer(L.H, L.dh, L.F, L.qkv, L.o, L.gu, L.down, L.gamma1, L.gamma2, 1e-5, L.cosT, L.sinT)
+    four = wl.Shape("four", **{**{k: getattr(shape, k) for k in ("d", "H", "F", "layers", "Nv", "Nt", "n_outlier", "vis_begin")}, "B": 4})
+    x, pos = wl.hidden_state(shape, 11), wl.positions(shape)
+    one = run_gpu(qb, L, shape, x, pos, 100)
+    many = run_gpu(qb, L, four, np.tile(x, (4, 1)), np.tile(pos, 4), 100)
+    for name in ("qkv", "o", "cm_inter", "cm_intra", "score", "keep_idx", "x1", "z", "x_next", "cache_kc", "cache_vs"):
+        for part in np.split(many[name], 4):
+            assert part.tobytes() == one[name].tobytes(), name
+
+
+def test_long_top_k_beside_the_fetch(qb):
+    """More than 3072 visual tokens with eight heads: attention and cues fill the chip, score and top-k run beside the fetch."""
+    shape = wl.Shape("long", d=512, H=8, F=5632, layers=1, B=1, Nv=3100, Nt=100, n_outlier=4, vis_begin=0)
+    W, L, cos, sin = build_layer(shape, 12)
+    got = run_gpu(qb, L, shape, wl.hidden_state(shape, 12), wl.positions(shape), 77)
+    score = oracle.score(got["sumsq"], got["ressq"], got["cm_inter"], got["cm_intra"])
+    assert np.array_equal(got["score"].view(np.uint32), score.view(np.uint32))
+    assert np.array_equal(got["keep_idx"], oracle.topk(score, 77))
