@@ -326,6 +326,45 @@ def test_kv_quant_of_every_group_maximum(qb):
     assert np.array_equal(host(out["v"]).view(np.uint16), vhat.view(np.uint16))
 
 
+def test_kv_quant_of_groups_that_are_not_finite(qb):
+    """Groups whose maximum is infinite (finite values become 0, infinities NaN and so -8), with a NaN beside finite values (the maximum
+    passes over it, its code is -8) and of NaNs alone: codes, scales and dequantized values as the definition gives them."""
+    from paper_2604_17320_amd.model import KVCache4
+    M, H, dh = 9, 2, 128
+    d = H * dh
+    r = wl.rng(41, "not finite")
+    v = r.standard_normal((M, d)).astype(np.float16)
+    bad = np.array([np.inf, -np.inf, np.nan], np.float16)
+    for row in range(1, M):                              # row 0 stays finite
+        for g in range(d // 64):
+            v[row, 64 * g + r.permutation(64)[: row]] = bad[r.integers(0, 3, row)] if row > 3 else bad[row - 1]
+    v[M - 1, :64] = np.nan
+    x = v.astype(np.float32).reshape(M, d // 64, 64)
+    a = np.fmax.reduce(np.abs(x), axis=2, initial=0.0)
+    scales = (a / np.float32(7)).astype(np.float16)
+    scales[scales == 0] = 1
+    s = scales.astype(np.float32)[:, :, None]
+    with np.errstate(invalid="ignore"):
+        t = x * (np.float32(1) / s)
+        codes = np.where(np.isnan(t), -8, np.clip(np.rint(t), -8, 7)).astype(np.float32)
+        hat = (codes * s).astype(np.float16).reshape(M, d)
+    codes = codes.astype(np.int8).reshape(M, d)
+    assert np.array_equal(codes[0], oracle.kv_quant(v[:1])[0][0]) and (codes[M - 1, :64] == -8).all()
+    qkv = np.concatenate([np.zeros_like(v), np.zeros_like(v), v], axis=1)
+    f16 = lambda *shape: torch.zeros(shape, dtype=torch.float16, device="cuda")
+    q8 = lambda: torch.zeros((M, d // 2), dtype=torch.uint8, device="cuda")
+    out = dict(q=f16(M, d), k=f16(M, d), v=f16(M, d), kc=q8(), ks=f16(M, d // 64), vc=q8(), vs=f16(M, d // 64))
+    cos, sin = wl.rope_tables(dh, 1)
+    qb.quota_rope_kv_quant(dev(qkv), M, H, dh, torch.zeros(M, dtype=torch.int32, device="cuda"), dev(cos), dev(sin), 1,
+                           out["q"], out["k"], out["v"], out["kc"], out["ks"], out["vc"], out["vs"])
+    cache = KVCache4(1, M, H, dh)
+    qb.quota_kv_quant_append(dev(v), dev(v), 1, M, H, dh, None, M, cache.desc)
+    for got_codes, got_scales in ((out["vc"], out["vs"]), (cache.k_codes[0], cache.k_scales[0]), (cache.v_codes[0], cache.v_scales[0])):
+        assert np.array_equal(unpack4(host(got_codes)), codes)
+        assert np.array_equal(host(got_scales).view(np.uint16), scales.view(np.uint16))
+    assert np.array_equal(host(out["v"]), hat, equal_nan=True)
+
+
 def test_kv_quant_append(qb):
     from paper_2604_17320_amd.model import KVCache4
     B, N, H, dh = 2, 24, 4, 128
