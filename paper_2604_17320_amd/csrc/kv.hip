@@ -195,7 +195,8 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
     }
     const f16 ksv = sks[srow * ng + min(tid, ng - 1)], vsv = svs[srow * ng + min(tid, ng - 1)];
     const int32_t pv = pos[srow];
-    const RowStore<OUT> store(tid, (int)drow);
+    RowStore<OUT> store;
+    store.make(tid, (int)drow);
     const OUT to = row_out(oq_out, drow, n16);
 
     // the attention-output row is copied and/or fed to the activation quantizer in front of the

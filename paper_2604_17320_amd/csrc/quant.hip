@@ -225,7 +225,8 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     double ss = 0.0;
 #pragma unroll
     for (int r = 0; r < NCH; ++r) v[r].u = xr[min(lane + GROUP * r, nchunk - 1)];
-    const RowStore<OUT> store(lane, row);
+    RowStore<OUT> store;
+    if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
@@ -241,6 +242,7 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     }
     group_reduce<GROUP, true, WANT_METRICS>(a, ss, sm);
     float s;
+    if (GROUP == 64) store.make(lane, row);
     double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
     if (WANT_METRICS) { float dummy = 0.0f; group_reduce<GROUP, false, true>(dummy, rs, sm); }
     if (lane == 0) {
@@ -279,7 +281,8 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
             ga[r][1] = gp[1];
         }
     }
-    const RowStore<OUT> store(lane, row);
+    RowStore<OUT> store;
+    if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
@@ -335,6 +338,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
     }
     group_reduce<GROUP, true, WANT_METRICS>(a, rs, sm);
     float s;
+    if (GROUP == 64) store.make(lane, row);
     quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
     if (lane == 0) {
         scale[row] = s;
@@ -370,7 +374,8 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
             uu[r].u = ur[c];
         }
     }
-    const RowStore<OUT> store(lane, row);
+    RowStore<OUT> store;
+    if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
@@ -391,6 +396,7 @@ __global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
     double none = 0.0;
     group_reduce<GROUP, true, false>(a, none, sm);
     float s;
+    if (GROUP == 64) store.make(lane, row);
     quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
     if (lane == 0) scale[row] = s;
 }

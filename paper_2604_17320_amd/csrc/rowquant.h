@@ -78,13 +78,16 @@ __host__ __device__ __forceinline__ RowOutA6Starts row_out(RowOutA6Starts o, siz
 }
 // Stores chunks (8 channels) of a row in the A6 format, chunk c by a thread whose chunks are all idx modulo 64; four
 // neighbouring lanes hold the chunks of 32 channels.  A pair's lanes put their shares of d0, d1 and d2 together; its first stores d0, its
-// second d1 and d2.  Masks and the place inside a group are the thread's own; a kernel makes them first of all, while it waits for its row.
+// second d1 and d2.  Masks and the place inside a group are the thread's own, made once: by kernels of a workgroup per row while they
+// wait for it, by kernels of a wave per row when the sums are done (their registers are what limits the rows in flight: early, 11264
+// rows of 4096 columns took 8 more, four waves a SIMD instead of five).
 typedef uint32_t u32x2_at4 __attribute__((ext_vector_type(2), aligned(4), may_alias));
 struct E6Store {
     E6Masks k;
     unsigned at;                         // bytes from the row's first dword to this thread's place in a group
-    __device__ __forceinline__ E6Store(int idx, int row) : k(e2m3_masks(idx & 1))
+    __device__ __forceinline__ void make(int idx, int row)
     {
+        k = e2m3_masks(idx & 1);
         const unsigned quarter = idx >> 2 & 3, main = quarter * 16, tail = 256 - 32 * (row & 3) + quarter * 8;
         at = idx & 1 ? (idx & 2 ? tail : main + 4) : main + (idx & 2 ? 12 : 0);
 #pragma unroll
@@ -104,7 +107,7 @@ struct E6Store {
 };
 // What the final phase below is handed for a row of the format OUT: an E6Store, or nothing
 struct NoStore {
-    __device__ __forceinline__ NoStore(int, int) {}
+    __device__ __forceinline__ void make(int, int) {}
 };
 template <typename OUT>
 using RowStore = std::conditional_t<OUT::A6, E6Store, NoStore>;
