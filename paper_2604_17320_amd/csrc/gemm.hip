@@ -92,25 +92,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Token scale and position of row tid of the tile.  Asked for beside the first stage where its loads go out all at once (SP = 0); where they
-    // are spread the compiler starts the first stage's weights behind its barrier, and a round trip in front costs less than waiting for
-    // them there (tile 32 x 64 in stages of 8, 42 x 2688 x 896: 4.0 us, 4.4 with the scales beside the stage).
-    float own_scale = 0.0f;
-    int own_pos = 0;
-    auto own_token = [&]() {
-        const int m = min(m0 + min(tid, BM - 1), M - 1);
-        own_scale = sa[m];
-        if constexpr (QKV) own_pos = qe.pos[m];
-    };
-    auto store_own_token = [&]() {
+    // Token scale and position of row tid of the tile.  On a layer's rows, where a stage's loads go out all at once (SP = 0), they are asked
+    // for beside the first stage (packed ones, 33 x 4096 x 11008: 31.6 us, 33.7 so).  Where loads are spread the compiler starts the first stage's
+    // weights behind its barrier, and a round trip in front costs less than waiting for them there (32 x 64 in stages of 8, 42 x 2688 x 896:
+    // 4.0 us, 4.4 with the scales beside the stage).
+    constexpr bool TOGETHER = !SP && !PACKED;
+    if constexpr (!TOGETHER) {
         if (tid < BM) {
-            row_scale[tid] = own_scale * F6_UNIT;
-            if constexpr (QKV) row_pos[tid] = min(max(own_pos, 0), qe.n_pos - 1);
+            const int m = min(m0 + tid, M - 1);
+            row_scale[tid] = sa[m] * F6_UNIT;
+            if constexpr (QKV) row_pos[tid] = min(max(qe.pos[m], 0), qe.n_pos - 1);
         }
-    };
-    if constexpr (SP != 0) {
-        own_token();
-        store_own_token();
     }
 
     // Global loads are unconditional with clamped addresses: rows past M and columns past N repeat the last
@@ -293,12 +285,20 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     static_assert(CH >= 4 ? CH % 4 == 0 : RT % (4 / CH) == 0, "whole row blocks, or groups, per quarter");
 #pragma unroll
     for (int k = 0; k < LOADS; ++k) load(k, 0, 0);
-    if constexpr (!SP) {
-        own_token();
-        asm volatile("" : "+v"(own_scale), "+v"(own_pos));               // (not behind the wait)
+    if constexpr (TOGETHER) {
+        const int m = min(m0 + min(tid, BM - 1), M - 1);
+        float scale = sa[m];
+        int pos = 0;
+        if constexpr (QKV) pos = qe.pos[m];
+        asm volatile("" : "+v"(scale), "+v"(pos));       // (asked for here, not behind the wait)
+        drain();
+        if (tid < BM) {
+            row_scale[tid] = scale * F6_UNIT;
+            if constexpr (QKV) row_pos[tid] = min(max(pos, 0), qe.n_pos - 1);
+        }
+    } else {
+        drain();
     }
-    drain();
-    if constexpr (!SP) store_own_token();
     store_packed(0);
     __syncthreads();
 
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             }
             gstage = g0 + CH;
             if (!PACKED) a0 += gstage < G ? CH * 384 : 0;
-            if (!SP && gstage < G) {
+            if (!TOGETHER || gstage < G) {
 #pragma unroll
-                for (int k = 0; k < LOADS; ++k) load(k, (set + 1) % WS, half ^ 1);
+                for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1);
             }
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
@@ -612,38 +612,53 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
     return QUOTA_OK;
 }
 
+ActFormat acts_of(int M) { return quota_a6_starts(M) ? A6_STARTS : A6; }       // a layer's M rows
+
 int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set_gemm_variant
 
-// Tile choice by a cost model fitted to measured kernel times on this GPU (us; 112 shapes of 40 to 11776 rows, 512 to
-// 37888 columns and 512 to 18944 channels, all tiles: the choice costs 0.6 % over the best of each on average, 7 % at
-// most).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
-// slope * x, and more for every round of `occ` workgroups, beyond; c0 is the launch, prologue and epilogue.
+// Tile choice by cost models fitted to measured kernel times on this GPU (us, over weights that no cache holds), one for a layer's rows
+// (112 shapes of 40 to 11776 rows, 512 to 37888 columns and 512 to 18944 channels; the 32 x 64 tile's line, which has changed since, by 270
+// of 33 to 511 rows and of narrow layers, where the choice costs 0.6 % over the best tile of each on average, 2.3 % with the line before) and one for
+// packed rows, whose stages are shorter (387 shapes of 33 to 11776 rows; 0.2 % on average, 10 % at most, 3.1 % by a layer's: 5808 x 4096 x
+// 11008 301 us, 236 so).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
+// slope * x, and more for every round of `occ` workgroups, beyond; c0 is the launch, prologue and epilogue, wg an epilogue more for every
+// workgroup beyond the first of a CU (a layer's was fitted without).
 // Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
 // tiles spread small problems over more waves.  Columns of a tile lie in [min_bn, max_bn] (the QKV
-// epilogue needs whole heads that stay inside q, k or v), its number below `tiles`.
-int choose_tile(int M, int N, int K, int min_bn, int max_bn, int tiles)
+// epilogue needs whole heads that stay inside q, k or v); `narrow`: what a tile of one block of columns per wave costs besides.
+int choose_tile(ActFormat acts, int M, int N, int K, int min_bn, int max_bn, float narrow = 0.0f)
 {
-    struct Cost { int ch; float c0; int n; float u[6], slope, round; int occ; };
-    static const Cost cost[TILES] = {
-        {2, 5.09f, 6, {0.559f, 0.764f, 1.159f, 1.816f, 1.906f, 2.348f}, 0.311f, 0.255f, 3},
-        {4, 4.37f, 6, {0.305f, 0.447f, 0.730f, 1.060f, 1.266f, 1.588f}, 0.192f, 0.174f, 3},
-        {4, 3.62f, 4, {0.252f, 0.343f, 0.550f, 0.819f}, 0.132f, 0.150f, 3},
-        {4, 3.89f, 4, {0.174f, 0.217f, 0.349f, 0.468f}, 0.100f, 0.040f, 4},
-        {2, 6.52f, 4, {0.840f, 1.190f, 2.370f, 2.580f}, 0.430f, 0.577f, 2},
-        {8, 3.45f, 3, {0.148f, 0.220f, 0.360f}, 0.125f, 0.039f, 3},
+    struct Cost { int ch; float c0, wg; int n; float u[6], slope, round; int occ; };
+    static const Cost layer[TILES] = {
+        {2, 5.09f, 0.0f, 6, {0.559f, 0.764f, 1.159f, 1.816f, 1.906f, 2.348f}, 0.311f, 0.255f, 3},
+        {4, 4.37f, 0.0f, 6, {0.305f, 0.447f, 0.730f, 1.060f, 1.266f, 1.588f}, 0.192f, 0.174f, 3},
+        {4, 3.62f, 0.0f, 4, {0.252f, 0.343f, 0.550f, 0.819f}, 0.132f, 0.150f, 3},
+        {4, 3.60f, 0.0f, 4, {0.181f, 0.200f, 0.335f, 0.468f}, 0.120f, 0.042f, 4},
+        {2, 6.52f, 0.0f, 4, {0.840f, 1.190f, 2.370f, 2.580f}, 0.430f, 0.577f, 2},
+        {8, 3.45f, 0.0f, 3, {0.148f, 0.220f, 0.360f}, 0.125f, 0.039f, 3},
     };
-    auto fits = [&](int v) { return kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn && (v < PINNED_TILES || !quota_a6_starts(M)); };
+    static const Cost packed[PINNED_TILES] = {
+        {2, 5.451f, 2.107f, 4, {0.768f, 1.041f, 1.756f, 2.103f}, 0.293f, 0.490f, 2},
+        {2, 3.767f, 1.160f, 5, {0.527f, 0.646f, 0.880f, 1.309f, 1.523f}, 0.227f, 0.231f, 4},
+        {4, 3.551f, 1.386f, 6, {0.378f, 0.500f, 0.663f, 0.918f, 1.045f, 1.344f}, 0.079f, 0.224f, 2},
+        {4, 3.186f, 0.795f, 6, {0.303f, 0.369f, 0.560f, 0.669f, 0.850f, 0.966f}, 0.116f, 0.168f, 5},
+        {1, 7.593f, 3.600f, 3, {1.174f, 1.471f, 2.663f}, 0.403f, 0.432f, 1},
+    };
+    const Cost *cost = acts == PACKED_INT4 ? packed : layer;
+    const int tiles = acts == A6 ? TILES : PINNED_TILES;
+    auto fits = [&](int v) { return v < tiles && kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn; };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
     const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     int best = -1;
     float best_t = 0.0f;
     for (int v = 0; v < tiles; ++v) {
         if (!fits(v)) continue;
-        const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn);
+        const Cost &c = cost[v];
+        const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn), cus = (wgs + 255) / 256;
         const float x = (float)wgs / 256.0f;
-        const int groups = (G + cost[v].ch - 1) / cost[v].ch * cost[v].ch, n = 256 * cost[v].occ;
-        const float t = cost[v].c0 + groups * (x <= (float)cost[v].n ? cost[v].u[(wgs + 255) / 256 - 1]
-                                                                     : cost[v].slope * x + cost[v].round * (float)((wgs + n - 1) / n));
+        const int groups = (G + c.ch - 1) / c.ch * c.ch, n = 256 * c.occ;
+        const float group = x <= (float)c.n ? c.u[cus - 1] : c.slope * x + c.round * (float)((wgs + n - 1) / n);
+        const float t = c.c0 + c.wg * (float)(cus - 1) + groups * group + (kTiles[v].bn < 128 ? narrow : 0.0f);
         if (best < 0 || t < best_t) { best = v; best_t = t; }
     }
     return best;
@@ -684,7 +699,7 @@ int quota_internal_w4a4_gemm_a6(const uint8_t *qa6, const float *sa, int M, cons
     if (!scales_on_dwords(W))
         return gemm_16_rows_at_a_time(qa6, QUOTA_ROWS16_A6, quota_a6_row_bytes(W->K), sa, M, W, (f16 *)y_f16, ldy,
                                       (const f16 *)residual_opt, ldr, st);
-    const int v = choose_tile(M, W->N, W->K, 0, 256, TILES);
+    const int v = choose_tile(acts_of(M), M, W->N, W->K, 0, 256);
     return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, PLAIN>(v) : tile_kernel<A6, PLAIN>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
 }
@@ -692,14 +707,15 @@ int quota_internal_w4a4_gemm_a6(const uint8_t *qa6, const float *sa, int M, cons
 // Gate/up projection with SiLU(gate) * up in the epilogue: z [M][N / 2], the bits of the plain projection and the
 // stand-alone product.  Returns QUOTA_ERR_SHAPE when the fused form does not fit (the caller then runs the two kernels
 // separately): with unaligned scales, or where the tile of choice has one block of columns per wave (projections
-// that leave the chip part idle, 37 x 2752 x 512: 4 us each way).
+// that leave the chip part idle, 37 x 2752 x 512: 4 us each way).  The product then takes the quantizer in front of down longer (33 to 80 rows
+// of 1376, 2816 and 11008 channels 0.3, 0.4 and 1.2 us).
 int quota_internal_w4a4_gemm_silu(const uint8_t *qa6, const float *sa, int M, const quota_weights *W, void *z_f16,
                                   hipStream_t st)
 {
     if (!qa6 || !sa || !W || !W->packed || !W->scales || !z_f16) return QUOTA_ERR_NULL;
     if (M <= 16 || W->N % 64 != 0 || W->K % 32 != 0 || !scales_on_dwords(W) || (reinterpret_cast<uintptr_t>(z_f16) & 15))
         return QUOTA_ERR_SHAPE;
-    const int v = choose_tile(M, W->N, W->K, 0, 256, TILES);
+    const int v = choose_tile(acts_of(M), M, W->N, W->K, 0, 256, 0.2f + 4.5e-5f * (float)W->N);
     if (kTiles[v].bn < 128) return QUOTA_ERR_SHAPE;
     return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, SILU_MUL>(v) : tile_kernel<A6, SILU_MUL>(v), v, kTiles[v].kernel_id,
                      qa6, sa, M, W, (f16 *)z_f16, W->N / 2, nullptr, 0, nullptr, st);
@@ -730,7 +746,7 @@ extern "C" int quota_w4a4_gemm(const uint8_t *qa, const float *sa, int M, const 
     if (!dwords) return gemm_16_rows_at_a_time(qa, QUOTA_ROWS16_PACKED, W->K / 2, sa, M, W, y, ldy, res, ldr, st);
     if (M <= 16)            // the decode step: stream the weights once
         return quota_internal_rows16(qa, QUOTA_ROWS16_PACKED, sa, M, W, y, ldy, res, ldr, st);
-    const int v = choose_tile(M, W->N, W->K, 0, 256, PINNED_TILES);
+    const int v = choose_tile(PACKED_INT4, M, W->N, W->K, 0, 256);
     return launch_f8(tile_kernel<PACKED_INT4, PLAIN>(v), v, kTiles[v].kernel_id, qa, sa, M, W, y, ldy, res, ldr, nullptr, st);
 }
 
@@ -750,7 +766,7 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa6, const float *sa, int M, con
         W->N != d + 2 * dkv || W->K % 32 != 0 || !scales_on_dwords(W))
         return QUOTA_ERR_SHAPE;
     if (M == 0) return QUOTA_OK;
-    const int v = choose_tile(M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128, TILES);
+    const int v = choose_tile(acts_of(M), M, W->N, W->K, qe->dh, d % 256 == 0 && dkv % 256 == 0 ? 256 : 128);
     return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, QKV_ROPE_KV>(v) : tile_kernel<A6, QKV_ROPE_KV>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_opt, W->N, nullptr, 0,
                      nullptr, st, qe);
 }
