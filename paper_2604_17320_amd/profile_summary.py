@@ -36,7 +36,8 @@ import sys
 # profiler kernel name (substring, first match counts) -> kernel class name used by the library's own timing; kernels
 # that it does not time go by their own names
 CLASSES = [
-    ("w4a4_f8_kernelILi4ELi2ELi4ELi2ELi6ELNS_9ActFormatE2ELb1E", "w4a4_gemm_other"),      # with the integer sums
+    ("w4a4_f8_kernelILi4ELi2ELi4ELi2ELi4ELNS_9ActFormatE2ELb1E", "w4a4_gemm_other"),      # with the integer sums
+    ("w4a4_f8_kernelILi4ELi2ELi4ELi2ELi6ELNS_9ActFormatE2ELb1E", "w4a4_gemm_other"),      # (as earlier profiles name it)
     ("w4a4_f8_kernelILi4ELi4ELi2ELi2ELi6ELb1ELb1E", "w4a4_gemm_other"),      # (as earlier profiles name it)
     ("w4a4_f8_kernelILi8ELi2ELi4E", "w4a4_gemm_128x128"),
     ("w4a4_f8_kernelILi4ELi4ELi4E", "w4a4_gemm_64x256"),                     # (as earlier profiles name it)

@@ -80,6 +80,20 @@ def test_profile_summary_knows_the_kernels_there_are():
     assert gemm | {"w4a4_gemm_other", "w4a4_gemm_rows16", "attention_decode", "score_tokens", "pack_weights"} <= timed
 
 
+def test_profile_summary_classes_of_the_built_gemm_tiles():
+    """The class of every GEMM tile by the name that it has in the library: by rows and columns, and the one with the integer sums apart."""
+    from paper_2604_17320_amd import binding
+    with open(binding.LIB_PATH, "rb") as f:
+        names = {m.decode() for m in re.findall(rb"_ZN12_GLOBAL__N_114w4a4_f8_kernel\w+", f.read())}
+    seen = set()
+    for name in names:
+        rt, ct, nw, sums = map(int, re.search(r"ILi(\d+)ELi(\d+)ELi(\d+)E.*?ActFormatE\dELb(\d)E", name).groups())
+        want = "w4a4_gemm_other" if sums else f"w4a4_gemm_{16 * rt}x{16 * ct * nw}"
+        assert ps.classify(name) == want, name
+        seen.add(want)
+    assert seen == {"w4a4_gemm_other"} | {f"w4a4_gemm_{t}" for t in ("128x128", "64x128", "32x128", "32x64", "128x256")}
+
+
 def test_profile_summary_stats_table(tmp_path, capsys):
     rows = [dict(Name="_Z19quantize_act_kernelILb0ELi64ELi8EEv", Calls=4, TotalDurationNs=100000),
             dict(Name="_ZN12_GLOBAL__N_115attn_fwd_kernelILi128EEEv", Calls=2, TotalDurationNs=30000),
