@@ -1,5 +1,5 @@
 // W4A4 GEMM for gfx950 on the fp6 matrix cores: y = (int4 activations) x (int4 weights)^T with an
-// fp32 scale per 128-channel weight group.
+// fp32 scale per 128-channel weight group.  ("f8" in the names is the matrix instruction's, v_mfma_..._f8f6f4.)
 //
 // Small integers are exact in fp6 (e2m3), and the fp32 accumulator of v_mfma_f32_16x16x128_f8f6f4 is
 // exact for sums below 2^24 units, so one such instruction returns the exact integer dot product of a
@@ -561,8 +561,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #define F8_TILE_2(P, A, QK) w4a4_f8_kernel<2, 2, 4, 4, 4, P, A, QK, 2>  // 32 x 128
 #define F8_TILE_3(P, A, QK) w4a4_f8_kernel<2, 1, 4, 4, 0, P, A, QK, 2>  // 32 x 64
 #define F8_TILE_4(P, A, QK) w4a4_f8_kernel<8, 4, 4, P == PACKED_INT4 ? 1 : 2, P == PACKED_INT4 ? 3 : 6, P, A, QK, 2>  // 128 x 256
-// 32 x 64 once more in longer stages, for launches that leave a CU with three workgroups at most (101 x 4096 x 11008 22.4 -> 19.5
-// us, 237 x 4096 x 11008 25.4 -> 24.4).  Activations of a layer only, not pinned.
+// 32 x 64 once more in longer stages, a layer's rows below 512 only, not pinned: chosen where its fitted time is the lowest, which is up to
+// one workgroup per CU and from five groups on (101 x 4096 x 11008 22.4 -> 19.5 us; at 237 x 4096 x 11008, 1.9 workgroups, 25.0 against
+// 24.3 in stages of four).
 #define F8_TILE_5(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 4, P, A, QK, 2>  // 32 x 64
 
 struct TileShape { int bm, bn, nt, kernel_id; };

@@ -65,9 +65,10 @@ int quota_internal_w4a4_gemm_qkv(const uint8_t *qa6, const float *sa, int M, con
 // (groups of a row in memory: stages of up to 8 groups may read past the last)
 __host__ __device__ inline int quota_a6_groups(int G) { return ((G + 7) & ~7) | 1; }
 inline size_t quota_a6_row_bytes(int K) { return (size_t)quota_a6_groups((K + 127) / 128) * 96; }
-// The sums cost the quantizers more than the GEMMs gain where those wait for memory anyway.  A 7B layer with and
-// without: all its products at 160 to 237 rows 147.0 and 146.1 us, first product at 640 rows 188.9 and 189.8,
-// 11264 and 5808 rows 1609 and 1656.
+// The sums cost the quantizers more than the GEMMs gain where those wait for memory anyway.  Pairs of whole layers by a line at 256, 512, 1024
+// and 2048 rows, us: 512 channels 78 to 198 at 270 to 2900 rows, within 1 % of each other; 7B shape 270 rows 259, 256, 256, 257, 640 rows 353, 351,
+// 356, 357, 1800 rows 835, 835, 834, 822, but 800 rows 463, 465, 430, 433; 13B shape 530 rows 522, 527, 492, 488, 800 rows 624, 621, 631, 633, 1800
+// rows 1153, 1156, 1152, 1182: not one line for all.
 inline bool quota_a6_starts(size_t M) { return M >= 512; }
 // Bytes of M rows in it, or as the few-row GEMM's fragments (up to 32 rows, 1 KB a group and 16 rows).
 inline size_t quota_a6_bytes(size_t M, int K)
