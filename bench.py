@@ -19,6 +19,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP6_TOPS = 10000.0     # MI355X dense fp6 MFMA, TOP/s: the W4A4 GEMM's tiles multiply int4 codes as e2m3 numbers
+PEAK_INT8_TOPS = 5000.0     # ... and dense int8 MFMA, the peak that an int8 contraction of the same codes would be held against
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, GB/s
 
 
@@ -513,6 +514,8 @@ def main():
                roofline=roofline,
                gemm_all=dict(TOPs=round(gemm_ops / (gemm_ms * 1e-3) / 1e12, 1) if gemm_ms else None,
                              frac_fp6_peak=round(gemm_ops / (gemm_ms * 1e-3) / 1e12 / PEAK_FP6_TOPS, 4)
+                             if gemm_ms else None,
+                             frac_int8_peak=round(gemm_ops / (gemm_ms * 1e-3) / 1e12 / PEAK_INT8_TOPS, 4)
                              if gemm_ms else None, step_ms=round(gemm_ms / args.profile_steps, 4)),
                kernels=kern)
     if not args.no_bandwidth:
