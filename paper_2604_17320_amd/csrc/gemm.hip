@@ -716,7 +716,7 @@ int quota_internal_w4a4_gemm_silu(const uint8_t *qa6, const float *sa, int M, co
     if (!qa6 || !sa || !W || !W->packed || !W->scales || !z_f16) return QUOTA_ERR_NULL;
     if (M <= 16 || W->N % 64 != 0 || W->K % 32 != 0 || !scales_on_dwords(W) || (reinterpret_cast<uintptr_t>(z_f16) & 15))
         return QUOTA_ERR_SHAPE;
-    const int v = choose_tile(acts_of(M), M, W->N, W->K, 0, 256, 0.2f + 4.5e-5f * (float)W->N);
+    const int v = choose_tile(acts_of(M), M, W->N, W->K, 0, 256, 0.15f + 4.5e-5f * (float)W->N);
     if (kTiles[v].bn < 128) return QUOTA_ERR_SHAPE;
     return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, SILU_MUL>(v) : tile_kernel<A6, SILU_MUL>(v), v, kTiles[v].kernel_id,
                      qa6, sa, M, W, (f16 *)z_f16, W->N / 2, nullptr, 0, nullptr, st);
