@@ -501,8 +501,7 @@ int quota_decode_layer(const quota_layer *L, const void *x_f16,
 
 /* Kernel classes the library launches.  The GEMM is split by tile shape
  * because each shape is a separate kernel (and a separate profiler row).
- * QUOTA_K_GEMM_64X256 keeps its place, so that the others keep theirs; no
- * kernel is launched under it any more. */
+ * (QUOTA_K_GEMM_64X256: packed rows only.) */
 enum {
     QUOTA_K_QUANTIZE_ACT = 0, QUOTA_K_RMSNORM_QUANTIZE_ACT, QUOTA_K_SILU_MUL_QUANTIZE_ACT,
     QUOTA_K_GEMM_64X256, QUOTA_K_GEMM_64X128, QUOTA_K_GEMM_32X128, QUOTA_K_GEMM_32X64, QUOTA_K_GEMM_128X256,

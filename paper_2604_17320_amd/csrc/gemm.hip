@@ -565,12 +565,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 // one workgroup per CU and from five groups on (101 x 4096 x 11008 22.4 -> 19.5 us; at 237 x 4096 x 11008, 1.9 workgroups, 25.0 against
 // 24.3 in stages of four).
 #define F8_TILE_5(P, A, QK) w4a4_f8_kernel<2, 1, 4, 8, 4, P, A, QK, 2>  // 32 x 64
+// 64 x 256, packed rows only, not pinned: of two rows of blocks fewer than 128 x 256 its registers hold stages of two groups, and launches of
+// one to two workgroups per CU take a tenth to a fifth less on it than on any other (320 x 22016 x 4096 51 us on 64 x 128, 41 so; 640 x
+// 12288 x 4096 47, 41; 1600 x 4096 x 4096 43, 38; a layer's rows do better on 128 x 128).
+#define F8_PACKED_TILE(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>
 
 struct TileShape { int bm, bn, nt, kernel_id; };
-constexpr int TILES = 6, PINNED_TILES = 5;
+constexpr int TILES = 7, PINNED_TILES = 5, LAYER_TILES = 6;
 const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128, 256, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
-                             {128, 256, 256, QUOTA_K_GEMM_128X256}, {32, 64, 256, QUOTA_K_GEMM_32X64}};
+                             {128, 256, 256, QUOTA_K_GEMM_128X256}, {32, 64, 256, QUOTA_K_GEMM_32X64},
+                             {64, 256, 256, QUOTA_K_GEMM_64X256}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
@@ -586,9 +591,12 @@ f8_kernel tile_kernel(int v)
         if constexpr (E == SILU_MUL) return nullptr;         // (one block of columns per wave: never chosen)
         else return F8_TILE_3(P, false, E);
     case 4: return F8_TILE_4(P, false, E);
-    default:
+    case 5:
         if constexpr (P != A6 || E == SILU_MUL) return nullptr;
         else return F8_TILE_5(P, false, E);
+    default:
+        if constexpr (P != PACKED_INT4) return nullptr;
+        else return F8_PACKED_TILE(P, false, E);
     }
 }
 
@@ -620,8 +628,9 @@ int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set
 // Tile choice by cost models fitted to measured kernel times on this GPU (us, over weights that no cache holds), one for a layer's rows
 // (112 shapes of 40 to 11776 rows, 512 to 37888 columns and 512 to 18944 channels; the 32 x 64 tile's line, which has changed since, by 270
 // of 33 to 511 rows and of narrow layers, where the choice costs 0.6 % over the best tile of each on average, 2.3 % with the line before) and one for
-// packed rows, whose stages are shorter (387 shapes of 33 to 11776 rows; 0.2 % on average, 10 % at most, 3.1 % by a layer's: 5808 x 4096 x
-// 11008 301 us, 236 so).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
+// packed rows, whose stages are shorter and tiles others (412 shapes of 33 to 11776 rows; 0.2 % on average, 10 % at most, where two tiles tie over
+// cold weights the one that is ahead over warm ones; by a layer's, without the
+// 64 x 256 tile, 3.7 %: 5808 x 4096 x 11008 301 us, 236 so).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
 // slope * x, and more for every round of `occ` workgroups, beyond; c0 is the launch, prologue and epilogue, wg an epilogue more for every
 // workgroup beyond the first of a CU (a layer's was fitted without).
 // Tall tiles read and unpack a weight for more rows and win once the launch fills the chip; the 32-row
@@ -630,7 +639,7 @@ int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set
 int choose_tile(ActFormat acts, int M, int N, int K, int min_bn, int max_bn, float narrow = 0.0f)
 {
     struct Cost { int ch; float c0, wg; int n; float u[6], slope, round; int occ; };
-    static const Cost layer[TILES] = {
+    static const Cost layer[LAYER_TILES] = {
         {2, 5.09f, 0.0f, 6, {0.559f, 0.764f, 1.159f, 1.816f, 1.906f, 2.348f}, 0.311f, 0.255f, 3},
         {4, 4.37f, 0.0f, 6, {0.305f, 0.447f, 0.730f, 1.060f, 1.266f, 1.588f}, 0.192f, 0.174f, 3},
         {4, 3.62f, 0.0f, 4, {0.252f, 0.343f, 0.550f, 0.819f}, 0.132f, 0.150f, 3},
@@ -638,21 +647,25 @@ int choose_tile(ActFormat acts, int M, int N, int K, int min_bn, int max_bn, flo
         {2, 6.52f, 0.0f, 4, {0.840f, 1.190f, 2.370f, 2.580f}, 0.430f, 0.577f, 2},
         {8, 3.45f, 0.0f, 3, {0.148f, 0.220f, 0.360f}, 0.125f, 0.039f, 3},
     };
-    static const Cost packed[PINNED_TILES] = {
-        {2, 5.451f, 2.107f, 4, {0.768f, 1.041f, 1.756f, 2.103f}, 0.293f, 0.490f, 2},
-        {2, 3.767f, 1.160f, 5, {0.527f, 0.646f, 0.880f, 1.309f, 1.523f}, 0.227f, 0.231f, 4},
-        {4, 3.551f, 1.386f, 6, {0.378f, 0.500f, 0.663f, 0.918f, 1.045f, 1.344f}, 0.079f, 0.224f, 2},
-        {4, 3.186f, 0.795f, 6, {0.303f, 0.369f, 0.560f, 0.669f, 0.850f, 0.966f}, 0.116f, 0.168f, 5},
-        {1, 7.593f, 3.600f, 3, {1.174f, 1.471f, 2.663f}, 0.403f, 0.432f, 1},
+    static const Cost packed[TILES] = {
+        {2, 4.519f, 2.113f, 4, {0.774f, 1.038f, 1.800f, 2.136f}, 0.305f, 0.453f, 2},
+        {2, 3.669f, 1.149f, 6, {0.509f, 0.655f, 0.891f, 1.298f, 1.524f, 1.792f}, 0.219f, 0.216f, 4},
+        {4, 3.531f, 1.388f, 6, {0.422f, 0.482f, 0.668f, 0.923f, 1.048f, 1.304f}, 0.067f, 0.257f, 2},
+        {4, 3.186f, 0.791f, 6, {0.303f, 0.415f, 0.559f, 0.669f, 0.851f, 0.967f}, 0.118f, 0.160f, 5},
+        {1, 7.545f, 3.655f, 3, {1.209f, 1.531f, 2.636f}, 0.328f, 0.480f, 1},
+        {},
+        {2, 4.606f, 2.327f, 4, {0.775f, 0.977f, 1.649f, 1.918f}, 0.222f, 0.498f, 2},
     };
     const Cost *cost = acts == PACKED_INT4 ? packed : layer;
-    const int tiles = acts == A6 ? TILES : PINNED_TILES;
-    auto fits = [&](int v) { return v < tiles && kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn; };
+    auto fits = [&](int v) {
+        const bool built = v < PINNED_TILES || (v < LAYER_TILES ? acts == A6 : acts == PACKED_INT4);
+        return built && kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn;
+    };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;
     const int G = (K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     int best = -1;
     float best_t = 0.0f;
-    for (int v = 0; v < tiles; ++v) {
+    for (int v = 0; v < TILES; ++v) {
         if (!fits(v)) continue;
         const Cost &c = cost[v];
         const long wgs = (long)((M + kTiles[v].bm - 1) / kTiles[v].bm) * ((N + kTiles[v].bn - 1) / kTiles[v].bn), cus = (wgs + 255) / 256;

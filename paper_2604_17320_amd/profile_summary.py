@@ -40,7 +40,7 @@ CLASSES = [
     ("w4a4_f8_kernelILi4ELi2ELi4ELi2ELi6ELNS_9ActFormatE2ELb1E", "w4a4_gemm_other"),      # (as earlier profiles name it)
     ("w4a4_f8_kernelILi4ELi4ELi2ELi2ELi6ELb1ELb1E", "w4a4_gemm_other"),      # (as earlier profiles name it)
     ("w4a4_f8_kernelILi8ELi2ELi4E", "w4a4_gemm_128x128"),
-    ("w4a4_f8_kernelILi4ELi4ELi4E", "w4a4_gemm_64x256"),                     # (as earlier profiles name it)
+    ("w4a4_f8_kernelILi4ELi4ELi4E", "w4a4_gemm_64x256"),                     # (packed rows)
     ("w4a4_f8_kernelILi4ELi2ELi4E", "w4a4_gemm_64x128"),
     ("w4a4_f8_kernelILi4ELi4ELi2E", "w4a4_gemm_64x128"),                     # (as earlier profiles name it)
     ("w4a4_f8_kernelILi2ELi2ELi4E", "w4a4_gemm_32x128"),

@@ -236,6 +236,22 @@ def test_w4a4_gemm_every_tile_bit_exact(qb, tile, pinned_gemm):
         assert np.array_equal(host(y).view(np.uint16), y_ref.view(np.uint16)), (tile, M, N, K)
 
 
+@pytest.mark.parametrize("M,N,K", [(257, 21952, 416), (641, 10944, 160), (513, 12224, 1056)])
+def test_w4a4_gemm_on_the_tile_of_packed_rows(qb, M, N, K):
+    """The 64 x 256 tile, which only the choice takes: ragged rows, columns that end inside a tile, two to nine groups, the last one
+    ragged, in stages of two; with a residual and without."""
+    from paper_2604_17320_amd.model import PackedLinear
+    qa, sa, qw, sw, res = _gemm_case(M, N, K, 24)
+    lin, qad, sad = PackedLinear.from_codes(dev(qw), dev(sw)), dev(_pack4(qa)), dev(sa)
+    y, yr = (torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    qb.quota_profile_begin(8)
+    qb.quota_w4a4_gemm(qad, sad, M, lin.desc, y, N)
+    qb.quota_w4a4_gemm(qad, sad, M, lin.desc, yr, N, dev(res), N)
+    assert qb.quota_profile_collect()["w4a4_gemm_64x256"]["launches"] == 2
+    assert np.array_equal(host(y).view(np.uint16), oracle.w4a4_gemm(qa, sa, qw, sw).view(np.uint16))
+    assert np.array_equal(host(yr).view(np.uint16), oracle.w4a4_gemm(qa, sa, qw, sw, residual=res).view(np.uint16))
+
+
 @pytest.mark.parametrize("M", [1, 16, 17, 45, 160])
 def test_w4a4_gemm_with_scales_at_an_odd_halfword(qb, M):
     """Weight scales that start between two dwords: the bits of the aligned call, output and integer sums."""

@@ -91,7 +91,7 @@ def test_profile_summary_classes_of_the_built_gemm_tiles():
         want = "w4a4_gemm_other" if sums else f"w4a4_gemm_{16 * rt}x{16 * ct * nw}"
         assert ps.classify(name) == want, name
         seen.add(want)
-    assert seen == {"w4a4_gemm_other"} | {f"w4a4_gemm_{t}" for t in ("128x128", "64x128", "32x128", "32x64", "128x256")}
+    assert seen == {"w4a4_gemm_other"} | {f"w4a4_gemm_{t}" for t in ("128x128", "64x128", "32x128", "32x64", "128x256", "64x256")}
 
 
 def test_profile_summary_stats_table(tmp_path, capsys):
