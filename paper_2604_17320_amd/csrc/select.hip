@@ -2,12 +2,11 @@
 // One workgroup per sequence: a chain of small steps, bound by their latencies.  Order statistics and the top-k
 // threshold come from an exact radix select on order-preserving uint32 keys, 8 bits a pass from the highest bit
 // in which any two keys differ (a float key's top byte is nearly constant: taken as the first digit, all lanes of
-// a wave add to the same few counters, one after the other).  All waves take part, with their keys in
-// registers: four per metric, both percentile bounds in the same passes, then all sixteen for the top-k; the
-// counters are integers, so the result does not depend on execution order.  576 / 2880 tokens (32 / 40
-// heads): 25 / 113 us with one wave per bound and per top-k and the head means of the attention cues taken here,
-// 10 / 19 us so, with the head means taken before it.  A select ends as soon as at most 64 keys share a rank's digits: one
-// wave ranks those (104 / 576 / 2880 tokens 8.6 / 9.7 / 19.1 -> 7.0 / 9.0 / 18.8 us).
+// a wave add to the same few counters, one after the other); the counters are integers, so the result does not depend
+// on execution order.  Up to 1024 tokens each select is one wave's, without a barrier (small_score_topk_kernel).  Beyond, all
+// waves take part, with their keys in registers: four per metric, both percentile bounds in the same passes, then all
+// sixteen for the top-k; a select ends as soon as at most 64 keys share a rank's digits, which one wave ranks (2880 tokens
+// 18.8 us; one wave per bound and per top-k with the head means of the attention cues took 113).
 #include "common.h"
 #include "internal.h"
 #include "prefetch.h"
@@ -198,6 +197,18 @@ __device__ __forceinline__ float robust_unit(float m, float lo, float hi)
     return fminf(fmaxf(v, 0.0f), 1.0f);
 }
 
+// Eq. 8, in the order it is written
+__device__ __forceinline__ float fuse_score(const quota_score_params &p, float g0, float g1, float g2, float g3)
+{
+    float a = p.w_m * g0;
+    float c = p.w_c * g1;
+    float s = p.w_s * g2;
+    float rr = p.w_r * g3;
+    float acc = a + c;
+    acc = acc + s;
+    return acc + rr;
+}
+
 struct MetricSrc {
     const float *sumsq, *ressq, *cm_inter, *cm_intra;
     size_t osq, ocm;        // offsets of this sequence in the sumsq/ressq and cm arrays
@@ -242,13 +253,7 @@ __device__ void score_phase(const MetricSrc &src, int B, int Nv, int b, const qu
             float g1 = robust_unit(key_float(mk[1 * cap + i]), lohi[2], lohi[3]);
             float g2 = robust_unit(key_float(mk[2 * cap + i]), lohi[4], lohi[5]);
             float g3 = robust_unit(key_float(mk[3 * cap + i]), lohi[6], lohi[7]);
-            float a = p.w_m * g0;
-            float c = p.w_c * g1;
-            float s = p.w_s * g2;
-            float rr = p.w_r * g3;
-            float acc = a + c;
-            acc = acc + s;
-            acc = acc + rr;
+            const float acc = fuse_score(p, g0, g1, g2, g3);
             size_t o = (size_t)b * Nv + i;
             score[o] = acc;
             key[r] = acc != acc ? 0u : float_key(acc);
@@ -344,6 +349,198 @@ __global__ __launch_bounds__(SCORE_THREADS) void score_topk_kernel(MetricSrc src
     topk_phase<PER>(key, Nv, k, out, hist, range, (int *)mk);
 }
 
+// ---- up to SCORE_THREADS tokens: each select by a wave of its own, whose 64 lanes hold all keys (key i in register i / 64 of lane
+// i % 64) and whose counters no other wave touches, so that it needs no barrier: eight waves find the percentile bounds, one the
+// top-k.
+constexpr int WAVE_KEYS = SCORE_THREADS / 64;
+
+// run(r) for the registers that hold keys, four at a time
+template <typename RUN>
+__device__ __forceinline__ void for_keys(int n, RUN run)
+{
+#pragma unroll
+    for (int r4 = 0; r4 < WAVE_KEYS; r4 += 4)
+        if (64 * r4 < n)
+#pragma unroll
+            for (int r = r4; r < r4 + 4; ++r) run(r);
+}
+// load(i): key i
+template <typename LOAD>
+__device__ __forceinline__ void wave_keys(int n, uint32_t (&key)[WAVE_KEYS], LOAD load)
+{
+    for_keys(n, [&](int r) { key[r] = load(min(64 * r + (int)(threadIdx.x & 63), n - 1)); });
+}
+// The rank-th smallest (0-based) of a wave's n keys; h: 256 ints of LDS.
+__device__ __forceinline__ uint32_t wave_select(const uint32_t (&key)[WAVE_KEYS], int n, int rank, int *h)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t kmax = 0, kinv = 0;                     // (past the last key its copies)
+    for_keys(n, [&](int r) {
+        kmax = max(kmax, key[r]);
+        kinv = max(kinv, ~key[r]);
+    });
+    kmax = wave_umax(kmax);
+    const uint32_t kmin = ~wave_umax(kinv);
+    if (kmin == kmax) return kmin;
+    int bits = 32 - __clz((int)(kmin ^ kmax)), left = rank;
+    uint32_t mask = bits == 32 ? 0u : ~0u << bits, prefix = kmin & mask;
+    while (true) {
+        const int width = min(8, bits), shift = bits - width;
+        const uint32_t digits = (1u << width) - 1;
+        *reinterpret_cast<i32x4 *>(h + 4 * lane) = i32x4{0, 0, 0, 0};
+        __builtin_amdgcn_wave_barrier();             // (a wave's accesses to LDS stay in their order)
+        for_keys(n, [&](int r) {
+            if ((key[r] & mask) == prefix && 64 * r + lane < n) atomicAdd(&h[(key[r] >> shift) & digits], 1);
+        });
+        __builtin_amdgcn_wave_barrier();
+        const i32x4 c = *reinterpret_cast<const i32x4 *>(h + 4 * lane);
+        __builtin_amdgcn_wave_barrier();
+        const int incl = wave_incl_scan(c[0] + c[1] + c[2] + c[3]);
+        // the first lane whose counters reach past the rank, and the counter there
+        const int from = __builtin_ctzll(__ballot(left < incl));
+        const int c0 = __builtin_amdgcn_readlane(c[0], from), c1 = __builtin_amdgcn_readlane(c[1], from),
+                  c2 = __builtin_amdgcn_readlane(c[2], from), c3 = __builtin_amdgcn_readlane(c[3], from);
+        left -= __builtin_amdgcn_readlane(incl, from) - (c0 + c1 + c2 + c3);
+        int digit = 4 * from, keys = c0;
+        if (left >= c0) { left -= c0; ++digit; keys = c1;
+            if (left >= c1) { left -= c1; ++digit; keys = c2;
+                if (left >= c2) { left -= c2; ++digit; keys = c3; } } }
+        prefix |= (uint32_t)digit << shift;
+        mask |= digits << shift;
+        bits = shift;
+        if (bits == 0) return prefix;
+        if (keys == 1) {                             // mostly after one or two of four passes
+            uint32_t found = prefix;
+            for_keys(n, [&](int r) {
+                const unsigned long long in = __ballot((key[r] & mask) == prefix);
+                if (in) found = (uint32_t)__builtin_amdgcn_readlane((int)key[r], __builtin_ctzll(in));
+            });
+            return found;
+        }
+    }
+}
+
+// first + the lanes below this one in a ballot
+__device__ __forceinline__ int count_before(unsigned long long ballot, int first)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ballot, first));
+}
+// One wave: indices of the K largest of the Nv keys, ties to the lower index, ascending; 0 < K < Nv.
+__device__ __forceinline__ void wave_topk(const uint32_t (&key)[WAVE_KEYS], int Nv, int K, int32_t *__restrict__ out, int *h)
+{
+    const int lane = threadIdx.x & 63;
+    const uint32_t thr = wave_select(key, Nv, Nv - K, h);       // K-th largest
+    int need = K;                                    // ties taken, lowest indices first
+    for_keys(Nv, [&](int r) { need -= __popcll(__ballot(key[r] > thr && 64 * r + lane < Nv)); });
+    int gb = 0, eb = 0;                              // above, at the threshold so far
+    for_keys(Nv, [&](int r) {
+        const bool live = 64 * r + lane < Nv, above = live && key[r] > thr, at = live && key[r] == thr;
+        const unsigned long long gt = __ballot(above), eq = __ballot(at);
+        const int g = count_before(gt, gb), e = count_before(eq, eb);
+        if (above || (at && e < need)) out[g + min(e, need)] = 64 * r + lane;
+        gb += __popcll(gt);
+        eb += __popcll(eq);
+    });
+}
+
+// score_topk_kernel for up to SCORE_THREADS tokens: one by each thread, beside the eight bounds by a wave each.  Three barriers in
+// front of the output and two around the counts in it, where a select by all waves takes three for every pass: 64 / 256 / 576 / 1000 tokens 6.7 /
+// 7.6 / 8.7 / 10.0 -> 4.5 / 5.2 / 7.0 / 8.8 us (with the output by the one wave too 576 tokens 7.8).
+template <typename PRE>
+__global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(MetricSrc src, long stride_sq, int B, int Nv, quota_score_params p,
+                                                                         float *__restrict__ score, float *__restrict__ normed, int K,
+                                                                         int32_t *__restrict__ keep_idx, PRE pre)
+{
+    if ((int)blockIdx.x >= B) {
+        prefetch<SCORE_THREADS>(pre, blockIdx.x - B, gridDim.x - B);
+        return;
+    }
+    __shared__ __align__(16) int counters[8][256];
+    __shared__ float lohi[8];
+    __shared__ uint32_t scores[SCORE_THREADS], threshold;
+    __shared__ int counts[SCORE_WAVES];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), b = blockIdx.x, at = min(tid, Nv - 1);
+    src.osq = (size_t)b * stride_sq;
+    src.ocm = (size_t)b * Nv;
+    float m[4] = {src.sumsq[src.osq + at], src.cm_inter[src.ocm + at], src.cm_intra[src.ocm + at], src.ressq[src.osq + at]};
+    if (wave < 8) {                                  // metric wave / 2, one of its bounds
+        const float *from = wave < 2 ? src.sumsq + src.osq : wave < 4 ? src.cm_inter + src.ocm
+                            : wave < 6 ? src.cm_intra + src.ocm : src.ressq + src.osq;
+        // The squares order as their roots do (the root is rounded to nearest, which keeps order), so that only the bound's root is
+        // taken; not where a caller hands in a negative number, whose root is none.
+        bool roots = wave < 2 || wave >= 6, negative = false;
+        uint32_t key[WAVE_KEYS];
+        wave_keys(Nv, key, [&](int i) { return __float_as_uint(from[i]); });
+        for_keys(Nv, [&](int r) { negative = negative || __uint_as_float(key[r]) < 0.0f; });
+        if (roots && __ballot(negative)) {
+            roots = false;
+            for_keys(Nv, [&](int r) { key[r] = __float_as_uint(sqrtf(__uint_as_float(key[r]))); });
+        }
+        for_keys(Nv, [&](int r) { key[r] = float_key(__uint_as_float(key[r])); });
+        const int pct = wave & 1 ? p.pct_hi : p.pct_lo;
+        float bound = key_float(wave_select(key, Nv, (pct * (Nv - 1) + 50) / 100, counters[wave]));
+        if (roots) bound = sqrtf(bound);
+        if ((tid & 63) == 0) lohi[wave] = bound;
+    }
+    __syncthreads();
+    if (tid < Nv) {
+        m[0] = sqrtf(m[0]);                          // m_mag
+        m[3] = sqrtf(m[3]);                          // m_res
+        float g[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] = robust_unit(m[i] + 0.0f, lohi[2 * i], lohi[2 * i + 1]);
+        const float acc = fuse_score(p, g[0], g[1], g[2], g[3]);
+        const size_t o = (size_t)b * Nv + tid;
+        score[o] = acc;
+        scores[tid] = acc != acc ? 0u : float_key(acc);          // NaN ranks lowest
+        if (normed)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) normed[i * ((size_t)B * Nv) + o] = g[i];
+    }
+    if (K < 0) return;
+    const int k = K < Nv ? K : Nv;
+    int32_t *out = keep_idx + (size_t)b * k;
+    if (k == Nv && tid < Nv) out[tid] = tid;
+    __syncthreads();
+    if (k == 0 || k == Nv) return;
+    if (wave == 0) {
+        uint32_t key[WAVE_KEYS];
+        wave_keys(Nv, key, [&](int i) { return scores[i]; });
+        const uint32_t thr = wave_select(key, Nv, Nv - k, counters[0]);
+        if (tid == 0) threshold = thr;
+    }
+    __syncthreads();
+    // a wave's tokens above and at the threshold, behind those of the waves before it
+    const uint32_t mine = scores[at], thr = threshold;
+    const bool above = tid < Nv && mine > thr, ties = tid < Nv && mine == thr;
+    const unsigned long long gt = __ballot(above), eq = __ballot(ties);
+    if ((tid & 63) == 0) counts[wave] = __popcll(gt) << 16 | __popcll(eq);
+    __syncthreads();
+    const int n = (tid & 63) < SCORE_WAVES ? counts[tid & 63] : 0, upto = wave_incl_scan(n);
+    const int before = __builtin_amdgcn_readlane(upto - n, wave), need = k - (__builtin_amdgcn_readlane(upto, 63) >> 16);
+    const int g = count_before(gt, before >> 16), e = count_before(eq, before & 0xFFFF);
+    if (above || (ties && e < need)) out[g + min(e, need)] = tid;          // (ties: lowest indices first)
+}
+
+// One wave per sequence of up to SCORE_THREADS tokens
+__global__ __launch_bounds__(64) void small_topk_kernel(const float *__restrict__ score, int Nv, int K, int32_t *__restrict__ keep_idx)
+{
+    __shared__ __align__(16) int counters[256];
+    const int b = blockIdx.x;
+    int32_t *out = keep_idx + (size_t)b * K;
+    if (K >= Nv) {          // host passes K <= Nv; K == Nv keeps every token
+        for (int i = threadIdx.x; i < Nv; i += 64) out[i] = i;
+        return;
+    }
+    uint32_t key[WAVE_KEYS];
+    wave_keys(Nv, key, [&](int i) { return __float_as_uint(score[(size_t)b * Nv + i]); });
+    for_keys(Nv, [&](int r) {
+        const float f = __uint_as_float(key[r]);
+        key[r] = f != f ? 0u : float_key(f);         // NaN ranks lowest
+    });
+    wave_topk(key, Nv, K, out, counters);
+}
+
 template <int PER>
 __global__ __launch_bounds__(SCORE_THREADS) void topk_kernel(const float *__restrict__ score, int Nv, int K,
                                                              int32_t *__restrict__ keep_idx)
@@ -371,6 +568,15 @@ __global__ __launch_bounds__(SCORE_THREADS) void topk_kernel(const float *__rest
 int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const quota_score_params &p,
                       float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st, PrefetchList *weights = nullptr)
 {
+    const auto share = weights ? weights->take(B, 7.0f, 4.0f) : PrefetchList::Share{};
+    if (Nv <= SCORE_THREADS) {
+        share.run([&](auto pre) {
+            small_score_topk_kernel<<<dim3(B + share.wgs), dim3(SCORE_THREADS), 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K,
+                                                                                        keep_idx, pre);
+        });
+        QUOTA_RETURN_IF_LAUNCH_FAILED();
+        return QUOTA_OK;
+    }
     const int cap = (Nv + 63) & ~63;
     const size_t lds = ((size_t)4 * cap + SELECT_HIST + SELECT_RANGE + 8) * sizeof(uint32_t);
     if (Nv > 2 * SCORE_THREADS) {          // the widest instantiations: up to 153 KB, above a launch's default 64 KB
@@ -387,11 +593,9 @@ int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const
             granted[dev] = true;
         }
     }
-    const auto share = weights ? weights->take(B, 7.0f, 4.0f) : PrefetchList::Share{};
     share.run([&](auto pre) {
         using P = decltype(pre);
-        auto kernel = Nv <= SCORE_THREADS ? score_topk_kernel<1, P>
-                      : Nv <= 3 * SCORE_THREADS ? score_topk_kernel<3, P> : score_topk_kernel<MAXV / SCORE_THREADS, P>;
+        auto kernel = Nv <= 3 * SCORE_THREADS ? score_topk_kernel<3, P> : score_topk_kernel<MAXV / SCORE_THREADS, P>;
         kernel<<<dim3(B + share.wgs), dim3(SCORE_THREADS), lds, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, cap, pre);
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -464,8 +668,8 @@ extern "C" int quota_topk_prune(const float *score, int B, int Nv, int K, int32_
     int k = K < Nv ? K : Nv;
     if (k == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_TOPK_PRUNE, 0, 4.0 * B * Nv + 4.0 * B * k, (hipStream_t)stream);
-    auto kernel = Nv <= SCORE_THREADS ? topk_kernel<1> : topk_kernel<MAXV / SCORE_THREADS>;
-    kernel<<<dim3(B), dim3(SCORE_THREADS), 0, (hipStream_t)stream>>>(score, Nv, k, keep_idx);
+    if (Nv <= SCORE_THREADS) small_topk_kernel<<<dim3(B), dim3(64), 0, (hipStream_t)stream>>>(score, Nv, k, keep_idx);
+    else topk_kernel<MAXV / SCORE_THREADS><<<dim3(B), dim3(SCORE_THREADS), 0, (hipStream_t)stream>>>(score, Nv, k, keep_idx);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

@@ -507,3 +507,20 @@ def test_long_top_k_beside_the_fetch(qb):
     score = oracle.score(got["sumsq"], got["ressq"], got["cm_inter"], got["cm_intra"])
     assert np.array_equal(got["score"].view(np.uint32), score.view(np.uint32))
     assert np.array_equal(got["keep_idx"], oracle.topk(score, 77))
+
+
+@pytest.mark.parametrize("Nv", [1, 2, 63, 64, 65, 256, 257, 576, 1023, 1024, 1025])
+def test_selection_of_tied_tokens(qb, Nv):
+    """Visual tokens that are copies of nine, under flat cues: most scores are tied, and the threshold falls among them.  Around the sizes where
+    a wave's registers of keys and the kernel change."""
+    shape = wl.Shape("ties", d=512, H=8, F=1376, layers=1, B=2, Nv=Nv, Nt=9, n_outlier=4, vis_begin=3)
+    W, L, cos, sin = build_layer(shape, 13)
+    r = wl.rng(13, "ties", Nv)
+    x = wl.hidden_state(shape, 13).reshape(2, shape.N, shape.d).copy()
+    x[:, 3:3 + Nv] = x[:, 3:4 + min(Nv - 1, 8)][:, r.integers(0, min(Nv, 9), Nv)]
+    flat = np.full((2, Nv), 0.5, np.float32)
+    for K in sorted({1, Nv // 3, Nv - 1, Nv} - {0}):
+        got = run_gpu(qb, L, shape, x.reshape(-1, shape.d), wl.positions(shape), K, dict(cm_inter=flat, cm_intra=flat))
+        score = oracle.score(got["sumsq"], got["ressq"], flat, flat)
+        assert np.array_equal(got["score"].view(np.uint32), score.view(np.uint32)), K
+        assert np.array_equal(got["keep_idx"], oracle.topk(score, K)), K

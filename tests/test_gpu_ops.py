@@ -454,6 +454,21 @@ def test_score_tokens_bit_exact(qb, B, Nv):
         assert np.array_equal(host(sc), sc_ref)
 
 
+@pytest.mark.parametrize("Nv", [1, 64, 65, 250, 1024, 1025])
+def test_score_tokens_of_odd_metrics(qb, Nv):
+    """Infinities, signed zeros, denormals and huge numbers among the metrics; squares whose roots are equal though they are not."""
+    ss, rs, ci, cv = _metrics(2, Nv, 63)
+    odd = np.array([0.0, -0.0, 1e-45, 3e38, np.inf, 1e-38], np.float32)
+    for m in (ss, rs, ci, cv):
+        m[0, : min(Nv, 6)] = odd[: min(Nv, 6)]
+    ss[1] = np.float32(4.0) + np.arange(Nv, dtype=np.float32)[::-1] * np.float32(2.0 ** -21)
+    sc_ref, g_ref = oracle.score(ss, rs, ci, cv, want_normed=True)
+    sc = torch.empty((2, Nv), dtype=torch.float32, device="cuda")
+    g = torch.empty((4, 2, Nv), dtype=torch.float32, device="cuda")
+    qb.quota_score_tokens(dev(ss), dev(rs), dev(ci), dev(cv), 2, Nv, qb.quota_score_params_default(), sc, g)
+    assert np.array_equal(host(g), g_ref, equal_nan=True) and np.array_equal(host(sc), sc_ref, equal_nan=True)
+
+
 def test_score_tokens_from_hidden(qb):
     shape = wl.CONFIGS[0]
     x = wl.hidden_state(shape, 7)
