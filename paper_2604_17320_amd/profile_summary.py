@@ -56,7 +56,9 @@ CLASSES = [
     ("attn_fwd_kernel", "attention_fwd"),
     ("colmass_reduce_kernel", "attention_colmass_reduce"),
     ("colmass_kernel", "attention_colmass"),
+    ("small_score_topk_kernel", "score_tokens"),
     ("score_topk_kernel", "score_tokens"),
+    ("small_topk_kernel", "topk_prune"),
     ("topk_kernel", "topk_prune"),
     ("compact_rows_kernel", "compact_rows"),
     ("decode_attention_kernel", "attention_decode"),
