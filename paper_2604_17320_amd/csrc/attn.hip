@@ -26,6 +26,7 @@
 #include "gemm_common.h"
 #include "ldscopy.h"
 #include "prefetch.h"
+#include "headmeans.h"
 
 namespace {
 
@@ -308,35 +309,19 @@ __global__ __launch_bounds__(256, 3) void colmass_kernel(
     if (key_ok && hl == 0) partial[((size_t)b * H + h) * Nv + (key - vis_begin)] = make_float2(acc_txt, acc_vis);
 }
 
-// Head means of the masses, [B][H][Nv] -> [B][Nv]: 64 keys of a sequence per workgroup, a quad of lanes per key.  Lane hq sums
-// heads [hq H/4 .. ) in head order, the four sums are combined as (s0 + s1) + (s2 + s3), then * (1/H).  A launch of its own:
+// Head means of the masses, [B][H][Nv] -> [B][Nv]: 64 keys of a sequence per workgroup, a quad of lanes per key.  A launch of its own:
 // left to the last workgroup of a key block in the pass above, behind a count that releases and acquires, it
 // costs more (forward, cues and means: 16 x 704 tokens, 32 heads 262 us against 196; 1 x 640 34.8 against 34.2), since
-// every release writes back the L2 of its XCD.
+// every release writes back the L2 of its XCD.  Where the masses are few a layer leaves the means to the kernel that scores them (select.hip).
 __global__ __launch_bounds__(256) void colmass_reduce_kernel(
     const float2 *__restrict__ partial, int H, int Nv, float *__restrict__ cm_inter, float *__restrict__ cm_intra)
 {
     const int n64 = (Nv + 63) / 64, b = blockIdx.x / n64, i = blockIdx.x % n64 * 64 + (threadIdx.x >> 2), hq = threadIdx.x & 3;
-    const int hper = (H + 3) / 4, h_lo = hq * hper, h_hi = min(h_lo + hper, H);
     const float invH = 1.0f / (float)H;
-    const float2 *pp = partial + (size_t)b * H * Nv + min(i, Nv - 1);
-    float st = 0.0f, sv = 0.0f;
-    for (int h0 = h_lo; h0 < h_hi; h0 += 8) {
-        float2 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = pp[(size_t)min(h0 + u, h_hi - 1) * Nv];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (h0 + u < h_hi) {
-                st += v[u].x;
-                sv += v[u].y;
-            }
-    }
-    st += __shfl_xor(st, 1, 64); sv += __shfl_xor(sv, 1, 64);
-    st += __shfl_xor(st, 2, 64); sv += __shfl_xor(sv, 2, 64);
+    const float2 sums = head_sums(partial + (size_t)b * H * Nv, H, Nv, i, hq);
     if (i < Nv && hq == 0) {
-        if (cm_inter) cm_inter[(size_t)b * Nv + i] = st * invH;
-        if (cm_intra) cm_intra[(size_t)b * Nv + i] = sv * invH;
+        if (cm_inter) cm_inter[(size_t)b * Nv + i] = sums.x * invH;
+        if (cm_intra) cm_intra[(size_t)b * Nv + i] = sums.y * invH;
     }
 }
 
@@ -364,7 +349,8 @@ extern "C" size_t quota_attention_workspace_bytes(int B, int N, int H, int dh)
 
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st, PrefetchList *weights)
+                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st, PrefetchList *weights,
+                             quota_cue_masses *masses)
 {
     if (!q_f16 || !khat_f16 || !vhat_f16 || !o_f16 || !ws) return QUOTA_ERR_NULL;
     if (B <= 0 || N < 0 || H <= 0 || Hkv <= 0 || vis_begin < 0 || Nv < 0 || vis_begin + Nv > N)
@@ -403,6 +389,10 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
             kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, (int)n2, pre);
         });
         QUOTA_RETURN_IF_LAUNCH_FAILED();
+        if (masses) {
+            *masses = {w.partial, H, cm_inter, cm_intra};
+            return QUOTA_OK;
+        }
         colmass_reduce_kernel<<<dim3((unsigned)((Nv + 63) / 64) * B), blk, 0, st>>>(w.partial, H, Nv, cm_inter, cm_intra);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
     }
@@ -415,7 +405,7 @@ extern "C" int quota_attention_prefill_gqa(const void *q_f16, const void *khat_f
                                            float *cm_intra, void *ws, void *stream)
 {
     return quota_internal_attention(q_f16, khat_f16, vhat_f16, B, N, H, Hkv, dh, vis_begin, Nv, o_f16, cm_inter, cm_intra,
-                                    ws, (hipStream_t)stream, nullptr);
+                                    ws, (hipStream_t)stream, nullptr, nullptr);
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include "../../include/quota.h"
 #include "prefetch.h"
+#include "headmeans.h"
 
 // score kernel with a separate sequence stride for the sumsq/ressq arrays, so
 // the layer can pass the per-row side outputs of the quantizer directly
@@ -11,16 +12,20 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
                          const float *cm_inter, const float *cm_intra, int B, int Nv,
                          const quota_score_params *p, float *score, float *normed, hipStream_t st);
 
-// score + top-k of the min(K, Nv) best tokens in one launch
+// score + top-k of the min(K, Nv) best tokens in one launch.  masses: the cues' head means are made there too, in the place
+// of cm_inter and cm_intra, and left where it says; only where quota_score_takes_means allows it.
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
                               const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
-                              hipStream_t st, PrefetchList *weights);
+                              hipStream_t st, PrefetchList *weights, const quota_cue_masses *masses);
+bool quota_score_takes_means(int Nv, int H);
 
-// attention and, if cm_inter or cm_intra is given, the cue pass with its head means [B][Nv]
+// attention and, if cm_inter or cm_intra is given, the cue pass with its head means [B][Nv]; masses: without the means, for whom they are
+// left then
 int quota_internal_attention(const void *q_f16, const void *khat_f16, const void *vhat_f16, int B,
                              int N, int H, int Hkv, int dh, int vis_begin, int Nv, void *o_f16,
-                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st, PrefetchList *weights);
+                             float *cm_inter, float *cm_intra, void *ws, hipStream_t st, PrefetchList *weights,
+                             quota_cue_masses *masses);
 
 struct quota_compact_args {
     int B, N, vis_begin, Nv, k_keep, n_keep, d, dkv;      // dkv: width of a K or V row (Hkv * dh)

@@ -234,17 +234,21 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     for (const quota_weights *p : {&L->o, &L->gu, &L->down}) weights.add(p->scales, quota_weights_scale_bytes(p->N, p->K));
     for (const quota_weights *p : {&L->o, &L->gu, &L->down}) weights.add(p->packed, quota_weights_packed_bytes(p->N, p->K));
     PrefetchList *fetch = Mk > 0 && weights.worth(M) ? &weights : nullptr;
+    // few masses: their head means are left to the score kernel
+    const bool inject_cm = t->inject_cm_inter && t->inject_cm_intra;
+    const bool leave_means = score && !inject_cm && quota_score_takes_means(Nv, H);
+    quota_cue_masses masses = {};
     TRY(quota_internal_attention(w.q_rot, w.khat, w.vhat, B, N, H, Hkv, dh, vb, Nv, w.o,
-                                 score ? w.cm_inter : nullptr, score ? w.cm_intra : nullptr, w.attn_ws, st, fetch));
+                                 score ? w.cm_inter : nullptr, score ? w.cm_intra : nullptr, w.attn_ws, st, fetch,
+                                 leave_means ? &masses : nullptr));
     TRY(dump(t->o, w.o, (size_t)M * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
-    const bool inject_cm = t->inject_cm_inter && t->inject_cm_intra;
 
     // Eq. 6-9: cues -> G -> fused score -> top-K_l over the visual tokens (candidate layers only)
     if (score) {
         TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, inject_cm ? t->inject_cm_inter : w.cm_inter,
                                       inject_cm ? t->inject_cm_intra : w.cm_intra, B, Nv, p, w.score, k_keep,
-                                      w.keep_idx, st, fetch));
+                                      w.keep_idx, st, fetch, leave_means ? &masses : nullptr));
         if (t->sumsq || t->ressq) {
             long n = (long)B * Nv;
             dim3 g((unsigned)((n + 255) / 256)), blk(256);

@@ -9,7 +9,9 @@
 // 18.8 us; one wave per bound and per top-k with the head means of the attention cues took 113).
 #include "common.h"
 #include "internal.h"
+#include <type_traits>
 #include "prefetch.h"
+#include "headmeans.h"
 
 namespace {
 
@@ -446,10 +448,11 @@ __device__ __forceinline__ void wave_topk(const uint32_t (&key)[WAVE_KEYS], int 
 // score_topk_kernel for up to SCORE_THREADS tokens: one by each thread, beside the eight bounds by a wave each.  Three barriers in
 // front of the output and two around the counts in it, where a select by all waves takes three for every pass: 64 / 256 / 576 / 1000 tokens 6.7 /
 // 7.6 / 8.7 / 10.0 -> 4.5 / 5.2 / 7.0 / 8.8 us (with the output by the one wave too 576 tokens 7.8).
-template <typename PRE>
+struct MeansThere {};            // (the cues' head means are in src)
+template <typename MEANS, typename PRE>
 __global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(MetricSrc src, long stride_sq, int B, int Nv, quota_score_params p,
                                                                          float *__restrict__ score, float *__restrict__ normed, int K,
-                                                                         int32_t *__restrict__ keep_idx, PRE pre)
+                                                                         int32_t *__restrict__ keep_idx, MEANS cues, PRE pre)
 {
     if ((int)blockIdx.x >= B) {
         prefetch<SCORE_THREADS>(pre, blockIdx.x - B, gridDim.x - B);
@@ -462,10 +465,27 @@ __global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(MetricS
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), b = blockIdx.x, at = min(tid, Nv - 1);
     src.osq = (size_t)b * stride_sq;
     src.ocm = (size_t)b * Nv;
-    float m[4] = {src.sumsq[src.osq + at], src.cm_inter[src.ocm + at], src.cm_intra[src.ocm + at], src.ressq[src.osq + at]};
+    constexpr bool TAKES_MEANS = std::is_same<MEANS, quota_cue_masses>::value;
+    __shared__ float means[2][TAKES_MEANS ? SCORE_THREADS : 1];
+    const float *inter = TAKES_MEANS ? means[0] : src.cm_inter + src.ocm, *intra = TAKES_MEANS ? means[1] : src.cm_intra + src.ocm;
+    float m[4] = {src.sumsq[src.osq + at], 0.0f, 0.0f, src.ressq[src.osq + at]};
+    if constexpr (TAKES_MEANS) {
+        const float invH = 1.0f / (float)cues.H;
+        for (int i = tid >> 2; i < Nv; i += SCORE_THREADS / 4) {         // (the lanes of a quad stay together)
+            const float2 sums = head_sums(cues.partial + (size_t)b * cues.H * Nv, cues.H, Nv, i, tid & 3);
+            if ((tid & 3) == 0) {
+                means[0][i] = sums.x * invH;
+                means[1][i] = sums.y * invH;
+                cues.cm_inter[src.ocm + i] = sums.x * invH;
+                cues.cm_intra[src.ocm + i] = sums.y * invH;
+            }
+        }
+        __syncthreads();
+    }
+    m[1] = inter[at];
+    m[2] = intra[at];
     if (wave < 8) {                                  // metric wave / 2, one of its bounds
-        const float *from = wave < 2 ? src.sumsq + src.osq : wave < 4 ? src.cm_inter + src.ocm
-                            : wave < 6 ? src.cm_intra + src.ocm : src.ressq + src.osq;
+        const float *from = wave < 2 ? src.sumsq + src.osq : wave < 4 ? inter : wave < 6 ? intra : src.ressq + src.osq;
         // The squares order as their roots do (the root is rounded to nearest, which keeps order), so that only the bound's root is
         // taken; not where a caller hands in a negative number, whose root is none.
         bool roots = wave < 2 || wave >= 6, negative = false;
@@ -566,13 +586,15 @@ __global__ __launch_bounds__(SCORE_THREADS) void topk_kernel(const float *__rest
 // Launches the score (+ top-k) kernel with the LDS its Nv needs: up to 153 KB at 8192 tokens, which
 // is above the default limit of a launch and has to be granted once per device.
 int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const quota_score_params &p,
-                      float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st, PrefetchList *weights = nullptr)
+                      float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st, PrefetchList *weights = nullptr,
+                      const quota_cue_masses *masses = nullptr)
 {
     const auto share = weights ? weights->take(B, 7.0f, 4.0f) : PrefetchList::Share{};
     if (Nv <= SCORE_THREADS) {
         share.run([&](auto pre) {
-            small_score_topk_kernel<<<dim3(B + share.wgs), dim3(SCORE_THREADS), 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K,
-                                                                                        keep_idx, pre);
+            const dim3 grid(B + share.wgs), block(SCORE_THREADS);
+            if (masses) small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, *masses, pre);
+            else small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, MeansThere{}, pre);
         });
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
@@ -626,11 +648,16 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
     return launch_score_topk(src, stride_sq, B, Nv, *p, score, normed, -1, nullptr, st);
 }
 
+// Whether the kernel above makes the cues' head means itself: one CU then reads all masses of a sequence, at some 15 KB a us, where their
+// own launch takes 2.4 us (8 heads) to 4.7.  Up to 80 KB it is ahead, one layer of a replayed stack, us less: 512 channels, 8 heads,
+// 64 tokens 0.7, 256 0.8, 576 0.2; 7B shape, 32 heads, 101 tokens 3.2, 160 2.9, 256 1.7, 300 0.0, 320 -0.7, 576 -5.6; 13B shape, 40 heads, 250 tokens 1.3.
+bool quota_score_takes_means(int Nv, int H) { return Nv <= SCORE_THREADS && (long)Nv * H <= 10240; }
+
 // score + top-k in one launch (the layer's path)
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
                               const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
-                              hipStream_t st, PrefetchList *weights)
+                              hipStream_t st, PrefetchList *weights, const quota_cue_masses *masses)
 {
     if (!sumsq || !ressq || !p || !score || !keep_idx || !cm_inter || !cm_intra) return QUOTA_ERR_NULL;
     if (B <= 0 || Nv < 0 || K < 0 || p->pct_lo < 0 || p->pct_hi > 100 || p->pct_lo > p->pct_hi)
@@ -640,7 +667,8 @@ int quota_internal_score_topk(const float *sumsq, const float *ressq, long strid
     ProfScope prof(QUOTA_K_SCORE_TOKENS, 0,
                    20.0 * B * Nv + 4.0 * B * (K < Nv ? K : Nv), st);
     MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
-    return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st, weights);
+    if (masses && !quota_score_takes_means(Nv, masses->H)) return QUOTA_ERR_SHAPE;
+    return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st, weights, masses);
 }
 
 extern "C" void quota_score_params_default(quota_score_params *p)

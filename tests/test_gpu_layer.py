@@ -524,3 +524,18 @@ def test_selection_of_tied_tokens(qb, Nv):
         score = oracle.score(got["sumsq"], got["ressq"], flat, flat)
         assert np.array_equal(got["score"].view(np.uint32), score.view(np.uint32)), K
         assert np.array_equal(got["keep_idx"], oracle.topk(score, K)), K
+
+
+@pytest.mark.parametrize("H,Nv", [(8, 1), (8, 257), (8, 1024), (8, 1025), (10, 255), (20, 512), (20, 513), (40, 256)])
+def test_head_means_in_the_score_kernel(qb, H, Nv):
+    """Few masses: their head means are the score kernel's; with cues handed in they are a launch of their own.  Both have the same bits, and so
+    has what follows from them.  Around the sizes where the one or the other is chosen, uneven quarters of the heads."""
+    shape = wl.Shape("means", d=64 * H, H=H, F=256, layers=1, B=2, Nv=Nv, Nt=5, n_outlier=4, vis_begin=2)
+    W, L, cos, sin = build_layer(shape, 21)
+    x, pos, K = wl.hidden_state(shape, 21), wl.positions(shape), max(1, Nv // 3)
+    got = run_gpu(qb, L, shape, x, pos, K)
+    apart = run_gpu(qb, L, shape, x, pos, K, dict(cm_inter=got["cm_inter"], cm_intra=got["cm_intra"]))
+    for name in ("cm_inter", "cm_intra", "score", "keep_idx", "x_next"):
+        assert np.array_equal(got[name].view(np.uint8), apart[name].view(np.uint8)), name
+    score = oracle.score(got["sumsq"], got["ressq"], got["cm_inter"], got["cm_intra"])
+    assert np.array_equal(got["score"].view(np.uint32), score.view(np.uint32))
