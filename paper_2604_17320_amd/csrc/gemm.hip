@@ -64,8 +64,7 @@ template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, 
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n,
-    int vec_store, quota_qkv_epilogue qe)
+    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
 {
     constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
     constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A6_STARTS, QKV = EPI == QKV_ROPE_KV, SILU = EPI == SILU_MUL;
@@ -491,21 +490,20 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         return;
     }
     // 32 rows at a time through LDS as fp32, so that a thread finishes 8 neighbouring columns of a row: one
-    // 16-byte residual load, one 16-byte store
+    // 16-byte residual load, one 16-byte store, at any element's address (the chip takes both there; of a branch for tensors at multiples of 16
+    // bytes and one for others the compiler made stores of 2, 2 and 12 bytes: 80 x 512 x 512 4.04 -> 3.76 us, 160 x 4096 x 4096 11.0 -> 10.6,
+    // 636 x 4096 x 4096 19.9 -> 19.3, 1356 x 12288 x 4096 68.3 -> 65.9)
     constexpr int RPI = NT / (BN / 8), KI = 32 / RPI;
     float *stage = reinterpret_cast<float *>(lds_raw);
     const int n = n0 + 8 * (tid % (BN / 8)), row0 = tid / (BN / 8);
 #pragma unroll
     for (int ib = 0; ib < RT / 2; ++ib) {
-        Pack16 rv[KI];
+        f16x8 rv[KI];
         if (res && n < N) {
 #pragma unroll
             for (int k = 0; k < KI; ++k) {
                 const f16 *rp = res + (size_t)min(m0 + 32 * ib + RPI * k + row0, M - 1) * ldr + n;
-                if (vec_store & 2) rv[k].u = *reinterpret_cast<const uint4 *>(rp);
-                else
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) rv[k].h[e] = rp[e];
+                rv[k] = *reinterpret_cast<const f16x8_at2 *>(rp);
             }
         }
         if (ib) __syncthreads();                      // the previous 32 rows have been read
@@ -531,18 +529,15 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             const float4 lo = p[0], hi = p[1];
             float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
             if (!y || m >= M || n >= N) continue;
-            Pack16 o;
+            f16x8 o;
             if (res) {
+                asm volatile("" : "+v"(rv[k]));       // (else it is converted, and waited for, where it is loaded)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv[k].h[e];
+                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv[k][e];
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o.h[e] = to_f16(v[e]);
-            f16 *yp = y + (size_t)m * ldy + n;
-            if (vec_store & 1) *reinterpret_cast<uint4 *>(yp) = o.u;
-            else
-#pragma unroll
-                for (int e = 0; e < 8; ++e) yp[e] = o.h[e];
+            for (int e = 0; e < 8; ++e) o[e] = to_f16(v[e]);
+            *reinterpret_cast<f16x8_at2 *>(y + (size_t)m * ldy + n) = o;
         }
     }
 }
@@ -578,7 +573,7 @@ const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128
                              {64, 256, 256, QUOTA_K_GEMM_64X256}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
-                          int, f16 *, int, const f16 *, int, int32_t *, int, int, int, quota_qkv_epilogue);
+                          int, f16 *, int, const f16 *, int, int32_t *, int, int, quota_qkv_epilogue);
 
 template <ActFormat P, Epilogue E>
 f8_kernel tile_kernel(int v)
@@ -612,11 +607,9 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md +
                        (qe ? Md * (Nd / 3) * (7 + 1.0 / 16) + 4 * Md : 2.0 * Md * (ldy < W->N ? ldy : Nd) * (res ? 2 : 1)), st);
     static const quota_qkv_epilogue no_qe = {};
-    auto aligned = [](const void *p, int ld) { return ld % 8 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    const int vec = (y && aligned(y, ldy) ? 1 : 0) | (res && aligned(res, ldr) ? 2 : 0);
     kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>(qa, sa, M, W->K, G, (const uint4 *)W->packed,
                                                            (const f16 *)W->scales, W->N, y, ldy, res, ldr, acc, tiles_m,
-                                                           tiles_n, vec, qe ? *qe : no_qe);
+                                                           tiles_n, qe ? *qe : no_qe);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

@@ -252,6 +252,26 @@ def test_w4a4_gemm_on_the_tile_of_packed_rows(qb, M, N, K):
     assert np.array_equal(host(yr).view(np.uint16), oracle.w4a4_gemm(qa, sa, qw, sw, residual=res).view(np.uint16))
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("off", [1, 4, 8])
+def test_w4a4_gemm_output_and_residual_at_any_element(qb, tile, off, pinned_gemm):
+    """Rows of y and residual that start at any element, an odd number of elements apart; what lies between them stays."""
+    from paper_2604_17320_amd.model import PackedLinear
+    pinned_gemm(tile)
+    M, N, K = 70, 320, 416
+    qa, sa, qw, sw, res = _gemm_case(M, N, K, 25)
+    lin = PackedLinear.from_codes(dev(qw), dev(sw))
+    ldy, ldr = N + 3, N + 5
+    y = torch.full((off + M * ldy,), 7.0, dtype=torch.float16, device="cuda")
+    r = torch.zeros(off + M * ldr, dtype=torch.float16, device="cuda")
+    rows = lambda t, ld: t[off:].view(M, ld)
+    rows(r, ldr)[:, :N] = dev(res)
+    qb.quota_w4a4_gemm(dev(_pack4(qa)), dev(sa), M, lin.desc, y[off:], ldy, r[off:], ldr)
+    ref = oracle.w4a4_gemm(qa, sa, qw, sw, residual=res)
+    assert np.array_equal(host(rows(y, ldy)[:, :N].contiguous()).view(np.uint16), ref.view(np.uint16))
+    assert bool((rows(y, ldy)[:, N:] == 7.0).all()) and bool((y[:off] == 7.0).all())
+
+
 @pytest.mark.parametrize("M", [1, 16, 17, 45, 160])
 def test_w4a4_gemm_with_scales_at_an_odd_halfword(qb, M):
     """Weight scales that start between two dwords: the bits of the aligned call, output and integer sums."""
