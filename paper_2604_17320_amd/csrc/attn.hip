@@ -21,10 +21,12 @@
 // permuted so that every access spreads over all banks; V stays row-major and is transposed by the LDS read;
 // the output is rescaled only when a maximum moved.  4 x 2944 tokens, 40 heads of 128: 562 us (V transposed
 // by 2-byte LDS stores, tiles through registers) -> 442 us; column masses 358 -> 247 us.
+#include <type_traits>
 #include "common.h"
 #include "internal.h"
 #include "gemm_common.h"
 #include "ldscopy.h"
+#include "ldsgrant.h"
 #include "prefetch.h"
 #include "headmeans.h"
 
@@ -44,19 +46,49 @@ __device__ __forceinline__ int tile_swizzle(int r)
 {
     return DH == 128 ? ((r & 3) << 2 | (r >> 2 & 3)) : ((r >> 1 & 1) << 2 | (r >> 2 & 1) << 1);
 }
-// Starts the copy of rows row0 .. row0 + KT - 1 (clamped to last) of a matrix into a tile: 256 threads
+// Copies of KT rows of a matrix into a tile, by four waves, each its share.  A thread's places in a tile are a fixed number of
+// rows apart and keep their swizzle, so its offsets are made once; rows behind the last come as zeros from the buffer's own
+// bounds instead of being clamped, and a tile behind the last fetches nothing, so that its pieces need no branch and can be
+// started one by one between the products.
 template <int DH>
-__device__ __forceinline__ void copy_tile(const f16 *base, int stride, int row0, int last, unsigned lds)
-{
-    constexpr int CPR = DH / 8, PER = KT * CPR / 256;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+struct TileCopy {
+    static constexpr int CPR = DH / 8, PER = KT * CPR / 256, ROWS = 256 / CPR;      // rows of a copy by four waves
+    unsigned row_bytes, off[PER], lds_wave;
+    __device__ __forceinline__ explicit TileCopy(int stride) : row_bytes(2 * stride)
+    {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
+        const int r = wave * (64 / CPR) + lane / CPR;
+        static_assert(ROWS % 16 == 0, "(the swizzle of a row takes its last four bits)");
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int r = (4 * j + wave) * (64 / CPR) + lane / CPR, c = lane % CPR ^ tile_swizzle<DH>(r);
-        copy16_to_lds(base + (size_t)row0 * stride, (unsigned)min(r, last - row0) * (unsigned)(2 * stride) + 16 * c,
-                      lds + (4 * j + wave) * 1024);
+        for (int j = 0; j < PER; ++j) {
+            off[j] = (unsigned)(r + ROWS * j) * row_bytes + 16 * (lane % CPR ^ tile_swizzle<DH>(r));
+            asm volatile("" : "+v"(off[j]));
+        }
+        lds_wave = wave * 1024;
     }
-}
+    // The copy of rows row0 .. row0 + KT - 1 of a matrix of `rows` into the tile at lds, in PER pieces: zeros behind the last row
+    struct Run {
+        i32x4 buffer;
+        unsigned lds;
+    };
+    __device__ __forceinline__ Run run(const f16 *base, int row0, int rows, unsigned lds) const
+    {
+        const int left = min(rows - row0, KT);
+        const uint64_t at = (uint64_t)base + (uint64_t)(unsigned)row0 * row_bytes;
+        return Run{i32x4{(int)(uint32_t)at, (int)(uint32_t)(at >> 32) & 0xffff, left > 0 ? (int)((left - 1) * row_bytes + 2 * DH) : 0, 0x00020000},
+                   lds + lds_wave};
+    }
+    __device__ __forceinline__ void piece(const Run &to, int j) const
+    {
+        asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(to.lds + 4096 * j), "v"(off[j]), "s"(to.buffer) : "memory");
+    }
+    __device__ __forceinline__ void operator()(const f16 *base, int row0, int rows, unsigned lds) const
+    {
+        const Run to = run(base, row0, rows, lds);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) piece(to, j);
+    }
+};
 // The 16-byte pieces 2 t + hl of row r of a tile, t = 0, 1, ...: piece t is at first ^ (32 t) bytes
 template <int DH>
 __device__ __forceinline__ int piece_address(int r, int hl) { return r * (2 * DH) + ((hl ^ tile_swizzle<DH>(r)) << 4); }
@@ -95,9 +127,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     const int dkv = Hkv * DH;
     const size_t kvbase = (size_t)b * N * dkv + (size_t)(h / (H / Hkv)) * DH;
     const int q_last_wg = min(q0 + 127, N - 1);
+    const TileCopy<DH> tile_copy(dkv);
     auto copy = [&](int kt0, int buf) {
-        copy_tile<DH>(khat + kvbase, dkv, kt0, N - 1, lds_address(sm[buf][0]));
-        copy_tile<DH>(vhat + kvbase, dkv, kt0, N - 1, lds_address(sm[buf][1]));
+        tile_copy(khat + kvbase, kt0, N, lds_address(sm[buf][0]));
+        tile_copy(vhat + kvbase, kt0, N, lds_address(sm[buf][1]));
     };
     copy(0, 0);
 
@@ -218,36 +251,45 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     }
 }
 
-// One workgroup per 128 visual keys of a (sequence, head); wave w owns the 32 keys kb .. kb+31.
-template <int DH, typename PRE>
-__global__ __launch_bounds__(256, 3) void colmass_kernel(
+// One workgroup per 128 visual keys of a (sequence, head); wave w of a group of four owns the 32 keys kb .. kb+31.
+// The first key block meets every query tile, a chain that bounds launches of few workgroups: there G = 2 groups take the tiles in
+// turn, each through LDS of its own, and the second's sums are added to the first's (32 heads, 165 / 400 / 640 tokens 10.3 / 15.2 / 16.6 ->
+// 9.3 / 13.2 / 13.1 us, 28 heads, 1101 tokens 25.7 -> 18.9; four groups take longer below a thousand tokens).
+template <int DH>
+constexpr size_t colmass_lds(int G) { return (size_t)G * 2 * (KT * DH * 2 + KT * 4) + (G - 1) * 128 * sizeof(float2); }
+template <int DH, int G, typename PRE>
+__global__ __launch_bounds__(256 * G, G == 1 ? 3 : 1) void colmass_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
     int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, int wgs, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
-        prefetch<256>(pre, blockIdx.x - wgs, gridDim.x - wgs);
+        prefetch<256 * G>(pre, blockIdx.x - wgs, gridDim.x - wgs);
         return;
     }
     constexpr int T = DH / 16, TB = KT * DH * 2;
-    __shared__ __align__(16) char sm_q[2][TB];
-    __shared__ __align__(16) float sm_lse[2][KT];
+    extern __shared__ __align__(16) char sm[];            // [group][buffer][tile], [group][buffer][lse], [group - 1][key]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3, l32 = lane & 31, hl = lane >> 5;
+    const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    char *const sm_q = sm + grp * 2 * TB;
+    float *const sm_lse = reinterpret_cast<float *>(sm + G * 2 * TB) + grp * 2 * KT;
+    float2 *const sm_sum = reinterpret_cast<float2 *>(sm + G * 2 * (TB + 4 * KT));
     // XCD-aware order, as in pass 1; the first keys have the most queries
     const int nk = (Nv + 127) / 128, work = xcd_remap(blockIdx.x, wgs), bh = work / nk, kb = work % nk;
     const int d = H * DH;
     const int b = bh / H, h = bh % H;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hl = lane >> 5;
     const int kwg = vis_begin + kb * 128;                 // first key of the workgroup
     const int key = kwg + wave * 32 + l32;                // this lane's key column
     const bool key_ok = key < vis_begin + Nv;
     const size_t base = (size_t)b * N * d + (size_t)h * DH;
     const float *lse = lse2 + ((size_t)b * H + h) * N;
 
+    const TileCopy<DH> tile_copy(d);
     auto copy = [&](int qt0, int buf) {
-        copy_tile<DH>(q + base, d, qt0, N - 1, lds_address(sm_q[buf]));
-        if (wave == 0) copy4_to_lds(lse, 4 * min(qt0 + lane, N - 1), lds_address(sm_lse[buf]));
+        tile_copy(q + base, qt0, N, lds_address(sm_q + buf * TB));
+        if (wave == 0) copy4_to_lds(lse, 4 * min(qt0 + lane, N - 1), lds_address(sm_lse + buf * KT));
     };
     const int qt_first = (kwg / KT) * KT;
-    copy(qt_first, 0);
+    if (qt_first + grp * KT < N) copy(qt_first + grp * KT, 0);
     f16x8 kf[T];
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -260,22 +302,32 @@ __global__ __launch_bounds__(256, 3) void colmass_kernel(
     float acc_txt = 0.0f, acc_vis = 0.0f;
     const int q_at = piece_address<DH>(l32, hl);
     int buf = 0;
-    for (int qt0 = qt_first; qt0 < N; qt0 += KT, buf ^= 1) {
+    for (int qg0 = qt_first; qg0 < N; qg0 += G * KT, buf ^= 1) {
         drain();
         __syncthreads();
-        if (qt0 + KT < N) copy(qt0 + KT, buf ^ 1);
-        if (qt0 + KT - 1 < kwg + wave * 32) continue;     // all queries before this wave's keys
+        const int qt0 = qg0 + grp * KT;
+        const bool more = qt0 + G * KT < N;
+        constexpr int PER = TileCopy<DH>::PER;             // (at the top they took the address unit all at once: 4 x 2944 tokens, 40 heads 252 -> 230 us)
+        const auto next = tile_copy.run(q + base, qt0 + G * KT, N, lds_address(sm_q + (buf ^ 1) * TB));
+        if (more && wave == 0) copy4_to_lds(lse, 4 * min(qt0 + G * KT + lane, N - 1), lds_address(sm_lse + (buf ^ 1) * KT));
+        if (qt0 + KT - 1 < kwg + wave * 32) {             // all queries before this wave's keys
+#pragma unroll
+            for (int j = 0; j < PER; ++j) tile_copy.piece(next, j);
+            continue;
+        }
+        if (G > 1 && qt0 >= N) continue;                  // (every group meets every barrier)
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
             f32x16 s;
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                f16x8 qf = *reinterpret_cast<const f16x8 *>(sm_q[buf] + (q_at ^ 32 * t) + 32 * sb * (2 * DH));
+                if (sb == 0 && t % (T / PER) == 0) tile_copy.piece(next, t / (T / PER));
+                f16x8 qf = *reinterpret_cast<const f16x8 *>(sm_q + buf * TB + (q_at ^ 32 * t) + 32 * sb * (2 * DH));
                 s = __builtin_amdgcn_mfma_f32_32x32x16_f16(qf, kf[t], t ? s : zero, 0, 0, 0);
             }
             // queries qb0 .. qb0 + 31; register r holds query qb0 + 8 (r / 4) + 4 hl + r % 4
             const int qb0 = qt0 + 32 * sb, vis_end = vis_begin + Nv;
-            const float *ls = sm_lse[buf] + 32 * sb + 4 * hl;
+            const float *ls = sm_lse + buf * KT + 32 * sb + 4 * hl;
             // the causal / end-of-sequence mask is only needed when the query block reaches this
             // wave's keys or the end of the sequence (lanes without a key accumulate values that
             // are never stored); a block of one kind of query adds to one sum
@@ -304,8 +356,20 @@ __global__ __launch_bounds__(256, 3) void colmass_kernel(
             }
         }
     }
+    drain();                                              // (pieces of a tile behind the last)
     acc_txt += __shfl_xor(acc_txt, 32, 64);
     acc_vis += __shfl_xor(acc_vis, 32, 64);
+    if constexpr (G > 1) {
+        if (grp && hl == 0) sm_sum[(grp - 1) * 128 + wave * 32 + l32] = make_float2(acc_txt, acc_vis);
+        __syncthreads();
+        if (grp) return;
+#pragma unroll
+        for (int g = 0; g < G - 1; ++g) {
+            const float2 v = sm_sum[g * 128 + wave * 32 + l32];
+            acc_txt += v.x;
+            acc_vis += v.y;
+        }
+    }
     if (key_ok && hl == 0) partial[((size_t)b * H + h) * Nv + (key - vis_begin)] = make_float2(acc_txt, acc_vis);
 }
 
@@ -379,15 +443,31 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if (cues) {
         const unsigned n2 = (unsigned)((Nv + 127) / 128) * H * B;
+        // two groups where every workgroup has a CU to itself, or half of one and a chain of eight tiles (2 x 640 tokens, 32 heads 18.7 -> 16.6 us, 8 x 300
+        // 16.4 -> 16.5, 4 x 640 as it was)
+        const bool split = n2 <= (N >= 512 ? 512u : 256u);
         const auto s2 = weights ? weights->take(n2, 3.0f + 1.1f * (float)((N + 63) / 64), 3.5f) : PrefetchList::Share{};
         dim3 g2(n2 + s2.wgs);
         // (query, visual key) pairs under the causal mask
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
+        bool granted = true;
+        auto launch = [&](auto dh_tag, auto groups, auto pre) {
+            constexpr int DH = decltype(dh_tag)::value, G = decltype(groups)::value;
+            constexpr auto kernel = colmass_kernel<DH, G, decltype(pre)>;
+            if ((granted = grant_lds<kernel>()))
+                kernel<<<g2, dim3(256 * G), colmass_lds<DH>(G), st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial,
+                                                                       scale_log2, (int)n2, pre);
+        };
         s2.run([&](auto pre) {
-            auto kernel = dh == 128 ? colmass_kernel<128, decltype(pre)> : colmass_kernel<64, decltype(pre)>;
-            kernel<<<g2, blk, 0, st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial, scale_log2, (int)n2, pre);
+            auto with_dh = [&](auto dh_tag) {
+                if (split) launch(dh_tag, std::integral_constant<int, 2>(), pre);
+                else launch(dh_tag, std::integral_constant<int, 1>(), pre);
+            };
+            if (dh == 128) with_dh(std::integral_constant<int, 128>());
+            else with_dh(std::integral_constant<int, 64>());
         });
+        if (!granted) return QUOTA_ERR_HIP;
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         if (masses) {
             *masses = {w.partial, H, cm_inter, cm_intra};

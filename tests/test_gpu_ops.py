@@ -448,6 +448,25 @@ def test_attention_prefill_and_column_masses(qb, B, N, H, dh, vb, Nv):
         assert np.allclose(cvg, cv_ref, rtol=2e-5, atol=1e-7), np.abs(cvg / cv_ref - 1).max()
 
 
+# two groups of waves take the query tiles in turn: one tile only, an odd number, keys that begin inside a tile, and past 256
+# workgroups of few tiles a single group
+@pytest.mark.parametrize("B,N,H,dh,vb,Nv", [(1, 64, 2, 128, 0, 64), (1, 33, 1, 64, 5, 20), (1, 193, 2, 64, 3, 150),
+                                             (1, 333, 2, 128, 200, 133), (1, 65, 3, 128, 64, 1), (3, 200, 90, 64, 0, 200)])
+def test_column_masses_by_groups(qb, B, N, H, dh, vb, Nv):
+    d = H * dh
+    q = _act(B * N, d, 54, 1.0)
+    _, _, khat = oracle.kv_quant(_act(B * N, d, 55, 1.0))
+    _, _, vhat = oracle.kv_quant(_act(B * N, d, 56, 1.0))
+    o_ref, ci_ref, cv_ref = oracle.attention(q, khat, vhat, B, N, H, dh, vb, Nv)
+    o = torch.empty((B * N, d), dtype=torch.float16, device="cuda")
+    ci, cv = (torch.full((B, Nv), -1.0, dtype=torch.float32, device="cuda") for _ in range(2))
+    ws = torch.empty(qb.quota_attention_workspace_bytes(B, N, H, dh), dtype=torch.uint8, device="cuda")
+    qb.quota_attention_prefill(dev(q), dev(khat), dev(vhat), B, N, H, dh, vb, Nv, o, ci, cv, ws)
+    assert close_f16(host(o), o_ref)
+    assert np.allclose(host(ci), ci_ref, rtol=2e-5, atol=1e-7)
+    assert np.allclose(host(cv), cv_ref, rtol=2e-5, atol=1e-7)
+
+
 # -------------------------------------------------------- score and top-k
 def _metrics(B, Nv, seed):
     r = wl.rng(seed, "metrics", B, Nv)
