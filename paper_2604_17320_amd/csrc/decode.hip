@@ -73,6 +73,10 @@ struct DecodeNew {
 //            the tokens; the token lanes are summed through LDS in a fixed order at the end.
 // step_dev (optional): the cache length is len + *step_dev + 1 (a HIP-graph-captured decode loop keeps
 // its step count on the device).
+// VS > 1: so many workgroups share the channels of V of a head, each with all scores: a lane's piece is 32 / VS channels, which makes
+// the products with V and the sum over the token lanes, two fifths of the instructions, shorter and leaves every sum in its order (the
+// same bits).  For launches that leave CUs idle.  Asked for beside K, or the next tile's K before the softmax, V and K make the step
+// slower (1260 -> 1281 us, 1264).
 // SPLIT: n_split workgroups share a K/V head's rows, split_tiles() tiles each; they leave unnormalized outputs,
 // maxima and sums in `part` for decode_combine_kernel.
 constexpr int DEC_TILE = 512;
@@ -93,9 +97,9 @@ constexpr int DEC_THREADS = 512;     // 8 waves: with two workgroups on a CU eve
 // at a time (4 bytes at a time 128 reads were 0.3 us longer), its start moved on by piece so that a wave's 64 writes
 // fall on 64 banks.
 constexpr int dec_red_row(int dh) { return DEC_THREADS / (dh / 32) + 4; }
-constexpr int dec_red_floats(int dh, int hp) { return hp * dh * dec_red_row(dh) + 64; }
+constexpr int dec_red_floats(int dh, int hp, int vs) { return hp * dh / vs * dec_red_row(dh) + 64; }
 
-template <int DH, int RC, int HP, bool MULTI, bool FUSED, bool SPLIT>
+template <int DH, int RC, int HP, bool MULTI, bool FUSED, bool SPLIT, int VS>
 __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void decode_attention_kernel(
     const f16 *__restrict__ q, int d, int dkv, int rep, uint32_t *__restrict__ kc, f16 *__restrict__ ks,
     uint32_t *__restrict__ vc, f16 *__restrict__ vs, int capacity, int len,
@@ -109,6 +113,8 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     constexpr int GPT = DH / 64;            // scale groups per token and head
     constexpr int NW = HP * DEC_THREADS / 64;       // waves
     static_assert(HP == 1 || (RC == 1 && !SPLIT), "");
+    static_assert(VS == 1 || ((VS == 2 || VS == 4) && HP == 1 && !SPLIT && FUSED), "");
+    constexpr int VC = 32 / VS, VD = 4 / VS;    // channels and dwords of V per lane
     extern __shared__ __align__(16) float red[];    // dec_red_floats
     constexpr int RROW = dec_red_row(DH);
     __shared__ h2 qp[HP * RC][DH / 2];      // q as pairs: qp[r][4 i + e] = (q[8 i + e], q[8 i + e + 4])
@@ -124,7 +130,8 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     const int work = xcd_remap(blockIdx.x, gridDim.x);
     const int r0 = (work % n_pass) * RC;
     const int sp = SPLIT ? work / n_pass % n_split : 0;
-    const int bh = work / (SPLIT ? n_pass * n_split : n_pass) * HP, h = bh % n_kv_heads, b = bh / n_kv_heads;  // (first) K/V head
+    const int vsp = VS > 1 ? work / n_pass % VS : 0;   // this workgroup's dwords of every piece of V
+    const int bh = work / (SPLIT ? n_pass * n_split : VS * n_pass) * HP, h = bh % n_kv_heads, b = bh / n_kv_heads;  // (first) K/V head
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int piece = tid % PPT, hs = tid / PPT % HP, tl = tid / (PPT * HP);
     constexpr int TPW = 64 / (PPT * HP);    // tokens per pass of a wave
@@ -153,6 +160,7 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     const auto ksbuf = buffer(ks + row0 * ng + h * GPT, 2 * ng, HP * GPT * 2);
     const auto vsbuf = buffer(vs + row0 * ng + h * GPT, 2 * ng, HP * GPT * 2);
     i32x4 slot[UN];                     // codes of a pass: K until its scores are taken, then V
+    uint32_t vword[VS > 1 ? UN : 1][VD];        // VS > 1: V has registers of its own
     uint32_t ksw, vsw;
     const int scale_t = (lane / HP / TPW) * TP + wave_t0 + lane / HP % TPW;
     const int code_off = tl * (4 * n32) + 16 * (tid % (PPT * HP)), scale_off = scale_t * (2 * ng) + lane % HP * (2 * GPT);
@@ -160,6 +168,17 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     auto load_codes = [&](auto buf, int t) {
         asm volatile("" : "+s"(t));
         return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, code_off + t * (4 * n32), 0, 0));
+    };
+    auto load_vwords = [&](uint32_t (&v)[VD], int t) {
+        asm volatile("" : "+s"(t));
+        const int at = code_off + 4 * VD * vsp + t * (4 * n32);
+        if constexpr (VD == 2) {
+            const auto two = __builtin_amdgcn_raw_buffer_load_b64(vbuf, at, 0, 0);
+            v[0] = two[0];
+            v[1] = two[1];
+        } else {
+            v[0] = __builtin_amdgcn_raw_buffer_load_b32(vbuf, at, 0, 0);
+        }
     };
     auto load_scales = [&](auto buf, int t) -> uint32_t {
         asm volatile("" : "+s"(t));
@@ -211,7 +230,7 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
                 const uint32_t word = kv_quant8(xo, &s8, nullptr);
                 new_codes[item][ph * WPT + cc] = word;
                 if ((cc & 7) == 0) new_scales[item][ph * GPT + (cc >> 3)] = s8;
-                if (r0 == 0 && L > t_begin && L <= t_end) {
+                if (r0 == 0 && vsp == 0 && L > t_begin && L <= t_end) {
                     const size_t row = row0 + L - 1;
                     (item == 0 ? kc : vc)[row * n32 + (h + ph) * WPT + cc] = word;
                     if ((cc & 7) == 0) (item == 0 ? ks : vs)[row * ng + (h + ph) * GPT + (cc >> 3)] = s8;
@@ -219,7 +238,7 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) qp[ph * RC + item - 2][4 * cc + e] = h2{xo.h[e], xo.h[e + 4]};
-                if (nw.q_rot && sp == 0 && item - 2 < nr)
+                if (nw.q_rot && sp == 0 && vsp == 0 && item - 2 < nr)
                     *reinterpret_cast<uint4 *>(nw.q_rot + (size_t)b * d + ((h + ph) * rep + r0 + item - 2) * DH + 8 * cc) = xo.u;
             }
         }
@@ -235,14 +254,14 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     for (int r = 0; r < RC; ++r)
 #pragma unroll
         for (int i = 0; i < 16; ++i) qr[r][i] = qp[hs * RC + r][16 * piece + i];
-    float m_run[HP * RC], l_run[RC], acc[RC][32];
+    float m_run[HP * RC], l_run[RC], acc[RC][VC];
 #pragma unroll
     for (int r = 0; r < HP * RC; ++r) m_run[r] = -INFINITY;
 #pragma unroll
     for (int r = 0; r < RC; ++r) {
         l_run[r] = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 32; ++e) acc[r][e] = 0.0f;
+        for (int e = 0; e < VC; ++e) acc[r][e] = 0.0f;
     }
     for (int t0 = t_begin; t0 < t_end; t0 += DEC_TILE) {
         const int tn = min(DEC_TILE, t_end - t0);
@@ -299,7 +318,8 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
                     if (ok) mx[r] = fmaxf(mx[r], v);
                 }
             }
-            slot[u] = load_codes(vbuf, t0 + u * TP);        // the freed slot takes V
+            if constexpr (VS == 1) slot[u] = load_codes(vbuf, t0 + u * TP);        // the freed slot takes V
+            else load_vwords(vword[u], t0 + u * TP);
         }
 #pragma unroll
         for (int r = 0; r < HP * RC; ++r) {
@@ -336,7 +356,7 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
             for (int w = 1; w < NW / HP; ++w) ts += wsum[hs * RC + r][w];
             l_run[r] = l_run[r] * alpha[r] + ts;
 #pragma unroll
-            for (int e = 0; e < 32; ++e) acc[r][e] *= alpha[r];
+            for (int e = 0; e < VC; ++e) acc[r][e] *= alpha[r];
         }
         // ---- p * v_hat; the freed slots take the next tile's K
         patch_scales(vsw, 1);
@@ -346,15 +366,20 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
             if (u * TP + wave_t0 < tn) {
                 const int t = u * TP + tl;
                 const bool ok = t < tn;
-                if (FUSED && new_pass == u) patch(slot[u], 1);
+                if (FUSED && new_pass == u) {
+                    if constexpr (VS == 1) patch(slot[u], 1);
+                    else if (tl == (L - 1 - t0) % TP)
+#pragma unroll
+                        for (int i = 0; i < VD; ++i) vword[u][i] = new_codes[1][4 * piece + VD * vsp + i];
+                }
                 const h2 s2 = scale_of(vsw, u);
                 float pv[RC];
 #pragma unroll
                 for (int r = 0; r < RC; ++r) pv[r] = ok ? sc[hs * RC + r][t] : 0.0f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int i = 0; i < VD; ++i) {
                     h2 vh[4];
-                    dequant(slot[u][i], s2, vh);
+                    dequant(VS == 1 ? (uint32_t)slot[u][i] : vword[VS > 1 ? u : 0][i], s2, vh);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -374,13 +399,13 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
         if (r >= nr) break;
         if (r) __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 32; ++e) red[(DH * hs + 32 * piece + e) * RROW + TPW * (PPT * hs + piece) + tl] = acc[r][e];
+        for (int e = 0; e < VC; ++e) red[(DH * hs + VC * piece + e) * RROW + TPW * (PPT * hs + piece) + tl] = acc[r][e];
         if (HP > 1 && lane < PPT * HP && piece == 0) lsum[hs] = l_run[r];       // (every lane has its head's)
         __syncthreads();
-        if (tid < HP * DH) {
-            const int hd = tid / DH, c = tid % DH;
+        if (tid < HP * DH / VS) {
+            const int hd = tid / DH, cv = tid % DH, c = VS == 1 ? cv : cv / VC * 32 + vsp * VC + cv % VC;
             float out = 0.0f;
-            const float4 *rp = reinterpret_cast<const float4 *>(red + (DH * hd + c) * RROW + TPW * (PPT * hd + c / 32));
+            const float4 *rp = reinterpret_cast<const float4 *>(red + (DH * hd + cv) * RROW + TPW * (PPT * hd + cv / VC));
 #pragma unroll 8
             for (int i = 0; i < TP / 4; ++i) {
                 const float4 v = rp[i];
@@ -436,31 +461,39 @@ int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o
         n_split = max(n_split, (n + t - 1) / t);
     }
     const bool one_tile = longest <= DEC_TILE;
-    auto run = [&](auto kernel_tag, int hp) {
+    auto run = [&](auto kernel_tag, int hp, int vs = 1) {
         constexpr auto kernel = decltype(kernel_tag)::value;
-        const size_t lds = dec_red_floats(DH, hp) * sizeof(float);
+        const size_t lds = dec_red_floats(DH, hp, vs) * sizeof(float);
         if (!grant_lds<kernel>()) return QUOTA_ERR_HIP;
-        kernel<<<dim3(heads * n_split / hp), dim3(hp * DEC_THREADS), lds, st>>>(
+        kernel<<<dim3(heads * n_split * vs / hp), dim3(hp * DEC_THREADS), lds, st>>>(
             q, d, dkv, rep, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes, (f16 *)c->v_scales,
             c->capacity, stepped ? c->len : len, c->step_dev, c->max_steps, o, c->H, nw, n_split, heads, part);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
     };
-#define KERNEL(RC, HP, MULTI, SPLIT)                                                                   \
-    std::integral_constant<decltype(&decode_attention_kernel<DH, RC, HP, MULTI, FUSED, SPLIT>),        \
-                           &decode_attention_kernel<DH, RC, HP, MULTI, FUSED, SPLIT>>()
+#define KERNEL(RC, HP, MULTI, SPLIT, VS)                                                               \
+    std::integral_constant<decltype(&decode_attention_kernel<DH, RC, HP, MULTI, FUSED, SPLIT, VS>),    \
+                           &decode_attention_kernel<DH, RC, HP, MULTI, FUSED, SPLIT, VS>>()
     if constexpr (FUSED) {
         if (n_split > 1) {
-            const int rcode = rep == 1 ? run(KERNEL(1, 1, true, true), 1) : run(KERNEL(2, 1, true, true), 1);
+            const int rcode = rep == 1 ? run(KERNEL(1, 1, true, true, 1), 1) : run(KERNEL(2, 1, true, true, 1), 1);
             if (rcode != QUOTA_OK) return rcode;
             decode_combine_kernel<DH><<<dim3(c->B * Hq), dim3(DH), 0, st>>>(part, n_split, o);
             QUOTA_RETURN_IF_LAUNCH_FAILED();
             return QUOTA_OK;
         }
+        // V's channels by four workgroups where that leaves one for every CU (32 layers of 7B, one sequence, 640 to 122 rows 1301 -> 1259 us a step; 8
+        // grouped-query layers, two sequences 453 -> 436), by two for pairs of query heads (eight sequences 518 -> 507; 7B, four: 457 -> 456)
+        if (heads * 4 <= DEC_SPLIT_GRID) {
+            if (rep == 1) return one_tile ? run(KERNEL(1, 1, false, false, 4), 1, 4) : run(KERNEL(1, 1, true, false, 4), 1, 4);
+            return one_tile ? run(KERNEL(2, 1, false, false, 4), 1, 4) : run(KERNEL(2, 1, true, false, 4), 1, 4);
+        }
+        if (rep > 1 && heads * 2 <= DEC_SPLIT_GRID)
+            return one_tile ? run(KERNEL(2, 1, false, false, 2), 1, 2) : run(KERNEL(2, 1, true, false, 2), 1, 2);
     }
-    if (pairs) return one_tile ? run(KERNEL(1, 2, false, false), 2) : run(KERNEL(1, 2, true, false), 2);
-    if (rep == 1) return one_tile ? run(KERNEL(1, 1, false, false), 1) : run(KERNEL(1, 1, true, false), 1);
-    return one_tile ? run(KERNEL(2, 1, false, false), 1) : run(KERNEL(2, 1, true, false), 1);
+    if (pairs) return one_tile ? run(KERNEL(1, 2, false, false, 1), 2) : run(KERNEL(1, 2, true, false, 1), 2);
+    if (rep == 1) return one_tile ? run(KERNEL(1, 1, false, false, 1), 1) : run(KERNEL(1, 1, true, false, 1), 1);
+    return one_tile ? run(KERNEL(2, 1, false, false, 1), 1) : run(KERNEL(2, 1, true, false, 1), 1);
 #undef KERNEL
 }
 

@@ -213,3 +213,24 @@ def test_decode_layer_silu_product_in_the_gate_up_projection(qb, F, B):
         L.decode(x, pos, cache, y, ws, make_taps(**taps))
         outs.append(host(y))
     assert np.isfinite(outs[0].astype(np.float32)).all() and eq16(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("H,Hkv,dh,B", [(8, 8, 128, 1), (4, 4, 64, 16),      # V's channels by four workgroups, one query head and pairs
+                                        (8, 2, 128, 4), (7, 1, 64, 16), (6, 2, 128, 20), (28, 4, 64, 8)])   # and by two
+@pytest.mark.parametrize("rows", [1, 4, 127, 128, 511, 512, 700, 1023])      # ends of passes and tiles
+def test_decode_layer_shared_channels_of_v_have_the_same_bits(qb, H, Hkv, dh, B, rows):
+    """How many workgroups share a head's V is no matter of its sums: the layer's attention leaves the bits of a call on the
+    rotated queries and the appended cache, whose workgroups own a head each."""
+    from paper_2604_17320_amd.model import make_taps
+    print(f"decode layer, {H}/{Hkv} heads of {dh}, {B} sequences of {rows} cached rows", flush=True)
+    W, L, cos, sin = layer(H, Hkv, dh, 160)
+    c = random_cache(rows, B, rows, Hkv, dh)
+    r = wl.rng(rows, "decode-shared", B)
+    x, pos = dev(r.standard_normal((B, H * dh)).astype(np.float16)), dev((7 + np.arange(B) % 50).astype(np.int32))
+    cache = poisoned_cache(c, B, rows, rows + 2, Hkv, dh)
+    q, o, y, whole = (torch.full((B, H * dh), float("nan"), dtype=torch.float16, device="cuda") for _ in range(4))
+    ws = torch.full((L.decode_workspace_bytes(B),), 0xFF, dtype=torch.uint8, device="cuda")
+    L.decode(x, pos, cache, y, ws, make_taps(q_rot=q, o=o))
+    assert cache.len == rows + 1
+    qb.quota_attention_decode_gqa(q, H, cache.desc, whole)
+    assert np.isfinite(host(o).astype(np.float32)).all() and eq16(host(o), host(whole))
