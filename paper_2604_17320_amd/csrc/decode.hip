@@ -427,17 +427,29 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     }
 }
 
-// One workgroup per (sequence, query head): the splits' outputs under a common maximum.
-template <int DH>
+// One workgroup per (sequence, query head): the splits' outputs under a common maximum.  MOST splits are loaded at once (past the last
+// the last one again, unused): the launch is a round trip to memory, not two (3 sequences of 4003 rows, 28 heads, 4 splits: layer 71.5 -> 69.7 us).
+template <int DH, int MOST>
 __global__ __launch_bounds__(DH) void decode_combine_kernel(const float *__restrict__ part, int n_split, f16 *__restrict__ o)
 {
     const float *p = part + (size_t)blockIdx.x * n_split * (DH + 2);
+    float pm[MOST], pl[MOST], po[MOST];
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) {
+        const float *ps = p + min(s, n_split - 1) * (DH + 2);
+        pm[s] = ps[DH];
+        pl[s] = ps[DH + 1];
+        po[s] = ps[threadIdx.x];
+    }
     float m = -INFINITY, l = 0.0f, out = 0.0f;
-    for (int s = 0; s < n_split; ++s) m = fmaxf(m, p[s * (DH + 2) + DH]);
-    for (int s = 0; s < n_split; ++s) {
-        const float a = __expf(p[s * (DH + 2) + DH] - m);       // 0 for a split without rows
-        l = __builtin_fmaf(a, p[s * (DH + 2) + DH + 1], l);
-        out = __builtin_fmaf(a, p[s * (DH + 2) + threadIdx.x], out);
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) m = fmaxf(m, pm[s]);
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) {
+        if (s >= n_split) break;
+        const float a = __expf(pm[s] - m);          // 0 for a split without rows
+        l = __builtin_fmaf(a, pl[s], l);
+        out = __builtin_fmaf(a, po[s], out);
     }
     o[(size_t)blockIdx.x * DH + threadIdx.x] = (f16)(out / l);
 }
@@ -478,7 +490,9 @@ int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o
         if (n_split > 1) {
             const int rcode = rep == 1 ? run(KERNEL(1, 1, true, true, 1), 1) : run(KERNEL(2, 1, true, true, 1), 1);
             if (rcode != QUOTA_OK) return rcode;
-            decode_combine_kernel<DH><<<dim3(c->B * Hq), dim3(DH), 0, st>>>(part, n_split, o);
+            static_assert(DEC_LMAX <= 16 * DEC_TILE, "");
+            const auto combine = n_split <= 4 ? decode_combine_kernel<DH, 4> : n_split <= 8 ? decode_combine_kernel<DH, 8> : decode_combine_kernel<DH, 16>;
+            combine<<<dim3(c->B * Hq), dim3(DH), 0, st>>>(part, n_split, o);
             QUOTA_RETURN_IF_LAUNCH_FAILED();
             return QUOTA_OK;
         }

@@ -84,7 +84,8 @@ HEADS = [(8, 8, 64), (4, 4, 128), (8, 2, 128), (6, 2, 64)]      # rep 1 and 4; a
 
 @pytest.mark.parametrize("H,Hkv,dh", HEADS)
 @pytest.mark.parametrize("rows", [511, 512, 700, 1023,          # one to two 512-row tiles: the new row last and first in a tile
-                                  1024, 1535, 2049, 3000])      # split over workgroups, one tile each
+                                  1024, 1535, 2049, 3000,       # split over workgroups, one tile each
+                                  5200])                        # into more than eight parts
 def test_decode_layer_walks_and_splits(qb, H, Hkv, dh, rows):
     print(f"decode layer, {H}/{Hkv} heads of {dh}, {rows} cached rows", flush=True)
     step_and_check(H, Hkv, dh, 160, 2, rows)
