@@ -298,8 +298,56 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     } else {
         drain();
     }
+    // The first stage's weights are here before the barrier: left alone the compiler starts them behind it, and the waits for them, which it puts into
+    // the loop and counts without the copies, wait there for loads of the next stage that have just been started (64 x 128 tile, 1101 x 3584 x
+    // 18944: main loop 113900 -> 111400 cycles).
+    if constexpr (!ACC_OUT) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+                asm volatile("" : "+v"(rw[0][c][j].x), "+v"(rw[0][c][j].y), "+v"(rw[0][c][j].z), "+v"(rw[0][c][j].w));
+    }
     store_packed(0);
     __syncthreads();
+
+    // What the epilogue needs from memory for 32 rows (round ib): a thread has row RPI * k + row0 of them, and 8 channels.  Tiles of one round ask for it
+    // here, a main loop ahead, the others in front of the epilogue for all residual rows and for the angles a round ahead: asked for round by round,
+    // each waited for memory (with the weights above, layers replayed: 512 channels, 16 x 80 tokens 63.2 -> 62.8 us, 7B shape, 165 / 320 tokens 117.5 /
+    // 148.2 -> 116.5 / 147.5, 13B, 400 tokens 195.2 -> 193.3, grouped-query, 1101 tokens 277.6 -> 276.4).
+    constexpr int RPI = NT / (BN / 8), KI = 32 / RPI, ROUNDS = RT / 2, AR = !QKV ? 1 : KI <= 2 && ROUNDS > 1 ? 2 : 1;
+    const int row0 = tid / (BN / 8), c8 = tid % (BN / 8), n8 = n0 + 8 * c8;
+    float cs[AR][QKV ? KI : 1][8], sn[AR][QKV ? KI : 1][8];
+    f16x8 rv[EPI == PLAIN ? ROUNDS : 1][EPI == PLAIN ? KI : 1];
+    const f16 *res_at = res;
+    asm volatile("" : "+s"(res_at));         // (else the loads sink to where they are used)
+    auto ask_angles = [&](int ib) {
+        const int half = qe.dh >> 4;         // chunks per half head (4 or 8)
+        if (n0 < qe.d + qe.dkv) {
+#pragma unroll
+            for (int k = 0; k < KI; ++k) {
+                const unsigned at = (unsigned)(row_pos[32 * ib + RPI * k + row0] * 8 * half + 8 * (c8 & (half - 1)));
+                float *cp = cs[ib % AR][k], *sp = sn[ib % AR][k];
+                *reinterpret_cast<float4 *>(cp) = *reinterpret_cast<const float4 *>(qe.cosT + at);
+                *reinterpret_cast<float4 *>(cp + 4) = *reinterpret_cast<const float4 *>(qe.cosT + at + 4);
+                *reinterpret_cast<float4 *>(sp) = *reinterpret_cast<const float4 *>(qe.sinT + at);
+                *reinterpret_cast<float4 *>(sp + 4) = *reinterpret_cast<const float4 *>(qe.sinT + at + 4);
+            }
+        }
+    };
+    auto ask_residual = [&](int ib) {
+        if (res && n8 < N) {
+#pragma unroll
+            for (int k = 0; k < KI; ++k) {
+                const f16 *rp = res_at + (size_t)min(m0 + 32 * ib + RPI * k + row0, M - 1) * ldr + n8;
+                rv[ib][k] = *reinterpret_cast<const f16x8_at2 *>(rp);
+            }
+        }
+    };
+    if constexpr (ROUNDS == 1) {
+        if constexpr (QKV) ask_angles(0);
+        if constexpr (EPI == PLAIN) ask_residual(0);
+    }
 
     i32x8 fb[CT];
     const int stages = (G + CH - 1) / CH;
@@ -385,20 +433,18 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 #pragma unroll
     for (int i = 0; i < LAG; ++i) scale_in(T - LAG + i, pend[i], pscale[i]);
 
-    // epilogue: token scale (with the 2^6 of the operands' units), residual, fp16.  What it needs from memory for 32
-    // rows is asked for before they are staged.
+    // epilogue: token scale (with the 2^6 of the operands' units), residual, fp16
     if constexpr (QKV) {
         // Fused epilogue of the QKV projection: 32 rows of the fp16 tile (whole heads: the tile width divides
         // the model width and is a multiple of the head size) at a time are staged in LDS by all waves; then
         // every thread takes (row, 8-channel chunk) items, of one chunk, and applies RoPE at the token's position id (q
         // and k tiles) and the 4-bit K/V group quantizer (k and v tiles) exactly as the stand-alone kernel
         // does.  q | k | v are column ranges [0,d) [d,d+dkv) [d+dkv,d+2dkv), so a tile lies in one of them.
-        constexpr int RPI = NT / (BN / 8), KI = 32 / RPI;                // rows of a round of items, rounds
         const MixMul mul;
         f16 *stage = reinterpret_cast<f16 *>(lds_raw);
         const int d = qe.d, dkv = qe.dkv;
         const int region = n0 < d ? 0 : (n0 < d + dkv ? 1 : 2);          // tile-uniform
-        const int half = qe.dh >> 4, c = tid % (BN / 8), row0 = tid / (BN / 8);        // chunks per half head (4 or 8)
+        const int half = qe.dh >> 4, c = c8;                             // chunks per half head (4 or 8)
         const bool second = c & half;
         const int width = region == 0 ? d : dkv, col = n0 - (region == 0 ? 0 : (region == 1 ? d : d + dkv)) + 8 * c;
         f16 *out16 = (region == 0 ? qe.q_rot : region == 1 ? qe.khat : qe.vhat) + (size_t)m0 * width + col;
@@ -406,16 +452,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         f16 *scales = (region == 1 ? qe.k_scales : qe.v_scales) + (((size_t)m0 * width + col) >> 6);
 #pragma unroll
         for (int ib = 0; ib < RT / 2; ++ib) {
-            float cs[KI][8], sn[KI][8];
-            if (region < 2) {
-#pragma unroll
-                for (int k = 0; k < KI; ++k) {
-                    const unsigned at = (unsigned)(row_pos[32 * ib + RPI * k + row0] * 8 * half + 8 * (c & (half - 1)));
-                    *reinterpret_cast<float4 *>(cs[k]) = *reinterpret_cast<const float4 *>(qe.cosT + at);
-                    *reinterpret_cast<float4 *>(cs[k] + 4) = *reinterpret_cast<const float4 *>(qe.cosT + at + 4);
-                    *reinterpret_cast<float4 *>(sn[k]) = *reinterpret_cast<const float4 *>(qe.sinT + at);
-                    *reinterpret_cast<float4 *>(sn[k] + 4) = *reinterpret_cast<const float4 *>(qe.sinT + at + 4);
-                }
+            if (AR > 1 && ib + 1 < ROUNDS) {          // (a round ahead; of 128 x 256 the registers hold one)
+                if (ib == 0) ask_angles(0);
+                ask_angles(ib + 1);
+            } else if (AR == 1 && ROUNDS > 1) {
+                ask_angles(ib);
             }
             if (ib) __syncthreads();                  // the previous 32 rows have been read
 #pragma unroll
@@ -439,7 +480,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
                 out = x;
                 if (region < 2) {
                     xp.u = *reinterpret_cast<const uint4 *>(stage + row * TROW + 8 * (c ^ half));
-                    rope8(x, xp, cs[k], sn[k], second, out, mul);
+                    rope8(x, xp, cs[ib % AR][k], sn[ib % AR][k], second, out, mul);
                 }
                 const unsigned at = (unsigned)(m * width);               // elements from the tile's first row
                 if (region == 0) {
@@ -493,19 +534,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     // 16-byte residual load, one 16-byte store, at any element's address (the chip takes both there; of a branch for tensors at multiples of 16
     // bytes and one for others the compiler made stores of 2, 2 and 12 bytes: 80 x 512 x 512 4.04 -> 3.76 us, 160 x 4096 x 4096 11.0 -> 10.6,
     // 636 x 4096 x 4096 19.9 -> 19.3, 1356 x 12288 x 4096 68.3 -> 65.9)
-    constexpr int RPI = NT / (BN / 8), KI = 32 / RPI;
     float *stage = reinterpret_cast<float *>(lds_raw);
-    const int n = n0 + 8 * (tid % (BN / 8)), row0 = tid / (BN / 8);
+    const int n = n8;
+    if constexpr (EPI == PLAIN && ROUNDS > 1) {
+#pragma unroll
+        for (int ib = 0; ib < ROUNDS; ++ib) ask_residual(ib);
+    }
 #pragma unroll
     for (int ib = 0; ib < RT / 2; ++ib) {
-        f16x8 rv[KI];
-        if (res && n < N) {
-#pragma unroll
-            for (int k = 0; k < KI; ++k) {
-                const f16 *rp = res + (size_t)min(m0 + 32 * ib + RPI * k + row0, M - 1) * ldr + n;
-                rv[k] = *reinterpret_cast<const f16x8_at2 *>(rp);
-            }
-        }
         if (ib) __syncthreads();                      // the previous 32 rows have been read
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -531,9 +567,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             if (!y || m >= M || n >= N) continue;
             f16x8 o;
             if (res) {
-                asm volatile("" : "+v"(rv[k]));       // (else it is converted, and waited for, where it is loaded)
+                asm volatile("" : "+v"(rv[ib][k]));   // (else it is converted, and waited for, where it is loaded)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv[k][e];
+                for (int e = 0; e < 8; ++e) v[e] = v[e] + (float)rv[ib][k][e];
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = to_f16(v[e]);
