@@ -16,7 +16,7 @@ namespace {
 // is multiplied; a stage costs one counted wait and one barrier.  What binds it is the round trip of a stage:
 // two workgroups of 128 x 128 on a CU with one stage on its way each left the waves waiting for 44 % of their
 // lives, and a launch that gives a CU one took as long as two (640 x 4096 x 4096 65 us).  A workgroup that has the
-// CU to itself, 8 waves and two to five stages on their way (one for 256 x 256) does it in 39, and leaves the choice of the tile to the
+// CU to itself, 8 waves and two to five stages on their way (one for 256 and 320 x 256) does it in 39, and leaves the choice of the tile to the
 // number of workgroups.  The next step's fragments are read, and a stage's copies started, between the products of
 // the current one (SPREAD: over how many of the stage's 4 steps; all at once they hold the address unit up: 1280 x 4096 x
 // 11008 178 us with one stage on its way, 160 spread over three steps and two on their way).  1280 rows: 1.06 PFLOP/s at 12288 x 4096,
@@ -316,8 +316,12 @@ int fp_gemm(const f16 *x, int M, int K, const void *W, int N, const f16 *residua
     const auto rounds = [&](int bm, int bn) {
         return (int)(((long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256);
     };
-    const int t64 = 30 * rounds(64, 128), t128 = 38 * rounds(128, 128), t256 = 57 * rounds(128, 256), t512 = 108 * rounds(256, 256);
-    if (t64 <= min(min(t128, t256), t512)) launch(fp_gemm_kernel<2, 4, 1, 1, 6, 3>, 64, 128);
+    const int t64 = 30 * rounds(64, 128), t128 = 38 * rounds(128, 128), t256 = 57 * rounds(128, 256), t512 = 108 * rounds(256, 256),
+              t640 = 118 * rounds(320, 256);
+    // (320 x 256 is no faster a tile, but where its rounds are fewer a launch is: 1280 x 15360 x 5120 on 240 workgroups 177 us, 262 on 300 of 256 x 256,
+    // 1280 x 27648 x 5120 337, 444)
+    if (t640 < min(min(t64, t128), min(t256, t512))) launch(fp_gemm_kernel<2, 4, 5, 2, 2, 1>, 320, 256);
+    else if (t64 <= min(min(t128, t256), t512)) launch(fp_gemm_kernel<2, 4, 1, 1, 6, 3>, 64, 128);
     else if (t128 <= min(t256, t512)) launch(fp_gemm_kernel<2, 4, 2, 1, 4, 3>, 128, 128);
     else if (t256 <= t512) launch(fp_gemm_kernel<2, 4, 2, 2, 3, 3>, 128, 256);
     else launch(fp_gemm_kernel<2, 4, 4, 2, 2, 1>, 256, 256);

@@ -80,9 +80,9 @@ def test_fp_block_against_oracle(qb, d, H, Hkv, dh, F, B, N):
     assert abs(np.linalg.norm(got) / np.linalg.norm(want) - 1.0) < 1e-3
 
 
-@pytest.mark.parametrize("B", [3, 20, 41])
+@pytest.mark.parametrize("B", [3, 20, 41, 49])
 def test_fp_block_tiles_give_the_same_bits(qb, B):
-    """A sequence of 125 tokens alone (64 x 128 tiles) and in a batch, whose 375 to 5125 rows take the other tiles, up to 256 x
+    """A sequence of 125 tokens alone (64 x 128 tiles) and in a batch, whose 375 to 6125 rows take the other tiles, up to 320 x
     256: sums run over the channels in one order in all of them.  1376 channels end inside a stage."""
     d, H, Hkv, dh, F, N = 1024, 8, 8, 128, 1376, 125
     _, _, _, Lf, _, _ = build_pair(d, H, Hkv, dh, F, 2 * N + 8, seed=77)
