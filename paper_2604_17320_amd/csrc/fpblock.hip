@@ -3,12 +3,38 @@
 // deviation norms ||x^q - x||_2 and ||x||_2, and the call that runs a block both ways on one
 // input.  Calibration-time code, outside the deployed forward pass, but a calibration runs it for
 // every layer and sample: its time is the fp16 GEMMs'.
+#include <type_traits>
 #include "common.h"
 #include "internal.h"
 #include "gemm_common.h"
 #include "ldscopy.h"
 
 namespace {
+
+// silu(gate) * up of eight channels
+__device__ __forceinline__ Pack16 silu_mul_fp(Pack16 g, const Pack16 &u)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float gv = (float)g.h[e];
+        g.h[e] = (f16)(gv / (1.0f + expf(-gv)) * (float)u.h[e]);
+    }
+    return g;
+}
+// Rotate-half RoPE of eight channels x of a head, whose partners half a head away are xp; cp, sp: the angles of their pairs
+__device__ __forceinline__ Pack16 rope_fp(Pack16 x, const Pack16 &xp, const float *cp, const float *sp, bool second)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const f32x4 cs = *reinterpret_cast<const f32x4_at4 *>(cp + 4 * i), sn = *reinterpret_cast<const f32x4_at4 *>(sp + 4 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float a = (float)x.h[4 * i + e] * cs[e], b = (float)xp.h[4 * i + e] * sn[e];
+            x.h[4 * i + e] = (f16)(second ? a + b : a - b);
+        }
+    }
+    return x;
+}
 
 // ---- y = x W^T (+ residual): fp16 operands, fp32 accumulation, fp16 result ------------------
 // WM x WN waves cover a tile, each 32 RT x 32 CT of it by v_mfma_f32_32x32x16_f16.  Both operands come to LDS 64
@@ -26,12 +52,23 @@ namespace {
 // step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.
 // Rows beyond M and N repeat the last one and are not stored.  Needs N % 64 == 0, K % 16 == 0, x and W at
 // multiples of 16 bytes; residual and y may lie anywhere.
-template <int WM, int WN, int RT, int CT, int RING, int SPREAD>
+// What is made of the result in front of the store, of its fp16 roundings (as launches of their own RoPE and the SiLU product took 17 us each for 1280
+// rows of the 7B shape and a second trip of q | k | v and gate | up through memory; the block and its low-bit one 1012 -> 994 us):
+struct FpPlain {};                       // nothing
+struct FpSilu {};                        // W's rows are gate | up: y [M][N / 2] = silu(gate) * up, a tile has as many columns of both
+struct FpRope {                          // N is q | k | v: q and k rotated by halves of a head at the tokens' position ids
+    const int32_t *pos;
+    const float *cosT, *sinT;
+    int n_pos, d, dkv, dh;
+    f16 *q, *k, *v;
+};
+template <int WM, int WN, int RT, int CT, int RING, int SPREAD, typename EPI>
 __global__ __launch_bounds__(64 * WM * WN, 2) void fp_gemm_kernel(const f16 *__restrict__ x, int M, int K,
                                                                     const f16 *__restrict__ W, int N,
                                                                     const f16 *__restrict__ residual,
-                                                                    f16 *__restrict__ y, int tiles_m, int tiles_n)
+                                                                    f16 *__restrict__ y, int tiles_m, int tiles_n, EPI epi)
 {
+    constexpr bool SILU = std::is_same_v<EPI, FpSilu>, ROPE = std::is_same_v<EPI, FpRope>;
     constexpr int NW = WM * WN, NT = 64 * NW, BM = 32 * RT * WM, BN = 32 * CT * WN;
     constexpr int KS = 64, PR = KS / 8, STG = (BM + BN) * PR, COPIES = STG / NT;       // a stage in 16-byte pieces, pieces per thread
     constexpr int FROW = BN + 4;                                // floats per staged output row
@@ -49,18 +86,23 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fp_gemm_kernel(const f16 *__r
 #pragma unroll
     for (int j = 0; j < COPIES; ++j) {
         const int r = (tid + NT * j) / PR;
-        row_at[j] = 2u * (unsigned)(r < BM ? min(m0 + r, M - 1) - m0 : min(n0 + r - BM, N - 1) - n0) * (unsigned)K;
+        int w = min(n0 + r - BM, N - 1) - n0;
+        if (SILU) w = min(n0 / 2 + (r - BM) % (BN / 2), N / 2 - 1) - n0 / 2;       // gate rows, then up rows of the same channels
+        row_at[j] = 2u * (unsigned)(r < BM ? min(m0 + r, M - 1) - m0 : w) * (unsigned)K;
         piece[j] = 16 * ((tid & 7) ^ (r & 7));
     }
-    const f16 *xb = x + (size_t)m0 * K, *wb = W + (size_t)n0 * K;
+    const f16 *xb = x + (size_t)m0 * K, *wb = W + (size_t)(SILU ? n0 / 2 : n0) * K;
+    const size_t up = SILU ? (size_t)(N / 2) * K : 0;            // from a gate row to its up row
     const int stages = (K + KS - 1) / KS;
     auto load = [&](int stage, int slot, int from, int to) {
         const int k0 = KS * min(stage, stages - 1);                     // (stages past the end keep the count of copies)
         const unsigned left = 2u * (unsigned)(K - k0) - 16;             // last whole piece of a row (a ragged end repeats it)
 #pragma unroll
-        for (int j = from; j < to; ++j)
-            copy16_to_lds((64 / PR * (wave + NW * j) < BM ? xb : wb) + k0, row_at[j] + min(piece[j], left),
+        for (int j = from; j < to; ++j) {
+            const int first = 64 / PR * (wave + NW * j);                // row of the copy
+            copy16_to_lds((first < BM ? xb : wb) + (k0 + (SILU && first >= BM + BN / 2 ? up : 0)), row_at[j] + min(piece[j], left),
                           lds0 + (unsigned)(slot * STG * 16 + (wave + NW * j) * 1024));
+        }
     };
     f32x16 acc[RT][CT];
 #pragma unroll
@@ -121,23 +163,52 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void fp_gemm_kernel(const f16 *__r
             for (int r = 0; r < 16; ++r)
                 stage[(32 * wm + 8 * (r >> 2) + 4 * half + (r & 3)) * FROW + 32 * CT * wn + 32 * j + l32] = acc[i][j][r];
         __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 32 * WM * (BN / 8) / NT; ++k) {
-            const int idx = k * NT + tid, row = idx / (BN / 8), c = 8 * (idx % (BN / 8));
-            const int m = m0 + 32 * RT * (row >> 5) + 32 * i + (row & 31), n = n0 + c;
-            if (m >= M || n >= N) continue;
-            const float4 lo = *reinterpret_cast<const float4 *>(stage + row * FROW + c);
-            const float4 hi = *reinterpret_cast<const float4 *>(stage + row * FROW + c + 4);
-            float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-            Pack16 o, rv;
-            if (residual) {
-                rv.u = load16_at2(residual + (size_t)m * N + n);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += (float)rv.h[e];
-            }
+        constexpr int WIDTH = SILU ? BN / 2 : BN;               // columns of a row that are stored
+        const int n_at = SILU ? n0 / 2 : n0, n_end = SILU ? N / 2 : N;
+        // eight staged results, and their fp16 roundings
+        auto take = [&](int row, int c, float (&v)[8]) {
+            *reinterpret_cast<float4 *>(v) = *reinterpret_cast<const float4 *>(stage + row * FROW + c);
+            *reinterpret_cast<float4 *>(v + 4) = *reinterpret_cast<const float4 *>(stage + row * FROW + c + 4);
+        };
+        auto rounded = [](const float (&v)[8]) {
+            Pack16 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) o.h[e] = (f16)v[e];
-            store16_at2(y + (size_t)m * N + n, o.u);
+            return o;
+        };
+#pragma unroll
+        for (int k = 0; k < 32 * WM * (WIDTH / 8) / NT; ++k) {
+            const int idx = k * NT + tid, row = idx / (WIDTH / 8), c = 8 * (idx % (WIDTH / 8));
+            const int m = m0 + 32 * RT * (row >> 5) + 32 * i + (row & 31), n = n_at + c;
+            if (m >= M || n >= n_end) continue;
+            float v[8];
+            take(row, c, v);
+            if constexpr (SILU) {
+                float up[8];
+                take(row, c + BN / 2, up);
+                store16_at2(y + (size_t)m * n_end + n, silu_mul_fp(rounded(v), rounded(up)).u);
+            } else if constexpr (ROPE) {
+                Pack16 o = rounded(v);
+                const int hd = epi.dh / 2, in = n & (epi.dh - 1);       // (64 or 128: tiles begin with a head)
+                if (n < epi.d + epi.dkv) {
+                    float w[8];
+                    take(row, in >= hd ? c - hd : c + hd, w);
+                    const int p = min(max(epi.pos[m], 0), epi.n_pos - 1);
+                    o = rope_fp(o, rounded(w), epi.cosT + (size_t)p * hd + in % hd, epi.sinT + (size_t)p * hd + in % hd, in >= hd);
+                }
+                f16 *to = n < epi.d ? epi.q + (size_t)m * epi.d + n
+                                    : (n < epi.d + epi.dkv ? epi.k + (size_t)m * epi.dkv + n - epi.d
+                                                           : epi.v + (size_t)m * epi.dkv + n - epi.d - epi.dkv);
+                *reinterpret_cast<uint4 *>(to) = o.u;
+            } else {
+                if (residual) {
+                    Pack16 rv;
+                    rv.u = load16_at2(residual + (size_t)m * N + n);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] += (float)rv.h[e];
+                }
+                store16_at2(y + (size_t)m * N + n, rounded(v).u);
+            }
         }
     }
 }
@@ -170,60 +241,6 @@ __global__ __launch_bounds__(256) void fp_rmsnorm_kernel(const f16 *__restrict__
         for (int e = 0; e < 8; ++e) v.h[e] = (f16)((float)v.h[e] * inv * g[e >> 2][e & 3]);
         out[c] = v.u;
     }
-}
-
-// ---- rotate-half RoPE of q and k at the tokens' position ids; v is copied --------------------
-// qkv [M][d + 2 dkv] -> q [M][d], k [M][dkv], v [M][dkv].  One thread per 8 channels.
-__global__ __launch_bounds__(256) void fp_rope_kernel(const f16 *__restrict__ qkv, int M, int d, int dkv,
-                                                       int dh, const int32_t *__restrict__ pos,
-                                                       const float *__restrict__ cosT,
-                                                       const float *__restrict__ sinT, int n_pos,
-                                                       f16 *__restrict__ q, f16 *__restrict__ k,
-                                                       f16 *__restrict__ v)
-{
-    const int hd = dh / 2, per_row = (d + 2 * dkv) / 8;
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long)M * per_row) return;
-    const int m = (int)(idx / per_row), c = 8 * (int)(idx % per_row);
-    const f16 *src = qkv + (size_t)m * (d + 2 * dkv);
-    Pack16 x;
-    x.u = *reinterpret_cast<const uint4 *>(src + c);
-    if (c < d + dkv) {                             // 8 rotated channels of q or k
-        const int in = c % dh, i = in % hd;        // place inside the head, first pair
-        const bool second = in >= hd;
-        Pack16 xp;
-        xp.u = *reinterpret_cast<const uint4 *>(src + (second ? c - hd : c + hd));
-        const int p = min(max(pos[m], 0), n_pos - 1);
-        const float *cp = cosT + (size_t)p * hd + i, *sp = sinT + (size_t)p * hd + i;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float a = (float)x.h[e] * cp[e], b = (float)xp.h[e] * sp[e];
-            x.h[e] = (f16)(second ? a + b : a - b);
-        }
-        if (c < d) *reinterpret_cast<uint4 *>(q + (size_t)m * d + c) = x.u;
-        else *reinterpret_cast<uint4 *>(k + (size_t)m * dkv + c - d) = x.u;
-    } else {
-        *reinterpret_cast<uint4 *>(v + (size_t)m * dkv + c - d - dkv) = x.u;
-    }
-}
-
-// ---- z = silu(gate) * up, gu [M][2F] rows gate | up; one thread per 8 channels ------------------
-__global__ __launch_bounds__(256) void fp_silu_mul_kernel(const f16 *__restrict__ gu, long M, int F,
-                                                           f16 *__restrict__ z)
-{
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * (F / 8)) return;
-    const long m = idx / (F / 8);
-    const int f = 8 * (int)(idx % (F / 8));
-    Pack16 g, u;
-    g.u = *reinterpret_cast<const uint4 *>(gu + m * 2 * F + f);
-    u.u = *reinterpret_cast<const uint4 *>(gu + m * 2 * F + F + f);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const float gv = (float)g.h[e];
-        g.h[e] = (f16)(gv / (1.0f + expf(-gv)) * (float)u.h[e]);
-    }
-    *reinterpret_cast<uint4 *>(z + m * F + f) = g.u;
 }
 
 // ---- Eq. 1 per sample: ||x^q - x||_2 and ||x||_2 over the n values of sample blockIdx.x --------
@@ -305,11 +322,12 @@ int deviation(const f16 *xq, const f16 *x, int B, long n, double *part, double *
 
 inline size_t up256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-int fp_gemm(const f16 *x, int M, int K, const void *W, int N, const f16 *residual, f16 *y, hipStream_t st)
+template <typename EPI = FpPlain>
+int fp_gemm(const f16 *x, int M, int K, const void *W, int N, const f16 *residual, f16 *y, hipStream_t st, const EPI &epi = {})
 {
     const auto launch = [&](auto kernel, int bm, int bn) {
         const int tiles_m = (M + bm - 1) / bm, tiles_n = (N + bn - 1) / bn;
-        kernel<<<dim3(tiles_m * tiles_n), dim3(512), 0, st>>>(x, M, K, (const f16 *)W, N, residual, y, tiles_m, tiles_n);
+        kernel<<<dim3(tiles_m * tiles_n), dim3(512), 0, st>>>(x, M, K, (const f16 *)W, N, residual, y, tiles_m, tiles_n, epi);
     };
     // By rounds of 256 workgroups, in us for 4096 channels (measured over 64 to 2560 rows, 4096 to 22016 columns and both
     // depths of a 7B block: a round of the smaller tiles is shorter by less than they are smaller)
@@ -320,11 +338,11 @@ int fp_gemm(const f16 *x, int M, int K, const void *W, int N, const f16 *residua
               t640 = 118 * rounds(320, 256);
     // (320 x 256 is no faster a tile, but where its rounds are fewer a launch is: 1280 x 15360 x 5120 on 240 workgroups 177 us, 262 on 300 of 256 x 256,
     // 1280 x 27648 x 5120 337, 444)
-    if (t640 < min(min(t64, t128), min(t256, t512))) launch(fp_gemm_kernel<2, 4, 5, 2, 2, 1>, 320, 256);
-    else if (t64 <= min(min(t128, t256), t512)) launch(fp_gemm_kernel<2, 4, 1, 1, 6, 3>, 64, 128);
-    else if (t128 <= min(t256, t512)) launch(fp_gemm_kernel<2, 4, 2, 1, 4, 3>, 128, 128);
-    else if (t256 <= t512) launch(fp_gemm_kernel<2, 4, 2, 2, 3, 3>, 128, 256);
-    else launch(fp_gemm_kernel<2, 4, 4, 2, 2, 1>, 256, 256);
+    if (t640 < min(min(t64, t128), min(t256, t512))) launch(fp_gemm_kernel<2, 4, 5, 2, 2, 1, EPI>, 320, 256);
+    else if (t64 <= min(min(t128, t256), t512)) launch(fp_gemm_kernel<2, 4, 1, 1, 6, 3, EPI>, 64, 128);
+    else if (t128 <= min(t256, t512)) launch(fp_gemm_kernel<2, 4, 2, 1, 4, 3, EPI>, 128, 128);
+    else if (t256 <= t512) launch(fp_gemm_kernel<2, 4, 2, 2, 3, 3, EPI>, 128, 256);
+    else launch(fp_gemm_kernel<2, 4, 4, 2, 2, 1, EPI>, 256, 256);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -343,7 +361,7 @@ int check_fp_layer(const quota_fp_layer *L, int B, int N)
 }
 
 struct FpWs {
-    f16 *h, *qkv, *q, *k, *v, *o, *x1, *gu, *z;
+    f16 *h, *q, *k, *v, *o, *x1, *z;
     void *attn;
     size_t bytes;
 };
@@ -356,13 +374,11 @@ FpWs carve_fp(void *ws, const quota_fp_layer *L, int B, int N)
     FpWs w;
     auto take = [&](size_t bytes) { void *r = p; p += up256(bytes); return r; };
     w.h = (f16 *)take(M * d * 2);
-    w.qkv = (f16 *)take(M * (d + 2 * dkv) * 2);
     w.q = (f16 *)take(M * d * 2);
     w.k = (f16 *)take(M * dkv * 2);
     w.v = (f16 *)take(M * dkv * 2);
     w.o = (f16 *)take(M * d * 2);
     w.x1 = (f16 *)take(M * d * 2);
-    w.gu = (f16 *)take(M * 2 * F * 2);
     w.z = (f16 *)take(M * F * 2);
     w.attn = take(quota_attention_workspace_bytes(B, N, L->H, L->dh));
     w.bytes = (size_t)(p - start) + QUOTA_WS_SLACK;
@@ -391,21 +407,15 @@ extern "C" int quota_fp_block(const quota_fp_layer *L, const void *x_f16, const 
 
     fp_rmsnorm_kernel<<<dim3(M), dim3(256), 0, st>>>(x, d, L->gamma1, L->eps, w.h);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
-    if ((rc = fp_gemm(w.h, M, d, L->wqkv, d + 2 * dkv, nullptr, w.qkv, st)) != QUOTA_OK) return rc;
-    const long pieces = (long)M * ((d + 2 * dkv) / 8);
-    fp_rope_kernel<<<dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st>>>(
-        w.qkv, M, d, dkv, dh, pos, L->cosT, L->sinT, L->n_pos, w.q, w.k, w.v);
-    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    const FpRope rope = {pos, L->cosT, L->sinT, L->n_pos, d, dkv, dh, w.q, w.k, w.v};
+    if ((rc = fp_gemm(w.h, M, d, L->wqkv, d + 2 * dkv, nullptr, nullptr, st, rope)) != QUOTA_OK) return rc;
     if ((rc = quota_attention_prefill_gqa(w.q, w.k, w.v, B, N, H, Hkv, dh, 0, 0, w.o, nullptr, nullptr, w.attn,
                                           stream)) != QUOTA_OK)
         return rc;
     if ((rc = fp_gemm(w.o, M, d, L->wo, d, x, w.x1, st)) != QUOTA_OK) return rc;
     fp_rmsnorm_kernel<<<dim3(M), dim3(256), 0, st>>>(w.x1, d, L->gamma2, L->eps, w.h);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
-    if ((rc = fp_gemm(w.h, M, d, L->wgu, 2 * F, nullptr, w.gu, st)) != QUOTA_OK) return rc;
-    const long nz = (long)M * (F / 8);
-    fp_silu_mul_kernel<<<dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st>>>(w.gu, M, F, w.z);
-    QUOTA_RETURN_IF_LAUNCH_FAILED();
+    if ((rc = fp_gemm(w.h, M, d, L->wgu, 2 * F, nullptr, w.z, st, FpSilu{})) != QUOTA_OK) return rc;
     return fp_gemm(w.z, M, F, L->wdown, d, w.x1, (f16 *)x_out_f16, st);
 }
 

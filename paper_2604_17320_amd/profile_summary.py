@@ -70,8 +70,6 @@ CLASSES = [
     ("pack_weights_kernel", "pack_weights"),
     ("fp_gemm_kernel", "fp_gemm"),
     ("fp_rmsnorm_kernel", "fp_rmsnorm"),
-    ("fp_rope_kernel", "fp_rope"),
-    ("fp_silu_mul_kernel", "fp_silu_mul"),
     ("deviation_finish_kernel", "deviation_finish"),
     ("deviation_kernel", "deviation"),
     ("advance_step_kernel", "advance_step"),
