@@ -113,6 +113,9 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     auto piece_of = [](int p, int row) { return p ^ (0x1320 >> (row & 12) & 3); };
     unsigned oa[PACKED ? LA : 1], om = 0, ot = 0;        // byte offsets of this thread's pieces, in group 0 or (A6) a group
     unsigned om2 = 0, dm = 0, dt = 0;                    // ... and where its wave's pieces go in LDS
+    // (96 rows: the blocks that a wave copies come round in threes, and change groups in between)
+    constexpr bool THREES = BB % NW != 0 && NW % BB != 0;
+    unsigned om3[THREES ? 3 : 1], ot3[THREES ? 3 : 1];
     int la[LA ? LA : 1], lt[LA ? LA : 1], pa[LA ? LA : 1];       // PACKED: LDS slots (16 bytes, 8 bytes) of the piece
     // (threads without one write a spare slot: a branch would let the compiler sink the scale chain behind it)
     if constexpr (PACKED) {
@@ -126,7 +129,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
         }
     } else {
         // A copy of first parts: lane l brings row l / 4 of 16 to piece l % 4; of second ones: row l / 2 of 32 to half l % 2
-        static_assert(BB <= 2 * NW && (BB % NW == 0 || NW % BB == 0) && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
+        static_assert(THREES ? BB == 6 && NW == 4 : BB <= 2 * NW && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
         const int last = fours - 1 - (m0 >> 2), row = lane >> 2, row2 = lane >> 1;
         const unsigned at = (row & 3) * 64 + 16 * piece_of(lane & 3, row);
         om = (unsigned)min(4 * (wave % BB) + (row >> 2), last) * four_bytes + at + wave / BB % NW * 384;
@@ -135,6 +138,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
              wave / TB % NW * 384;
         dm = lds0 + wave / BB % NW * (AST * 16) + wave % BB * 1024;
         dt = lds0 + wave / TB % NW * (AST * 16) + BM * 64 + wave % TB * 1024;
+        if constexpr (THREES) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                om3[j] = (unsigned)min(4 * ((wave + NW * j) % BB) + (row >> 2), last) * four_bytes + at;
+                ot3[j] = (unsigned)min(8 * ((wave + NW * j) % TB) + (row2 >> 2), last) * four_bytes + 256 + (row2 & 3) * 32 +
+                         16 * ((lane ^ row2 >> 3) & 1);
+            }
+        }
     }
     // SILU: columns are gate | up, F = N / 2 of each, and a tile takes BN / 2 of either: a wave's first CT / 2 blocks are gate
     // columns, the others up columns of the same channels.
@@ -194,7 +205,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
             if (r == LG - 1) wnext = (const uint4 *)((const char *)wnext + (G - gstage > c + 1 ? wstep : 0u));
         } else if (k < LC) {
             const int j = k - CH * LG;
-            if (j < MC) {                                // block wave + NW j of the stage's, BB to a group
+            if constexpr (THREES) {
+                const bool first = j < MC;
+                const int i = first ? j : j - MC, n = first ? BB : TB, blk = wave + NW * i, c = blk / n, b = blk % n;
+                copy16_to_lds(a0 + c * 384, first ? om3[i % 3] : ot3[i % 3],
+                              lds0 + (to + (unsigned)(c * (AST * 16) + b * 1024 + (first ? 0 : BM * 64))));
+            } else if (j < MC) {                                // block wave + NW j of the stage's, BB to a group
                 const int c = BB >= NW ? j * NW / BB : j * (NW / BB), b = BB >= NW ? j * NW % BB : 0;
                 copy16_to_lds(a0 + c * 384, BB > NW && j % 2 ? om2 : om, dm + (to + (unsigned)(c * AST * 16 + b * 1024)));
             } else {
@@ -601,12 +617,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 // 12288 x 4096 47, 41; 1600 x 4096 x 4096 43, 38; a layer's rows do better on 128 x 128).
 #define F8_PACKED_TILE(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>
 
+// 96 x 128, a layer's rows below 512 only, not pinned, up to two workgroups per CU: 129 to 192 rows are two of it and three of 64 x 128, which at 22016 columns
+// are 516 workgroups, three for a few CUs (160 x 22016 x 4096 25.2 -> 23.2 us, 160 x 27648 x 5120 31.8 -> 27.6), 320 to 444 rows four and five to seven
+// (384 x 12288 x 4096 27.2 -> 24.7; at 224 rows, three and four, 20.6 against 24.3).  Stages of four groups leave room for two workgroups.
+#define F8_TILE_7(P, A, QK) w4a4_f8_kernel<6, 2, 4, 4, 4, P, A, QK, 2>  // 96 x 128
+
 struct TileShape { int bm, bn, nt, kernel_id; };
-constexpr int TILES = 7, PINNED_TILES = 5, LAYER_TILES = 6;
+constexpr int TILES = 8, PINNED_TILES = 5, PACKED_TILE = 6;
 const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128, 256, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
                              {128, 256, 256, QUOTA_K_GEMM_128X256}, {32, 64, 256, QUOTA_K_GEMM_32X64},
-                             {64, 256, 256, QUOTA_K_GEMM_64X256}};
+                             {64, 256, 256, QUOTA_K_GEMM_64X256}, {96, 128, 256, QUOTA_K_GEMM_OTHER}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, quota_qkv_epilogue);
@@ -625,6 +646,9 @@ f8_kernel tile_kernel(int v)
     case 5:
         if constexpr (P != A6 || E == SILU_MUL) return nullptr;
         else return F8_TILE_5(P, false, E);
+    case 7:
+        if constexpr (P != A6) return nullptr;
+        else return F8_TILE_7(P, false, E);
     default:
         if constexpr (P != PACKED_INT4) return nullptr;
         else return F8_PACKED_TILE(P, false, E);
@@ -656,7 +680,8 @@ int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set
 
 // Tile choice by cost models fitted to measured kernel times on this GPU (us, over weights that no cache holds), one for a layer's rows
 // (112 shapes of 40 to 11776 rows, 512 to 37888 columns and 512 to 18944 channels; the 32 x 64 tile's line, which has changed since, by 270
-// of 33 to 511 rows and of narrow layers, where the choice costs 0.6 % over the best tile of each on average, 2.3 % with the line before) and one for
+// of 33 to 511 rows and of narrow layers, where the choice costs 0.6 % over the best tile of each on average, 2.3 % with the line before; the 96 x 128 tile's by
+// launches of 160 to 444 rows) and one for
 // packed rows, whose stages are shorter and tiles others (412 shapes of 33 to 11776 rows; 0.2 % on average, 10 % at most, where two tiles tie over
 // cold weights the one that is ahead over warm ones; by a layer's, without the
 // 64 x 256 tile, 3.7 %: 5808 x 4096 x 11008 301 us, 236 so).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
@@ -668,13 +693,15 @@ int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set
 int choose_tile(ActFormat acts, int M, int N, int K, int min_bn, int max_bn, float narrow = 0.0f)
 {
     struct Cost { int ch; float c0, wg; int n; float u[6], slope, round; int occ; };
-    static const Cost layer[LAYER_TILES] = {
+    static const Cost layer[TILES] = {
         {2, 5.09f, 0.0f, 6, {0.559f, 0.764f, 1.159f, 1.816f, 1.906f, 2.348f}, 0.311f, 0.255f, 3},
         {4, 4.37f, 0.0f, 6, {0.305f, 0.447f, 0.730f, 1.060f, 1.266f, 1.588f}, 0.192f, 0.174f, 3},
         {4, 3.62f, 0.0f, 4, {0.252f, 0.343f, 0.550f, 0.819f}, 0.132f, 0.150f, 3},
         {4, 3.60f, 0.0f, 4, {0.181f, 0.200f, 0.335f, 0.468f}, 0.120f, 0.042f, 4},
         {2, 6.52f, 0.0f, 4, {0.840f, 1.190f, 2.370f, 2.580f}, 0.430f, 0.577f, 2},
         {8, 3.45f, 0.0f, 3, {0.148f, 0.220f, 0.360f}, 0.125f, 0.039f, 3},
+        {},
+        {4, 4.70f, 0.0f, 2, {0.490f, 0.610f}, 0.300f, 0.300f, 2},
     };
     static const Cost packed[TILES] = {
         {2, 4.519f, 2.113f, 4, {0.774f, 1.038f, 1.800f, 2.136f}, 0.305f, 0.453f, 2},
@@ -687,7 +714,7 @@ int choose_tile(ActFormat acts, int M, int N, int K, int min_bn, int max_bn, flo
     };
     const Cost *cost = acts == PACKED_INT4 ? packed : layer;
     auto fits = [&](int v) {
-        const bool built = v < PINNED_TILES || (v < LAYER_TILES ? acts == A6 : acts == PACKED_INT4);
+        const bool built = v < PINNED_TILES || acts == (v == PACKED_TILE ? PACKED_INT4 : A6);
         return built && kTiles[v].bn >= min_bn && kTiles[v].bn <= max_bn;
     };
     if (g_gemm_variant >= 0 && fits(g_gemm_variant)) return g_gemm_variant;

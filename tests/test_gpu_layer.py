@@ -391,10 +391,10 @@ def test_layer_silu_product_in_the_gate_up_projection(qb, tile, F, Nt, K, pinned
 
 
 @pytest.mark.parametrize("d,dh,F,N", [(2048, 128, 2048, 480), (2048, 128, 2048, 641), (1024, 128, 1376, 1000), (1024, 64, 1376, 100),
-                                      (1024, 64, 96, 33)])
+                                      (1024, 64, 96, 33), (1152, 128, 11008, 132), (1152, 128, 11008, 170), (4096, 128, 1376, 331)])
 def test_layer_tiles_in_long_stages(qb, d, dh, F, N, pinned_gemm):
     """The tiles of the choice, in stages of four groups, with and without start values, and 32 x 64 in stages of eight, which
-    only the choice takes (100 and 33 rows), over whole and ragged numbers of groups: the bits of the pinned 128 x 128 tile."""
+    only the choice takes (100 and 33 rows), as it does 96 x 128 (gate/up of 22016 columns, QKV of 12288), over whole and ragged numbers of groups: the bits of the pinned 128 x 128 tile."""
     from paper_2604_17320_amd.model import KVCache4
     shape = wl.Shape("stages", d=d, H=d // dh, F=F, layers=1, B=1, Nv=N - 8, Nt=8, n_outlier=4, vis_begin=0)
     W, L, cos, sin = build_layer(shape, 9)
