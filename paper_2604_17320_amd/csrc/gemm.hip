@@ -620,7 +620,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 // 96 x 128, a layer's rows below 512 only, not pinned, up to two workgroups per CU: 129 to 192 rows are two of it and three of 64 x 128, which at 22016 columns
 // are 516 workgroups, three for a few CUs (160 x 22016 x 4096 25.2 -> 23.2 us, 160 x 27648 x 5120 31.8 -> 27.6), 320 to 444 rows four and five to seven
 // (384 x 12288 x 4096 27.2 -> 24.7; at 224 rows, three and four, 20.6 against 24.3).  Stages of four groups leave room for two workgroups.
-#define F8_TILE_7(P, A, QK) w4a4_f8_kernel<6, 2, 4, 4, 4, P, A, QK, 2>  // 96 x 128
+#define F8_96_ROW_TILE(P, A, QK) w4a4_f8_kernel<6, 2, 4, 4, 4, P, A, QK, 2>  // 96 x 128
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 constexpr int TILES = 8, PINNED_TILES = 5, PACKED_TILE = 6;
@@ -648,7 +648,7 @@ f8_kernel tile_kernel(int v)
         else return F8_TILE_5(P, false, E);
     case 7:
         if constexpr (P != A6) return nullptr;
-        else return F8_TILE_7(P, false, E);
+        else return F8_96_ROW_TILE(P, false, E);
     default:
         if constexpr (P != PACKED_INT4) return nullptr;
         else return F8_PACKED_TILE(P, false, E);
