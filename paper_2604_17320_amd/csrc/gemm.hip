@@ -60,8 +60,8 @@ namespace {
 // are swapped in rows 8 to 15 of 16, so that the lanes of a read do not share banks.
 enum ActFormat { A6, A6_STARTS, PACKED_INT4 };
 enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL };
-template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
-__global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
+template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI>
+__device__ __forceinline__ void w4a4_tile(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
     const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
@@ -594,6 +594,24 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     }
 }
 
+template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
+__global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
+    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
+    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
+    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
+{
+    w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, qe);
+}
+// The tile of 96 rows, which only the choice takes, under a name of its own: profiles tell it by that from the tiles that can be pinned.
+template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
+__global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows96_kernel(
+    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
+    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
+    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
+{
+    w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, qe);
+}
+
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
 //                                            RT CT NW CH SP          OCC
 // 128 x 128 as waves of 128 x 32: three workgroups per CU, so that a launch's last round is finer than with 128 x 256 (5808 x
@@ -620,7 +638,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 // 96 x 128, a layer's rows below 512 only, not pinned, up to two workgroups per CU: 129 to 192 rows are two of it and three of 64 x 128, which at 22016 columns
 // are 516 workgroups, three for a few CUs (160 x 22016 x 4096 25.2 -> 23.2 us, 160 x 27648 x 5120 31.8 -> 27.6), 320 to 444 rows four and five to seven
 // (384 x 12288 x 4096 27.2 -> 24.7; at 224 rows, three and four, 20.6 against 24.3).  Stages of four groups leave room for two workgroups.
-#define F8_96_ROW_TILE(P, A, QK) w4a4_f8_kernel<6, 2, 4, 4, 4, P, A, QK, 2>  // 96 x 128
+#define F8_96_ROW_TILE(P, A, QK) w4a4_rows96_kernel<6, 2, 4, 4, 4, P, A, QK, 2>  // 96 x 128
 
 struct TileShape { int bm, bn, nt, kernel_id; };
 constexpr int TILES = 8, PINNED_TILES = 5, PACKED_TILE = 6;
