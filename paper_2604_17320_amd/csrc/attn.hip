@@ -254,7 +254,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
 // One workgroup per 128 visual keys of a (sequence, head); wave w of a group of four owns the 32 keys kb .. kb+31.
 // The first key block meets every query tile, a chain that bounds launches of few workgroups: there G = 2 groups take the tiles in
 // turn, each through LDS of its own, and the second's sums are added to the first's (32 heads, 165 / 400 / 640 tokens 10.3 / 15.2 / 16.6 ->
-// 9.3 / 13.2 / 13.1 us, 28 heads, 1101 tokens 25.7 -> 18.9; four groups take longer below a thousand tokens).
+// 9.3 / 13.2 / 13.1 us, 28 heads, 1101 tokens 25.7 -> 18.9; four groups take longer below a thousand tokens).  A group alone keeps two
+// pairs of sums, which its tiles add to in turn: a sequence has the same masses however many share its launch (4 x 2944 tokens,
+// 40 heads 237.7 us with one pair, 239.1 so, 16 x 704 0.2 more; the two turns inlined instead of the sums exchanged: 32 x 80 tokens, 8 heads 7.1 -> 7.9).
 template <int DH>
 constexpr size_t colmass_lds(int G) { return (size_t)G * 2 * (KT * DH * 2 + KT * 4) + (G - 1) * 128 * sizeof(float2); }
 template <int DH, int G, typename PRE>
@@ -299,10 +301,19 @@ __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 1) void colmass_kernel(
 #pragma unroll
     for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
     asm volatile("" : "+v"(zero));
-    float acc_txt = 0.0f, acc_vis = 0.0f;
+    float acc_txt = 0.0f, acc_vis = 0.0f, other_txt = 0.0f, other_vis = 0.0f;      // G = 1: other: of the tiles before and behind this one
+    auto next_sums = [&] {
+        if constexpr (G == 1) {
+            const float txt = acc_txt, vis = acc_vis;
+            acc_txt = other_txt;
+            acc_vis = other_vis;
+            other_txt = txt;
+            other_vis = vis;
+        }
+    };
     const int q_at = piece_address<DH>(l32, hl);
     int buf = 0;
-    for (int qg0 = qt_first; qg0 < N; qg0 += G * KT, buf ^= 1) {
+    for (int qg0 = qt_first; qg0 < N; qg0 += G * KT, buf ^= 1, next_sums()) {
         drain();
         __syncthreads();
         const int qt0 = qg0 + grp * KT;
@@ -369,6 +380,9 @@ __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 1) void colmass_kernel(
             acc_txt += v.x;
             acc_vis += v.y;
         }
+    } else {
+        acc_txt += other_txt + __shfl_xor(other_txt, 32, 64);
+        acc_vis += other_vis + __shfl_xor(other_vis, 32, 64);
     }
     if (key_ok && hl == 0) partial[((size_t)b * H + h) * Nv + (key - vis_begin)] = make_float2(acc_txt, acc_vis);
 }
@@ -443,7 +457,7 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if (cues) {
         const unsigned n2 = (unsigned)((Nv + 127) / 128) * H * B;
-        // two groups where every workgroup has a CU to itself, or half of one and a chain of eight tiles (2 x 640 tokens, 32 heads 18.7 -> 16.6 us, 8 x 300
+        // two groups (the same sums) where every workgroup has a CU to itself, or half of one and a chain of eight tiles (2 x 640 tokens, 32 heads 18.7 -> 16.6 us, 8 x 300
         // 16.4 -> 16.5, 4 x 640 as it was)
         const bool split = n2 <= (N >= 512 ? 512u : 256u);
         const auto s2 = weights ? weights->take(n2, 3.0f + 1.1f * (float)((N + 63) / 64), 3.5f) : PrefetchList::Share{};

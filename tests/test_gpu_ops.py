@@ -467,6 +467,31 @@ def test_column_masses_by_groups(qb, B, N, H, dh, vb, Nv):
     assert np.allclose(host(cv), cv_ref, rtol=2e-5, atol=1e-7)
 
 
+# (from 512 tokens on a launch of more than 512 workgroups, one per head and 128 visual keys, has one group of waves a workgroup, before from
+# 256; the sequence alone has two groups)
+@pytest.mark.parametrize("N,H,dh,vb,Nv,B", [(300, 8, 64, 14, 250, 17), (193, 6, 128, 0, 193, 22), (520, 8, 64, 60, 390, 17),
+                                            (643, 8, 128, 3, 577, 13), (705, 6, 64, 100, 600, 18)])
+def test_cues_of_a_sequence_do_not_depend_on_the_others(qb, N, H, dh, vb, Nv, B):
+    """The masses of a sequence in a batch have the bits of the same sequence alone, whichever form of the cue pass a launch takes."""
+    d, per = H * dh, H * ((Nv + 127) // 128)
+    most = 512 if N >= 512 else 256
+    assert per <= most < per * B                     # (the two forms)
+    q = dev(_act(B * N, d, 64, 1.0))
+    khat, vhat = (dev(oracle.kv_quant(_act(B * N, d, seed, 1.0))[2]) for seed in (65, 66))
+
+    def cues(first, n):
+        rows = slice(first * N, (first + n) * N)
+        o = torch.empty((n * N, d), dtype=torch.float16, device="cuda")
+        ci, cv = (torch.full((n, Nv), -1.0, dtype=torch.float32, device="cuda") for _ in range(2))
+        ws = torch.empty(qb.quota_attention_workspace_bytes(n, N, H, dh), dtype=torch.uint8, device="cuda")
+        qb.quota_attention_prefill(q[rows], khat[rows], vhat[rows], n, N, H, dh, vb, Nv, o, ci, cv, ws)
+        return host(ci), host(cv)
+    batch = cues(0, B)
+    for b in (0, B // 2, B - 1):
+        for got, alone in zip(batch, cues(b, 1)):
+            assert np.array_equal(got[b].view(np.uint32), alone[0].view(np.uint32))
+
+
 # -------------------------------------------------------- score and top-k
 def _metrics(B, Nv, seed):
     r = wl.rng(seed, "metrics", B, Nv)
