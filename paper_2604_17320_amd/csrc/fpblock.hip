@@ -11,13 +11,13 @@
 
 namespace {
 
-// silu(gate) * up of eight channels
+// silu(gate) * up of eight channels, the product rounded to fp32 and that to fp16
 __device__ __forceinline__ Pack16 silu_mul_fp(Pack16 g, const Pack16 &u)
 {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const float gv = (float)g.h[e];
-        g.h[e] = (f16)(gv / (1.0f + expf(-gv)) * (float)u.h[e]);
+        g.h[e] = to_f16(gv / (1.0f + expf(-gv)) * (float)u.h[e]);
     }
     return g;
 }
