@@ -316,7 +316,7 @@ __device__ __forceinline__ void w4a4_tile(
     }
     // The first stage's weights are here before the barrier: left alone the compiler starts them behind it, and the waits for them, which it puts into
     // the loop and counts without the copies, wait there for loads of the next stage that have just been started (64 x 128 tile, 1101 x 3584 x
-    // 18944: main loop 113900 -> 111400 cycles).
+    // 18944: main loop 113900 -> 111400 cycles; 128 x 128, 1700 x 4096 x 4096 29.5 -> 28.5 us, 640 x 12288 x 4096 35.0 -> 34.4; the 32-row tiles as before).
     if constexpr (!ACC_OUT) {
 #pragma unroll
         for (int c = 0; c < CH; ++c)
@@ -327,10 +327,12 @@ __device__ __forceinline__ void w4a4_tile(
     store_packed(0);
     __syncthreads();
 
-    // What the epilogue needs from memory for 32 rows (round ib): a thread has row RPI * k + row0 of them, and 8 channels.  Tiles of one round ask for it
-    // here, a main loop ahead, the others in front of the epilogue for all residual rows and for the angles a round ahead: asked for round by round,
-    // each waited for memory (with the weights above, layers replayed: 512 channels, 16 x 80 tokens 63.2 -> 62.8 us, 7B shape, 165 / 320 tokens 117.5 /
-    // 148.2 -> 116.5 / 147.5, 13B, 400 tokens 195.2 -> 193.3, grouped-query, 1101 tokens 277.6 -> 276.4).
+    // What the epilogue needs from memory for 32 rows (round ib): a thread has row RPI * k + row0 of them, and 8 channels.  Asked for round by round,
+    // each waited for memory.  The residual rows of tiles of one round come a main loop ahead (100 x 3584 x 18944 28.35 -> 28.11 us, 80 x 512 x 512
+    // 3.11 -> 3.04), except of packed rows, whose 32 x 128 tile the registers would cost one of three workgroups per CU (450 x 3584 x 18944 73.1 -> 75.0).
+    // Else all rounds' are asked for in front of the epilogue, and the angles a round ahead (300 x 12288 x 4096 23.3 -> 23.1).  Angles held through the
+    // main loop, 16 registers a row, take a workgroup per CU from 32 x 128 (three) and 32 x 64 (five) and give nothing where there is room (1400 x 1536 x
+    // 512 9.6 us, 7.8 without, 100 x 6144 x 2048 7.2, 6.9).
     constexpr int RPI = NT / (BN / 8), KI = 32 / RPI, ROUNDS = RT / 2, AR = !QKV ? 1 : KI <= 2 && ROUNDS > 1 ? 2 : 1;
     const int row0 = tid / (BN / 8), c8 = tid % (BN / 8), n8 = n0 + 8 * c8;
     float cs[AR][QKV ? KI : 1][8], sn[AR][QKV ? KI : 1][8];
@@ -360,10 +362,8 @@ __device__ __forceinline__ void w4a4_tile(
             }
         }
     };
-    if constexpr (ROUNDS == 1) {
-        if constexpr (QKV) ask_angles(0);
-        if constexpr (EPI == PLAIN) ask_residual(0);
-    }
+    constexpr bool AHEAD = EPI == PLAIN && ROUNDS == 1 && !PACKED;
+    if constexpr (AHEAD) ask_residual(0);
 
     i32x8 fb[CT];
     const int stages = (G + CH - 1) / CH;
@@ -471,7 +471,7 @@ __device__ __forceinline__ void w4a4_tile(
             if (AR > 1 && ib + 1 < ROUNDS) {          // (a round ahead; of 128 x 256 the registers hold one)
                 if (ib == 0) ask_angles(0);
                 ask_angles(ib + 1);
-            } else if (AR == 1 && ROUNDS > 1) {
+            } else if (AR == 1) {
                 ask_angles(ib);
             }
             if (ib) __syncthreads();                  // the previous 32 rows have been read
@@ -552,7 +552,7 @@ __device__ __forceinline__ void w4a4_tile(
     // 636 x 4096 x 4096 19.9 -> 19.3, 1356 x 12288 x 4096 68.3 -> 65.9)
     float *stage = reinterpret_cast<float *>(lds_raw);
     const int n = n8;
-    if constexpr (EPI == PLAIN && ROUNDS > 1) {
+    if constexpr (EPI == PLAIN && !AHEAD) {
 #pragma unroll
         for (int ib = 0; ib < ROUNDS; ++ib) ask_residual(ib);
     }

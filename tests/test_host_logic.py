@@ -5,9 +5,11 @@ import csv
 import glob
 import os
 import re
+import struct
 import subprocess
 import sys
 
+import msgpack
 import numpy as np
 
 from paper_2604_17320_amd import profile_summary as ps, workloads as wl
@@ -92,6 +94,53 @@ def test_profile_summary_classes_of_the_built_gemm_tiles():
         assert ps.classify(name) == want, name
         seen.add(want)
     assert seen == {"w4a4_gemm_other"} | {f"w4a4_gemm_{t}" for t in ("128x128", "64x128", "32x128", "32x64", "128x256", "64x256")}
+
+
+def kernel_resources(path):
+    """{kernel name: its metadata} of the gfx950 code objects inside a library built here."""
+    with open(path, "rb") as f:
+        data = f.read()
+    kernels = {}
+    for m in re.finditer(b"\x7fELF\x02\x01\x01\x40", data):                       # (0x40: the AMD HSA ABI)
+        elf = data[m.start():]
+        at, size, n = struct.unpack_from("<Q", elf, 40)[0], *struct.unpack_from("<HH", elf, 58)
+        for i in range(n):
+            kind, = struct.unpack_from("<I", elf, at + size * i + 4)
+            first, length = struct.unpack_from("<QQ", elf, at + size * i + 24)
+            while kind == 7 and length >= 12:                                       # notes
+                name, desc, note = struct.unpack_from("<III", elf, first)
+                body = first + 12 + (name + 3 & ~3)
+                if note == 32:                                                      # AMDGPU metadata
+                    for k in msgpack.unpackb(elf[body:body + desc])["amdhsa.kernels"]:
+                        kernels[k[".name"]] = k
+                step = 12 + (name + 3 & ~3) + (desc + 3 & ~3)
+                first, length = first + step, length - step
+    return kernels
+
+
+def workgroups_per_cu(k):
+    """Resident workgroups of four waves, one per SIMD: 512 registers a lane of a SIMD in eights, 160 KB of LDS."""
+    by_registers = min(8, 512 // (k[".vgpr_count"] + 7 & ~7))
+    lds = k[".group_segment_fixed_size"]
+    return min(by_registers, 160 * 1024 // lds)
+
+
+def test_gemm_tiles_leave_room_for_the_workgroups_that_their_choice_counts_on():
+    """The choice of a tile goes by times that were measured with so many of its workgroups on a CU: one fewer, for a few registers more, and
+    launches of more workgroups take a fifth longer."""
+    from paper_2604_17320_amd import binding
+    room = {"8ELi2": 3, "4ELi2": 3, "2ELi2": 3, "2ELi1": 5, "8ELi4": 2, "6ELi2": 2}         # a layer's rows; row and column blocks of a wave
+    packed = {"8ELi2": 2, "4ELi2": 3, "2ELi2": 3, "2ELi1": 4, "8ELi4": 2, "4ELi4": 2}
+    seen = set()
+    for name, k in kernel_resources(binding.LIB_PATH).items():
+        m = re.search(r"w4a4_(?:f8|rows96)_kernelILi(\d+ELi\d+)ELi4ELi(\d+)E\w*?ActFormatE(\d)E", name)
+        if not m:
+            continue
+        blocks, stage, acts = m.groups()
+        want = packed[blocks] if acts == "2" else 3 if (blocks, stage) == ("2ELi1", "8") else room[blocks]
+        assert workgroups_per_cu(k) >= want, (name, k[".vgpr_count"], k[".group_segment_fixed_size"])
+        seen.add((blocks, acts == "2"))
+    assert seen == {(b, False) for b in room} | {(b, True) for b in packed}
 
 
 def test_profile_summary_stats_table(tmp_path, capsys):
