@@ -501,7 +501,8 @@ int quota_decode_layer(const quota_layer *L, const void *x_f16,
 
 /* Kernel classes the library launches.  The GEMM is split by tile shape
  * because each shape is a separate kernel (and a separate profiler row).
- * (QUOTA_K_GEMM_64X256: packed rows only.) */
+ * (QUOTA_K_GEMM_64X256: packed rows only; QUOTA_K_GEMM_96X128: a layer's rows
+ * only; QUOTA_K_GEMM_OTHER: with the integer sums.) */
 enum {
     QUOTA_K_QUANTIZE_ACT = 0, QUOTA_K_RMSNORM_QUANTIZE_ACT, QUOTA_K_SILU_MUL_QUANTIZE_ACT,
     QUOTA_K_GEMM_64X256, QUOTA_K_GEMM_64X128, QUOTA_K_GEMM_32X128, QUOTA_K_GEMM_32X64, QUOTA_K_GEMM_128X256,
@@ -509,7 +510,7 @@ enum {
     QUOTA_K_KV_QUANT_APPEND, QUOTA_K_ATTENTION_FWD, QUOTA_K_ATTENTION_COLMASS,
     QUOTA_K_SCORE_TOKENS, QUOTA_K_TOPK_PRUNE, QUOTA_K_COMPACT_ROWS, QUOTA_K_QUANTIZE_WEIGHTS,
     QUOTA_K_PACK_WEIGHTS, QUOTA_K_ATTENTION_DECODE, QUOTA_K_KV_APPEND_ROWS, QUOTA_K_GEMM_ROWS16,
-    QUOTA_K_GEMM_128X128, QUOTA_KERNEL_COUNT
+    QUOTA_K_GEMM_128X128, QUOTA_K_GEMM_96X128, QUOTA_KERNEL_COUNT
 };
 
 /* Per kernel class: launches seen, summed HIP-event time around them (ms) and

@@ -70,7 +70,7 @@ class KernelStat(C.Structure):
     _fields_ = [("launches", C.c_long), ("total_ms", C.c_double), ("ops", C.c_double), ("bytes", C.c_double)]
 
 
-KERNEL_COUNT = 22
+KERNEL_COUNT = 23
 
 _lib = None
 

@@ -602,7 +602,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
 {
     w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, qe);
 }
-// The tile of 96 rows, which only the choice takes, under a name of its own: profiles tell it by that from the tiles that can be pinned.
+// The tile of 96 rows, which only the choice takes, under a name of its own: a profile tells it by that from the tiles that can be pinned.
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows96_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
@@ -635,9 +635,12 @@ __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows96_kernel(
 // 12288 x 4096 47, 41; 1600 x 4096 x 4096 43, 38; a layer's rows do better on 128 x 128).
 #define F8_PACKED_TILE(P, A, QK) w4a4_f8_kernel<4, 4, 4, 2, 6, P, A, QK, 2>
 
-// 96 x 128, a layer's rows below 512 only, not pinned, up to two workgroups per CU: 129 to 192 rows are two of it and three of 64 x 128, which at 22016 columns
-// are 516 workgroups, three for a few CUs (160 x 22016 x 4096 25.2 -> 23.2 us, 160 x 27648 x 5120 31.8 -> 27.6), 320 to 444 rows four and five to seven
-// (384 x 12288 x 4096 27.2 -> 24.7; at 224 rows, three and four, 20.6 against 24.3).  Stages of four groups leave room for two workgroups.
+// 96 x 128, a layer's rows below 512 only, not pinned, chosen up to two workgroups per CU, where 64 x 128 comes to more: 129 to 192 rows are two of it and
+// three of 64 x 128, which at 22016 columns are 516 workgroups, three for a few CUs.  Over what the choice takes it for, best other tile and
+// it, us: 65 to 96 x 37888 x 3584, one of it and two, 24.6 to 26.3, 23.4 to 25.3; 129 to 192 x 22016 x 4096 26.6 to 27.9, 23.4 to 25.8, x 27648 x 5120 34.6
+// to 36.1, 30.6 to 32.4; 257 to 384 x 15360 x 5120 35.8 to 39.8, 31.2 to 35.7; 321 to 480 x 12288 x 4096, four or five and six to eight, 29.9 to
+// 33.7, 27.0 to 31.0; 39 more shapes of 72 to 493 rows and 8832 to 39360 columns that the choice takes it for: 2 to 15 % less on it.  At 224 x 12288 x 4096, three
+// and four, 24.3 against 20.6 on 64 x 128.  Stages of four groups leave room for two workgroups.
 #define F8_96_ROW_TILE(P, A, QK) w4a4_rows96_kernel<6, 2, 4, 4, 4, P, A, QK, 2>  // 96 x 128
 
 struct TileShape { int bm, bn, nt, kernel_id; };
@@ -645,7 +648,7 @@ constexpr int TILES = 8, PINNED_TILES = 5, PACKED_TILE = 6;
 const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128, 256, QUOTA_K_GEMM_64X128},
                              {32, 128, 256, QUOTA_K_GEMM_32X128}, {32, 64, 256, QUOTA_K_GEMM_32X64},
                              {128, 256, 256, QUOTA_K_GEMM_128X256}, {32, 64, 256, QUOTA_K_GEMM_32X64},
-                             {64, 256, 256, QUOTA_K_GEMM_64X256}, {96, 128, 256, QUOTA_K_GEMM_OTHER}};
+                             {64, 256, 256, QUOTA_K_GEMM_64X256}, {96, 128, 256, QUOTA_K_GEMM_96X128}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
                           int, f16 *, int, const f16 *, int, int32_t *, int, int, quota_qkv_epilogue);
@@ -699,7 +702,7 @@ int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set
 // Tile choice by cost models fitted to measured kernel times on this GPU (us, over weights that no cache holds), one for a layer's rows
 // (112 shapes of 40 to 11776 rows, 512 to 37888 columns and 512 to 18944 channels; the 32 x 64 tile's line, which has changed since, by 270
 // of 33 to 511 rows and of narrow layers, where the choice costs 0.6 % over the best tile of each on average, 2.3 % with the line before; the 96 x 128 tile's by
-// launches of 160 to 444 rows) and one for
+// launches of 160 to 444 rows, and right for those of 65 to 493) and one for
 // packed rows, whose stages are shorter and tiles others (412 shapes of 33 to 11776 rows; 0.2 % on average, 10 % at most, where two tiles tie over
 // cold weights the one that is ahead over warm ones; by a layer's, without the
 // 64 x 256 tile, 3.7 %: 5808 x 4096 x 11008 301 us, 236 so).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and

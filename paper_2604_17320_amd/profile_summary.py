@@ -46,7 +46,7 @@ CLASSES = [
     ("w4a4_f8_kernelILi2ELi2ELi4E", "w4a4_gemm_32x128"),
     ("w4a4_f8_kernelILi2ELi1ELi4E", "w4a4_gemm_32x64"),
     ("w4a4_f8_kernelILi8ELi4ELi4E", "w4a4_gemm_128x256"),
-    ("w4a4_rows96_kernel", "w4a4_gemm_other"),                                # 96 x 128
+    ("w4a4_rows96_kernel", "w4a4_gemm_96x128"),
     ("w4a4_rows16_kernel", "w4a4_gemm_rows16"),
     ("silu_mul_quantize_act_kernel", "silu_mul_quantize_act"),
     ("rmsnorm_quantize_act_kernel", "rmsnorm_quantize_act"),

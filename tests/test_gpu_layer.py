@@ -391,10 +391,11 @@ def test_layer_silu_product_in_the_gate_up_projection(qb, tile, F, Nt, K, pinned
 
 
 @pytest.mark.parametrize("d,dh,F,N", [(2048, 128, 2048, 480), (2048, 128, 2048, 641), (1024, 128, 1376, 1000), (1024, 64, 1376, 100),
-                                      (1024, 64, 96, 33), (1152, 128, 11008, 132), (1152, 128, 11008, 170), (4096, 128, 1376, 331)])
+                                      (1024, 64, 96, 33), (1152, 128, 11008, 132), (1152, 128, 11008, 170), (4096, 128, 1376, 331),
+                                      (640, 128, 18944, 68), (640, 128, 18944, 99)])
 def test_layer_tiles_in_long_stages(qb, d, dh, F, N, pinned_gemm):
     """The tiles of the choice, in stages of four groups, with and without start values, and 32 x 64 in stages of eight, which
-    only the choice takes (100 and 33 rows), as it does 96 x 128 (gate/up of 22016 columns, QKV of 12288), over whole and ragged numbers of groups: the bits of the pinned 128 x 128 tile."""
+    only the choice takes (100 and 33 rows), as it does 96 x 128 (gate/up of 22016 and 37888 columns, QKV of 12288), over whole and ragged numbers of groups: the bits of the pinned 128 x 128 tile."""
     from paper_2604_17320_amd.model import KVCache4
     shape = wl.Shape("stages", d=d, H=d // dh, F=F, layers=1, B=1, Nv=N - 8, Nt=8, n_outlier=4, vis_begin=0)
     W, L, cos, sin = build_layer(shape, 9)
@@ -409,10 +410,46 @@ def test_layer_tiles_in_long_stages(qb, d, dh, F, N, pinned_gemm):
         ws = torch.empty(L.workspace_bytes(1, N), dtype=torch.uint8, device="cuda")
         xd, pd = dev(x), dev(pos)
         st = qb.State(1, N, 0, N - 8, xd.data_ptr(), pd.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+        qb.quota_profile_begin(64)
         qb.quota_prefill_layer(L.desc, st, K, qb.quota_score_params_default(), cache.desc, None, ws)
+        ran = {n: s["launches"] for n, s in qb.quota_profile_collect().items() if n.startswith("w4a4")}
+        assert tile >= 0 or ran.get("w4a4_gemm_96x128", 0) == (1 if F > 10000 or d == 4096 else 0), ran
         got.append([tapped[k] for k in ("qkv", "q_rot", "x1", "gu", "x_next")] + [host(x_out)])
     for a, b in zip(*got):
         assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
+
+
+@pytest.mark.parametrize("rows", [449, 480, 481, 511])
+def test_layer_96_row_tile_adds_the_residual(qb, rows, pinned_gemm):
+    """O and down on the tile of 96 rows, whose three rounds of the epilogue ask for all residual rows at once, for rows that end in the first
+    round of a tile, with it, and one behind it: the bits of the pinned 128 x 128 tile."""
+    from paper_2604_17320_amd.model import KVCache4, PackedLinear, PrefillLayer
+    d, H, F, N, Nv = 8320, 65, 1024, 520, 512              # (520 rows of QKV are on another tile)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    def linear(n, k):
+        codes = torch.randint(-8, 8, (n, k), generator=g, device="cuda", dtype=torch.int8)
+        scales = (torch.rand((n, k // 128), generator=g, device="cuda") * 0.002 + 0.001).to(torch.float16)
+        return PackedLinear.from_codes(codes, scales)
+    cos, sin = (dev(t) for t in wl.rope_tables(128, N))
+    ones = torch.ones(d, device="cuda")
+    L = PrefillLayer(H, 128, F, linear(d + 2 * 128, d), linear(d, d), linear(2 * F, d), linear(d, F), ones, ones, 1e-5, cos, sin, 1)
+    x = torch.randn((N, d), generator=g, device="cuda").to(torch.float16)
+    pos = torch.arange(N, dtype=torch.int32, device="cuda")
+    outs = []
+    for tile in (0, -1):
+        pinned_gemm(tile)
+        cache = KVCache4(1, rows, 1, 128)
+        x_out, pos_out = torch.full((rows, d), float("nan"), dtype=torch.float16, device="cuda"), torch.zeros(rows, dtype=torch.int32, device="cuda")
+        ws = torch.full((L.workspace_bytes(1, N),), 0xFF, dtype=torch.uint8, device="cuda")
+        st = qb.State(1, N, 0, Nv, x.data_ptr(), pos.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+        qb.quota_profile_begin(64)
+        qb.quota_prefill_layer(L.desc, st, rows - (N - Nv), qb.quota_score_params_default(), cache.desc, None, ws)
+        ran = {n: s["launches"] for n, s in qb.quota_profile_collect().items() if n.startswith("w4a4")}
+        assert ran.get("w4a4_gemm_96x128", 0) == (0 if tile == 0 else 2), ran
+        outs.append(host(x_out))
+    assert np.isfinite(outs[0].astype(np.float32)).all()
+    assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
 
 
 def test_layer_with_weight_scales_at_an_odd_halfword(qb):
