@@ -92,9 +92,9 @@ __device__ __forceinline__ void w4a4_tile(
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Token scale and position of row tid of the tile.  On a layer's rows, where a stage's loads go out all at once (SP = 0), they are asked
-    // for beside the first stage (packed ones, 33 x 4096 x 11008: 31.6 us, 33.7 so).  Where loads are spread the compiler starts the first stage's
-    // weights behind its barrier, and a round trip in front costs less than waiting for them there (32 x 64 in stages of 8, 42 x 2688 x 896:
-    // 4.0 us, 4.4 with the scales beside the stage).
+    // for beside the first stage (packed ones, 33 x 4096 x 11008: 31.6 us, 33.7 so).  Where loads are spread they take a round trip in front: beside the
+    // stage they are no better over these tiles (36 launches of a layer's rows, within 0.5 % on average: 150 x 12288 x 4096 17.3 -> 16.7 us, 637 x 4096 x
+    // 11008 41.5 -> 41.2, but 165 x 22016 x 4096 24.0 -> 24.6, 300 x 4096 x 11008 34.5 -> 35.0, 600 x 2752 x 512 5.2 -> 5.3).
     constexpr bool TOGETHER = !SP && !PACKED;
     if constexpr (!TOGETHER) {
         if (tid < BM) {
