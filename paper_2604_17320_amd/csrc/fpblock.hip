@@ -46,7 +46,7 @@ __device__ __forceinline__ Pack16 rope_fp(Pack16 x, const Pack16 &xp, const floa
 // number of workgroups.  The next step's fragments are read, and a stage's copies started, between the products of
 // the current one (SPREAD: over how many of the stage's 4 steps; all at once they hold the address unit up: 1280 x 4096 x
 // 11008 178 us with one stage on its way, 160 spread over three steps and two on their way).  1280 rows: 1.06 PFLOP/s at 12288 x 4096,
-// 0.99 at 22016 x 4096, 0.70 and 0.73 at 4096 x 4096 and 4096 x 11008 (0.91, 0.86, 0.62 and 0.67 before).
+// 0.99 at 22016 x 4096 (0.99 and 0.97 with RoPE and the SiLU product), 0.70 and 0.73 at 4096 x 4096 and 4096 x 11008 (0.91, 0.86, 0.62 and 0.67 before).
 // LDS rows are 128 bytes, 16-byte piece p of row r at p ^ (r % 8).
 // Lane l supplies 8 consecutive k of row (l % 32) to both operands (k slots 8 (l / 32) .. +7 of the
 // step), and receives column l % 32 of the tile, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0..15.
