@@ -46,22 +46,21 @@ __device__ __forceinline__ int tile_swizzle(int r)
 {
     return DH == 128 ? ((r & 3) << 2 | (r >> 2 & 3)) : ((r >> 1 & 1) << 2 | (r >> 2 & 1) << 1);
 }
-// Copies of KT rows of a matrix into a tile, by four waves, each its share.  A thread's places in a tile are a fixed number of
-// rows apart and keep their swizzle, so its offsets are made once; rows behind the last come as zeros from the buffer's own
+// Copies of KT rows of a matrix into a tile, by W waves, each its share.  A thread's places in a tile are a fixed number of
+// rows apart, and their offsets are made once; rows behind the last come as zeros from the buffer's own
 // bounds instead of being clamped, and a tile behind the last fetches nothing, so that its pieces need no branch and can be
 // started one by one between the products.
-template <int DH>
+template <int DH, int W>
 struct TileCopy {
-    static constexpr int CPR = DH / 8, PER = KT * CPR / 256, ROWS = 256 / CPR;      // rows of a copy by four waves
+    static constexpr int CPR = DH / 8, PER = KT * CPR / (64 * W), ROWS = 64 * W / CPR;      // rows of a copy by W waves
     unsigned row_bytes, off[PER], lds_wave;
     __device__ __forceinline__ explicit TileCopy(int stride) : row_bytes(2 * stride)
     {
-        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % W;
         const int r = wave * (64 / CPR) + lane / CPR;
-        static_assert(ROWS % 16 == 0, "(the swizzle of a row takes its last four bits)");
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            off[j] = (unsigned)(r + ROWS * j) * row_bytes + 16 * (lane % CPR ^ tile_swizzle<DH>(r));
+            off[j] = (unsigned)(r + ROWS * j) * row_bytes + 16 * (lane % CPR ^ tile_swizzle<DH>(r + ROWS * j));
             asm volatile("" : "+v"(off[j]));
         }
         lds_wave = wave * 1024;
@@ -80,7 +79,7 @@ struct TileCopy {
     }
     __device__ __forceinline__ void piece(const Run &to, int j) const
     {
-        asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(to.lds + 4096 * j), "v"(off[j]), "s"(to.buffer) : "memory");
+        asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"{m0}"(to.lds + 1024 * W * j), "v"(off[j]), "s"(to.buffer) : "memory");
     }
     __device__ __forceinline__ void operator()(const f16 *base, int row0, int rows, unsigned lds) const
     {
@@ -103,13 +102,13 @@ __device__ __forceinline__ float halves_max(float v)
     return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 
-template <int DH, typename PRE>
-__global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
+template <int DH, int W, typename PRE>
+__global__ __launch_bounds__(64 * W, W / 2) void attn_fwd_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
     int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int wgs, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
-        prefetch<256>(pre, blockIdx.x - wgs, gridDim.x - wgs);
+        prefetch<64 * W>(pre, blockIdx.x - wgs, gridDim.x - wgs);
         return;
     }
     constexpr int T = DH / 16;       // k-steps (16 channels each) of the QK product
@@ -117,8 +116,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     constexpr int TB = KT * DH * 2;  // bytes of a tile
     __shared__ __align__(16) char sm[2][2][TB];         // [buffer][K, V]
     // XCD-aware order: a head's workgroups, longest first, run on one XCD, whose L2 holds its K and V
-    const int nq = (N + 127) / 128, work = xcd_remap(blockIdx.x, wgs), bh = work / nq;
-    const int b = bh / H, h = bh % H, q0 = (nq - 1 - work % nq) * 128;
+    constexpr int QB = 32 * W;       // queries of a workgroup
+    const int nq = (N + QB - 1) / QB, work = xcd_remap(blockIdx.x, wgs), bh = work / nq;
+    const int b = bh / H, h = bh % H, q0 = (nq - 1 - work % nq) * QB;
     const int d = H * DH;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hl = lane >> 5;
     const int qw0 = q0 + wave * 32, qi = qw0 + l32;       // this lane's query
@@ -126,8 +126,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     // K/V rows have Hkv heads; query head h reads K/V head h / (H / Hkv)
     const int dkv = Hkv * DH;
     const size_t kvbase = (size_t)b * N * dkv + (size_t)(h / (H / Hkv)) * DH;
-    const int q_last_wg = min(q0 + 127, N - 1);
-    const TileCopy<DH> tile_copy(dkv);
+    const int q_last_wg = min(q0 + QB - 1, N - 1);
+    const TileCopy<DH, W> tile_copy(dkv);
     auto copy = [&](int kt0, int buf) {
         tile_copy(khat + kvbase, kt0, N, lds_address(sm[buf][0]));
         tile_copy(vhat + kvbase, kt0, N, lds_address(sm[buf][1]));
@@ -251,41 +251,42 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(
     }
 }
 
-// One workgroup per 128 visual keys of a (sequence, head); wave w of a group of four owns the 32 keys kb .. kb+31.
+// One workgroup per 32 W visual keys of a (sequence, head); wave w of a group of W owns 32 of them.
 // The first key block meets every query tile, a chain that bounds launches of few workgroups: there G = 2 groups take the tiles in
 // turn, each through LDS of its own, and the second's sums are added to the first's (32 heads, 165 / 400 / 640 tokens 10.3 / 15.2 / 16.6 ->
 // 9.3 / 13.2 / 13.1 us, 28 heads, 1101 tokens 25.7 -> 18.9; four groups take longer below a thousand tokens).  A group alone keeps two
 // pairs of sums, which its tiles add to in turn: a sequence has the same masses however many share its launch (4 x 2944 tokens,
 // 40 heads 237.7 us with one pair, 239.1 so, 16 x 704 0.2 more; the two turns inlined instead of the sums exchanged: 32 x 80 tokens, 8 heads 7.1 -> 7.9).
 template <int DH>
-constexpr size_t colmass_lds(int G) { return (size_t)G * 2 * (KT * DH * 2 + KT * 4) + (G - 1) * 128 * sizeof(float2); }
-template <int DH, int G, typename PRE>
-__global__ __launch_bounds__(256 * G, G == 1 ? 3 : 1) void colmass_kernel(
+constexpr size_t colmass_lds(int G, int W) { return (size_t)G * 2 * (KT * DH * 2 + KT * 4) + (G - 1) * 32 * W * sizeof(float2); }
+template <int DH, int G, int W, typename PRE>
+__global__ __launch_bounds__(64 * W * G, G == 1 ? 3 : 1) void colmass_kernel(
     const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
     int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, int wgs, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
-        prefetch<256 * G>(pre, blockIdx.x - wgs, gridDim.x - wgs);
+        prefetch<64 * W * G>(pre, blockIdx.x - wgs, gridDim.x - wgs);
         return;
     }
     constexpr int T = DH / 16, TB = KT * DH * 2;
     extern __shared__ __align__(16) char sm[];            // [group][buffer][tile], [group][buffer][lse], [group - 1][key]
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3, l32 = lane & 31, hl = lane >> 5;
-    const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6) % W, l32 = lane & 31, hl = lane >> 5;
+    const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (64 * W));
     char *const sm_q = sm + grp * 2 * TB;
     float *const sm_lse = reinterpret_cast<float *>(sm + G * 2 * TB) + grp * 2 * KT;
     float2 *const sm_sum = reinterpret_cast<float2 *>(sm + G * 2 * (TB + 4 * KT));
     // XCD-aware order, as in pass 1; the first keys have the most queries
-    const int nk = (Nv + 127) / 128, work = xcd_remap(blockIdx.x, wgs), bh = work / nk, kb = work % nk;
+    constexpr int KB = 32 * W;       // keys of a workgroup
+    const int nk = (Nv + KB - 1) / KB, work = xcd_remap(blockIdx.x, wgs), bh = work / nk, kb = work % nk;
     const int d = H * DH;
     const int b = bh / H, h = bh % H;
-    const int kwg = vis_begin + kb * 128;                 // first key of the workgroup
+    const int kwg = vis_begin + kb * KB;                 // first key of the workgroup
     const int key = kwg + wave * 32 + l32;                // this lane's key column
     const bool key_ok = key < vis_begin + Nv;
     const size_t base = (size_t)b * N * d + (size_t)h * DH;
     const float *lse = lse2 + ((size_t)b * H + h) * N;
 
-    const TileCopy<DH> tile_copy(d);
+    const TileCopy<DH, W> tile_copy(d);
     auto copy = [&](int qt0, int buf) {
         tile_copy(q + base, qt0, N, lds_address(sm_q + buf * TB));
         if (wave == 0) copy4_to_lds(lse, 4 * min(qt0 + lane, N - 1), lds_address(sm_lse + buf * KT));
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 1) void colmass_kernel(
         __syncthreads();
         const int qt0 = qg0 + grp * KT;
         const bool more = qt0 + G * KT < N;
-        constexpr int PER = TileCopy<DH>::PER;             // (at the top they took the address unit all at once: 4 x 2944 tokens, 40 heads 252 -> 230 us)
+        constexpr int PER = TileCopy<DH, W>::PER;             // (at the top they took the address unit all at once: 4 x 2944 tokens, 40 heads 252 -> 230 us)
         const auto next = tile_copy.run(q + base, qt0 + G * KT, N, lds_address(sm_q + (buf ^ 1) * TB));
         if (more && wave == 0) copy4_to_lds(lse, 4 * min(qt0 + G * KT + lane, N - 1), lds_address(sm_lse + (buf ^ 1) * KT));
         if (qt0 + KT - 1 < kwg + wave * 32) {             // all queries before this wave's keys
@@ -371,12 +372,12 @@ __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 1) void colmass_kernel(
     acc_txt += __shfl_xor(acc_txt, 32, 64);
     acc_vis += __shfl_xor(acc_vis, 32, 64);
     if constexpr (G > 1) {
-        if (grp && hl == 0) sm_sum[(grp - 1) * 128 + wave * 32 + l32] = make_float2(acc_txt, acc_vis);
+        if (grp && hl == 0) sm_sum[(grp - 1) * KB + wave * 32 + l32] = make_float2(acc_txt, acc_vis);
         __syncthreads();
         if (grp) return;
 #pragma unroll
         for (int g = 0; g < G - 1; ++g) {
-            const float2 v = sm_sum[g * 128 + wave * 32 + l32];
+            const float2 v = sm_sum[g * KB + wave * 32 + l32];
             acc_txt += v.x;
             acc_vis += v.y;
         }
@@ -440,7 +441,14 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
     const AttnWs w(ws, (size_t)B * H * N);
     float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
     const bool cues = Nv > 0 && (cm_inter || cm_intra);
-    const unsigned n1 = (unsigned)((N + 127) / 128) * H * B;
+    // Workgroups of two waves, 64 queries or keys each, where those of four leave many CUs without one: shorter ones start and end sooner, and a short prompt's
+    // last block is half as wide.  Four and two waves, us: forward, 32 heads, 122 / 165 / 500 / 640 tokens 7.1 / 7.8 / 14.7 / 17.1, 6.3 / 7.5 / 13.7 / 17.0, 8
+    // heads of 64, 80 / 640 tokens 5.2 / 11.7, 4.5 / 11.0; cues and means behind it 7.6 / 9.7 / 12.8 / 13.3 and 6.5 / 10.3, 7.5 / 9.2 / 12.1 / 12.6 and 6.0 / 9.2.
+    // Beyond 160 of four they come to the same or take longer: 40 heads, 640 tokens (200) 17.6, 18.1; 2 x 300, 32 heads (192) 10.7, 11.4; cues of 28 heads,
+    // 1101 tokens (224) 18.9, 20.3.  A forward launch that also fetches stays with four (a layer of 640 tokens over changing weights 148.8, 149.7 with two).
+    auto waves_for = [&](int rows) { return (long)((rows + 127) / 128) * H * B <= 160 ? 2 : 4; };
+    const int w1 = weights ? 4 : waves_for(N);
+    const unsigned n1 = (unsigned)((N + 32 * w1 - 1) / (32 * w1)) * H * B;
     // (time by the tiles of the longest workgroup; more than 2 MB a microsecond hold its own tiles up)
     const auto s1 = weights ? weights->take(n1, 3.0f + 1.5f * (float)((N + 63) / 64), 2.0f) : PrefetchList::Share{};
     dim3 g1(n1 + s1.wgs), blk(256);
@@ -450,33 +458,40 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
         ProfScope prof(QUOTA_K_ATTENTION_FWD, 4.0 * B * dd * ((double)N * (N + 1) / 2),
                        4.0 * dM * dd + 4.0 * dM * Hkv * dh, st);
         s1.run([&](auto pre) {
-            auto kernel = dh == 128 ? attn_fwd_kernel<128, decltype(pre)> : attn_fwd_kernel<64, decltype(pre)>;
-            kernel<<<g1, blk, 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, (int)n1, pre);
+            auto kernel = w1 == 4 ? (dh == 128 ? attn_fwd_kernel<128, 4, decltype(pre)> : attn_fwd_kernel<64, 4, decltype(pre)>)
+                                  : (dh == 128 ? attn_fwd_kernel<128, 2, decltype(pre)> : attn_fwd_kernel<64, 2, decltype(pre)>);
+            kernel<<<g1, dim3(64 * w1), 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, (int)n1, pre);
         });
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     if (cues) {
-        const unsigned n2 = (unsigned)((Nv + 127) / 128) * H * B;
+        const int w2 = waves_for(Nv);
+        const unsigned four2 = (unsigned)((Nv + 127) / 128) * H * B, n2 = (unsigned)((Nv + 32 * w2 - 1) / (32 * w2)) * H * B;
         // two groups (the same sums) where every workgroup has a CU to itself, or half of one and a chain of eight tiles (2 x 640 tokens, 32 heads 18.7 -> 16.6 us, 8 x 300
         // 16.4 -> 16.5, 4 x 640 as it was)
-        const bool split = n2 <= (N >= 512 ? 512u : 256u);
-        const auto s2 = weights ? weights->take(n2, 3.0f + 1.1f * (float)((N + 63) / 64), 3.5f) : PrefetchList::Share{};
-        dim3 g2(n2 + s2.wgs);
+        const bool split = four2 <= (N >= 512 ? 512u : 256u);
+        const auto s2 = weights ? weights->take(four2, 3.0f + 1.1f * (float)((N + 63) / 64), 3.5f) : PrefetchList::Share{};
+        // (fetching workgroups of half the width: twice as many up to 192; a layer of 640 tokens over changing weights 148.8 us, 152.4 with as many as before, one
+        // of 165 113.7, 114.2 with always twice as many)
+        dim3 g2(n2 + (w2 == 2 ? min(2 * s2.wgs, 192u) : s2.wgs));
         // (query, visual key) pairs under the causal mask
         const double pairs = (double)Nv * (N - vis_begin) - (double)Nv * (Nv - 1) / 2;
         ProfScope prof(QUOTA_K_ATTENTION_COLMASS, 2.0 * B * dd * pairs, 2.0 * dM * dd + 2.0 * dM * Hkv * dh, st);
         bool granted = true;
-        auto launch = [&](auto dh_tag, auto groups, auto pre) {
-            constexpr int DH = decltype(dh_tag)::value, G = decltype(groups)::value;
-            constexpr auto kernel = colmass_kernel<DH, G, decltype(pre)>;
+        auto launch = [&](auto dh_tag, auto groups, auto waves, auto pre) {
+            constexpr int DH = decltype(dh_tag)::value, G = decltype(groups)::value, W = decltype(waves)::value;
+            constexpr auto kernel = colmass_kernel<DH, G, W, decltype(pre)>;
             if ((granted = grant_lds<kernel>()))
-                kernel<<<g2, dim3(256 * G), colmass_lds<DH>(G), st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial,
+                kernel<<<g2, dim3(64 * W * G), colmass_lds<DH>(G, W), st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial,
                                                                        scale_log2, (int)n2, pre);
         };
         s2.run([&](auto pre) {
             auto with_dh = [&](auto dh_tag) {
-                if (split) launch(dh_tag, std::integral_constant<int, 2>(), pre);
-                else launch(dh_tag, std::integral_constant<int, 1>(), pre);
+                typedef std::integral_constant<int, 2> Two;
+                typedef std::integral_constant<int, 4> Four;
+                if (w2 == 2) launch(dh_tag, Two(), Two(), pre);              // (160 at most: two groups)
+                else if (split) launch(dh_tag, Two(), Four(), pre);
+                else launch(dh_tag, std::integral_constant<int, 1>(), Four(), pre);
             };
             if (dh == 128) with_dh(std::integral_constant<int, 128>());
             else with_dh(std::integral_constant<int, 64>());

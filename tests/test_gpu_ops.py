@@ -492,6 +492,32 @@ def test_cues_of_a_sequence_do_not_depend_on_the_others(qb, N, H, dh, vb, Nv, B)
             assert np.array_equal(got[b].view(np.uint32), alone[0].view(np.uint32))
 
 
+# (workgroups of two waves up to 160 of four, one per head and 128 queries or visual keys: the sequence alone; of four in the batch)
+@pytest.mark.parametrize("N,H,Hkv,dh,vb,Nv,B", [(64, 8, 8, 64, 0, 64, 21), (65, 8, 2, 128, 1, 63, 21), (127, 8, 8, 64, 14, 65, 21), (129, 8, 8, 128, 0, 129, 11),
+                                                (193, 6, 6, 128, 65, 128, 14), (640, 28, 4, 128, 30, 576, 2)])
+def test_attention_of_two_and_of_four_waves(qb, N, H, Hkv, dh, vb, Nv, B):
+    """Outputs and masses of a sequence have the same bits from workgroups of either width, and the outputs those of the reference."""
+    d, dkv, blocks = H * dh, Hkv * dh, H * ((N + 127) // 128)
+    assert blocks <= 160 < blocks * B
+    q = _act(B * N, d, 74, 1.0)
+    khat, vhat = (oracle.kv_quant(_act(B * N, dkv, seed, 1.0))[2] for seed in (75, 76))
+    qd, kd, vd = dev(q), dev(khat), dev(vhat)
+
+    def run(first, n):
+        rows = slice(first * N, (first + n) * N)
+        o = torch.full((n * N, d), float("nan"), dtype=torch.float16, device="cuda")
+        ci, cv = (torch.full((n, Nv), -1.0, dtype=torch.float32, device="cuda") for _ in range(2))
+        ws = torch.full((qb.quota_attention_workspace_bytes(n, N, H, dh),), 0xFF, dtype=torch.uint8, device="cuda")
+        qb.quota_attention_prefill_gqa(qd[rows], kd[rows], vd[rows], n, N, H, Hkv, dh, vb, Nv, o, ci, cv, ws)
+        return host(o).reshape(n, N * d), host(ci), host(cv)
+    batch = run(0, B)
+    for b in (0, B - 1):
+        for got, alone in zip(batch, run(b, 1)):
+            assert np.array_equal(got[b].view(np.uint8), alone[0].view(np.uint8))
+    if H == Hkv:
+        assert close_f16(batch[0][0].reshape(N, d), oracle.attention(q[:N], khat[:N], vhat[:N], 1, N, H, dh, vb, Nv)[0])
+
+
 # -------------------------------------------------------- score and top-k
 def _metrics(B, Nv, seed):
     r = wl.rng(seed, "metrics", B, Nv)
