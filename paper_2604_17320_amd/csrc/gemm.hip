@@ -60,12 +60,19 @@ namespace {
 // are swapped in rows 8 to 15 of 16, so that the lanes of a read do not share banks.
 enum ActFormat { A6, A6_STARTS, PACKED_INT4 };
 enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL };
+// What some launches take besides, by their epilogue (QKV_ROPE_KV; PLAIN: rows to pick, if keep_idx is given).  One place for both: every argument costs the
+// host time.
+union GemmMore {
+    quota_qkv_epilogue qkv;
+    quota_kept_rows kept;
+};
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI>
 __device__ __forceinline__ void w4a4_tile(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
+    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, const GemmMore &more)
 {
+    const quota_qkv_epilogue &qe = more.qkv;
     constexpr int NT = 64 * NW, BM = 16 * RT, WN = 16 * CT, BN = NW * WN, T = RT * CT;
     constexpr bool PACKED = ACTS == PACKED_INT4, STARTS = ACTS == A6_STARTS, QKV = EPI == QKV_ROPE_KV, SILU = EPI == SILU_MUL;
     static_assert(!SILU || (CT % 2 == 0 && !ACC_OUT), "as many blocks of gate as of up columns");
@@ -96,7 +103,20 @@ __device__ __forceinline__ void w4a4_tile(
     // stage they are no better over these tiles (36 launches of a layer's rows, within 0.5 % on average: 150 x 12288 x 4096 17.3 -> 16.7 us, 637 x 4096 x
     // 11008 41.5 -> 41.2, but 165 x 22016 x 4096 24.0 -> 24.6, 300 x 4096 x 11008 34.5 -> 35.0, 600 x 2752 x 512 5.2 -> 5.3).
     constexpr bool TOGETHER = !SP && !PACKED;
-    if constexpr (!TOGETHER) {
+    // A launch that picks its rows (PICKS: may): rows m of activations and residual are rows src of the tensors handed in.  The indices are asked for ahead of the
+    // first weights and looked up behind them.
+    constexpr bool PICKS = EPI == PLAIN && ACTS == A6 && !ACC_OUT;
+    __shared__ int row_src[PICKS ? BM : 1];
+    const quota_kept_rows &kept = more.kept;
+    const bool picks = PICKS && kept.keep_idx;
+    int pick_j = 0, pick_b = 0, pick = 0;
+    if (PICKS && picks) {
+        const int m = min(m0 + min(tid, BM - 1), M - 1);
+        pick_b = m / kept.n_keep;
+        pick_j = m - pick_b * kept.n_keep;
+        pick = kept.index(pick_b, pick_j);
+    }
+    if (!TOGETHER && !picks) {
         if (tid < BM) {
             const int m = min(m0 + tid, M - 1);
             row_scale[tid] = sa[m] * F6_UNIT;
@@ -188,7 +208,7 @@ __device__ __forceinline__ void w4a4_tile(
     constexpr int LG = CT + LA, LC = CH * LG + MC + TC, LOADS = LC + KD;
     const uint4 *wnext = wp + (size_t)nw * 4;
     const unsigned wstep = (unsigned)N * 64u;
-    const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : qa + (size_t)(m0 >> 2) * four_bytes;
+    const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : picks ? qa : qa + (size_t)(m0 >> 2) * four_bytes;
     int gstage = 0;                                       // first group of the stage being loaded
     static_assert(!LATE || (CH == 2 && SP && (LOADS - LG) * SPAN / LOADS >= T), "the first group's products cover what comes before");
     auto load = [&](int at, int set, int half) {
@@ -298,10 +318,36 @@ __device__ __forceinline__ void w4a4_tile(
     // step, multiply together and wait together (237 x 4096 x 11008 25.6 -> 23.4 us, 160 x 22016 x 4096 28.0 -> 26.0, 1280 x
     // 4096 x 11008 64.1 -> 61.2, 5808 x 22016 x 4096 400 -> 396; lowest at products, highest around the barrier: nothing).
     static_assert(CH >= 4 ? CH % 4 == 0 : RT % (4 / CH) == 0, "whole row blocks, or groups, per quarter");
+    constexpr int AHEAD_OF_PICKS = PICKS && !LATE ? CH * LG : 0;
 #pragma unroll
-    for (int k = 0; k < LOADS; ++k) load(k, 0, 0);
-    if constexpr (TOGETHER) {
-        const int m = min(m0 + min(tid, BM - 1), M - 1);
+    for (int k = 0; k < AHEAD_OF_PICKS; ++k) load(k, 0, 0);
+    if (PICKS && picks) {                    // where the copies' rows lie
+        if (tid < BM) row_src[tid] = pick_b * kept.N + kept.row(pick_j, pick);
+        __syncthreads();
+        const int row = lane >> 2, row2 = lane >> 1;
+        auto first = [&](int blk) {
+            const unsigned src = row_src[16 * (blk % BB) + row];
+            return (src >> 2) * four_bytes + (src & 3) * 64 + 16 * piece_of(lane & 3, row);
+        };
+        auto second = [&](int blk) {
+            const unsigned src = row_src[32 * (blk % TB) + row2];
+            return (src >> 2) * four_bytes + 256 + (src & 3) * 32 + 16 * ((lane ^ row2 >> 3) & 1);
+        };
+        om = first(wave) + wave / BB % NW * 384;
+        if (BB > NW) om2 = first(wave + NW);
+        ot = second(wave) + wave / TB % NW * 384;
+        if constexpr (THREES) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                om3[j] = first(wave + NW * j);
+                ot3[j] = second(wave + NW * j);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = AHEAD_OF_PICKS; k < LOADS; ++k) load(k, 0, 0);
+    if (TOGETHER || picks) {
+        const int m = picks ? row_src[min(tid, BM - 1)] : min(m0 + min(tid, BM - 1), M - 1);
         float scale = sa[m];
         int pos = 0;
         if constexpr (QKV) pos = qe.pos[m];
@@ -361,7 +407,8 @@ __device__ __forceinline__ void w4a4_tile(
         if (res && n8 < N) {
 #pragma unroll
             for (int k = 0; k < KI; ++k) {
-                rv[ib][k] = *(global_f16x8)(res_at + 2 * ((size_t)min(m0 + 32 * ib + RPI * k + row0, M - 1) * ldr + n8));
+                const int m = 32 * ib + RPI * k + row0;
+                rv[ib][k] = *(global_f16x8)(res_at + 2 * ((size_t)(picks ? row_src[m] : min(m0 + m, M - 1)) * ldr + n8));
             }
         }
     };
@@ -601,18 +648,18 @@ template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, 
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
+    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, GemmMore more)
 {
-    w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, qe);
+    w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, more);
 }
 // The tile of 96 rows, which only the choice takes, under a name of its own: a profile tells it by that from the tiles that can be pinned.
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows96_kernel(
     const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, quota_qkv_epilogue qe)
+    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, GemmMore more)
 {
-    w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, qe);
+    w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, more);
 }
 
 // Tile instantiations; the number is what quota_set_gemm_variant pins.
@@ -654,7 +701,7 @@ const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128
                              {64, 256, 256, QUOTA_K_GEMM_64X256}, {96, 128, 256, QUOTA_K_GEMM_96X128}};
 
 typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
-                          int, f16 *, int, const f16 *, int, int32_t *, int, int, quota_qkv_epilogue);
+                          int, f16 *, int, const f16 *, int, int32_t *, int, int, GemmMore);
 
 template <ActFormat P, Epilogue E>
 f8_kernel tile_kernel(int v)
@@ -681,7 +728,7 @@ f8_kernel tile_kernel(int v)
 
 int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const float *sa, int M,
               const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int32_t *acc, hipStream_t st,
-              const quota_qkv_epilogue *qe = nullptr)
+              const quota_qkv_epilogue *qe = nullptr, const quota_kept_rows *kept = nullptr)
 {
     const TileShape &t = kTiles[v];
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
@@ -690,10 +737,12 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
     ProfScope prof(kernel_id, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md +
                        (qe ? Md * (Nd / 3) * (7 + 1.0 / 16) + 4 * Md : 2.0 * Md * (ldy < W->N ? ldy : Nd) * (res ? 2 : 1)), st);
-    static const quota_qkv_epilogue no_qe = {};
+    GemmMore more = {};
+    if (qe) more.qkv = *qe;
+    else if (kept) more.kept = *kept;
     kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>(qa, sa, M, W->K, G, (const uint4 *)W->packed,
                                                            (const f16 *)W->scales, W->N, y, ldy, res, ldr, acc, tiles_m,
-                                                           tiles_n, qe ? *qe : no_qe);
+                                                           tiles_n, more);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -796,6 +845,19 @@ int quota_internal_w4a4_gemm_a6(const uint8_t *qa6, const float *sa, int M, cons
     const int v = choose_tile(acts_of(M), M, W->N, W->K, 0, 256);
     return launch_f8(quota_a6_starts(M) ? tile_kernel<A6_STARTS, PLAIN>(v) : tile_kernel<A6, PLAIN>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_f16, ldy,
                      (const f16 *)residual_opt, ldr, nullptr, st);
+}
+
+bool quota_gemm_gathers(int M, const quota_weights *W)
+{
+    return M > 16 && !quota_a6_starts(M) && W->N % 64 == 0 && W->K % 32 == 0 && scales_on_dwords(W);
+}
+int quota_internal_w4a4_gemm_a6_kept(const uint8_t *qa6, const float *sa, int M, const quota_kept_rows *kept, const quota_weights *W, void *y_f16, int ldy,
+                                     const void *residual, int ldr, hipStream_t st)
+{
+    if (!qa6 || !sa || !kept || !kept->keep_idx || !W || !W->packed || !W->scales || !y_f16 || !residual) return QUOTA_ERR_NULL;
+    if (!quota_gemm_gathers(M, W) || kept->k_keep <= 0 || kept->n_keep <= 0) return QUOTA_ERR_SHAPE;
+    const int v = choose_tile(A6, M, W->N, W->K, 0, 256);
+    return launch_f8(tile_kernel<A6, PLAIN>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_f16, ldy, (const f16 *)residual, ldr, nullptr, st, nullptr, kept);
 }
 
 // Gate/up projection with SiLU(gate) * up in the epilogue: z [M][N / 2], the bits of the plain projection and the

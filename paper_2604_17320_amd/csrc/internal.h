@@ -6,6 +6,40 @@
 #include "prefetch.h"
 #include "headmeans.h"
 
+// The rows that a layer keeps, [B][n_keep] of [B][N]: text before the visual tokens, the kept ones of those, text behind.  keep_idx: null: the first k_keep.
+struct quota_kept_rows {
+    const int32_t *keep_idx;
+    int N, vis_begin, Nv, k_keep, n_keep;
+    // The index that row j of sequence b needs, and with it the row of the sequence: never one outside it
+    __device__ __forceinline__ int index(int b, int j) const
+    {
+        return keep_idx ? keep_idx[(size_t)b * k_keep + min(max(j - vis_begin, 0), k_keep - 1)] : j - vis_begin;
+    }
+    __device__ __forceinline__ int row(int j, int idx) const
+    {
+        const int src = j < vis_begin ? j : j < vis_begin + k_keep ? vis_begin + idx : j - k_keep + Nv;
+        return min(max(src, 0), N - 1);
+    }
+};
+// Rows to quantize beside a launch that leaves CUs idle: fp16 [M][d] into the A6 format without start values.
+struct quota_rows_beside {
+    const f16 *x;
+    uint32_t *q;
+    float *scale;
+    int M, d;
+};
+// What is left of the compaction where nobody gathers rows: the kept rows' 4-bit K/V into the cache, their positions and numbers.
+struct quota_kept_copies {
+    quota_kept_rows kept;
+    int rows, dkv, capacity, len;                // rows: of all sequences
+    const uint32_t *skc, *svc;
+    const f16 *sks, *svs;
+    const int32_t *pos;
+    uint32_t *ckc, *cvc;
+    f16 *cks, *cvs;
+    int32_t *pos_out, *rows_out;
+};
+
 // score kernel with a separate sequence stride for the sumsq/ressq arrays, so
 // the layer can pass the per-row side outputs of the quantizer directly
 int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
@@ -17,8 +51,10 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
                               const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
-                              hipStream_t st, PrefetchList *weights, const quota_cue_masses *masses);
+                              hipStream_t st, PrefetchList *weights, const quota_cue_masses *masses, const quota_rows_beside *beside = nullptr);
 bool quota_score_takes_means(int Nv, int H);
+// Whether it takes rows to quantize beside it
+bool quota_score_quantizes_beside(int Nv, int M, int d);
 
 // attention and, if cm_inter or cm_intra is given, the cue pass with its head means [B][Nv]; masses: without the means, for whom they are
 // left then
@@ -83,12 +119,16 @@ inline size_t quota_a6_bytes(size_t M, int K)
     return (rows > frag ? rows : frag) + (quota_a6_starts(M) ? M * G * sizeof(float) : 0);
 }
 int quota_internal_rmsnorm_quantize_a6(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa6,
-                                       float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st);
+                                       float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st, const quota_kept_copies *copies = nullptr);
 int quota_internal_silu_mul_quantize_a6(const void *gu_f16, int M, int F, uint8_t *qa6, float *scale, void *z_opt,
                                         const void *z_inject_opt, hipStream_t st);
 int quota_internal_quantize_a6(const void *x_f16, int M, int d, uint8_t *qa6, float *scale, hipStream_t st);
 int quota_internal_w4a4_gemm_a6(const uint8_t *qa6, const float *sa, int M, const quota_weights *W, void *y_f16, int ldy,
                                 const void *residual_opt, int ldr, hipStream_t st);
+// The same on the kept rows of activations and residual, M of B * N: M > 16, below quota_a6_starts, scales on dwords (quota_gemm_gathers)
+bool quota_gemm_gathers(int M, const quota_weights *W);
+int quota_internal_w4a4_gemm_a6_kept(const uint8_t *qa6, const float *sa, int M, const quota_kept_rows *kept, const quota_weights *W, void *y_f16, int ldy,
+                                     const void *residual, int ldr, hipStream_t st);
 int quota_internal_w4a4_gemm_silu(const uint8_t *qa6, const float *sa, int M, const quota_weights *W, void *z_f16, hipStream_t st);
 
 // GEMM of at most 16 rows, or as fragments 32 (rows16.hip).  The quantizing forms take fp16 rows, for the M and K that

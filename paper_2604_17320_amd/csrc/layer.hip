@@ -121,14 +121,14 @@ static int qkv_rope_kv_quant(const quota_layer *L, const LayerWs &w, int M, cons
 // format, and a few leave the quantizer to the GEMM.
 #define ROWS_FRAG 32
 static int rmsnorm_gemm(const LayerWs &w, const void *x, int M, int d, const float *gamma, float eps,
-                        const quota_weights *W, void *y, int ldy, hipStream_t st)
+                        const quota_weights *W, void *y, int ldy, hipStream_t st, const quota_kept_copies *copies = nullptr)
 {
     if (quota_internal_rows16_quantizes(M, d)) return quota_internal_rows16_rmsnorm(x, gamma, eps, M, W, y, ldy, false, st);
     if (M <= ROWS_FRAG) {
         TRY(quota_internal_rmsnorm_quantize_frag(x, M, d, gamma, eps, w.qa, w.sa, st));
         return quota_internal_rows16(w.qa, QUOTA_ROWS16_FRAG, w.sa, M, W, y, ldy, nullptr, 0, st);
     }
-    TRY(quota_internal_rmsnorm_quantize_a6(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st));
+    TRY(quota_internal_rmsnorm_quantize_a6(x, M, d, gamma, eps, w.qa, w.sa, nullptr, nullptr, st, copies));
     return quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, W, y, ldy, nullptr, 0, st);
 }
 static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const quota_weights *W, void *y, int ldy,
@@ -145,7 +145,9 @@ static int quantize_gemm(const LayerWs &w, const void *x, int M, int d, const qu
 // The SwiGLU block on rows x1, added to them: RMSNorm, quantizer, gate/up, SiLU product, quantizer, down.  Without taps that
 // want the gate | up rows or z, the gate/up projection makes the product itself, where its tile can, and w.gu holds z.
 // Else it stores gate | up and the quantizer in front of down makes the product (any number of rows, in the A6 format).
-static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1, const quota_taps *t, void *x_out, hipStream_t st)
+// copies: what the first quantizer takes along (more than ROWS_FRAG rows).
+static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1, const quota_taps *t, void *x_out, hipStream_t st,
+                  const quota_kept_copies *copies = nullptr)
 {
     const int d = L->H * L->dh, F = L->F;
     if (!t->gu && !t->z && !t->inject_z) {
@@ -156,14 +158,14 @@ static int swiglu(const quota_layer *L, const LayerWs &w, int M, const void *x1,
             TRY(quota_internal_rmsnorm_quantize_frag(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, st));
             rc = quota_internal_rows16_frag_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
         } else {
-            TRY(quota_internal_rmsnorm_quantize_a6(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st));
+            TRY(quota_internal_rmsnorm_quantize_a6(x1, M, d, L->gamma2, L->eps, w.qa, w.sa, nullptr, nullptr, st, copies));
             rc = quota_internal_w4a4_gemm_silu(w.qa, w.sa, M, &L->gu, w.gu, st);
         }
         if (rc == QUOTA_OK) return quantize_gemm(w, w.gu, M, F, &L->down, x_out, d, x1, d, st);
         if (rc != QUOTA_ERR_SHAPE) return rc;
         TRY(quota_internal_w4a4_gemm_a6(w.qa, w.sa, M, &L->gu, w.gu, 2 * F, nullptr, 0, st));
     } else {
-        TRY(rmsnorm_gemm(w, x1, M, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st));
+        TRY(rmsnorm_gemm(w, x1, M, d, L->gamma2, L->eps, &L->gu, w.gu, 2 * F, st, copies));
         TRY(dump(t->gu, w.gu, (size_t)M * 2 * F * 2, st));
     }
     TRY(quota_internal_silu_mul_quantize_a6(w.gu, M, F, w.qa, w.sa, t->z, t->inject_z, st));
@@ -244,11 +246,19 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
     TRY(dump(t->o, w.o, (size_t)M * d * 2, st));
     const f16 *o_used = t->inject_o ? (const f16 *)t->inject_o : w.o;
 
+    // Few rows are not gathered: the attention output's are all quantized beside the scoring, which leaves nearly all CUs idle, the output projection picks the
+    // kept ones of them and of the hidden state, and the quantizer behind it takes their K/V along.  That is a launch less, 2.2 us beside its own 2.4: 32 layers of
+    // 7B, 640 to 122 tokens, 4134 -> 4025 us, a layer of 640 tokens over changing weights 147.4 -> 143.1, of 165 tokens 113.6 -> 109.8, one of 512 channels and 80
+    // tokens, replayed, 47.2 -> 44.8.  Only below 512 kept rows of at most 1024: more take longer to quantize than tokens to score, and the dropped ones are
+    // quantized for nothing.
+    const bool picked = score && k_keep > 0 && Mk > ROWS_FRAG && quota_score_quantizes_beside(Nv, M, d) && quota_gemm_gathers(Mk, &L->o);
+    const quota_rows_beside o_rows = {o_used, (uint32_t *)w.qa, w.sa, M, d};
+
     // Eq. 6-9: cues -> G -> fused score -> top-K_l over the visual tokens (candidate layers only)
     if (score) {
         TRY(quota_internal_score_topk(w.sumsq + vb, w.ressq + vb, N, inject_cm ? t->inject_cm_inter : w.cm_inter,
                                       inject_cm ? t->inject_cm_intra : w.cm_intra, B, Nv, p, w.score, k_keep,
-                                      w.keep_idx, st, fetch, leave_means ? &masses : nullptr));
+                                      w.keep_idx, st, fetch, leave_means ? &masses : nullptr, picked ? &o_rows : nullptr));
         if (t->sumsq || t->ressq) {
             long n = (long)B * Nv;
             dim3 g((unsigned)((n + 255) / 256)), blk(256);
@@ -260,6 +270,21 @@ extern "C" int quota_prefill_layer(const quota_layer *L, quota_state *s, int K_l
         TRY(dump(t->cm_intra, w.cm_intra, (size_t)B * Nv * 4, st));
         TRY(dump(t->score, w.score, (size_t)B * Nv * 4, st));
         TRY(dump(t->keep_idx, w.keep_idx, (size_t)B * k_keep * 4, st));
+    }
+
+    if (picked) {
+        const quota_kept_rows kept = {w.keep_idx, N, vb, Nv, k_keep, n_keep};
+        const quota_kept_copies copies = {kept, Mk, dkv, cache->capacity, cache->len, (const uint32_t *)w.skc, (const uint32_t *)w.svc, w.sks, w.svs, s->pos,
+                                          (uint32_t *)cache->k_codes, (uint32_t *)cache->v_codes, (f16 *)cache->k_scales, (f16 *)cache->v_scales,
+                                          s->pos_out, w.rows};
+        TRY(quota_internal_w4a4_gemm_a6_kept(w.qa, w.sa, Mk, &kept, &L->o, w.x1, d, s->x, d, st));
+        TRY(dump(t->x1, w.x1, (size_t)Mk * d * 2, st));
+        TRY(swiglu(L, w, Mk, w.x1, t, s->x_out, st, &copies));
+        TRY(dump(t->rows, w.rows, (size_t)Mk * 4, st));
+        cache->len += n_keep;
+        s->N = n_keep;
+        s->Nv = k_keep;
+        return QUOTA_OK;
     }
 
     // compaction: kept rows of x / pos move on, their 4-bit K/V go to the cache, and the kept

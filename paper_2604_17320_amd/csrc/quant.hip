@@ -254,12 +254,41 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
     }
 }
 
-template <bool WANT_METRICS, int GROUP, int NCH, typename OUT>
+// Workgroups behind the quantizer's, one per kept row (see quota_kept_copies)
+struct NoCopies {};
+__device__ __forceinline__ void copy_kept_row(const NoCopies &, int) {}
+__device__ __forceinline__ void copy_kept_row(const quota_kept_copies &c, int m)
+{
+    const int b = m / c.kept.n_keep, j = m - b * c.kept.n_keep, src = c.kept.row(j, c.kept.index(b, j));
+    const size_t from = (size_t)b * c.kept.N + src, to = (size_t)b * c.capacity + c.len + j;
+    const int nkv = c.dkv >> 3, ng = c.dkv >> 6;         // dwords of codes, group scales per K or V row
+    for (int i = threadIdx.x; i < nkv; i += ROW_THREADS) {
+        const uint32_t k = c.skc[from * nkv + i], v = c.svc[from * nkv + i];
+        c.ckc[to * nkv + i] = k;
+        c.cvc[to * nkv + i] = v;
+    }
+    if ((int)threadIdx.x < ng) {
+        c.cks[to * ng + threadIdx.x] = c.sks[from * ng + threadIdx.x];
+        c.cvs[to * ng + threadIdx.x] = c.svs[from * ng + threadIdx.x];
+    }
+    if (threadIdx.x == 0) {
+        c.pos_out[m] = c.pos[from];
+        c.rows_out[m] = src;
+    }
+}
+
+template <bool WANT_METRICS, int GROUP, int NCH, typename OUT, typename COPIES = NoCopies>
 __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
     const f16 *__restrict__ x, int M, int d, long ldx, const float *__restrict__ gamma, float eps,
     OUT q, float *__restrict__ scale, float *__restrict__ sumsq,
-    float *__restrict__ ressq, f16 *__restrict__ h_out)
+    float *__restrict__ ressq, f16 *__restrict__ h_out, COPIES copies)
 {
+    if constexpr (!std::is_same_v<COPIES, NoCopies>) {
+        if ((int)blockIdx.x >= M) {
+            copy_kept_row(copies, blockIdx.x - M);
+            return;
+        }
+    }
     ROW_PROLOGUE();
     const int nchunk = d >> 3;
     const uint4 *xr = reinterpret_cast<const uint4 *>(x + (size_t)row * ldx);
@@ -533,7 +562,7 @@ static int rmsnorm_quantize(const void *x_f16, int M, int d, int ldx, const floa
         if constexpr (METRICS)
             if (sumsq_opt || ressq_opt) kernel = rmsnorm_quantize_act_kernel<true, group(), nch(), OUT>;
         kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, gamma, eps, q, scale, sumsq_opt, ressq_opt,
-                                                   (f16 *)h_opt);
+                                                   (f16 *)h_opt, NoCopies{});
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
@@ -554,11 +583,21 @@ extern "C" int quota_rmsnorm_quantize_act(const void *x_f16, int M, int d, int l
 }
 
 int quota_internal_rmsnorm_quantize_a6(const void *x_f16, int M, int d, const float *gamma, float eps, uint8_t *qa6,
-                                       float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st)
+                                       float *scale, float *sumsq_opt, float *ressq_opt, hipStream_t st, const quota_kept_copies *copies)
 {
     int rc = check_rows(x_f16, M, d, d, qa6, scale);
     if (rc != QUOTA_OK) return rc;
     if (M == 0) return QUOTA_OK;
+    if (copies) {                            // (quota_score_quantizes_beside: rows of at most 8192 columns, less than quota_a6_starts of them)
+        if (quota_a6_starts(M) || d > 8192) return QUOTA_ERR_SHAPE;
+        ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
+        auto kernel = d <= 4096 ? rmsnorm_quantize_act_kernel<false, 256, 2, RowOutA6, quota_kept_copies>
+                                : rmsnorm_quantize_act_kernel<false, 256, 4, RowOutA6, quota_kept_copies>;
+        kernel<<<dim3(M + copies->rows), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, gamma, eps, RowOutA6{(uint32_t *)qa6}, scale, nullptr,
+                                                                     nullptr, nullptr, *copies);
+        QUOTA_RETURN_IF_LAUNCH_FAILED();
+        return QUOTA_OK;
+    }
     return with_a6_out(qa6, M, [&](auto out) { return rmsnorm_quantize(x_f16, M, d, d, gamma, eps, out, scale, sumsq_opt, ressq_opt, nullptr, st); });
 }
 

@@ -12,6 +12,7 @@
 #include <type_traits>
 #include "prefetch.h"
 #include "headmeans.h"
+#include "rowquant.h"
 
 namespace {
 
@@ -449,13 +450,49 @@ __device__ __forceinline__ void wave_topk(const uint32_t (&key)[WAVE_KEYS], int 
 // front of the output and two around the counts in it, where a select by all waves takes three for every pass: 64 / 256 / 576 / 1000 tokens 6.7 /
 // 7.6 / 8.7 / 10.0 -> 4.5 / 5.2 / 7.0 / 8.8 us (with the output by the one wave too 576 tokens 7.8).
 struct MeansThere {};            // (the cues' head means are in src)
-template <typename MEANS, typename PRE>
+// Workgroups between the sequences' and the fetching ones: four rows each, a quarter of the threads to a row.
+struct NoRows {
+    __device__ __forceinline__ int wgs() const { return 0; }
+    __device__ __forceinline__ void operator()(int) const {}
+};
+template <int NCH>
+struct RowsBeside {
+    quota_rows_beside r;
+    __host__ __device__ __forceinline__ int wgs() const { return (r.M + 3) / 4; }
+    __device__ __forceinline__ void operator()(int wg) const
+    {
+        __shared__ float top[SCORE_WAVES];
+        const int lane = threadIdx.x & 255, quarter = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+        const int row = min(4 * wg + quarter, r.M - 1), nchunk = r.d >> 3;       // (past the last: the same once more)
+        const uint4 *xr = reinterpret_cast<const uint4 *>(r.x + (size_t)row * r.d);
+        Pack16 v[NCH];
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) v[i].u = xr[min(lane + 256 * i, nchunk - 1)];
+        E6Store store;
+        store.make(lane, row);
+        float a = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf((float)v[i].h[e]));       // (a clamped chunk repeats one of the row's)
+        a = wave_absmax(a);
+        if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = a;
+        __syncthreads();
+        a = fmaxf(fmaxf(top[4 * quarter], top[4 * quarter + 1]), fmaxf(top[4 * quarter + 2], top[4 * quarter + 3]));
+        float s;
+        quantize_cached_row<false, 256, NCH>(v, nchunk, lane, a, row_out(RowOutA6{r.q}, row, nchunk), store, s);
+        if (lane == 0) r.scale[row] = s;
+    }
+};
+template <typename MEANS, typename PRE, typename ROWS>
 __global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(MetricSrc src, long stride_sq, int B, int Nv, quota_score_params p,
                                                                          float *__restrict__ score, float *__restrict__ normed, int K,
-                                                                         int32_t *__restrict__ keep_idx, MEANS cues, PRE pre)
+                                                                         int32_t *__restrict__ keep_idx, MEANS cues, PRE pre, ROWS rows)
 {
     if ((int)blockIdx.x >= B) {
-        prefetch<SCORE_THREADS>(pre, blockIdx.x - B, gridDim.x - B);
+        const int beside = rows.wgs(), wg = blockIdx.x - B;
+        if (wg < beside) rows(wg);
+        else prefetch<SCORE_THREADS>(pre, wg - beside, gridDim.x - B - beside);
         return;
     }
     __shared__ __align__(16) int counters[8][256];
@@ -587,14 +624,19 @@ __global__ __launch_bounds__(SCORE_THREADS) void topk_kernel(const float *__rest
 // is above the default limit of a launch and has to be granted once per device.
 int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const quota_score_params &p,
                       float *score, float *normed, int K, int32_t *keep_idx, hipStream_t st, PrefetchList *weights = nullptr,
-                      const quota_cue_masses *masses = nullptr)
+                      const quota_cue_masses *masses = nullptr, const quota_rows_beside *beside = nullptr)
 {
     const auto share = weights ? weights->take(B, 7.0f, 4.0f) : PrefetchList::Share{};
     if (Nv <= SCORE_THREADS) {
         share.run([&](auto pre) {
-            const dim3 grid(B + share.wgs), block(SCORE_THREADS);
-            if (masses) small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, *masses, pre);
-            else small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, MeansThere{}, pre);
+            auto launch = [&](auto rows, int more) {
+                const dim3 grid(B + more + share.wgs), block(SCORE_THREADS);
+                if (masses) small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, *masses, pre, rows);
+                else small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, MeansThere{}, pre, rows);
+            };
+            if (!beside) launch(NoRows{}, 0);
+            else if (beside->d <= 4096) launch(RowsBeside<2>{*beside}, RowsBeside<2>{*beside}.wgs());
+            else launch(RowsBeside<4>{*beside}, RowsBeside<4>{*beside}.wgs());
         });
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
@@ -653,11 +695,14 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
 // 64 tokens 0.7, 256 0.8, 576 0.2; 7B shape, 32 heads, 101 tokens 3.2, 160 2.9, 256 1.7, 300 0.0, 320 -0.7, 576 -5.6; 13B shape, 40 heads, 250 tokens 1.3.
 bool quota_score_takes_means(int Nv, int H) { return Nv <= SCORE_THREADS && (long)Nv * H <= 10240; }
 
+// Rows to quantize beside it: as many as fit the chip at once, four to a workgroup and two workgroups a CU, are done before the tokens are scored.
+bool quota_score_quantizes_beside(int Nv, int M, int d) { return Nv > 0 && Nv <= SCORE_THREADS && M > 0 && M <= 1024 && d % 128 == 0 && d <= 8192; }
+
 // score + top-k in one launch (the layer's path)
 int quota_internal_score_topk(const float *sumsq, const float *ressq, long stride_sq,
                               const float *cm_inter, const float *cm_intra, int B, int Nv,
                               const quota_score_params *p, float *score, int K, int32_t *keep_idx,
-                              hipStream_t st, PrefetchList *weights, const quota_cue_masses *masses)
+                              hipStream_t st, PrefetchList *weights, const quota_cue_masses *masses, const quota_rows_beside *beside)
 {
     if (!sumsq || !ressq || !p || !score || !keep_idx || !cm_inter || !cm_intra) return QUOTA_ERR_NULL;
     if (B <= 0 || Nv < 0 || K < 0 || p->pct_lo < 0 || p->pct_hi > 100 || p->pct_lo > p->pct_hi)
@@ -668,7 +713,8 @@ int quota_internal_score_topk(const float *sumsq, const float *ressq, long strid
                    20.0 * B * Nv + 4.0 * B * (K < Nv ? K : Nv), st);
     MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
     if (masses && !quota_score_takes_means(Nv, masses->H)) return QUOTA_ERR_SHAPE;
-    return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st, weights, masses);
+    if (beside && !quota_score_quantizes_beside(Nv, beside->M, beside->d)) return QUOTA_ERR_SHAPE;
+    return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st, weights, masses, beside);
 }
 
 extern "C" void quota_score_params_default(quota_score_params *p)

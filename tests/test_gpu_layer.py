@@ -452,6 +452,54 @@ def test_layer_96_row_tile_adds_the_residual(qb, rows, pinned_gemm):
     assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
 
 
+# A layer that picks its kept rows (33 to 511 of at most 1024): the fewest, sequences with text on both sides, a single kept token, rows of two and of four chunks a
+# thread, the most rows in and kept, each pinned tile; and beside each limit, where it gathers them.
+@pytest.mark.parametrize("tile,H,Hkv,dh,B,N,vb,Nv,K", [(-1, 8, 8, 64, 1, 80, 0, 64, 17), (-1, 8, 8, 64, 1, 80, 0, 64, 16), (-1, 8, 4, 64, 3, 101, 14, 70, 1),
+                                                       (-1, 40, 8, 128, 1, 333, 30, 290, 157), (-1, 8, 8, 64, 1, 1024, 1, 1020, 507),
+                                                       (-1, 8, 8, 64, 1, 1024, 1, 1020, 508), (-1, 8, 8, 64, 1, 1025, 0, 1024, 300),
+                                                       (-1, 10, 2, 128, 2, 512, 5, 500, 200), (0, 8, 8, 64, 2, 200, 7, 150, 60), (1, 8, 8, 64, 2, 200, 7, 150, 60),
+                                                       (2, 8, 8, 64, 2, 200, 7, 150, 60), (3, 8, 8, 64, 2, 200, 7, 150, 60), (4, 8, 8, 64, 2, 200, 7, 150, 60)])
+def test_layer_that_picks_its_rows(qb, tile, H, Hkv, dh, B, N, vb, Nv, K, pinned_gemm):
+    """Hidden state, positions, kept rows and cache have the bits of the layer whose output projection, with weight scales between two dwords, takes gathered
+    rows; the launches say which of the two ran."""
+    from paper_2604_17320_amd.model import KVCache4, PackedLinear, PrefillLayer, make_taps
+    d, F, n_keep = H * dh, 640, N - Nv + K
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + K)
+    def linear(n, k):
+        codes = torch.randint(-8, 8, (n, k), generator=g, device="cuda", dtype=torch.int8)
+        scales = (torch.rand((n, (k + 127) // 128), generator=g, device="cuda") * 0.002 + 0.001).to(torch.float16)
+        return PackedLinear.from_codes(codes, scales)
+    cos, sin = (dev(t) for t in wl.rope_tables(dh, N))
+    ones = torch.ones(d, device="cuda")
+    L = PrefillLayer(H, dh, F, linear(d + 2 * Hkv * dh, d), linear(d, d), linear(2 * F, d), linear(d, F), ones, ones, 1e-5, cos, sin, Hkv)
+    x = torch.randn((B * N, d), generator=g, device="cuda").to(torch.float16)
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").repeat(B) + 3
+    odd = torch.cat([L.o.scales.new_zeros(1), L.o.scales.flatten()])
+    even = L.desc.o.scales
+    outs = []
+    for scales in (odd[1:].data_ptr(), even):
+        L.desc.o.scales = scales
+        pinned_gemm(tile)
+        cache = KVCache4(B, n_keep + 3, Hkv, dh)
+        for t in (cache.k_codes, cache.v_codes, cache.k_scales, cache.v_scales):
+            t.zero_()
+        cache.desc.len = 2
+        x_out = torch.full((B * n_keep, d), float("nan"), dtype=torch.float16, device="cuda")
+        pos_out, rows = (torch.full((B * n_keep,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        ws = torch.full((L.workspace_bytes(B, N),), 0xFF, dtype=torch.uint8, device="cuda")
+        st = qb.State(B, N, vb, Nv, x.data_ptr(), pos.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+        qb.quota_profile_begin(64)
+        qb.quota_prefill_layer(L.desc, st, K, qb.quota_score_params_default(), cache.desc, make_taps(rows=rows), ws)
+        gathers = qb.quota_profile_collect().get("compact_rows", {}).get("launches", 0)
+        assert gathers == (0 if scales == even and 32 < B * n_keep < 512 and B * N <= 1024 and Nv <= 1024 else 1)
+        assert (st.N, st.Nv, cache.len) == (n_keep, K, n_keep + 2)
+        outs.append([host(t) for t in (x_out, pos_out, rows, cache.k_codes, cache.v_codes, cache.k_scales, cache.v_scales)])
+    assert np.isfinite(outs[0][0].astype(np.float32)).all()
+    for a, b in zip(*outs):
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+
+
 def test_layer_with_weight_scales_at_an_odd_halfword(qb):
     """Weight scales that start between two dwords: a prefill layer and its decode-sized remainder give the bits of the
     aligned layer (the fused QKV epilogue and the tiles step aside)."""
