@@ -189,9 +189,10 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
 // to back, the reductions are wave shuffles and there is no workgroup barrier.  GROUP = 256 (up to
 // 32768 columns): the whole workgroup owns the row and reduces through LDS.
 // Below this many rows the launch cannot fill the chip with one wave per row, and a row is
-// finished sooner by a whole workgroup.
+// finished sooner by a whole workgroup (512 threads for a layer's few wide rows, see with_row_shape).
 #define ROW_WAVE_MIN_ROWS 2048
 
+constexpr int row_threads(int group) { return group == 64 ? 256 : group; }
 template <int GROUP, bool MAX, bool SUM>
 __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
 {
@@ -199,18 +200,18 @@ __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
         if (MAX) mx = wave_absmax(mx);
         if (SUM) sum = wave_sum(sum);
     } else {
-        block_max_sum<4, MAX, SUM>(mx, sum, sm);
+        block_max_sum<GROUP / 64, MAX, SUM>(mx, sum, sm);
     }
 }
 #define ROW_PROLOGUE()                                                                         \
-    __shared__ double sm[8];                                                                   \
+    __shared__ double sm[GROUP == 64 ? 8 : GROUP / 32];                                                                   \
     const int lane = threadIdx.x % GROUP;                                                      \
-    const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (ROW_THREADS / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
+    const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (row_threads(GROUP) / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
     (void)sm
 
 template <bool WANT_METRICS, int GROUP, int NCH, typename OUT>
-__global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
+__global__ __launch_bounds__(row_threads(GROUP)) void quantize_act_kernel(
     const f16 *__restrict__ x, int M, int d, long ldx, int rows_per_seq, long seq_stride,
     OUT q, float *__restrict__ scale, float *__restrict__ sumsq,
     float *__restrict__ ressq)
@@ -256,13 +257,13 @@ __global__ __launch_bounds__(ROW_THREADS) void quantize_act_kernel(
 
 // Workgroups behind the quantizer's, one per kept row (see quota_kept_copies)
 struct NoCopies {};
-__device__ __forceinline__ void copy_kept_row(const NoCopies &, int) {}
+template <int THREADS>
 __device__ __forceinline__ void copy_kept_row(const quota_kept_copies &c, int m)
 {
     const int b = m / c.kept.n_keep, j = m - b * c.kept.n_keep, src = c.kept.row(j, c.kept.index(b, j));
     const size_t from = (size_t)b * c.kept.N + src, to = (size_t)b * c.capacity + c.len + j;
     const int nkv = c.dkv >> 3, ng = c.dkv >> 6;         // dwords of codes, group scales per K or V row
-    for (int i = threadIdx.x; i < nkv; i += ROW_THREADS) {
+    for (int i = threadIdx.x; i < nkv; i += THREADS) {
         const uint32_t k = c.skc[from * nkv + i], v = c.svc[from * nkv + i];
         c.ckc[to * nkv + i] = k;
         c.cvc[to * nkv + i] = v;
@@ -278,14 +279,14 @@ __device__ __forceinline__ void copy_kept_row(const quota_kept_copies &c, int m)
 }
 
 template <bool WANT_METRICS, int GROUP, int NCH, typename OUT, typename COPIES = NoCopies>
-__global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
+__global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kernel(
     const f16 *__restrict__ x, int M, int d, long ldx, const float *__restrict__ gamma, float eps,
     OUT q, float *__restrict__ scale, float *__restrict__ sumsq,
     float *__restrict__ ressq, f16 *__restrict__ h_out, COPIES copies)
 {
     if constexpr (!std::is_same_v<COPIES, NoCopies>) {
         if ((int)blockIdx.x >= M) {
-            copy_kept_row(copies, blockIdx.x - M);
+            copy_kept_row<row_threads(GROUP)>(copies, blockIdx.x - M);
             return;
         }
     }
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(ROW_THREADS) void rmsnorm_quantize_act_kernel(
 // EARLY: every load before the first use (short launches, latency counts); otherwise chunk by
 // chunk (long launches: fewer live registers, more waves per SIMD to hide the latency instead).
 template <int GROUP, int NCH, bool EARLY, typename OUT>
-__global__ __launch_bounds__(ROW_THREADS) void silu_mul_quantize_act_kernel(
+__global__ __launch_bounds__(row_threads(GROUP)) void silu_mul_quantize_act_kernel(
     const f16 *__restrict__ gu, int M, int F, OUT q, float *__restrict__ scale,
     f16 *__restrict__ z_out, const f16 *__restrict__ z_inject)
 {
@@ -449,10 +450,22 @@ static void with_row_shape(int M, int d, LAUNCH launch)
             return;
         }
     }
-    if (d <= 256 * 8 * 2) go(workgroup, std::integral_constant<int, 2>());
-    else if (d <= 256 * 8 * 4) go(workgroup, std::integral_constant<int, 4>());
-    else if (d <= 256 * 8 * 8) go(workgroup, std::integral_constant<int, 8>());
-    else if constexpr (MOST > 256 * 8 * 8) go(workgroup, std::integral_constant<int, 16>());
+    // A layer's few rows, wider than 2048 columns, by 512 threads each: one wave a SIMD waits between its instructions.  (16 x 4096 and 16 x 11008 of a decode
+    // step of 16 sequences over 32 layers, 1904 -> 1885 us; 32 layers of 640 to 122 rows 4158 -> 4137, one of 165 rows 109.7 -> 109.0; 1024 threads 1907, 4161 and 109.5;
+    // 16 layers of 512 channels take 0.5 % longer with 512.)
+    if constexpr (!OUT::MANY) {
+        const std::integral_constant<int, 512> wide;
+        if (d <= 2048) go(workgroup, std::integral_constant<int, 2>());
+        else if (d <= 512 * 8) go(wide, std::integral_constant<int, 1>());
+        else if (d <= 512 * 8 * 2) go(wide, std::integral_constant<int, 2>());
+        else if (d <= 512 * 8 * 4) go(wide, std::integral_constant<int, 4>());
+        else if constexpr (MOST > 512 * 8 * 4) go(wide, std::integral_constant<int, 8>());
+    } else {
+        if (d <= 256 * 8 * 2) go(workgroup, std::integral_constant<int, 2>());
+        else if (d <= 256 * 8 * 4) go(workgroup, std::integral_constant<int, 4>());
+        else if (d <= 256 * 8 * 8) go(workgroup, std::integral_constant<int, 8>());
+        else if constexpr (MOST > 256 * 8 * 8) go(workgroup, std::integral_constant<int, 16>());
+    }
 }
 
 extern "C" size_t quota_weights_packed_bytes(int N, int K)
@@ -542,7 +555,7 @@ extern "C" int quota_quantize_act(const void *x_f16, int M, int d, int ldx, uint
     with_row_shape<RowOutPacked>(M, d, [&](auto group, auto nch, dim3 grid) {
         auto kernel = sumsq_opt || ressq_opt ? quantize_act_kernel<true, group(), nch(), RowOutPacked>
                                              : quantize_act_kernel<false, group(), nch(), RowOutPacked>;
-        kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, M, 0, RowOutPacked{(uint32_t *)q_packed},
+        kernel<<<grid, dim3(row_threads(group())), 0, st>>>((const f16 *)x_f16, M, d, ldx, M, 0, RowOutPacked{(uint32_t *)q_packed},
                                                    scale, sumsq_opt, ressq_opt);
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -561,7 +574,7 @@ static int rmsnorm_quantize(const void *x_f16, int M, int d, int ldx, const floa
         auto kernel = rmsnorm_quantize_act_kernel<false, group(), nch(), OUT>;
         if constexpr (METRICS)
             if (sumsq_opt || ressq_opt) kernel = rmsnorm_quantize_act_kernel<true, group(), nch(), OUT>;
-        kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, ldx, gamma, eps, q, scale, sumsq_opt, ressq_opt,
+        kernel<<<grid, dim3(row_threads(group())), 0, st>>>((const f16 *)x_f16, M, d, ldx, gamma, eps, q, scale, sumsq_opt, ressq_opt,
                                                    (f16 *)h_opt, NoCopies{});
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -591,9 +604,10 @@ int quota_internal_rmsnorm_quantize_a6(const void *x_f16, int M, int d, const fl
     if (copies) {                            // (quota_score_quantizes_beside: rows of at most 8192 columns, less than quota_a6_starts of them)
         if (quota_a6_starts(M) || d > 8192) return QUOTA_ERR_SHAPE;
         ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
-        auto kernel = d <= 4096 ? rmsnorm_quantize_act_kernel<false, 256, 2, RowOutA6, quota_kept_copies>
-                                : rmsnorm_quantize_act_kernel<false, 256, 4, RowOutA6, quota_kept_copies>;
-        kernel<<<dim3(M + copies->rows), dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, gamma, eps, RowOutA6{(uint32_t *)qa6}, scale, nullptr,
+        auto kernel = d <= 2048   ? rmsnorm_quantize_act_kernel<false, 256, 2, RowOutA6, quota_kept_copies>
+                      : d <= 4096 ? rmsnorm_quantize_act_kernel<false, 512, 1, RowOutA6, quota_kept_copies>
+                                  : rmsnorm_quantize_act_kernel<false, 512, 2, RowOutA6, quota_kept_copies>;
+        kernel<<<dim3(M + copies->rows), dim3(d <= 2048 ? 256 : 512), 0, st>>>((const f16 *)x_f16, M, d, d, gamma, eps, RowOutA6{(uint32_t *)qa6}, scale, nullptr,
                                                                      nullptr, nullptr, *copies);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
@@ -607,12 +621,12 @@ static int silu_mul_quantize(const void *gu_f16, int M, int F, OUT q, float *sca
 {
     ProfScope prof(QUOTA_K_SILU_MUL_QUANTIZE_ACT, 0, 4.5 * M * F + 4.0 * M, st);
     with_row_shape<OUT>(M, F, [&](auto group, auto nch, dim3 grid) {
-        constexpr bool can_be_early = group() == 256 && nch() < 16;
+        constexpr bool can_be_early = group() >= 256 && nch() < 16;
         auto kernel = silu_mul_quantize_act_kernel<group(), nch(), can_be_early, OUT>;
         if constexpr (OUT::MANY && nch() > 2) {              // (two chunks: such a launch is the waves')
             if (M >= ROW_WAVE_MIN_ROWS) kernel = silu_mul_quantize_act_kernel<group(), nch(), false, OUT>;
         }
-        kernel<<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt);
+        kernel<<<grid, dim3(row_threads(group())), 0, st>>>((const f16 *)gu_f16, M, F, q, scale, (f16 *)z_opt, (const f16 *)z_inject_opt);
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
@@ -643,7 +657,7 @@ static int quantize_rows(const void *x_f16, int M, int d, OUT q, float *scale, h
 {
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M, st);
     with_row_shape<OUT>(M, d, [&](auto group, auto nch, dim3 grid) {
-        quantize_act_kernel<false, group(), nch(), OUT><<<grid, dim3(ROW_THREADS), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, q,
+        quantize_act_kernel<false, group(), nch(), OUT><<<grid, dim3(row_threads(group())), 0, st>>>((const f16 *)x_f16, M, d, d, M, 0, q,
                                                                                             scale, nullptr, nullptr);
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -685,7 +699,7 @@ int quota_internal_vector_metrics(const void *v_f16, int B, int Nv, int d, int l
     if (Nv == 0) return QUOTA_OK;
     ProfScope prof(QUOTA_K_QUANTIZE_ACT, 0, 2.0 * B * Nv * d + 8.0 * B * Nv, st);
     with_row_shape<RowOutPacked>(B * Nv, d, [&](auto group, auto nch, dim3 grid) {
-        quantize_act_kernel<true, group(), nch(), RowOutPacked><<<grid, dim3(ROW_THREADS), 0, st>>>(
+        quantize_act_kernel<true, group(), nch(), RowOutPacked><<<grid, dim3(row_threads(group())), 0, st>>>(
             (const f16 *)v_f16, B * Nv, d, ldv, Nv, stride_b, RowOutPacked{nullptr}, nullptr, sumsq, ressq);
     });
     QUOTA_RETURN_IF_LAUNCH_FAILED();
