@@ -22,6 +22,7 @@ FLAGS = [
     "-ffp-contract=off",                       # every fp32 step rounds; fma only where written
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",     # MFMA results in VGPRs: the epilogue reads them directly
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",     # a kernel's first arguments are in registers when a wave starts
     "-Wall", "-Wno-unused-function",
 ]
 

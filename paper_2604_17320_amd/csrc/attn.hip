@@ -104,8 +104,8 @@ __device__ __forceinline__ float halves_max(float v)
 
 template <int DH, int W, typename PRE>
 __global__ __launch_bounds__(64 * W, W / 2) void attn_fwd_kernel(
-    const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, int N,
-    int H, int Hkv, f16 *__restrict__ o, float *__restrict__ lse2, float scale_log2, int wgs, PRE pre)
+    int wgs, int N, int H, int Hkv, const f16 *__restrict__ q, const f16 *__restrict__ khat, const f16 *__restrict__ vhat, f16 *__restrict__ o,
+    float scale_log2, float *__restrict__ lse2, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
         prefetch<64 * W>(pre, blockIdx.x - wgs, gridDim.x - wgs);
@@ -261,8 +261,8 @@ template <int DH>
 constexpr size_t colmass_lds(int G, int W) { return (size_t)G * 2 * (KT * DH * 2 + KT * 4) + (G - 1) * 32 * W * sizeof(float2); }
 template <int DH, int G, int W, typename PRE>
 __global__ __launch_bounds__(64 * W * G, G == 1 ? 3 : 1) void colmass_kernel(
-    const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2, int N,
-    int H, int Hkv, int vis_begin, int Nv, float2 *__restrict__ partial, float scale_log2, int wgs, PRE pre)
+    int wgs, int N, int H, int Hkv, int vis_begin, int Nv, const f16 *__restrict__ q, const f16 *__restrict__ khat, const float *__restrict__ lse2,
+    float2 *__restrict__ partial, float scale_log2, PRE pre)
 {
     if ((int)blockIdx.x >= wgs) {
         prefetch<64 * W * G>(pre, blockIdx.x - wgs, gridDim.x - wgs);
@@ -460,7 +460,7 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
         s1.run([&](auto pre) {
             auto kernel = w1 == 4 ? (dh == 128 ? attn_fwd_kernel<128, 4, decltype(pre)> : attn_fwd_kernel<64, 4, decltype(pre)>)
                                   : (dh == 128 ? attn_fwd_kernel<128, 2, decltype(pre)> : attn_fwd_kernel<64, 2, decltype(pre)>);
-            kernel<<<g1, dim3(64 * w1), 0, st>>>(q, k, v, N, H, Hkv, (f16 *)o_f16, w.lse2, scale_log2, (int)n1, pre);
+            kernel<<<g1, dim3(64 * w1), 0, st>>>((int)n1, N, H, Hkv, q, k, v, (f16 *)o_f16, scale_log2, w.lse2, pre);
         });
     }
     QUOTA_RETURN_IF_LAUNCH_FAILED();
@@ -482,8 +482,8 @@ int quota_internal_attention(const void *q_f16, const void *khat_f16, const void
             constexpr int DH = decltype(dh_tag)::value, G = decltype(groups)::value, W = decltype(waves)::value;
             constexpr auto kernel = colmass_kernel<DH, G, W, decltype(pre)>;
             if ((granted = grant_lds<kernel>()))
-                kernel<<<g2, dim3(64 * W * G), colmass_lds<DH>(G, W), st>>>(q, k, w.lse2, N, H, Hkv, vis_begin, Nv, w.partial,
-                                                                       scale_log2, (int)n2, pre);
+                kernel<<<g2, dim3(64 * W * G), colmass_lds<DH>(G, W), st>>>((int)n2, N, H, Hkv, vis_begin, Nv, q, k, w.lse2, w.partial,
+                                                                            scale_log2, pre);
         };
         s2.run([&](auto pre) {
             auto with_dh = [&](auto dh_tag) {

@@ -101,11 +101,16 @@ constexpr int dec_red_floats(int dh, int hp, int vs) { return hp * dh / vs * dec
 
 template <int DH, int RC, int HP, bool MULTI, bool FUSED, bool SPLIT, int VS>
 __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void decode_attention_kernel(
-    const f16 *__restrict__ q, int d, int dkv, int rep, uint32_t *__restrict__ kc, f16 *__restrict__ ks,
-    uint32_t *__restrict__ vc, f16 *__restrict__ vs, int capacity, int len,
-    const int32_t *__restrict__ step_dev, int max_steps, f16 *__restrict__ o, int n_kv_heads, DecodeNew nw,
-    int n_split, int heads, float *__restrict__ part)
+    const int32_t *__restrict__ step_dev, const int32_t *__restrict__ pos, int wgs, int n_kv_heads, int rep_arg, int n_split, int d, int dkv,
+    const f16 *__restrict__ q, uint32_t *__restrict__ kc, f16 *__restrict__ ks, uint32_t *__restrict__ vc, f16 *__restrict__ vs, int capacity, int len,
+    int max_steps, int heads, f16 *__restrict__ o, DecodeNew nw, float *__restrict__ part)
 {
+    // The step count (without one: any number there is) and the new token's position are asked for together, before anything else needs them: by scalar loads,
+    // from address space 4, since nothing writes them while the kernel runs.
+    typedef const __attribute__((address_space(4))) int32_t *scalar_i32;
+    const int rep = RC == 1 ? 1 : rep_arg;
+    int step = 0;
+    if (FUSED || step_dev) step = *(scalar_i32)(uint64_t)(FUSED && !step_dev ? pos : step_dev);
     constexpr int PPT = DH / 32;            // 16-byte pieces (lanes) per token and head
     constexpr int TP = DEC_THREADS / PPT;   // tokens per pass of the workgroup
     constexpr int UN = DEC_TILE / TP;       // passes per tile
@@ -126,19 +131,22 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
     // (sequence, head) pairs are dealt to the 8 XCDs in contiguous ranges: the heads of a sequence
     // share the 128-byte lines of its cache rows (two heads' codes, all heads' scales), and each
     // XCD has its own L2
-    const int n_pass = (rep + RC - 1) / RC;            // workgroups per K/V head: RC query heads each
-    const int work = xcd_remap(blockIdx.x, gridDim.x);
-    const int r0 = (work % n_pass) * RC;
-    const int sp = SPLIT ? work / n_pass % n_split : 0;
-    const int vsp = VS > 1 ? work / n_pass % VS : 0;   // this workgroup's dwords of every piece of V
-    const int bh = work / (SPLIT ? n_pass * n_split : VS * n_pass) * HP, h = bh % n_kv_heads, b = bh / n_kv_heads;  // (first) K/V head
+    const unsigned n_pass = RC == 1 ? 1u : (unsigned)(rep + RC - 1) / RC;            // workgroups per K/V head: RC query heads each
+    const unsigned work = xcd_remap(blockIdx.x, wgs), passes = work / n_pass;
+    const int r0 = (int)(work - passes * n_pass) * RC;
+    const unsigned parts = SPLIT ? n_split : VS, own = passes / parts;
+    const int sp = SPLIT ? (int)(passes - own * parts) : 0;
+    const int vsp = VS > 1 ? (int)(passes - own * parts) : 0;         // this workgroup's dwords of every piece of V
+    const unsigned bh = own * HP;
+    const int b = (int)(bh / (unsigned)n_kv_heads), h = (int)(bh - b * (unsigned)n_kv_heads);        // (first) K/V head
+    const int new_pos = FUSED ? ((scalar_i32)(uint64_t)pos)[b] : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int piece = tid % PPT, hs = tid / PPT % HP, tl = tid / (PPT * HP);
     constexpr int TPW = 64 / (PPT * HP);    // tokens per pass of a wave
     const int wave_t0 = wave * TPW;         // first token of this wave within a pass
     const int n32 = dkv >> 3, ng = dkv >> 6;
     int L = len;
-    if (step_dev) L += min(max(*step_dev, 0), max_steps - 1) + 1;      // the row this step appends included
+    if (step_dev) L += min(max(step, 0), max_steps - 1) + 1;      // the row this step appends included
     const int stored = FUSED ? L - 1 : L;   // rows read from the cache
     const int share = SPLIT ? split_tiles((L + DEC_TILE - 1) / DEC_TILE, heads) * DEC_TILE : L;
     const int t_begin = SPLIT ? sp * share : 0, t_end = SPLIT ? min(t_begin + share, L) : L;
@@ -204,7 +212,7 @@ __global__ __launch_bounds__(HP * DEC_THREADS, RC == 1 && !SPLIT ? 4 : 2) void d
             const int hq = (h + ph) * rep + min(r0 + max(item - 2, 0), rep - 1);
             const int first = item == 0 ? d + (h + ph) * DH : item == 1 ? d + dkv + (h + ph) * DH : hq * DH;
             x.u = *reinterpret_cast<const uint4 *>(nw.qkv + (size_t)b * (d + 2 * dkv) + first + 8 * cc);
-            const int pr = min(max(nw.pos[b], 0), nw.n_pos - 1);     // never index outside the tables
+            const int pr = min(max(new_pos, 0), nw.n_pos - 1);       // never index outside the tables
             const float *cp = nw.cosT + (size_t)pr * (DH / 2) + 8 * (cc % HALF);
             const float *ssp = nw.sinT + (size_t)pr * (DH / 2) + 8 * (cc % HALF);
             *reinterpret_cast<float4 *>(cs) = *reinterpret_cast<const float4 *>(cp);
@@ -479,8 +487,8 @@ int launch_decode(const f16 *q, int Hq, const quota_kv_cache *c, int len, f16 *o
         const size_t lds = dec_red_floats(DH, hp, vs) * sizeof(float);
         if (!grant_lds<kernel>()) return QUOTA_ERR_HIP;
         kernel<<<dim3(heads * n_split * vs / hp), dim3(hp * DEC_THREADS), lds, st>>>(
-            q, d, dkv, rep, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes, (f16 *)c->v_scales,
-            c->capacity, stepped ? c->len : len, c->step_dev, c->max_steps, o, c->H, nw, n_split, heads, part);
+            c->step_dev, nw.pos, heads * n_split * vs / hp, c->H, rep, n_split, d, dkv, q, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,
+            (f16 *)c->v_scales, c->capacity, stepped ? c->len : len, c->max_steps, heads, o, nw, part);
         QUOTA_RETURN_IF_LAUNCH_FAILED();
         return QUOTA_OK;
     };

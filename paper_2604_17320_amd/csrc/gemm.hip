@@ -98,13 +98,10 @@ __device__ __forceinline__ void w4a4_tile(
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Token scale and position of row tid of the tile.  On a layer's rows, where a stage's loads go out all at once (SP = 0), they are asked
-    // for beside the first stage (packed ones, 33 x 4096 x 11008: 31.6 us, 33.7 so).  Where loads are spread they take a round trip in front: beside the
-    // stage they are no better over these tiles (36 launches of a layer's rows, within 0.5 % on average: 150 x 12288 x 4096 17.3 -> 16.7 us, 637 x 4096 x
-    // 11008 41.5 -> 41.2, but 165 x 22016 x 4096 24.0 -> 24.6, 300 x 4096 x 11008 34.5 -> 35.0, 600 x 2752 x 512 5.2 -> 5.3).
-    constexpr bool TOGETHER = !SP && !PACKED;
-    // A launch that picks its rows (PICKS: may): rows m of activations and residual are rows src of the tensors handed in.  The indices are asked for ahead of the
-    // first weights and looked up behind them.
+    // Token scale and position of row tid of the tile: a layer's are asked for beside the first stage, packed rows' in front (33 x 4096 x 11008: 31.6 us, 33.7 beside).
+    constexpr bool AT_ONCE = !SP && !PACKED;             // a stage's loads go out all at once
+    // PICKS: row m of activations and residual is row row_src[m] of the tensors handed in, which a launch may pick.  The indices are asked for ahead of the first
+    // weights and looked up behind them.
     constexpr bool PICKS = EPI == PLAIN && ACTS == A6 && !ACC_OUT;
     __shared__ int row_src[PICKS ? BM : 1];
     const quota_kept_rows &kept = more.kept;
@@ -116,7 +113,7 @@ __device__ __forceinline__ void w4a4_tile(
         pick_j = m - pick_b * kept.n_keep;
         pick = kept.index(pick_b, pick_j);
     }
-    if (!TOGETHER && !picks) {
+    if constexpr (PACKED) {
         if (tid < BM) {
             const int m = min(m0 + tid, M - 1);
             row_scale[tid] = sa[m] * F6_UNIT;
@@ -146,25 +143,6 @@ __device__ __forceinline__ void w4a4_tile(
             pa[j] = 16 * p;
             la[j] = row < BM ? row * 4 + piece_of(p, row) : BM * 6;
             lt[j] = row < BM ? BM * 8 + row * 4 + ((p >> 1 ^ (row >> 3 & 1)) << 1) + (p & 1) : BM * 12 + 2;
-        }
-    } else {
-        // A copy of first parts: lane l brings row l / 4 of 16 to piece l % 4; of second ones: row l / 2 of 32 to half l % 2
-        static_assert(THREES ? BB == 6 && NW == 4 : BB <= 2 * NW && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
-        const int last = fours - 1 - (m0 >> 2), row = lane >> 2, row2 = lane >> 1;
-        const unsigned at = (row & 3) * 64 + 16 * piece_of(lane & 3, row);
-        om = (unsigned)min(4 * (wave % BB) + (row >> 2), last) * four_bytes + at + wave / BB % NW * 384;
-        if (BB > NW) om2 = (unsigned)min(4 * (wave + NW) + (row >> 2), last) * four_bytes + at;
-        ot = (unsigned)min(8 * (wave % TB) + (row2 >> 2), last) * four_bytes + 256 + (row2 & 3) * 32 + 16 * ((lane ^ row2 >> 3) & 1) +
-             wave / TB % NW * 384;
-        dm = lds0 + wave / BB % NW * (AST * 16) + wave % BB * 1024;
-        dt = lds0 + wave / TB % NW * (AST * 16) + BM * 64 + wave % TB * 1024;
-        if constexpr (THREES) {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                om3[j] = (unsigned)min(4 * ((wave + NW * j) % BB) + (row >> 2), last) * four_bytes + at;
-                ot3[j] = (unsigned)min(8 * ((wave + NW * j) % TB) + (row2 >> 2), last) * four_bytes + 256 + (row2 & 3) * 32 +
-                         16 * ((lane ^ row2 >> 3) & 1);
-            }
         }
     }
     // SILU: columns are gate | up, F = N / 2 of each, and a tile takes BN / 2 of either: a wave's first CT / 2 blocks are gate
@@ -208,7 +186,7 @@ __device__ __forceinline__ void w4a4_tile(
     constexpr int LG = CT + LA, LC = CH * LG + MC + TC, LOADS = LC + KD;
     const uint4 *wnext = wp + (size_t)nw * 4;
     const unsigned wstep = (unsigned)N * 64u;
-    const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : picks ? qa : qa + (size_t)(m0 >> 2) * four_bytes;
+    const uint8_t *a0 = PACKED ? qa + (size_t)m0 * Kb : PICKS ? qa : qa + (size_t)(m0 >> 2) * four_bytes;
     int gstage = 0;                                       // first group of the stage being loaded
     static_assert(!LATE || (CH == 2 && SP && (LOADS - LG) * SPAN / LOADS >= T), "the first group's products cover what comes before");
     auto load = [&](int at, int set, int half) {
@@ -318,24 +296,36 @@ __device__ __forceinline__ void w4a4_tile(
     // step, multiply together and wait together (237 x 4096 x 11008 25.6 -> 23.4 us, 160 x 22016 x 4096 28.0 -> 26.0, 1280 x
     // 4096 x 11008 64.1 -> 61.2, 5808 x 22016 x 4096 400 -> 396; lowest at products, highest around the barrier: nothing).
     static_assert(CH >= 4 ? CH % 4 == 0 : RT % (4 / CH) == 0, "whole row blocks, or groups, per quarter");
-    constexpr int AHEAD_OF_PICKS = PICKS && !LATE ? CH * LG : 0;
+    // The first weights go out as soon as their address is there, ahead of the copies' addresses and of what the epilogue needs.
+    constexpr int WEIGHTS_FIRST = PACKED ? 0 : LATE ? LG : CH * LG;
 #pragma unroll
-    for (int k = 0; k < AHEAD_OF_PICKS; ++k) load(k, 0, 0);
-    if (PICKS && picks) {                    // where the copies' rows lie
-        if (tid < BM) row_src[tid] = pick_b * kept.N + kept.row(pick_j, pick);
-        __syncthreads();
-        const int row = lane >> 2, row2 = lane >> 1;
+    for (int k = 0; k < WEIGHTS_FIRST; ++k) load(k, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!PACKED) {
+        // A copy of first parts: lane l brings row l / 4 of 16 to piece l % 4; of second ones: row l / 2 of 32 to half l % 2
+        static_assert(THREES ? BB == 6 && NW == 4 : BB <= 2 * NW && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
+        const int last = fours - 1 - (m0 >> 2), row = lane >> 2, row2 = lane >> 1;
+        if constexpr (PICKS) {               // where its rows lie
+            int src = min(m0 + min(tid, BM - 1), M - 1);
+            if (picks) src = pick_b * kept.N + kept.row(pick_j, pick);
+            if (tid < BM) row_src[tid] = src;
+            __syncthreads();
+        }
         auto first = [&](int blk) {
-            const unsigned src = row_src[16 * (blk % BB) + row];
+            const int r4 = min(4 * (blk % BB) + (row >> 2), last);
+            const unsigned src = PICKS ? row_src[16 * (blk % BB) + row] : 4 * r4 + (row & 3);
             return (src >> 2) * four_bytes + (src & 3) * 64 + 16 * piece_of(lane & 3, row);
         };
         auto second = [&](int blk) {
-            const unsigned src = row_src[32 * (blk % TB) + row2];
+            const int r4 = min(8 * (blk % TB) + (row2 >> 2), last);
+            const unsigned src = PICKS ? row_src[32 * (blk % TB) + row2] : 4 * r4 + (row2 & 3);
             return (src >> 2) * four_bytes + 256 + (src & 3) * 32 + 16 * ((lane ^ row2 >> 3) & 1);
         };
         om = first(wave) + wave / BB % NW * 384;
         if (BB > NW) om2 = first(wave + NW);
         ot = second(wave) + wave / TB % NW * 384;
+        dm = lds0 + wave / BB % NW * (AST * 16) + wave % BB * 1024;
+        dt = lds0 + wave / TB % NW * (AST * 16) + BM * 64 + wave % TB * 1024;
         if constexpr (THREES) {
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
@@ -343,14 +333,12 @@ __device__ __forceinline__ void w4a4_tile(
                 ot3[j] = second(wave + NW * j);
             }
         }
-    }
-#pragma unroll
-    for (int k = AHEAD_OF_PICKS; k < LOADS; ++k) load(k, 0, 0);
-    if (TOGETHER || picks) {
-        const int m = picks ? row_src[min(tid, BM - 1)] : min(m0 + min(tid, BM - 1), M - 1);
+        const int m = PICKS ? row_src[min(tid, BM - 1)] : min(m0 + min(tid, BM - 1), M - 1);
         float scale = sa[m];
         int pos = 0;
         if constexpr (QKV) pos = qe.pos[m];
+#pragma unroll
+        for (int k = WEIGHTS_FIRST; k < LOADS; ++k) load(k, 0, 0);
         asm volatile("" : "+v"(scale), "+v"(pos));       // (asked for here, not behind the wait)
         drain();
         if (tid < BM) {
@@ -358,6 +346,8 @@ __device__ __forceinline__ void w4a4_tile(
             if constexpr (QKV) row_pos[tid] = min(max(pos, 0), qe.n_pos - 1);
         }
     } else {
+#pragma unroll
+        for (int k = 0; k < LOADS; ++k) load(k, 0, 0);
         drain();
     }
     // The first stage's weights are here before the barrier: left alone the compiler starts them behind it, and the waits for them, which it puts into
@@ -408,7 +398,7 @@ __device__ __forceinline__ void w4a4_tile(
 #pragma unroll
             for (int k = 0; k < KI; ++k) {
                 const int m = 32 * ib + RPI * k + row0;
-                rv[ib][k] = *(global_f16x8)(res_at + 2 * ((size_t)(picks ? row_src[m] : min(m0 + m, M - 1)) * ldr + n8));
+                rv[ib][k] = *(global_f16x8)(res_at + 2 * ((size_t)(PICKS ? row_src[m] : min(m0 + m, M - 1)) * ldr + n8));
             }
         }
     };
@@ -432,7 +422,7 @@ __device__ __forceinline__ void w4a4_tile(
             }
             gstage = g0 + CH;
             if (!PACKED) a0 += gstage < G ? CH * 384 : 0;
-            if (!TOGETHER || gstage < G) {
+                if (!AT_ONCE || gstage < G) {
 #pragma unroll
                 for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1);
             }
@@ -644,20 +634,19 @@ __device__ __forceinline__ void w4a4_tile(
     }
 }
 
+// (The arguments that the first loads need come first: they are in registers when a wave starts.)
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_f8_kernel(
-    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
-    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, GemmMore more)
+    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, const uint8_t *__restrict__ qa, const float *__restrict__ sa, int tiles_m, int tiles_n,
+    int M, int N, int K, int G, f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, GemmMore more)
 {
     w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, more);
 }
 // The tile of 96 rows, which only the choice takes, under a name of its own: a profile tells it by that from the tiles that can be pinned.
 template <int RT, int CT, int NW, int CH, int SP, ActFormat ACTS, bool ACC_OUT, Epilogue EPI, int OCC>
 __global__ __launch_bounds__(64 * NW, OCC) void w4a4_rows96_kernel(
-    const uint8_t *__restrict__ qa, const float *__restrict__ sa, int M, int K, int G,
-    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N, f16 *__restrict__ y, int ldy,
-    const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, GemmMore more)
+    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, const uint8_t *__restrict__ qa, const float *__restrict__ sa, int tiles_m, int tiles_n,
+    int M, int N, int K, int G, f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, int32_t *__restrict__ acc_out, GemmMore more)
 {
     w4a4_tile<RT, CT, NW, CH, SP, ACTS, ACC_OUT, EPI>(qa, sa, M, K, G, wp, sw, N, y, ldy, res, ldr, acc_out, tiles_m, tiles_n, more);
 }
@@ -700,8 +689,8 @@ const TileShape kTiles[TILES] = {{128, 128, 256, QUOTA_K_GEMM_128X128}, {64, 128
                              {128, 256, 256, QUOTA_K_GEMM_128X256}, {32, 64, 256, QUOTA_K_GEMM_32X64},
                              {64, 256, 256, QUOTA_K_GEMM_64X256}, {96, 128, 256, QUOTA_K_GEMM_96X128}};
 
-typedef void (*f8_kernel)(const uint8_t *, const float *, int, int, int, const uint4 *, const f16 *,
-                          int, f16 *, int, const f16 *, int, int32_t *, int, int, GemmMore);
+typedef void (*f8_kernel)(const uint4 *, const f16 *, const uint8_t *, const float *, int, int, int, int, int, int, f16 *, int, const f16 *, int,
+                          int32_t *, GemmMore);
 
 template <ActFormat P, Epilogue E>
 f8_kernel tile_kernel(int v)
@@ -740,9 +729,8 @@ int launch_f8(f8_kernel kernel, int v, int kernel_id, const uint8_t *qa, const f
     GemmMore more = {};
     if (qe) more.qkv = *qe;
     else if (kept) more.kept = *kept;
-    kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>(qa, sa, M, W->K, G, (const uint4 *)W->packed,
-                                                           (const f16 *)W->scales, W->N, y, ldy, res, ldr, acc, tiles_m,
-                                                           tiles_n, more);
+    kernel<<<dim3(tiles_m * tiles_n), dim3(t.nt), 0, st>>>((const uint4 *)W->packed, (const f16 *)W->scales, qa, sa, tiles_m, tiles_n,
+                                                           M, W->N, W->K, G, y, ldy, res, ldr, acc, more);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

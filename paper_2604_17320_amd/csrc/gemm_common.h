@@ -104,8 +104,8 @@ __device__ __forceinline__ void codes_e2m3(const i32x4 &v, uint32_t (&d)[6])
 // would give every workgroup its own activations: at 11264 rows that cost 2x in traffic beyond L2).
 __device__ __forceinline__ void tile_of(int tile, int tiles_m, int tiles_n, int &tm, int &tn)
 {
-    const int band = tile / (8 * tiles_n), first = 8 * band, rows = min(8, tiles_m - first);
-    const int i = tile - band * 8 * tiles_n;
-    tm = first + i % rows;
-    tn = i / rows;
+    const unsigned wide = 8u * (unsigned)tiles_n, band = (unsigned)tile / wide, first = 8 * band, rows = min(8u, (unsigned)tiles_m - first);
+    const unsigned i = (unsigned)tile - band * wide;
+    tn = (int)(i / rows);
+    tm = (int)(first + i - (unsigned)tn * rows);
 }

@@ -174,9 +174,11 @@ __device__ __forceinline__ void unsigned_e4m3(const uint4 &p, uint4 &lo, uint4 &
 // RB: 16-row blocks, 2 for fragments of 17 to 32 rows: a weight read serves both.
 template <int NB, int U, int MODE, int NC, bool GLU, int RB>
 __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
-    RowsIn in, int M, int K, int G, const uint4 *__restrict__ wp, const f16 *__restrict__ sw, int N,
-    f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, int code_stride)
+    const uint4 *__restrict__ wp, const f16 *__restrict__ sw, const void *rows, const float *beside, int M, int N, int K, int G,
+    f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, float eps, int code_stride)
 {
+    // (plain arguments, those of the first loads in front: they are in registers when a wave starts)
+    const RowsIn in = {(const uint8_t *)rows, beside, (const f16 *)rows, beside, eps};
     constexpr int R = 8 * U;                        // groups per round
     constexpr int SD = 8 * NB * R;                  // scale dwords (two columns of a group) per round
     constexpr int SPT = (SD + RT_THREADS - 1) / RT_THREADS;
@@ -376,7 +378,8 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + (GLU ? 1.0 : 2.0) * Md * Nd * (res ? 2 : 1), st);
     const int per_cu = min(PER_CU, (int)(160 * 1024 / lds));
     w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
-        in, M, W->K, G, (const uint4 *)W->packed, (const f16 *)W->scales, W->N, y, ldy, res, ldr, code_stride);
+        (const uint4 *)W->packed, (const f16 *)W->scales, MODE > ROWS_FRAG ? (const void *)in.x : in.qa, MODE > ROWS_FRAG ? in.gamma : in.sa, M, W->N, W->K, G, y,
+        ldy, res, ldr, in.eps, code_stride);
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }

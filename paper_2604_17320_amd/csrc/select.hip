@@ -485,10 +485,12 @@ struct RowsBeside {
     }
 };
 template <typename MEANS, typename PRE, typename ROWS>
-__global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(MetricSrc src, long stride_sq, int B, int Nv, quota_score_params p,
-                                                                         float *__restrict__ score, float *__restrict__ normed, int K,
-                                                                         int32_t *__restrict__ keep_idx, MEANS cues, PRE pre, ROWS rows)
+__global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(const float *sumsq, const float *ressq, const float *cm_inter,
+                                                                         const float *cm_intra, int B, int Nv, int K, int stride_sq,
+                                                                         float *__restrict__ score, int32_t *__restrict__ keep_idx, float *__restrict__ normed,
+                                                                         quota_score_params p, MEANS cues, PRE pre, ROWS rows)
 {
+    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};       // (plain arguments, the first ones in front: in registers when a wave starts)
     if ((int)blockIdx.x >= B) {
         const int beside = rows.wgs(), wg = blockIdx.x - B;
         if (wg < beside) rows(wg);
@@ -631,8 +633,12 @@ int launch_score_topk(const MetricSrc &src, long stride_sq, int B, int Nv, const
         share.run([&](auto pre) {
             auto launch = [&](auto rows, int more) {
                 const dim3 grid(B + more + share.wgs), block(SCORE_THREADS);
-                if (masses) small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, *masses, pre, rows);
-                else small_score_topk_kernel<<<grid, block, 0, st>>>(src, stride_sq, B, Nv, p, score, normed, K, keep_idx, MeansThere{}, pre, rows);
+                auto with = [&](auto means) {
+                    small_score_topk_kernel<<<grid, block, 0, st>>>(src.sumsq, src.ressq, src.cm_inter, src.cm_intra, B, Nv, K, (int)stride_sq, score, keep_idx,
+                                                                    normed, p, means, pre, rows);
+                };
+                if (masses) with(*masses);
+                else with(MeansThere{});
             };
             if (!beside) launch(NoRows{}, 0);
             else if (beside->d <= 4096) launch(RowsBeside<2>{*beside}, RowsBeside<2>{*beside}.wgs());
