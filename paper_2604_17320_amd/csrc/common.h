@@ -99,28 +99,47 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
+// The fp32 number nearest to 1 / sqrt(x).  A division by a square root in doubles is a chain of some forty instructions in front of
+// everything a row's normalisation does; the estimate y is good to 2^-23, so that e = 1 - x y^2 is as small, and three terms of
+// y (1 - e)^(-1/2) = y (1 + e / 2 + 3 e^2 / 8 + ...) leave an error of 2^-70 and the last roundings'.
+__device__ __forceinline__ float inv_sqrt(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x), e = __builtin_fma(-x * y, y, 1.0);
+    const double r = __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+    return (float)(x > 0.0 && x < INFINITY ? r : y);             // 0, infinity and NaN: e is none
+}
+
 // block-wide (blockDim.x = 64*NW) max of a float that is not negative and/or sum of a double; every thread gets the result.
-// `sm` needs 2*NW doubles of LDS.
-template <int NW, bool MAX, bool SUM>
+// `sm` needs 2*NW doubles of LDS.  FRESH: nothing read its part of them (the maxima's, the sums') in this workgroup before.
+template <int NW, bool MAX, bool SUM, bool FRESH = false>
 __device__ __forceinline__ void block_max_sum(float &mx, double &sum, double *sm)
 {
     if (MAX) mx = wave_absmax(mx);
     if (SUM) sum = wave_sum(sum);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     float *fm = reinterpret_cast<float *>(sm);
-    __syncthreads();          // protect sm against the previous use
+    if (!FRESH) __syncthreads();          // protect sm against the previous use
     if (l == 0) {
         if (MAX) fm[w] = mx;
         if (SUM) sm[NW + w] = sum;
     }
     __syncthreads();
-    if (MAX) mx = fm[0];
-    if (SUM) sum = sm[NW];
+    uint32_t m[NW];
+    double s[NW];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) {
-        if (MAX) mx = fmaxf(mx, fm[i]);
-        if (SUM) sum += sm[NW + i];
+    for (int i = 0; i < NW; ++i) {        // (in pairs, and the maximum by integers: short chains)
+        if (MAX) m[i] = __float_as_uint(fm[i]);
+        if (SUM) s[i] = sm[NW + i];
     }
+#pragma unroll
+    for (int n = NW / 2; n; n /= 2)
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+            if (MAX) m[i] = max(m[2 * i], m[2 * i + 1]);
+            if (SUM) s[i] = s[2 * i] + s[2 * i + 1];
+        }
+    if (MAX) mx = __uint_as_float(m[0]);
+    if (SUM) sum = s[0];
 }
 
 // Consecutive workgroups go round-robin over the 8 XCDs, each with its own L2: this gives each XCD a contiguous range
@@ -172,10 +191,6 @@ __device__ __forceinline__ uint32_t code_bits(float t)
 // gemm.hip); as e4m3 numbers (rows16.hip), code / 512, it counts in 2^-18.
 #define F6_UNIT 64.0f
 #define F8_UNIT 262144.0f
-__device__ __forceinline__ float code_unit(uint32_t bits)       // code / 512, exact
-{
-    return __builtin_fmaf(__uint_as_float(bits), 1.0f / 512.0f, -ROW_MAGIC / 512.0f);
-}
 // 8 such units as e4m3 bytes, evens then odds
 __device__ __forceinline__ uint2 units_to_e4m3(const float unit[8])
 {

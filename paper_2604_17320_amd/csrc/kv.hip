@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
     }
     if (oq_out.q) {
         double none = 0.0;
-        block_max_sum<4, true, false>(a, none, sm);
+        block_max_sum<4, true, false, true>(a, none, sm);
         float s;
         quantize_cached_row<false, ROW_THREADS, NCH>(v, n16, tid, a, to, store, s);
         if (tid == 0) os_out[drow] = s;

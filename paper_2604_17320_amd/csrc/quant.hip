@@ -193,14 +193,14 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
 #define ROW_WAVE_MIN_ROWS 2048
 
 constexpr int row_threads(int group) { return group == 64 ? 256 : group; }
-template <int GROUP, bool MAX, bool SUM>
+template <int GROUP, bool MAX, bool SUM, bool FRESH = false>
 __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
 {
     if (GROUP == 64) {
         if (MAX) mx = wave_absmax(mx);
         if (SUM) sum = wave_sum(sum);
     } else {
-        block_max_sum<GROUP / 64, MAX, SUM>(mx, sum, sm);
+        block_max_sum<GROUP / 64, MAX, SUM, FRESH>(mx, sum, sm);
     }
 }
 #define ROW_PROLOGUE()                                                                         \
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void quantize_act_kernel(
             }
         }
     }
-    group_reduce<GROUP, true, WANT_METRICS>(a, ss, sm);
+    group_reduce<GROUP, true, WANT_METRICS, true>(a, ss, sm);
     float s;
     if (GROUP == 64) store.make(lane, row);
     double rs = quantize_cached_row<WANT_METRICS, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
@@ -292,6 +292,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
     }
     ROW_PROLOGUE();
     const int nchunk = d >> 3;
+    const double per_channel = 1.0 / (double)d;
     const uint4 *xr = reinterpret_cast<const uint4 *>(x + (size_t)row * ldx);
     Pack16 v[NCH];
     float a_raw = 0.0f;
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
             }
         }
     }
-    group_reduce<GROUP, WANT_METRICS, true>(a_raw, ss, sm);
+    group_reduce<GROUP, WANT_METRICS, true, true>(a_raw, ss, sm);
     if (!GAINS_EARLY) {
         // the row stays packed (32 registers for 4096 columns): without this the compiler keeps the 64
         // converted floats of the first pass alive for the second one
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
         for (int r = 0; r < NCH; ++r)
             asm volatile("" : "+v"(v[r].u.x), "+v"(v[r].u.y), "+v"(v[r].u.z), "+v"(v[r].u.w));
     }
-    float rn = (float)(1.0 / sqrt(ss / (double)d + (double)eps));
+    const float rn = inv_sqrt(ss * per_channel + (double)eps);
     float s_raw = 1.0f, inv_raw = 0.0f;
     if (a_raw != 0.0f) { s_raw = a_raw / 7.0f; inv_raw = 7.0f / a_raw; }
     float a = 0.0f;
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
         // keep the compiler from hoisting every chunk's gain loads to the top (that costs 64 registers)
         if (!GAINS_EARLY) __builtin_amdgcn_sched_barrier(0);
     }
-    group_reduce<GROUP, true, WANT_METRICS>(a, rs, sm);
+    group_reduce<GROUP, true, WANT_METRICS, !WANT_METRICS>(a, rs, sm);
     float s;
     if (GROUP == 64) store.make(lane, row);
     quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, to, store, s);
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void silu_mul_quantize_act_kern
         }
     }
     double none = 0.0;
-    group_reduce<GROUP, true, false>(a, none, sm);
+    group_reduce<GROUP, true, false, true>(a, none, sm);
     float s;
     if (GROUP == 64) store.make(lane, row);
     quantize_cached_row<false, GROUP, NCH>(v, nchunk, lane, a, to, store, s);

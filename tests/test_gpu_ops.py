@@ -156,6 +156,33 @@ def test_rmsnorm_quantize_act(qb, M, d):
     assert torch.equal(qp2, qp) and torch.equal(sc2, sc)
 
 
+@pytest.mark.parametrize("d,eps", [(512, 0.0), (4096, 1e-5), (6144, 1e-30)])
+def test_rmsnorm_of_rows_without_a_finite_scale(qb, d, eps):
+    """Rows of zeros, of the smallest and the largest numbers, with an infinity and with a NaN: 1 / sqrt(mean + eps) as the definition gives
+    it, infinite, zero and NaN included."""
+    x = np.zeros((6, d), np.float16)
+    x[1] = 6e-8
+    x[2] = 65504
+    x[3] = _act(1, d, 31, 1.0)
+    x[4:] = x[3]
+    x[4, 5], x[5, d - 1] = np.inf, np.nan
+    gamma = wl.rng(31, "gamma", d).uniform(0.5, 1.5, d).astype(np.float32)
+    f = x.astype(np.float32)
+    with np.errstate(all="ignore"):
+        rn = (1.0 / np.sqrt((f.astype(np.float64) ** 2).mean(1) + np.float64(np.float32(eps)))).astype(np.float32)
+        h = (f * rn[:, None] * gamma).astype(np.float16)
+        a = np.fmax.reduce(np.abs(h.astype(np.float32)), axis=1, initial=0.0)
+        s = np.where(a == 0, np.float32(1), a / np.float32(7))
+        t = h.astype(np.float32) * np.where(a == 0, np.float32(0), np.float32(7) / a)[:, None]
+        q = np.where(np.isnan(t), -8, np.clip(np.rint(t), -8, 7)).astype(np.int8)
+    qp = torch.empty((6, d // 2), dtype=torch.uint8, device="cuda")
+    sc = torch.empty(6, dtype=torch.float32, device="cuda")
+    hh = torch.empty((6, d), dtype=torch.float16, device="cuda")
+    qb.quota_rmsnorm_quantize_act(dev(x), 6, d, d, dev(gamma), eps, qp, sc, None, None, hh)
+    assert np.array_equal(host(hh), h, equal_nan=True)
+    assert np.array_equal(host(sc), s) and np.array_equal(unpack4(host(qp)), q)
+
+
 @pytest.mark.parametrize("M,F", [(35, 1376), (9, 11008), (7, 18944), (2, 32768)])
 def test_silu_mul_quantize_act(qb, M, F):
     gu = (_act(M, 2 * F, 13, 1.5))
