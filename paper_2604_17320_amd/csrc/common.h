@@ -90,6 +90,24 @@ __device__ __forceinline__ float wave_sum(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// sum or maximum over each row of 16 lanes, in all of them
+__device__ __forceinline__ double row16_all(double v)
+{
+#define STEP(ctrl)                                                                                          \
+    v += __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true),                \
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true));
+    STEP(0xB1) STEP(0x4E) STEP(0x141) STEP(0x140)          // from lane 1 and 2 over, from the other half's mirror, the row's
+#undef STEP
+    return v;
+}
+__device__ __forceinline__ uint32_t row16_all(uint32_t v)
+{
+#define STEP(ctrl) v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xf, 0xf, true));
+    STEP(0xB1) STEP(0x4E) STEP(0x141) STEP(0x140)
+#undef STEP
+    return v;
+}
+
 // sum over each row of 16 lanes, in its last lane
 __device__ __forceinline__ float row16_sum(float v)
 {
@@ -109,37 +127,36 @@ __device__ __forceinline__ float inv_sqrt(double x)
     return (float)(x > 0.0 && x < INFINITY ? r : y);             // 0, infinity and NaN: e is none
 }
 
-// block-wide (blockDim.x = 64*NW) max of a float that is not negative and/or sum of a double; every thread gets the result.
-// `sm` needs 2*NW doubles of LDS.  FRESH: nothing read its part of them (the maxima's, the sums') in this workgroup before.
+// Sum and / or maximum (of floats that are not negative) over waves `first` to `first` + NW - 1 of a workgroup, NW a power of two up to
+// 8, in all their threads.  Every 16 lanes leave theirs in LDS; a lane reads two of the 4 NW and adds them up with its neighbours'.
+// (Every lane reading all of them takes the LDS of a CU some 400 clocks for 8 waves, this 100.)  A barrier of the
+// whole workgroup in between.  FRESH: nothing read `sums` or `maxima` (4 each per wave of the workgroup, as wanted) in this workgroup before.
+template <bool MAX, bool SUM, bool FRESH>
+__device__ __forceinline__ void waves_max_sum(float &mx, double &sum, double *sums, uint32_t *maxima, int wave, int first, int nw)
+{
+    const int lane = threadIdx.x & 63, put = 4 * wave + (lane >> 4), get = 4 * first + 2 * (lane & (2 * nw - 1));
+    const bool reads = (lane & 15) < 2 * nw;                  // (the others add nothing)
+    uint32_t m = 0;
+    if (MAX) m = row16_all(__float_as_uint(mx));
+    if (SUM) sum = row16_all(sum);
+    if (!FRESH) __syncthreads();
+    if ((lane & 15) == 0) {
+        if (MAX) maxima[put] = m;
+        if (SUM) sums[put] = sum;
+    }
+    __syncthreads();
+    uint2 m2 = make_uint2(0, 0);
+    double2 s2 = make_double2(0.0, 0.0);
+    if (MAX) m2 = *reinterpret_cast<const uint2 *>(maxima + get);
+    if (SUM) s2 = *reinterpret_cast<const double2 *>(sums + get);
+    if (MAX) mx = __uint_as_float(row16_all(reads ? max(m2.x, m2.y) : 0u));
+    if (SUM) sum = row16_all(reads ? s2.x + s2.y : 0.0);
+}
+// ... over all NW of them; `sm`, aligned to 16 bytes, needs 6 * NW doubles of LDS.
 template <int NW, bool MAX, bool SUM, bool FRESH = false>
 __device__ __forceinline__ void block_max_sum(float &mx, double &sum, double *sm)
 {
-    if (MAX) mx = wave_absmax(mx);
-    if (SUM) sum = wave_sum(sum);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    float *fm = reinterpret_cast<float *>(sm);
-    if (!FRESH) __syncthreads();          // protect sm against the previous use
-    if (l == 0) {
-        if (MAX) fm[w] = mx;
-        if (SUM) sm[NW + w] = sum;
-    }
-    __syncthreads();
-    uint32_t m[NW];
-    double s[NW];
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {        // (in pairs, and the maximum by integers: short chains)
-        if (MAX) m[i] = __float_as_uint(fm[i]);
-        if (SUM) s[i] = sm[NW + i];
-    }
-#pragma unroll
-    for (int n = NW / 2; n; n /= 2)
-#pragma unroll
-        for (int i = 0; i < n; ++i) {
-            if (MAX) m[i] = max(m[2 * i], m[2 * i + 1]);
-            if (SUM) s[i] = s[2 * i] + s[2 * i + 1];
-        }
-    if (MAX) mx = __uint_as_float(m[0]);
-    if (SUM) sum = s[0];
+    waves_max_sum<MAX, SUM, FRESH>(mx, sum, sm, reinterpret_cast<uint32_t *>(sm + 4 * NW), (int)(threadIdx.x >> 6), 0, NW);
 }
 
 // Consecutive workgroups go round-robin over the 8 XCDs, each with its own L2: this gives each XCD a contiguous range
@@ -174,6 +191,20 @@ __device__ __forceinline__ int code_from(float r)
 {
     r = fminf(fmaxf(r, -8.0f), 7.0f);
     return (int)r;
+}
+
+// s = a / 7 and inv = 7 / a of a row's absmax, an fp16 number; 1 and 0 for a = 0.  The same bits as the divisions', which take
+// some ten dependent instructions each: the quotient by the reciprocal, corrected once by its exact remainder, is the
+// nearest number for every finite fp16 a, whichever reciprocal within one unit in the last place the estimate is.
+__device__ __forceinline__ void sevenths(float a, float &s, float &inv)
+{
+    constexpr float SEVENTH = 1.0f / 7.0f;
+    const float qs = a * SEVENTH, y0 = __builtin_amdgcn_rcpf(a);
+    const float y = __builtin_fmaf(__builtin_fmaf(-a, y0, 1.0f), y0, y0), qi = 7.0f * y;
+    s = __builtin_fmaf(__builtin_fmaf(-7.0f, qs, a), SEVENTH, qs);
+    inv = __builtin_fmaf(__builtin_fmaf(-a, qi, 7.0f), y, qi);
+    if (!(a < INFINITY)) { s = a; inv = 0.0f; }
+    if (a == 0.0f) { s = 1.0f; inv = 0.0f; }
 }
 
 // The int4 code of a scaled value t = x * (7 / absmax), without a round / convert / mask chain:

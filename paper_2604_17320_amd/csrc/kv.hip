@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
     const uint4 *xs = reinterpret_cast<const uint4 *>(x + srow * d);
     const uint4 *os = reinterpret_cast<const uint4 *>(o + srow * d);
     const bool want_o = o_out || oq_out.q;
-    __shared__ double sm[8];
+    __shared__ __align__(16) double sm[24];
     uint4 xv[NCH];
     Pack16 v[NCH];
     uint32_t kw[NCH], vw[NCH];

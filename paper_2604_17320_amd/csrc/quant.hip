@@ -204,7 +204,7 @@ __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
     }
 }
 #define ROW_PROLOGUE()                                                                         \
-    __shared__ double sm[GROUP == 64 ? 8 : GROUP / 32];                                                                   \
+    __shared__ __align__(16) double sm[GROUP == 64 ? 2 : 6 * GROUP / 64];                                                  \
     const int lane = threadIdx.x % GROUP;                                                      \
     const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (row_threads(GROUP) / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
@@ -292,7 +292,6 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
     }
     ROW_PROLOGUE();
     const int nchunk = d >> 3;
-    const double per_channel = 1.0 / (double)d;
     const uint4 *xr = reinterpret_cast<const uint4 *>(x + (size_t)row * ldx);
     Pack16 v[NCH];
     float a_raw = 0.0f;
@@ -315,6 +314,11 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
     RowStore<OUT> store;
     if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
+    double per_channel = 1.0 / (double)d;
+    if (GROUP != 64) {
+        asm volatile("" : "+v"(per_channel));
+        __builtin_amdgcn_sched_barrier(0);               // (here, while the row is on its way)
+    }
 #pragma unroll
     for (int r = 0; r < NCH; ++r) {
         int c = lane + GROUP * r;

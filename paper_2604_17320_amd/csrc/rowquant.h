@@ -118,8 +118,8 @@ template <bool WANT_RES, int GROUP, int NCH, typename OUT>
 __device__ __forceinline__ double quantize_cached_row(const Pack16 *v, int nchunk, int idx, float a,
                                                       OUT out, const RowStore<OUT> &store, float &s_out)
 {
-    float s = 1.0f, inv = 0.0f;
-    if (a != 0.0f) { s = a / 7.0f; inv = 7.0f / a; }
+    float s, inv;
+    sevenths(a, s, inv);
     s_out = s;
     static_assert(!(OUT::A6 && WANT_RES), "(chunks past the row repeat one)");
     double rs = 0.0;

@@ -52,9 +52,9 @@ constexpr int RT_THREADS = 512;
 // The rows' quantizer: 8 / rows (rounded to a power of two) waves per row, a thread caches its NC chunks of 8
 // channels; the same arithmetic as the row kernels in quant.hip.  Leaves e4m3 rows of `stride` bytes and
 // the token scales in LDS.  fetch() sets off the first weights, behind the loads that the rows wait for.
-// Everything waits for it, so its chain is short: no integer division, a barrier each for the sum and the maximum, 1 / sqrt by
-// inv_sqrt, codes that the conversion rounds (a 7B decode step of one row over 32 layers 1247 -> 1214 us, of which the codes 15; four GQA
-// rows over a long context 67.7 -> 65.3).
+// Everything waits for it, so its chain is short: no integer division, a barrier each for the sum and the maximum and one trip to LDS
+// of two numbers a lane, what does not depend on the row ahead of it, 1 / sqrt by inv_sqrt, 7 / absmax by sevenths, codes that the
+// conversion rounds: a 7B decode step of one row over 32 layers 1247 -> 1150 us, four GQA rows over a long context 67.7 -> 64.4.
 template <int MODE, int NC, typename Fetch>
 __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, int G, uint8_t *codes, int stride,
                                               float *scales, double *red, Fetch fetch)
@@ -62,33 +62,8 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
     const int shift = M == 1 ? 3 : M == 2 ? 2 : 1, wpr = 1 << shift;     // waves per row
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, row = wave >> shift, part = wave & (wpr - 1);
     const int T = 64 * wpr, idx = part * 64 + lane, nchunk = K >> 3;
-    const double per_channel = MODE == ROWS_RMSNORM ? 1.0 / (double)K : 0.0;
     const bool live = row < M;
     const int r = live ? row : M - 1;
-    // The sums and the maxima of the waves, each a trip to LDS of its own: neither waits for the other's readers.
-    float *const maxima = reinterpret_cast<float *>(red + 8);
-    auto row_sum = [&](double mine) {
-        mine = wave_sum(mine);
-        if (lane == 0) red[wave] = mine;
-        __syncthreads();
-        double all[8];
-#pragma unroll
-        for (int w = 0; w < 8; ++w) all[w] = red[w];        // (all at once: one trip to LDS)
-#pragma unroll
-        for (int w = 0; w < 8; ++w) all[w] = w >> shift == row ? all[w] : 0.0;
-        return ((all[0] + all[1]) + (all[2] + all[3])) + ((all[4] + all[5]) + (all[6] + all[7]));
-    };
-    auto row_max = [&](float mine) {
-        mine = wave_absmax(mine);
-        if (lane == 0) maxima[wave] = mine;
-        __syncthreads();
-        uint32_t all[8], m = 0;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) all[w] = __float_as_uint(maxima[w]);
-#pragma unroll
-        for (int w = 0; w < 8; ++w) m = max(m, w >> shift == row ? all[w] : 0u);
-        return __uint_as_float(m);
-    };
     // The weights are asked for behind all waves' loads of the rows, which would else queue behind other waves' weights.
     auto weights = [&] {
         __builtin_amdgcn_sched_barrier(0);
@@ -114,6 +89,9 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
             ga[c][1] = gp[1];
         }
         weights();
+        double per_channel = 1.0 / (double)K, eps = (double)in.eps;
+        asm volatile("" : "+v"(per_channel), "+v"(eps));
+        __builtin_amdgcn_sched_barrier(0);                  // (here, while the rows are on their way)
 #pragma unroll
         for (int c = 0; c < NC; ++c)
             if (idx + T * c < nchunk)
@@ -122,7 +100,8 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
                     const double f = (double)(float)v[c].h[e];
                     ss = __builtin_fma(f, f, ss);
                 }
-        const float rn = inv_sqrt(row_sum(ss) * per_channel + (double)in.eps);
+        waves_max_sum<false, true, true>(a, ss, red, nullptr, wave, row << shift, wpr);
+        const float rn = inv_sqrt(ss * per_channel + eps);
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             if (!EARLY) {
@@ -143,9 +122,9 @@ __device__ __forceinline__ void quantize_rows(const RowsIn &in, int M, int K, in
     for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf((float)v[c].h[e]));
-    a = row_max(a);
-    float s = 1.0f, inv = 0.0f;
-    if (a != 0.0f) { s = a / 7.0f; inv = 7.0f / a; }
+    waves_max_sum<true, false, true>(a, ss, nullptr, reinterpret_cast<uint32_t *>(red + 32), wave, row << shift, wpr);
+    float s, inv;
+    sevenths(a, s, inv);
     const float inv_unit = inv * (1.0f / 512.0f);                // (exact)
     if (live) {
         if (idx == 0) scales[row] = s;
@@ -200,8 +179,8 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     extern __shared__ __align__(16) uint4 lds_rows[];
     float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
     float *row_scale = xbuf + 2 * BUF;                                            // [16]
-    double *red = reinterpret_cast<double *>(row_scale + 16);                     // [16]
-    uint8_t *codes = reinterpret_cast<uint8_t *>(red + 16);                       // [M][code_stride], MODE > FRAG
+    double *red = reinterpret_cast<double *>(row_scale + 16);                     // [48]: sums, maxima
+    uint8_t *codes = reinterpret_cast<uint8_t *>(red + 48);                       // [M][code_stride], MODE > FRAG
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -254,7 +233,10 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     const int nblk = C / BC;
     int blk = blockIdx.x, r0 = 0, par = 0;
     if constexpr (MODE > ROWS_FRAG)
-        quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] { fetch(blk * BC, 0); });
+        quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] {
+            fetch(blk * BC, 0);
+            asm volatile("" : "+s"(res), "+s"(ldr), "+s"(ldy), "+s"(code_stride));       // (behind the loads, not in the quantizer's chain)
+        });
     else
         fetch(blk * BC, 0);
     const i32x8 minus8 = E2M3 ? i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0} : i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
@@ -380,7 +362,7 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 {
     constexpr int R = 8 * U;
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
-    const size_t lds = 2 * (R * NB * RB * (MODE > ROWS_FRAG ? 256 : 1024) + 16 * NB * (R + 8) * 2) + 64 + 128 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
+    const size_t lds = 2 * (R * NB * RB * (MODE > ROWS_FRAG ? 256 : 1024) + 16 * NB * (R + 8) * 2) + 64 + 384 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
     if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB>>()) return QUOTA_ERR_HIP;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,

@@ -183,6 +183,24 @@ def test_rmsnorm_of_rows_without_a_finite_scale(qb, d, eps):
     assert np.array_equal(host(sc), s) and np.array_equal(unpack4(host(qp)), q)
 
 
+def test_quantize_act_of_every_absmax(qb):
+    """Rows whose largest magnitude is each fp16 number once, infinity included: scales and codes are those of the two divisions, bit by bit."""
+    M, d = 0x7c01, 64
+    a = np.arange(M, dtype=np.uint16).view(np.float16).astype(np.float32)
+    x = (a[:, None] * wl.rng(37, "every absmax").uniform(-1, 1, (M, d)).astype(np.float32)).astype(np.float16)
+    x[:, 7] = a
+    x[M - 1, 8:] = 1
+    with np.errstate(all="ignore"):
+        s = np.where(a == 0, np.float32(1), a / np.float32(7))
+        inv = np.where(a == 0, np.float32(0), np.float32(7) / a)
+        t = x.astype(np.float32) * inv[:, None]
+        q = np.where(np.isnan(t), -8, np.clip(np.rint(t), -8, 7)).astype(np.int8)
+    qp = torch.empty((M, d // 2), dtype=torch.uint8, device="cuda")
+    sc = torch.empty(M, dtype=torch.float32, device="cuda")
+    qb.quota_quantize_act(dev(x), M, d, d, qp, sc)
+    assert np.array_equal(host(sc), s) and np.array_equal(unpack4(host(qp)), q)
+
+
 @pytest.mark.parametrize("M,F", [(35, 1376), (9, 11008), (7, 18944), (2, 32768)])
 def test_silu_mul_quantize_act(qb, M, F):
     gu = (_act(M, 2 * F, 13, 1.5))
