@@ -231,14 +231,41 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     };
     constexpr int BC = GLU ? 16 : 16 * NB;          // output columns per workgroup
     const int nblk = C / BC;
-    int blk = blockIdx.x, r0 = 0, par = 0;
+    int blk = blockIdx.x, r0 = 0, par = 0, grid = gridDim.x;
+    // What the outputs take besides the sums is asked for with their first weights, not at the end of their chain.  Every thread
+    // asks for something, so that the loads in flight can be counted: without residuals for the scales.
+    f16 rsd[OPT];
+    float sa_out = 0.0f;
+    const int om_in = min(om, M - 1);
+    auto residuals = [&](int b) {
+        if constexpr (!GLU) {
+            const f16 *rp = res ? res + (size_t)om_in * ldr : sw;
+#pragma unroll
+            for (int o = 0; o < OPT; ++o) rsd[o] = rp[b * BC + 16 * min(o + oj, NB - 1) + (ol & 15)];
+        }
+    };
+    // where this thread leaves a round's scales and finds those and the sums of its outputs
+    int scale_at[SPT], codes_at = arow_at * code_stride + 32 * q;
+    int chain_scales = (16 * oj + (ol & 15)) * SROW, chain_sums = (oj * RB + oi) * XS + oreg * (XS / 4) + ol;
+#pragma unroll
+    for (int k = 0; k < SPT; ++k) {
+        const int d = tid + RT_THREADS * k;
+        scale_at[k] = 2 * (d % (8 * NB)) * SROW + d / (8 * NB);
+    }
     if constexpr (MODE > ROWS_FRAG)
         quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] {
             fetch(blk * BC, 0);
-            asm volatile("" : "+s"(res), "+s"(ldr), "+s"(ldy), "+s"(code_stride));       // (behind the loads, not in the quantizer's chain)
+            residuals(blk);
+            // (these come here, behind the loads, not between the quantizer and the first product)
+            asm volatile("" : "+s"(ldy), "+s"(grid), "+v"(codes_at), "+v"(chain_scales), "+v"(chain_sums));
+#pragma unroll
+            for (int k = 0; k < SPT; ++k) asm volatile("" : "+v"(scale_at[k]));
         });
-    else
+    else {
         fetch(blk * BC, 0);
+        residuals(blk);
+        sa_out = in.sa[om_in];
+    }
     const i32x8 minus8 = E2M3 ? i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0} : i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
     while (true) {                                  // rounds of this workgroup's column blocks
@@ -261,7 +288,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                     unsigned_e4m3(ra[u][i], a0, a1);
                 } else {
                     const int g = min(r0 + 8 * u + wave, G - 1);
-                    const uint4 *ag = reinterpret_cast<const uint4 *>(codes + (size_t)min(c16, M - 1) * code_stride + g * 128 + 32 * q);
+                    const uint4 *ag = reinterpret_cast<const uint4 *>(codes + codes_at + g * 128);
                     a0 = ag[0];
                     a1 = ag[1];
                 }
@@ -292,13 +319,12 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             if (SD % RT_THREADS == 0 || d < SD) {
                 union { uint32_t w; f16 h[2]; } t;
                 t.w = rsv[k];
-                const int col = 2 * (d % (8 * NB)), gi = d / (8 * NB);
-                scs[col * SROW + gi] = t.h[0];
-                scs[(col + 1) * SROW + gi] = t.h[1];
+                scs[scale_at[k]] = t.h[0];
+                scs[scale_at[k] + SROW] = t.h[1];
             }
         }
         const bool last = r0 + R >= G;
-        const int nblk_next = last ? blk + (int)gridDim.x : blk, r_next = last ? 0 : r0 + R;
+        const int nblk_next = last ? blk + grid : blk, r_next = last ? 0 : r0 + R;
         if (nblk_next < nblk) fetch(nblk_next * BC, r_next);       // the next loads fly during the exchange
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -313,9 +339,8 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
         if (owner) {
 #pragma unroll
             for (int o = 0; o < OPT; ++o) {
-                const int j = o + oj;
-                const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + (16 * j + (ol & 15)) * SROW);
-                const float *ap = accs + (j * RB + oi) * XS + oreg * (XS / 4) + ol;
+                const Pack16 *sp = reinterpret_cast<const Pack16 *>(scs + chain_scales + 16 * o * SROW);
+                const float *ap = accs + chain_sums + o * RB * XS;
 #pragma unroll
                 for (int i8 = 0; i8 < U; ++i8) {
                     if (!FEW && r0 + 8 * i8 >= G) break;
@@ -331,12 +356,12 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             }
             if (last) {
                 if (om < M) {
-                    const float sa = MODE <= ROWS_FRAG ? in.sa[om] : row_scale[om];
+                    const float sa = MODE <= ROWS_FRAG ? sa_out : row_scale[om];
 #pragma unroll
                     for (int o = 0; o < (GLU ? 1 : OPT); ++o) {
                         const int on = blk * BC + 16 * (o + oj) + (ol & 15);
                         float v = y32[o] * (sa * UNIT);
-                        if (res) v = v + (float)res[(size_t)om * ldr + on];
+                        if (!GLU && res) v = v + (float)rsd[o];
                         f16 out = to_f16(v);
                         if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * UNIT)));
                         y[(size_t)om * ldy + on] = out;
@@ -347,6 +372,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
             }
         }
         if (nblk_next >= nblk) break;
+        if (last) residuals(nblk_next);
         blk = nblk_next;
         r0 = r_next;
         par ^= 1;
