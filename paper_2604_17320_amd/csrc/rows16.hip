@@ -410,12 +410,21 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
 // 12.4 -> 10.9, 1 x 8448 x 8192 13.2 -> 11.6; with three rows whose quantizer one workgroup per CU does alone a layer takes 1 %
 // longer; six chunks of a row per thread leave no registers for it: 2 x 12288 x 8192 18.0 us, 17.0 to 17.7 with 32 columns).
 // Workgroups walk over the columns.
+// Short rows end in their first round, half of which is empty with two groups per wave: one per wave for up to 8 groups, us: 1 x 1536 x 512
+// 3.10 -> 2.96, 1 x 6144 x 768 3.63 -> 3.19, 4 x 1024 x 1024 2.79 -> 2.59, fragments 16 x 1536 x 512 2.44 -> 2.24 (1 x 12288 x 1024,
+// more columns than the chip takes at once, 4.00 and 4.08).  Gate/up up to 16 groups and a column block for each of 512 workgroups: 1 x 2752 x 512
+// 3.47 -> 3.08, 1 x 11008 x 2048 5.54 -> 4.96, 16 x 8192 x 2048 4.20 -> 3.82 (4 x 22016 x 2048 8.93 and 10.11).
 // Packed, 16 rows, us at 4096 x 11008 / 5120 x 13824 / 22016 x 4096: <1, 2> 9.6 / 16.0 / 16.5, <1, 4> 9.3 / 17.5 / 17.3,
 // <2, 2> 11.6 / 13.7 / 13.2, <2, 1> 12.4 / 15.4 / 12.9.
 template <int MODE, int NC, int RB = 1>
 int rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int ldy, const f16 *res, int ldr, int code_stride,
            hipStream_t st)
 {
+    if constexpr (NC == 1)
+        if (W->K <= 1024 && W->N <= 8192) {
+            if (W->N <= 4096) return launch_rows16<1, 1, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
+            return launch_rows16<2, 1, 2, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
+        }
     if (W->N <= 4096) {
         if constexpr (MODE != ROWS_RMSNORM && !(MODE == ROWS_QUANT && NC == 1))      // (one chunk: 4096 channels at most)
             if (W->K > 8192) return launch_rows16<1, 4, 1, MODE, NC, false, RB>(in, M, W, y, ldy, res, ldr, code_stride, st);
@@ -435,6 +444,8 @@ int rows16_glu(const RowsIn &in, int M, const quota_weights *W, f16 *z, int code
     const int F = W->N / 2;
     if constexpr (MODE <= ROWS_FRAG)
         if (W->N > 8192) return launch_rows16<2, 1, 3, MODE, NC, true, RB>(in, M, W, z, F, nullptr, 0, code_stride, st);
+    if constexpr (NC <= 3)
+        if (W->K <= 2048 && W->N <= 16384) return launch_rows16<2, 1, 2, MODE, NC, true, RB>(in, M, W, z, F, nullptr, 0, code_stride, st);
     return launch_rows16<2, 2, 2, MODE, NC, true, RB>(in, M, W, z, F, nullptr, 0, code_stride, st);
 }
 

@@ -139,6 +139,14 @@ def test_decode_layer_small_batch_prefix(qb):
     check_decode(qb, shape, 1, 7, steps=2)
 
 
+@pytest.mark.parametrize("B,d,H,F", [(1, 1024, 16, 992), (4, 1088, 17, 1024), (17, 1024, 16, 1056), (2, 2048, 16, 1408)])
+def test_decode_layer_of_short_rows(qb, B, d, H, F):
+    """Projections of 1024 channels and of a few more, gate/up of 2048: on both sides of where a wave takes one group a round."""
+    base = wl.CONFIGS[0]
+    shape = wl.Shape("dec_short", d=d, H=H, F=F, layers=1, B=B, Nv=base.Nv, Nt=5, n_outlier=base.n_outlier, vis_begin=1)
+    check_decode(qb, shape, 3, 9, steps=1)
+
+
 def test_decode_layer_7b_shape(qb):
     """7B-shaped layer, batch 4, cache pruned to 30 % of 576 visual tokens plus 64 text tokens."""
     base = wl.CONFIGS[1]

@@ -266,6 +266,12 @@ def test_w4a4_gemm_bit_exact(qb, M, N, K):
     assert np.array_equal(host(y3).view(np.uint16), yr_ref.view(np.uint16))
 
 
+@pytest.mark.parametrize("M,N,K", [(16, 4096, 1024), (9, 4160, 1024), (3, 8192, 992), (5, 8256, 1024), (12, 8192, 1056), (16, 64, 1024)])
+def test_w4a4_gemm_of_few_short_rows(qb, M, N, K):
+    """At most 16 rows of at most 1024 channels and 8192 columns, and just past each."""
+    test_w4a4_gemm_bit_exact(qb, M, N, K)
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
 def test_w4a4_gemm_every_tile_bit_exact(qb, tile, pinned_gemm):
     """Each of the five tile instantiations, pinned with quota_set_gemm_variant, on shapes with ragged
