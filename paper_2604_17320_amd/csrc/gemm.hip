@@ -340,6 +340,8 @@ __device__ __forceinline__ void w4a4_tile(
 #pragma unroll
         for (int k = WEIGHTS_FIRST; k < LOADS; ++k) load(k, 0, 0);
         asm volatile("" : "+v"(scale), "+v"(pos));       // (asked for here, not behind the wait)
+        // (the first touch of the epilogue's arguments comes from far away: here, not behind the main loop)
+        if constexpr (QKV) asm volatile("" ::"s"(qe.v_scales));
         drain();
         if (tid < BM) {
             row_scale[tid] = scale * F6_UNIT;

@@ -203,10 +203,24 @@ __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
         block_max_sum<GROUP / 64, MAX, SUM, FRESH>(mx, sum, sm);
     }
 }
+// A launch's arguments that are not in registers when a wave starts (structures and what is behind them) come from memory, the first touch of
+// each 64 bytes from far away.  Left alone the compiler asks for them where they are used, in the middle of a row's chain: they are wanted
+// here, where the row's loads are on their way.
+template <typename ARG>
+__device__ __forceinline__ void argument_now(ARG &a) { asm volatile("" : "+s"(a)); }
+template <int GROUP, typename OUT, typename... ARGS>
+__device__ __forceinline__ void row_arguments_now(OUT &q, ARGS &...args)
+{
+    if constexpr (GROUP != 64) {                         // (long launches take what registers there are)
+        argument_now(q.q);
+        if constexpr (OUT::STARTS) argument_now(q.rows);
+        (argument_now(args), ...);
+    }
+}
 #define ROW_PROLOGUE()                                                                         \
     __shared__ __align__(16) double sm[GROUP == 64 ? 2 : 6 * GROUP / 64];                                                  \
     const int lane = threadIdx.x % GROUP;                                                      \
-    const int row = row_wg<OUT>(blockIdx.x, gridDim.x) * (row_threads(GROUP) / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
+    const int row = row_wg<OUT>(blockIdx.x, (M + row_threads(GROUP) / GROUP - 1) / (row_threads(GROUP) / GROUP)) * (row_threads(GROUP) / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
     if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
     (void)sm
 
@@ -226,6 +240,8 @@ __global__ __launch_bounds__(row_threads(GROUP)) void quantize_act_kernel(
     double ss = 0.0;
 #pragma unroll
     for (int r = 0; r < NCH; ++r) v[r].u = xr[min(lane + GROUP * r, nchunk - 1)];
+    row_arguments_now<GROUP>(q, scale);
+    if constexpr (WANT_METRICS) row_arguments_now<GROUP>(q, sumsq, ressq);
     RowStore<OUT> store;
     if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
@@ -311,6 +327,8 @@ __global__ __launch_bounds__(row_threads(GROUP)) void rmsnorm_quantize_act_kerne
             ga[r][1] = gp[1];
         }
     }
+    row_arguments_now<GROUP>(q, scale, h_out);
+    if constexpr (WANT_METRICS) row_arguments_now<GROUP>(q, sumsq, ressq);
     RowStore<OUT> store;
     if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
@@ -409,6 +427,7 @@ __global__ __launch_bounds__(row_threads(GROUP)) void silu_mul_quantize_act_kern
             uu[r].u = ur[c];
         }
     }
+    row_arguments_now<GROUP>(q, scale, z_out);
     RowStore<OUT> store;
     if (GROUP != 64) store.make(lane, row);
     const OUT to = row_out(q, row, nchunk);
