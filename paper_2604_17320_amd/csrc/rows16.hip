@@ -160,7 +160,8 @@ __device__ __forceinline__ void unsigned_e4m3(const uint4 &p, uint4 &lo, uint4 &
 // GLU: the columns are gate | up, NB = 2 and a workgroup has 16 of each, of the same channels: it stores SiLU(gate) * up of
 // their fp16 roundings, y is [M][N / 2].
 // RB: 16-row blocks, 2 for fragments of 17 to 32 rows: a weight read serves both.
-template <int NB, int U, int MODE, int NC, bool GLU, int RB>
+// RES: residuals are added.
+template <int NB, int U, int MODE, int NC, bool GLU, int RB, bool RES>
 __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     const uint4 *__restrict__ wp, const f16 *__restrict__ sw, const void *rows, const float *beside, int M, int N, int K, int G,
     f16 *__restrict__ y, int ldy, const f16 *__restrict__ res, int ldr, float eps, int code_stride)
@@ -175,6 +176,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     constexpr int XS = FEW ? 64 : 256;              // sums of a group and block
     constexpr int OPT = GLU || RB == 2 ? NB : 1;    // outputs per owner thread
     constexpr int BUF = R * NB * RB * XS + 8 * NB * SROW;   // floats of one exchange buffer
+    static_assert(!(RES && (GLU || MODE == ROWS_RMSNORM)), "(never together)");
     static_assert((NB <= 2 || (FEW && !GLU)) && (!GLU || NB == 2) && (RB == 1 || (RB == 2 && MODE == ROWS_FRAG)), "an owner per output");
     extern __shared__ __align__(16) uint4 lds_rows[];
     float *xbuf = reinterpret_cast<float *>(lds_rows);      // 2 x { sums [R][NB][4][64]; scales f16 [16 NB][SROW] }
@@ -233,30 +235,41 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
     const int nblk = C / BC;
     int blk = blockIdx.x, r0 = 0, par = 0, grid = gridDim.x;
     // What the outputs take besides the sums is asked for with their first weights, not at the end of their chain.  Every thread
-    // asks for something, so that the loads in flight can be counted: without residuals for the scales.
-    f16 rsd[OPT];
+    // asks for the same, so that the loads in flight can be counted; a launch without residuals is an instantiation without these
+    // loads (weight scales in their place, for the count: fragments 16 x 12288 x 4096 7.0 us, 7.6 so, four rows with their RMSNorm 10.7, 11.0).
+    f16 rsd[RES ? OPT : 1];
     float sa_out = 0.0f;
     const int om_in = min(om, M - 1);
     auto residuals = [&](int b) {
-        if constexpr (!GLU) {
-            const f16 *rp = res ? res + (size_t)om_in * ldr : sw;
+        if constexpr (RES) {
+            const f16 *rp = res + (size_t)om_in * ldr;
 #pragma unroll
             for (int o = 0; o < OPT; ++o) rsd[o] = rp[b * BC + 16 * min(o + oj, NB - 1) + (ol & 15)];
         }
     };
     // where this thread leaves a round's scales and finds those and the sums of its outputs
-    int scale_at[SPT], codes_at = arow_at * code_stride + 32 * q;
-    int chain_scales = (16 * oj + (ol & 15)) * SROW, chain_sums = (oj * RB + oi) * XS + oreg * (XS / 4) + ol;
+    int scale_at[SPT], codes_at, chain_scales, chain_sums;
+    auto places = [&] {
+        codes_at = arow_at * code_stride + 32 * q;
+        chain_scales = (16 * oj + (ol & 15)) * SROW;
+        chain_sums = (oj * RB + oi) * XS + oreg * (XS / 4) + ol;
 #pragma unroll
-    for (int k = 0; k < SPT; ++k) {
-        const int d = tid + RT_THREADS * k;
-        scale_at[k] = 2 * (d % (8 * NB)) * SROW + d / (8 * NB);
-    }
+        for (int k = 0; k < SPT; ++k) {
+            const int d = tid + RT_THREADS * k;
+            scale_at[k] = 2 * (d % (8 * NB)) * SROW + d / (8 * NB);
+        }
+    };
+    if constexpr (GLU) places();
     if constexpr (MODE > ROWS_FRAG)
         quantize_rows<MODE, NC>(in, M, K, G, codes, code_stride, row_scale, red, [&] {
             fetch(blk * BC, 0);
             residuals(blk);
-            // (these come here, behind the loads, not between the quantizer and the first product)
+            // (these come here, behind the loads, not in front of the weights or between the quantizer and the first product: a 7B decode
+            // step of one row over 32 layers 1153 -> 1136 us; gate/up, whose share is longer, takes 1 % less with its own in front)
+            if constexpr (!GLU) {
+                __builtin_amdgcn_sched_barrier(0);
+                places();
+            }
             asm volatile("" : "+s"(ldy), "+s"(grid), "+v"(codes_at), "+v"(chain_scales), "+v"(chain_sums));
 #pragma unroll
             for (int k = 0; k < SPT; ++k) asm volatile("" : "+v"(scale_at[k]));
@@ -265,6 +278,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
         fetch(blk * BC, 0);
         residuals(blk);
         sa_out = in.sa[om_in];
+        if constexpr (!GLU) places();
     }
     const i32x8 minus8 = E2M3 ? i32x8{(int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, (int)0x28A28A28, (int)0x8A28A28A, (int)0xA28A28A2, 0, 0} : i32x8{(int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888,
                                (int)0x88888888, (int)0x88888888, (int)0x88888888, (int)0x88888888};
@@ -361,7 +375,7 @@ __global__ __launch_bounds__(RT_THREADS, 4) void w4a4_rows16_kernel(
                     for (int o = 0; o < (GLU ? 1 : OPT); ++o) {
                         const int on = blk * BC + 16 * (o + oj) + (ol & 15);
                         float v = y32[o] * (sa * UNIT);
-                        if (!GLU && res) v = v + (float)rsd[o];
+                        if constexpr (RES) v = v + (float)rsd[o];
                         f16 out = to_f16(v);
                         if (GLU) out = silu_mul((float)out, (float)to_f16(y32[OPT - 1] * (sa * UNIT)));
                         y[(size_t)om * ldy + on] = out;
@@ -389,14 +403,23 @@ int launch_rows16(const RowsIn &in, int M, const quota_weights *W, f16 *y, int l
     constexpr int R = 8 * U;
     const int G = (W->K + QUOTA_GROUP_W - 1) / QUOTA_GROUP_W;
     const size_t lds = 2 * (R * NB * RB * (MODE > ROWS_FRAG ? 256 : 1024) + 16 * NB * (R + 8) * 2) + 64 + 384 + (MODE > ROWS_FRAG ? (size_t)M * code_stride : 0);
-    if (!grant_lds<w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB>>()) return QUOTA_ERR_HIP;
     const double Md = M, Nd = W->N, Kd = W->K;
     ProfScope prof(QUOTA_K_GEMM_ROWS16, 2.0 * Md * Nd * Kd,
                    Nd * Kd / 2 + 2.0 * Nd * G + Md * Kd / 2 + 4 * Md + (GLU ? 1.0 : 2.0) * Md * Nd * (res ? 2 : 1), st);
     const int per_cu = min(PER_CU, (int)(160 * 1024 / lds));
-    w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB><<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
-        (const uint4 *)W->packed, (const f16 *)W->scales, MODE > ROWS_FRAG ? (const void *)in.x : in.qa, MODE > ROWS_FRAG ? in.gamma : in.sa, M, W->N, W->K, G, y,
-        ldy, res, ldr, in.eps, code_stride);
+    auto run = [&](auto with_res) {
+        constexpr auto kernel = w4a4_rows16_kernel<NB, U, MODE, NC, GLU, RB, decltype(with_res)::value>;
+        if (!grant_lds<kernel>()) return false;
+        kernel<<<dim3(min(W->N / (16 * NB), 256 * per_cu)), dim3(RT_THREADS), lds, st>>>(
+            (const uint4 *)W->packed, (const f16 *)W->scales, MODE > ROWS_FRAG ? (const void *)in.x : in.qa, MODE > ROWS_FRAG ? in.gamma : in.sa, M, W->N, W->K, G, y,
+            ldy, res, ldr, in.eps, code_stride);
+        return true;
+    };
+    bool granted;
+    if constexpr (GLU || MODE == ROWS_RMSNORM) granted = run(std::false_type());
+    else if constexpr (MODE == ROWS_QUANT) granted = run(std::true_type());
+    else granted = res ? run(std::true_type()) : run(std::false_type());
+    if (!granted) return QUOTA_ERR_HIP;
     QUOTA_RETURN_IF_LAUNCH_FAILED();
     return QUOTA_OK;
 }
@@ -495,6 +518,7 @@ int quota_internal_rows16_frag_silu(const uint8_t *qf, const float *sa, int M, c
 int quota_internal_rows16_quantize(const void *x, int M, const quota_weights *W, void *y, int ldy, const void *res,
                                    int ldr, hipStream_t st)
 {
+    if (!res) return QUOTA_ERR_NULL;                      // (the projections that add one)
     RowsIn in = {};
     in.x = (const f16 *)x;
     return rows16_quantizing(M, W->K, [&](auto nc, int stride) {

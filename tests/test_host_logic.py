@@ -143,6 +143,22 @@ def test_gemm_tiles_leave_room_for_the_workgroups_that_their_choice_counts_on():
     assert seen == {(b, False) for b in room} | {(b, True) for b in packed}
 
 
+def test_few_row_gemm_loads_residuals_only_where_they_are_added():
+    """Whether there are residuals is an argument of the kernel's template: packed rows, A6 rows and fragments come both ways,
+    rows quantized in the launch only with them, normalised ones and gate/up only without."""
+    from paper_2604_17320_amd import binding
+    by_mode = {}
+    for name in kernel_resources(binding.LIB_PATH):
+        m = re.search(r"w4a4_rows16_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELb(\d)ELi(\d)ELb(\d)E", name)
+        assert m or "w4a4_rows16" not in name, name
+        if m:
+            nb, u, mode, nc, glu, rb, res = map(int, m.groups())
+            by_mode.setdefault((mode, glu, nb, u, nc, rb), set()).add(res)
+    assert {k[:2] for k in by_mode} == {(0, 0), (1, 0), (2, 0), (2, 1), (3, 0), (4, 0), (4, 1)}       # A6, packed, fragments, quantizing, RMSNorm
+    for (mode, glu, *_), res in by_mode.items():
+        assert res == ({0} if glu or mode == 4 else {1} if mode == 3 else {0, 1}), (mode, glu, res)
+
+
 def test_profile_summary_stats_table(tmp_path, capsys):
     rows = [dict(Name="_Z19quantize_act_kernelILb0ELi64ELi8EEv", Calls=4, TotalDurationNs=100000),
             dict(Name="_ZN12_GLOBAL__N_115attn_fwd_kernelILi128EEEv", Calls=2, TotalDurationNs=30000),
