@@ -59,8 +59,8 @@ namespace {
 // and 8 of the second; 16-byte piece q of row r's first part sits at q ^ {0, 2, 3, 1}[r / 4 % 4], and the halves of the second
 // are swapped in rows 8 to 15 of 16, so that the lanes of a read do not share banks.
 enum ActFormat { A6, A6_STARTS, PACKED_INT4 };
-enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL };
-// What some launches take besides, by their epilogue (QKV_ROPE_KV; PLAIN: rows to pick, if keep_idx is given).  One place for both: every argument costs the
+enum Epilogue { PLAIN, QKV_ROPE_KV, SILU_MUL, PLAIN_PICKED };     // PICKED: of rows picked through indices
+// What some launches take besides, by their epilogue (QKV_ROPE_KV, PLAIN_PICKED).  One place for both: every argument costs the
 // host time.
 union GemmMore {
     quota_qkv_epilogue qkv;
@@ -100,14 +100,16 @@ __device__ __forceinline__ void w4a4_tile(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Token scale and position of row tid of the tile: a layer's are asked for beside the first stage, packed rows' in front (33 x 4096 x 11008: 31.6 us, 33.7 beside).
     constexpr bool AT_ONCE = !SP && !PACKED;             // a stage's loads go out all at once
-    // PICKS: row m of activations and residual is row row_src[m] of the tensors handed in, which a launch may pick.  The indices are asked for ahead of the first
-    // weights and looked up behind them.
-    constexpr bool PICKS = EPI == PLAIN && ACTS == A6 && !ACC_OUT;
+    // PICKS: row m of activations and residual is row row_src[m] of the tensors handed in.  The indices are asked for ahead of the first
+    // weights and looked up behind them.  (An instantiation of its own: with the table of rows in all
+    // PLAIN launches those that pick none took a barrier and a trip to LDS before their first activations: 122 x 4096 x 4096 7.39 us, 7.25 so, 256 x 4096 x 11008
+    // 23.4, 23.0, 64 x 5120 x 5120 10.8, 10.4.)
+    constexpr bool PICKS = EPI == PLAIN_PICKED, ADDS = EPI == PLAIN || PICKS;
+    static_assert(!PICKS || (ACTS == A6 && !ACC_OUT), "(the layer's output projection)");
     __shared__ int row_src[PICKS ? BM : 1];
     const quota_kept_rows &kept = more.kept;
-    const bool picks = PICKS && kept.keep_idx;
     int pick_j = 0, pick_b = 0, pick = 0;
-    if (PICKS && picks) {
+    if constexpr (PICKS) {
         const int m = min(m0 + min(tid, BM - 1), M - 1);
         pick_b = m / kept.n_keep;
         pick_j = m - pick_b * kept.n_keep;
@@ -306,9 +308,7 @@ __device__ __forceinline__ void w4a4_tile(
         static_assert(THREES ? BB == 6 && NW == 4 : BB <= 2 * NW && (TB % NW == 0 || NW % TB == 0), "blocks of rows by wave");
         const int last = fours - 1 - (m0 >> 2), row = lane >> 2, row2 = lane >> 1;
         if constexpr (PICKS) {               // where its rows lie
-            int src = min(m0 + min(tid, BM - 1), M - 1);
-            if (picks) src = pick_b * kept.N + kept.row(pick_j, pick);
-            if (tid < BM) row_src[tid] = src;
+            if (tid < BM) row_src[tid] = pick_b * kept.N + kept.row(pick_j, pick);
             __syncthreads();
         }
         auto first = [&](int blk) {
@@ -374,7 +374,7 @@ __device__ __forceinline__ void w4a4_tile(
     constexpr int RPI = NT / (BN / 8), KI = 32 / RPI, ROUNDS = RT / 2, AR = !QKV ? 1 : KI <= 2 && ROUNDS > 1 ? 2 : 1;
     const int row0 = tid / (BN / 8), c8 = tid % (BN / 8), n8 = n0 + 8 * c8;
     float cs[AR][QKV ? KI : 1][8], sn[AR][QKV ? KI : 1][8];
-    f16x8 rv[EPI == PLAIN ? ROUNDS : 1][EPI == PLAIN ? KI : 1];
+    f16x8 rv[ADDS ? ROUNDS : 1][ADDS ? KI : 1];
     // (The address passes the assembly as a number and is one of global memory again behind it: loads of an address of unknown memory count as LDS
     // reads too, and in the 32-row tiles, which ask ahead of the main loop, every wait for LDS in the first stage of its body was a wait for all of
     // them: 237 x 4096 x 4096 9.4 -> 9.2 us, 80 x 1024 x 1024 4.0 -> 3.8.)
@@ -404,7 +404,7 @@ __device__ __forceinline__ void w4a4_tile(
             }
         }
     };
-    constexpr bool AHEAD = EPI == PLAIN && ROUNDS == 1 && !PACKED;
+    constexpr bool AHEAD = ADDS && ROUNDS == 1 && !PACKED;
     if constexpr (AHEAD) ask_residual(0);
 
     i32x8 fb[CT];
@@ -424,7 +424,7 @@ __device__ __forceinline__ void w4a4_tile(
             }
             gstage = g0 + CH;
             if (!PACKED) a0 += gstage < G ? CH * 384 : 0;
-                if (!AT_ONCE || gstage < G) {
+            if (!AT_ONCE || gstage < G) {
 #pragma unroll
                 for (int k = 0; k < (SP ? 0 : LOADS); ++k) load(k, (set + 1) % WS, half ^ 1);
             }
@@ -594,7 +594,7 @@ __device__ __forceinline__ void w4a4_tile(
     // 636 x 4096 x 4096 19.9 -> 19.3, 1356 x 12288 x 4096 68.3 -> 65.9)
     float *stage = reinterpret_cast<float *>(lds_raw);
     const int n = n8;
-    if constexpr (EPI == PLAIN && !AHEAD) {
+    if constexpr (ADDS && !AHEAD) {
 #pragma unroll
         for (int ib = 0; ib < ROUNDS; ++ib) ask_residual(ib);
     }
@@ -847,7 +847,7 @@ int quota_internal_w4a4_gemm_a6_kept(const uint8_t *qa6, const float *sa, int M,
     if (!qa6 || !sa || !kept || !kept->keep_idx || !W || !W->packed || !W->scales || !y_f16 || !residual) return QUOTA_ERR_NULL;
     if (!quota_gemm_gathers(M, W) || kept->k_keep <= 0 || kept->n_keep <= 0) return QUOTA_ERR_SHAPE;
     const int v = choose_tile(A6, M, W->N, W->K, 0, 256);
-    return launch_f8(tile_kernel<A6, PLAIN>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_f16, ldy, (const f16 *)residual, ldr, nullptr, st, nullptr, kept);
+    return launch_f8(tile_kernel<A6, PLAIN_PICKED>(v), v, kTiles[v].kernel_id, qa6, sa, M, W, (f16 *)y_f16, ldy, (const f16 *)residual, ldr, nullptr, st, nullptr, kept);
 }
 
 // Gate/up projection with SiLU(gate) * up in the epilogue: z [M][N / 2], the bits of the plain projection and the

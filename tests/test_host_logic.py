@@ -143,6 +143,20 @@ def test_gemm_tiles_leave_room_for_the_workgroups_that_their_choice_counts_on():
     assert seen == {(b, False) for b in room} | {(b, True) for b in packed}
 
 
+def test_gemm_keeps_a_table_of_rows_only_where_it_picks_them():
+    """The tiles that pick rows have LDS for their rows' numbers, the others of a layer's rows none."""
+    from paper_2604_17320_amd import binding
+    lds = {}
+    for name, k in kernel_resources(binding.LIB_PATH).items():
+        m = re.search(r"w4a4_\w+_kernelI(Li(\d+)E(?:Li\d+E)*).*?ActFormatE0ELb0ELNS_8EpilogueE(\d)E", name)
+        if m:
+            lds.setdefault((m.group(1), 16 * int(m.group(2))), {})[int(m.group(3))] = k[".group_segment_fixed_size"]
+    picked = {tile: by for tile, by in lds.items() if 3 in by}
+    assert len(picked) == 7                                                    # every tile that a layer's rows can take
+    for (tile, rows), by in picked.items():
+        assert by[3] >= by[0] + 4 * rows, tile
+
+
 def test_few_row_gemm_loads_residuals_only_where_they_are_added():
     """Whether there are residuals is an argument of the kernel's template: packed rows, A6 rows and fragments come both ways,
     rows quantized in the launch only with them, normalised ones and gate/up only without."""
