@@ -99,6 +99,10 @@ __device__ __forceinline__ void w4a4_tile(
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Token scale and position of row tid of the tile: a layer's are asked for beside the first stage, packed rows' in front (33 x 4096 x 11008: 31.6 us, 33.7 beside).
+    // A layer's in front, where a stage's loads are spread, over scales that the caches hold: QKV 165 x 12288 x 4096 20.4 us, 20.0 beside, gate/up 165 x 22016 x 4096 23.7,
+    // 23.45, with start values 1500 x 4096 x 11008 65.8, 65.5; plain rows without them 300 x 3584 x 18944 54.4, 54.9, 400 x 4096 x 11008 32.6, 33.0, 122 x 4096 x 4096
+    // 7.12, 7.25.  But in a layer the quantizer has just written the scales: there O and down of 288 rows take 20.4 us either way, and with all four
+    // projections so a stack of 32 layers 0.5 % longer.
     constexpr bool AT_ONCE = !SP && !PACKED;             // a stage's loads go out all at once
     // PICKS: row m of activations and residual is row row_src[m] of the tensors handed in.  The indices are asked for ahead of the first
     // weights and looked up behind them.  (An instantiation of its own: with the table of rows in all
