@@ -205,11 +205,12 @@ __device__ __forceinline__ void group_reduce(float &mx, double &sum, double *sm)
 }
 // A launch's arguments that are not in registers when a wave starts (structures and what is behind them) come from memory, the first touch of
 // each 64 bytes from far away.  Left alone the compiler asks for them where they are used, in the middle of a row's chain: they are wanted
-// here, where the row's loads are on their way.
+// here, where the row's loads are on their way.  (Read, not replaced: of a pointer that comes out of assembly the compiler does not know that its
+// memory is global, and stores through it are flat ones, which take the LDS's path too: 3 x 18944 3.31 us, 3.04 so, 32 x 13824 3.06, 2.78, 640 x 11008 7.85, 7.33.)
 template <typename ARG>
-__device__ __forceinline__ void argument_now(ARG &a) { asm volatile("" : "+s"(a)); }
+__device__ __forceinline__ void argument_now(const ARG &a) { asm volatile("" ::"s"(a)); }
 template <int GROUP, typename OUT, typename... ARGS>
-__device__ __forceinline__ void row_arguments_now(OUT &q, ARGS &...args)
+__device__ __forceinline__ void row_arguments_now(const OUT &q, const ARGS &...args)
 {
     if constexpr (GROUP != 64) {                         // (long launches take what registers there are)
         argument_now(q.q);

@@ -509,7 +509,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void small_score_topk_kernel(const f
     const float *inter = TAKES_MEANS ? means[0] : src.cm_inter + src.ocm, *intra = TAKES_MEANS ? means[1] : src.cm_intra + src.ocm;
     float m[4] = {src.sumsq[src.osq + at], 0.0f, 0.0f, src.ressq[src.osq + at]};
     // (asked for here, while the metrics are on their way, not between the selects: their first touch comes from far away)
-    asm volatile("" : "+s"(score), "+s"(keep_idx), "+s"(normed));
+    asm volatile("" ::"s"(score), "s"(keep_idx), "s"(normed));
     if constexpr (TAKES_MEANS) {
         const float invH = 1.0f / (float)cues.H;
         for (int i = tid >> 2; i < Nv; i += SCORE_THREADS / 4) {         // (the lanes of a quad stay together)

@@ -49,6 +49,22 @@ def test_the_rule_sees_a_hand_over():
     assert handed_over("kernel.hip", "atomicAdd(&h[i], 1);") and not handed_over("select.hip", "atomicAdd(&h[i], 1);")
 
 
+def replaced_pointers(text):
+    """Operands in scalar registers that an asm statement reads and replaces and that the source does not declare as whole numbers."""
+    def number(op):
+        return re.search(rf"\b(?:int|unsigned|uint64_t)\b[^;{{}}*]*?\b{op}\b", text) and not re.search(rf"\*(?:const |__restrict__ )?{op}\b", text)
+    return [op for stmt in re.findall(r"\basm\b[^;]*?\((.*?)\)\s*;", text, re.S) for op in re.findall(r'"\+s"\s*\((\w+)', stmt) if not number(op)]
+
+
+def test_assembly_replaces_no_pointers():
+    """A pointer that comes out of an asm statement is one of unknown memory to the compiler, and what goes through it are flat accesses, which count as
+    LDS operations too: addresses pass as numbers, and arguments that are wanted early are read only."""
+    for name, text in sources():
+        assert not replaced_pointers(text), (name, replaced_pointers(text))
+    assert replaced_pointers('void now(ARG &a) { asm volatile("" : "+s"(a)); }') == ["a"]
+    assert replaced_pointers('int n, float *__restrict__ score) { asm volatile("" : "+s"(score), "+s"(n)); }') == ["score"]
+
+
 def test_assembly_leaves_m0_to_the_compiler():
     """The asynchronous copies get their LDS base as an m0 operand; no asm statement writes m0 behind the compiler's
     back (which merges and moves its own writes of it)."""
