@@ -628,7 +628,9 @@ int quota_internal_rmsnorm_quantize_a6(const void *x_f16, int M, int d, const fl
     if (M == 0) return QUOTA_OK;
     if (copies) {                            // (quota_score_quantizes_beside: rows of at most 8192 columns, less than quota_a6_starts of them)
         if (quota_a6_starts(M) || d > 8192) return QUOTA_ERR_SHAPE;
-        ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d, st);
+        // (with the kept rows' codes and scales of K and V and their positions, read and written, and their numbers)
+        const double kv = copies->dkv * (1 + 1.0 / 16);
+        ProfScope prof(QUOTA_K_RMSNORM_QUANTIZE_ACT, 0, 2.5 * M * d + 4.0 * M + 4.0 * d + copies->rows * (2 * kv + 12), st);
         auto kernel = d <= 2048   ? rmsnorm_quantize_act_kernel<false, 256, 2, RowOutA6, quota_kept_copies>
                       : d <= 4096 ? rmsnorm_quantize_act_kernel<false, 512, 1, RowOutA6, quota_kept_copies>
                                   : rmsnorm_quantize_act_kernel<false, 512, 2, RowOutA6, quota_kept_copies>;

@@ -717,11 +717,11 @@ int quota_internal_score_topk(const float *sumsq, const float *ressq, long strid
         return QUOTA_ERR_INVALID_ARG;
     if (Nv > MAXV) return QUOTA_ERR_SHAPE;
     if (Nv == 0) return QUOTA_OK;
-    ProfScope prof(QUOTA_K_SCORE_TOKENS, 0,
-                   20.0 * B * Nv + 4.0 * B * (K < Nv ? K : Nv), st);
-    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
     if (masses && !quota_score_takes_means(Nv, masses->H)) return QUOTA_ERR_SHAPE;
     if (beside && !quota_score_quantizes_beside(Nv, beside->M, beside->d)) return QUOTA_ERR_SHAPE;
+    ProfScope prof(QUOTA_K_SCORE_TOKENS, 0,
+                   20.0 * B * Nv + 4.0 * B * (K < Nv ? K : Nv) + (beside ? 2.5 * beside->M * beside->d + 4.0 * beside->M : 0.0), st);
+    MetricSrc src{sumsq, ressq, cm_inter, cm_intra, 0, 0};
     return launch_score_topk(src, stride_sq, B, Nv, *p, score, nullptr, K, keep_idx, st, weights, masses, beside);
 }
 

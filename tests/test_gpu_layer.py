@@ -500,6 +500,32 @@ def test_layer_that_picks_its_rows(qb, tile, H, Hkv, dh, B, N, vb, Nv, K, pinned
         assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
 
 
+@pytest.mark.parametrize("H,Hkv,dh,B,N,Nv,K", [(8, 8, 64, 1, 80, 64, 17), (16, 4, 128, 3, 101, 70, 20)])
+def test_profile_of_a_layer_that_picks_its_rows(qb, H, Hkv, dh, B, N, Nv, K):
+    """The score launch counts the attention rows that are quantized beside it, the second RMSNorm's the kept K/V, positions and numbers that it copies."""
+    from paper_2604_17320_amd.model import KVCache4, PackedLinear, PrefillLayer
+    d, dkv, F, n_keep = H * dh, Hkv * dh, 640, N - Nv + K
+    def linear(n, k):
+        return PackedLinear.from_codes(torch.ones((n, k), device="cuda", dtype=torch.int8), torch.full((n, (k + 127) // 128), 0.001, device="cuda").to(torch.float16))
+    cos, sin = (dev(t) for t in wl.rope_tables(dh, N))
+    ones = torch.ones(d, device="cuda")
+    L = PrefillLayer(H, dh, F, linear(d + 2 * dkv, d), linear(d, d), linear(2 * F, d), linear(d, F), ones, ones, 1e-5, cos, sin, Hkv)
+    x = torch.randn((B * N, d), generator=torch.Generator(device="cuda").manual_seed(N), device="cuda").to(torch.float16)
+    pos = torch.arange(N, dtype=torch.int32, device="cuda").repeat(B)
+    x_out, pos_out = torch.empty((B * n_keep, d), dtype=torch.float16, device="cuda"), torch.empty(B * n_keep, dtype=torch.int32, device="cuda")
+    ws = torch.empty(L.workspace_bytes(B, N), dtype=torch.uint8, device="cuda")
+    st = qb.State(B, N, 0, Nv, x.data_ptr(), pos.data_ptr(), x_out.data_ptr(), pos_out.data_ptr())
+    cache = KVCache4(B, n_keep, Hkv, dh)
+    qb.quota_profile_begin(64)
+    qb.quota_prefill_layer(L.desc, st, K, qb.quota_score_params_default(), cache.desc, None, ws)
+    ran = qb.quota_profile_collect()
+    assert "compact_rows" not in ran and ran["rmsnorm_quantize_act"]["launches"] == 2
+    rows = lambda M: 2.5 * M * d + 4 * M                  # fp16 in, half a byte and a token scale out
+    kept = 2 * (dkv // 2) + 2 * 2 * (dkv // 64)           # codes and fp16 scales of K and V of a row
+    assert ran["score_tokens"]["bytes"] == 20 * B * Nv + 4 * B * K + rows(B * N)
+    assert ran["rmsnorm_quantize_act"]["bytes"] == rows(B * N) + rows(B * n_keep) + 2 * 4 * d + B * n_keep * (2 * kept + 2 * 4 + 4)
+
+
 def test_layer_with_weight_scales_at_an_odd_halfword(qb):
     """Weight scales that start between two dwords: a prefill layer and its decode-sized remainder give the bits of the
     aligned layer (the fused QKV epilogue and the tiles step aside)."""
