@@ -6,15 +6,13 @@
 #include "prefetch.h"
 #include "headmeans.h"
 
-// The rows that a layer keeps, [B][n_keep] of [B][N]: text before the visual tokens, the kept ones of those, text behind.  keep_idx: null: the first k_keep.
+// The rows that a layer keeps, [B][n_keep] of [B][N]: text before the visual tokens, the kept ones of those, text behind.
 struct quota_kept_rows {
     const int32_t *keep_idx;
     int N, vis_begin, Nv, k_keep, n_keep;
-    // The index that row j of sequence b needs, and with it the row of the sequence: never one outside it
-    __device__ __forceinline__ int index(int b, int j) const
-    {
-        return keep_idx ? keep_idx[(size_t)b * k_keep + min(max(j - vis_begin, 0), k_keep - 1)] : j - vis_begin;
-    }
+    // The index that row j of sequence b needs (k_keep > 0, keep_idx given; row j of the text reads one that it does not need), and with it the row of the
+    // sequence: never one outside it
+    __device__ __forceinline__ int index(int b, int j) const { return keep_idx[(size_t)b * k_keep + min(max(j - vis_begin, 0), k_keep - 1)]; }
     __device__ __forceinline__ int row(int j, int idx) const
     {
         const int src = j < vis_begin ? j : j < vis_begin + k_keep ? vis_begin + idx : j - k_keep + Nv;

@@ -152,8 +152,7 @@ __global__ __launch_bounds__(256) void kv_quant_append_kernel(
 // needs a single memory round trip.
 template <int NCH, typename OUT>
 __global__ __launch_bounds__(256) void compact_rows_kernel(
-    int N, int vis_begin, int Nv, int k_keep, int n_keep, const int32_t *__restrict__ keep_idx,
-    int d, int dkv, const f16 *__restrict__ x, const f16 *__restrict__ o, const int32_t *__restrict__ pos,
+    quota_kept_rows kept, int d, int dkv, const f16 *__restrict__ x, const f16 *__restrict__ o, const int32_t *__restrict__ pos,
     const uint32_t *__restrict__ skc, const f16 *__restrict__ sks, const uint32_t *__restrict__ svc,
     const f16 *__restrict__ svs, f16 *__restrict__ x_out, f16 *__restrict__ o_out,
     OUT oq_out, float *__restrict__ os_out,
@@ -163,17 +162,14 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(
 {
     int j = blockIdx.x, b = blockIdx.y;
     if (OUT::STARTS) {
-        const int wg = row_wg<OUT>(b * n_keep + j, n_keep * gridDim.y);
-        b = wg / n_keep;
-        j = wg - b * n_keep;
+        const int wg = row_wg<OUT>(b * kept.n_keep + j, kept.n_keep * gridDim.y);
+        b = wg / kept.n_keep;
+        j = wg - b * kept.n_keep;
     }
     const int tid = threadIdx.x;
-    int src;
-    if (j < vis_begin) src = j;
-    else if (j < vis_begin + k_keep) src = vis_begin + (keep_idx ? keep_idx[(size_t)b * k_keep + (j - vis_begin)] : j - vis_begin);
-    else src = j - k_keep + Nv;
-    src = min(max(src, 0), N - 1);
-    const size_t srow = (size_t)b * N + src, drow = (size_t)b * n_keep + j;
+    const int vis = j - kept.vis_begin;                   // (without indices the first k_keep visual tokens, of which there may be none)
+    const int src = kept.row(j, kept.keep_idx && vis >= 0 && vis < kept.k_keep ? kept.keep_idx[(size_t)b * kept.k_keep + vis] : vis);
+    const size_t srow = (size_t)b * kept.N + src, drow = (size_t)b * kept.n_keep + j;
     const size_t crow = (size_t)b * capacity + len + j;
     const int n16 = d >> 3;       // 16-byte pieces in an fp16 row
     const int nkv = dkv >> 3;     // dwords of codes per K or V row (<= n16)
@@ -252,7 +248,7 @@ int quota_internal_compact(const quota_compact_args *a, hipStream_t st)
         auto kernel = a->d <= 4096 ? compact_rows_kernel<2, OUT> : a->d <= 8192 ? compact_rows_kernel<4, OUT>
                                                                                 : compact_rows_kernel<8, OUT>;
         kernel<<<dim3(a->n_keep, a->B), dim3(256), 0, st>>>(
-            a->N, a->vis_begin, a->Nv, a->k_keep, a->n_keep, a->keep_idx, a->d, a->dkv, (const f16 *)a->x,
+            quota_kept_rows{a->keep_idx, a->N, a->vis_begin, a->Nv, a->k_keep, a->n_keep}, a->d, a->dkv, (const f16 *)a->x,
             (const f16 *)a->o, a->pos, (const uint32_t *)a->skc, (const f16 *)a->sks, (const uint32_t *)a->svc,
             (const f16 *)a->svs, (f16 *)a->x_out, (f16 *)a->o_out, out, a->os_out, a->pos_out,
             a->rows_out, c->capacity, c->len, (uint32_t *)c->k_codes, (f16 *)c->k_scales, (uint32_t *)c->v_codes,

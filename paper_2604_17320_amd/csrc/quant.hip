@@ -272,7 +272,8 @@ __global__ __launch_bounds__(row_threads(GROUP)) void quantize_act_kernel(
     }
 }
 
-// Workgroups behind the quantizer's, one per kept row (see quota_kept_copies)
+// Workgroups behind the quantizer's, one per kept row (see quota_kept_copies; the gather of kv.hip has such copies among the loads and stores of the row
+// that it quantizes)
 struct NoCopies {};
 template <int THREADS>
 __device__ __forceinline__ void copy_kept_row(const quota_kept_copies &c, int m)
