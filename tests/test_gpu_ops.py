@@ -545,11 +545,12 @@ def test_cues_of_a_sequence_do_not_depend_on_the_others(qb, N, H, dh, vb, Nv, B)
 
 # (workgroups of two waves up to 160 of four, one per head and 128 queries or visual keys: the sequence alone; of four in the batch)
 @pytest.mark.parametrize("N,H,Hkv,dh,vb,Nv,B", [(64, 8, 8, 64, 0, 64, 21), (65, 8, 2, 128, 1, 63, 21), (127, 8, 8, 64, 14, 65, 21), (129, 8, 8, 128, 0, 129, 11),
-                                                (193, 6, 6, 128, 65, 128, 14), (640, 28, 4, 128, 30, 576, 2)])
+                                                (193, 6, 6, 128, 65, 128, 27), (640, 28, 4, 128, 30, 576, 2)])
 def test_attention_of_two_and_of_four_waves(qb, N, H, Hkv, dh, vb, Nv, B):
     """Outputs and masses of a sequence have the same bits from workgroups of either width, and the outputs those of the reference."""
-    d, dkv, blocks = H * dh, Hkv * dh, H * ((N + 127) // 128)
-    assert blocks <= 160 < blocks * B
+    d, dkv = H * dh, Hkv * dh
+    for blocks in (H * ((N + 127) // 128), H * ((Nv + 127) // 128)):           # of the forward pass, of the cue pass
+        assert blocks <= 160 < blocks * B
     q = _act(B * N, d, 74, 1.0)
     khat, vhat = (oracle.kv_quant(_act(B * N, dkv, seed, 1.0))[2] for seed in (75, 76))
     qd, kd, vd = dev(q), dev(khat), dev(vhat)
