@@ -118,8 +118,8 @@ __device__ __forceinline__ float row16_sum(float v)
 }
 
 // The fp32 number nearest to 1 / sqrt(x).  A division by a square root in doubles is a chain of some forty instructions in front of
-// everything a row's normalisation does; the estimate y is good to 2^-23, so that e = 1 - x y^2 is as small, and three terms of
-// y (1 - e)^(-1/2) = y (1 + e / 2 + 3 e^2 / 8 + ...) leave an error of 2^-70 and the last roundings'.  Over 4 million x from 1e-12 to 4e9 and estimates
+// everything a row's normalisation does; the estimate y is good to 2^-23, so that e = 1 - x y^2 is below 2^-22, and three terms of
+// y (1 - e)^(-1/2) = y (1 + e / 2 + 3 e^2 / 8 + 5 e^3 / 16 + ...) leave an error of 2^-67.7 and the last roundings'.  Over 4 million x from 1e-12 to 4e9 and estimates
 // off by up to 2^-22 the result is 1.24 x 2^-53 off at most, the division by the root 1.49, and both round to the nearest fp32 number every time.
 __device__ __forceinline__ float inv_sqrt(double x)
 {

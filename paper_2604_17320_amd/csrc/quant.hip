@@ -186,10 +186,10 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
 // issued before the first use (unconditional loads at clamped indices instead of guarded ones, so
 // that nothing separates them): one memory round trip per kernel.  GROUP = 64 (rows of up to 6144
 // columns): one WAVE per row, four rows per workgroup -- a lane issues all its 16-byte loads back
-// to back, the reductions are wave shuffles and there is no workgroup barrier.  GROUP = 256 (up to
+// to back, the reductions are wave shuffles and there is no workgroup barrier.  GROUP = 256 or 512 (up to
 // 32768 columns): the whole workgroup owns the row and reduces through LDS.
 // Below this many rows the launch cannot fill the chip with one wave per row, and a row is
-// finished sooner by a whole workgroup (512 threads for a layer's few wide rows, see with_row_shape).
+// finished sooner by a whole workgroup (512 threads for a layer's few wide rows: with_row_shape).
 #define ROW_WAVE_MIN_ROWS 2048
 
 constexpr int row_threads(int group) { return group == 64 ? 256 : group; }
@@ -222,7 +222,7 @@ __device__ __forceinline__ void row_arguments_now(const OUT &q, const ARGS &...a
     __shared__ __align__(16) double sm[GROUP == 64 ? 2 : 6 * GROUP / 64];                                                  \
     const int lane = threadIdx.x % GROUP;                                                      \
     const int row = row_wg<OUT>(blockIdx.x, (M + row_threads(GROUP) / GROUP - 1) / (row_threads(GROUP) / GROUP)) * (row_threads(GROUP) / GROUP) + (GROUP == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GROUP) : 0); \
-    if (row >= M) return;     /* GROUP = 64: the whole wave leaves; GROUP = 256: never taken */ \
+    if (row >= M) return;     /* GROUP = 64: the whole wave leaves; else never taken */ \
     (void)sm
 
 template <bool WANT_METRICS, int GROUP, int NCH, typename OUT>
@@ -478,7 +478,9 @@ static void with_row_shape(int M, int d, LAUNCH launch)
     }
     // A layer's few rows, wider than 2048 columns, by 512 threads each: one wave a SIMD waits between its instructions.  (16 x 4096 and 16 x 11008 of a decode
     // step of 16 sequences over 32 layers, 1904 -> 1885 us; 32 layers of 640 to 122 rows 4158 -> 4137, one of 165 rows 109.7 -> 109.0; 1024 threads 1907, 4161 and 109.5;
-    // 16 layers of 512 channels take 0.5 % longer with 512.)
+    // 16 layers of 512 channels take 0.5 % longer with 512.)  The plain quantizers gain most: with 256 threads and 512, us, 16 x 4096 2.30, 2.05, 16 x 11008 3.64, 2.63, 32 x
+    // 13824 4.00, 2.77, 165 x 11008 4.51, 3.60, 500 x 11008 6.55, 5.65, with the SiLU product 165 x 11008 5.62, 5.03; with RMSNorm 16 x 4096 2.56, 2.41, 165 x 4096 3.00, 2.81,
+    // 300 and 500 x 4096 as long; all of them so a 16-sequence step 1793, 1750 and the batch-1 stack 4001, 3972.
     if constexpr (!OUT::MANY) {
         const std::integral_constant<int, 512> wide;
         if (d <= 2048) go(workgroup, std::integral_constant<int, 2>());

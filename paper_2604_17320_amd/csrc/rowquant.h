@@ -1,5 +1,5 @@
 // Row-quantizer pieces shared by the row kernels.  A row is owned by a GROUP of threads (one wave,
-// or a whole 256-thread workgroup) and cached in registers as 16-byte chunks: chunk c belongs to
+// or a whole workgroup of 256 or 512 threads) and cached in registers as 16-byte chunks: chunk c belongs to
 // thread c % GROUP of the group, as its (c / GROUP)-th chunk.
 #pragma once
 #include <type_traits>
@@ -9,7 +9,7 @@
 #include "gemm_common.h"
 
 #define ROW_THREADS 256
-#define ROW_MAXCHUNK 16  // workgroup-per-row kernels: 16 chunks * 8 halves * 256 threads = 32768 columns
+#define ROW_MAXCHUNK 16  // workgroup-per-row kernels: 16 chunks * 8 halves * 256 threads = 32768 columns, as 8 chunks of 512 threads
 #define ROW_MAXCOLS 32768
 
 // Where a quantized row goes: packed int4 (the public format, two codes per byte), the GEMM's A6 format -- e2m3 numbers,

@@ -703,7 +703,10 @@ int quota_internal_score(const float *sumsq, const float *ressq, long stride_sq,
 // 64 tokens 0.7, 256 0.8, 576 0.2; 7B shape, 32 heads, 101 tokens 3.2, 160 2.9, 256 1.7, 300 0.0, 320 -0.7, 576 -5.6; 13B shape, 40 heads, 250 tokens 1.3.
 bool quota_score_takes_means(int Nv, int H) { return Nv <= SCORE_THREADS && (long)Nv * H <= 10240; }
 
-// Rows to quantize beside it: as many as fit the chip at once, four to a workgroup and two workgroups a CU, are done before the tokens are scored.
+// Rows to quantize beside it, four to a workgroup: up to 1024, one workgroup of 1024 threads a CU, are done before the tokens are scored.  A layer that so picks
+// its rows against one that gathers them, replayed, us less (1024 rows in, kept share of the image 0.04 / 0.1 / 0.3 / 0.45): 4096 columns -0.1 / 0.5 / 1.5 / 2.8, 5120
+// at 0.05 and 0.4 1.6 and 4.3, 8192 at 0.04 and 0.4 0.3 and 1.4, 512 1.7 and 2.1, 1024 1.5 and 2.9, 2048 1.1 and 2.4; 640 rows at 0.02 4096 columns 3.9, at 0.05 5120 2.7,
+// 8192 3.3; 165 rows 2.8; 2 x 512 rows at 0.05 and 0.4 0.9 and 2.9, 8 x 128 at 0.2 -0.2.
 bool quota_score_quantizes_beside(int Nv, int M, int d) { return Nv > 0 && Nv <= SCORE_THREADS && M > 0 && M <= 1024 && d % 128 == 0 && d <= 8192; }
 
 // score + top-k in one launch (the layer's path)
