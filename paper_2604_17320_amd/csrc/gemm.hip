@@ -748,7 +748,8 @@ int g_gemm_variant = -1;      // -1: chosen per launch; else pinned by quota_set
 // Tile choice by cost models fitted to measured kernel times on this GPU (us, over weights that no cache holds), one for a layer's rows
 // (112 shapes of 40 to 11776 rows, 512 to 37888 columns and 512 to 18944 channels; the 32 x 64 tile's line, which has changed since, by 270
 // of 33 to 511 rows and of narrow layers, where the choice costs 0.6 % over the best tile of each on average, 2.3 % with the line before; the 96 x 128 tile's by
-// launches of 160 to 444 rows, and right for those of 65 to 493) and one for
+// launches of 160 to 444 rows, and right for those of 65 to 493; all from before first weights went out ahead of everything else, which moved no line: over 266
+// other shapes of 33 to 2000 rows the choice costs 1.8 % over the best of the tiles that can be pinned, 1.6 before) and one for
 // packed rows, whose stages are shorter and tiles others (412 shapes of 33 to 11776 rows; 0.2 % on average, 10 % at most, where two tiles tie over
 // cold weights the one that is ahead over warm ones; by a layer's, without the
 // 64 x 256 tile, 3.7 %: 5808 x 4096 x 11008 301 us, 236 so).  With x workgroups per CU a group of the K loop, in whole stages of ch, takes u[ceil(x) - 1] for x <= n and
